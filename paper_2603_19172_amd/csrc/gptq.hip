@@ -16,195 +16,443 @@
 // for the trailing update (it would round differently), but the same work as
 // a chain of fp32 FMAs in registers.
 //
-// Rows are independent, columns are not.  Per group of 64 columns two kinds of launch:
-//   group kernel   a lane owns a row: the group's 64 values in registers, the
-//                  64 x 64 diagonal block of U staged in LDS and read as
-//                  broadcasts (every lane needs the same value); quantises the 64 columns
-//                  in order, applies the corrections inside the group, writes
-//                  codes, scale, zero and the 64 errors e of the row;
-//   trail kernel   v[:, j] for later columns j: 64 chained FMAs per element and
-//                  group, a workgroup on a 64-row x 128-column tile with the
-//                  errors and the 64 x 128 block of U in LDS, 8 x 4 elements per
-//                  thread.  Groups go in pairs: the first group's corrections
-//                  reach the second group's columns at once, and both groups'
-//                  128 corrections then go over the remaining columns in one pass.
+// The fp32 matrix instructions of this chip are such a chain: v_mfma_f32_{16x16x4,32x32x2}_f32 give, bit for bit,
+// what one fma after the other over ascending k gives, subnormals included (compared on 14 million random results with
+// equal, cancelling, tiny and subnormal operands; a test sweeps rows against the plain chain as well).  So the
+// corrections go through the matrix cores at twice the rate of the unpacked vector fma and keep the reference's bits.
+//
+// Rows are independent, columns are not.  Columns go in panels of 256 (four groups of 64), two launches each:
+//   group kernel   a wavefront owns 16 rows through the whole panel: a group's values lose the corrections of the
+//                  panel's earlier groups (16x16x4 products, errors from LDS), are turned round so that four lanes
+//                  share a row (a lane every fourth column), and are quantised column by column; codes, scale, zero
+//                  and the errors e of the row are written;
+//   trail kernel   v[:, j] for the columns behind the panel: 256 chained fmas per element.
 // The working copy v of the matrix (fp32) lives in the caller's workspace.
 #include "common.hpp"
 
 namespace dymoe {
 
-constexpr int kGqGroup = 64;        // columns per group = columns per step
-constexpr int kGqRows = 64;         // rows per workgroup in both kernels
-constexpr int kGqTrailCols = 128;   // columns per workgroup of the trail kernel
-constexpr int kGqTrailThreads = 256;
+constexpr int kGqGroup = 64;        // columns per group
+constexpr int kGqRows = 64;         // rows per row block
+constexpr int kGqPanel = 4;         // groups per panel
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 static inline size_t gq_round256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline long gq_rows_padded(long N) { return (N + kGqRows - 1) / kGqRows * kGqRows; }
 
-__global__ __launch_bounds__(256) void gptq_widen_kernel(const uint16_t* __restrict__ w, long n_elems,
-                                                         float* __restrict__ v)
+// Where the (negated) errors of a panel of four groups are kept between the two kernels.  The panel's own columns of
+// v are dead once its values are in registers, and a row block's 64 x 256 of them hold its 256 x 64 errors exactly:
+// element (column c of the panel, row r of the block) sits in row c / 4 of the block at offset (c % 4) * 64 + r.  The
+// ragged last row block has too few rows for that and uses a linear buffer of the same arrangement (row stride 256).
+struct GqErr {
+    float* whole;     // v + first column of the panel
+    long ld;          // row stride of v
+    float* tail;      // linear buffer of the ragged block
+    long full_blocks;
+};
+__device__ __forceinline__ float* gq_err_block(const GqErr& g, long block, long& ld)
 {
-    const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 8;
-    if (i >= n_elems) return;                       // n_elems is a multiple of 64
-    const uint4 raw = load_global<uint4>(w + i);
-    float4 a, b;
-    a.x = bf16_lo(raw.x); a.y = bf16_hi(raw.x); a.z = bf16_lo(raw.y); a.w = bf16_hi(raw.y);
-    b.x = bf16_lo(raw.z); b.y = bf16_hi(raw.z); b.z = bf16_lo(raw.w); b.w = bf16_hi(raw.w);
-    *reinterpret_cast<float4*>(v + i) = a;
-    *reinterpret_cast<float4*>(v + i + 4) = b;
+    const bool full = block < g.full_blocks;
+    ld = full ? g.ld : 256;
+    return full ? g.whole + block * kGqRows * g.ld : g.tail;
 }
 
-// One group of 64 columns for the rows [row_begin, row_end), a lane per row.
-//   BITS = 2, 4, 8   the quantizer: codes, scale and zero of the group are written, e is the scaled rounding error;
-//   BITS = 0         nothing is quantised and e = x[c] / D[c,c]: the row is solved against the upper triangular
-//                    diagonal block D (forward substitution; the factorisation below is built from this).
-// x: the rows' current values of the group's columns, x[row * ldx + c]; d: the 64 x 64 diagonal block, d[c * ldd + j].
-// e of (column c, row) goes to own_p[c * own_cs + row * own_rs] (OWN; the row range must then be whole blocks of 64)
-// and to pad_p[c * pad_cs + slot * pad_rs] (PAD) for every lane of the grid, rows rounded up to 64: a buffer of that
-// many rows, from which the trail kernel loads whole 64-row tiles.  Which of the two are written is fixed at compile
-// time: with run-time tests around the stores the 64 unrolled columns fall apart into basic blocks, and the
-// values the compiler keeps across them spill.
-template <int BITS, bool OWN, bool PAD>
-__global__ __launch_bounds__(kGqRows) void gptq_group_kernel(
-    const float* __restrict__ x_in, long ldx, const float* __restrict__ d, long ldd, long row_begin, long row_end,
-    float* __restrict__ own_p, long own_cs, long own_rs, float* __restrict__ pad_p, long pad_cs, long pad_rs,
-    uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero,
-    long code_row_bytes, long groups_per_row)
+// x of column C, held by lane C % 4 of a quad in register C / 4, to the quad's four lanes
+template <int Q>
+__device__ __forceinline__ float quad_bcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), Q * 0x55, 0xF, 0xF, true));
+}
+
+// The two values a step of the column chain needs from the diagonal block of U besides its row: 1 / U[c,c] in 64 bits
+// and U[c,c].  e = rest / U[c,c] is taken as (float)((double)rest * (1 / U)): the product is within 2^-52 of the
+// quotient, and a quotient of two 24-bit numbers that is not itself halfway between two floats is at least 2^-49 away
+// from it, so the rounding to float is the quotient's own, in 3 dependent instructions instead of the dozen of an IEEE
+// division.  Halfway cases only exist among subnormal quotients: those are recognised and the group is done again with
+// the division itself.
+template <int BITS, typename Emit>
+__device__ __forceinline__ bool gq_group_chain(float (&x)[16], int q, float m, float s, float inv, const float* s_d,
+                                               const double* s_inv, uint32_t* words, Emit emit)
 {
 #pragma clang fp contract(off)
-    const long slot = row_begin + (long)blockIdx.x * kGqRows + threadIdx.x;
-    const bool mine = slot < row_end;
-    const long row = min(slot, row_end - 1);        // lanes past the last row redo it and keep the result to themselves
-    float x[kGqGroup];
+    constexpr int qmax = (1 << BITS) - 1;
+    constexpr int per_word = 32 / BITS;
+    bool subnormal = false;
+    float keep = 0.0f;
+    // the rows of the diagonal block, two steps' worth at a time, one batch ahead of their use: the scheduling barriers
+    // keep the compiler from fetching the whole block up front (and spilling it) or each row only when it is needed
+    float4 d[2][2][4];
+    double rcp[2][2];
+    auto fetch = [&](int b) {
 #pragma unroll
-    for (int c = 0; c < kGqGroup / 4; c++) {
-        const float4 q = *reinterpret_cast<const float4*>(x_in + row * ldx + 4 * c);
-        x[4 * c + 0] = q.x; x[4 * c + 1] = q.y; x[4 * c + 2] = q.z; x[4 * c + 3] = q.w;
-    }
-    constexpr int qmax = BITS ? (1 << BITS) - 1 : 1;
-    constexpr int per_word = BITS ? 32 / BITS : 32;
-    constexpr int n_words = BITS ? kGqGroup / per_word : 1;   // 16 (int8), 8 (int4), 4 (int2)
-    float m = 0.0f, s = 0.0f, inv = 0.0f;
-    _Float16 zh = (_Float16)0.0f, sh = (_Float16)0.0f;
-    if constexpr (BITS != 0) {
-        float lo = x[0], hi = x[0];
+        for (int c = 0; c < 2; c++) {
+            rcp[b & 1][c] = s_inv[2 * b + c];
 #pragma unroll
-        for (int i = 1; i < kGqGroup; i++) {
-            lo = fminf(lo, x[i]);
-            hi = fmaxf(hi, x[i]);
+            for (int j = 0; j < 4; j++)
+                if (4 * j + 3 >= b / 2) d[b & 1][c][j] = *reinterpret_cast<const float4*>(s_d + (2 * b + c) * kGqGroup + q * 16 + 4 * j);
         }
-        zh = (_Float16)lo;                          // round to nearest even
-        const float range = hi - lo;
-        const float step = range / (float)qmax;     // correctly rounded division
-        sh = (_Float16)step;
-        m = (float)zh;
-        s = (float)sh;
-        inv = (s > 0.0f) ? (1.0f / s) : 0.0f;
-    }
-    // The diagonal block goes through LDS: every lane needs every value, one row per column step, and fetched row
-    // by row from memory (the scalar cache's way) each step would wait out a full memory latency: 64 in a chain.
-    __shared__ __attribute__((aligned(16))) float s_d[kGqGroup][kGqGroup + 4];   // + 4: the row-per-lane staging stores spread over the banks
+    };
+    fetch(0);
 #pragma unroll
-    for (int c = 0; c < kGqGroup / 4; c++)
-        *reinterpret_cast<float4*>(&s_d[threadIdx.x][4 * c]) =
-            *reinterpret_cast<const float4*>(d + (long)threadIdx.x * ldd + 4 * c);
-    __syncthreads();
-    uint32_t words[n_words];
+    for (int b = 0; b < kGqGroup / 2; b++) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (b + 1 < kGqGroup / 2) fetch(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int k = b / 2;
 #pragma unroll
-    for (int i = 0; i < n_words; i++) words[i] = 0u;
-#pragma unroll
-    for (int i = 0; i < kGqGroup; i++) {
-        float rest = x[i];
-        if constexpr (BITS != 0) {
-            const float t = x[i] - m;
+        for (int h = 0; h < 2; h++) {
+            const int i = 2 * b + h, c = i & 3;
+            const float xi = c == 0 ? quad_bcast<0>(x[k]) : c == 1 ? quad_bcast<1>(x[k]) : c == 2 ? quad_bcast<2>(x[k]) : quad_bcast<3>(x[k]);
+            const float t = xi - m;
             float r = __builtin_rintf(t * inv);
             r = fminf(fmaxf(r, 0.0f), (float)qmax);
+            if (i % per_word == 0) words[i / per_word] = 0u;
             words[i / per_word] |= (uint32_t)(int)r << (BITS * (i % per_word));
             float dq = r * s;
             dq = dq + m;
-            rest = x[i] - dq;
+            const float rest = xi - dq;
+            const float e = (float)((double)rest * rcp[b & 1][h]);
+            subnormal |= __builtin_amdgcn_classf(e, 0x90);
+            const float ne = -e;
+            keep = (q == c) ? ne : keep;
+            // (columns of register k that are already done change too; nothing reads them any more)
+#pragma unroll
+            for (int j = (c == 3) ? k + 1 : k; j < 16; j++) {
+                const float4& dd = d[b & 1][h][j >> 2];
+                x[j] = __builtin_fmaf(ne, (j & 3) == 0 ? dd.x : (j & 3) == 1 ? dd.y : (j & 3) == 2 ? dd.z : dd.w, x[j]);
+            }
         }
-        const float e = rest / s_d[i][i];
-        if constexpr (OWN) own_p[(long)i * own_cs + slot * own_rs] = e;
-        if constexpr (PAD) pad_p[(long)i * pad_cs + slot * pad_rs] = e;
-        const float ne = -e;
-#pragma unroll
-        for (int j = i + 1; j < kGqGroup; j++) x[j] = __builtin_fmaf(ne, s_d[i][j], x[j]);
+        if (b & 1) emit(k, keep);
     }
-    if constexpr (BITS != 0) {
-        if (mine) {
-            uint8_t* dst = codes + row * code_row_bytes;
+    return subnormal;
+}
+
+// The same group with the division itself, for rows with subnormal quotients: rare, so rolled up and in LDS (sx: the
+// wavefront's 16 x 64 values, overwritten).
+template <int BITS, typename Emit>
+__device__ __forceinline__ void gq_group_chain_exact(float* sx, int r, int q, float m, float s, float inv, const float* s_d,
+                                                  uint32_t* words, Emit emit)
+{
+#pragma clang fp contract(off)
+    constexpr int qmax = (1 << BITS) - 1;
+    constexpr int per_word = 32 / BITS;
+    float* const row = sx + r * (kGqGroup + 4);
+    float keep = 0.0f;
+#pragma unroll 1
+    for (int i = 0; i < kGqGroup; i++) {
+        const float xi = row[i];
+        float t = (xi - m) * inv;
+        t = fminf(fmaxf(__builtin_rintf(t), 0.0f), (float)qmax);
+        float dq = t * s;
+        dq = dq + m;
+        const float ne = -((xi - dq) / s_d[i * kGqGroup + (i & 3) * 16 + (i >> 2)]);
+        keep = (q == (i & 3)) ? ne : keep;
+        if ((i & 3) == 3) emit(i >> 2, keep);
+        for (int j = (i & ~3) + q; j < kGqGroup; j += 4)
+            if (j > i) row[j] = __builtin_fmaf(ne, s_d[i * kGqGroup + q * 16 + (j >> 2)], row[j]);
+        if (q == (i & 3)) row[i] = t;                           // the code, in the place of the value
+    }
 #pragma unroll
-            for (int i = 0; i < n_words / 4; i++)
-                store_global(dst + 16 * i, make_uint4(words[4 * i], words[4 * i + 1], words[4 * i + 2], words[4 * i + 3]));
-            store_global(scale + row * groups_per_row, (uint16_t)f16_bits(sh));
-            store_global(zero + row * groups_per_row, (uint16_t)f16_bits(zh));
+    for (int i = 0; i < kGqGroup; i++) {
+        if (i % per_word == 0) words[i / per_word] = 0u;
+        words[i / per_word] |= (uint32_t)(int)row[i] << (BITS * (i % per_word));
+    }
+}
+
+// One panel of up to four groups: rows in blocks of 64 (a workgroup), 16 rows a wavefront.  FIRST: the values come from
+// the bf16 matrix itself (nothing has been corrected yet), so the working copy is never filled by a pass of its own.
+// Bound: the chain of 64 dependent quantise-and-correct steps per group.  Splitting a row over four lanes keeps the fmas
+// of a step (16 at most) under the step's latency and puts 896 wavefronts on the chip's 1024 SIMDs for 14336 rows, where
+// a lane per row had 224 wavefronts with up to 63 fmas to issue in a step.  14336 x 4096, int4: 40 us per panel, i.e.
+// 10 us per group with the corrections inside the panel; a lane per row took 19 us per group and 11 us for those.
+template <int BITS, bool FIRST>
+__global__ __launch_bounds__(256) void gptq_group_kernel(
+    const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K, long base,
+    int n_groups, GqErr err, uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
+{
+#pragma clang fp contract(off)
+    constexpr int qmax = (1 << BITS) - 1;
+    constexpr int n_words = kGqGroup * BITS / 32;               // 16 (int8), 8 (int4), 4 (int2)
+    constexpr int kStride = kGqGroup + 4;
+    __shared__ __attribute__((aligned(16))) float s_d[kGqPanel][kGqGroup * kGqGroup];   // [c][j % 4][j / 4]
+    __shared__ __attribute__((aligned(16))) double s_inv[kGqPanel * kGqGroup];
+    __shared__ __attribute__((aligned(16))) float s_e[4][kGqPanel * kGqGroup * 16];   // per wavefront [column][row], negated
+    __shared__ __attribute__((aligned(16))) float s_x[4][16 * kStride];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long row0 = (long)blockIdx.x * kGqRows + 16 * wave;
+    // matrix-instruction layout: this lane holds rows 4 rg .. 4 rg + 3, columns 4 cl .. 4 cl + 3 of the 16 x 64 values
+    const int rg = lane >> 4, cl = lane & 15;
+    float4 cur[kGqPanel][4];
+#pragma unroll
+    for (int g = 0; g < kGqPanel; g++) {
+        if (g >= n_groups) break;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const long row = min(row0 + 4 * rg + i, N - 1);     // rows past the last one redo it and keep the result to themselves
+            const long at = row * K + base + kGqGroup * g + 4 * cl;
+            if constexpr (FIRST) {
+                const uint2 raw = load_global<uint2>(w + at);
+                cur[g][i] = make_float4(bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y));
+            } else {
+                cur[g][i] = *reinterpret_cast<const float4*>(v + at);
+            }
+        }
+    }
+    for (int at = tid; at < n_groups * kGqGroup; at += 256) {
+        const long c = base + at;
+        s_inv[at] = 1.0 / (double)u[c * K + c];
+    }
+    for (int at = tid; at < n_groups * kGqGroup * 16; at += 256) {
+        const int g = at >> 10, c = (at >> 4) & 63, m = at & 15;
+        const float4 d = *reinterpret_cast<const float4*>(u + (base + kGqGroup * g + c) * K + base + kGqGroup * g + 4 * m);
+        float* dst = &s_d[g][c * kGqGroup + m];
+        dst[0] = d.x; dst[16] = d.y; dst[32] = d.z; dst[48] = d.w;
+    }
+    __syncthreads();            // and every wavefront has its values in registers: v may now be overwritten by errors
+    const int r = lane >> 2, q = lane & 3;                      // the chain's layout: row r, columns 4 m + q
+    const long row = row0 + r;
+    long eld;
+    float* const eb = gq_err_block(err, blockIdx.x, eld) + q * kGqRows + 16 * wave + r;
+    // The rows of U that a group's values are corrected with come straight from memory, 32 columns ahead of their use; the
+    // first batch of the next group is requested before this group's chain and lies in registers behind it.
+    constexpr int kAhead = 8;
+    float4 ub[2][kAhead];
+    const float* bp = u + (base + rg) * K + base + kGqGroup + 4 * cl;
+    auto fetch = [&](int buf, const float* from) {
+#pragma unroll
+        for (int i = 0; i < kAhead; i++) ub[buf][i] = load_global<float4>(from + (long)i * 4 * K);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll 1
+    for (int g = 0; g < n_groups; g++) {
+        if (g > 0) {
+            // the group's values move to the front (a run-time index would put them into private memory)
+#pragma unroll
+            for (int o = 1; o < kGqPanel; o++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) cur[o - 1][i] = cur[o][i];
+            f32x4_t acc[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                acc[0][i] = cur[0][i].x; acc[1][i] = cur[0][i].y; acc[2][i] = cur[0][i].z; acc[3][i] = cur[0][i].w;
+            }
+            const float* ap = &s_e[wave][lane];
+            auto multiply = [&](int buf) {
+#pragma unroll
+                for (int i = 0; i < kAhead; i++) {
+                    const float a = ap[i * 64];
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].x, acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].y, acc[1], 0, 0, 0);
+                    acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].z, acc[2], 0, 0, 0);
+                    acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].w, acc[3], 0, 0, 0);
+                }
+                ap += kAhead * 64;
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            const float* from = bp;
+#pragma unroll 1
+            for (int h = 1; h < g; h++) {                       // a group's 64 columns are two batches
+                fetch(1, from + (long)kAhead * 4 * K);
+                multiply(0);
+                from += (long)2 * kAhead * 4 * K;
+                fetch(0, from);
+                multiply(1);
+            }
+            fetch(1, from + (long)kAhead * 4 * K);
+            multiply(0);
+            multiply(1);
+            bp += kGqGroup;
+#pragma unroll
+            for (int i = 0; i < 4; i++) cur[0][i] = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
+        }
+        if (g + 1 < n_groups) fetch(0, bp);
+        float* const sx = s_x[wave];                            // one wavefront's own: no barrier
+#pragma unroll
+        for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * rg + i) * kStride + 4 * cl]) = cur[0][i];
+        float x[16];
+#pragma unroll
+        for (int m = 0; m < 16; m++) x[m] = sx[r * kStride + 4 * m + q];
+        float lo = x[0], hi = x[0];
+#pragma unroll
+        for (int m = 1; m < 16; m++) {
+            lo = fminf(lo, x[m]);
+            hi = fmaxf(hi, x[m]);
+        }
+        lo = fminf(lo, dpp_get<0xB1, 0xF>(lo));
+        hi = fmaxf(hi, dpp_get<0xB1, 0xF>(hi));
+        lo = fminf(lo, dpp_get<0x4E, 0xF>(lo));
+        hi = fmaxf(hi, dpp_get<0x4E, 0xF>(hi));
+        const _Float16 zh = (_Float16)lo;                       // round to nearest even
+        const float range = hi - lo;
+        const float step = range / (float)qmax;                 // correctly rounded division
+        const _Float16 sh = (_Float16)step;
+        const float m = (float)zh, s = (float)sh;
+        const float inv = (s > 0.0f) ? (1.0f / s) : 0.0f;
+        uint32_t words[n_words];
+        float* const se = &s_e[wave][g * kGqGroup * 16 + q * 16 + r];
+        auto emit = [&](int k, float ne) {                      // the errors of columns 4 k .. 4 k + 3, this lane's 4 k + q
+            se[k * 64] = ne;
+            eb[(long)(16 * g + k) * eld] = ne;                  // (unread behind the last panel; the place is dead all the same)
+        };
+        if (__any(gq_group_chain<BITS>(x, q, m, s, inv, s_d[g], &s_inv[g * kGqGroup], words, emit)))
+            gq_group_chain_exact<BITS>(sx, r, q, m, s, inv, s_d[g], words, emit);
+        if (row < N) {
+            uint8_t* dst = codes + (row * K + base + kGqGroup * g) * BITS / 8;
+            constexpr int mine = n_words / 4;                   // each lane of a quad writes a quarter of the row's codes
+            uint32_t out[mine];
+#pragma unroll
+            for (int k = 0; k < mine; k++)
+                out[k] = (q & 2) ? ((q & 1) ? words[3 * mine + k] : words[2 * mine + k]) : ((q & 1) ? words[mine + k] : words[k]);
+            if constexpr (mine == 4) store_global(dst + 16 * q, make_uint4(out[0], out[1], out[2], out[3]));
+            else if constexpr (mine == 2) store_global(dst + 8 * q, make_uint2(out[0], out[1]));
+            else store_global(dst + 4 * q, out[0]);
+            const long sg = row * (K / kGqGroup) + base / kGqGroup + g;
+            if (q == 0) store_global(scale + sg, (uint16_t)f16_bits(sh));
+            if (q == 1) store_global(zero + sg, (uint16_t)f16_bits(zh));
         }
     }
 }
 
-// v[r, j] = fma(-E[c, r], B[c, j], v[r, j]) for c = 0 .. 64 n_chunks - 1 in that order (one or two groups' worth of
-// corrections in one pass over v: the working copy is what this kernel streams), rows [row_begin, row_end) in tiles of
-// 64 from row_begin, columns [col_begin, col_end) in tiles of 128 from col_begin.  E[c, r] = e[c * lde + r] (whole
-// 64-row tiles are loaded: the buffer covers the rows rounded up), B[c, j] = b[c * ldb + j].  lower_only: tiles that
-// lie wholly above the diagonal (every row < every column) are left alone.
-__global__ __launch_bounds__(kGqTrailThreads) void gptq_trail_kernel(
-    float* __restrict__ v, long ldv, const float* __restrict__ e, long lde, const float* __restrict__ b, long ldb,
-    long row_begin, long row_end, long col_begin, long col_end, int n_chunks, int lower_only)
+// 64 x 64 values in the layout of 4 x 4 tiles of v_mfma_f32_16x16x4_f32 whose rows and columns are interleaved: tile (a, b)
+// register i of lane (rg = lane / 16, cl = lane % 16) is row 16 rg + 4 i + a, column 4 cl + b.  So a lane's operands for
+// four tiles are four neighbouring floats, its 64 values are 16 rows of four neighbouring floats, and every load and
+// store moves 16 bytes per lane, 256 bytes per row.
+struct GqTile {
+    f32x4_t t[4][4];
+};
+
+// acc += sum over c of A[c, row] B[c, column], c ascending, n a multiple of 16, for the 2 x 2 tiles of a workgroup (wavefront
+// w: rows of tile row w / 2, columns of tile column w % 2).  Sixteen c's at a time go through LDS, fetched one stage
+// (2048 cycles of products per wavefront) before they are stored there: a wavefront that streams its own operands
+// from L2 twice as far ahead was bound by that traffic (85 TFLOP/s: the 32 KB of L1 hold no two wavefronts' batches).
+// ap, bp: this wavefront's share of the operands, tile w % 2 and the c's 4 (w / 2) .. + 3 and 8 + 4 (w / 2) .. + 3 of a stage, at the
+// lane's own place (c = rg, row or column 4 cl); lda4, ldb4: four c's further.
+template <bool NEG_A>
+__device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, const float* ap, long lda4, const float* bp, long ldb4, int n)
 {
-    __shared__ __attribute__((aligned(16))) float s_e[kGqGroup][kGqRows];
-    __shared__ __attribute__((aligned(16))) float s_u[kGqGroup][kGqTrailCols];
-    const int tid = threadIdx.x;
-    const long col0 = col_begin + (long)blockIdx.x * kGqTrailCols;
-    const long row0 = row_begin + (long)blockIdx.y * kGqRows;
-    if (lower_only && row0 + kGqRows - 1 < col0) return;        // the whole workgroup
-    const int tx = tid & 31, ty = tid >> 5;
-    const long col = col0 + 4 * tx;
-    const long row = row0 + 8 * ty;
-    const bool in_cols = col < col_end;
-    float4 acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-        acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (in_cols && row + i < row_end) acc[i] = *reinterpret_cast<const float4*>(v + (row + i) * ldv + col);
-    }
-    for (int ch = 0; ch < n_chunks; ch++) {
-        if (ch) __syncthreads();                    // the previous chunk's reads of LDS are done
-        const float* ec = e + (long)ch * kGqGroup * lde;
-        const float* bc = b + (long)ch * kGqGroup * ldb;
-#pragma unroll
-        for (int i = 0; i < kGqGroup * kGqRows / 4 / kGqTrailThreads; i++) {
-            const int at = (i * kGqTrailThreads + tid) * 4;
-            const int c = at / kGqRows, r = at % kGqRows;
-            *reinterpret_cast<float4*>(&s_e[c][r]) = *reinterpret_cast<const float4*>(ec + (long)c * lde + row0 + r);
-        }
-#pragma unroll
-        for (int i = 0; i < kGqGroup * kGqTrailCols / 4 / kGqTrailThreads; i++) {
-            const int at = (i * kGqTrailThreads + tid) * 4;
-            const int c = at / kGqTrailCols, n = at % kGqTrailCols;
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (col0 + n < col_end) q = *reinterpret_cast<const float4*>(bc + (long)c * ldb + col0 + n);
-            *reinterpret_cast<float4*>(&s_u[c][n]) = q;
-        }
+    constexpr int kStage = 2 * 16 * kGqGroup;                   // floats of one operand
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float* const put = s_op + (wave & 1) * 16 * kGqGroup + (wave >> 1) * 4 * kGqGroup + 4 * lane;
+    const float* const get_a = s_op + (wave >> 1) * 16 * kGqGroup + 4 * lane;
+    const float* const get_b = s_op + kStage + (wave & 1) * 16 * kGqGroup + 4 * lane;
+    float4 fa[2], fb[2];
+    auto fetch = [&] {
+        fa[0] = load_global<float4>(ap);
+        fa[1] = load_global<float4>(ap + 2 * lda4);
+        fb[0] = load_global<float4>(bp);
+        fb[1] = load_global<float4>(bp + 2 * ldb4);
+        ap += 4 * lda4;
+        bp += 4 * ldb4;
+        __builtin_amdgcn_sched_barrier(0);                      // or they move down to their use
+    };
+    auto park = [&](int buf) {
+        float* const at = put + buf * 2 * kStage;
+        *reinterpret_cast<float4*>(at) = fa[0];
+        *reinterpret_cast<float4*>(at + 8 * kGqGroup) = fa[1];
+        *reinterpret_cast<float4*>(at + kStage) = fb[0];
+        *reinterpret_cast<float4*>(at + kStage + 8 * kGqGroup) = fb[1];
         __syncthreads();
-#pragma unroll 4
-        for (int c = 0; c < kGqGroup; c++) {
-            const float4 e0 = *reinterpret_cast<const float4*>(&s_e[c][8 * ty]);
-            const float4 e1 = *reinterpret_cast<const float4*>(&s_e[c][8 * ty + 4]);
-            const float4 uu = *reinterpret_cast<const float4*>(&s_u[c][4 * tx]);
-            const float ne[8] = {-e0.x, -e0.y, -e0.z, -e0.w, -e1.x, -e1.y, -e1.z, -e1.w};
+    };
+    auto multiply = [&](int buf) {
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
-                acc[i].x = __builtin_fmaf(ne[i], uu.x, acc[i].x);
-                acc[i].y = __builtin_fmaf(ne[i], uu.y, acc[i].y);
-                acc[i].z = __builtin_fmaf(ne[i], uu.z, acc[i].z);
-                acc[i].w = __builtin_fmaf(ne[i], uu.w, acc[i].w);
-            }
+        for (int k = 0; k < 4; k++) {
+            const float4 av = *reinterpret_cast<const float4*>(get_a + buf * 2 * kStage + k * 4 * kGqGroup);
+            const float4 bv = *reinterpret_cast<const float4*>(get_b + buf * 2 * kStage + k * 4 * kGqGroup);
+            const float ar[4] = {NEG_A ? -av.x : av.x, NEG_A ? -av.y : av.y, NEG_A ? -av.z : av.z, NEG_A ? -av.w : av.w};
+            const float br[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+            for (int x = 0; x < 4; x++)
+#pragma unroll
+                for (int y = 0; y < 4; y++) acc.t[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[x], br[y], acc.t[x][y], 0, 0, 0);
         }
+    };
+    fetch();
+    park(0);
+    int buf = 0;
+#pragma unroll 1
+    for (int c = 16; c < n; c += 16) {
+        fetch();
+        multiply(buf);
+        buf ^= 1;
+        park(buf);              // this buffer's last readers passed the barrier of the stage before
     }
+    multiply(buf);
+}
+
+// v[r, j] = fma(-E[c, r], U[c, j], v[r, j]) for the panel's n_cols columns c in ascending order, every row r, columns
+// [col_begin, K).  A wavefront owns 64 x 64 values, a workgroup 128 x 128; FIRST: v's values are still those of w.
+// Bound: fp32 matrix instructions (a register-only loop holds 150 TFLOP/s).  14336 rows, 256 columns over the 3840 behind
+// them: 250 us = 113 TFLOP/s, and v is passed over 16 times for 4096 columns; as vector fmas, 128 columns a pass, the
+// same corrections took 3.9 ms per matrix at 57 TFLOP/s where these take 2.1 ms.
+template <bool FIRST>
+__global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u,
+                                                         long N, long K, long base, int n_cols, long col_begin, GqErr err)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rg = lane >> 4, cl = lane & 15;
+    // Workgroups are dealt to the eight XCDs in turn: an XCD takes every eighth pair of row blocks, and walks them eight
+    // pairs at a time across all columns, so that the 64 tiles it runs at a time share 8 row and 8 column operands in its L2.
+    const uint32_t row_pairs = (uint32_t)((N + 2 * kGqRows - 1) / (2 * kGqRows));
+    const uint32_t col_pairs = (uint32_t)((K - col_begin + 2 * kGqGroup - 1) / (2 * kGqGroup));
+    const uint32_t xcd = blockIdx.x & 7, at = blockIdx.x >> 3;
+    const uint32_t per_xcd = (row_pairs + 7) >> 3;
+    const uint32_t band = at / (8 * col_pairs), in_band = at - band * 8 * col_pairs;
+    const uint32_t height = min(8u, per_xcd - 8 * band);
+    const uint32_t cp = in_band / height, rp = xcd + 8 * (8 * band + in_band - cp * height);
+    if (rp >= row_pairs) return;
+    // a wavefront whose block lies outside (an odd number of blocks) works on the last one as well and keeps it to itself
+    const long n_blocks = (N + kGqRows - 1) / kGqRows;
+    const long block = min(2 * (long)rp + (wave >> 1), n_blocks - 1);
+    const long col0 = min(col_begin + (2 * (long)cp + (wave & 1)) * kGqGroup, K - kGqGroup);
+    const bool mine = 2 * (long)rp + (wave >> 1) == block && col_begin + (2 * (long)cp + (wave & 1)) * kGqGroup == col0;
+    const long row0 = block * kGqRows;
+    const bool whole = row0 + kGqRows <= N;
+    __shared__ __attribute__((aligned(16))) float s_op[2 * 2 * 2 * 16 * kGqGroup];
+    const uint32_t off = 16 * rg * (uint32_t)K + 4 * cl;
+    GqTile acc;
+    auto load = [&](int i, int a, const void* at) {
+        float4 val;
+        if constexpr (FIRST) {
+            const uint2 raw = load_global<uint2>(at);
+            val = make_float4(bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y));
+        } else {
+            val = load_global<float4>(at);
+        }
+        acc.t[a][0][i] = val.x; acc.t[a][1][i] = val.y; acc.t[a][2][i] = val.z; acc.t[a][3][i] = val.w;
+    };
+    const auto* src = [&] {
+        if constexpr (FIRST) return w + row0 * K + col0;
+        else return (const float*)v + row0 * K + col0;
+    }();
+    if (whole) {
 #pragma unroll
-    for (int i = 0; i < 8; i++)
-        if (in_cols && row + i < row_end) *reinterpret_cast<float4*>(v + (row + i) * ldv + col) = acc[i];
+        for (int r = 0; r < 16; r++) load(r >> 2, r & 3, src + r * K + off);
+    } else {
+        const int last = (int)(N - 1 - row0);
+#pragma unroll
+        for (int r = 0; r < 16; r++) load(r >> 2, r & 3, src + min(16 * rg + r, last) * K + 4 * cl);
+    }
+    long eld;
+    const float* const eb = gq_err_block(err, min(2 * (long)rp + (wave & 1), n_blocks - 1), eld);
+    gq_tile_products<false>(acc, s_op, eb + (wave >> 1) * eld + 4 * lane, eld, u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl,
+                            4 * K, n_cols);
+    if (!mine) return;
+    float* dst = v + row0 * K + col0;
+    asm("" : "+s"(dst));        // the loads' 16 addresses are worked out again here, not kept through the products
+    auto store = [&](int r) {
+        const int i = r >> 2, a = r & 3;
+        store_global(dst + r * K + off, make_float4(acc.t[a][0][i], acc.t[a][1][i], acc.t[a][2][i], acc.t[a][3][i]));
+    };
+    if (whole) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) store(r);
+    } else {
+        const int rows = (int)(N - row0);
+#pragma unroll
+        for (int r = 0; r < 16; r++)
+            if (16 * rg + r < rows) store(r);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -326,15 +574,17 @@ __global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t
 
 // ---------------------------------------------------------------------------
 // Factor of the inverse Hessian: U upper triangular, (H + damping)^-1 = U^T U.
-// With J the order-reversing permutation and J (H + damping) J = R^T R (R upper triangular, plain Cholesky),
-// U = J R^-T J.  Both steps are built from the two kernels above:
-//   Cholesky, per block of 64 columns: the 64 x 64 diagonal block is factored by one wavefront; the rows
-//     below it are solved against that block (group kernel without quantisation: e = the new column block of
-//     L = R^T, stored as rows of R); the rest of the lower triangle loses L_panel L_panel^T (trail kernel with
-//     the panel, read from R, on both sides);
-//   inverse: the rows of R^-T come from forward substitution of the unit vectors against R, which is the
-//     quantizer's sweep with nothing quantised and the identity as the matrix; a row c only starts at its own
-//     column, so a step touches rows [0, base + 64) only.  e is written straight to U's mirrored position.
+// With J the order-reversing permutation and A = J (H + damping) J = L L^T (plain Cholesky), U = J L^-1 J.
+// Cholesky and inverse run together, block of 64 columns after block: L^-1 is what forward substitution makes of the
+// unit vectors, and the columns of A to the left of a block are dead by the time their part of the substitution starts,
+// so both live in one lower triangle v.  Step k, two launches:
+//   solve kernel   P = the block row that every later row is corrected with, 64 x K: for rows j below the block the new
+//                  column block of L (P[c, j] = L[j, 64 k + c]: row j of A solved against L_kk), for columns j left of it
+//                  the finished rows of L^-1 (column j of the right-hand sides solved against L_kk), the inverse of L_kk
+//                  itself in between (unit vectors); the finished rows go to their mirrored place in u;
+//   update kernel  v[i, j] -= sum_c P[c, i] P[c, j] for the rows i below the block, columns j <= i (columns of the block
+//                  itself start from zero): fp32 matrix products.  Its first workgroup does the next diagonal block
+//                  before all else and factors it while the others are at work.
 
 // damping = damp * mean of the diagonal, a zero diagonal entry counting as (and becoming) 1
 __global__ __launch_bounds__(256) void gptq_damping_kernel(const float* __restrict__ hess, long K, float damp,
@@ -355,47 +605,250 @@ __global__ __launch_bounds__(256) void gptq_damping_kernel(const float* __restri
     if (threadIdx.x == 0) *lambda = (float)((double)damp * s_part[0] / (double)K);
 }
 
-// v = J (H + damping) J
+// v = the lower triangle of J (H + damping) J, whole 64 x 64 blocks, a workgroup per 64 rows x 256 columns
 __global__ __launch_bounds__(256) void gptq_reverse_kernel(const float* __restrict__ hess, long K,
                                                            const float* __restrict__ lambda, float* __restrict__ v)
 {
-    const long at = (long)blockIdx.x * 256 + threadIdx.x;
-    if (at >= K * K) return;
-    const long i = at / K, j = at - i * K;
-    float val = hess[(K - 1 - i) * K + (K - 1 - j)];
-    if (i == j) val = ((val == 0.0f) ? 1.0f : val) + *lambda;
-    v[at] = val;
+    const long row0 = (long)blockIdx.y * kGqGroup;
+    const long j = (long)blockIdx.x * 256 + threadIdx.x;
+    if (j >= row0 + kGqGroup) return;
+    const float add = *lambda;
+    for (int r = 0; r < kGqGroup; r++) {
+        const long i = row0 + r;
+        float val = hess[(K - 1 - i) * K + (K - 1 - j)];
+        if (i == j) val = ((val == 0.0f) ? 1.0f : val) + add;
+        v[i * K + j] = val;
+    }
 }
 
-__global__ __launch_bounds__(256) void gptq_fill_kernel(float* __restrict__ m, long K, float diag)
+// Cholesky of the 64 x 64 block in LDS (lower triangle; row stride 68), by the whole workgroup: 16 columns at a time by the
+// first wavefront, a lane per row with the 16 values in registers (pivots and multipliers through v_readlane), then the
+// 16 columns' products taken from what is right of them by all threads.  r[c * 64 + j] = L[j, c] for j >= c, 0 otherwise.
+__device__ __forceinline__ void gq_chol_block(float* s_m, float* __restrict__ r)
 {
-    const long at = (long)blockIdx.x * 256 + threadIdx.x;
-    if (at >= K * K) return;
-    const long i = at / K, j = at - i * K;
-    m[at] = (i == j) ? diag : 0.0f;
+    constexpr int kLd = kGqGroup + 4;
+    const int tid = threadIdx.x;
+    for (int p = 0; p < kGqGroup; p += 16) {
+        if (tid < kWave) {
+            float a[16];
+            bool ordinary = true;
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const float4 t = *reinterpret_cast<const float4*>(s_m + tid * kLd + p + 4 * c);
+                a[4 * c] = t.x; a[4 * c + 1] = t.y; a[4 * c + 2] = t.z; a[4 * c + 3] = t.w;
+            }
+#pragma unroll
+            for (int c = 0; c < 16; c++) {
+                const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[c]), p + c));
+                // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each
+                const float y = __builtin_amdgcn_rsqf(d);
+                const float s0 = d * y, l0 = a[c] * y;
+                const float sq = __builtin_fmaf(__builtin_fmaf(-s0, s0, d), 0.5f * y, s0);
+                float l = __builtin_fmaf(__builtin_fmaf(-sq, l0, a[c]), y, l0);
+                l = (tid == p + c) ? sq : l;
+                ordinary &= d > 1e-30f && d < 1e30f;
+                a[c] = l;
+#pragma unroll
+                for (int j = c + 1; j < 16; j++) {
+                    const float lj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), p + j));
+                    a[j] = __builtin_fmaf(-l, lj, a[j]);
+                }
+            }
+            if (ordinary) {                                         // the same in every lane
+#pragma unroll
+                for (int c = 0; c < 4; c++)
+                    *reinterpret_cast<float4*>(s_m + tid * kLd + p + 4 * c) = make_float4(a[4 * c], a[4 * c + 1], a[4 * c + 2], a[4 * c + 3]);
+            } else {
+                // a pivot so large or small that the estimate's steps may leave the range (or none at all: NaN): root and
+                // division as they are, in LDS
+#pragma unroll 1
+                for (int c = 0; c < 16; c++) {
+                    const float root = sqrtf(s_m[(p + c) * kLd + p + c]);
+                    const float l = (tid == p + c) ? root : s_m[tid * kLd + p + c] / root;
+                    s_m[tid * kLd + p + c] = l;
+                    for (int j = c + 1; j < 16; j++)
+                        s_m[tid * kLd + p + j] = __builtin_fmaf(-l, s_m[(p + j) * kLd + p + c], s_m[tid * kLd + p + j]);
+                }
+            }
+        }
+        __syncthreads();
+        const int ty = tid >> 4, tx = tid & 15, n = 3 - p / 16;
+        float4 ri[3][4], rj[3][4];
+#pragma unroll
+        for (int t = 0; t < 3; t++) {
+            if (t >= n) break;
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                ri[t][c] = *reinterpret_cast<const float4*>(s_m + (p + 16 + ty + 16 * t) * kLd + p + 4 * c);
+                rj[t][c] = *reinterpret_cast<const float4*>(s_m + (p + 16 + tx + 16 * t) * kLd + p + 4 * c);
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            if (a >= n) break;
+#pragma unroll
+            for (int b = 0; b <= a; b++) {                      // (the whole of a 16 x 16 diagonal tile; its upper half is not read)
+                float* const at = s_m + (p + 16 + ty + 16 * a) * kLd + p + 16 + tx + 16 * b;
+                float acc = *at;
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    acc = __builtin_fmaf(-ri[a][c].x, rj[b][c].x, acc);
+                    acc = __builtin_fmaf(-ri[a][c].y, rj[b][c].y, acc);
+                    acc = __builtin_fmaf(-ri[a][c].z, rj[b][c].z, acc);
+                    acc = __builtin_fmaf(-ri[a][c].w, rj[b][c].w, acc);
+                }
+                *at = acc;
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < kGqGroup * kGqGroup / 256; i++) {
+        const int at = i * 256 + tid, c = at >> 6, j = at & 63;
+        r[at] = (j >= c) ? s_m[j * kLd + c] : 0.0f;
+    }
 }
 
-// R_JJ^T R_JJ = A, A = the 64 x 64 diagonal block at (j0, j0) of v (its lower triangle is current), R_JJ
-// written to r[(j0 + c) * K + j0 + j] (zeros below the diagonal).  One wavefront, lane j holds column j.
-__global__ __launch_bounds__(kWave) void gptq_chol_diag_kernel(const float* __restrict__ v, long K, long j0,
-                                                               float* __restrict__ r)
+__global__ __launch_bounds__(256) void gptq_chol_diag_kernel(const float* __restrict__ v, long K, float* __restrict__ r)
 {
-    const int j = threadIdx.x;
-    float col[kGqGroup];                                          // A[i, j], read from the lower triangle
+    __shared__ __attribute__((aligned(16))) float s_m[kGqGroup * (kGqGroup + 4)];
 #pragma unroll
-    for (int i = 0; i < kGqGroup; i++) col[i] = v[(j0 + max(i, j)) * K + j0 + min(i, j)];
-    // row c of R is handed from lane to lane through LDS (one write, broadcast reads)
-    __shared__ __attribute__((aligned(16))) float s_row[2][kGqGroup];
+    for (int i = 0; i < 4; i++) {
+        const int at = i * 256 + threadIdx.x, row = at >> 4, col = 4 * (at & 15);
+        *reinterpret_cast<float4*>(s_m + row * (kGqGroup + 4) + col) = load_global<float4>(v + (long)row * K + col);
+    }
+    __syncthreads();
+    gq_chol_block(s_m, r);
+}
+
+// Step k's block row P (see above) against r = the diagonal block's factor, a workgroup per 64 columns j of P, a wavefront
+// 16 of them with four lanes each, as in the group kernel.  Bound: the chain of 64 steps (divide, hand over, correct), 9 us;
+// a lane per column took 17 us, twice per step (Cholesky's panel and the substitution were separate passes).
+__global__ __launch_bounds__(256) void gptq_solve_kernel(const float* __restrict__ v, long K, long k, const float* __restrict__ r,
+                                                         float* __restrict__ p_row, float* __restrict__ u)
+{
+    constexpr int kStride = kGqGroup + 4;
+    __shared__ __attribute__((aligned(16))) float s_d[kGqGroup * kGqGroup];     // [c][j % 4][j / 4]
+    __shared__ __attribute__((aligned(16))) float2 s_inv[kGqGroup];             // diagonal entry and its reciprocal
+    __shared__ __attribute__((aligned(16))) float s_x[4][16 * kStride];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const long jb = blockIdx.x, base = k * kGqGroup;
+    const int rr = lane >> 2, q = lane & 3;
+    const long j = jb * kGqGroup + 16 * wave + rr;
+    float x[16];
+    float4 raw[4];
+    if (jb > k) {
 #pragma unroll
-    for (int c = 0; c < kGqGroup; c++) {
-        const float dcc = __shfl(col[c], c, kWave);
-        const float rd = sqrtf(dcc);
-        const float rj = (j >= c) ? col[c] / rd : 0.0f;           // R[c, j]
-        r[(j0 + c) * K + j0 + j] = rj;
-        s_row[c & 1][j] = rj;
-        __syncthreads();                                          // one wavefront: orders the LDS write before the reads
+        for (int i = 0; i < 4; i++)
+            raw[i] = *reinterpret_cast<const float4*>(v + (jb * kGqGroup + 16 * wave + 4 * (lane >> 4) + i) * K + base + 4 * (lane & 15));
+    } else if (jb < k) {
 #pragma unroll
-        for (int i = c + 1; i < kGqGroup; i++) col[i] = __builtin_fmaf(-s_row[c & 1][i], rj, col[i]);
+        for (int m = 0; m < 16; m++) x[m] = v[(base + 4 * m + q) * K + j];
+    } else {
+#pragma unroll
+        for (int m = 0; m < 16; m++) x[m] = (base + 4 * m + q == j) ? 1.0f : 0.0f;
+    }
+    if (tid < kGqGroup) {
+        const float dg = r[tid * kGqGroup + tid];
+        s_inv[tid] = make_float2(dg, 1.0f / dg);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int at = i * 256 + tid, c = at >> 4, m = at & 15;
+        const float4 d = *reinterpret_cast<const float4*>(r + c * kGqGroup + 4 * m);
+        float* dst = &s_d[c * kGqGroup + m];
+        dst[0] = d.x; dst[16] = d.y; dst[32] = d.z; dst[48] = d.w;
+    }
+    if (jb > k) {
+        float* const sx = s_x[wave];
+#pragma unroll
+        for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * (lane >> 4) + i) * kStride + 4 * (lane & 15)]) = raw[i];
+#pragma unroll
+        for (int m = 0; m < 16; m++) x[m] = sx[rr * kStride + 4 * m + q];
+    }
+    __syncthreads();
+    float* const pj = p_row + (long)q * K + j;
+    float* const uj = u + (K - 1 - base - q) * K + (K - 1 - j);
+    float keep = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kGqGroup; i++) {
+        const int k4 = i / 4, c = i % 4;
+        const float xi = c == 0 ? quad_bcast<0>(x[k4]) : c == 1 ? quad_bcast<1>(x[k4]) : c == 2 ? quad_bcast<2>(x[k4]) : quad_bcast<3>(x[k4]);
+        const float2 dg = s_inv[i];
+        const float e0 = xi * dg.y;
+        const float e = __builtin_fmaf(__builtin_fmaf(-dg.x, e0, xi), dg.y, e0);    // the quotient: one residual step
+        keep = (q == c) ? e : keep;
+        if (c == 3) {
+            pj[(long)4 * k4 * K] = keep;
+            uj[-(long)4 * k4 * K] = (jb > k) ? 0.0f : keep;
+        }
+#pragma unroll
+        for (int m = (c == 3) ? k4 + 1 : k4; m < 16; m++) x[m] = __builtin_fmaf(-e, s_d[i * kGqGroup + q * 16 + m], x[m]);
+    }
+}
+
+// v[i, j] -= sum_c P[c, i] P[c, j] for the 64 x 64 blocks (ib, jb) with k < ib, jb <= ib, the block column k starting from
+// zero; a wavefront a block, a workgroup 2 x 2 of them.  Workgroup 0 does block (k + 1, k + 1) and factors it into r.
+// K = 4096: 25 us for the first steps (bound by the blocks' way from and to memory) down to 13 us for the last (bound by
+// workgroup 0: the products, 7.5 us of Cholesky); a whole factor takes 1.83 ms where the separate passes over 64 x 128
+// tiles of vector fmas, with a one-wavefront Cholesky of 20 us between them, took 5.65 ms.
+__global__ __launch_bounds__(256, 3) void gptq_update_kernel(float* v, long K, long k, const float* __restrict__ p_row,
+                                                          float* __restrict__ r)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ln = lane & 31, h = lane >> 5;
+    __shared__ __attribute__((aligned(16))) float s_op[2 * 2 * 2 * 16 * kGqGroup];
+    if (blockIdx.x == 0) {
+        constexpr int kLd = kGqGroup + 4;
+        float* const s_m = s_op;                                // 64 rows of 68
+        __builtin_amdgcn_s_setprio(3);                          // the launch's longest chain, beside wavefronts that only add work
+        const long i0 = (k + 1) * kGqGroup;
+        const int wi = wave >> 1, wj = wave & 1;
+        float16_t acc;
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            acc[i] = v[(i0 + 32 * wi + 8 * (i >> 2) + 4 * h + (i & 3)) * K + i0 + 32 * wj + ln];
+        const float* ap = p_row + (long)h * K + i0 + 32 * wi + ln;
+        const float* bp = p_row + (long)h * K + i0 + 32 * wj + ln;
+#pragma unroll 16
+        for (int c = 0; c < kGqGroup; c += 2)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[(long)c * K], bp[(long)c * K], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 16; i++) s_m[(32 * wi + 8 * (i >> 2) + 4 * h + (i & 3)) * kLd + 32 * wj + ln] = acc[i];
+        __syncthreads();
+        gq_chol_block(s_m, r);
+        return;
+    }
+    // pairs of block rows from (k + 1) / 2 on, pair s with s + 1 pairs of block columns
+    const long s0 = (k + 1) >> 1;
+    const long at = (long)blockIdx.x - 1 + s0 * (s0 + 1) / 2;
+    long s = (long)((sqrt(8.0 * (double)at + 1.0) - 1.0) * 0.5);
+    while (s * (s + 1) / 2 > at) s--;
+    while ((s + 1) * (s + 2) / 2 <= at) s++;
+    const long last = K / kGqGroup - 1, sj = at - s * (s + 1) / 2;
+    const long ib = min(2 * s + (wave >> 1), last), jb = min(2 * sj + (wave & 1), last);
+    const long ia = min(2 * s + (wave & 1), last);              // the block whose rows this wavefront fetches for all four
+    const bool mine = ib > k && jb <= ib && 2 * s + (wave >> 1) <= last && !(ib == k + 1 && jb == k + 1);
+    const long i0 = ib * kGqGroup, j0 = jb * kGqGroup;
+    const int rg = lane >> 4, cl = lane & 15;
+    const uint32_t off = 16 * rg * (uint32_t)K + 4 * cl;
+    GqTile acc;
+    const float* const src = v + i0 * K + j0;
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        float4 val = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (jb != k) val = load_global<float4>(src + r * K + off);
+        acc.t[r & 3][0][r >> 2] = val.x; acc.t[r & 3][1][r >> 2] = val.y; acc.t[r & 3][2][r >> 2] = val.z; acc.t[r & 3][3][r >> 2] = val.w;
+    }
+    const float* const own = p_row + (long)(4 * (wave >> 1) + rg) * K + 4 * cl;
+    gq_tile_products<true>(acc, s_op, own + ia * kGqGroup, 4 * K, own + j0, 4 * K, kGqGroup);
+    if (!mine) return;
+    float* dst = v + i0 * K + j0;
+    asm("" : "+s"(dst));
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        const int i = r >> 2, a = r & 3;
+        store_global(dst + r * K + off, make_float4(acc.t[a][0][i], acc.t[a][1][i], acc.t[a][2][i], acc.t[a][3][i]));
     }
 }
 
@@ -424,56 +877,33 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
     if (workspace_bytes < dymoe_gptq_workspace_bytes(N, K)) return DYMOE_ENOSPC;
     if (!ctx) return DYMOE_ENOCTX;
     hipStream_t st = (hipStream_t)stream;
-    const long n_pad = gq_rows_padded(N);
+    const long n_blocks = gq_rows_padded(N) / kGqRows;
     float* v = reinterpret_cast<float*>(workspace);
-    float* err = reinterpret_cast<float*>((char*)workspace + gq_round256((size_t)N * (size_t)K * 4));
-    const long n_elems = N * K;
-    hipLaunchKernelGGL(gptq_widen_kernel, dim3((unsigned)((n_elems / 8 + 255) / 256)), dim3(256), 0, st,
-                       (const uint16_t*)w_bf16, n_elems, v);
-    DYMOE_HIP_LAUNCH_CHECK();
-    const dim3 grid_a((unsigned)(n_pad / kGqRows));
-    const long G = K / kGqGroup;
-    // one group of 64 columns: codes, scale, zero; its 64 errors per row go to err rows [64 * slot, 64 * slot + 64)
-    auto group_step = [&](long base, int slot) {
-        const float* xg = v + base;
-        const float* dg = u + base * K + base;
-        uint8_t* cg = codes + base * bits / 8;
-        uint16_t* sg = (uint16_t*)scale + base / kGqGroup;
-        uint16_t* zg = (uint16_t*)zero + base / kGqGroup;
-        float* eg = err + (long)slot * kGqGroup * n_pad;
-        float* const none = nullptr;
-        switch (bits) {
-        case 8:
-            dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, (gptq_group_kernel<8, false, true>), grid_a, dim3(kGqRows), 0, st, xg, K, dg, K,
-                         0L, N, none, 0L, 0L, eg, n_pad, 1L, cg, sg, zg, K * bits / 8, G);
-            break;
-        case 4:
-            dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, (gptq_group_kernel<4, false, true>), grid_a, dim3(kGqRows), 0, st, xg, K, dg, K,
-                         0L, N, none, 0L, 0L, eg, n_pad, 1L, cg, sg, zg, K * bits / 8, G);
-            break;
-        default:
-            dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, (gptq_group_kernel<2, false, true>), grid_a, dim3(kGqRows), 0, st, xg, K, dg, K,
-                         0L, N, none, 0L, 0L, eg, n_pad, 1L, cg, sg, zg, K * bits / 8, G);
-            break;
-        }
-    };
-    // corrections of `chunks` groups starting at column `base`, applied to the columns [col_begin, col_end)
-    auto trail_step = [&](long base, int chunks, long col_begin, long col_end) {
-        const dim3 grid_b((unsigned)((col_end - col_begin + kGqTrailCols - 1) / kGqTrailCols), (unsigned)(n_pad / kGqRows));
-        dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, gptq_trail_kernel, grid_b, dim3(kGqTrailThreads), 0, st, v, K,
-                     (const float*)err, n_pad, u + base * K, K, 0L, N, col_begin, col_end, chunks, 0);
-    };
-    // Two groups per pass over the working copy: the first group's corrections reach the second group's 64 columns
-    // at once, the second group is quantised, and both groups' 128 corrections then go over the remaining columns
-    // together, in the same order as one group at a time (so the same roundings) at half the traffic.
-    for (long base = 0; base < K; base += 2 * kGqGroup) {
-        group_step(base, 0);
+    float* tail = reinterpret_cast<float*>((char*)workspace + gq_round256((size_t)N * (size_t)K * 4));
+    // Panels of four groups, except where all rows make one ragged block: the linear buffer then holds 128 columns' errors.
+    const int panel = (N < kGqRows) ? kGqPanel / 2 : kGqPanel;
+    const uint16_t* w = (const uint16_t*)w_bf16;
+    uint16_t* sc = (uint16_t*)scale;
+    uint16_t* zr = (uint16_t*)zero;
+    for (long base = 0; base < K; base += panel * kGqGroup) {
+        const long left = (K - base) / kGqGroup;
+        const int groups = (int)(left < panel ? left : panel);
+        const long next = base + groups * kGqGroup;
+        const GqErr err = {v + base, K, tail, N / kGqRows};
+        auto go = [&](auto kernel) {
+            dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, kernel, dim3((unsigned)n_blocks), dim3(256), 0, st, w, v, u, N, K, base,
+                         groups, err, codes, sc, zr);
+        };
+        const bool first = base == 0;
+        if (bits == 8) first ? go(gptq_group_kernel<8, true>) : go(gptq_group_kernel<8, false>);
+        else if (bits == 4) first ? go(gptq_group_kernel<4, true>) : go(gptq_group_kernel<4, false>);
+        else first ? go(gptq_group_kernel<2, true>) : go(gptq_group_kernel<2, false>);
         DYMOE_HIP_LAUNCH_CHECK();
-        if (base + kGqGroup >= K) break;
-        trail_step(base, 1, base + kGqGroup, base + 2 * kGqGroup);
-        group_step(base + kGqGroup, 1);
-        DYMOE_HIP_LAUNCH_CHECK();
-        if (base + 2 * kGqGroup < K) trail_step(base, 2, base + 2 * kGqGroup, K);
+        if (next >= K) break;
+        const long row_pairs = (n_blocks + 1) / 2, col_pairs = (K - next + 2 * kGqGroup - 1) / (2 * kGqGroup);
+        const dim3 grid((unsigned)(8 * ((row_pairs + 7) / 8) * col_pairs));
+        dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, first ? gptq_trail_kernel<true> : gptq_trail_kernel<false>, grid, dim3(256), 0, st,
+                     w, v, u, N, K, base, groups * kGqGroup, next, err);
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;
@@ -511,67 +941,23 @@ int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, flo
     hipStream_t st = (hipStream_t)stream;
     const size_t mat = gq_round256((size_t)K * (size_t)K * 4);
     float* v = reinterpret_cast<float*>(workspace);
-    float* r = reinterpret_cast<float*>((char*)workspace + mat);
-    float* err = reinterpret_cast<float*>((char*)workspace + 2 * mat);
-    float* lambda = reinterpret_cast<float*>((char*)workspace + 2 * mat + gq_round256(2 * (size_t)kGqGroup * (size_t)K * 4));
-    const dim3 whole((unsigned)((K * K + 255) / 256));
+    float* p_row = reinterpret_cast<float*>((char*)workspace + mat);                    // 64 x K
+    float* r = reinterpret_cast<float*>((char*)workspace + 2 * mat);                     // 64 x 64
+    float* lambda = r + kGqGroup * kGqGroup;
     hipLaunchKernelGGL(gptq_damping_kernel, dim3(1), dim3(256), 0, st, hess, K, damp, lambda);
-    hipLaunchKernelGGL(gptq_reverse_kernel, whole, dim3(256), 0, st, hess, K, (const float*)lambda, v);
-    hipLaunchKernelGGL(gptq_fill_kernel, whole, dim3(256), 0, st, r, K, 0.0f);
+    hipLaunchKernelGGL(gptq_reverse_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)(K / kGqGroup)), dim3(256), 0, st, hess, K,
+                       (const float*)lambda, v);
     DYMOE_HIP_LAUNCH_CHECK();
-    float* const none = nullptr;
-    // (both loops take two blocks of 64 per pass over the trailing matrix, as the quantizer's sweep does)
-    auto trail = [&](long row_begin, long row_end, long col_begin, long col_end, const float* e, long lde, const float* b,
-                     int chunks, int lower_only) {
-        const dim3 grid_b((unsigned)((col_end - col_begin + kGqTrailCols - 1) / kGqTrailCols),
-                          (unsigned)((row_end - row_begin) / kGqRows));
-        dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, gptq_trail_kernel, grid_b, dim3(kGqTrailThreads), 0, st, v, K, e, lde, b, K,
-                     row_begin, row_end, col_begin, col_end, chunks, lower_only);
-    };
-    // J (H + damping) J = R^T R
-    // diagonal block at j0, then the rows below it solved against it: the panel of L goes into R as rows,
-    // L[row, j0 + c] = R[j0 + c, row]
-    auto chol_block = [&](long j0) {
-        dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_chol_diag_kernel, dim3(1), dim3(kWave), 0, st, (const float*)v, K, j0, r);
-        const long below = K - j0 - kGqGroup;
-        if (below > 0)
-            dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, (gptq_group_kernel<0, true, false>), dim3((unsigned)(below / kGqRows)),
-                         dim3(kGqRows), 0, st, (const float*)(v + j0), K, (const float*)(r + j0 * K + j0), K, j0 + kGqGroup, K,
-                         r + j0 * K, K, 1L, none, 0L, 0L, (uint8_t*)nullptr, (uint16_t*)nullptr, (uint16_t*)nullptr, 0L, 0L);
-    };
-    for (long j0 = 0; j0 < K; j0 += 2 * kGqGroup) {
-        const long j1 = j0 + kGqGroup, j2 = j0 + 2 * kGqGroup;
-        chol_block(j0);
+    dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_chol_diag_kernel, dim3(1), dim3(256), 0, st, (const float*)v, K, r);
+    const long nb = K / kGqGroup, pairs = (nb + 1) / 2;
+    for (long k = 0; k < nb; k++) {
+        dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, gptq_solve_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const float*)v, K, k,
+                     (const float*)r, p_row, u);
         DYMOE_HIP_LAUNCH_CHECK();
-        if (j1 >= K) break;
-        trail(j1, K, j1, j2, r + j0 * K, K, r + j0 * K, 1, 1);          // the next block's columns first
-        chol_block(j1);
-        DYMOE_HIP_LAUNCH_CHECK();
-        if (j2 < K) trail(j2, K, j2, K, r + j0 * K, K, r + j0 * K, 2, 1);  // then both panels over the rest of the lower triangle
-        DYMOE_HIP_LAUNCH_CHECK();
-    }
-    // rows of R^-T by forward substitution of the unit vectors, mirrored into U
-    hipLaunchKernelGGL(gptq_fill_kernel, whole, dim3(256), 0, st, v, K, 1.0f);
-    hipLaunchKernelGGL(gptq_fill_kernel, whole, dim3(256), 0, st, u, K, 0.0f);
-    DYMOE_HIP_LAUNCH_CHECK();
-    // one block of 64 columns for the rows [0, rows): e of (row c, column base + i) is U[K - 1 - base - i, K - 1 - c];
-    // rows that have not started yet (c >= base + 64) hold zeros there and give e = 0
-    auto subst_block = [&](long base, long rows, int slot) {
-        dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, (gptq_group_kernel<0, true, true>), dim3((unsigned)(rows / kGqRows)), dim3(kGqRows),
-                     0, st, (const float*)(v + base), K, (const float*)(r + base * K + base), K, 0L, rows,
-                     u + (K - 1 - base) * K + (K - 1), -K, -1L, err + (long)slot * kGqGroup * K, K, 1L, (uint8_t*)nullptr,
-                     (uint16_t*)nullptr, (uint16_t*)nullptr, 0L, 0L);
-    };
-    for (long base = 0; base < K; base += 2 * kGqGroup) {
-        const long b1 = base + kGqGroup, b2 = base + 2 * kGqGroup;
-        const long rows = (b2 < K) ? b2 : K;
-        subst_block(base, rows, 0);
-        DYMOE_HIP_LAUNCH_CHECK();
-        if (b1 >= K) break;
-        trail(0, b1, b1, b2, err, K, r + base * K, 1, 0);
-        subst_block(b1, rows, 1);
-        DYMOE_HIP_LAUNCH_CHECK();
-        if (b2 < K) trail(0, b2, b2, K, err, K, r + base * K, 2, 0);
+        if (k + 1 == nb) break;
+        const long s0 = (k + 1) / 2;
+        dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, gptq_update_kernel, dim3((unsigned)(1 + pairs * (pairs + 1) / 2 - s0 * (s0 + 1) / 2)),
+                     dim3(256), 0, st, v, K, k, (const float*)p_row, r);
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;

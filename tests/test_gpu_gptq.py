@@ -289,3 +289,48 @@ def test_gptq_sweep_edge_rows(ctx):
     h = ctx.gptq_hessian(to_bf16(xb))
     torch.cuda.synchronize()
     assert np.allclose(h.cpu().numpy(), O.gptq_hessian(xb), rtol=1e-6, atol=0)
+
+
+# a panel is four groups of 64 columns, a row block 64 rows, a trail workgroup two row blocks by two groups: rows below,
+# at and beyond each edge (below 64 rows panels are two groups wide), columns that end inside a panel and inside a pair
+@pytest.mark.parametrize("N,K,bits", [(63, 320, 4), (64, 512, 2), (65, 576, 8), (127, 256, 4), (129, 832, 2), (200, 704, 4)])
+def test_gptq_sweep_panel_edges(ctx, N, K, bits):
+    _, wb, U = _case(800 + N, N, K)
+    want = O.gptq_quantize_pack(wb, U, bits)
+    got = ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(U).to(DEV), bits)
+    assert _same(got, want)
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_gptq_sweep_subnormal_errors(ctx, bits):
+    """Rows so small that rest / U[c,c] is subnormal (the groups that are done again with an IEEE division): the
+    corrections they pass on, and the groups behind them, must still be the exact sequence's."""
+    N, K = 66, 320
+    _, wb, U = _case(850, N, K)
+    w = synth.bf16_bits_to_f32(wb).copy()
+    w[3] *= 1e-37
+    w[20] *= 3e-36
+    w[64, 64:128] = 0.0
+    w[65] = 1e-39
+    wb = synth.f32_to_bf16_bits(w)
+    for scale in (1.0, 1e3):
+        u = (U * np.float32(scale)).astype(np.float32)
+        want = O.gptq_quantize_pack(wb, u, bits)
+        got = ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(u).to(DEV), bits)
+        assert _same(got, want)
+
+
+# blocks of 64, updated in 2 x 2: one block, two, an odd number, and pivots outside the range of the estimate's steps
+@pytest.mark.parametrize("K,size", [(128, 1.0), (320, 1.0), (704, 1.0), (192, 1e-34), (192, 1e32)])
+def test_gptq_factor_block_edges(ctx, K, size):
+    xb = synth.calibration_inputs(870 + K, 2 * K, K)
+    H = O.gptq_hessian(xb)
+    H32 = (H * size / np.diag(H).mean()).astype(np.float32)
+    want = O.gptq_factor(H32.astype(np.float64))
+    u = ctx.gptq_factor(torch.from_numpy(H32).to(DEV))
+    torch.cuda.synchronize()
+    U = u.cpu().numpy().astype(np.float64)
+    rel = np.abs(U - want).max(axis=1) / np.abs(want).max(axis=1)
+    print("K=%d size %.0e: max row-relative error %.2e" % (K, size, rel.max()))
+    # the same bound as for the other sizes: fp32 Cholesky of a matrix with a condition number of about 1e3
+    assert np.array_equal(U, np.triu(U)) and rel.max() < 2e-4
