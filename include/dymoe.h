@@ -250,6 +250,16 @@ int dymoe_assign_precision(dymoe_ctx* ctx, int phase, const void* importance,
                            uint8_t* bits, int32_t* rank, void* stream);
 
 /*
+ * dymoe_expert_importance and dymoe_assign_precision behind it in as few launches as the sizes allow (one in the decode
+ * phase and for short prefills), with the same arguments, limits, errors and results, bit for bit.
+ * rank must not be NULL.  x not NULL (prefill; [T, H] bf16, 16-byte aligned, H a multiple of 8): token_score is an output,
+ * filled as by dymoe_token_score_norm first; x NULL: token_score is the caller's.
+ */
+int dymoe_rank_experts(dymoe_ctx* ctx, int phase, const void* x, int H, const int32_t* idx, const float* probs, float* token_score,
+                       int T, int E, int k, int k_hh, int n_tiers, const int32_t* tier_count, const uint8_t* tier_bits,
+                       int floor_bits, void* importance, int32_t* load, uint8_t* bits, int32_t* rank, void* stream);
+
+/*
  * Decode-step front end: dymoe_route_topk, dymoe_expert_importance (decode
  * phase: importance = gate score, Sec. 4.2.2 Eq. 3) and dymoe_assign_precision
  * (Sec. 4.3, Sec. 5) in one launch, for steps of 1 <= T <= DYMOE_FRONT_MAX_TOKENS

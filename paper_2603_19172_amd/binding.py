@@ -34,7 +34,7 @@ EXPORTS = [
     "dymoe_create", "dymoe_destroy", "dymoe_strerror", "dymoe_workspace_bytes", "dymoe_ffn_plan_offset",
     "dymoe_route_topk", "dymoe_token_score_norm", "dymoe_attention_workspace_bytes",
     "dymoe_token_score_attention", "dymoe_expert_importance",
-    "dymoe_depth_schedule", "dymoe_assign_precision", "dymoe_quantize_pack",
+    "dymoe_depth_schedule", "dymoe_assign_precision", "dymoe_rank_experts", "dymoe_quantize_pack",
     "dymoe_gptq_workspace_bytes", "dymoe_gptq_quantize_pack", "dymoe_gptq_hessian",
     "dymoe_gptq_factor_workspace_bytes", "dymoe_gptq_factor",
     "dymoe_quantize_experts", "dymoe_pack_tiles", "dymoe_pack_code_tiles", "dymoe_moe_ffn_mixed", "dymoe_moe_ffn_mixed_noalloc",
@@ -139,6 +139,8 @@ lib.dymoe_assign_precision.restype = _i
 lib.dymoe_assign_precision.argtypes = [_vp, _i, _vp, _vp, _i, _i, _vp, _vp, _i, _vp, _vp, _vp]
 lib.dymoe_quantize_pack.restype = _i
 lib.dymoe_quantize_pack.argtypes = [_vp, _vp, _l, _l, _i, _i, _vp, _vp, _vp, _vp]
+lib.dymoe_rank_experts.restype = _i
+lib.dymoe_rank_experts.argtypes = [_vp, _i, _vp, _i, _vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp, _i, _vp, _vp, _vp, _vp, _vp]
 lib.dymoe_gptq_workspace_bytes.restype = _sz
 lib.dymoe_gptq_workspace_bytes.argtypes = [_l, _l]
 lib.dymoe_gptq_hessian.restype = _i

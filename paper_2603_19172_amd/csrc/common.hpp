@@ -265,6 +265,23 @@ __device__ __forceinline__ float wave_max_dpp(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// sqrt(sum of the row's H squares), by one wavefront, in every lane; H a multiple of 8
+__device__ __forceinline__ float token_norm(const uint16_t* __restrict__ row, int H, int lane)
+{
+    float acc = 0.0f;
+    for (int col = lane * 8; col < H; col += kWave * 8) {
+        const uint4 v = *reinterpret_cast<const uint4*>(row + col);
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const float a = bf16_lo(u[i]), b = bf16_hi(u[i]);
+            acc = fmaf(a, a, acc);
+            acc = fmaf(b, b, acc);
+        }
+    }
+    return sqrtf(wave_sum(acc));
+}
+
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll

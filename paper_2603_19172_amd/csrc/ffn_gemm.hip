@@ -80,6 +80,54 @@ __host__ __device__ inline PlanPtrs plan_ptrs(int32_t* base, int E, int P)
     return p;
 }
 
+// Column order in which the code fields of a dword come out of the mask-and-or
+// extraction: inside every 8 columns (int4) 0,4,1,5,2,6,3,7; inside every 16
+// columns (int2) 0,8,1,9,...,7,15.  Inputs are packed pairs of 16-bit values.
+__device__ __forceinline__ uint4 perm8(const uint4 v)
+{
+    uint4 o;
+    o.x = (v.x & 0xffffu) | (v.z << 16);
+    o.y = (v.x >> 16) | (v.z & 0xffff0000u);
+    o.z = (v.y & 0xffffu) | (v.w << 16);
+    o.w = (v.y >> 16) | (v.w & 0xffff0000u);
+    return o;
+}
+
+__device__ __forceinline__ void perm16(const uint4 a, const uint4 b, uint4& o0, uint4& o1)
+{
+    o0.x = (a.x & 0xffffu) | (b.x << 16);
+    o0.y = (a.x >> 16) | (b.x & 0xffff0000u);
+    o0.z = (a.y & 0xffffu) | (b.y << 16);
+    o0.w = (a.y >> 16) | (b.y & 0xffff0000u);
+    o1.x = (a.z & 0xffffu) | (b.z << 16);
+    o1.y = (a.z >> 16) | (b.z & 0xffff0000u);
+    o1.z = (a.w & 0xffffu) | (b.w << 16);
+    o1.w = (a.w >> 16) | (b.w & 0xffff0000u);
+}
+
+// Three fp16 copies of the bf16 activations (exact inside fp16's normal range):
+// one in each of the column orders above and one in the natural order (int8
+// codes come out of a dword in order).  A thread converts 16 columns.
+__device__ __forceinline__ void prep_x(const uint16_t* __restrict__ x, long i, uint16_t* __restrict__ xh4,
+                                       uint16_t* __restrict__ xh2, uint16_t* __restrict__ xh8)
+{
+    const uint4 a = reinterpret_cast<const uint4*>(x)[2 * i];
+    const uint4 b = reinterpret_cast<const uint4*>(x)[2 * i + 1];
+    uint4 ha, hb;
+    ha.x = pack_half2(bf16_lo(a.x), bf16_hi(a.x)); ha.y = pack_half2(bf16_lo(a.y), bf16_hi(a.y));
+    ha.z = pack_half2(bf16_lo(a.z), bf16_hi(a.z)); ha.w = pack_half2(bf16_lo(a.w), bf16_hi(a.w));
+    hb.x = pack_half2(bf16_lo(b.x), bf16_hi(b.x)); hb.y = pack_half2(bf16_lo(b.y), bf16_hi(b.y));
+    hb.z = pack_half2(bf16_lo(b.z), bf16_hi(b.z)); hb.w = pack_half2(bf16_lo(b.w), bf16_hi(b.w));
+    reinterpret_cast<uint4*>(xh4)[2 * i] = perm8(ha);
+    reinterpret_cast<uint4*>(xh4)[2 * i + 1] = perm8(hb);
+    uint4 o0, o1;
+    perm16(ha, hb, o0, o1);
+    reinterpret_cast<uint4*>(xh2)[2 * i] = o0;
+    reinterpret_cast<uint4*>(xh2)[2 * i + 1] = o1;
+    reinterpret_cast<uint4*>(xh8)[2 * i] = ha;
+    reinterpret_cast<uint4*>(xh8)[2 * i + 1] = hb;
+}
+
 // One workgroup of 16 wavefronts.  Counting and scattering go through one
 // histogram per wavefront when they fit in LDS (E <= kPlanPrivE), so that the
 // atomics of a popular expert do not queue up across the whole workgroup; a
@@ -87,6 +135,8 @@ __host__ __device__ inline PlanPtrs plan_ptrs(int32_t* base, int E, int P)
 // wavefronts) + (its turn inside its wavefront).  Tiles are laid out by one
 // thread per expert after a scan of the per-expert tile counts, staged in LDS
 // when the list fits, and sorted by rank counting.
+// The workgroups behind the first one make the fp16 copies of x (prep_x) meanwhile: neither needs the other, and as a
+// launch of their own the copies took 3 us (61 tokens of 2048) to 12 us (1357 of 4096) after the plan's 9 to 25.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kPlanPrivE = 256;        // 16 x 256 counters = 16 KiB
@@ -97,8 +147,16 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
                                                             const uint8_t* __restrict__ bits,
                                                             const dymoe_expert_fmt* __restrict__ table, int P, int E,
                                                             int tile_m, int max_tiles,
-                                                            int32_t* __restrict__ plan, unsigned* __restrict__ flags)
+                                                            int32_t* __restrict__ plan, unsigned* __restrict__ flags,
+                                                            const uint16_t* __restrict__ x, long n16,
+                                                            uint16_t* __restrict__ xh4, uint16_t* __restrict__ xh2,
+                                                            uint16_t* __restrict__ xh8)
 {
+    if (blockIdx.x > 0) {
+        const long i = (long)(blockIdx.x - 1) * kPlanThreads + threadIdx.x;
+        if (i < n16) prep_x(x, i, xh4, xh2, xh8);
+        return;
+    }
     __shared__ int32_t s_count[DYMOE_MAX_EXPERTS];
     __shared__ int32_t s_off[DYMOE_MAX_EXPERTS + 1];
     __shared__ int32_t s_tile0[DYMOE_MAX_EXPERTS + 1];       // first tile of each expert
@@ -108,6 +166,21 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     const PlanPtrs pp = plan_ptrs(plan, E, P);
     const int tid = threadIdx.x, wave = tid / kWave;
     const bool priv = E <= kPlanPrivE;
+    // (the expert indices of a batch of pairs are requested together and looked at afterwards: one pair at a time, every
+    // iteration waited a memory latency for its own index, 16 latencies per pass on the 128-expert layer)
+    constexpr int kPlanBatch = 16;
+    // up to 16 x 1024 pairs: a thread's indices stay in registers from the counting pass to the scattering pass, and are
+    // requested before the chain bits -> table entry -> its pointers
+    const bool one_pass = P <= kPlanBatch * kPlanThreads;
+    int es[kPlanBatch];
+    auto fetch = [&](int p0) {
+#pragma unroll
+        for (int u = 0; u < kPlanBatch; u++) {
+            const int p = p0 + u * kPlanThreads;
+            es[u] = (p < P) ? idx[p] : -1;
+        }
+    };
+    if (one_pass) fetch(tid);
     for (int e = tid; e < E; e += kPlanThreads) {
         s_count[e] = 0;
         int b = bits[e];
@@ -123,12 +196,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     if (priv)
         for (int i = tid; i < kPlanWaves * E; i += kPlanThreads) s_priv[i] = 0;
     __syncthreads();
-    // (the expert indices of a batch of pairs are requested together and looked at afterwards: one pair at a time, every
-    // iteration waited a memory latency for its own index, 16 latencies per pass on the 128-expert layer)
-    constexpr int kPlanBatch = 16;
-    // up to 16 x 1024 pairs: a thread's indices stay in registers from the counting pass to the scattering pass
-    const bool one_pass = P <= kPlanBatch * kPlanThreads;
-    int es[kPlanBatch];
     auto counted = [&](int e) {
         if (e < 0 || e >= E) return false;
         const int b = s_bits[e];
@@ -139,11 +206,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         return b != 0;
     };
     for (int p0 = tid; p0 < P || p0 == tid; p0 += kPlanBatch * kPlanThreads) {
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; u++) {
-            const int p = p0 + u * kPlanThreads;
-            es[u] = (p < P) ? idx[p] : -1;
-        }
+        if (!one_pass) fetch(p0);
 #pragma unroll
         for (int u = 0; u < kPlanBatch; u++)
             if (counted(es[u])) atomicAdd(priv ? &s_priv[wave * E + es[u]] : &s_count[es[u]], 1);
@@ -270,13 +333,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
     __syncthreads();
     // order inside an expert is arbitrary: every row of a tile is computed independently
     for (int p0 = tid; p0 < P || p0 == tid; p0 += kPlanBatch * kPlanThreads) {
-        if (!one_pass) {
-#pragma unroll
-            for (int u = 0; u < kPlanBatch; u++) {
-                const int p = p0 + u * kPlanThreads;
-                es[u] = (p < P) ? idx[p] : -1;
-            }
-        }
+        if (!one_pass) fetch(p0);
 #pragma unroll
         for (int u = 0; u < kPlanBatch; u++) {
             const int e = es[u];
@@ -285,58 +342,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
             pp.perm[pos] = p0 + u * kPlanThreads;
         }
     }
-}
-
-// Column order in which the code fields of a dword come out of the mask-and-or
-// extraction: inside every 8 columns (int4) 0,4,1,5,2,6,3,7; inside every 16
-// columns (int2) 0,8,1,9,...,7,15.  Inputs are packed pairs of 16-bit values.
-__device__ __forceinline__ uint4 perm8(const uint4 v)
-{
-    uint4 o;
-    o.x = (v.x & 0xffffu) | (v.z << 16);
-    o.y = (v.x >> 16) | (v.z & 0xffff0000u);
-    o.z = (v.y & 0xffffu) | (v.w << 16);
-    o.w = (v.y >> 16) | (v.w & 0xffff0000u);
-    return o;
-}
-
-__device__ __forceinline__ void perm16(const uint4 a, const uint4 b, uint4& o0, uint4& o1)
-{
-    o0.x = (a.x & 0xffffu) | (b.x << 16);
-    o0.y = (a.x >> 16) | (b.x & 0xffff0000u);
-    o0.z = (a.y & 0xffffu) | (b.y << 16);
-    o0.w = (a.y >> 16) | (b.y & 0xffff0000u);
-    o1.x = (a.z & 0xffffu) | (b.z << 16);
-    o1.y = (a.z >> 16) | (b.z & 0xffff0000u);
-    o1.z = (a.w & 0xffffu) | (b.w << 16);
-    o1.w = (a.w >> 16) | (b.w & 0xffff0000u);
-}
-
-// Three fp16 copies of the bf16 activations (exact inside fp16's normal range):
-// one in each of the column orders above and one in the natural order (int8
-// codes come out of a dword in order).  A thread converts 16 columns.
-__global__ __launch_bounds__(256) void prep_x_kernel(const uint16_t* __restrict__ x, long n16,
-                                                     uint16_t* __restrict__ xh4,
-                                                     uint16_t* __restrict__ xh2,
-                                                     uint16_t* __restrict__ xh8)
-{
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n16) return;
-    const uint4 a = reinterpret_cast<const uint4*>(x)[2 * i];
-    const uint4 b = reinterpret_cast<const uint4*>(x)[2 * i + 1];
-    uint4 ha, hb;
-    ha.x = pack_half2(bf16_lo(a.x), bf16_hi(a.x)); ha.y = pack_half2(bf16_lo(a.y), bf16_hi(a.y));
-    ha.z = pack_half2(bf16_lo(a.z), bf16_hi(a.z)); ha.w = pack_half2(bf16_lo(a.w), bf16_hi(a.w));
-    hb.x = pack_half2(bf16_lo(b.x), bf16_hi(b.x)); hb.y = pack_half2(bf16_lo(b.y), bf16_hi(b.y));
-    hb.z = pack_half2(bf16_lo(b.z), bf16_hi(b.z)); hb.w = pack_half2(bf16_lo(b.w), bf16_hi(b.w));
-    reinterpret_cast<uint4*>(xh4)[2 * i] = perm8(ha);
-    reinterpret_cast<uint4*>(xh4)[2 * i + 1] = perm8(hb);
-    uint4 o0, o1;
-    perm16(ha, hb, o0, o1);
-    reinterpret_cast<uint4*>(xh2)[2 * i] = o0;
-    reinterpret_cast<uint4*>(xh2)[2 * i + 1] = o1;
-    reinterpret_cast<uint4*>(xh8)[2 * i] = ha;
-    reinterpret_cast<uint4*>(xh8)[2 * i + 1] = hb;
 }
 
 // ----------------------------------------------------------------------------
@@ -1129,14 +1134,12 @@ int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     int32_t* plan = reinterpret_cast<int32_t*>(ws + L.plan);
     const uint16_t* xb = (const uint16_t*)x;
 
-    dymoe_launch(ctx, DYMOE_K_PLAN, plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, idx, bits, table, P, E, kGemmTileM,
-                 L.max_tiles, plan, ctx->device_flags);
+    const long n16 = (long)T * H / 16;
+    dymoe_launch(ctx, DYMOE_K_PLAN, plan_kernel, dim3((unsigned)(1 + (n16 + kPlanThreads - 1) / kPlanThreads)), dim3(kPlanThreads), 0,
+                 st, idx, bits, table, P, E, kGemmTileM, L.max_tiles, plan, ctx->device_flags, xb, n16, xh4, xh2, xh8);
+    DYMOE_HIP_LAUNCH_CHECK();
     // what the kernels after the plan take as the bit widths: the plan's copy, 0 where the table lacks the format
     const uint8_t* run_bits = reinterpret_cast<const uint8_t*>(plan_ptrs(plan, E, P).cursor);
-    DYMOE_HIP_LAUNCH_CHECK();
-    const long n16 = (long)T * H / 16;
-    hipLaunchKernelGGL(prep_x_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, xb, n16, xh4, xh2, xh8);
-    DYMOE_HIP_LAUNCH_CHECK();
     constexpr size_t kLdsBytes = kGemmLdsBytes;
     const int max_tiles = P / kGemmTileM + E;
     const int cols1 = 32 * kGmWaves, cols2 = 64 * kGmWaves;

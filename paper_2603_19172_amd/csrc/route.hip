@@ -419,20 +419,8 @@ __global__ __launch_bounds__(256) void token_norm_kernel(const uint16_t* __restr
     const int lane = threadIdx.x & (kWave - 1);
     const int t = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
     if (t >= T) return;
-    const uint16_t* row = x + (size_t)t * H;
-    float acc = 0.0f;
-    for (int col = lane * 8; col < H; col += kWave * 8) {
-        const uint4 v = *reinterpret_cast<const uint4*>(row + col);
-        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const float a = bf16_lo(u[i]), b = bf16_hi(u[i]);
-            acc = fmaf(a, a, acc);
-            acc = fmaf(b, b, acc);
-        }
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) score[t] = sqrtf(acc);
+    const float n = token_norm(x + (size_t)t * H, H, lane);
+    if (lane == 0) score[t] = n;
 }
 
 template <int TW, int NCH, int NW>

@@ -96,6 +96,16 @@ class MoELayer:
                                               self.floor_bits, self.bits.data_ptr(),
                                               self.rank.data_ptr(), st), "dymoe_assign_precision")
 
+    def rank_experts(self, x, st):
+        """S2 + S3 (token scores, importance, assignment) in one or two launches."""
+        prefill = self.phase == B.PHASE_PREFILL
+        B._check(B.lib.dymoe_rank_experts(self.ctx._h, self.phase, x.data_ptr() if prefill else None, self.H,
+                                          self.idx.data_ptr(), self.probs.data_ptr(), self.score.data_ptr(), self.T, self.E,
+                                          self.k, self.k_hh, self._nt, C.cast(self._tc, C.c_void_p),
+                                          C.cast(self._tb, C.c_void_p), self.floor_bits, self.imp.data_ptr(),
+                                          self.load.data_ptr(), self.bits.data_ptr(), self.rank.data_ptr(), st),
+                 "dymoe_rank_experts")
+
     def quantize(self, store, st):
         B._check(B.lib.dymoe_quantize_experts(self.ctx._h, store.table.data_ptr(), self.bits.data_ptr(),
                                               self.load.data_ptr(), self.E, self.H, self.F, self.group,
@@ -136,7 +146,8 @@ class MoELayer:
     def step(self, x, wg, bias, store, quantize=True, stream=None, fused_front=True):
         """The whole hot path for one batch.  quantize=False assumes the formats
         the assignment selects are already materialised in `store`.  Small decode
-        steps take the single-launch front end unless fused_front is False."""
+        steps take the single-launch front end and the others the fused ranking unless
+        fused_front is False."""
         st = B._stream(stream)
         if (fused_front and self.use_decode_step and not quantize and self.phase == B.PHASE_DECODE
                 and self.path != B.PATH_GEMM and self.layout == B.LAYOUT_ROWMAJOR
@@ -144,6 +155,9 @@ class MoELayer:
             return self.y
         if fused_front and self.phase == B.PHASE_DECODE and self.T <= B.FRONT_MAX_TOKENS:
             self.front(x, wg, bias, st)
+        elif fused_front:
+            self.route(x, wg, bias, st)
+            self.rank_experts(x, st)
         else:
             self.route(x, wg, bias, st)
             self.importance(x, st)

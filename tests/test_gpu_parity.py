@@ -951,3 +951,54 @@ def test_quantize_pack_smallest_and_odd_sizes(ctx):
     w = synth.f32_to_bf16_bits((rng.standard_normal((4, 128)) * 8000.0).astype(np.float32))
     for bits in (8, 4, 2):
         _check_quant(ctx, w, bits)
+
+
+# one workgroup up to 256 tokens of prefill (norms inside up to 64 KiB of x), three launches beyond; one workgroup for any
+# decode, 8192 probabilities at a time: sizes on both sides of each edge, tied scores, a floor
+@pytest.mark.parametrize("phase,T,H,E,k,k_hh", [
+    ("prefill", 1, 256, 8, 2, 1), ("prefill", 17, 256, 8, 2, 3), ("prefill", 64, 512, 30, 4, 5), ("prefill", 65, 512, 30, 4, 0),
+    ("prefill", 255, 128, 128, 8, 13), ("prefill", 256, 128, 1024, 8, 256), ("prefill", 257, 128, 128, 8, 13),
+    ("prefill", 1357, 64, 60, 6, 68), ("decode", 1, 64, 8, 2, 0), ("decode", 17, 64, 1000, 8, 0), ("decode", 61, 64, 128, 8, 0),
+    ("decode", 300, 64, 128, 4, 0)])
+def test_rank_experts_equals_the_separate_calls(ctx, phase, T, H, E, k, k_hh):
+    g = torch.Generator(device=DEV).manual_seed(T * 1000 + E)
+    x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
+    x[T // 2:] = x[:T - T // 2].clone()                                    # equal norms: order by token index
+    wg = (torch.randn((E, H), generator=g, device=DEV) * 0.05).bfloat16()
+    idx, w, probs = ctx.route_topk(x, wg, None, k)
+    counts, tbits = [E // 4, E // 4, E - 2 * (E // 4)], [16, 4, 2]
+    prefill = phase == "prefill"
+    ph = B.PHASE_PREFILL if prefill else B.PHASE_DECODE
+    tc, tb = (ctypes.c_int32 * 3)(*counts), (ctypes.c_uint8 * 3)(*tbits)
+
+    def buffers():
+        return (torch.full((E,), -7, dtype=torch.int32 if prefill else torch.float32, device=DEV),
+                torch.full((E,), -7, dtype=torch.int32, device=DEV), torch.full((E,), 77, dtype=torch.uint8, device=DEV),
+                torch.full((E,), -7, dtype=torch.int32, device=DEV), torch.full((T,), float("nan"), device=DEV))
+
+    st = B._stream(None)
+    a, b, c = buffers(), buffers(), buffers()
+    if prefill:
+        B._check(B.lib.dymoe_token_score_norm(ctx._h, x.data_ptr(), T, H, a[4].data_ptr(), st), "norm")
+        c[4].copy_(a[4])
+    B._check(B.lib.dymoe_expert_importance(ctx._h, ph, idx.data_ptr(), probs.data_ptr(), a[4].data_ptr(), T, E, k, k_hh,
+                                           a[0].data_ptr(), a[1].data_ptr(), st), "importance")
+    B._check(B.lib.dymoe_assign_precision(ctx._h, ph, a[0].data_ptr(), a[1].data_ptr(), E, 3, ctypes.cast(tc, ctypes.c_void_p),
+                                          ctypes.cast(tb, ctypes.c_void_p), 4, a[2].data_ptr(), a[3].data_ptr(), st), "assign")
+    for out, xp in ((b, x.data_ptr() if prefill else None), (c, None)):
+        B._check(B.lib.dymoe_rank_experts(ctx._h, ph, xp, H, idx.data_ptr(), probs.data_ptr(), out[4].data_ptr(), T, E, k, k_hh, 3,
+                                          ctypes.cast(tc, ctypes.c_void_p), ctypes.cast(tb, ctypes.c_void_p), 4, out[0].data_ptr(),
+                                          out[1].data_ptr(), out[2].data_ptr(), out[3].data_ptr(), st), "rank")
+    torch.cuda.synchronize()
+    for out in (b, c):
+        assert all(torch.equal(u, v) for u, v in zip(a[:4], out[:4]))
+        assert not prefill or torch.equal(a[4], out[4])
+    # and the separate calls against the definition
+    ref_load = torch.bincount(idx.reshape(-1).long(), minlength=E)
+    assert torch.equal(a[1].long(), ref_load)
+    if prefill:
+        heavy = torch.sort(a[4], descending=True, stable=True).indices[:k_hh]
+        assert torch.equal(a[0].long(), torch.bincount(idx[heavy].reshape(-1).long(), minlength=E))
+    else:
+        # a sum of T fp32 probabilities in token order against 64 bits: T roundings of 2^-24
+        assert torch.allclose(a[0].double(), probs.double().mean(0), rtol=(T + 1) * 2.0 ** -24, atol=0)
