@@ -19,7 +19,8 @@ namespace dymoe {
 
 constexpr int kAtThreads = 256;
 constexpr int kAtWaves = kAtThreads / kWave;
-constexpr int kAtWideFrags = 32;       // from this many 32-token fragments on (T > 992): the LDS-staged kernels
+constexpr int kAtWideFrags = 32;       // from this many 32-token fragments on (T > 992) and beyond
+constexpr long kAtNarrowFrags = 512;   // so many over all heads: the LDS-staged kernels
 
 // One lane's share of a 32-token fragment of one head (D columns): lane (ln, kb)
 // holds row ln; piece c covers columns 32 (c / 2) + 16 kb + 8 (c % 2) .. + 7, i.e.
@@ -205,17 +206,20 @@ __global__ __launch_bounds__(kAtThreads) void attn_colsum_kernel(
 }
 
 // ----------------------------------------------------------------------------
-// Long sequences: the streamed operand goes through LDS.  A workgroup owns 128
-// tokens (one 32-token fragment per wavefront, kept in registers) and all four
-// wavefronts multiply against the same streamed fragment, which the workgroup
-// fetches once with whole-row coalesced loads and parks in LDS (two buffers;
-// 16-byte chunk c of row r at chunk position c ^ (r mod chunks-per-row), so that
-// the operand reads of 16 consecutive rows fall on different banks).  A quarter
-// of the global traffic of the short-sequence kernels, and no merge between
-// wavefronts: each owns its tokens' statistics or sums outright.
+// Long sequences: the streamed operand goes through LDS.  A workgroup owns 128 tokens (one 32-token fragment per
+// wavefront, kept in registers) and all four wavefronts multiply against the same streamed tokens, 64 at a time, which the
+// workgroup fetches once with whole-row coalesced loads, one stage ahead, and parks in LDS (two buffers; 16-byte chunk c
+// of row r at chunk position c ^ (r mod chunks-per-row), so that the operand reads of 16 consecutive rows fall on
+// different banks).  No merge between wavefronts: each owns its tokens' statistics or sums outright.
+// Bound: per 32 x 32 logits at d = 128 256 cycles of matrix instructions and about as many each of vector work and of
+// exponentials, overlapped between a SIMD's wavefronts.  4096 tokens, 32 / 8 heads x 128, both passes: causal 292 -> 209 us,
+// unmasked 392 -> 358 us since two logits tiles are worked on side by side per barrier, the register-held fragment
+// is waited for before the loop, and blocks are dealt out by length; d = 64 causal 247 -> 139 us.
+constexpr int kAtStageFrags = 2;
+
 template <int D>
 struct AtStage {
-    static constexpr int kPerThread = 32 * (D / 8) / kAtThreads;      // 2 (D = 128) or 1 (D = 64)
+    static constexpr int kPerThread = kAtStageFrags * 32 * (D / 8) / kAtThreads;      // 4 (D = 128) or 2 (D = 64)
     uint4 v[kPerThread];
 };
 
@@ -230,6 +234,7 @@ __device__ __forceinline__ void stage_fetch(const uint16_t* __restrict__ head_ba
         const int r = at / CH, c = at % CH;
         st.v[i] = load_global<uint4>(head_base + (long)min(row0 + r, T - 1) * row_stride + c * 8);
     }
+    __builtin_amdgcn_sched_barrier(0);      // the loads leave here, not where they are stored to LDS
 }
 
 template <int D>
@@ -244,79 +249,134 @@ __device__ __forceinline__ void stage_store(char* buf, const AtStage<D>& st)
     }
 }
 
-// the lane's share of the staged fragment, in the piece order of load_frag
+// The fragment has arrived from here on.  Without this the compiler waits for it inside the loop, and as loads return in
+// order that is a wait for the stage fetched in the same trip.
 template <int D>
-__device__ __forceinline__ void frag_from_lds(const char* buf, int ln, int kb, AtFrag<D>& f)
+__device__ __forceinline__ void settle(AtFrag<D>& f)
 {
+#pragma unroll
+    for (int c = 0; c < D / 16; c++) asm volatile("" : "+v"(f.c[c].x), "+v"(f.c[c].y), "+v"(f.c[c].z), "+v"(f.c[c].w));
+}
+
+// Workgroup -> (block of four fragments, head) for the two kernels below.  An XCD gets whole heads, as above.  Under the
+// causal mask a block's work grows (pass 1) or shrinks (pass 2) with its position, and all workgroups of 4096 tokens x 32
+// heads are on the chip at once: dealt out head by head, a compute unit (every 32nd workgroup of its XCD) got the same
+// position of every head, the last one four of the longest blocks.  So the XCD's blocks are ordered by length over all its
+// heads and dealt out to and fro in rounds of 32.
+__device__ __forceinline__ void block_and_head(int nblk, int n_heads, int causal, int& blk, int& head)
+{
+    const int lin = blockIdx.x;
+    if (n_heads % 8 == 0) {
+        const int per = n_heads >> 3, xcd = lin & 7, j = lin >> 3;
+        const int round = j >> 5, in_round = min(32, per * nblk - 32 * round);
+        const int at = 32 * round + ((causal && (round & 1)) ? in_round - 1 - (j & 31) : (j & 31));
+        blk = at / per;
+        head = xcd * per + (at - blk * per);
+    } else {
+        head = lin / nblk;
+        blk = lin - head * nblk;
+        if (causal && (head & 1)) blk = nblk - 1 - blk;
+    }
+}
+
+// The stage's two logits tiles against one register-held fragment, side by side: sixteen matrix instructions in two
+// chains, so that one chain's latency passes behind the other.  KEYS_STAGED: the staged rows are the keys.
+template <int D, bool KEYS_STAGED>
+__device__ __forceinline__ void stage_tiles(const char* buf, int ln, int kb, const AtFrag<D>& own, float16_t (&acc)[2])
+{
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[s][i] = 0.0f;
     constexpr int CH = D / 8;
 #pragma unroll
     for (int c = 0; c < D / 16; c++) {
         const int ch = (c >> 1) * 4 + kb * 2 + (c & 1);
-        f.c[c] = *reinterpret_cast<const uint4*>(buf + ln * (D * 2) + ((ch ^ (ln & (CH - 1))) << 4));
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+            const bf16x8_t staged = __builtin_bit_cast(
+                bf16x8_t, *reinterpret_cast<const uint4*>(buf + s * (32 * D * 2) + ln * (D * 2) + ((ch ^ (ln & (CH - 1))) << 4)));
+            const bf16x8_t mine = __builtin_bit_cast(bf16x8_t, own.c[c]);
+            acc[s] = KEYS_STAGED ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(staged, mine, acc[s], 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(mine, staged, acc[s], 0, 0, 0);
+        }
     }
 }
 
-// Pass 1, long sequences: wavefront w owns queries 128 blk + 32 w .. + 31; keys stream through LDS.
+// Pass 1, long sequences: wavefront w owns the query fragment 4 blk + w; keys stream through LDS.
 template <int D>
-__global__ __launch_bounds__(kAtThreads) void attn_rowstats_wide_kernel(
+__global__ __launch_bounds__(kAtThreads, 3) void attn_rowstats_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, float2* __restrict__ stats)
 {
-    __shared__ __attribute__((aligned(16))) char s_buf[2][32 * D * 2];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ __attribute__((aligned(16))) char s_buf[2][kAtStageFrags * 32 * D * 2];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, kb = lane >> 5;
     const int nfrag = (T + 31) >> 5;
     int blk, h;
-    fragment_and_head((nfrag + 3) >> 2, n_heads, blk, h);
+    block_and_head((nfrag + 3) >> 2, n_heads, causal, blk, h);
     const long q_stride = (long)n_heads * D, k_stride = (long)(n_heads / group) * D;
     const uint16_t* qh = q + (long)h * D;
     const uint16_t* kh = k + (long)(h / group) * D;
     const int qf = 4 * blk + wave;
     const int query = qf * 32 + ln;
-    AtFrag<D> fq, fk;
+    AtFrag<D> fq;
     load_frag<D>(qh, q_stride, min(query, T - 1), kb, fq);
     const int kf_last = causal ? min(4 * blk + 3, nfrag - 1) : nfrag - 1;
+    const int mine_last = (qf >= nfrag) ? -1 : causal ? qf : kf_last;        // the last fragment this wavefront's queries see
+    // the fragments before this one need no mask: all but the diagonal and a ragged last one
+    const int plain_end = min(causal ? qf : nfrag, T >> 5);
     AtStage<D> st;
     stage_fetch<D>(kh, k_stride, 0, T, st);
     stage_store<D>(s_buf[0], st);
     __syncthreads();
+    settle<D>(fq);
     float m = kMasked, l = 0.0f;
-    for (int kf = 0; kf <= kf_last; kf++) {
-        const bool more = kf < kf_last;                         // the same in every thread
-        if (more) stage_fetch<D>(kh, k_stride, (kf + 1) * 32, T, st);
-        if (qf < nfrag && (!causal || kf <= qf)) {              // the same in every lane of the wavefront
-            frag_from_lds<D>(s_buf[kf & 1], ln, kb, fk);
-            const float16_t acc = logits_tile<D>(fk, fq);
-            if (kf * 32 + 31 < T && (!causal || kf < qf)) {
-                // nothing to mask (the rule for all but the diagonal and the last fragment): the scale is positive,
-                // so the maximum is taken over the raw logits and the scale rides in the exponent's multiply-add
-                float raw = acc[0];
+    for (int kf0 = 0, buf = 0; kf0 <= kf_last; kf0 += kAtStageFrags, buf ^= 1) {
+        const bool more = kf0 + kAtStageFrags <= kf_last;       // the same in every thread
+        if (more) stage_fetch<D>(kh, k_stride, (kf0 + kAtStageFrags) * 32, T, st);
+        if (kf0 <= mine_last) {                                 // the same in every lane of the wavefront
+            float16_t acc[2];
+            stage_tiles<D, true>(s_buf[buf], ln, kb, fq, acc);
+            if (kf0 + 1 < plain_end) {
+                // the scale is positive, so the maximum is taken over the raw logits and the scale rides in the exponent's
+                // multiply-add
+                float raw0 = acc[0][0], raw1 = acc[1][0];
 #pragma unroll
-                for (int i = 1; i < 16; i++) raw = fmaxf(raw, acc[i]);
-                const float mx = fmaxf(m, raw * scale_log2);
-                float add = 0.0f;
-#pragma unroll
-                for (int i = 0; i < 16; i++) add += __builtin_amdgcn_exp2f(fmaf(acc[i], scale_log2, -mx));
-                l = l * __builtin_amdgcn_exp2f(m - mx) + add;
-                m = mx;
-            } else {
-                float sv[16];
-                float mx = m;
+                for (int i = 1; i < 16; i++) {
+                    raw0 = fmaxf(raw0, acc[0][i]);
+                    raw1 = fmaxf(raw1, acc[1][i]);
+                }
+                const float mx = fmaxf(m, fmaxf(raw0, raw1) * scale_log2);
+                float add[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int i = 0; i < 16; i++) {
-                    const int key = tile_key(kf, kb, i);
-                    const bool ok = key < T && (!causal || key <= query);
-                    sv[i] = ok ? acc[i] * scale_log2 : kMasked;
-                    mx = fmaxf(mx, sv[i]);
+                    add[i & 1] += __builtin_amdgcn_exp2f(fmaf(acc[0][i], scale_log2, -mx));
+                    add[2 + (i & 1)] += __builtin_amdgcn_exp2f(fmaf(acc[1][i], scale_log2, -mx));
                 }
-                float add = 0.0f;
-#pragma unroll
-                for (int i = 0; i < 16; i++) add += (sv[i] > 0.5f * kMasked) ? __builtin_amdgcn_exp2f(sv[i] - mx) : 0.0f;
-                l = l * __builtin_amdgcn_exp2f(m - mx) + add;
+                l = l * __builtin_amdgcn_exp2f(m - mx) + ((add[0] + add[1]) + (add[2] + add[3]));
                 m = mx;
+            } else {
+#pragma unroll
+                for (int s = 0; s < kAtStageFrags; s++) {
+                    float sv[16];
+                    float mx = m;
+#pragma unroll
+                    for (int i = 0; i < 16; i++) {
+                        const int key = tile_key(kf0 + s, kb, i);
+                        const bool ok = key < T && (!causal || key <= query);
+                        sv[i] = ok ? acc[s][i] * scale_log2 : kMasked;
+                        mx = fmaxf(mx, sv[i]);
+                    }
+                    float add = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < 16; i++) add += (sv[i] > 0.5f * kMasked) ? __builtin_amdgcn_exp2f(sv[i] - mx) : 0.0f;
+                    l = l * __builtin_amdgcn_exp2f(m - mx) + add;
+                    m = mx;
+                }
             }
         }
-        if (more) stage_store<D>(s_buf[(kf + 1) & 1], st);
+        if (more) stage_store<D>(s_buf[buf ^ 1], st);
         __syncthreads();
     }
     const float m2 = __shfl_xor(m, 32, kWave), l2 = __shfl_xor(l, 32, kWave);
@@ -326,55 +386,73 @@ __global__ __launch_bounds__(kAtThreads) void attn_rowstats_wide_kernel(
     if (kb == 0 && query < T) stats[(long)h * T + query] = make_float2(M + __builtin_amdgcn_logf(L), 0.0f);
 }
 
-// Pass 2, long sequences: wavefront w owns keys 128 blk + 32 w .. + 31; queries stream through LDS.
+// Pass 2, long sequences: wavefront w owns the key fragment 4 blk + w; queries stream through LDS.
 template <int D>
-__global__ __launch_bounds__(kAtThreads) void attn_colsum_wide_kernel(
+__global__ __launch_bounds__(kAtThreads, 3) void attn_colsum_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, const float2* __restrict__ stats, float* __restrict__ partial)
 {
-    __shared__ __attribute__((aligned(16))) char s_buf[2][32 * D * 2];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ __attribute__((aligned(16))) char s_buf[2][kAtStageFrags * 32 * D * 2];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, kb = lane >> 5;
     const int nfrag = (T + 31) >> 5;
     int blk, h;
-    fragment_and_head((nfrag + 3) >> 2, n_heads, blk, h);
+    block_and_head((nfrag + 3) >> 2, n_heads, causal, blk, h);
     const long q_stride = (long)n_heads * D, k_stride = (long)(n_heads / group) * D;
     const uint16_t* qh = q + (long)h * D;
     const uint16_t* kh = k + (long)(h / group) * D;
     const float2* sh = stats + (long)h * T;
     const int kf = 4 * blk + wave;
-    AtFrag<D> fk, fq;
+    AtFrag<D> fk;
     load_frag<D>(kh, k_stride, min(kf * 32 + ln, T - 1), kb, fk);
     const int qf_first = causal ? 4 * blk : 0;
     AtStage<D> st;
+    float next[kAtStageFrags], shift[kAtStageFrags];
+    auto shifts = [&](int qf) {
+#pragma unroll
+        for (int s = 0; s < kAtStageFrags; s++) next[s] = -sh[min((qf + s) * 32 + ln, T - 1)].x;
+    };
+    shifts(qf_first);
     stage_fetch<D>(qh, q_stride, qf_first * 32, T, st);
     stage_store<D>(s_buf[0], st);
     __syncthreads();
+    settle<D>(fk);
     float col[16];
 #pragma unroll
     for (int i = 0; i < 16; i++) col[i] = 0.0f;
-    for (int qf = qf_first; qf < nfrag; qf++) {
-        const bool more = qf + 1 < nfrag;
-        if (more) stage_fetch<D>(qh, q_stride, (qf + 1) * 32, T, st);
-        if (kf < nfrag && (!causal || qf >= kf)) {
-            const int query = qf * 32 + ln;
-            const float shift = -sh[min(query, T - 1)].x;
-            frag_from_lds<D>(s_buf[(qf - qf_first) & 1], ln, kb, fq);
-            const float16_t acc = logits_tile<D>(fk, fq);
-            if (qf * 32 + 31 < T && kf * 32 + 31 < T && (!causal || kf < qf)) {
+    for (int qf0 = qf_first, buf = 0; qf0 < nfrag; qf0 += kAtStageFrags, buf ^= 1) {
+        const bool more = qf0 + kAtStageFrags < nfrag;
 #pragma unroll
-                for (int i = 0; i < 16; i++) col[i] += __builtin_amdgcn_exp2f(fmaf(acc[i], scale_log2, shift));
-            } else {
+        for (int s = 0; s < kAtStageFrags; s++) shift[s] = next[s];
+        if (more) {
+            shifts(qf0 + kAtStageFrags);
+            stage_fetch<D>(qh, q_stride, (qf0 + kAtStageFrags) * 32, T, st);
+        }
+        if (kf < nfrag && (!causal || qf0 + 1 >= kf)) {         // the same in every lane of the wavefront
+            float16_t acc[2];
+            stage_tiles<D, false>(s_buf[buf], ln, kb, fk, acc);
+            if ((qf0 + 2) * 32 <= T && kf * 32 + 32 <= T && (!causal || kf < qf0)) {
 #pragma unroll
                 for (int i = 0; i < 16; i++) {
-                    const int key = tile_key(kf, kb, i);
-                    const bool ok = query < T && key < T && (!causal || key <= query);
-                    const float p = __builtin_amdgcn_exp2f(fmaf(acc[i], scale_log2, shift));
-                    col[i] += ok ? p : 0.0f;
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(acc[0][i], scale_log2, shift[0]));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(acc[1][i], scale_log2, shift[1]));
+                    col[i] += p0 + p1;
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < kAtStageFrags; s++) {
+                    const int query = (qf0 + s) * 32 + ln;
+#pragma unroll
+                    for (int i = 0; i < 16; i++) {
+                        const int key = tile_key(kf, kb, i);
+                        const bool ok = query < T && key < T && (!causal || key <= query);
+                        const float p = __builtin_amdgcn_exp2f(fmaf(acc[s][i], scale_log2, shift[s]));
+                        col[i] += ok ? p : 0.0f;
+                    }
                 }
             }
         }
-        if (more) stage_store<D>(s_buf[(qf + 1 - qf_first) & 1], st);
+        if (more) stage_store<D>(s_buf[buf ^ 1], st);
         __syncthreads();
     }
 #pragma unroll
@@ -440,29 +518,31 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     const float s = (scale > 0.0f) ? scale : 1.0f / sqrtf((float)head_dim);
     const float scale_log2 = s * 1.44269504088896340736f;
     const int nfrag = (T + 31) / 32;
-    // short sequences: a workgroup per 32-token fragment (many workgroups, operands straight from global memory);
-    // long ones: a workgroup per 128 tokens with the streamed operand shared through LDS
-    const bool wide = nfrag >= dymoe::kAtWideFrags;
-    const dim3 grid((unsigned)(wide ? (nfrag + 3) / 4 : nfrag), (unsigned)n_heads);
+    // Few fragments over all heads: a workgroup per 32-token fragment, its wavefronts sharing the streamed tokens (many
+    // workgroups, operands straight from global memory).  Else a workgroup per 128 tokens with the streamed operand in LDS:
+    // per logits tile several times cheaper, but a serial chain of all the tokens, 1 us per 32 of them, however few
+    // heads there are.  Both passes, us, narrow / wide at d = 128, causal: 500 tokens x 32 heads 33 / 34, 1000 x 16 43 / 44,
+    // 1000 x 32 77 / 49, 2500 x 4 72 / 88, 2500 x 16 119 / 93, 4096 x 4 124 / 133, 4096 x 8 158 / 133, 4096 x 32 548 / 209.
+    // (Below 32 fragments the narrow pair stays for every number of heads: its four partial sums per key round less.)
+    const bool wide = nfrag >= dymoe::kAtWideFrags && (long)nfrag * n_heads > dymoe::kAtNarrowFrags;
+    const dim3 grid = wide ? dim3((unsigned)((nfrag + 3) / 4) * (unsigned)n_heads) : dim3((unsigned)nfrag, (unsigned)n_heads);
+#define DYMOE_ATTN_PAIR(STATS_, COLSUM_)                                                                               \
+    do {                                                                                                               \
+        dymoe_launch(ctx, DYMOE_K_ATTN_STATS, STATS_, grid, dim3(dymoe::kAtThreads), 0, st, qb, kbp, T, n_heads, group,  \
+                     scale_log2, causal, stats);                                                                       \
+        DYMOE_HIP_LAUNCH_CHECK();                                                                                      \
+        dymoe_launch(ctx, DYMOE_K_ATTN_COLSUM, COLSUM_, grid, dim3(dymoe::kAtThreads), 0, st, qb, kbp, T, n_heads, group, \
+                     scale_log2, causal, (const float2*)stats, partial);                                               \
+    } while (0)
 #define DYMOE_ATTN_LAUNCH(D_)                                                                                          \
     do {                                                                                                               \
-        if (wide) {                                                                                                    \
-            dymoe_launch(ctx, DYMOE_K_ATTN_STATS, dymoe::attn_rowstats_wide_kernel<D_>, grid, dim3(dymoe::kAtThreads), 0, st, \
-                         qb, kbp, T, n_heads, group, scale_log2, causal, stats);                                       \
-            DYMOE_HIP_LAUNCH_CHECK();                                                                                  \
-            dymoe_launch(ctx, DYMOE_K_ATTN_COLSUM, dymoe::attn_colsum_wide_kernel<D_>, grid, dim3(dymoe::kAtThreads), 0, st, \
-                         qb, kbp, T, n_heads, group, scale_log2, causal, (const float2*)stats, partial);               \
-        } else {                                                                                                       \
-            dymoe_launch(ctx, DYMOE_K_ATTN_STATS, dymoe::attn_rowstats_kernel<D_>, grid, dim3(dymoe::kAtThreads), 0, st,  \
-                         qb, kbp, T, n_heads, group, scale_log2, causal, stats);                                       \
-            DYMOE_HIP_LAUNCH_CHECK();                                                                                  \
-            dymoe_launch(ctx, DYMOE_K_ATTN_COLSUM, dymoe::attn_colsum_kernel<D_>, grid, dim3(dymoe::kAtThreads), 0, st,   \
-                         qb, kbp, T, n_heads, group, scale_log2, causal, (const float2*)stats, partial);               \
-        }                                                                                                              \
+        if (wide) DYMOE_ATTN_PAIR(dymoe::attn_rowstats_wide_kernel<D_>, dymoe::attn_colsum_wide_kernel<D_>);           \
+        else DYMOE_ATTN_PAIR(dymoe::attn_rowstats_kernel<D_>, dymoe::attn_colsum_kernel<D_>);                          \
     } while (0)
     if (head_dim == 64) DYMOE_ATTN_LAUNCH(64);
     else DYMOE_ATTN_LAUNCH(128);
 #undef DYMOE_ATTN_LAUNCH
+#undef DYMOE_ATTN_PAIR
     DYMOE_HIP_LAUNCH_CHECK();
     hipLaunchKernelGGL(dymoe::attn_score_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, st,
                        (const float*)partial, T, n_heads, 1.0f / ((float)n_heads * (float)T), score);

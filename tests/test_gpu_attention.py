@@ -52,6 +52,19 @@ def test_attention_score_matches_the_oracle(ctx, T, Hh, Hkv, d, causal):
     assert abs(got.sum() - 1.0) < 1e-5                      # every query hands out one unit of attention
 
 
+# the LDS-staged kernels need 32 fragments and more than 512 over all heads: both sides of that line, 64-token stages that
+# end whole, half and ragged, head counts that the XCD mapping divides and does not, rounds of blocks that are not whole
+@pytest.mark.parametrize("T,Hh,Hkv,d", [(1024, 16, 4, 128), (1025, 16, 4, 128), (1057, 17, 1, 64), (1088, 24, 6, 64),
+                                        (1120, 20, 5, 128), (2111, 8, 2, 128)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
+    cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=160 + T)
+    q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, d, boost=1.0)
+    ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+    got = _run(ctx, q, k, causal)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
 def test_attention_score_explicit_scale_and_determinism(ctx):
     cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=200, k_hh=10, config_id=71)
     q, k, _ = synth.attention_inputs(cfg, 4, 4, 64)
