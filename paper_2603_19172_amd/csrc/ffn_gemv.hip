@@ -194,7 +194,7 @@ __device__ __forceinline__ bool mat_present(const ExpertMat& m, int b)
 
 // what one lane loads of one row: NSEG segments starting at column seg0 * 2048
 template <int BITS, int NSEG> struct RowRegs;
-template <int NSEG> struct RowRegs<16, NSEG> { uint4 c[NSEG][4]; };
+template <int NSEG> struct RowRegs<16, NSEG> { uint4 c[NSEG][4]; };      // (the first NCH of 4, see load_row)
 template <int NSEG> struct RowRegs<4, NSEG> { uint4 c[NSEG]; uint16_t sz[NSEG]; };
 template <int NSEG> struct RowRegs<2, NSEG> { uint2 c[NSEG]; uint16_t sz[NSEG]; };
 template <int NSEG> struct RowRegs<8, NSEG> { uint4 c[NSEG][2]; uint16_t sz[NSEG]; };
@@ -203,7 +203,8 @@ template <int NSEG> struct RowRegs<8, NSEG> { uint4 c[NSEG][2]; uint16_t sz[NSEG
 // re-read its tail: finite weights against zero activations add nothing.
 // Weights are read once per step: where a load instruction covers whole cache
 // lines (consecutive lanes, consecutive 16 or 8 bytes) it is marked non-temporal.
-template <int BITS, int NSEG>
+// NCH: how many of a bf16 segment's four 512-column chunks the rows reach into.
+template <int BITS, int NSEG, int NCH = 4>
 __device__ __forceinline__ void load_row(const ExpertMat& m, long row, int K, int seg0, int lane,
                                          RowRegs<BITS, NSEG>& rr)
 {
@@ -212,7 +213,7 @@ __device__ __forceinline__ void load_row(const ExpertMat& m, long row, int K, in
 #pragma unroll
         for (int s = 0; s < NSEG; s++)
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
+            for (int j = 0; j < NCH; j++) {
                 const int col = min((seg0 + s) * kSeg + (j * kWave + lane) * 8, K - 8);
                 rr.c[s][j] = load_global_nt<uint4>(base + col);
             }
@@ -506,16 +507,16 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
 
 // ---------------------------------------------------------------- phase 2
 // y[t,j] = sum_slot w[t,slot] * sum_f W2_e[j,f] * h[p,f],  p = t*k + slot, e = idx[p]
-// A workgroup owns kP2Rows consecutive rows j of one token, over every slot and every 2048-column segment of F:
+// A workgroup owns ROWS consecutive rows j of one token, over every slot and every 2048-column segment of F:
 // the (slot, segment) units are dealt out to its wavefronts.  A wavefront keeps the activations of its unit in
 // registers, streams the unit's piece of every row and adds gate * partial into per-lane, per-row accumulators;
 // only after its last unit are the accumulators summed over the lanes (once per row instead of once per row and
 // segment), then over the wavefronts through LDS in a fixed order, and y is written: no partial sums in memory
 // and no separate combining launch.
 
-template <int BITS> struct Phase2Rows { static constexpr int R = (BITS == 16 || BITS == 8) ? 4 : 8; };
+// rows a wavefront requests at a time: two batches at least
+template <int BITS, int ROWS> struct Phase2Rows { static constexpr int R = (ROWS == 4) ? 2 : (BITS == 16 || BITS == 8 || ROWS == 8) ? 4 : 8; };
 
-constexpr int kP2Rows = 16;
 constexpr int kP2MaxWaves = 8;
 
 // fp32 intermediate against bf16 weights
@@ -523,11 +524,12 @@ struct LaneH {
     float v[4][8];
 };
 
+template <int NCH>
 __device__ __forceinline__ float dot_row_h(const RowRegs<16, 1>& rr, const LaneH& lh)
 {
     float acc = 0.0f;
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
+    for (int c = 0; c < NCH; c++) {
         const uint4 u = rr.c[0][c];
         acc = fmaf(bf16_lo(u.x), lh.v[c][0], acc); acc = fmaf(bf16_hi(u.x), lh.v[c][1], acc);
         acc = fmaf(bf16_lo(u.y), lh.v[c][2], acc); acc = fmaf(bf16_hi(u.y), lh.v[c][3], acc);
@@ -537,19 +539,19 @@ __device__ __forceinline__ float dot_row_h(const RowRegs<16, 1>& rr, const LaneH
     return acc;
 }
 
-// one unit: segment `seg` of rows j_begin .. j_begin + kP2Rows - 1 (clamped to the last row H - 1)
-template <int BITS, typename XT, typename DotFn>
+// one unit: segment `seg` of rows j_begin .. j_begin + ROWS - 1 (clamped to the last row H - 1)
+template <int BITS, int ROWS, int NCH, typename XT, typename DotFn>
 __device__ __forceinline__ void phase2_unit(const ExpertMat& m2, int F, int seg, int j_begin, int H,
-                                            float gate, float (&tot)[kP2Rows], const XT& lx, DotFn dot)
+                                            float gate, float (&tot)[ROWS], const XT& lx, DotFn dot)
 {
-    constexpr int R = Phase2Rows<BITS>::R;
-    constexpr int NB = kP2Rows / R;                 // 4 or 2 batches of rows
+    constexpr int R = Phase2Rows<BITS, ROWS>::R;
+    constexpr int NB = ROWS / R;                 // 4 or 2 batches of rows
     static_assert(NB % 2 == 0, "batches come in pairs");
     const int lane = threadIdx.x & (kWave - 1);
     RowRegs<BITS, 1> ra[R], rb[R];                  // used in turn, as in phase 1
     auto fetch = [&](RowRegs<BITS, 1>(&dst)[R], int j0) {
 #pragma unroll
-        for (int i = 0; i < R; i++) load_row<BITS, 1>(m2, min(j0 + i, H - 1), F, seg, lane, dst[i]);
+        for (int i = 0; i < R; i++) load_row<BITS, 1, NCH>(m2, min(j0 + i, H - 1), F, seg, lane, dst[i]);
     };
     fetch(ra, j_begin);
 #pragma unroll
@@ -566,13 +568,13 @@ __device__ __forceinline__ void phase2_unit(const ExpertMat& m2, int F, int seg,
 // Two units of narrow formats (int4, int2) side by side: a wavefront's start-up chain (pair -> expert -> bit width ->
 // table entry -> activations -> first rows) is a string of dependent latencies, and with 16 rows of int4 or int2
 // there is little streaming to hide the second unit's chain behind.  Taken together, both chains run at once.
-template <int BA, int BB>
+template <int BA, int BB, int ROWS>
 __device__ __forceinline__ void phase2_two_units(const ExpertMat& ma, const ExpertMat& mb, int F, int sa, int sb,
                                                  int j_begin, int H, float ga, float gb,
-                                                 float (&tot)[kP2Rows], const LaneX (&la)[1], const LaneX (&lb)[1])
+                                                 float (&tot)[ROWS], const LaneX (&la)[1], const LaneX (&lb)[1])
 {
-    constexpr int R = (BA == 2 && BB == 2) ? 8 : 4;
-    constexpr int NB = kP2Rows / R;
+    constexpr int R = (ROWS == 4) ? 2 : (BA == 2 && BB == 2 && ROWS > 8) ? 8 : 4;
+    constexpr int NB = ROWS / R;
     static_assert(NB % 2 == 0, "batches come in pairs");
     const int lane = threadIdx.x & (kWave - 1);
     RowRegs<BA, 1> a0[R], a1[R];
@@ -602,20 +604,21 @@ __device__ __forceinline__ void phase2_two_units(const ExpertMat& ma, const Expe
     }
 }
 
+template <int ROWS, int NCH>
 __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
     const float* __restrict__ hbuf, const int32_t* __restrict__ idx, const float* __restrict__ w,
     const uint8_t* __restrict__ bits, const dymoe_expert_fmt* __restrict__ table, int H, int F,
     int E, int k, int nseg, int out_dtype, void* __restrict__ y, unsigned* __restrict__ flags)
 {
-    __shared__ float s_red[kP2MaxWaves][kP2Rows];
+    __shared__ float s_red[kP2MaxWaves][ROWS];
     const int t = blockIdx.y;
-    const int j_begin = blockIdx.x * kP2Rows;
+    const int j_begin = blockIdx.x * ROWS;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int nwaves = blockDim.x / kWave;
-    float tot[kP2Rows];
+    float tot[ROWS];
 #pragma unroll
-    for (int i = 0; i < kP2Rows; i++) tot[i] = 0.0f;
+    for (int i = 0; i < ROWS; i++) tot[i] = 0.0f;
     const int units = k * nseg;
     const int rounds = (units + nwaves - 1) / nwaves;
     // odd wavefronts take their units in reverse: the slots of a token differ in format (the later, the narrower),
@@ -661,7 +664,7 @@ __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
             if (!mat_present(m2, 16)) return missing();
             LaneH lh;
 #pragma unroll
-            for (int c = 0; c < 4; c++) {
+            for (int c = 0; c < NCH; c++) {
                 const int col = s * kSeg + (c * kWave + lane) * 8;
 #pragma unroll
                 for (int i = 0; i < 8; i++) lh.v[c][i] = 0.0f;
@@ -672,8 +675,8 @@ __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
                     lh.v[c][4] = hi.x; lh.v[c][5] = hi.y; lh.v[c][6] = hi.z; lh.v[c][7] = hi.w;
                 }
             }
-            phase2_unit<16>(m2, F, s, j_begin, H, gate, tot, lh,
-                            [](const RowRegs<16, 1>& rr, const LaneH& l) { return dot_row_h(rr, l); });
+            phase2_unit<16, ROWS, NCH>(m2, F, s, j_begin, H, gate, tot, lh,
+                            [](const RowRegs<16, 1>& rr, const LaneH& l) { return dot_row_h<NCH>(rr, l); });
         } else {
             const ExpertMat m2 = (b == 8) ? pick_mat(ex, 2, 8) : (b == 4) ? pick_mat(ex, 2, 4) : pick_mat(ex, 2, 2);
             if (!mat_present(m2, b)) return missing();
@@ -682,15 +685,15 @@ __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
             LaneX lx[1];
             if (b == 8) {
                 arrange_lane_x<8>(v, lx[0]);
-                phase2_unit<8>(m2, F, s, j_begin, H, gate, tot, lx,
+                phase2_unit<8, ROWS, 4>(m2, F, s, j_begin, H, gate, tot, lx,
                                [](const RowRegs<8, 1>& rr, const LaneX (&l)[1]) { return dot_row_q<8, 1>(rr, l); });
             } else if (b == 4) {
                 arrange_lane_x<4>(v, lx[0]);
-                phase2_unit<4>(m2, F, s, j_begin, H, gate, tot, lx,
+                phase2_unit<4, ROWS, 4>(m2, F, s, j_begin, H, gate, tot, lx,
                                [](const RowRegs<4, 1>& rr, const LaneX (&l)[1]) { return dot_row_q<4, 1>(rr, l); });
             } else {
                 arrange_lane_x<2>(v, lx[0]);
-                phase2_unit<2>(m2, F, s, j_begin, H, gate, tot, lx,
+                phase2_unit<2, ROWS, 4>(m2, F, s, j_begin, H, gate, tot, lx,
                                [](const RowRegs<2, 1>& rr, const LaneX (&l)[1]) { return dot_row_q<2, 1>(rr, l); });
             }
         }
@@ -720,13 +723,13 @@ __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
                 else arrange_lane_x<2>(v, lb[0]);
             }
             if (ua.b == 4 && ub.b == 4)
-                phase2_two_units<4, 4>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
+                phase2_two_units<4, 4, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
             else if (ua.b == 4)
-                phase2_two_units<4, 2>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
+                phase2_two_units<4, 2, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
             else if (ub.b == 4)
-                phase2_two_units<2, 4>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
+                phase2_two_units<2, 4, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
             else
-                phase2_two_units<2, 2>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
+                phase2_two_units<2, 2, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
         } else {
             if (ua.valid) one_unit(ua);
             if (ub.valid) one_unit(ub);
@@ -735,14 +738,14 @@ __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
     // lanes, then wavefronts (in wavefront order: the result does not depend on timing)
     float o = 0.0f;
 #pragma unroll
-    for (int i = 0; i < kP2Rows; i++) {
+    for (int i = 0; i < ROWS; i++) {
         const float r = wave_sum_dpp(tot[i]);
         if (lane == i) o = r;
     }
-    if (lane < kP2Rows) s_red[wave][lane] = o;
+    if (lane < ROWS) s_red[wave][lane] = o;
     __syncthreads();
     const int j = j_begin + (int)threadIdx.x;
-    if (threadIdx.x < kP2Rows && j < H) {
+    if (threadIdx.x < ROWS && j < H) {
         float acc = 0.0f;
         for (int wv = 0; wv < nwaves; wv++) acc += s_red[wv][threadIdx.x];
         const long i = (long)t * H + j;
@@ -773,9 +776,20 @@ static int phase2_launch(dymoe_ctx* ctx, const float* hbuf, const int32_t* idx, 
         const int rounds = (units + nwaves - 1) / nwaves;
         while (nwaves > 1 && (units + nwaves - 2) / (nwaves - 1) == rounds) nwaves--;
     }
-    const dim3 g2((unsigned)((H + kP2Rows - 1) / kP2Rows), (unsigned)T);
-    dymoe_launch(ctx, DYMOE_K_GEMV_PHASE2, gemv_phase2_kernel, g2, dim3((unsigned)(nwaves * kWave)), 0, st, hbuf, idx, w,
-                 bits, table, H, F, E, k, nseg2, out_dtype, y, ctx->device_flags);
+    // 16 rows per workgroup, fewer while the workgroups then still find a compute unit each: more of them on a unit only
+    // repeat the start-up chain.  One token, us with 16 / 8 / 4 rows: H = 4096, F = 14336, int4 18 / 23 / -; 2048 x 768, eight
+    // experts 8.9 / 7.0 / 8.5; 1024 x 3072 9.2 / 7.0 / 5.7; 512 x 1024 8.5 / 6.3 / 5.0; two tokens of 2048 x 768 12.3 / 14.6 / 18.6.
+    int rows = 16;
+    while (rows > 4 && (long)T * ((H + rows / 2 - 1) / (rows / 2)) <= ctx->num_cu) rows /= 2;
+    const dim3 g2((unsigned)((H + rows - 1) / rows), (unsigned)T), block((unsigned)(nwaves * kWave));
+    auto go = [&](auto kernel) {
+        dymoe_launch(ctx, DYMOE_K_GEMV_PHASE2, kernel, g2, block, 0, st, hbuf, idx, w, bits, table, H, F, E, k, nseg2, out_dtype, y,
+                     ctx->device_flags);
+    };
+    // a segment's bf16 rows are four chunks of 512 columns: rows of at most 1024 columns need no more than two (2048 x 768,
+    // eight bf16 experts: 12.4 us with all four, lanes past the end re-reading the tail, 10.2 with two)
+    if (F <= kSeg / 2) rows == 4 ? go(gemv_phase2_kernel<4, 2>) : rows == 8 ? go(gemv_phase2_kernel<8, 2>) : go(gemv_phase2_kernel<16, 2>);
+    else rows == 4 ? go(gemv_phase2_kernel<4, 4>) : rows == 8 ? go(gemv_phase2_kernel<8, 4>) : go(gemv_phase2_kernel<16, 4>);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
 }

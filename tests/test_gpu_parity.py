@@ -1002,3 +1002,26 @@ def test_rank_experts_equals_the_separate_calls(ctx, phase, T, H, E, k, k_hh):
     else:
         # a sum of T fp32 probabilities in token order against 64 bits: T roundings of 2^-24
         assert torch.allclose(a[0].double(), probs.double().mean(0), rtol=(T + 1) * 2.0 ** -24, atol=0)
+
+
+# the second GEMV phase: 16, 8 or 4 rows per workgroup by the number of workgroups (256 compute units), ragged last ones,
+# and two or four chunks of a bf16 row (F up to 1024 or beyond)
+@pytest.mark.parametrize("T,H,F", [(1, 1024, 1024), (1, 1088, 1088), (1, 2048, 960), (1, 2112, 1024), (2, 1024, 2112), (2, 2112, 704),
+                                   (3, 320, 1024)])
+def test_gemv_rows_per_workgroup(ctx, T, H, F):
+    cfg = synth.scaled(synth.CONFIGS["tiny"], T=T, H=H, F=F, E=4, k=4, config_id=980 + H % 97)
+    x, _ = synth.activations(cfg)
+    mats = [synth.expert_weights(cfg, e) for e in range(4)]
+    bits = np.array([16, 8, 4, 2], np.uint8)
+    host_q = {e: oracle_quantize_expert(mats[e], int(bits[e])) for e in range(1, 4)}
+    table, keep = B.make_expert_table([{"w": [to_bf16(m) for m in mats[0]]}] +
+                                      [{"q%d" % bits[e]: upload_q(host_q[e])} for e in range(1, 4)], DEV)
+    rng = np.random.default_rng(H)
+    idx = np.stack([rng.permutation(4) for _ in range(T)]).astype(np.int32)
+    g = (rng.random((T, 4)) + 0.1).astype(np.float32)
+    y = ctx.moe_ffn_mixed(to_bf16(x), torch.from_numpy(idx).to(DEV), torch.from_numpy(g).to(DEV), torch.from_numpy(bits).to(DEV),
+                          table, F, out_dtype=B.OUT_F32, path=B.PATH_GEMV)
+    torch.cuda.synchronize()
+    ref = O.moe_ffn_mixed(x, idx, g.astype(np.float64), bits, [{"w": mats[0]}] + [{"q": host_q[e]} for e in range(1, 4)])
+    # fp16 activations of the quantised formats: 2^-11 each, random sign over H and F terms; 2e-2 is the layer's bar
+    assert rel_err_per_token(y.cpu().numpy().astype(np.float64), ref) <= 2e-2
