@@ -504,16 +504,21 @@ __global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t
 #pragma unroll
             for (int i = 0; i < 16; i++) acc[a][b][i] = 0.0f;
     uint4 raw[8];
+    // Loads without a condition (rows and columns past the end re-read the last ones): behind a test per load the compiler
+    // waits for each before the test of the next, and the fetch is no longer in flight during the products.  Columns past
+    // the end only reach results that are not stored; rows past the end are cleared below.
+    const uint16_t* const xc = x + min(lcol, K - 8);
     auto fetch = [&](long s0) {
 #pragma unroll
-        for (int r = 0; r < 8; r++) {
-            const long smp = s0 + 8 * sgrp + r;
-            raw[r] = make_uint4(0u, 0u, 0u, 0u);
-            if (smp < n && lcol < K) raw[r] = load_global<uint4>(x + smp * K + lcol);
-        }
+        for (int r = 0; r < 8; r++) raw[r] = load_global<uint4>(xc + min(s0 + 8 * sgrp + r, n - 1) * K);
+        __builtin_amdgcn_sched_barrier(0);
     };
     fetch(0);
     for (long s0 = 0; s0 < n; s0 += kHsSamples) {
+        if (s0 + kHsSamples > n)                    // the last step
+#pragma unroll
+            for (int r = 0; r < 8; r++)
+                if (s0 + 8 * sgrp + r >= n) raw[r] = make_uint4(0u, 0u, 0u, 0u);
         // 8 x 8 transpose of 16-bit values: pair up the rows, split even and odd columns
         uint4 out[8];
 #pragma unroll
