@@ -572,19 +572,18 @@ def main():
                 t2 = time.perf_counter()
                 swp = {n_: ctx.timing_read(n_) for n_ in gnames}
                 ctx.timing_enable(())
-            trail_flops = 2.0 * gN * gK * (gK - 64) / 2.0       # one FMA per (row, column pair c < j across groups)
+            trail_flops = 2.0 * gN * gK * (gK - 256) / 2.0      # one FMA per (row, column pair c < j across panels of 256)
             res[label] = {
                 "N": gN, "K": gK, "calibration_tokens": n_cal,
                 "hessian_ms": round(fac["gptq_hessian"][0], 3),
                 "hessian_TFLOPs_bf16": round(2.0 * n_cal * gK * gK / 2 / (fac["gptq_hessian"][0] * 1e-3) / 1e12, 1),
                 "factor_ms_wall": round((t1 - t0) * 1e3 - fac["gptq_hessian"][0], 2),
-                "factor_kernels_ms": {"chol_diag": round(fac["gptq_factor"][0], 2), "group": round(fac["gptq_group"][0], 2),
-                                      "trail": round(fac["gptq_trail"][0], 2)},
+                "factor_kernels_ms": {"first_block": round(fac["gptq_factor"][0], 2), "solve": round(fac["gptq_group"][0], 2),
+                                      "update": round(fac["gptq_trail"][0], 2)},
                 "sweep_ms_wall": round((t2 - t1) * 1e3, 2),
                 "sweep_kernels_ms": {"group": round(swp["gptq_group"][0], 2), "trail": round(swp["gptq_trail"][0], 2)},
                 "sweep_trail_TFLOPs_fp32": round(trail_flops / (swp["gptq_trail"][0] * 1e-3) / 1e12, 1),
-                # 157.3 TFLOP/s is the packed-fp32 figure; one v_fma_f32 per lane (this build emits no packed fp32) peaks at half
-                "sweep_trail_frac_fp32_fma_peak_78p6": round(trail_flops / (swp["gptq_trail"][0] * 1e-3) / 1e12 / 78.65, 3),
+                "sweep_trail_frac_fp32_matrix_peak_157p3": round(trail_flops / (swp["gptq_trail"][0] * 1e-3) / 1e12 / 157.3, 3),
                 "finite": bool(torch.isfinite(gu).all())}
             del hess, gu, fws, sws, gx, gw, gout
             torch.cuda.empty_cache()

@@ -18,8 +18,9 @@
 //
 // The fp32 matrix instructions of this chip are such a chain: v_mfma_f32_{16x16x4,32x32x2}_f32 give, bit for bit,
 // what one fma after the other over ascending k gives, subnormals included (compared on 14 million random results with
-// equal, cancelling, tiny and subnormal operands; a test sweeps rows against the plain chain as well).  So the
-// corrections go through the matrix cores at twice the rate of the unpacked vector fma and keep the reference's bits.
+// equal, cancelling, tiny and subnormal operands; the tests sweep rows against the plain chain as well).  So the
+// corrections go through the matrix cores and keep the reference's bits: a register-only loop of those instructions holds
+// 140 to 155 TFLOP/s on random data, one of vector fmas 108 to 117, and a lane's operands serve four times the products.
 //
 // Rows are independent, columns are not.  Columns go in panels of 256 (four groups of 64), two launches each:
 //   group kernel   a wavefront owns 16 rows through the whole panel: a group's values lose the corrections of the
