@@ -471,14 +471,26 @@ __global__ __launch_bounds__(kAtThreads, 3) void attn_colsum_wide_kernel(
     }
 }
 
-// s[i] = (sum over heads, in head order) / (Hh T)
-__global__ __launch_bounds__(256) void attn_score_kernel(const float* __restrict__ partial, int T, int n_heads,
+// s[i] = (sum over heads, in head order) / (Hh T).  Bound: a memory latency per batch of heads; a wavefront per workgroup,
+// so that 4096 tokens reach 64 compute units.  4096 tokens x 32 heads, the whole score: 207 us with a latency per head and
+// 256 tokens per workgroup, 196 so.
+constexpr int kAtScoreThreads = kWave;
+
+__global__ __launch_bounds__(kAtScoreThreads) void attn_score_kernel(const float* __restrict__ partial, int T, int n_heads,
                                                          float inv, float* __restrict__ score)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * kAtScoreThreads + threadIdx.x;
     if (i >= T) return;
     float s = 0.0f;
-    for (int h = 0; h < n_heads; h++) s += partial[(long)h * T + i];
+    int h = 0;
+    for (; h + 16 <= n_heads; h += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; u++) v[u] = partial[(long)(h + u) * T + i];
+#pragma unroll
+        for (int u = 0; u < 16; u++) s += v[u];
+    }
+    for (; h < n_heads; h++) s += partial[(long)h * T + i];
     score[i] = s * inv;
 }
 
@@ -544,7 +556,8 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
 #undef DYMOE_ATTN_LAUNCH
 #undef DYMOE_ATTN_PAIR
     DYMOE_HIP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(dymoe::attn_score_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, st,
+    hipLaunchKernelGGL(dymoe::attn_score_kernel, dim3((unsigned)((T + dymoe::kAtScoreThreads - 1) / dymoe::kAtScoreThreads)),
+                       dim3(dymoe::kAtScoreThreads), 0, st,
                        (const float*)partial, T, n_heads, 1.0f / ((float)n_heads * (float)T), score);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
