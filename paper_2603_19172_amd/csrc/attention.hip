@@ -472,8 +472,8 @@ __global__ __launch_bounds__(kAtThreads, 3) void attn_colsum_wide_kernel(
 }
 
 // s[i] = (sum over heads, in head order) / (Hh T).  Bound: a memory latency per batch of heads; a wavefront per workgroup,
-// so that 4096 tokens reach 64 compute units.  4096 tokens x 32 heads, the whole score: 207 us with a latency per head and
-// 256 tokens per workgroup, 196 so.
+// so that 4096 tokens reach 64 compute units.  4096 tokens x 32 heads: 10.5 us of the score's 207
+// with a latency per head and 256 tokens per workgroup; the whole score takes 196 us so.
 constexpr int kAtScoreThreads = kWave;
 
 __global__ __launch_bounds__(kAtScoreThreads) void attn_score_kernel(const float* __restrict__ partial, int T, int n_heads,

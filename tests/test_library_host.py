@@ -131,6 +131,20 @@ def test_argument_validation_happens_before_any_device_work():
     assert ta(None, P + 2, P, 77, 8, 2, 128, 0.0, 1, P, P, aw, None) == B.EINVAL
     assert ta(None, P, P, 77, 8, 2, 128, 0.0, 1, None, P, aw, None) == B.EINVAL
     assert ta(None, None, None, 0, 8, 2, 128, 0.0, 1, None, None, 0, None) == B.ENOCTX   # T = 0 needs only a context
+    # importance and assignment in one call
+    tc, tb = (C.c_int32 * 2)(3, 5), (C.c_uint8 * 2)(4, 2)
+    tcp, tbp = C.cast(tc, C.c_void_p), C.cast(tb, C.c_void_p)
+    rk = lib.dymoe_rank_experts
+    assert rk(None, 0, P, 128, P, None, P, 7, 8, 2, 1, 2, tcp, tbp, 0, P, P, P, P, None) == B.ENOCTX
+    assert rk(None, 0, None, 0, P, None, P, 7, 8, 2, 1, 2, tcp, tbp, 0, P, P, P, P, None) == B.ENOCTX
+    assert rk(None, 0, P, 100, P, None, P, 7, 8, 2, 1, 2, tcp, tbp, 0, P, P, P, P, None) == B.EINVAL      # H
+    assert rk(None, 0, P, 128, P, None, None, 7, 8, 2, 1, 2, tcp, tbp, 0, P, P, P, P, None) == B.EINVAL   # no scores
+    assert rk(None, 0, P, 128, P, None, P, 7, 8, 2, 8, 2, tcp, tbp, 0, P, P, P, P, None) == B.EINVAL      # k_hh > T
+    assert rk(None, 0, P, 128, P, None, P, 7, 9, 2, 1, 2, tcp, tbp, 0, P, P, P, P, None) == B.EINVAL      # tiers
+    assert rk(None, 0, P, 128, P, None, P, 7, 8, 2, 1, 2, tcp, tbp, 3, P, P, P, P, None) == B.EINVAL      # floor
+    assert rk(None, 0, P, 128, P, None, P, 7, 8, 2, 1, 2, tcp, tbp, 0, P, P, P, None, None) == B.EINVAL   # rank
+    assert rk(None, 1, None, 0, P, None, None, 7, 8, 2, 0, 2, tcp, tbp, 0, P, P, P, P, None) == B.EINVAL  # decode, no probs
+    assert rk(None, 1, None, 0, P, P, None, 7, 8, 2, 0, 2, tcp, tbp, 0, P, P, P, P, None) == B.ENOCTX
     # error-compensated quantizer
     gq = lib.dymoe_gptq_quantize_pack
     gw = int(lib.dymoe_gptq_workspace_bytes(100, 256))
