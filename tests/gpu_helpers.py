@@ -81,3 +81,21 @@ def margin_ok(logits: np.ndarray, k: int, tol: float = 1e-4) -> np.ndarray:
     """Per token: every adjacent pair among the k+1 largest logits differs by > tol."""
     s = -np.sort(-logits, axis=1)[:, :min(k + 1, logits.shape[1])]
     return (s[:, :-1] - s[:, 1:] > tol).all(axis=1)
+
+
+def subnormal_sweep_inputs(seed, N, K, halfway):
+    """w [N, K] (bf16 bits) and u [K, K] fp32 for the compensated sweep, every error e = rest / u[c, c] subnormal and every
+    correction e * u[c, j] an ordinary number of the weights' own size, so that the last bit of e decides codes.
+    halfway: every value is a multiple of 2^-28, diagonals are odd numbers whose 64-bit reciprocals round badly times
+    2^122 and the rest whole multiples of 2^121, so that the sweep's arithmetic is exact but for the errors and about one
+    in a hundred of their quotients lies exactly halfway between two subnormal numbers."""
+    rng = np.random.default_rng(seed)
+    if not halfway:
+        x = synth.calibration_inputs(seed, 2 * K, K)
+        u = O.gptq_factor(O.gptq_hessian(x)) * 2.0 ** 125
+        return synth.normal_bf16(seed, 77, (N, K), 0.02), u.astype(np.float32)
+    w = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits((rng.standard_normal((N, K)) * 2.0 ** -13).astype(np.float32)))
+    w = (np.rint(w.astype(np.float64) * 2.0 ** 28) * 2.0 ** -28).astype(np.float32)
+    u = np.triu(rng.integers(-3, 4, size=(K, K)), 1) * 2.0 ** 121
+    u[np.diag_indices(K)] = rng.choice([41, 47, 49, 55, 61], size=K) * 2.0 ** 122
+    return synth.f32_to_bf16_bits(w), u.astype(np.float32)

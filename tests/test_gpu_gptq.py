@@ -8,7 +8,7 @@ import torch
 from oracle import dymoe_oracle as O
 from paper_2603_19172_amd import binding as B
 from paper_2603_19172_amd import synth
-from gpu_helpers import DEV, bits_of, to_bf16
+from gpu_helpers import DEV, bits_of, subnormal_sweep_inputs, to_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -303,8 +303,9 @@ def test_gptq_sweep_panel_edges(ctx, N, K, bits):
 
 @pytest.mark.parametrize("bits", [2, 4, 8])
 def test_gptq_sweep_subnormal_errors(ctx, bits):
-    """Rows so small that rest / U[c,c] is subnormal (the groups that are done again with an IEEE division): the
-    corrections they pass on, and the groups behind them, must still be the exact sequence's."""
+    """Rows so small that rest / U[c,c] is subnormal, beside ordinary ones in the same groups: the ordinary rows' codes, and
+    scale and zero of the small ones.  (Scale 0 makes every code of the small rows 0: what their errors are cannot be seen
+    here, but in the test below.)"""
     N, K = 66, 320
     _, wb, U = _case(850, N, K)
     w = synth.bf16_bits_to_f32(wb).copy()
@@ -318,6 +319,19 @@ def test_gptq_sweep_subnormal_errors(ctx, bits):
         want = O.gptq_quantize_pack(wb, u, bits)
         got = ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(u).to(DEV), bits)
         assert _same(got, want)
+
+
+# every error subnormal, at a size with panels of two groups and one with a whole panel and a ragged row block; on the
+# halfway inputs a reciprocal in the place of the division changes up to 59 code bytes, a flush of subnormal numbers more
+# than 1000 (tests/test_oracle_pins.py makes both mistakes)
+@pytest.mark.parametrize("halfway", [False, True])
+@pytest.mark.parametrize("N,K", [(24, 192), (66, 320)])
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_gptq_sweep_subnormal_errors_reach_the_codes(ctx, N, K, bits, halfway):
+    wb, u = subnormal_sweep_inputs(1, N, K, halfway)
+    want = O.gptq_quantize_pack(wb, u, bits)
+    got = ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(u).to(DEV), bits)
+    assert _same(got, want)
 
 
 # blocks of 64, updated in 2 x 2: one block, two, an odd number, and pivots outside the range of the estimate's steps

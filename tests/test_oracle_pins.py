@@ -868,3 +868,50 @@ def test_gptq_lowers_the_output_error_on_correlated_inputs(bits):
     direct = float((((w - O.dequantize(codes, sc, ze, bits)) @ x.T) ** 2).sum())
     assert abs(direct - e_comp) <= 1e-9 * e_comp
     assert e_comp < 0.5 * e_plain
+
+
+def _sweep_binary32(wb, u, bits, quotient):
+    """The compensated sweep in numpy float32, the quotient given; the fused multiply-add through 64 bits, exact on values
+    that are whole multiples of one number.  Returns codes [N, K]."""
+    v = synth.bf16_bits_to_f32(wb).copy()
+    qmax = np.float32((1 << bits) - 1)
+    q = np.zeros(v.shape, np.uint8)
+    for c in range(v.shape[1]):
+        if c % 64 == 0:
+            lo, hi = v[:, c:c + 64].min(axis=1), v[:, c:c + 64].max(axis=1)
+            m, s = lo.astype(np.float16).astype(np.float32), ((hi - lo) / qmax).astype(np.float16).astype(np.float32)
+            inv = np.float32(1.0) / s
+        r = np.clip(np.rint((v[:, c] - m) * inv), np.float32(0), qmax)
+        q[:, c] = r
+        e = quotient(v[:, c] - (r * s + m), u[c, c])
+        v[:, c + 1:] = (v[:, c + 1:] - e[:, None].astype(np.float64) * u[c, c + 1:]).astype(np.float32)
+    return q
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_gptq_subnormal_error_inputs_show_a_wrong_quotient(bits):
+    """The inputs on which the device's subnormal errors are compared bit for bit: IEEE division gives the oracle's codes,
+    a 64-bit reciprocal in its place and a flush of subnormal quotients do not."""
+    from gpu_helpers import subnormal_sweep_inputs
+    tiny = np.float32(2.0 ** -126)
+
+    def flushed(rest, d):
+        e = rest / d
+        return np.where(np.abs(e) < tiny, np.float32(0), e)
+
+    def reciprocal(rest, d):
+        return (rest.astype(np.float64) * (1.0 / np.float64(d))).astype(np.float32)
+
+    for halfway in (False, True):
+        wb, u = subnormal_sweep_inputs(1, 66, 320, halfway)
+        codes = O.gptq_quantize_pack(wb, u, bits)[0]
+        want = ((codes[:, :, None] >> (bits * np.arange(8 // bits))) & ((1 << bits) - 1)).reshape(66, 320)
+        exact = _sweep_binary32(wb, u, bits, lambda rest, d: rest / d)
+        wrong = (_sweep_binary32(wb, u, bits, flushed) != want).sum()
+        by_inv = (_sweep_binary32(wb, u, bits, reciprocal) != want).sum()
+        print("halfway %d, %d bits: codes changed by a flush %d, by a reciprocal %d" % (halfway, bits, wrong, by_inv))
+        assert wrong > 1000
+        if halfway:
+            assert np.array_equal(exact, want) and by_inv > 0
+        else:
+            assert (exact != want).sum() <= 2      # (the emulated fma rounds twice, rarely otherwise than once)
