@@ -35,8 +35,9 @@ def _run(ctx, q, k, causal, scale=0.0):
 
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(16, 2, 2, 64), (77, 4, 2, 128), (1, 2, 1, 64), (33, 3, 3, 64),
                                         (160, 8, 2, 128), (512, 32, 8, 128),
-                                        # from 993 tokens on the streamed operand goes through LDS: ragged ends,
-                                        # a head count the XCD mapping does not divide, both head sizes
+                                        # many tokens, few heads (512 fragments over all heads at most: operands
+                                        # straight from memory): ragged ends, a head count the XCD mapping does not
+                                        # divide, both head sizes
                                         (993, 8, 2, 128), (1100, 3, 3, 64), (1057, 5, 1, 128), (2048, 8, 8, 64),
                                         (4100, 2, 1, 128)])
 @pytest.mark.parametrize("causal", [True, False])
@@ -53,9 +54,11 @@ def test_attention_score_matches_the_oracle(ctx, T, Hh, Hkv, d, causal):
 
 
 # the LDS-staged kernels need 32 fragments and more than 512 over all heads: both sides of that line, 64-token stages that
-# end whole, half and ragged, head counts that the XCD mapping divides and does not, rounds of blocks that are not whole
+# end whole, half and ragged, head counts that the XCD mapping divides and does not, rounds of blocks that are not whole.
+# The last four reach the second round of 32 blocks per XCD, which a causal mask deals in reverse: 36, 48, 48 and 33 blocks
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(1024, 16, 4, 128), (1025, 16, 4, 128), (1057, 17, 1, 64), (1088, 24, 6, 64),
-                                        (1120, 20, 5, 128), (2111, 8, 2, 128)])
+                                        (1120, 20, 5, 128), (2111, 8, 2, 128), (1100, 32, 8, 128), (1500, 32, 8, 128),
+                                        (1500, 32, 8, 64), (4200, 8, 2, 64)])
 @pytest.mark.parametrize("causal", [True, False])
 def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
     cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=160 + T)
