@@ -104,8 +104,8 @@ __global__ __launch_bounds__(kImpThreads) void importance_prefill_kernel(
 //   prefill  up to 256 tokens: as many lanes per token as 1024 threads give (at least four) share its comparisons with the
 //            T scores, which are the caller's or, x given, the row norms of x (token_norm_kernel's arithmetic; stored to
 //            score as well)
-//   decode   any number of tokens: probabilities pass through LDS, 8192 at a time, and a thread adds up its expert's in
-//            token order
+//   decode   any number of tokens: a thread adds up its expert's probabilities in token order, more than eight tokens of
+//            fewer than 768 experts through LDS, 8192 at a time
 // Bound: latency of two or three dependent trips to memory.  61 tokens x 128 experts, decode: 5 us with the assignment,
 // where zero-fill, load histogram, the sum with a thread walking the tokens in memory and the assignment took 4 + 4.4 +
 // 15 + 4.8 us; 16 tokens, prefill: 4 us with norms and assignment for 2.1 + 4 + 2.4.  The comparisons grow with the square of
@@ -177,21 +177,38 @@ __global__ __launch_bounds__(kImpBlock) void importance_block_kernel(
         }
         float g = 0.0f;                                                     // of expert tid
         const int step = kImpProbs / E;
-        for (int t0 = 0; t0 < T; t0 += step) {
-            const int n = min(step, T - t0);
-            float v[kImpProbs / kImpBlock];
-#pragma unroll
-            for (int u = 0; u < kImpProbs / kImpBlock; u++) {
-                const int i = u * kImpBlock + tid;
-                v[u] = (i < n * E) ? probs[(size_t)t0 * E + i] : 0.0f;
-            }
-            __syncthreads();                                                // the previous trip's have been read
-#pragma unroll
-            for (int u = 0; u < kImpProbs / kImpBlock; u++) s_buf[u * kImpBlock + tid] = v[u];
-            __syncthreads();
+        // A batch of at most eight tokens is one trip to memory either way, and staging adds two barriers to it; from 768
+        // experts on the experts' own threads have as much in flight as the whole workgroup.  Straight from memory / staged,
+        // us: 1 token x 8 experts 2.0 / 2.4, 8 x 768 2.4 / 2.7, 1024 x 768 65 / 73, but 1024 x 513 64 / 59.
+        if (T == 1) {
+            if (tid < E) g += probs[tid];
+        } else if (T <= 8 || E >= 768) {
             if (tid < E)
+                for (int t0 = 0; t0 < T; t0 += 8) {
+                    float v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; u++) v[u] = probs[(size_t)min(t0 + u, T - 1) * E + tid];
+#pragma unroll
+                    for (int u = 0; u < 8; u++)
+                        if (t0 + u < T) g += v[u];
+                }
+        } else {
+            for (int t0 = 0; t0 < T; t0 += step) {
+                const int n = min(step, T - t0);
+                float v[kImpProbs / kImpBlock];
+#pragma unroll
+                for (int u = 0; u < kImpProbs / kImpBlock; u++) {
+                    const int i = u * kImpBlock + tid;
+                    v[u] = (i < n * E) ? probs[(size_t)t0 * E + i] : 0.0f;
+                }
+                __syncthreads();                                            // the previous trip's have been read
+#pragma unroll
+                for (int u = 0; u < kImpProbs / kImpBlock; u++) s_buf[u * kImpBlock + tid] = v[u];
+                __syncthreads();
+                if (tid < E)
 #pragma unroll 8
-                for (int t = 0; t < n; t++) g += s_buf[t * E + tid];
+                    for (int t = 0; t < n; t++) g += s_buf[t * E + tid];
+            }
         }
         if (tid < E) s_imp[tid] = (T <= 1) ? g : g / (float)T;
     }

@@ -265,7 +265,7 @@ def test_token_score_norm(ctx):
 
 def test_importance_prefill_bit_exact(ctx):
     rng = np.random.default_rng(4)
-    # up to 32 tokens: one workgroup, one launch; beyond: zero-fill and the many-workgroup kernel
+    # up to 256 tokens: one workgroup, one launch; beyond: zero-fill and the many-workgroup kernel
     for T, E, k, k_hh in ((16, 8, 2, 1), (32, 8, 2, 3), (33, 8, 2, 3), (200, 16, 4, 10), (700, 128, 8, 35),
                            (513, 8, 2, 513), (300, 16, 4, 0), (2048, 128, 8, 103), (5000, 16, 4, 250)):
         idx = np.stack([rng.permutation(E)[:k] for _ in range(T)]).astype(np.int32)
@@ -293,6 +293,22 @@ def test_importance_decode(ctx):
             assert np.array_equal(imp.cpu().numpy(), p[0])
         assert np.allclose(imp.cpu().numpy(), ref, rtol=1e-6)
         assert np.array_equal(load.cpu().numpy(), np.bincount(idx.ravel(), minlength=8))
+
+
+# probabilities straight from memory up to 8 tokens and from 768 experts on, through LDS (8192 / E tokens a trip) otherwise
+@pytest.mark.parametrize("T,E", [(1, 8), (1, 1024), (2, 30), (8, 128), (9, 128), (64, 128), (65, 128), (8, 767), (11, 767), (9, 768),
+                                 (16, 768), (17, 1024)])
+def test_importance_decode_sums_in_token_order(ctx, T, E):
+    rng = np.random.default_rng(100 * T + E)
+    p = rng.random((T, E)).astype(np.float32)
+    idx = np.stack([rng.permutation(E)[:2] for _ in range(T)]).astype(np.int32)
+    imp, load = ctx.expert_importance(B.PHASE_DECODE, torch.from_numpy(idx).to(DEV), E, probs=torch.from_numpy(p).to(DEV))
+    sync()
+    s = np.zeros(E, np.float32)
+    for t in range(T):
+        s = s + p[t]
+    assert np.array_equal(imp.cpu().numpy(), s / np.float32(T))
+    assert np.array_equal(load.cpu().numpy(), np.bincount(idx.ravel(), minlength=E))
 
 
 def test_assign_precision_bit_exact(ctx):
