@@ -113,7 +113,8 @@ __global__ __launch_bounds__(kImpThreads) void importance_prefill_kernel(
 // take 5.5 + 5.
 constexpr int kImpBlock = 1024;
 constexpr int kImpBlockTokens = 256;                     // prefill
-constexpr int kImpNormBytes = 64 << 10;                  // x up to this size: its norms are taken here as well
+constexpr int kImpNormBytes = 64 << 10;                  // x up to this size and ...
+constexpr int kImpNormTokens = 64;                       // ... this many rows: its norms are taken here as well
 constexpr int kImpProbs = 8192;
 
 template <bool PREFILL, bool ASSIGN>
@@ -323,8 +324,10 @@ int dymoe_rank_experts(dymoe_ctx* ctx, int phase, const void* x, int H, const in
         return DYMOE_OK;
     }
     if (T <= dymoe::kImpBlockTokens) {
-        // one workgroup does not read more than 64 KiB of x in the time of a launch: beyond, the norms have one of their own
-        const bool inside = x && (size_t)T * H * 2 <= (size_t)dymoe::kImpNormBytes;
+        // One workgroup does not read more than 64 KiB of x in the time of a launch, nor, however short the rows, more than
+        // four after the other by each of its 16 wavefronts: beyond, the norms have a launch of their own.  Inside / outside,
+        // us: 64 x 128 5.1 / 5.2, 80 x 128 5.7 / 5.4, 256 x 128 13.3 / 7.9, 64 x 512 5.1 / 5.3 (8 experts).
+        const bool inside = x && T <= dymoe::kImpNormTokens && (size_t)T * H * 2 <= (size_t)dymoe::kImpNormBytes;
         if (x && !inside && T > 0) {
             const int rc = dymoe_token_score_norm(ctx, x, T, H, token_score, stream);
             if (rc != DYMOE_OK) return rc;

@@ -969,7 +969,7 @@ def test_quantize_pack_smallest_and_odd_sizes(ctx):
         _check_quant(ctx, w, bits)
 
 
-# one workgroup up to 256 tokens of prefill (norms inside up to 64 KiB of x), three launches beyond; one workgroup for any
+# one workgroup up to 256 tokens of prefill (norms inside up to 64 tokens and 64 KiB of x), three launches beyond; one workgroup for any
 # decode, 8192 probabilities at a time: sizes on both sides of each edge, tied scores, a floor
 @pytest.mark.parametrize("phase,T,H,E,k,k_hh", [
     ("prefill", 1, 256, 8, 2, 1), ("prefill", 17, 256, 8, 2, 3), ("prefill", 64, 512, 30, 4, 5), ("prefill", 65, 512, 30, 4, 0),
@@ -1018,6 +1018,25 @@ def test_rank_experts_equals_the_separate_calls(ctx, phase, T, H, E, k, k_hh):
     else:
         # a sum of T fp32 probabilities in token order against 64 bits: T roundings of 2^-24
         assert torch.allclose(a[0].double(), probs.double().mean(0), rtol=(T + 1) * 2.0 ** -24, atol=0)
+
+
+# the norms' own launch: from 65 tokens and beyond 64 KiB of x
+@pytest.mark.parametrize("T,H,launches", [(1, 128, 0), (64, 128, 0), (65, 128, 1), (256, 128, 1), (64, 512, 0), (64, 520, 1)])
+def test_rank_experts_takes_few_short_norms_itself(ctx, T, H, launches):
+    E, k = 8, 2
+    x = torch.randn((T, H), generator=torch.Generator(device=DEV).manual_seed(T + H), device=DEV).bfloat16()
+    idx = torch.arange(T * k, device=DEV).reshape(T, k).remainder(E).int()
+    imp, load, rank = (torch.empty((E,), dtype=torch.int32, device=DEV) for _ in range(3))
+    bits, score = torch.empty((E,), dtype=torch.uint8, device=DEV), torch.empty((T,), device=DEV)
+    tc, tb = (ctypes.c_int32 * 2)(4, 4), (ctypes.c_uint8 * 2)(4, 2)
+    ctx.timing_enable(["token_norm"])
+    B._check(B.lib.dymoe_rank_experts(ctx._h, B.PHASE_PREFILL, x.data_ptr(), H, idx.data_ptr(), None, score.data_ptr(), T, E, k, 1, 2,
+                                      ctypes.cast(tc, ctypes.c_void_p), ctypes.cast(tb, ctypes.c_void_p), 0, imp.data_ptr(),
+                                      load.data_ptr(), bits.data_ptr(), rank.data_ptr(), B._stream(None)), "rank")
+    _, n = ctx.timing_read("token_norm")
+    ctx.timing_enable([])
+    assert n == launches
+    assert torch.equal(score, ctx.token_score_norm(x))
 
 
 # the second GEMV phase: 16, 8 or 4 rows per workgroup by the number of workgroups (256 compute units), ragged last ones,
