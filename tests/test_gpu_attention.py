@@ -68,6 +68,16 @@ def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
+# the sum over heads: one or two of them, batches of sixteen, whole, short by one and with one head left
+@pytest.mark.parametrize("Hh", [1, 2, 3, 15, 16, 17, 31, 32, 33])
+def test_attention_score_sums_every_head_once(ctx, Hh):
+    T, d = 70, 64
+    q, k = (synth.normal_bf16(180 + Hh, 9100 + i, (T, Hh, d), 1.0) for i in range(2))
+    ref = O.token_score_attention(q, k, Hh, Hh, causal=True)
+    got = _run(ctx, q, k, True)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL)
+
+
 def test_attention_score_explicit_scale_and_determinism(ctx):
     cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=200, k_hh=10, config_id=71)
     q, k, _ = synth.attention_inputs(cfg, 4, 4, 64)
