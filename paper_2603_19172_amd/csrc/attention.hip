@@ -265,7 +265,7 @@ __device__ __forceinline__ void settle(AtFrag<D>& f)
 // heads and dealt out to and fro in rounds of 32.
 __device__ __forceinline__ void block_and_head(int nblk, int n_heads, int causal, int& blk, int& head)
 {
-    const int lin = blockIdx.x;
+    const int lin = blockIdx.x + nblk * blockIdx.y;           // grid = nblk n_heads, or (nblk, n_heads) if that is too long
     if (n_heads % 8 == 0) {
         const int per = n_heads >> 3, xcd = lin & 7, j = lin >> 3;
         const int round = j >> 5, in_round = min(32, per * nblk - 32 * round);
@@ -552,7 +552,12 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     // 1000 x 32 77 / 49, 2500 x 4 72 / 88, 2500 x 16 119 / 93, 4096 x 4 124 / 133, 4096 x 8 158 / 133, 4096 x 32 548 / 209.
     // (Below 32 fragments the narrow pair stays for every number of heads: its four partial sums per key round less.)
     const bool wide = nfrag >= dymoe::kAtWideFrags && (long)nfrag * n_heads > dymoe::kAtNarrowFrags;
-    const dim3 grid = wide ? dim3((unsigned)((nfrag + 3) / 4) * (unsigned)n_heads) : dim3((unsigned)nfrag, (unsigned)n_heads);
+    // A dimension of a launch holds fewer than 2^32 threads: beyond that (from 275 GB of queries on) a head per y, as in the
+    // narrow pair's launches; 4096 x 32 takes 201 us that way and 199 in one dimension.
+    const long blocks = (nfrag + 3L) / 4 * n_heads;
+    const dim3 grid = !wide ? dim3((unsigned)nfrag, (unsigned)n_heads)
+                      : blocks * dymoe::kAtThreads < 1L << 32 ? dim3((unsigned)blocks)
+                                                              : dim3((unsigned)((nfrag + 3) / 4), (unsigned)n_heads);
 #define DYMOE_ATTN_PAIR(STATS_, COLSUM_)                                                                               \
     do {                                                                                                               \
         dymoe_launch(ctx, DYMOE_K_ATTN_STATS, STATS_, grid, dim3(dymoe::kAtThreads), 0, st, qb, kbp, T, n_heads, group,  \
