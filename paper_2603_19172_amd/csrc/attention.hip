@@ -19,8 +19,9 @@ namespace dymoe {
 
 constexpr int kAtThreads = 256;
 constexpr int kAtWaves = kAtThreads / kWave;
-constexpr int kAtWideFrags = 32;       // from this many 32-token fragments on (T > 992) and beyond
-constexpr long kAtNarrowFrags = 512;   // so many over all heads: the LDS-staged kernels
+// the LDS-staged kernels from this many 32-token fragments on (T > 992) ...
+constexpr int kAtWideFrags = 32;
+constexpr long kAtNarrowFrags = 512;   // ... if there are more than this over all heads
 
 // One lane's share of a 32-token fragment of one head (D columns): lane (ln, kb)
 // holds row ln; piece c covers columns 32 (c / 2) + 16 kb + 8 (c % 2) .. + 7, i.e.
@@ -212,9 +213,10 @@ __global__ __launch_bounds__(kAtThreads) void attn_colsum_kernel(
 // of row r at chunk position c ^ (r mod chunks-per-row), so that the operand reads of 16 consecutive rows fall on
 // different banks).  No merge between wavefronts: each owns its tokens' statistics or sums outright.
 // Bound: per 32 x 32 logits at d = 128 256 cycles of matrix instructions and about as many each of vector work and of
-// exponentials, overlapped between a SIMD's wavefronts.  4096 tokens, 32 / 8 heads x 128, both passes: causal 292 -> 209 us,
-// unmasked 392 -> 358 us since two logits tiles are worked on side by side per barrier, the register-held fragment
-// is waited for before the loop, and blocks are dealt out by length; d = 64 causal 247 -> 139 us.
+// exponentials, overlapped between a SIMD's wavefronts.  4096 tokens, 32 / 8 heads, the whole score: d = 128 causal
+// 292 -> 195 us, unmasked 392 -> 341, d = 64 causal 247 -> 128, since two logits tiles are worked on side by side per
+// barrier, the register-held fragment is waited for before the loop, and blocks are dealt out by length (209, 358 and 139
+// before the sum over the heads asked for sixteen of them at a time).
 constexpr int kAtStageFrags = 2;
 
 template <int D>
@@ -548,8 +550,16 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     // Few fragments over all heads: a workgroup per 32-token fragment, its wavefronts sharing the streamed tokens (many
     // workgroups, operands straight from global memory).  Else a workgroup per 128 tokens with the streamed operand in LDS:
     // per logits tile several times cheaper, but a serial chain of all the tokens, 1 us per 32 of them, however few
-    // heads there are.  Both passes, us, narrow / wide at d = 128, causal: 500 tokens x 32 heads 33 / 34, 1000 x 16 43 / 44,
-    // 1000 x 32 77 / 49, 2500 x 4 72 / 88, 2500 x 16 119 / 93, 4096 x 4 124 / 133, 4096 x 8 158 / 133, 4096 x 32 548 / 209.
+    // heads there are.  Whole score, us, narrow / wide by tokens x heads (fragments):
+    //                      d = 128, causal   unmasked    d = 64, causal   unmasked
+    //    1024 x 16 (512)      40 /  41       41 /  39       24 /  32      25 /  30
+    //    4096 x  4 (512)     126 / 131      128 / 136       68 /  99      71 / 103
+    //    1500 x 12 (564)      64 /  61       80 /  66       37 /  48      46 /  53
+    //    2500 x  8 (632)      79 /  87      120 / 100       45 /  66      66 /  79
+    //    4096 x  6 (768)     184 / 135      188 / 138       99 / 100     102 / 105
+    //    2048 x 16 (1024)    100 /  71      130 /  70       55 /  54      70 /  52
+    // so the line is right for d = 128; at d = 64, where a wavefront's share of the products is half as long, the narrow pair
+    // stays ahead up to about 768 fragments, by up to 30 %.
     // (Below 32 fragments the narrow pair stays for every number of heads: its four partial sums per key round less.)
     const bool wide = nfrag >= dymoe::kAtWideFrags && (long)nfrag * n_heads > dymoe::kAtNarrowFrags;
     // A dimension of a launch holds fewer than 2^32 threads: beyond that (from 275 GB of queries on) a head per y, as in the
