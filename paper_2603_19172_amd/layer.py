@@ -97,7 +97,8 @@ class MoELayer:
                                               self.rank.data_ptr(), st), "dymoe_assign_precision")
 
     def rank_experts(self, x, st):
-        """S2 + S3 (token scores, importance, assignment) in one or two launches."""
+        """S2 + S3 (token scores, importance, assignment): one launch for a decode step or a few tokens' prefill, one more
+        for the norms of a prefill of up to 256 tokens, three beyond."""
         prefill = self.phase == B.PHASE_PREFILL
         B._check(B.lib.dymoe_rank_experts(self.ctx._h, self.phase, x.data_ptr() if prefill else None, self.H,
                                           self.idx.data_ptr(), self.probs.data_ptr(), self.score.data_ptr(), self.T, self.E,
