@@ -316,8 +316,8 @@ int dymoe_quantize_pack(dymoe_ctx* ctx, const void* w, long N, long K, int bits,
  * u [K,K] fp32 row-major, device, 16-byte aligned (only the upper triangle is
  * read; U[c,c] > 0); from dymoe_gptq_factor or the caller's own.  The identity
  * gives dymoe_quantize_pack's result.  workspace: dymoe_gptq_workspace_bytes(N,
- * K) bytes of device memory, 256-byte aligned (an fp32 copy of the matrix and
- * 128 values per row); its contents are garbage afterwards.  Other arguments,
+ * K) bytes of device memory, 256-byte aligned (an fp32 copy of the matrix and, N
+ * not a multiple of 64, up to 64 KiB); its contents are garbage afterwards.  Other arguments,
  * limits and errors as dymoe_quantize_pack; DYMOE_ENOSPC if the workspace is
  * too small.  Enqueues about K/128 launches on `stream`; never synchronises.
  */
@@ -332,8 +332,8 @@ int dymoe_quantize_pack(dymoe_ctx* ctx, const void* w, long N, long K, int bits,
  * lambda = damp * mean(diag H); a diagonal entry that is exactly zero (a column
  * no input ever reached) counts as 1 and becomes 1 (+ lambda).  fp32 throughout.
  * hess is read only; u [K, K] fp32, fully written (zeros below the diagonal);
- * workspace of dymoe_gptq_factor_workspace_bytes(K) bytes (two K x K fp32
- * matrices and change), 256-byte aligned.  K multiple of 64, K <= 65536, damp >=
+ * workspace of dymoe_gptq_factor_workspace_bytes(K) bytes (a K x K fp32 matrix,
+ * 64 rows of it and change), 256-byte aligned.  K multiple of 64, K <= 65536, damp >=
  * 0 (the published default is 0.01).  H + lambda I must be positive definite in
  * fp32 (a square root of a negative pivot gives NaNs in u, nothing is checked).
  * Errors as elsewhere; both enqueue on `stream` and return without waiting.

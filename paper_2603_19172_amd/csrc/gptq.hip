@@ -40,7 +40,14 @@ constexpr int kGqPanel = 4;         // groups per panel
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 static inline size_t gq_round256(size_t v) { return (v + 255) & ~(size_t)255; }
-static inline long gq_rows_padded(long N) { return (N + kGqRows - 1) / kGqRows * kGqRows; }
+static inline long gq_row_blocks(long N) { return (N + kGqRows - 1) / kGqRows; }
+
+// Groups per panel.  Where all rows make one ragged block, no block can keep its errors in v (see GqErr), and half a panel
+// is kept in the linear buffer.
+static inline int gq_panel(long N) { return (N < kGqRows) ? kGqPanel / 2 : kGqPanel; }
+
+// bytes of the ragged row block's errors, a panel's columns of 64 rows; no ragged block, no buffer
+static inline size_t gq_tail_bytes(long N) { return (N % kGqRows) ? (size_t)gq_panel(N) * kGqGroup * kGqRows * sizeof(float) : 0; }
 
 // Where the (negated) errors of a panel of four groups are kept between the two kernels.  The panel's own columns of
 // v are dead once its values are in registers, and a row block's 64 x 256 of them hold its 256 x 64 errors exactly:
@@ -865,8 +872,7 @@ extern "C" {
 size_t dymoe_gptq_workspace_bytes(long N, long K)
 {
     if (N <= 0 || K <= 0) return 0;
-    return dymoe::gq_round256((size_t)N * (size_t)K * 4) +
-           dymoe::gq_round256(2 * (size_t)dymoe::kGqGroup * (size_t)dymoe::gq_rows_padded(N) * 4);
+    return dymoe::gq_round256((size_t)N * (size_t)K * 4) + dymoe::gq_tail_bytes(N);
 }
 
 int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u, long N, long K, int bits, int group,
@@ -883,11 +889,10 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
     if (workspace_bytes < dymoe_gptq_workspace_bytes(N, K)) return DYMOE_ENOSPC;
     if (!ctx) return DYMOE_ENOCTX;
     hipStream_t st = (hipStream_t)stream;
-    const long n_blocks = gq_rows_padded(N) / kGqRows;
+    const long n_blocks = gq_row_blocks(N);
     float* v = reinterpret_cast<float*>(workspace);
     float* tail = reinterpret_cast<float*>((char*)workspace + gq_round256((size_t)N * (size_t)K * 4));
-    // Panels of four groups, except where all rows make one ragged block: the linear buffer then holds 128 columns' errors.
-    const int panel = (N < kGqRows) ? kGqPanel / 2 : kGqPanel;
+    const int panel = gq_panel(N);
     const uint16_t* w = (const uint16_t*)w_bf16;
     uint16_t* sc = (uint16_t*)scale;
     uint16_t* zr = (uint16_t*)zero;
@@ -931,8 +936,9 @@ int dymoe_gptq_hessian(dymoe_ctx* ctx, const void* x_bf16, long n, long K, int a
 size_t dymoe_gptq_factor_workspace_bytes(long K)
 {
     if (K <= 0) return 0;
-    // the reversed damped Hessian (later the substitution's right-hand sides), its Cholesky factor, 128 errors per row, damping
-    return 2 * dymoe::gq_round256((size_t)K * (size_t)K * 4) + dymoe::gq_round256(2 * (size_t)dymoe::kGqGroup * (size_t)K * 4) + 256;
+    // the triangle that becomes factor and inverse, a block row P, the diagonal block's factor, the damping
+    return dymoe::gq_round256((size_t)K * (size_t)K * 4) + dymoe::gq_round256((size_t)dymoe::kGqGroup * (size_t)K * 4) +
+           dymoe::gq_round256(((size_t)dymoe::kGqGroup * dymoe::kGqGroup + 1) * 4);
 }
 
 int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, float* u, void* workspace,
@@ -948,7 +954,7 @@ int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, flo
     const size_t mat = gq_round256((size_t)K * (size_t)K * 4);
     float* v = reinterpret_cast<float*>(workspace);
     float* p_row = reinterpret_cast<float*>((char*)workspace + mat);                    // 64 x K
-    float* r = reinterpret_cast<float*>((char*)workspace + 2 * mat);                     // 64 x 64
+    float* r = reinterpret_cast<float*>((char*)p_row + gq_round256((size_t)kGqGroup * (size_t)K * 4));   // 64 x 64
     float* lambda = r + kGqGroup * kGqGroup;
     hipLaunchKernelGGL(gptq_damping_kernel, dim3(1), dim3(256), 0, st, hess, K, damp, lambda);
     hipLaunchKernelGGL(gptq_reverse_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)(K / kGqGroup)), dim3(256), 0, st, hess, K,

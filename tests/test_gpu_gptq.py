@@ -348,3 +348,22 @@ def test_gptq_factor_block_edges(ctx, K, size):
     print("K=%d size %.0e: max row-relative error %.2e" % (K, size, rel.max()))
     # the same bound as for the other sizes: fp32 Cholesky of a matrix with a condition number of about 1e3
     assert np.array_equal(U, np.triu(U)) and rel.max() < 2e-4
+
+
+# workspaces of exactly the bytes asked for, one value everywhere before and behind them: what lies behind stays, and the
+# results do not depend on what lay inside
+@pytest.mark.parametrize("N,K", [(24, 192), (64, 320), (65, 64), (130, 576)])
+def test_gptq_workspaces_are_as_large_as_asked_for(ctx, N, K):
+    _, wb, _ = _case(900 + N, N, K)
+    hess = ctx.gptq_hessian(to_bf16(synth.calibration_inputs(900 + N, 2 * K, K)))
+    want_u = ctx.gptq_factor(hess)
+    want = ctx.gptq_quantize_pack(to_bf16(wb), want_u, 4)
+    for fill in (0x00, 0xFF):
+        need = int(B.lib.dymoe_gptq_factor_workspace_bytes(K))
+        ws = torch.full((need + 4096,), fill, dtype=torch.uint8, device=DEV)
+        u = ctx.gptq_factor(hess, workspace=ws[:need])
+        assert torch.equal(u, want_u) and (ws[need:] == fill).all()
+        need = int(B.lib.dymoe_gptq_workspace_bytes(N, K))
+        ws = torch.full((need + 65536,), fill, dtype=torch.uint8, device=DEV)
+        got = ctx.gptq_quantize_pack(to_bf16(wb), want_u, 4, workspace=ws[:need])
+        assert all(torch.equal(a, b) for a, b in zip(got, want)) and (ws[need:] == fill).all()

@@ -149,6 +149,9 @@ def test_argument_validation_happens_before_any_device_work():
     gq = lib.dymoe_gptq_quantize_pack
     gw = int(lib.dymoe_gptq_workspace_bytes(100, 256))
     assert gw >= 100 * 256 * 4 + 64 * 128 * 4 and gw % 256 == 0 and lib.dymoe_gptq_workspace_bytes(0, 256) == 0
+    # the matrix in fp32 and a panel's errors of the row block that is not whole: 128 columns below 64 rows, 256 above
+    for n, kk, errors in ((63, 320, 128 * 64), (64, 320, 0), (65, 320, 256 * 64), (14336, 4096, 0), (14337, 4096, 256 * 64)):
+        assert lib.dymoe_gptq_workspace_bytes(n, kk) == (n * kk * 4 + 255) // 256 * 256 + errors * 4
     assert gq(None, P, P, 100, 256, 4, 64, P, P, P, P, gw, None) == B.ENOCTX
     assert gq(None, P, P, 100, 256, 4, 64, P, P, P, P, gw - 1, None) == B.ENOSPC
     assert gq(None, P, P, 100, 256, 3, 64, P, P, P, P, gw, None) == B.EINVAL
@@ -165,7 +168,10 @@ def test_argument_validation_happens_before_any_device_work():
     assert gh(None, P, 300, 256, 0, None, None) == B.EINVAL
     gf = lib.dymoe_gptq_factor
     fw = int(lib.dymoe_gptq_factor_workspace_bytes(256))
-    assert fw >= 2 * 256 * 256 * 4 + 64 * 256 * 4 and lib.dymoe_gptq_factor_workspace_bytes(0) == 0
+    assert fw >= 256 * 256 * 4 + 64 * 256 * 4 + 64 * 64 * 4 + 4 and lib.dymoe_gptq_factor_workspace_bytes(0) == 0
+    # one matrix, 64 rows of it, a 64 x 64 block and a number, each rounded up: nothing that grows with a second matrix
+    for kk in (64, 4096, 14336, 65536):
+        assert lib.dymoe_gptq_factor_workspace_bytes(kk) == kk * kk * 4 + 64 * kk * 4 + 64 * 64 * 4 + 256
     assert gf(None, P, 256, 0.01, 2 * P, P, fw, None) == B.ENOCTX
     assert gf(None, P, 256, 0.01, 2 * P, P, fw - 1, None) == B.ENOSPC
     assert gf(None, P, 200, 0.01, 2 * P, P, fw, None) == B.EINVAL
