@@ -12,11 +12,9 @@
 // The arithmetic is an exact sequence of binary32 operations, columns in
 // ascending order, one fused multiply-add per correction (this file is built
 // with -ffp-contract=off, the fma is written out): the codes must equal the
-// reference's bit for bit.  That fixes the structure: no matrix-core product
-// for the trailing update (it would round differently), but the same work as
-// a chain of fp32 FMAs in registers.
+// reference's bit for bit, so the corrections may not be regrouped.
 //
-// The fp32 matrix instructions of this chip are such a chain: v_mfma_f32_{16x16x4,32x32x2}_f32 give, bit for bit,
+// The fp32 matrix instructions of this chip do not regroup them: v_mfma_f32_{16x16x4,32x32x2}_f32 give, bit for bit,
 // what one fma after the other over ascending k gives, subnormals included (compared on 14 million random results with
 // equal, cancelling, tiny and subnormal operands; the tests sweep rows against the plain chain as well).  So the
 // corrections go through the matrix cores and keep the reference's bits: a register-only loop of those instructions holds
@@ -653,7 +651,8 @@ __device__ __forceinline__ void gq_chol_block(float* s_m, float* __restrict__ r)
 #pragma unroll
             for (int c = 0; c < 16; c++) {
                 const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[c]), p + c));
-                // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each
+                // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each (finite
+                // operands; see the solve kernel for infinite ones)
                 const float y = __builtin_amdgcn_rsqf(d);
                 const float s0 = d * y, l0 = a[c] * y;
                 const float sq = __builtin_fmaf(__builtin_fmaf(-s0, s0, d), 0.5f * y, s0);
@@ -737,6 +736,9 @@ __global__ __launch_bounds__(256) void gptq_chol_diag_kernel(const float* __rest
 // Step k's block row P (see above) against r = the diagonal block's factor, a workgroup per 64 columns j of P, a wavefront
 // 16 of them with four lanes each, as in the group kernel.  Bound: the chain of 64 steps (divide, hand over, correct), 9 us;
 // a lane per column took 17 us, twice per step (Cholesky's panel and the substitution were separate passes).
+// The quotient is the product with the reciprocal and one residual step.  For finite operands that differs from a division
+// in the last place at most; an infinite operand or quotient gives NaN where the division gives infinity, but it has no
+// place in a positive definite matrix: what it is subtracted from, a later pivot, becomes NaN either way.
 __global__ __launch_bounds__(256) void gptq_solve_kernel(const float* __restrict__ v, long K, long k, const float* __restrict__ r,
                                                          float* __restrict__ p_row, float* __restrict__ u)
 {
