@@ -477,6 +477,7 @@ __global__ __launch_bounds__(kAtThreads, 3) void attn_colsum_wide_kernel(
 // batch asks for the last head again where it is not whole.  A wavefront per workgroup, so that 4096 tokens reach 64
 // compute units.  The whole score, us, one head at a time and 256 tokens per workgroup / so: 4096 tokens x 32 heads 207 / 196,
 // 200 x 32 18.0 / 12.3, 200 x 12 14.1 / 12.1, 200 x 4 12.2 / 11.8, 200 x 1 11.2 / 11.3 (d = 128, causal).
+// This kernel alone in a trace of 4096 x 32: 10.6 -> 4.8 us.
 constexpr int kAtScoreThreads = kWave;
 
 __global__ __launch_bounds__(kAtScoreThreads) void attn_score_kernel(const float* __restrict__ partial, int T, int n_heads,
