@@ -44,7 +44,7 @@ __device__ __forceinline__ void route_select(float* lg, float* selp, int t, int 
 // token tw is finished (softmax, top-k) by wavefront tw mod NW.  Few tokens:
 // TW = 1 and the experts spread over 8 wavefronts; many tokens: TW = NW = 4, so
 // that a router row is read once per four tokens.
-template <int TW, int NCH, int NW>
+template <int TW, int NCH, int NW, int EB>
 __global__ __launch_bounds__(NW* kWave) void route_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
     const float* __restrict__ bias, int T, int H, int E, int k, int renorm,
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NW* kWave) void route_kernel(
     float* logit = smem;                                  // [TW][E]
     float* selp = smem + (size_t)TW * E + (size_t)wave * k;   // [NW][k]
     const int t0 = blockIdx.x * TW;
-    route_logits<TW, NCH, NW>(x, wg, bias, T, H, E, t0, logit);
+    route_logits<TW, NCH, NW, EB>(x, wg, bias, T, H, E, t0, logit);
     __syncthreads();
     for (int tw = wave; tw < TW; tw += NW) {
         const int t = t0 + tw;
@@ -423,13 +423,13 @@ __global__ __launch_bounds__(256) void token_norm_kernel(const uint16_t* __restr
     if (lane == 0) score[t] = n;
 }
 
-template <int TW, int NCH, int NW>
+template <int TW, int NCH, int NW, int EB>
 static int launch_route(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E,
                         int k, int renorm, int32_t* idx, float* w, float* probs, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((T + TW - 1) / TW);
     const size_t smem = ((size_t)TW * E + (size_t)NW * k) * sizeof(float);
-    dymoe_launch(ctx, DYMOE_K_ROUTE, (route_kernel<TW, NCH, NW>), dim3(blocks), dim3(NW * kWave), smem, st,
+    dymoe_launch(ctx, DYMOE_K_ROUTE, (route_kernel<TW, NCH, NW, EB>), dim3(blocks), dim3(NW * kWave), smem, st,
                        (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm, idx, w,
                        probs);
     DYMOE_HIP_LAUNCH_CHECK();
@@ -490,11 +490,28 @@ int dymoe_route_topk(dymoe_ctx* ctx, const void* x, const void* wg, const float*
     }
     // tokens per workgroup chosen so that their activations fit in 128 VGPRs;
     // few tokens: one per workgroup, its experts spread over 8 wavefronts
-    if (H <= 4096 && T >= 1024)
-        return dymoe::launch_route<4, 8, 4>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, st);
-    if (H <= 4096) return dymoe::launch_route<1, 8, 8>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, st);
-    if (H <= 8192) return dymoe::launch_route<1, 16, 8>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, st);
-    return dymoe::launch_route<1, 32, 8>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, st);
+#define DYMOE_ROUTE(TW_, NCH_, NW_, EB_) \
+    return dymoe::launch_route<TW_, NCH_, NW_, EB_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, st)
+    if (H <= 4096 && T >= 1024) DYMOE_ROUTE(4, 8, 4, 1);
+    // One token per workgroup: few rounds to memory (16 wavefronts from 17 experts on, unless the tokens alone keep more than
+    // a workgroup on every compute unit; registers for the row lengths there are), and no row requested twice.  us, before
+    // (8 wavefronts of 128 registers for any row, two experts a round) / now: 61 tokens x 2048, 128 experts 17.2 / 11.0;
+    // 512 x 4096, 8 experts 8.7 / 6.8; 24 x 4096, 8 experts 6.7 / 5.2; 16 x 256, 8 experts 4.8 / 3.8.
+    const bool many = E > 16 && T <= ctx->num_cu;
+    if (H <= 2048) {
+        if (many) DYMOE_ROUTE(1, 4, 16, 4);
+        if (E > 16) DYMOE_ROUTE(1, 4, 8, 4);
+        if (E > 8) DYMOE_ROUTE(1, 4, 8, 2);
+        DYMOE_ROUTE(1, 4, 8, 1);
+    }
+    if (H <= 4096) {
+        if (many) DYMOE_ROUTE(1, 8, 16, 2);
+        if (E > 8) DYMOE_ROUTE(1, 8, 8, 2);
+        DYMOE_ROUTE(1, 8, 8, 1);
+    }
+    if (H <= 8192) DYMOE_ROUTE(1, 16, 8, 1);
+    DYMOE_ROUTE(1, 32, 8, 1);
+#undef DYMOE_ROUTE
 }
 
 int dymoe_decode_front(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias,

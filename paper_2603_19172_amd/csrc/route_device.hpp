@@ -9,8 +9,10 @@ namespace dymoe {
 
 // Logits of tokens t0 .. t0+TW-1 into LDS (logit[tw * E + e]).  Every wavefront
 // of the workgroup keeps all TW activation rows in registers and computes the
-// experts e = wave, wave + NW, ...
-template <int TW, int NCH, int NW>
+// experts e = wave, wave + NW, ..., EB of them per round (all their rows
+// requested before the first is used): with one token the loop is nothing but
+// memory latency, one round trip per round.
+template <int TW, int NCH, int NW, int EB = (TW == 1) ? ((NCH <= 4) ? 4 : (NCH <= 8) ? 2 : 1) : 1>
 __device__ __forceinline__ void route_logits(const uint16_t* __restrict__ x,
                                              const uint16_t* __restrict__ wg,
                                              const float* __restrict__ bias, int T, int H, int E,
@@ -29,9 +31,6 @@ __device__ __forceinline__ void route_logits(const uint16_t* __restrict__ x,
                 xr[tw][c] = *reinterpret_cast<const uint4*>(x + (size_t)(t0 + tw) * H + col);
         }
     }
-    // A wavefront takes EB experts per round (all their rows requested before the first is used): with one token
-    // the loop is nothing but memory latency, one round trip per round.
-    constexpr int EB = (TW == 1) ? ((NCH <= 4) ? 4 : (NCH <= 8) ? 2 : 1) : 1;
     for (int e0 = wave; e0 < E; e0 += NW * EB) {
         uint4 wv[EB][NCH];
 #pragma unroll

@@ -228,6 +228,18 @@ def test_route_topk_many_experts_multi_token_wavefronts(ctx):
         _check_route(ctx, x, wg, None, 2)
 
 
+# a token per workgroup: rows up to 2048 / 4096 columns and beyond, one or several of a wavefront's experts per round, 8 or 16
+# wavefronts (16 up to as many tokens as compute units), remainders of experts in the last round
+@pytest.mark.parametrize("T,H,E,k", [(5, 2048, 8, 2), (5, 2048, 9, 3), (6, 2040, 17, 2), (7, 2056, 8, 2), (7, 2056, 9, 2),
+                                     (9, 4096, 33, 6), (9, 4104, 33, 2), (61, 2048, 130, 8), (127, 1024, 100, 5), (256, 512, 30, 4),
+                                     (257, 512, 30, 4), (257, 2304, 30, 4), (1025, 264, 17, 2)])
+def test_route_topk_one_token_per_workgroup(ctx, T, H, E, k):
+    c = synth.scaled(synth.CONFIGS["fine_grained"], config_id=17 + T, T=T, E=E, H=H, k=k)
+    x, _ = synth.activations(c)
+    wg, bias = synth.router(c)
+    _check_route(ctx, x, wg[:E], bias[:E], k, min_ok=0.8)
+
+
 def test_route_topk_without_probabilities_takes_the_one_kernel_form_and_agrees(ctx):
     """The two-pass router keeps its logits in the caller's probs array; a caller that passes none gets the
     one-kernel form.  Same experts (outside the margin) and the same gate weights either way."""
@@ -456,6 +468,22 @@ def test_ffn_gemm_ragged_tiles(ctx):
     err = rel_err_per_token(run_ffn(ctx, cfg, x, idx, w, bits_np, table, B.PATH_GEMM), ref)
     print("gemm ragged, 8-bit experts err=%.3e" % err)
     assert err <= FFN_TOL
+
+
+# the combining pass takes 1, 2, 4 or 8 slots at a time: whole and partial groups, slots of an expert that is left out, one
+# and several K splits (F = 128 / 4224)
+@pytest.mark.parametrize("F,k", [(128, 1), (128, 2), (128, 3), (4224, 4), (4224, 5), (128, 8), (4224, 9)])
+def test_ffn_gemm_combine_slots(ctx, F, k):
+    cfg = synth.scaled(synth.CONFIGS["tiny"], config_id=25 + k, T=11, H=128, F=F, E=10, k=k, tier_count=(10,))
+    x, _ = synth.activations(cfg)
+    idx, w = routed(cfg, x)
+    bits_np = np.array([16, 4, 2, 0, 8, 4, 2, 16, 4, 8], np.uint8)
+    host, dev, table, keep = build_layer(cfg, bits_np, path=B.PATH_GEMM)
+    y = run_ffn(ctx, cfg, x, idx, w, bits_np, table, B.PATH_GEMM)
+    ref = oracle_ffn(cfg, x, idx, w, bits_np, host)
+    some = (bits_np[idx] != 0).any(axis=1)                      # (a token whose only expert is left out: zeros)
+    assert some.any() and rel_err_per_token(y[some], ref[some]) <= FFN_TOL
+    assert (y[~some] == 0).all()
 
 
 def test_ffn_gemm_many_tiles_per_expert_and_two_k_splits(ctx):
