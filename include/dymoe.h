@@ -425,6 +425,22 @@ int dymoe_decode_step(dymoe_ctx* ctx, const void* x, const void* wg, const float
                       void* y, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * A layer's step on the grouped-GEMM path in as few launches as the steps' hand-overs allow: dymoe_route_topk,
+ * dymoe_rank_experts (prefill: by the row norms of x, left in token_score), dymoe_quantize_experts (quantize not 0; tile
+ * layout) and dymoe_moe_ffn_mixed(path = DYMOE_PATH_GEMM), with their arguments, layouts, limits and errors; every output
+ * (idx, w, probs, token_score, importance, load, bits, rank, the quantised formats, y) holds bit for bit what those calls
+ * in turn write.  The norms come from the router's launch, and ranking, bit widths and the GEMM's token grouping are one
+ * launch.  probs and rank must not be NULL; token_score may be in the decode phase.
+ * DYMOE_ENOTSUP outside E <= 256, T <= 8192, T * k <= 32768, k <= 256 and what the calls themselves cover: the caller then
+ * makes the calls.
+ */
+int dymoe_layer_step(dymoe_ctx* ctx, int phase, const void* x, const void* wg, const float* bias, int T, int H, int F, int E,
+                     int k, int renorm, int k_hh, int n_tiers, const int32_t* tier_count, const uint8_t* tier_bits,
+                     int floor_bits, const dymoe_expert_fmt* table, int group, int quantize, int out_dtype, int32_t* idx,
+                     float* w, float* probs, float* token_score, void* importance, int32_t* load, uint8_t* bits,
+                     int32_t* rank, void* y, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Diagnostic (tests, profiling): where the grouped-GEMM path of dymoe_moe_ffn_mixed leaves its token
  * grouping in the workspace, so that a caller can see which (token, slot) pair went to which row of which
  * tile (paper Sec. 4.2.1: the per-expert token lists Tokens_j).  Returns the byte offset of an int32 array

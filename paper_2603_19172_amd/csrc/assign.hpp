@@ -33,6 +33,19 @@ inline int make_tier_table(int E, int n_tiers, const int32_t* tier_count, const 
     return total == E ? DYMOE_OK : DYMOE_EINVAL;
 }
 
+// Bit width of the expert at rank position pos.  Every tier by a constant index: kernel arguments then are scalars loaded
+// once; indexed by the lane's own tier they are read from the argument segment in memory.
+__device__ __forceinline__ int tier_bits_at(int pos, const TierTable& tiers, int floor_bits)
+{
+    int b = tiers.bits[0], upto = 0;
+#pragma unroll
+    for (int i = 1; i < DYMOE_MAX_TIERS; i++) {
+        upto += tiers.count[i - 1];
+        b = (i < tiers.n && pos >= upto) ? tiers.bits[i] : b;
+    }
+    return b < floor_bits ? floor_bits : b;
+}
+
 // Expert e counts the experts that precede it in the order (importance
 // descending, load descending, index ascending) -> rank -> tier -> bits.
 // s_imp / s_load: all E values (LDS).  S adjacent lanes share an expert (S a
@@ -60,13 +73,7 @@ __device__ __forceinline__ void assign_shared(int e, int part, int E, const ImpT
 #pragma unroll
     for (int o = 1; o < S; o <<= 1) pos += __shfl_xor(pos, o, kWave);
     if (e >= E || part != 0) return;
-    int tier = 0, upto = tiers.count[0];
-    while (pos >= upto && tier + 1 < tiers.n) {
-        tier++;
-        upto += tiers.count[tier];
-    }
-    int b = tiers.bits[tier];
-    if (b < floor_bits) b = floor_bits;
+    const int b = tier_bits_at(pos, tiers, floor_bits);
     bits[e] = (uint8_t)b;
     if (rank) rank[e] = pos;
 }

@@ -104,6 +104,21 @@ __host__ __device__ inline bool dymoe_fmt_present(const dymoe_expert_fmt& ex, in
     return false;
 }
 
+// The bit widths (2, 4, 8, 16, added up) a table entry holds.  All its pointers are read at once: one after the other, each
+// behind the test of the last, they are two dozen trips to the cache.
+__device__ __forceinline__ int dymoe_formats_held(const dymoe_expert_fmt& ex)
+{
+    int held = 0;
+    auto all = [](const void* const (&p)[3]) { return (p[0] != nullptr) & (p[1] != nullptr) & (p[2] != nullptr); };
+    auto all8 = [](const uint8_t* const (&p)[3]) { return (p[0] != nullptr) & (p[1] != nullptr) & (p[2] != nullptr); };
+    const dymoe_expert_fmt e = ex;
+    held |= all(e.w) ? 16 : 0;
+    held |= (all8(e.q8) & all(e.s8) & all(e.z8)) ? 8 : 0;
+    held |= (all8(e.q4) & all(e.s4) & all(e.z4)) ? 4 : 0;
+    held |= (all8(e.q2) & all(e.s2) & all(e.z2)) ? 2 : 0;
+    return held;
+}
+
 namespace dymoe {
 
 constexpr int kWave = 64;
@@ -252,6 +267,18 @@ __device__ __forceinline__ int wave_sum_dpp_i32(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);
     return __builtin_amdgcn_readlane(v, 63);
+}
+
+// inclusive prefix sum over the 64 lanes
+__device__ __forceinline__ int wave_scan_dpp_i32(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1, 2, 4, 8: inside the rows of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);   // row_bcast15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);   // row_bcast31 into rows 2 and 3
+    return v;
 }
 
 __device__ __forceinline__ float wave_max_dpp(float v)

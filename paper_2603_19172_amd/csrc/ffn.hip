@@ -37,8 +37,14 @@ int ffn_gemv_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
                     int out_dtype, void* y, void* workspace, hipStream_t st);
 int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const float* w, const uint8_t* bits,
                     const dymoe_expert_fmt* table, int T, int H, int F, int E, int k,
-                    int out_dtype, void* y, void* workspace, hipStream_t st);
+                    int out_dtype, void* y, void* workspace, bool planned, hipStream_t st);
 bool ffn_gemm_fits(int T, int H, int F, int E, int k);
+bool rank_plan_fits(int T, int E, int k);
+int rank_plan_launch(dymoe_ctx* ctx, bool prefill, const void* x, const int32_t* idx, const float* probs, const float* score, int T, int H,
+                     int E, int k, int k_hh, const TierTable& tiers, int floor_bits, const dymoe_expert_fmt* table, void* importance,
+                     int32_t* load, uint8_t* bits, int32_t* rank, const FfnLayout& L, char* ws, hipStream_t st);
+int route_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E, int k, int renorm, int32_t* idx,
+                 float* w, float* probs, float* score, hipStream_t st);
 bool decode_fused_fits(int T, int H, int E, int k);
 int decode_fused_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, const TierTable& tt,
                         int floor_bits, const dymoe_expert_fmt* table, int T, int H, int F, int E, int k, int renorm,
@@ -83,7 +89,7 @@ extern "C" int dymoe_moe_ffn_mixed(dymoe_ctx* ctx, const void* x, const int32_t*
     if (path == DYMOE_PATH_GEMV)
         return dymoe::ffn_gemv_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, workspace,
                                       (hipStream_t)stream);
-    return dymoe::ffn_gemm_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, workspace,
+    return dymoe::ffn_gemm_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, workspace, false,
                                   (hipStream_t)stream);
 }
 
@@ -105,7 +111,7 @@ extern "C" int dymoe_moe_ffn_mixed_noalloc(dymoe_ctx* ctx, const void* x, const 
     ctx->timing_mask = 0;
     const int out = (path == DYMOE_PATH_GEMV)
         ? dymoe::ffn_gemv_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, ws, (hipStream_t)stream)
-        : dymoe::ffn_gemm_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, ws, (hipStream_t)stream);
+        : dymoe::ffn_gemm_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, ws, false, (hipStream_t)stream);
     ctx->timing_mask = mask;
     return out;
 }
@@ -131,4 +137,38 @@ extern "C" int dymoe_decode_step(dymoe_ctx* ctx, const void* x, const void* wg, 
     if (!ctx) return DYMOE_ENOCTX;
     return dymoe::decode_fused_launch(ctx, x, wg, bias, tt, floor_bits, table, T, H, F, E, k, renorm, out_dtype, idx, w,
                                       probs, importance, load, bits, rank, y, workspace, (hipStream_t)stream);
+}
+
+extern "C" int dymoe_layer_step(dymoe_ctx* ctx, int phase, const void* x, const void* wg, const float* bias, int T, int H, int F, int E,
+                                int k, int renorm, int k_hh, int n_tiers, const int32_t* tier_count, const uint8_t* tier_bits,
+                                int floor_bits, const dymoe_expert_fmt* table, int group, int quantize, int out_dtype, int32_t* idx,
+                                float* w, float* probs, float* token_score, void* importance, int32_t* load, uint8_t* bits,
+                                int32_t* rank, void* y, void* workspace, size_t workspace_bytes, void* stream)
+{
+    // the checks of the calls it stands for: routing, ranking, (quantiser,) FFN
+    DYMOE_REQUIRE(phase == DYMOE_PHASE_PREFILL || phase == DYMOE_PHASE_DECODE);
+    DYMOE_REQUIRE(T >= 1 && H > 0 && F > 0 && E > 0 && k > 0 && k <= E && H % 8 == 0);
+    DYMOE_REQUIRE(x && wg && idx && w && probs && importance && load && bits && rank);
+    DYMOE_REQUIRE(dymoe_aligned(x, 16) && dymoe_aligned(wg, 16));
+    const bool prefill = phase == DYMOE_PHASE_PREFILL;
+    if (prefill) DYMOE_REQUIRE(token_score && k_hh >= 0 && k_hh <= T);
+    DYMOE_REQUIRE(floor_bits == 0 || floor_bits == 2 || floor_bits == 4 || floor_bits == 8 || floor_bits == 16);
+    dymoe::TierTable tt;
+    DYMOE_REQUIRE(dymoe::make_tier_table(E, n_tiers, tier_count, tier_bits, tt) == DYMOE_OK);
+    int path = DYMOE_PATH_GEMM;
+    const int rc = ffn_check(x, idx, w, bits, table, T, H, F, E, k, group, out_dtype, &path, y, workspace, workspace_bytes);
+    if (rc != DYMOE_OK) return rc;
+    if (H > 16384 || !dymoe::rank_plan_fits(T, E, k)) return DYMOE_ENOTSUP;
+    if (!ctx) return DYMOE_ENOCTX;
+    hipStream_t st = (hipStream_t)stream;
+    int r = dymoe::route_launch(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, prefill ? token_score : nullptr, st);
+    if (r != DYMOE_OK) return r;
+    r = dymoe::rank_plan_launch(ctx, prefill, x, idx, probs, token_score, T, H, E, k, k_hh, tt, floor_bits, table, importance, load, bits,
+                                rank, dymoe::ffn_layout(T, H, F, E, k), (char*)workspace, st);
+    if (r != DYMOE_OK) return r;
+    if (quantize) {
+        r = dymoe_quantize_experts(ctx, table, bits, load, E, H, F, group, DYMOE_LAYOUT_TILE, stream);
+        if (r != DYMOE_OK) return r;
+    }
+    return dymoe::ffn_gemm_launch(ctx, x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, workspace, true, st);
 }

@@ -31,6 +31,7 @@
 
 #include "common.hpp"
 #include "ffn_layout.hpp"
+#include "plan_device.hpp"
 
 namespace dymoe {
 
@@ -38,311 +39,6 @@ constexpr int kGmThreads = 256;
 constexpr int kGmWaves = 4;         // one per SIMD; two workgroups share a compute unit
 constexpr int kBK = 128;            // K-tile
 constexpr int kXsBufBytes = kGemmTileTall * kBK * 2;   // one token tile in LDS: up to 160 rows x 256 bytes, no padding
-
-// Tiles of one expert with c pairs at b bits: 128 rows each, the last one shorter.  For the int4 and int2 formats a
-// last remainder of 1..32 rows is attached to the tile before it instead (5 fragments of 32 tokens, 160 rows): a
-// remainder tile streams and dequantises the expert's whole weight matrices once more for a handful of tokens, which
-// costs a third to a half of a full tile's time and all of its memory traffic.  (bf16 and int8 strips leave no
-// registers for a fifth pair of accumulators.)
-__device__ __forceinline__ bool plan_tall(int c, int b)
-{
-    const int r = c % kGemmTileM;
-    return (b == 4 || b == 2) && c > kGemmTileM && r >= 1 && r <= kGemmTileTall - kGemmTileM;
-}
-__device__ __forceinline__ int plan_tiles_of(int c, int b)
-{
-    return (c + kGemmTileM - 1) / kGemmTileM - (plan_tall(c, b) ? 1 : 0);
-}
-
-// ----------------------------------------------------------------------------
-// plan: counting sort of the (token, slot) pairs by expert + tile list
-// ints: counts[E] | offsets[E+1] | cursor[E] | ntiles (8 ints) | perm[P] | tiles[4*max_tiles] | draft[4*max_tiles]
-// (cursor: its first E BYTES hold the bit width every expert is run at, which is bits[e] unless the table lacks that
-// format, then 0; the GEMM and combine kernels read these instead of bits[])
-struct PlanPtrs {
-    int32_t* counts;
-    int32_t* offsets;
-    int32_t* cursor;
-    int32_t* ntiles;
-    int32_t* perm;
-    int32_t* tiles;
-};
-
-__host__ __device__ inline PlanPtrs plan_ptrs(int32_t* base, int E, int P)
-{
-    PlanPtrs p;
-    p.counts = base;
-    p.offsets = p.counts + E;
-    p.cursor = p.offsets + E + 1;
-    p.ntiles = p.cursor + E;
-    p.perm = p.ntiles + 8;
-    p.tiles = p.perm + P;
-    return p;
-}
-
-// Column order in which the code fields of a dword come out of the mask-and-or
-// extraction: inside every 8 columns (int4) 0,4,1,5,2,6,3,7; inside every 16
-// columns (int2) 0,8,1,9,...,7,15.  Inputs are packed pairs of 16-bit values.
-__device__ __forceinline__ uint4 perm8(const uint4 v)
-{
-    uint4 o;
-    o.x = (v.x & 0xffffu) | (v.z << 16);
-    o.y = (v.x >> 16) | (v.z & 0xffff0000u);
-    o.z = (v.y & 0xffffu) | (v.w << 16);
-    o.w = (v.y >> 16) | (v.w & 0xffff0000u);
-    return o;
-}
-
-__device__ __forceinline__ void perm16(const uint4 a, const uint4 b, uint4& o0, uint4& o1)
-{
-    o0.x = (a.x & 0xffffu) | (b.x << 16);
-    o0.y = (a.x >> 16) | (b.x & 0xffff0000u);
-    o0.z = (a.y & 0xffffu) | (b.y << 16);
-    o0.w = (a.y >> 16) | (b.y & 0xffff0000u);
-    o1.x = (a.z & 0xffffu) | (b.z << 16);
-    o1.y = (a.z >> 16) | (b.z & 0xffff0000u);
-    o1.z = (a.w & 0xffffu) | (b.w << 16);
-    o1.w = (a.w >> 16) | (b.w & 0xffff0000u);
-}
-
-// Three fp16 copies of the bf16 activations (exact inside fp16's normal range):
-// one in each of the column orders above and one in the natural order (int8
-// codes come out of a dword in order).  A thread converts 16 columns.
-__device__ __forceinline__ void prep_x(const uint16_t* __restrict__ x, long i, uint16_t* __restrict__ xh4,
-                                       uint16_t* __restrict__ xh2, uint16_t* __restrict__ xh8)
-{
-    const uint4 a = reinterpret_cast<const uint4*>(x)[2 * i];
-    const uint4 b = reinterpret_cast<const uint4*>(x)[2 * i + 1];
-    uint4 ha, hb;
-    ha.x = pack_half2(bf16_lo(a.x), bf16_hi(a.x)); ha.y = pack_half2(bf16_lo(a.y), bf16_hi(a.y));
-    ha.z = pack_half2(bf16_lo(a.z), bf16_hi(a.z)); ha.w = pack_half2(bf16_lo(a.w), bf16_hi(a.w));
-    hb.x = pack_half2(bf16_lo(b.x), bf16_hi(b.x)); hb.y = pack_half2(bf16_lo(b.y), bf16_hi(b.y));
-    hb.z = pack_half2(bf16_lo(b.z), bf16_hi(b.z)); hb.w = pack_half2(bf16_lo(b.w), bf16_hi(b.w));
-    reinterpret_cast<uint4*>(xh4)[2 * i] = perm8(ha);
-    reinterpret_cast<uint4*>(xh4)[2 * i + 1] = perm8(hb);
-    uint4 o0, o1;
-    perm16(ha, hb, o0, o1);
-    reinterpret_cast<uint4*>(xh2)[2 * i] = o0;
-    reinterpret_cast<uint4*>(xh2)[2 * i + 1] = o1;
-    reinterpret_cast<uint4*>(xh8)[2 * i] = ha;
-    reinterpret_cast<uint4*>(xh8)[2 * i + 1] = hb;
-}
-
-// One workgroup of 16 wavefronts.  Counting and scattering go through one
-// histogram per wavefront when they fit in LDS (E <= kPlanPrivE), so that the
-// atomics of a popular expert do not queue up across the whole workgroup; a
-// pair's position is then (expert offset) + (pairs of the expert in earlier
-// wavefronts) + (its turn inside its wavefront).  Tiles are laid out by one
-// thread per expert after a scan of the per-expert tile counts, staged in LDS
-// when the list fits, and sorted by rank counting.
-// The workgroups behind the first one make the fp16 copies of x (prep_x) meanwhile: neither needs the other, and as a
-// launch of their own the copies took 3 us (61 tokens of 2048) to 12 us (1357 of 4096) after the plan's 9 to 25.
-constexpr int kPlanThreads = 1024;
-constexpr int kPlanWaves = kPlanThreads / kWave;
-constexpr int kPlanPrivE = 256;        // 16 x 256 counters = 16 KiB
-constexpr int kPlanLdsTiles = 1024;    // 4 ints each = 16 KiB
-constexpr int kPlanRankStrides = 4;    // tile lists of up to 4 x 64 entries are ranked from registers
-
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __restrict__ idx,
-                                                            const uint8_t* __restrict__ bits,
-                                                            const dymoe_expert_fmt* __restrict__ table, int P, int E,
-                                                            int tile_m, int max_tiles,
-                                                            int32_t* __restrict__ plan, unsigned* __restrict__ flags,
-                                                            const uint16_t* __restrict__ x, long n16,
-                                                            uint16_t* __restrict__ xh4, uint16_t* __restrict__ xh2,
-                                                            uint16_t* __restrict__ xh8)
-{
-    if (blockIdx.x > 0) {
-        const long i = (long)(blockIdx.x - 1) * kPlanThreads + threadIdx.x;
-        if (i < n16) prep_x(x, i, xh4, xh2, xh8);
-        return;
-    }
-    __shared__ int32_t s_count[DYMOE_MAX_EXPERTS];
-    __shared__ int32_t s_off[DYMOE_MAX_EXPERTS + 1];
-    __shared__ int32_t s_tile0[DYMOE_MAX_EXPERTS + 1];       // first tile of each expert
-    __shared__ int32_t s_priv[kPlanWaves * kPlanPrivE];
-    __shared__ __attribute__((aligned(16))) int32_t s_draft[4 * kPlanLdsTiles];
-    __shared__ uint8_t s_bits[DYMOE_MAX_EXPERTS];
-    const PlanPtrs pp = plan_ptrs(plan, E, P);
-    const int tid = threadIdx.x, wave = tid / kWave;
-    const bool priv = E <= kPlanPrivE;
-    // (the expert indices of a batch of pairs are requested together and looked at afterwards: one pair at a time, every
-    // iteration waited a memory latency for its own index, 16 latencies per pass on the 128-expert layer)
-    constexpr int kPlanBatch = 16;
-    // up to 16 x 1024 pairs: a thread's indices stay in registers from the counting pass to the scattering pass, and are
-    // requested before the chain bits -> table entry -> its pointers
-    const bool one_pass = P <= kPlanBatch * kPlanThreads;
-    int es[kPlanBatch];
-    auto fetch = [&](int p0) {
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; u++) {
-            const int p = p0 + u * kPlanThreads;
-            es[u] = (p < P) ? idx[p] : -1;
-        }
-    };
-    if (one_pass) fetch(tid);
-    for (int e = tid; e < E; e += kPlanThreads) {
-        s_count[e] = 0;
-        int b = bits[e];
-        if (b == 16 || b == 8 || b == 4 || b == 2) {
-            // a format the table does not hold: the expert is left out, as at 0 bits.  Whether it had pairs is not
-            // known yet, but the decode path reports the same condition only for routed experts: checked below.
-            if (!dymoe_fmt_present(table[e], b)) b = 0x80 | b;
-        } else {
-            b = 0;
-        }
-        s_bits[e] = (uint8_t)b;
-    }
-    if (priv)
-        for (int i = tid; i < kPlanWaves * E; i += kPlanThreads) s_priv[i] = 0;
-    __syncthreads();
-    auto counted = [&](int e) {
-        if (e < 0 || e >= E) return false;
-        const int b = s_bits[e];
-        if (b & 0x80) {                       // routed to, selected format absent: say so, leave the pair out
-            atomicOr(flags, DYMOE_FLAG_FORMAT_MISSING);
-            return false;
-        }
-        return b != 0;
-    };
-    for (int p0 = tid; p0 < P || p0 == tid; p0 += kPlanBatch * kPlanThreads) {
-        if (!one_pass) fetch(p0);
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; u++)
-            if (counted(es[u])) atomicAdd(priv ? &s_priv[wave * E + es[u]] : &s_count[es[u]], 1);
-    }
-    __syncthreads();
-    if (priv) {
-        // per expert: total, and every wavefront's first position among the expert's pairs
-        for (int e = tid; e < E; e += kPlanThreads) {
-            int run = 0;
-            for (int wv = 0; wv < kPlanWaves; wv++) {
-                const int c = s_priv[wv * E + e];
-                s_priv[wv * E + e] = run;
-                run += c;
-            }
-            s_count[e] = run;
-        }
-        __syncthreads();
-    }
-    // exclusive scans over the experts (pairs and tiles): E is at most 1024, one wavefront walks it in strides
-    if (wave == 0) {
-        const int lane = tid;
-        int run = 0, trun = 0, with_tiles = 0;
-        for (int e0 = 0; e0 < E; e0 += kWave) {
-            const int e = e0 + lane;
-            const int c = (e < E) ? s_count[e] : 0;
-            const int nt_e = (e < E) ? plan_tiles_of(c, s_bits[e]) : 0;
-            int incl = c, tincl = nt_e;
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int a = __shfl_up(incl, o, kWave), b2 = __shfl_up(tincl, o, kWave);
-                if (lane >= o) {
-                    incl += a;
-                    tincl += b2;
-                }
-            }
-            if (e < E) {
-                s_off[e] = run + incl - c;
-                s_tile0[e] = trun + tincl - nt_e;
-            }
-            run += __shfl(incl, kWave - 1, kWave);
-            trun += __shfl(tincl, kWave - 1, kWave);
-            with_tiles += __popcll(__ballot(nt_e > 0));
-        }
-        if (lane == 0) {
-            s_off[E] = run;
-            s_tile0[E] = trun;
-            pp.ntiles[0] = trun;
-            pp.ntiles[1] = run;
-            pp.ntiles[2] = with_tiles;      // experts with at least one tile (the GEMM launches pick their XCD mapping by it)
-        }
-    }
-    __syncthreads();
-    const int nt_all = s_tile0[E];
-    // (written once for a draft in LDS and once for a draft in memory, so that neither is reached through flat accesses)
-    auto lay_out_and_rank = [&](int32_t* draft) {
-        for (int e = tid; e < E; e += kPlanThreads) {
-            const int c = s_count[e], b = s_bits[e];
-            int nt = s_tile0[e];
-            const int nt_end = nt + plan_tiles_of(c, b);
-            for (int m0 = 0; nt < nt_end; m0 += tile_m, nt++) {
-                const int rows = (nt == nt_end - 1) ? c - m0 : tile_m;     // (the last tile: up to 160 rows when tall)
-                draft[4 * nt + 0] = e;
-                draft[4 * nt + 1] = s_off[e] + m0;
-                draft[4 * nt + 2] = rows;
-                // cost key, roughly the time a workgroup spends on the tile: streaming (bf16)
-                // or dequantising (int4, int2) the weights costs the same whatever the number
-                // of tokens; the MFMA work grows with the 32-token fragments
-                draft[4 * nt + 3] = (b == 16 ? 100 : (b == 2 ? 60 : 61)) + 10 * ((rows + 31) >> 5);
-            }
-        }
-        __syncthreads();        // (workgroup-wide visibility also of the draft kept in global memory)
-        // Longest first: workgroups are dispatched in tile order, so the cheap tiles
-        // (few tokens) fill the end of the launch instead of stretching it.
-        // Rank by counting, (key descending, position ascending): a permutation.
-        // A wavefront per tile: its lanes share the comparisons against all tiles (one thread per tile walked the
-        // whole list alone, a dependent LDS read per step: 9 us for the 174 tiles of the 128-expert layer).
-        const int lane = tid & (kWave - 1);
-        if (nt_all <= kPlanRankStrides * kWave) {
-            // up to 256 tiles: a lane keeps the keys of tiles lane, 64 + lane, ... in registers, counts on the vector
-            // unit and the counts meet through DPP: a trip of the loop is one LDS read long (with the keys re-read
-            // and a ballot per stride counted on the scalar unit a trip was a chain of five dependent LDS reads and
-            // as many vector-to-scalar hand-overs: 8.2 us for the 197 tiles of the 128-expert layer)
-            int keys[kPlanRankStrides];
-#pragma unroll
-            for (int u = 0; u < kPlanRankStrides; u++) {
-                const int j = u * kWave + lane;
-                keys[u] = (j < nt_all) ? draft[4 * j + 3] : -1;          // (-1: below every key)
-            }
-            for (int i = wave; i < nt_all; i += kPlanWaves) {
-                const int rec = draft[4 * i + (lane & 3)];
-                const int key = __builtin_amdgcn_readlane(rec, 3);
-                int cnt = 0;
-#pragma unroll
-                for (int u = 0; u < kPlanRankStrides; u++) {
-                    const int j = u * kWave + lane;
-                    cnt += (keys[u] > key || (keys[u] == key && j < i)) ? 1 : 0;
-                }
-                const int pos = wave_sum_dpp_i32(cnt);
-                if (lane < 4) pp.tiles[4 * pos + lane] = rec;
-            }
-        } else {
-            for (int i = wave; i < nt_all; i += kPlanWaves) {
-                const int key = draft[4 * i + 3];
-                int pos = 0;        // the same in every lane: each stride of 64 tiles adds the number of its lanes that precede i
-                for (int j0 = 0; j0 < nt_all; j0 += kWave) {
-                    const int j = j0 + lane;
-                    const int kj = (j < nt_all) ? draft[4 * j + 3] : -1;
-                    pos += __popcll(__ballot(j < nt_all && (kj > key || (kj == key && j < i))));
-                }
-                if (lane < 4) pp.tiles[4 * pos + lane] = draft[4 * i + lane];
-            }
-        }
-    };
-    if (max_tiles <= kPlanLdsTiles) lay_out_and_rank(s_draft);
-    else lay_out_and_rank(pp.tiles + 4 * (size_t)max_tiles);
-    for (int e = tid; e < E; e += kPlanThreads) {
-        pp.counts[e] = s_count[e];
-        pp.offsets[e] = s_off[e];
-        reinterpret_cast<uint8_t*>(pp.cursor)[e] = (s_bits[e] & 0x80) ? 0 : s_bits[e];
-    }
-    if (tid == 0) pp.offsets[E] = s_off[E];
-    __syncthreads();
-    for (int e = tid; e < E; e += kPlanThreads) s_count[e] = 0;    // reused as the scatter cursor
-    __syncthreads();
-    // order inside an expert is arbitrary: every row of a tile is computed independently
-    for (int p0 = tid; p0 < P || p0 == tid; p0 += kPlanBatch * kPlanThreads) {
-        if (!one_pass) fetch(p0);
-#pragma unroll
-        for (int u = 0; u < kPlanBatch; u++) {
-            const int e = es[u];
-            if (!counted(e)) continue;
-            const int pos = s_off[e] + (priv ? atomicAdd(&s_priv[wave * E + e], 1) : atomicAdd(&s_count[e], 1));
-            pp.perm[pos] = p0 + u * kPlanThreads;
-        }
-    }
-}
 
 // ----------------------------------------------------------------------------
 // weight strips (32 rows x one K-tile of 128), as one lane holds them
@@ -1136,9 +832,13 @@ bool ffn_gemm_fits(int T, int H, int F, int E, int k)
     return true;
 }
 
+int plan_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const uint8_t* bits, const dymoe_expert_fmt* table, int T, int H,
+                int E, int k, const FfnLayout& L, char* ws, hipStream_t st);
+
+// planned: the workspace already holds the plan and the copies of x (rank_plan_launch)
 int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const float* w, const uint8_t* bits,
                     const dymoe_expert_fmt* table, int T, int H, int F, int E, int k,
-                    int out_dtype, void* y, void* workspace, hipStream_t st)
+                    int out_dtype, void* y, void* workspace, bool planned, hipStream_t st)
 {
     const FfnLayout L = ffn_layout(T, H, F, E, k);
     const int P = T * k;
@@ -1152,10 +852,10 @@ int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     int32_t* plan = reinterpret_cast<int32_t*>(ws + L.plan);
     const uint16_t* xb = (const uint16_t*)x;
 
-    const long n16 = (long)T * H / 16;
-    dymoe_launch(ctx, DYMOE_K_PLAN, plan_kernel, dim3((unsigned)(1 + (n16 + kPlanThreads - 1) / kPlanThreads)), dim3(kPlanThreads), 0,
-                 st, idx, bits, table, P, E, kGemmTileM, L.max_tiles, plan, ctx->device_flags, xb, n16, xh4, xh2, xh8);
-    DYMOE_HIP_LAUNCH_CHECK();
+    if (!planned) {
+        const int rc = plan_launch(ctx, x, idx, bits, table, T, H, E, k, L, ws, st);
+        if (rc != DYMOE_OK) return rc;
+    }
     // what the kernels after the plan take as the bit widths: the plan's copy, 0 where the table lacks the format
     const uint8_t* run_bits = reinterpret_cast<const uint8_t*>(plan_ptrs(plan, E, P).cursor);
     constexpr size_t kLdsBytes = kGemmLdsBytes;

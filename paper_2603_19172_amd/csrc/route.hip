@@ -40,6 +40,16 @@ __device__ __forceinline__ void route_select(float* lg, float* selp, int t, int 
     route_select_batch<1>(lgs, sps, ts, E, k, renorm, idx, w, probs, prob_sum, load_cnt);
 }
 
+// score[t] = norm of token t's row, by one wavefront: token_norm_kernel's value
+__device__ __forceinline__ void store_norm(const uint16_t* __restrict__ x, int t, int H, float* __restrict__ score)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const float n = token_norm(x + (size_t)t * H, H, lane);
+    if (lane == 0) score[t] = n;
+}
+
+// score (may be NULL) of the routing kernels below: the tokens' norms for a caller that ranks by them next, which would
+// otherwise wait for a launch of their own (5 us) behind this one.
 // A workgroup of NW wavefronts owns TW tokens: logits by all wavefronts, then
 // token tw is finished (softmax, top-k) by wavefront tw mod NW.  Few tokens:
 // TW = 1 and the experts spread over 8 wavefronts; many tokens: TW = NW = 4, so
@@ -48,7 +58,7 @@ template <int TW, int NCH, int NW, int EB>
 __global__ __launch_bounds__(NW* kWave) void route_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
     const float* __restrict__ bias, int T, int H, int E, int k, int renorm,
-    int32_t* __restrict__ idx, float* __restrict__ w, float* __restrict__ probs)
+    int32_t* __restrict__ idx, float* __restrict__ w, float* __restrict__ probs, float* __restrict__ score)
 {
     extern __shared__ float smem[];
     const int wave = threadIdx.x / kWave;
@@ -57,6 +67,11 @@ __global__ __launch_bounds__(NW* kWave) void route_kernel(
     const int t0 = blockIdx.x * TW;
     route_logits<TW, NCH, NW, EB>(x, wg, bias, T, H, E, t0, logit);
     __syncthreads();
+    if (score) {                                          // the tokens' norms, by the wavefronts that select last
+        const int tw = (wave + NW - 1) % NW;
+        static_assert(TW <= NW, "a wavefront takes one norm at most");
+        if (tw < TW && t0 + tw < T) store_norm(x, t0 + tw, H, score);
+    }
     for (int tw = wave; tw < TW; tw += NW) {
         const int t = t0 + tw;
         if (t >= T) break;
@@ -91,7 +106,7 @@ constexpr int kRmWChunks = kRmExperts * (kRmBK / 8) / kRmThreads;      // 16-byt
 __global__ __launch_bounds__(kRmThreads) void route_mfma_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
     const float* __restrict__ bias, int T, int H, int E, int k, int renorm,
-    int32_t* __restrict__ idx, float* __restrict__ w, float* __restrict__ probs)
+    int32_t* __restrict__ idx, float* __restrict__ w, float* __restrict__ probs, float* __restrict__ score)
 {
     extern __shared__ __attribute__((aligned(1024))) float smem[];
     static_assert(kRmTokens * (kRmBK / 8) == kRmThreads, "one chunk of the token tile per thread");
@@ -157,6 +172,8 @@ __global__ __launch_bounds__(kRmThreads) void route_mfma_kernel(
         }
         __syncthreads();
     }
+    if (score)
+        for (int tw = wave; tw < kRmTokens && t0 + tw < T; tw += kRmWaves) store_norm(x, t0 + tw, H, score);
     // wavefront `wave` finishes tokens wave, wave + 8, wave + 16, wave + 24, side by side
     {
         float* lgs[kRmBatch];
@@ -276,12 +293,14 @@ constexpr int kRsThreads = kRsWaves * kWave;
 // tokens only and reads their logits straight from memory (a lane holds every 64th expert).
 __global__ __launch_bounds__(kRsThreads) void route_select_kernel(
     int T, int E, int k, int renorm, int32_t* __restrict__ idx, float* __restrict__ w,
-    float* probs /* in: logits, out: probabilities */)
+    float* probs /* in: logits, out: probabilities */, const uint16_t* __restrict__ x, int H, float* __restrict__ score)
 {
     extern __shared__ float smem[];                                  // [4 wavefronts][kRsBatch][k], used when k > 64
     const int wave = threadIdx.x / kWave;
     const int t0 = (blockIdx.x * kRsWaves + wave) * kRsBatch;
     if (t0 >= T) return;
+    if (score)
+        for (int t = t0; t < min(t0 + kRsBatch, T); t++) store_norm(x, t, H, score);
     float* lgs[kRsBatch];
     float* sps[kRsBatch];
     int ts[kRsBatch];
@@ -425,13 +444,13 @@ __global__ __launch_bounds__(256) void token_norm_kernel(const uint16_t* __restr
 
 template <int TW, int NCH, int NW, int EB>
 static int launch_route(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E,
-                        int k, int renorm, int32_t* idx, float* w, float* probs, hipStream_t st)
+                        int k, int renorm, int32_t* idx, float* w, float* probs, float* score, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((T + TW - 1) / TW);
     const size_t smem = ((size_t)TW * E + (size_t)NW * k) * sizeof(float);
     dymoe_launch(ctx, DYMOE_K_ROUTE, (route_kernel<TW, NCH, NW, EB>), dim3(blocks), dim3(NW * kWave), smem, st,
                        (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm, idx, w,
-                       probs);
+                       probs, score);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
 }
@@ -448,50 +467,38 @@ int route_init()
     return DYMOE_OK;
 }
 
-}  // namespace dymoe
-
-extern "C" {
-
-int dymoe_route_topk(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias,
-                     int T, int H, int E, int k, int renorm,
-                     int32_t* idx, float* w, float* probs, void* stream)
+// dymoe_route_topk behind its checks; score not NULL: the tokens' norms as well
+int route_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E, int k, int renorm, int32_t* idx,
+                 float* w, float* probs, float* score, hipStream_t st)
 {
-    DYMOE_REQUIRE(T >= 0 && H > 0 && E > 0 && k > 0 && k <= E);
-    DYMOE_REQUIRE(H % 8 == 0);
-    DYMOE_REQUIRE(wg != nullptr && dymoe_aligned(wg, 16));
-    if (T > 0) DYMOE_REQUIRE(x && idx && w && dymoe_aligned(x, 16));  // empty step: nothing to read or write
-    if (E > DYMOE_MAX_EXPERTS || H > 16384) return DYMOE_ENOTSUP;
-    if (!ctx) return DYMOE_ENOCTX;
-    if (T == 0) return DYMOE_OK;
-    hipStream_t st = (hipStream_t)stream;
     // many tokens and experts: a dense contraction, on the matrix cores (when its tiles fit in the LDS it may ask for)
-    const size_t mfma_lds = (size_t)(dymoe::kRmTokens + dymoe::kRmExperts) * dymoe::kRmBK * 2 +
-                            (2 * (size_t)dymoe::kRmTokens * dymoe::kRmExperts + (size_t)dymoe::kRmTokens * E +
-                             (size_t)dymoe::kRmWaves * dymoe::kRmBatch * k) * sizeof(float);
+    const size_t mfma_lds = (size_t)(kRmTokens + kRmExperts) * kRmBK * 2 +
+                            (2 * (size_t)kRmTokens * kRmExperts + (size_t)kRmTokens * E +
+                             (size_t)kRmWaves * kRmBatch * k) * sizeof(float);
     // few token tiles: cut by experts too and select in a second pass (the logits wait in the probs array)
-    const int token_tiles = (T + dymoe::kRmTokens - 1) / dymoe::kRmTokens;
-    const size_t select_lds = (size_t)dymoe::kRsWaves * dymoe::kRsBatch * k * sizeof(float);
-    if (T >= 128 && E >= 64 && H % dymoe::kRlBK == 0 && probs && 2 * token_tiles <= ctx->num_cu) {
-        dymoe_launch(ctx, DYMOE_K_ROUTE, dymoe::route_logits_kernel<dymoe::kRlBK>, dim3((unsigned)token_tiles, (unsigned)((E + 31) / 32)),
-                     dim3(dymoe::kRlThreads), 0, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, probs);
+    const int token_tiles = (T + kRmTokens - 1) / kRmTokens;
+    const size_t select_lds = (size_t)kRsWaves * kRsBatch * k * sizeof(float);
+    if (T >= 128 && E >= 64 && H % kRlBK == 0 && probs && 2 * token_tiles <= ctx->num_cu) {
+        dymoe_launch(ctx, DYMOE_K_ROUTE, route_logits_kernel<kRlBK>, dim3((unsigned)token_tiles, (unsigned)((E + 31) / 32)),
+                     dim3(kRlThreads), 0, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, probs);
         DYMOE_HIP_LAUNCH_CHECK();
-        const int per_wg = dymoe::kRsWaves * dymoe::kRsBatch;
-        dymoe_launch(ctx, DYMOE_K_ROUTE_SELECT, dymoe::route_select_kernel, dim3((unsigned)((T + per_wg - 1) / per_wg)),
-                     dim3(dymoe::kRsThreads), select_lds, st, T, E, k, renorm, idx, w, probs);
+        const int per_wg = kRsWaves * kRsBatch;
+        dymoe_launch(ctx, DYMOE_K_ROUTE_SELECT, route_select_kernel, dim3((unsigned)((T + per_wg - 1) / per_wg)),
+                     dim3(kRsThreads), select_lds, st, T, E, k, renorm, idx, w, probs, (const uint16_t*)x, H, score);
         DYMOE_HIP_LAUNCH_CHECK();
         return DYMOE_OK;
     }
-    if (T >= 128 && E >= 32 && H % 128 == 0 && mfma_lds <= dymoe::kRouteMfmaMaxLds) {
-        dymoe_launch(ctx, DYMOE_K_ROUTE, dymoe::route_mfma_kernel, dim3((unsigned)((T + dymoe::kRmTokens - 1) / dymoe::kRmTokens)),
-                     dim3(dymoe::kRmThreads), mfma_lds, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm,
-                     idx, w, probs);
+    if (T >= 128 && E >= 32 && H % 128 == 0 && mfma_lds <= kRouteMfmaMaxLds) {
+        dymoe_launch(ctx, DYMOE_K_ROUTE, route_mfma_kernel, dim3((unsigned)((T + kRmTokens - 1) / kRmTokens)),
+                     dim3(kRmThreads), mfma_lds, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm,
+                     idx, w, probs, score);
         DYMOE_HIP_LAUNCH_CHECK();
         return DYMOE_OK;
     }
     // tokens per workgroup chosen so that their activations fit in 128 VGPRs;
     // few tokens: one per workgroup, its experts spread over 8 wavefronts
 #define DYMOE_ROUTE(TW_, NCH_, NW_, EB_) \
-    return dymoe::launch_route<TW_, NCH_, NW_, EB_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, st)
+    return launch_route<TW_, NCH_, NW_, EB_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, score, st)
     if (H <= 4096 && T >= 1024) DYMOE_ROUTE(4, 8, 4, 1);
     // One token per workgroup: few rounds to memory (16 wavefronts from 17 experts on, unless the tokens alone keep more than
     // a workgroup on every compute unit; registers for the row lengths there are), and no row requested twice.  us, before
@@ -512,6 +519,24 @@ int dymoe_route_topk(dymoe_ctx* ctx, const void* x, const void* wg, const float*
     if (H <= 8192) DYMOE_ROUTE(1, 16, 8, 1);
     DYMOE_ROUTE(1, 32, 8, 1);
 #undef DYMOE_ROUTE
+}
+
+}  // namespace dymoe
+
+extern "C" {
+
+int dymoe_route_topk(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias,
+                     int T, int H, int E, int k, int renorm,
+                     int32_t* idx, float* w, float* probs, void* stream)
+{
+    DYMOE_REQUIRE(T >= 0 && H > 0 && E > 0 && k > 0 && k <= E);
+    DYMOE_REQUIRE(H % 8 == 0);
+    DYMOE_REQUIRE(wg != nullptr && dymoe_aligned(wg, 16));
+    if (T > 0) DYMOE_REQUIRE(x && idx && w && dymoe_aligned(x, 16));  // empty step: nothing to read or write
+    if (E > DYMOE_MAX_EXPERTS || H > 16384) return DYMOE_ENOTSUP;
+    if (!ctx) return DYMOE_ENOCTX;
+    if (T == 0) return DYMOE_OK;
+    return dymoe::route_launch(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, nullptr, (hipStream_t)stream);
 }
 
 int dymoe_decode_front(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias,

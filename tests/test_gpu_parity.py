@@ -1088,3 +1088,103 @@ def test_gemv_rows_per_workgroup(ctx, T, H, F):
     ref = O.moe_ffn_mixed(x, idx, g.astype(np.float64), bits, [{"w": mats[0]}] + [{"q": host_q[e]} for e in range(1, 4)])
     # fp16 activations of the quantised formats: 2^-11 each, random sign over H and F terms; 2e-2 is the layer's bar
     assert rel_err_per_token(y.cpu().numpy().astype(np.float64), ref) <= 2e-2
+
+
+# the whole step in one call against the separate calls: tokens on both sides of the direct ranking (256), pairs on both sides of what
+# a thread keeps (2, 16, 32 a thread), experts and formats at their limits, tied scores at the boundary, every and no token heavy, staged
+# probabilities in one and several trips
+@pytest.mark.parametrize("phase,T,H,E,k,k_hh,bits,floor,quantize", [
+    ("prefill", 5, 128, 8, 2, 1, [16, 4, 2], 0, True), ("prefill", 17, 256, 30, 4, 3, [8, 4, 0], 0, False),
+    ("prefill", 256, 128, 256, 8, 13, [16, 4, 2], 4, False), ("prefill", 257, 256, 256, 8, 13, [8, 4, 2], 0, False),
+    ("prefill", 1024, 128, 8, 2, 51, [4, 2], 0, True), ("prefill", 1025, 128, 8, 2, 0, [4, 2], 0, False),
+    ("prefill", 1357, 128, 60, 6, 1357, [16, 4, 2], 0, False), ("prefill", 2048, 256, 16, 8, 700, [16, 4, 2], 0, False),
+    ("prefill", 2049, 128, 16, 8, 102, [16, 4, 2], 0, False), ("prefill", 4096, 128, 9, 8, 1, [16, 8, 2], 0, False),
+    ("prefill", 2500, 128, 4, 1, 1250, [4, 2], 0, False), ("decode", 5, 256, 8, 2, 0, [16, 4, 2], 0, True),
+    ("decode", 32, 128, 256, 8, 0, [8, 4, 2], 0, False), ("decode", 33, 128, 250, 3, 0, [4, 2], 8, False),
+    ("decode", 300, 128, 128, 7, 0, [16, 4, 2], 0, False), ("decode", 1, 128, 8, 2, 0, [4, 2], 0, False)])
+def test_layer_step_equals_the_separate_calls(ctx, phase, T, H, E, k, k_hh, bits, floor, quantize):
+    from paper_2603_19172_amd.layer import ExpertStore, MoELayer
+    g = torch.Generator(device=DEV).manual_seed(T * 1000 + E)
+    F = 128
+    x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
+    x[T // 2:] = x[:T - T // 2].clone()                                    # equal norms: order by token index
+    if T > 300:
+        x[T // 3] = float("nan")                                           # a token that is routed nowhere
+    wg = (torch.randn((E, H), generator=g, device=DEV) * 0.05).bfloat16()
+    w = [[(torch.randn(s, generator=g, device=DEV) * 0.05).bfloat16() for s in ((F, H), (F, H), (H, F))] for _ in range(E)]
+    counts = [E // 4] * (len(bits) - 1) + [E - (E // 4) * (len(bits) - 1)]
+    formats = sorted({max(b, floor) for b in bits} - {0, 16})
+    outs = []
+    for fused in (False, True):
+        layer = MoELayer(ctx, T, H, F, E, k, phase, counts, bits, k_hh=k_hh, floor_bits=floor, out_dtype=B.OUT_F32, path=B.PATH_GEMM)
+        store = ExpertStore(w, H, F, DEV, formats=formats, ctx=ctx)
+        if not quantize:
+            for b in formats:
+                ctx.quantize_experts(store.table, torch.full((E,), b, dtype=torch.uint8, device=DEV), None, E, H, F, layout=B.LAYOUT_TILE)
+        layer.ws.fill_(0xCC)
+        layer.score.fill_(0)
+        if fused:
+            assert layer.layer_step(x, wg, None, store, quantize, B._stream(None))
+        else:
+            layer.step(x, wg, None, store, quantize=quantize, fused_front=False)
+        o = int(B.lib.dymoe_ffn_plan_offset(T, H, F, E, k))
+        plan = layer.ws[o:o + 4 * (3 * E + 9 + T * k)].view(torch.int32).cpu().numpy()
+        pairs = plan[3 * E + 2]
+        perm = plan[3 * E + 9:3 * E + 9 + pairs]
+        groups = [sorted(perm[plan[E + e]:plan[E + e + 1]].tolist()) for e in range(E)]
+        outs.append(([layer.idx, layer.gate, layer.probs, layer.imp, layer.load, layer.bits, layer.rank, layer.y] +
+                     ([layer.score] if phase == "prefill" else []) + ([m[0] for b in formats for ex in store.q[b] for m in ex] if quantize else []),
+                     (plan[:2 * E + 1].tolist(), plan[3 * E + 1:3 * E + 4].tolist(), groups, layer, store)))
+    torch.cuda.synchronize()
+    (a, pa), (b, pb) = outs
+    assert pa[:3] == pb[:3]
+    load = a[4].long()
+    for i, (u, v) in enumerate(zip(a, b)):
+        if i >= len(a) - (3 * E * len(formats) if quantize else 0):
+            continue                                                       # formats: only where they were asked for, below
+        assert torch.equal(torch.nan_to_num(u.float(), nan=-7.0), torch.nan_to_num(v.float(), nan=-7.0)), i
+    assert int(load.sum()) == int((a[0] >= 0).sum())
+    if quantize:
+        for e in range(E):
+            be = int(a[5][e])
+            if be in formats and int(load[e]) > 0:
+                for m in range(3):
+                    for u, v in zip(pa[4].q[be][e][m], pb[4].q[be][e][m]):
+                        assert torch.equal(u, v)
+
+
+def test_layer_step_declines_what_it_does_not_cover(ctx):
+    from paper_2603_19172_amd.layer import ExpertStore, MoELayer
+    H = F = 128
+    for T, E, k in ((5, 257, 2), (4097, 8, 8)):
+        w = [[torch.zeros(s, dtype=torch.bfloat16, device=DEV) for s in ((F, H), (F, H), (H, F))] for _ in range(E)]
+        layer = MoELayer(ctx, T, H, F, E, k, "prefill", [E], [16], k_hh=1, path=B.PATH_GEMM)
+        store = ExpertStore(w, H, F, DEV, formats=(), ctx=ctx)
+        x, wg = torch.ones((T, H), device=DEV).bfloat16(), torch.zeros((E, H), dtype=torch.bfloat16, device=DEV)
+        assert not layer.layer_step(x, wg, None, store, False, B._stream(None))
+        layer.step(x, wg, None, store, quantize=False)                     # takes the separate calls
+        assert int(layer.load.sum()) == T * k
+
+
+# a plan of 1024 tiles (a thread each) and of one more (laid out in memory): 1024 experts with the same weights, a few of them with
+# more pairs than a tile holds; every row is what one expert with all the tokens gives
+@pytest.mark.parametrize("more", [0, 1])
+def test_plan_with_long_tile_lists(ctx, more):
+    E, H, F = 1024, 128, 128
+    per = torch.full((E,), 1)
+    per[:3] = torch.tensor([128, 128 + 33 * more, 2])
+    tok = torch.repeat_interleave(torch.arange(E), per).int()
+    tok = tok[torch.randperm(len(tok), generator=torch.Generator().manual_seed(5))].to(DEV)
+    T = len(tok)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
+    w = [(torch.randn(s, generator=g, device=DEV) * 0.05).bfloat16() for s in ((F, H), (F, H), (H, F))]
+    entry = {"w": w, "wt": [ctx.pack_tiles(m) for m in w], "q4": empty_q(F, H, 4)}
+    table, keep = B.make_expert_table([entry] * E, DEV)
+    ctx.quantize_experts(table, torch.full((1,), 4, dtype=torch.uint8, device=DEV), None, 1, H, F, layout=B.LAYOUT_TILE)
+    gate = torch.ones((T, 1), device=DEV)
+    bits = torch.full((E,), 4, dtype=torch.uint8, device=DEV)
+    y = ctx.moe_ffn_mixed(x, tok[:, None].contiguous(), gate, bits, table, F, out_dtype=B.OUT_F32, path=B.PATH_GEMM)
+    one = ctx.moe_ffn_mixed(x, torch.zeros((T, 1), dtype=torch.int32, device=DEV), gate, bits, table, F, out_dtype=B.OUT_F32,
+                            path=B.PATH_GEMM)
+    assert torch.equal(y, one)

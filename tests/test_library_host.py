@@ -117,6 +117,16 @@ def test_argument_validation_happens_before_any_device_work():
     assert df(None, P, P, None, 1, 256, 8, 2, 1, 3, tcp, tbp, 3, P, P, P, P, P, P, P, None) == B.EINVAL
     assert df(None, P, P, None, 1, 256, 8, 2, 1, 3, tcp, tbp, 0, P, P, None, P, P, P, None, None) == B.ENOCTX  # probs, rank optional
     assert df(None, P, P, None, 1, 256, 8, 2, 1, 3, tcp, tbp, 0, P, P, P, None, P, P, P, None) == B.EINVAL
+    # a layer's step in one call
+    wsl = int(lib.dymoe_workspace_bytes(7, 256, 512, 8, 2))
+    ls = lib.dymoe_layer_step
+    step = lambda phase=0, x=P, T=7, H=256, E=8, k=2, k_hh=1, floor=0, probs=P, score=P, rank=P, ws=wsl: ls(
+        None, phase, x, P, None, T, H, 512, E, k, 1, k_hh, 3, tcp, tbp, floor, P, 64, 0, 0, P, P, probs, score, P, P, P, rank, P, P, ws, None)
+    assert step() == B.ENOCTX and step(phase=1, score=None) == B.ENOCTX
+    assert step(phase=2) == B.EINVAL and step(x=None) == B.EINVAL and step(T=0) == B.EINVAL and step(E=9) == B.EINVAL
+    assert step(k_hh=8) == B.EINVAL and step(floor=3) == B.EINVAL and step(score=None) == B.EINVAL
+    assert step(probs=None) == B.EINVAL and step(rank=None) == B.EINVAL and step(ws=wsl - 1) == B.ENOSPC
+    assert step(H=192, ws=1 << 40) == B.ENOTSUP                                                # no GEMM path
     # attention-derived token score
     ta = lib.dymoe_token_score_attention
     aw = int(lib.dymoe_attention_workspace_bytes(77, 8))
