@@ -359,7 +359,7 @@ def main():
                             "GBps": round(ffn_bytes / (sec_ffn / args.steps) / 1e9, 1),
                             "frac_hbm": round(ffn_bytes / (sec_ffn / args.steps) / 1e9 / HBM_PEAK_GBS, 4),
                             "launch": ffn_mode, "us_per_step_by_launch_mode": ffn_launch_us,
-                            "note": "S1+S2+S3+S5 with the selected formats already materialised (dymoe_decode_step: two launches)"},
+                            "note": "S1+S2+S3+S5 with the selected formats already materialised (dymoe_decode_layer: two launches)"},
     }
 
     # ---------------------------------------------------------------- prefill 512 on the same layer

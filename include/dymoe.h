@@ -404,7 +404,7 @@ int dymoe_moe_ffn_mixed(dymoe_ctx* ctx, const void* x, const int32_t* idx, const
                         void* y, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * A whole decode step on resident formats in two launches: dymoe_decode_front
+ * A whole decode step on resident formats in two launches (three from nine router rows times tokens on): dymoe_decode_front
  * (Sec. 4.2.2 Eq. 3 importance, Sec. 4.3 assignment) and dymoe_moe_ffn_mixed on its
  * GEMV path (Sec. 4.1: the executor on the mixed-precision weight set), with the
  * front end worked out by every workgroup of the FFN's first launch for itself
@@ -423,6 +423,20 @@ int dymoe_decode_step(dymoe_ctx* ctx, const void* x, const void* wg, const float
                       int floor_bits, const dymoe_expert_fmt* table, int group, int out_dtype, int32_t* idx,
                       float* w, float* probs, float* importance, int32_t* load, uint8_t* bits, int32_t* rank,
                       void* y, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * dymoe_decode_step for more sizes and for a chain of layers: the same arguments, layouts, errors and outputs, bit for bit.
+ * y_prev NULL: x is the layer's input.  y_prev not NULL (one token): x [H] is the input of the layer before, y_prev [H] fp32
+ * its output, and the layer's input is what dymoe_residual_rmsnorm(x, y_prev, alpha) gives; it is written to h_out [H] bf16
+ * (not x) as well.  h_out and y_prev 16-byte aligned; y may be y_prev.
+ * DYMOE_ENOTSUP outside T <= 4 (with y_prev T = 1), E <= 128, E <= k * H beyond 64 experts, k <= 8, H a multiple of 64 up to
+ * 8192: the caller then makes the separate calls.
+ */
+int dymoe_decode_layer(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg,
+                       const float* bias, int T, int H, int F, int E, int k, int renorm, int n_tiers,
+                       const int32_t* tier_count, const uint8_t* tier_bits, int floor_bits, const dymoe_expert_fmt* table,
+                       int group, int out_dtype, int32_t* idx, float* w, float* probs, float* importance, int32_t* load,
+                       uint8_t* bits, int32_t* rank, void* y, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * A layer's step on the grouped-GEMM path in as few launches as the steps' hand-overs allow: dymoe_route_topk,

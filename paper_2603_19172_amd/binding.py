@@ -39,7 +39,7 @@ EXPORTS = [
     "dymoe_gptq_factor_workspace_bytes", "dymoe_gptq_factor",
     "dymoe_quantize_experts", "dymoe_pack_tiles", "dymoe_pack_code_tiles", "dymoe_moe_ffn_mixed", "dymoe_moe_ffn_mixed_noalloc",
     "dymoe_stream_copy", "dymoe_mfma_peak", "dymoe_device_flags", "dymoe_format_present",
-    "dymoe_decode_front", "dymoe_decode_step", "dymoe_layer_step", "dymoe_prefetch_submit", "dymoe_prefetch_wait", "dymoe_prefetch_done",
+    "dymoe_decode_front", "dymoe_decode_step", "dymoe_decode_layer", "dymoe_layer_step", "dymoe_prefetch_submit", "dymoe_prefetch_wait", "dymoe_prefetch_done",
     "dymoe_prefetch_release", "dymoe_residual_rmsnorm",
     "dymoe_cache_create", "dymoe_cache_create_pools", "dymoe_cache_destroy", "dymoe_cache_request", "dymoe_cache_request_at",
     "dymoe_cache_set_cyclic", "dymoe_cache_lookup",
@@ -105,6 +105,8 @@ lib.dymoe_decode_front.argtypes = [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i, _
 lib.dymoe_decode_step.restype = _i
 lib.dymoe_decode_step.argtypes = [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i, _i, _vp, _vp, _i, _vp, _i, _i,
                                   _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
+lib.dymoe_decode_layer.restype = _i
+lib.dymoe_decode_layer.argtypes = [_vp, _vp, _vp, C.c_float, _vp, _vp, _vp] + [_i] * 7 + [_vp, _vp, _i, _vp, _i, _i] + [_vp] * 9 + [_sz, _vp]
 lib.dymoe_layer_step.restype = _i
 lib.dymoe_layer_step.argtypes = [_vp, _i, _vp, _vp, _vp] + [_i] * 8 + [_vp, _vp, _i, _vp, _i, _i, _i] + [_vp] * 10 + [_sz, _vp]
 lib.dymoe_prefetch_submit.restype = _i

@@ -46,8 +46,9 @@ int rank_plan_launch(dymoe_ctx* ctx, bool prefill, const void* x, const int32_t*
 int route_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E, int k, int renorm, int32_t* idx,
                  float* w, float* probs, float* score, hipStream_t st);
 bool decode_fused_fits(int T, int H, int E, int k);
-int decode_fused_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, const TierTable& tt,
-                        int floor_bits, const dymoe_expert_fmt* table, int T, int H, int F, int E, int k, int renorm,
+bool decode_layer_fits(int T, int H, int E, int k, bool residual);
+int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
+                        const TierTable& tt, int floor_bits, const dymoe_expert_fmt* table, int T, int H, int F, int E, int k, int renorm,
                         int out_dtype, int32_t* idx, float* w, float* probs, float* importance, int32_t* load,
                         uint8_t* bits, int32_t* rank, void* y, void* workspace, hipStream_t st);
 }  // namespace dymoe
@@ -116,12 +117,11 @@ extern "C" int dymoe_moe_ffn_mixed_noalloc(dymoe_ctx* ctx, const void* x, const 
     return out;
 }
 
-extern "C" int dymoe_decode_step(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int F,
-                                 int E, int k, int renorm, int n_tiers, const int32_t* tier_count,
-                                 const uint8_t* tier_bits, int floor_bits, const dymoe_expert_fmt* table, int group,
-                                 int out_dtype, int32_t* idx, float* w, float* probs, float* importance,
-                                 int32_t* load, uint8_t* bits, int32_t* rank, void* y, void* workspace,
-                                 size_t workspace_bytes, void* stream)
+static int decode_layer(dymoe_ctx* ctx, bool (*fits)(int, int, int, int), const void* x, const float* y_prev, float alpha, void* h_out,
+                        const void* wg, const float* bias, int T, int H, int F, int E, int k, int renorm, int n_tiers,
+                        const int32_t* tier_count, const uint8_t* tier_bits, int floor_bits, const dymoe_expert_fmt* table, int group,
+                        int out_dtype, int32_t* idx, float* w, float* probs, float* importance, int32_t* load, uint8_t* bits,
+                        int32_t* rank, void* y, void* workspace, size_t workspace_bytes, void* stream)
 {
     // the front end's checks, then the FFN's
     DYMOE_REQUIRE(T >= 1 && H > 0 && F > 0 && E > 0 && k > 0 && k <= E && H % 8 == 0);
@@ -133,10 +133,37 @@ extern "C" int dymoe_decode_step(dymoe_ctx* ctx, const void* x, const void* wg, 
     int path = DYMOE_PATH_GEMV;
     const int rc = ffn_check(x, idx, w, bits, table, T, H, F, E, k, group, out_dtype, &path, y, workspace, workspace_bytes);
     if (rc != DYMOE_OK) return rc;
-    if (!dymoe::decode_fused_fits(T, H, E, k)) return DYMOE_ENOTSUP;
+    if (!fits(T, H, E, k)) return DYMOE_ENOTSUP;
     if (!ctx) return DYMOE_ENOCTX;
-    return dymoe::decode_fused_launch(ctx, x, wg, bias, tt, floor_bits, table, T, H, F, E, k, renorm, out_dtype, idx, w,
-                                      probs, importance, load, bits, rank, y, workspace, (hipStream_t)stream);
+    return dymoe::decode_fused_launch(ctx, x, y_prev, alpha, h_out, wg, bias, tt, floor_bits, table, T, H, F, E, k, renorm, out_dtype, idx,
+                                      w, probs, importance, load, bits, rank, y, workspace, (hipStream_t)stream);
+}
+
+extern "C" int dymoe_decode_step(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int F,
+                                 int E, int k, int renorm, int n_tiers, const int32_t* tier_count,
+                                 const uint8_t* tier_bits, int floor_bits, const dymoe_expert_fmt* table, int group,
+                                 int out_dtype, int32_t* idx, float* w, float* probs, float* importance,
+                                 int32_t* load, uint8_t* bits, int32_t* rank, void* y, void* workspace,
+                                 size_t workspace_bytes, void* stream)
+{
+    return decode_layer(ctx, dymoe::decode_fused_fits, x, nullptr, 0.0f, nullptr, wg, bias, T, H, F, E, k, renorm, n_tiers, tier_count,
+                        tier_bits, floor_bits, table, group, out_dtype, idx, w, probs, importance, load, bits, rank, y, workspace,
+                        workspace_bytes, stream);
+}
+
+extern "C" int dymoe_decode_layer(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg,
+                                  const float* bias, int T, int H, int F, int E, int k, int renorm, int n_tiers,
+                                  const int32_t* tier_count, const uint8_t* tier_bits, int floor_bits, const dymoe_expert_fmt* table,
+                                  int group, int out_dtype, int32_t* idx, float* w, float* probs, float* importance, int32_t* load,
+                                  uint8_t* bits, int32_t* rank, void* y, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (y_prev) DYMOE_REQUIRE(h_out && h_out != x && dymoe_aligned(y_prev, 16) && dymoe_aligned(h_out, 16));
+    auto plain = [](int t, int h, int e, int kk) { return dymoe::decode_layer_fits(t, h, e, kk, false); };
+    auto chained = [](int t, int h, int e, int kk) { return dymoe::decode_layer_fits(t, h, e, kk, true); };
+    bool (*fits)(int, int, int, int) = plain;
+    if (y_prev) fits = chained;
+    return decode_layer(ctx, fits, x, y_prev, alpha, h_out, wg, bias, T, H, F, E, k, renorm, n_tiers, tier_count, tier_bits, floor_bits,
+                        table, group, out_dtype, idx, w, probs, importance, load, bits, rank, y, workspace, workspace_bytes, stream);
 }
 
 extern "C" int dymoe_layer_step(dymoe_ctx* ctx, int phase, const void* x, const void* wg, const float* bias, int T, int H, int F, int E,

@@ -26,9 +26,12 @@
 //   sum_k (s q_k + m) x_k = s * (sum_k (2^n_k + q_k) x_k - sum_k 2^n_k x_k) + m * sum_k x_k.
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "assign.hpp"
 #include "ffn_layout.hpp"
+#include "norm_device.hpp"
 #include "route_device.hpp"
 
 namespace dymoe {
@@ -442,39 +445,141 @@ __global__ __launch_bounds__(kGvThreads) void gemv_phase1_kernel(
 
 // The first phase with the decode step's front end in front of it (router gating and top-k, decode importance,
 // bit-width assignment: the arithmetic of dymoe_decode_front, same device functions, same order of every sum, so the
-// same bits).  Every workgroup works the front end out for itself, in LDS, from the router (64 KiB for 8 experts of
-// 4096: read from L2 by all but the first workgroups) and goes on to its rows without a launch boundary and without
-// the chain of dependent loads (pair -> expert -> bit width) the stand-alone kernel starts with; workgroup (0, 0)
-// also writes the front end's outputs to memory for the second phase and for the caller.
-// Limits (checked by the launcher): T <= kFusedMaxTokens, E <= 64, k <= kFusedMaxK.
-constexpr int kFusedMaxTokens = 4, kFusedMaxK = 8, kFusedMaxE = 64;
+// same bits).  Every workgroup works the front end out for itself, in LDS, and goes on to its rows without a launch
+// boundary and without the chain of dependent loads (pair -> expert -> bit width) the stand-alone kernel starts with;
+// workgroup (0, 0) also writes the front end's outputs to memory for the second phase and for the caller.  FRONT says
+// where the logits come from:
+//   kFrontRouter    the router's rows, read by every workgroup (64 KiB for 8 experts of 4096: from L2 by all but the first)
+//   kFrontResidual  the same, of the row that residual and normalisation make of the layer before (one token): every
+//                   workgroup works that out as well, while its first router rows are on their way.  As a launch of its own
+//                   between two layers the step took 4.7 us of 55 (Mixtral shape, int4 experts).
+//   kFrontLogits    front_logits_kernel's launch (more router rows than a workgroup reads in one trip), which takes residual
+//                   and normalisation as well
+// Limits (checked by the launcher): T <= kFusedMaxTokens, E <= 64 NC, k <= kFusedMaxK.
+constexpr int kFusedMaxTokens = 4, kFusedMaxK = 8, kFusedMaxE = 128;
+enum { kFrontRouter, kFrontResidual, kFrontLogits };
 
-template <int NSEG, int NCH>
-__global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, const float* __restrict__ bias,
-    const dymoe_expert_fmt* __restrict__ table, int T, int H, int F, int E, int k, int renorm, TierTable tiers,
-    int floor_bits, int rows_per_block, int32_t* __restrict__ idx, float* __restrict__ w, float* __restrict__ probs,
-    float* __restrict__ importance, int32_t* __restrict__ load, uint8_t* __restrict__ bits,
-    int32_t* __restrict__ rank, float* __restrict__ hbuf, unsigned* __restrict__ flags)
+struct FusedFront {
+    const uint16_t* x;        // [T,H]; kFrontResidual: the layer before's input row h
+    const float* y_prev;      // kFrontResidual: ... its output, and where the normalised row goes
+    float alpha;
+    uint16_t* h_out;
+    const uint16_t* wg;
+    const float* bias;
+    const float* logits;      // kFrontLogits: [T,E]
+    int renorm, floor_bits;
+    TierTable tiers;
+    int32_t* idx;
+    float* w;
+    float* probs;
+    float* importance;
+    int32_t* load;
+    uint8_t* bits;
+    int32_t* rank;
+};
+
+// Logits of one token from its row in LDS, which is made between the request for the first router rows and their use
+// (route_logits' arithmetic for TW = 1).
+template <int NCH, typename MakeRow>
+__device__ __forceinline__ void route_logits_of_row(const uint16_t* s_row, const uint16_t* __restrict__ wg, const float* __restrict__ bias,
+                                                    int H, int E, float* logit, MakeRow make_row)
 {
-    __shared__ float s_logit[kFusedMaxE];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    constexpr int EB = (NCH <= 8) ? 2 : 1;
+    uint4 wv[EB][NCH], xr[NCH];
+    auto fetch = [&](int e0) {
+#pragma unroll
+        for (int i = 0; i < EB; i++) {
+            const uint16_t* row = wg + (size_t)min(e0 + i * kGvWaves, E - 1) * H;
+#pragma unroll
+            for (int c = 0; c < NCH; c++) {
+                wv[i][c] = make_uint4(0, 0, 0, 0);
+                if (c * kWave * 8 < H) wv[i][c] = load_global<uint4>(row + min((c * kWave + lane) * 8, H - 8));
+            }
+        }
+    };
+    fetch(wave);
+    make_row();
+#pragma unroll
+    for (int c = 0; c < NCH; c++) {
+        const int col = (c * kWave + lane) * 8;
+        xr[c] = make_uint4(0, 0, 0, 0);
+        if (col < H) xr[c] = *reinterpret_cast<const uint4*>(s_row + col);
+    }
+    for (int e0 = wave; e0 < E; e0 += kGvWaves * EB) {
+        if (e0 != wave) fetch(e0);
+#pragma unroll
+        for (int i = 0; i < EB; i++) {
+            const int e = e0 + i * kGvWaves;
+            float acc = 0.0f;
+#pragma unroll
+            for (int c = 0; c < NCH; c++)
+                if (c * kWave * 8 < H) {
+                    acc = dot2_bf16(wv[i][c].x, xr[c].x, acc);
+                    acc = dot2_bf16(wv[i][c].y, xr[c].y, acc);
+                    acc = dot2_bf16(wv[i][c].z, xr[c].z, acc);
+                    acc = dot2_bf16(wv[i][c].w, xr[c].w, acc);
+                }
+            const float b = (bias && e < E) ? bias[e] : 0.0f;
+            const float s = wave_sum(acc);
+            if (lane == 0 && e < E) logit[e] = s + b;
+        }
+    }
+}
+
+template <int NSEG, int NCH, int NC, int FRONT>
+__global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
+    const FusedFront f, const dymoe_expert_fmt* __restrict__ table, int T, int H, int F, int E, int k, int rows_per_block,
+    float* __restrict__ hbuf, unsigned* __restrict__ flags)
+{
+    __shared__ float s_logit[64 * NC];
     __shared__ float s_selp[kFusedMaxK];
-    __shared__ float s_imp[kFusedMaxE];
-    __shared__ int32_t s_load[kFusedMaxE];
+    __shared__ float s_imp[64 * NC];
+    __shared__ int32_t s_load[64 * NC];
     __shared__ int32_t s_idx[kFusedMaxTokens * kFusedMaxK];
     __shared__ float s_w[kFusedMaxTokens * kFusedMaxK];
-    __shared__ float s_probs[kFusedMaxTokens * kFusedMaxE];
-    __shared__ uint8_t s_bits[kFusedMaxE];
-    __shared__ int32_t s_rank[kFusedMaxE];
+    __shared__ float s_probs[kFusedMaxTokens * 64 * NC];
+    __shared__ uint8_t s_bits[64 * NC];
+    __shared__ int32_t s_rank[64 * NC];
+    __shared__ float s_part[kNormThreads / kWave];
+    __shared__ __attribute__((aligned(16))) uint16_t s_row[FRONT == kFrontResidual ? NSEG * kSeg : 8];
     const int wave = threadIdx.x / kWave;
+    const bool first = blockIdx.x == 0 && blockIdx.y == 0;
     for (int e = threadIdx.x; e < E; e += kGvThreads) {
         s_imp[e] = 0.0f;
         s_load[e] = 0;
     }
     for (int t = 0; t < T; t++) {
-        route_logits<1, NCH, kGvWaves>(x, wg, bias, T, H, E, t, s_logit);
+        if constexpr (FRONT == kFrontResidual) {
+            route_logits_of_row<NCH>(s_row, f.wg, f.bias, H, E, s_logit, [&] {
+                float v[NSEG][8], ss = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NSEG; i++) {
+                    const int j = (i * kNormThreads + (int)threadIdx.x) * 8;
+                    if (j < H) {
+                        residual_value<float, true>(f.x, f.y_prev, f.alpha, j, v[i]);
+                        residual_square<true>(v[i], ss);
+                    }
+                }
+                const float inv = residual_inv_rms(ss, H, s_part);
+#pragma unroll
+                for (int i = 0; i < NSEG; i++) {
+                    const int j = (i * kNormThreads + (int)threadIdx.x) * 8;
+                    if (j < H) {
+                        const uint4 o = residual_pack(v[i], inv);
+                        *reinterpret_cast<uint4*>(s_row + j) = o;
+                        if (first) *reinterpret_cast<uint4*>(f.h_out + j) = o;
+                    }
+                }
+                __syncthreads();
+            });
+        } else if constexpr (FRONT == kFrontLogits) {
+            for (int e = threadIdx.x; e < E; e += kGvThreads) s_logit[e] = f.logits[(size_t)t * E + e];
+        } else {
+            route_logits<1, NCH, kGvWaves>(f.x, f.wg, f.bias, T, H, E, t, s_logit);
+        }
         __syncthreads();
-        if (wave == 0) route_select_fixed<1>(s_logit, s_selp, t, E, k, renorm, s_idx, s_w, s_probs, s_imp, s_load);
+        if (wave == 0) route_select_fixed<NC>(s_logit, s_selp, t, E, k, f.renorm, s_idx, s_w, s_probs, s_imp, s_load);
         __syncthreads();
     }
     for (int e = threadIdx.x; e < E; e += kGvThreads) {
@@ -482,27 +587,41 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
         s_imp[e] = (T <= 1) ? g : g / (float)T;
     }
     __syncthreads();
-    assign_all<float>(kGvThreads, E, s_imp, s_load, tiers, floor_bits, s_bits, s_rank);
-    __syncthreads();
-    if (blockIdx.x == 0 && blockIdx.y == 0) {
-        for (int i = threadIdx.x; i < T * k; i += kGvThreads) {
-            idx[i] = s_idx[i];
-            w[i] = s_w[i];
-        }
-        if (probs)
-            for (int i = threadIdx.x; i < T * E; i += kGvThreads) probs[i] = s_probs[i];
-        for (int e = threadIdx.x; e < E; e += kGvThreads) {
-            importance[e] = s_imp[e];
-            load[e] = s_load[e];
-            bits[e] = s_bits[e];
-            if (rank) rank[e] = s_rank[e];
-        }
-    }
     const int p = (int)gridDim.y - 1 - (int)blockIdx.y;
     const int e = s_idx[p];
-    const int b = s_bits[e];
-    if (b != 16 && b != 8 && b != 4 && b != 2) return;
-    phase1_pair<NSEG>(x, table, p, e, b, H, F, k, rows_per_block, hbuf, flags);
+    int b = 0;
+    if (first) {
+        assign_all<float>(kGvThreads, E, s_imp, s_load, f.tiers, f.floor_bits, s_bits, s_rank);
+        __syncthreads();
+        for (int i = threadIdx.x; i < T * k; i += kGvThreads) {
+            f.idx[i] = s_idx[i];
+            f.w[i] = s_w[i];
+        }
+        if (f.probs)
+            for (int i = threadIdx.x; i < T * E; i += kGvThreads) f.probs[i] = s_probs[i];
+        for (int i = threadIdx.x; i < E; i += kGvThreads) {
+            f.importance[i] = s_imp[i];
+            f.load[i] = s_load[i];
+            f.bits[i] = s_bits[i];
+            if (f.rank) f.rank[i] = s_rank[i];
+        }
+        b = s_bits[max(e, 0)];
+    } else if (e >= 0) {
+        // the others need the bit width of one expert: its position is the number of lanes whose experts precede it
+        const float mi = s_imp[e];
+        const int ml = s_load[e];
+        int pos = 0;
+#pragma unroll
+        for (int c = 0; c < NC; c++) {
+            const int j = c * kWave + (int)(threadIdx.x & (kWave - 1));
+            const float oi = s_imp[min(j, E - 1)];
+            const int ol = s_load[min(j, E - 1)];
+            pos += __popcll(__ballot(j < E && (oi > mi || (oi == mi && (ol > ml || (ol == ml && j < e))))));
+        }
+        b = tier_bits_at(pos, f.tiers, f.floor_bits);
+    }
+    if (e < 0 || (b != 16 && b != 8 && b != 4 && b != 2)) return;
+    phase1_pair<NSEG>(FRONT == kFrontResidual ? s_row : f.x, table, p, e, b, H, F, k, rows_per_block, hbuf, flags);
 }
 
 // ---------------------------------------------------------------- phase 2
@@ -821,11 +940,32 @@ int ffn_gemv_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
 // Whether the fused decode step covers these sizes.
 bool decode_fused_fits(int T, int H, int E, int k)
 {
-    return T >= 1 && T <= kFusedMaxTokens && E <= kFusedMaxE && k <= kFusedMaxK && H % 64 == 0 && H <= 4 * kSeg;
+    return T >= 1 && T <= kFusedMaxTokens && E <= 64 && k <= kFusedMaxK && H % 64 == 0 && H <= 4 * kSeg;
 }
 
-int decode_fused_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, const TierTable& tt,
-                        int floor_bits, const dymoe_expert_fmt* table, int T, int H, int F, int E, int k, int renorm,
+// Where the logits come from: a launch of their own (3 us) unless a workgroup has all the router rows it needs in one trip to
+// memory (4 wavefronts, two rows each up to 4096 columns): every further trip costs every workgroup of the first phase 2 to 3
+// us.  us a step, in the workgroups / apart: 8 experts x 4096, one token 15.2 / 16.5, four 32.0 / 30.8; 16 x 4096 20.5 / 19.4;
+// 30 x 2048 18.3 / 15.4; 60 x 512 21.7 / 14.0; 64 x 1024, four tokens 71.9 / 38.5.  They wait in the workspace's part area,
+// P * H floats at least.
+static bool fused_logits_apart(int T, int H, int E, int k)
+{
+    return (long)T * E > (H <= 2 * kSeg ? 2 * kGvWaves : kGvWaves) && (size_t)E <= (size_t)k * H;
+}
+
+// ... and the decode layer: up to kFusedMaxE experts, and one token behind the layer before's residual
+bool decode_layer_fits(int T, int H, int E, int k, bool residual)
+{
+    if (T < 1 || T > (residual ? 1 : kFusedMaxTokens) || E > kFusedMaxE || k > kFusedMaxK || H % 64 != 0 || H > 4 * kSeg) return false;
+    return E <= 64 || fused_logits_apart(T, H, E, k);
+}
+
+int front_logits_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
+                        int T, int H, int E, float* logits, hipStream_t st);
+
+// y_prev not NULL: x is the layer before's input, y_prev its output, and the normalised row goes to h_out as well
+int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
+                        const TierTable& tt, int floor_bits, const dymoe_expert_fmt* table, int T, int H, int F, int E, int k, int renorm,
                         int out_dtype, int32_t* idx, float* w, float* probs, float* importance, int32_t* load,
                         uint8_t* bits, int32_t* rank, void* y, void* workspace, hipStream_t st)
 {
@@ -835,21 +975,38 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const void* wg, const flo
     const int nseg1 = (H + kSeg - 1) / kSeg;
     const int rows1 = phase1_rows_per_block((long)F * P);
     const dim3 g1((unsigned)((F + rows1 - 1) / rows1), (unsigned)P);
-    const uint16_t* xb = (const uint16_t*)x;
-    const uint16_t* wb = (const uint16_t*)wg;
+    FusedFront f = {};
+    f.x = (const uint16_t*)x; f.y_prev = y_prev; f.alpha = alpha; f.h_out = (uint16_t*)h_out;
+    f.wg = (const uint16_t*)wg; f.bias = bias; f.renorm = renorm; f.floor_bits = floor_bits; f.tiers = tt;
+    f.idx = idx; f.w = w; f.probs = probs; f.importance = importance; f.load = load; f.bits = bits; f.rank = rank;
+    auto go = [&](auto kernel) {
+        dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, kernel, g1, dim3(kGvThreads), 0, st, f, table, T, H, F, E, k, rows1, hbuf,
+                     ctx->device_flags);
+    };
     // NCH: 16-byte chunks of an activation row per lane, as in dymoe_decode_front (8 up to 4096 columns, then 16)
-#define DYMOE_FUSED(NSEG_, NCH_)                                                                                        \
-    dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (decode_fused_phase1_kernel<NSEG_, NCH_>), g1, dim3(kGvThreads), 0, st, xb, wb,  \
-                 bias, table, T, H, F, E, k, renorm, tt, floor_bits, rows1, idx, w, probs, importance, load, bits, rank, hbuf,  \
-                 ctx->device_flags)
-    switch (nseg1) {
-    case 1: DYMOE_FUSED(1, 8); break;
-    case 2: DYMOE_FUSED(2, 8); break;
-    case 3: DYMOE_FUSED(3, 16); break;
-    case 4: DYMOE_FUSED(4, 16); break;
-    default: return DYMOE_ENOTSUP;
+    auto by_width = [&](auto experts, auto front) {
+        constexpr int NC = decltype(experts)::value, FR = decltype(front)::value;
+        switch (nseg1) {
+        case 1: go(decode_fused_phase1_kernel<1, 8, NC, FR>); break;
+        case 2: go(decode_fused_phase1_kernel<2, 8, NC, FR>); break;
+        case 3: go(decode_fused_phase1_kernel<3, 16, NC, FR>); break;
+        default: go(decode_fused_phase1_kernel<4, 16, NC, FR>); break;
+        }
+    };
+    if (nseg1 > 4) return DYMOE_ENOTSUP;
+    if (fused_logits_apart(T, H, E, k)) {
+        float* logits = reinterpret_cast<float*>((char*)workspace + L.part);
+        const int rc = front_logits_launch(ctx, x, y_prev, alpha, h_out, wg, bias, T, H, E, logits, st);
+        if (rc != DYMOE_OK) return rc;
+        f.logits = logits;
+        if (y_prev) f.x = (const uint16_t*)h_out;
+        if (E <= 64) by_width(std::integral_constant<int, 1>(), std::integral_constant<int, kFrontLogits>());
+        else by_width(std::integral_constant<int, 2>(), std::integral_constant<int, kFrontLogits>());
+    } else if (y_prev) {
+        by_width(std::integral_constant<int, 1>(), std::integral_constant<int, kFrontResidual>());
+    } else {
+        by_width(std::integral_constant<int, 1>(), std::integral_constant<int, kFrontRouter>());
     }
-#undef DYMOE_FUSED
     DYMOE_HIP_LAUNCH_CHECK();
     return phase2_launch(ctx, hbuf, idx, w, bits, table, T, H, F, E, k, out_dtype, y, st);
 }

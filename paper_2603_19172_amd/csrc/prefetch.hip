@@ -4,14 +4,11 @@
 #include <math.h>
 
 #include "common.hpp"
+#include "norm_device.hpp"
 
 namespace dymoe {
 
-// v = h[t,:] + alpha * y[t,:];  h_out[t,:] = bf16(v / rms(v)), fp32 arithmetic.  One workgroup per token: a thread
-// takes 8 consecutive elements at a time (16-byte loads; VEC = false: one element at a time, for row lengths or
-// pointers that rule those out), the squares are summed per thread, per wavefront, then over the wavefronts in order.
-constexpr int kNormThreads = 256;
-
+// h_out[t,:] = bf16 of (h + alpha * y) / rms (norm_device.hpp), one workgroup per token.
 template <typename YT, bool VEC>
 __global__ __launch_bounds__(kNormThreads) void residual_rmsnorm_kernel(const uint16_t* __restrict__ h,
                                                                        const YT* __restrict__ y, float alpha,
@@ -23,57 +20,18 @@ __global__ __launch_bounds__(kNormThreads) void residual_rmsnorm_kernel(const ui
     const YT* yr = y + (size_t)t * H;
     uint16_t* orow = out + (size_t)t * H;
     constexpr int W = VEC ? 8 : 1;
-    auto value = [&](int j, float (&v)[W]) {
-        if constexpr (VEC) {
-            float hv[8], yv[8];
-            const uint4 hraw = *reinterpret_cast<const uint4*>(hr + j);
-            hv[0] = bf16_lo(hraw.x); hv[1] = bf16_hi(hraw.x); hv[2] = bf16_lo(hraw.y); hv[3] = bf16_hi(hraw.y);
-            hv[4] = bf16_lo(hraw.z); hv[5] = bf16_hi(hraw.z); hv[6] = bf16_lo(hraw.w); hv[7] = bf16_hi(hraw.w);
-            if constexpr (sizeof(YT) == 2) {
-                const uint4 yraw = *reinterpret_cast<const uint4*>(yr + j);
-                yv[0] = bf16_lo(yraw.x); yv[1] = bf16_hi(yraw.x); yv[2] = bf16_lo(yraw.y); yv[3] = bf16_hi(yraw.y);
-                yv[4] = bf16_lo(yraw.z); yv[5] = bf16_hi(yraw.z); yv[6] = bf16_lo(yraw.w); yv[7] = bf16_hi(yraw.w);
-            } else {
-                const float4 a = *reinterpret_cast<const float4*>(yr + j);
-                const float4 b = *reinterpret_cast<const float4*>(yr + j + 4);
-                yv[0] = a.x; yv[1] = a.y; yv[2] = a.z; yv[3] = a.w; yv[4] = b.x; yv[5] = b.y; yv[6] = b.z; yv[7] = b.w;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[i] = fmaf(alpha, yv[i], hv[i]);
-        } else {
-            float yv;
-            if constexpr (sizeof(YT) == 2) yv = bf16_bits_to_f32(yr[j]);
-            else yv = yr[j];
-            v[0] = fmaf(alpha, yv, bf16_bits_to_f32(hr[j]));
-        }
-    };
     float ss = 0.0f;
     for (int j = threadIdx.x * W; j < H; j += kNormThreads * W) {
         float v[W];
-        value(j, v);
-#pragma unroll
-        for (int i = 0; i < W; i++) ss = fmaf(v[i], v[i], ss);
+        residual_value<YT, VEC>(hr, yr, alpha, j, v);
+        residual_square<VEC>(v, ss);
     }
-    ss = wave_sum(ss);
-    if ((threadIdx.x & (kWave - 1)) == 0) s_part[threadIdx.x / kWave] = ss;
-    __syncthreads();
-    float tot = 0.0f;
-#pragma unroll
-    for (int wv = 0; wv < kNormThreads / kWave; wv++) tot += s_part[wv];
-    const float inv = (tot > 0.0f) ? 1.0f / sqrtf(tot / (float)H) : 0.0f;
+    const float inv = residual_inv_rms(ss, H, s_part);
     for (int j = threadIdx.x * W; j < H; j += kNormThreads * W) {
         float v[W];
-        value(j, v);
-        if constexpr (VEC) {
-            uint4 o;
-            o.x = f32_to_bf16_bits(v[0] * inv) | (f32_to_bf16_bits(v[1] * inv) << 16);
-            o.y = f32_to_bf16_bits(v[2] * inv) | (f32_to_bf16_bits(v[3] * inv) << 16);
-            o.z = f32_to_bf16_bits(v[4] * inv) | (f32_to_bf16_bits(v[5] * inv) << 16);
-            o.w = f32_to_bf16_bits(v[6] * inv) | (f32_to_bf16_bits(v[7] * inv) << 16);
-            *reinterpret_cast<uint4*>(orow + j) = o;
-        } else {
-            orow[j] = (uint16_t)f32_to_bf16_bits(v[0] * inv);
-        }
+        residual_value<YT, VEC>(hr, yr, alpha, j, v);
+        if constexpr (VEC) *reinterpret_cast<uint4*>(orow + j) = residual_pack(v, inv);
+        else orow[j] = (uint16_t)f32_to_bf16_bits(v[0] * inv);
     }
 }
 

@@ -9,6 +9,7 @@
 
 #include "common.hpp"
 #include "assign.hpp"
+#include "norm_device.hpp"
 #include "route_device.hpp"
 
 namespace dymoe {
@@ -360,23 +361,54 @@ __global__ __launch_bounds__(8 * kWave) void decode_front_kernel(
 // latency.  Here a wavefront owns one router row, kept in registers, and meets every token with it (the row is
 // read once whatever T); the logits go to the probs buffer, and a single workgroup then does what is left.
 //   logit[t, e] -> probs[t * E + e]      (overwritten with the probabilities by the second launch)
-template <int NCH>
+// RESIDUAL (one token): the row is what residual and normalisation make of h = x and y_prev; every workgroup works it out
+// (by 256 of its threads, the sums in norm_device.hpp's order) while its router rows are on their way, the first one stores it.
+template <int NCH, bool RESIDUAL>
 __global__ __launch_bounds__(8 * kWave) void front_logits_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, const float* __restrict__ bias, int T, int H,
+    const uint16_t* __restrict__ x, const float* __restrict__ y_prev, float alpha, uint16_t* __restrict__ h_out,
+    const uint16_t* __restrict__ wg, const float* __restrict__ bias, int T, int H,
     int E, float* __restrict__ logit)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int e = blockIdx.x * 8 + threadIdx.x / kWave;
-    if (e >= E) return;
-    const uint16_t* row = wg + (size_t)e * H;
+    if (!RESIDUAL && e >= E) return;
+    const uint16_t* row = wg + (size_t)min(e, E - 1) * H;
     uint4 wv[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; c++) {
         wv[c] = make_uint4(0, 0, 0, 0);
         if (c * kWave * 8 < H) wv[c] = *reinterpret_cast<const uint4*>(row + min((c * kWave + lane) * 8, H - 8));
     }
+    __shared__ float s_part[kNormThreads / kWave];
+    __shared__ __attribute__((aligned(16))) uint16_t s_row[RESIDUAL ? NCH * kWave * 8 : 8];
+    if constexpr (RESIDUAL) {
+        constexpr int kTrips = (NCH * kWave + kNormThreads - 1) / kNormThreads;
+        float v[kTrips][8], ss = 0.0f;
+        const bool mine = threadIdx.x < kNormThreads;
+#pragma unroll
+        for (int i = 0; i < kTrips; i++) {
+            const int j = (i * kNormThreads + (int)threadIdx.x) * 8;
+            if (mine && j < H) {
+                residual_value<float, true>(x, y_prev, alpha, j, v[i]);
+                residual_square<true>(v[i], ss);
+            }
+        }
+        const float inv = residual_inv_rms(ss, H, s_part);
+#pragma unroll
+        for (int i = 0; i < kTrips; i++) {
+            const int j = (i * kNormThreads + (int)threadIdx.x) * 8;
+            if (mine && j < H) {
+                const uint4 o = residual_pack(v[i], inv);
+                *reinterpret_cast<uint4*>(s_row + j) = o;
+                if (blockIdx.x == 0) *reinterpret_cast<uint4*>(h_out + j) = o;
+            }
+        }
+        __syncthreads();
+        if (e >= E) return;
+    }
     const float b = bias ? bias[e] : 0.0f;
     for (int t = 0; t < T; t++) {
+        const uint16_t* xt = RESIDUAL ? s_row : x + (size_t)t * H;
         float acc = 0.0f;
 #pragma unroll
         for (int c = 0; c < NCH; c++) {
@@ -384,7 +416,7 @@ __global__ __launch_bounds__(8 * kWave) void front_logits_kernel(
                 const int col = (c * kWave + lane) * 8;
                 // lanes past the end meet the re-read tail of the row with zero activations
                 uint4 xv = make_uint4(0, 0, 0, 0);
-                if (col < H) xv = *reinterpret_cast<const uint4*>(x + (size_t)t * H + col);
+                if (col < H) xv = *reinterpret_cast<const uint4*>(xt + col);
                 acc = dot2_bf16(wv[c].x, xv.x, acc);
                 acc = dot2_bf16(wv[c].y, xv.y, acc);
                 acc = dot2_bf16(wv[c].z, xv.z, acc);
@@ -394,6 +426,25 @@ __global__ __launch_bounds__(8 * kWave) void front_logits_kernel(
         const float s = wave_sum(acc);
         if (lane == 0) logit[(size_t)t * E + e] = s + b;
     }
+}
+
+int front_logits_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
+                        int T, int H, int E, float* logits, hipStream_t st)
+{
+    auto go = [&](auto kernel) {
+        dymoe_launch(ctx, DYMOE_K_ROUTE, kernel, dim3((unsigned)((E + 7) / 8)), dim3(8 * kWave), 0, st, (const uint16_t*)x, y_prev, alpha,
+                     (uint16_t*)h_out, (const uint16_t*)wg, bias, T, H, E, logits);
+    };
+    if (y_prev) {
+        if (H <= 2048) go(front_logits_kernel<4, true>);
+        else if (H <= 4096) go(front_logits_kernel<8, true>);
+        else go(front_logits_kernel<16, true>);                     // (the decode layer's rows end at 8192 columns)
+    } else if (H <= 2048) go(front_logits_kernel<4, false>);
+    else if (H <= 4096) go(front_logits_kernel<8, false>);
+    else if (H <= 8192) go(front_logits_kernel<16, false>);
+    else go(front_logits_kernel<32, false>);
+    DYMOE_HIP_LAUNCH_CHECK();
+    return DYMOE_OK;
 }
 
 template <int NC>
@@ -560,20 +611,8 @@ int dymoe_decode_front(dymoe_ctx* ctx, const void* x, const void* wg, const floa
     const uint16_t* wb = (const uint16_t*)wg;
     // many experts (router of 256 KiB and more) and a probs buffer to pass the logits through: two launches
     if (probs && (size_t)E * (size_t)H * 2 >= ((size_t)256 << 10)) {
-        const dim3 grid((unsigned)((E + 7) / 8));
-        if (H <= 2048)
-            dymoe_launch(ctx, DYMOE_K_ROUTE, (dymoe::front_logits_kernel<4>), grid, dim3(8 * dymoe::kWave), 0, st, xb, wb, bias,
-                         T, H, E, probs);
-        else if (H <= 4096)
-            dymoe_launch(ctx, DYMOE_K_ROUTE, (dymoe::front_logits_kernel<8>), grid, dim3(8 * dymoe::kWave), 0, st, xb, wb, bias,
-                         T, H, E, probs);
-        else if (H <= 8192)
-            dymoe_launch(ctx, DYMOE_K_ROUTE, (dymoe::front_logits_kernel<16>), grid, dim3(8 * dymoe::kWave), 0, st, xb, wb, bias,
-                         T, H, E, probs);
-        else
-            dymoe_launch(ctx, DYMOE_K_ROUTE, (dymoe::front_logits_kernel<32>), grid, dim3(8 * dymoe::kWave), 0, st, xb, wb, bias,
-                         T, H, E, probs);
-        DYMOE_HIP_LAUNCH_CHECK();
+        const int rc = dymoe::front_logits_launch(ctx, x, nullptr, 0.0f, nullptr, wg, bias, T, H, E, probs, st);
+        if (rc != DYMOE_OK) return rc;
 #define DYMOE_FINISH(NC_)                                                                                              \
     dymoe_launch(ctx, DYMOE_K_DECODE_FRONT, (dymoe::front_finish_kernel<NC_>), dim3(1), dim3(8 * dymoe::kWave), smem, st, T, E, \
                  k, renorm, idx, w, probs, tt, floor_bits, importance, load, bits, rank)

@@ -67,7 +67,7 @@ class MoELayer:
         self.layout = B.LAYOUT_TILE if gemm else B.LAYOUT_ROWMAJOR
         self.ws_bytes = B.workspace_bytes(T, H, F, E, k)
         self.ws = torch.empty((self.ws_bytes,), dtype=torch.uint8, device=dev)
-        # a decode step on resident formats: dymoe_decode_step (two launches) instead of front end + FFN (three)
+        # a decode step on resident formats: dymoe_decode_layer (two or three launches) instead of front end + FFN (three or four)
         self.use_decode_step = True
 
     # the individual steps; each is one C call
@@ -144,6 +144,19 @@ class MoELayer:
         B._check(rc, "dymoe_decode_step")
         return True
 
+    def decode_layer(self, x, wg, bias, store, st):
+        """decode_step for more experts; False when the sizes are outside what it covers."""
+        rc = B.lib.dymoe_decode_layer(self.ctx._h, x.data_ptr(), None, 0.0, None, wg.data_ptr(),
+                                      bias.data_ptr() if bias is not None else None, self.T, self.H, self.F, self.E, self.k, 1, self._nt,
+                                      C.cast(self._tc, C.c_void_p), C.cast(self._tb, C.c_void_p), self.floor_bits,
+                                      store.table.data_ptr(), self.group, self.out_dtype, self.idx.data_ptr(), self.gate.data_ptr(),
+                                      self.probs.data_ptr(), self.imp.data_ptr(), self.load.data_ptr(), self.bits.data_ptr(),
+                                      self.rank.data_ptr(), self.y.data_ptr(), self.ws.data_ptr(), self.ws_bytes, st)
+        if rc == B.ENOTSUP:
+            return False
+        B._check(rc, "dymoe_decode_layer")
+        return True
+
     def layer_step(self, x, wg, bias, store, quantize, st):
         """The whole step on the grouped-GEMM path in one call; False when the sizes are outside what it covers (the
         caller then makes the separate calls)."""
@@ -166,7 +179,7 @@ class MoELayer:
         st = B._stream(stream)
         if (fused_front and self.use_decode_step and not quantize and self.phase == B.PHASE_DECODE
                 and self.path != B.PATH_GEMM and self.layout == B.LAYOUT_ROWMAJOR
-                and self.decode_step(x, wg, bias, store, st)):
+                and self.decode_layer(x, wg, bias, store, st)):
             return self.y
         if (fused_front and self.layout == B.LAYOUT_TILE and self.path != B.PATH_GEMV and self.T > 0
                 and self.layer_step(x, wg, bias, store, quantize, st)):

@@ -583,7 +583,8 @@ class ResidentDecodeStack:
     Nothing is copied and nothing is decided on the host: the importance of an expert and its bit width are still
     chosen per token and layer on the device (Sec. 4.2.2, Sec. 4.3), and the FFN reads, through the layer's format
     table, the format the assignment names.  A step is therefore a fixed chain of launches (per layer
-    dymoe_decode_step, or dymoe_decode_front and dymoe_moe_ffn_mixed with fused=False, then dymoe_residual_rmsnorm),
+    dymoe_decode_layer, which takes the residual step behind the layer before into its front end, or with fused=False
+    dymoe_decode_front, dymoe_moe_ffn_mixed and dymoe_residual_rmsnorm; a last dymoe_residual_rmsnorm at the end),
     enqueued one by one or (graph=True) replayed as one HIP graph.
 
     pool: a HostExpertPool holding every format in `tier_bits` and the floors (row-major codes); its entries are
@@ -636,20 +637,30 @@ class ResidentDecodeStack:
 
     def _enqueue(self, st):
         ctx, H, F, E, k = self.ctx._h, self.H, self.F, self.E, self.k
+        h, owed = self.h[0], False       # owed: a layer's input is still to be made of h and y (residual + normalisation)
         for l in range(self.L):
-            h, nxt = self.h[l % 2], self.h[(l + 1) % 2]
+            nxt = self.h[1] if h is self.h[0] else self.h[0]
             idx, gate, bits, table = self.idx[l].data_ptr(), self.gate[l].data_ptr(), self.bits[l].data_ptr(), \
                 self.tables[l].data_ptr()
+            # residual, front end and FFN in two launches, or without the residual; sizes those do not cover take the separate calls
             rc = B.ENOTSUP
-            if self.fused:       # front end and FFN in two launches; sizes it does not cover take the separate calls
-                rc = B.lib.dymoe_decode_step(ctx, h.data_ptr(), self.routers[l].data_ptr(), None, 1, H, F, E, k, 1,
-                                             self._nt, C.cast(self._tc[l], C.c_void_p), C.cast(self._tb, C.c_void_p),
-                                             self.floor[l], table, 64, B.OUT_F32, idx, gate, self.probs.data_ptr(),
-                                             self.imp.data_ptr(), self.load.data_ptr(), bits, self.rank.data_ptr(),
-                                             self.y.data_ptr(), self.ws.data_ptr(), self.ws_bytes, st)
+            for with_residual in ((True, False) if owed else (False,)) if self.fused else ():
+                if owed and not with_residual:
+                    h, nxt, owed = self._settle(h, st), h, False
+                rc = B.lib.dymoe_decode_layer(ctx, h.data_ptr(), self.y.data_ptr() if owed else None, self.alpha,
+                                              nxt.data_ptr() if owed else None, self.routers[l].data_ptr(), None, 1, H, F, E, k, 1,
+                                              self._nt, C.cast(self._tc[l], C.c_void_p), C.cast(self._tb, C.c_void_p),
+                                              self.floor[l], table, 64, B.OUT_F32, idx, gate, self.probs.data_ptr(),
+                                              self.imp.data_ptr(), self.load.data_ptr(), bits, self.rank.data_ptr(),
+                                              self.y.data_ptr(), self.ws.data_ptr(), self.ws_bytes, st)
                 if rc != B.ENOTSUP:
-                    B._check(rc, "dymoe_decode_step")
+                    B._check(rc, "dymoe_decode_layer")
+                    if owed:
+                        h = nxt
+                    break
             if rc == B.ENOTSUP:
+                if owed:
+                    h = self._settle(h, st)
                 B._check(B.lib.dymoe_decode_front(ctx, h.data_ptr(), self.routers[l].data_ptr(), None, 1, H, E, k, 1,
                                                   self._nt, C.cast(self._tc[l], C.c_void_p), C.cast(self._tb, C.c_void_p),
                                                   self.floor[l], idx, gate, self.probs.data_ptr(), self.imp.data_ptr(),
@@ -658,8 +669,16 @@ class ResidentDecodeStack:
                 B._check(B.lib.dymoe_moe_ffn_mixed(ctx, h.data_ptr(), idx, gate, bits, table, 1, H, F, E, k, 64, B.OUT_F32,
                                                    B.PATH_GEMV, self.y.data_ptr(), self.ws.data_ptr(), self.ws_bytes, st),
                          "dymoe_moe_ffn_mixed")
-            B._check(B.lib.dymoe_residual_rmsnorm(ctx, h.data_ptr(), self.y.data_ptr(), B.OUT_F32, self.alpha, 1, H,
-                                                  nxt.data_ptr(), st), "dymoe_residual_rmsnorm")
+            owed = True
+        if owed:
+            self._settle(h, st)
+
+    def _settle(self, h, st):
+        """Residual and normalisation between two layers; returns the buffer that holds the result."""
+        nxt = self.h[1] if h is self.h[0] else self.h[0]
+        B._check(B.lib.dymoe_residual_rmsnorm(self.ctx._h, h.data_ptr(), self.y.data_ptr(), B.OUT_F32, self.alpha, 1, self.H,
+                                              nxt.data_ptr(), st), "dymoe_residual_rmsnorm")
+        return nxt
 
     def step(self, h0):
         """h0: [1,H] bf16 on the device.  Returns the final hidden states (a buffer the next step overwrites)."""

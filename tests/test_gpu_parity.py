@@ -1188,3 +1188,44 @@ def test_plan_with_long_tile_lists(ctx, more):
     one = ctx.moe_ffn_mixed(x, torch.zeros((T, 1), dtype=torch.int32, device=DEV), gate, bits, table, F, out_dtype=B.OUT_F32,
                             path=B.PATH_GEMM)
     assert torch.equal(y, one)
+
+
+# the decode layer: logits in the workgroups and from a launch of their own (from nine rows, five beyond 4096 columns), one and two
+# logits per lane, the largest step; behind a layer before (one token): rows of one to four segments, whole and ragged
+@pytest.mark.parametrize("T,H,E,k,floor,chained", [
+    (1, 2048, 128, 8, 0, False), (4, 1088, 128, 8, 0, False), (3, 2048, 65, 3, 4, False), (2, 2048, 64, 8, 0, False),
+    (2, 2112, 60, 4, 0, False), (1, 64, 8, 1, 0, False), (1, 8192, 4, 1, 0, False), (1, 8192, 5, 2, 0, False), (4, 256, 5, 2, 0, False),
+    (1, 256, 8, 2, 0, True), (1, 320, 9, 2, 4, True), (1, 2048, 63, 8, 0, True), (1, 2304, 128, 8, 0, True), (1, 64, 10, 2, 0, True),
+    (1, 4096, 8, 2, 0, True), (1, 4160, 4, 2, 0, True), (1, 4160, 16, 4, 0, True), (1, 8192, 15, 2, 0, True)])
+def test_decode_layer_equals_the_separate_calls(ctx, T, H, E, k, floor, chained):
+    g = torch.Generator(device=DEV).manual_seed(H + E)
+    F = 192
+    rnd = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.05).bfloat16()
+    store = ExpertStore([[rnd(F, H), rnd(F, H), rnd(H, F)] for _ in range(E)], H, F, DEV, formats=(8, 4, 2))
+    for b in (8, 4, 2):
+        ctx.quantize_experts(store.table, torch.full((E,), b, dtype=torch.uint8, device=DEV), None, E, H, F, layout=B.LAYOUT_ROWMAJOR)
+    counts, tbits = [E // 5, E // 5, E // 5, E - 3 * (E // 5)], [16, 8, 4, 2]
+    wg, bias = rnd(E, H), torch.linspace(-0.2, 0.2, E, device=DEV)
+    x = (torch.randn((T, H), generator=g, device=DEV)).bfloat16()
+    la, lb = (MoELayer(ctx, T, H, F, E, k, "decode", counts, tbits, floor_bits=floor, out_dtype=B.OUT_F32, device=DEV) for _ in range(2))
+    st = B._stream(None)
+    la.ws.fill_(0xCC)
+    if chained:
+        y_prev = torch.randn((T, H), generator=g, device=DEV)
+        h_out, row = torch.zeros_like(x), torch.empty_like(x)
+        la.y.copy_(y_prev)                                                 # the step may overwrite the output it starts from
+        B._check(B.lib.dymoe_decode_layer(
+            ctx._h, x.data_ptr(), la.y.data_ptr(), 0.125, h_out.data_ptr(), wg.data_ptr(), bias.data_ptr(), 1, H, F, E, k, 1, 4,
+            ctypes.cast(la._tc, ctypes.c_void_p), ctypes.cast(la._tb, ctypes.c_void_p), floor, store.table.data_ptr(), 64, B.OUT_F32,
+            la.idx.data_ptr(), la.gate.data_ptr(), la.probs.data_ptr(), la.imp.data_ptr(), la.load.data_ptr(), la.bits.data_ptr(),
+            la.rank.data_ptr(), la.y.data_ptr(), la.ws.data_ptr(), la.ws_bytes, st), "dymoe_decode_layer")
+        B._check(B.lib.dymoe_residual_rmsnorm(ctx._h, x.data_ptr(), y_prev.data_ptr(), B.OUT_F32, 0.125, 1, H, row.data_ptr(), st), "norm")
+        assert torch.equal(row, h_out)
+        x = row
+    else:
+        assert la.decode_layer(x, wg, bias, store, st)
+    lb.front(x, wg, bias, st)
+    lb.ffn(x, store, st)
+    for u, v in zip((la.idx, la.gate, la.probs, la.imp, la.load, la.bits, la.rank, la.y),
+                    (lb.idx, lb.gate, lb.probs, lb.imp, lb.load, lb.bits, lb.rank, lb.y)):
+        assert torch.equal(u, v)

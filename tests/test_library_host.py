@@ -127,6 +127,18 @@ def test_argument_validation_happens_before_any_device_work():
     assert step(k_hh=8) == B.EINVAL and step(floor=3) == B.EINVAL and step(score=None) == B.EINVAL
     assert step(probs=None) == B.EINVAL and step(rank=None) == B.EINVAL and step(ws=wsl - 1) == B.ENOSPC
     assert step(H=192, ws=1 << 40) == B.ENOTSUP                                                # no GEMM path
+    # the decode layer, alone and behind a layer before
+    wsl = int(lib.dymoe_workspace_bytes(4, 256, 512, 128, 2))
+    tc2, tb2 = (C.c_int32 * 1)(8), (C.c_uint8 * 1)(4)
+    dl = lib.dymoe_decode_layer
+    layer = lambda x=P, yp=None, ho=None, T=1, H=256, E=8, k=2, ws=wsl: (
+        tc2.__setitem__(0, E), dl(None, x, yp, 0.5, ho, P, None, T, H, 512, E, k, 1, 1, C.cast(tc2, C.c_void_p), C.cast(tb2, C.c_void_p), 0,
+                                  P, 64, 0, P, P, P, P, P, P, P, P, P, ws, None))[1]
+    assert layer() == B.ENOCTX and layer(T=4) == B.ENOCTX and layer(yp=P, ho=2 * P) == B.ENOCTX
+    assert layer(yp=P) == B.EINVAL and layer(yp=P, ho=P) == B.EINVAL and layer(yp=P + 4, ho=2 * P) == B.EINVAL
+    assert layer(T=5, ws=1 << 40) == B.ENOTSUP and layer(E=129, ws=1 << 40) == B.ENOTSUP
+    assert layer(E=80, ws=1 << 40) == B.ENOCTX and layer(E=80, H=64, k=1, ws=1 << 40) == B.ENOTSUP
+    assert layer(yp=P, ho=2 * P, T=2) == B.ENOTSUP and layer(ws=64) == B.ENOSPC
     # attention-derived token score
     ta = lib.dymoe_token_score_attention
     aw = int(lib.dymoe_attention_workspace_bytes(77, 8))
