@@ -3,6 +3,7 @@
 #include "common.hpp"
 #include "assign.hpp"
 #include "ffn_layout.hpp"
+#include "plan_device.hpp"
 
 // Scratch of the entry point that allocates nothing.  One copy per GPU the library runs on, held until the
 // process ends; every call on a GPU shares that GPU's copy.  In host code the array's name is only a stand-in: the
@@ -42,7 +43,8 @@ bool ffn_gemm_fits(int T, int H, int F, int E, int k);
 bool rank_plan_fits(int T, int E, int k);
 int rank_plan_launch(dymoe_ctx* ctx, bool prefill, const void* x, const int32_t* idx, const float* probs, const float* score, int T, int H,
                      int E, int k, int k_hh, const TierTable& tiers, int floor_bits, const dymoe_expert_fmt* table, void* importance,
-                     int32_t* load, uint8_t* bits, int32_t* rank, const FfnLayout& L, char* ws, hipStream_t st);
+                     int32_t* load, uint8_t* bits, int32_t* rank, const SplitRule& splits, const FfnLayout& L, char* ws, hipStream_t st);
+SplitRule split_rule(const dymoe_ctx* ctx, int T, int H, int F, int E, int k, const FfnLayout& L);
 int route_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E, int k, int renorm, int32_t* idx,
                  float* w, float* probs, float* score, hipStream_t st);
 bool decode_fused_fits(int T, int H, int E, int k);
@@ -188,10 +190,11 @@ extern "C" int dymoe_layer_step(dymoe_ctx* ctx, int phase, const void* x, const 
     if (H > 16384 || !dymoe::rank_plan_fits(T, E, k)) return DYMOE_ENOTSUP;
     if (!ctx) return DYMOE_ENOCTX;
     hipStream_t st = (hipStream_t)stream;
+    const dymoe::FfnLayout L = dymoe::ffn_layout(T, H, F, E, k);
     int r = dymoe::route_launch(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, prefill ? token_score : nullptr, st);
     if (r != DYMOE_OK) return r;
     r = dymoe::rank_plan_launch(ctx, prefill, x, idx, probs, token_score, T, H, E, k, k_hh, tt, floor_bits, table, importance, load, bits,
-                                rank, dymoe::ffn_layout(T, H, F, E, k), (char*)workspace, st);
+                                rank, dymoe::split_rule(ctx, T, H, F, E, k, L), L, (char*)workspace, st);
     if (r != DYMOE_OK) return r;
     if (quantize) {
         r = dymoe_quantize_experts(ctx, table, bits, load, E, H, F, group, DYMOE_LAYOUT_TILE, stream);

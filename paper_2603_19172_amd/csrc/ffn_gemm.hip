@@ -643,7 +643,7 @@ __global__ __launch_bounds__(kGmThreads, 2) void gemm_kernel(
     const uint16_t* __restrict__ hbuf_in,
     const uint8_t* __restrict__ bits, const dymoe_expert_fmt* __restrict__ table,
     const int32_t* __restrict__ plan, int P, int E, int k_route, int H, int F,
-    uint16_t* __restrict__ hbuf_out, float* __restrict__ opair, int max_tiles, int splits)
+    uint16_t* __restrict__ hbuf_out, float* __restrict__ opair, int max_tiles)
 {
     // two token-tile buffers; the swizzle works on the address bits inside a row
     extern __shared__ __attribute__((aligned(1024))) uint16_t xs_raw[];
@@ -651,6 +651,7 @@ __global__ __launch_bounds__(kGmThreads, 2) void gemm_kernel(
     const PlanPtrs pp = plan_ptrs(const_cast<int32_t*>(plan), E, P);
     const int K = (MODE == 1) ? H : F;
     const int N = (MODE == 1) ? F : H;
+    const int splits = (MODE == 2) ? pp.ntiles[kPlanSplits] : 1;
     // Which (column block, tile, K split) this workgroup takes.  Both launches are one-dimensional: workgroups go to the
     // 8 XCDs (each with an L2 of its own) in turn by launch index, L -> XCD c = L % 8, place j = L / 8 in that XCD's
     // sequence, and the units (a tile's rows over one K split) are handed out 8 at a time, all their column blocks,
@@ -756,9 +757,10 @@ __global__ __launch_bounds__(kGmThreads, 2) void gemm_kernel(
 template <int SLOTS>
 __global__ __launch_bounds__(256) void gemm_combine_kernel(
     const float* __restrict__ opair, const int32_t* __restrict__ idx, const float* __restrict__ w,
-    const uint8_t* __restrict__ bits, int T, int H, int E, int k, int splits, int out_dtype,
+    const uint8_t* __restrict__ bits, const int32_t* __restrict__ n_splits, int T, int H, int E, int k, int out_dtype,
     void* __restrict__ y)
 {
+    const int splits = *n_splits;
     const long i4 = (long)blockIdx.x * 256 + threadIdx.x;  // groups of 4 columns
     const long n4 = (long)T * (H >> 2);
     if (i4 >= n4) return;
@@ -777,6 +779,7 @@ __global__ __launch_bounds__(256) void gemm_combine_kernel(
             g[u] = w[p[u]];
             o[u] = load_global<float4>(opair + p[u] * H + j);
         }
+#pragma unroll 8 / SLOTS
         for (int z = 1; z < splits; z++) {
 #pragma unroll
             for (int u = 0; u < SLOTS; u++) {
@@ -832,8 +835,27 @@ bool ffn_gemm_fits(int T, int H, int F, int E, int k)
     return true;
 }
 
+// The intermediate takes half of its area (16-bit values where the other path has fp32): the slabs start behind it.
+static size_t slabs_offset(int T, int F, int k, const FfnLayout& L) { return L.hbuf + round256((size_t)T * k * F * 2); }
+
+SplitRule split_rule(const dymoe_ctx* ctx, int T, int H, int F, int E, int k, const FfnLayout& L)
+{
+    const long P = (long)T * k;
+    SplitRule r;
+    r.nblk = (H + 64 * kGmWaves - 1) / (64 * kGmWaves);
+    r.n_kt = F / kBK;
+    r.num_cu = ctx->num_cu;
+    long most = (long)((L.xh - slabs_offset(T, F, k, L)) / ((size_t)P * H * 4));        // slabs the workspace holds
+    if (most > F / 256) most = F / 256;                                                 // two K-tiles per split at least
+    // no more workgroups than 4 per compute unit if every expert has tokens (every one of them has a tile, and P / 128 more at most)
+    const long blocks = r.nblk * ((E < P ? E : P) + P / (2 * kGemmTileM));
+    if (most > 4L * r.num_cu / blocks) most = 4L * r.num_cu / blocks;
+    r.max = (int)(most > 8 ? 8 : most < 1 ? 1 : most);
+    return r;
+}
+
 int plan_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const uint8_t* bits, const dymoe_expert_fmt* table, int T, int H,
-                int E, int k, const FfnLayout& L, char* ws, hipStream_t st);
+                int E, int k, const SplitRule& splits, const FfnLayout& L, char* ws, hipStream_t st);
 
 // planned: the workspace already holds the plan and the copies of x (rank_plan_launch)
 int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const float* w, const uint8_t* bits,
@@ -848,12 +870,12 @@ int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     uint16_t* xh4 = reinterpret_cast<uint16_t*>(ws + L.xh);      // [T,H] fp16, int4 column order
     uint16_t* xh2 = xh4 + round256((size_t)T * H * 2) / 2;       // [T,H] fp16, int2 column order
     uint16_t* xh8 = xh2 + round256((size_t)T * H * 2) / 2;       // [T,H] fp16, natural column order (int8)
-    float* opair = reinterpret_cast<float*>(ws + L.part);
+    float* opair = reinterpret_cast<float*>(ws + slabs_offset(T, F, k, L));
     int32_t* plan = reinterpret_cast<int32_t*>(ws + L.plan);
     const uint16_t* xb = (const uint16_t*)x;
 
     if (!planned) {
-        const int rc = plan_launch(ctx, x, idx, bits, table, T, H, E, k, L, ws, st);
+        const int rc = plan_launch(ctx, x, idx, bits, table, T, H, E, k, split_rule(ctx, T, H, F, E, k, L), L, ws, st);
         if (rc != DYMOE_OK) return rc;
     }
     // what the kernels after the plan take as the bit widths: the plan's copy, 0 where the table lacks the format
@@ -864,30 +886,21 @@ int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     const int nblk1 = (F + cols1 - 1) / cols1;
     const dim3 g1((unsigned)(8 * nblk1 * ((max_tiles + 7) / 8)));
     dymoe_launch(ctx, DYMOE_K_GEMM1, (gemm_kernel<1>), g1, dim3(kGmThreads), kLdsBytes, st, xb, xh4, xh2, xh8,
-                 (const uint16_t*)nullptr, run_bits, table, plan, P, E, k, H, F, hbuf, (float*)nullptr, max_tiles, 1);
+                 (const uint16_t*)nullptr, run_bits, table, plan, P, E, k, H, F, hbuf, (float*)nullptr, max_tiles);
     DYMOE_HIP_LAUNCH_CHECK();
-    // The down projection has few output tiles: split K so that the launch still covers the chip (two workgroups per
-    // compute unit, about one and a half rounds of them; measured on the Mixtral prefill: 2 to 7 splits lie within
-    // 7 % of each other, 4 is best).  Each split writes its own slab of per-pair outputs and the combine kernel adds
-    // the slabs in a fixed order, so every extra split also costs a slab of traffic each way.  The number of tiles is
-    // only known on the device; from the sizes: every expert with tokens has one, and P / 128 more at most.
+    // The down projection has few output tiles: K is split so that the launch covers the chip.  Each split writes its own slab
+    // of per-pair outputs and the combine kernel adds the slabs in a fixed order.  The plan chooses the number (it knows the
+    // tiles); workgroups beyond it end at once.
     const int nblk2 = (H + cols2 - 1) / cols2;
-    const long est_tiles = (E < P ? E : P) + (long)P / (2 * kGemmTileM);
-    const long est_blocks = (long)nblk2 * est_tiles;
-    int splits = (int)(3L * ctx->num_cu / est_blocks);
-    const int max_splits = (F + kSeg - 1) / kSeg;     // slabs the workspace holds
-    if (splits > max_splits) splits = max_splits;
-    if (splits > 8) splits = 8;
-    if (splits < 1) splits = 1;
-    const int units = max_tiles * splits;
+    const int units = max_tiles * split_rule(ctx, T, H, F, E, k, L).max;
     const dim3 g2((unsigned)(8 * nblk2 * ((units + 7) / 8)));
     dymoe_launch(ctx, DYMOE_K_GEMM2, (gemm_kernel<2>), g2, dim3(kGmThreads), kLdsBytes, st, xb, xh4, xh2, xh8, hbuf,
-                 run_bits, table, plan, P, E, k, H, F, (uint16_t*)nullptr, opair, max_tiles, splits);
+                 run_bits, table, plan, P, E, k, H, F, (uint16_t*)nullptr, opair, max_tiles);
     DYMOE_HIP_LAUNCH_CHECK();
     const long n4 = (long)T * (H / 4);
     auto combine = [&](auto kernel) {
-        dymoe_launch(ctx, DYMOE_K_GEMM_COMBINE, kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, opair, idx, w, run_bits, T,
-                     H, E, k, splits, out_dtype, y);
+        dymoe_launch(ctx, DYMOE_K_GEMM_COMBINE, kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, opair, idx, w, run_bits,
+                     plan_ptrs(plan, E, P).ntiles + kPlanSplits, T, H, E, k, out_dtype, y);
     };
     if (k == 1) combine(gemm_combine_kernel<1>);
     else if (k == 2) combine(gemm_combine_kernel<2>);

@@ -19,7 +19,7 @@ namespace dymoe {
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __restrict__ idx,
                                                             const uint8_t* __restrict__ bits,
                                                             const dymoe_expert_fmt* __restrict__ table, int P, int E,
-                                                            int tile_m, int max_tiles,
+                                                            int tile_m, int max_tiles, SplitRule splits,
                                                             int32_t* __restrict__ plan, unsigned* __restrict__ flags,
                                                             const uint16_t* __restrict__ x, long n16,
                                                             uint16_t* __restrict__ xh4, uint16_t* __restrict__ xh2,
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         s_count[e] = (b != 0 && !(b & 0x80)) ? total : 0;                           // ... and leave its pairs out
     }
     __syncthreads();
-    plan_scan(E, s_count, s_bits, s_off, s_tile0, pp);
+    plan_scan(E, s_count, s_bits, s_off, s_tile0, splits, pp);
     if (s_tile0[E] <= kPlanShortList) plan_tile_list(E, tile_m, s_count, s_bits, s_off, s_tile0, s_cnt, pp);
     else plan_tile_list_long(E, tile_m, s_count, s_bits, s_off, s_tile0, pp.tiles + 4 * (size_t)max_tiles, pp);
     plan_tables(E, s_count, s_bits, s_off, pp);
@@ -109,14 +109,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
 }
 
 int plan_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const uint8_t* bits, const dymoe_expert_fmt* table, int T, int H,
-                int E, int k, const FfnLayout& L, char* ws, hipStream_t st)
+                int E, int k, const SplitRule& splits, const FfnLayout& L, char* ws, hipStream_t st)
 {
     uint16_t* xh4 = reinterpret_cast<uint16_t*>(ws + L.xh);
     uint16_t* xh2 = xh4 + round256((size_t)T * H * 2) / 2;
     uint16_t* xh8 = xh2 + round256((size_t)T * H * 2) / 2;
     const long n16 = (long)T * H / 16;
     dymoe_launch(ctx, DYMOE_K_PLAN, plan_kernel, dim3((unsigned)(1 + (n16 + kPlanThreads - 1) / kPlanThreads)), dim3(kPlanThreads), 0,
-                 st, idx, bits, table, T * k, E, kGemmTileM, L.max_tiles, reinterpret_cast<int32_t*>(ws + L.plan), ctx->device_flags,
+                 st, idx, bits, table, T * k, E, kGemmTileM, L.max_tiles, splits, reinterpret_cast<int32_t*>(ws + L.plan), ctx->device_flags,
                  (const uint16_t*)x, n16, xh4, xh2, xh8);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
@@ -146,6 +146,7 @@ struct RankPlanArgs {
     int32_t* rank;
     const dymoe_expert_fmt* table;
     int formats;                       // sum of the bit widths the tiers can assign
+    SplitRule splits;
     int32_t* plan;
     unsigned* flags;
     const uint16_t* x;
@@ -417,7 +418,7 @@ __global__ __launch_bounds__(kPlanThreads) void rank_plan_kernel(const RankPlanA
         s_count[tid] = b ? total : 0;
     }
     __syncthreads();
-    plan_scan(E, s_count, s_bits, s_off, s_tile0, pp);
+    plan_scan(E, s_count, s_bits, s_off, s_tile0, a.splits, pp);
     // the wavefronts' first positions among all pairs; negative where the expert is left out
     for (int i = tid; i < kPlanWaves * E; i += kPlanThreads) {
         const int e = i % E;
@@ -457,7 +458,7 @@ bool rank_plan_fits(int T, int E, int k)
 
 int rank_plan_launch(dymoe_ctx* ctx, bool prefill, const void* x, const int32_t* idx, const float* probs, const float* score, int T, int H,
                      int E, int k, int k_hh, const TierTable& tiers, int floor_bits, const dymoe_expert_fmt* table, void* importance,
-                     int32_t* load, uint8_t* bits, int32_t* rank, const FfnLayout& L, char* ws, hipStream_t st)
+                     int32_t* load, uint8_t* bits, int32_t* rank, const SplitRule& splits, const FfnLayout& L, char* ws, hipStream_t st)
 {
     RankPlanArgs a = {};
     a.idx = idx; a.score = score; a.probs = probs;
@@ -467,6 +468,7 @@ int rank_plan_launch(dymoe_ctx* ctx, bool prefill, const void* x, const int32_t*
     a.table = table;
     for (int i = 0; i < tiers.n; i++)
         if (tiers.count[i] > 0) a.formats |= tiers.bits[i] < floor_bits ? floor_bits : tiers.bits[i];
+    a.splits = splits;
     a.plan = reinterpret_cast<int32_t*>(ws + L.plan);
     a.flags = ctx->device_flags;
     a.x = (const uint16_t*)x;

@@ -120,10 +120,44 @@ __device__ __forceinline__ int plan_gather(int e, int E, int32_t* s_priv)
     return run;
 }
 
+// Number of K splits of the second GEMM: nblk column blocks, n_kt K-tiles, up to max splits, num_cu compute units that hold two
+// workgroups each.
+struct SplitRule {
+    int nblk, n_kt, max, num_cu;
+};
+constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the tile counts
+
+// Tiles of one fragment stream weights of different widths: one and a half rounds of workgroups level them out (24 tokens of
+// the Mixtral shape, 8 tiles x 16 blocks: GEMM and combine 87 us with 2 splits, 86 with 4, 73 with 5, 67 with 6, 69 with 8).
+// Tiles of more rows keep the matrix cores busy, and their workgroups last about the same: in units of a round of two
+// unsplit workgroups per compute unit, a launch takes 0.55 / s where each has a unit of its own, 1 / s up to one round and
+// (rounds + 0.3) / s beyond, and every split writes and reads a slab, 0.0147 blocks / n_kt (a copy's rate against the matrix
+// cores').  us, GEMM and combine: 512 tokens of the Mixtral shape (9 x 16) 1 split 328, 2 209, 3 170, 4 189, 6 180; 433
+// tokens x 4 of 2048 x 6272 (16 x 8) 101, 68, 77, 73; 580 x 4 of 896 x 2560 (20 x 4) 59, 39, 34; 315 x 2 of 1792 x 3584
+// (16 x 7) 40, 29, 31.
+// By one wavefront, a lane per number (max <= 64); the least cost, the smaller number of equals.
+__device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRule& r, const PlanPtrs& pp)
+{
+    const int lane = threadIdx.x & (kWave - 1), s = lane + 1;
+    const int blocks = max(1, r.nblk * tiles);
+    int best = 1;
+    if (r.max > 1) {
+        if (pairs <= 32 * tiles) {
+            best = max(1, min(r.max, 3 * r.num_cu / blocks));
+        } else {
+            const int n = blocks * s;
+            const float rounds = n <= r.num_cu ? 0.55f : n <= 2 * r.num_cu ? 1.0f : 0.5f * (float)n / (float)r.num_cu + 0.3f;
+            const float cost = s <= r.max ? rounds / (float)s + 0.0147f * (float)blocks * (float)s / (float)r.n_kt : 1e30f;
+            best = __ffsll((long long)__ballot(cost == -wave_max_dpp(-cost)));
+        }
+    }
+    if (lane == 0) pp.ntiles[kPlanSplits] = best;
+}
+
 // s_count, s_bits: pairs and bit width of every expert (no pairs where it does not run) -> first pair and first tile of
 // each, the totals to memory.  The caller's s_count and s_bits are visible to all; so are the results.
 __device__ __forceinline__ void plan_scan(int E, const int32_t* s_count, const uint8_t* s_bits, int32_t* s_off, int32_t* s_tile0,
-                                          const PlanPtrs& pp)
+                                          const SplitRule& splits, const PlanPtrs& pp)
 {
     const int tid = threadIdx.x, wave = tid / kWave;
     // E is at most 1024: one wavefront walks the experts in strides
@@ -152,6 +186,7 @@ __device__ __forceinline__ void plan_scan(int E, const int32_t* s_count, const u
         }
     }
     __syncthreads();
+    if (wave == kPlanWaves - 1) plan_splits(s_tile0[E], s_off[E], splits, pp);
 }
 
 // Cost key of a tile, roughly the time a workgroup spends on it: streaming (bf16) or dequantising (int4, int2) the weights
