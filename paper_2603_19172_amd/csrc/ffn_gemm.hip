@@ -749,6 +749,245 @@ __global__ __launch_bounds__(kGmThreads, 2) void gemm_kernel(
 #undef DYMOE_TILE
 }
 
+// ----------------------------------------------------------------------------
+// Tiles of one fragment (up to 32 token rows): decode batches, where an expert meets a few tokens and the launch is a stream
+// of weights.  In gemm_kernel the four wavefronts of a workgroup own different columns and share the token tile, one K-tile
+// ahead: with int4 weights that is 33 KB in flight per compute unit (4.2 TB/s), and where the workgroups do not fill the chip,
+// a microsecond per K-tile.  Here the wavefronts of a workgroup share their columns (two strips of 32 weight rows) and split
+// the K-tiles: nothing is shared before the end, so there are no barriers and no LDS in the loop, a wavefront keeps the next
+// K-tile's codes in registers and reads its token rows straight from the cache (a lane's 128 bytes of a row per K-tile), three
+// workgroups share a compute unit, and a chain is a quarter as long.  At the end the four partial sums meet in LDS, in
+// wavefront order.
+constexpr int kSmThreads = 256;
+constexpr int kSmWaves = kSmThreads / kWave;
+
+template <int BITS>
+struct SmallStrips {
+    StripRaw<BITS> a, b;
+};
+
+// A strip's K-tiles as a base that is the same for the whole wavefront and this lane's 32-bit offset: the loads then take the
+// base from scalar registers, where 64-bit addresses per lane and load would not fit beside the operands.
+template <int BITS>
+struct SmallSrc {
+    const char* p;
+    const char* s;            // scale, zero
+    const char* z;
+    uint32_t off;
+    int kt_stride, c_stride;
+};
+
+template <int BITS>
+__device__ __forceinline__ SmallSrc<BITS> small_src(const MatPtr& m, long nt, int K, int lane)
+{
+    SmallSrc<BITS> src;
+    const long tile_row = nt * (K >> 7);
+    src.s = reinterpret_cast<const char*>(m.s + tile_row * 64);
+    src.z = reinterpret_cast<const char*>(m.z + tile_row * 64);
+    src.off = (uint32_t)(lane * 16);
+    src.c_stride = 1024;
+    if constexpr (BITS == 16) {
+        src.kt_stride = 8192;
+        src.p = m.wt + tile_row * 8192;
+        if (!m.wt) {
+            src.p = reinterpret_cast<const char*>(m.w + nt * 32 * K);
+            src.off = (uint32_t)((lane & 31) * K * 2 + 128 * (lane >> 5));
+            src.kt_stride = 256;
+            src.c_stride = 16;
+        }
+    } else {
+        src.kt_stride = 512 * BITS;
+        src.p = m.q + tile_row * (512 * BITS);
+    }
+    return src;
+}
+
+template <int BITS>
+__device__ __forceinline__ uint4 small_chunk(const SmallSrc<BITS>& src, int kt, int c)
+{
+    if constexpr (BITS == 16) return load_global<uint4>(src.p + ((long)kt * src.kt_stride + c * src.c_stride) + src.off);
+    else return load_global<uint4>(src.p + (long)kt * (512 * BITS) + src.off + c * 1024);
+}
+
+template <int BITS>
+__device__ __forceinline__ void small_strip(const SmallSrc<BITS>& src, int kt, uint32_t off2, StripRaw<BITS>& raw)
+{
+    constexpr int kChunks = (BITS == 16) ? 8 : (BITS == 8 ? 4 : (BITS == 4 ? 2 : 1));
+#pragma unroll
+    for (int c = 0; c < kChunks; c++) raw.r[c] = small_chunk<BITS>(src, kt, c);
+    if constexpr (BITS != 16) {
+        raw.s2 = load_global<uint16_t>(src.s + (long)kt * 128 + off2);
+        raw.m2 = load_global<uint16_t>(src.z + (long)kt * 128 + off2);
+    }
+}
+
+template <int MODE, int BITS>
+__device__ __forceinline__ void small_tile(const uint16_t* __restrict__ act, const int32_t* __restrict__ perm, int k_route,
+                                           const dymoe_expert_fmt& ex, int K, int N, int kt_begin, int kt_end, int row0, int rows,
+                                           int nblock, uint16_t* __restrict__ hout, float* __restrict__ oout, float* s_red)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int ln = lane & 31, kb = lane >> 5;
+    const long nt_a = (MODE == 1) ? nblock : 2L * nblock, nt_b = (MODE == 1) ? nblock : 2L * nblock + 1;
+    const SmallSrc<BITS> sa = small_src<BITS>(mat_ptr(ex, MODE == 1 ? 0 : 2, BITS), nt_a, K, lane);
+    const SmallSrc<BITS> sb = small_src<BITS>(mat_ptr(ex, MODE == 1 ? 1 : 2, BITS), nt_b, K, lane);
+    const int n = kt_end - kt_begin;
+    const int k0 = kt_begin + n * wave / kSmWaves, k1 = kt_begin + n * (wave + 1) / kSmWaves;
+    float16_t acc[2];
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[s][i] = 0.0f;
+    if (k0 < k1) {
+        const int r = min(ln, rows - 1);                // rows past the last token re-read it: computed and dropped
+        const long src_row = (MODE == 1) ? (long)(perm[row0 + r] / k_route) : (long)(row0 + r);
+        const char* const xp = reinterpret_cast<const char*>(act);
+        const uint32_t xoff = (uint32_t)(src_row * K * 2 + 128 * kb);       // < 4 GiB, checked by the launcher
+        const uint32_t off2 = (uint32_t)(lane * 2);
+        uint4 x[8];
+#pragma unroll
+        for (int c = 0; c < 8; c++) x[c] = load_global<uint4>(xp + (long)k0 * 256 + xoff + 16 * c);
+        // the K-tile in `w` against x; x, and for bf16 and int8 w itself, are refilled from K-tile kn as soon as they have been used
+        auto compute = [&](SmallStrips<BITS>& w, int kn) {
+#pragma unroll
+            for (int jj = 0; jj < 4; jj++) {
+                uint4 a0, a1, b0, b1;
+                strip_frags<BITS>(w.a, jj, a0, a1);
+                strip_frags<BITS>(w.b, jj, b0, b1);
+                acc[0] = mfma16<BITS>(a0, x[2 * jj], acc[0]);
+                acc[1] = mfma16<BITS>(b0, x[2 * jj], acc[1]);
+                acc[0] = mfma16<BITS>(a1, x[2 * jj + 1], acc[0]);
+                acc[1] = mfma16<BITS>(b1, x[2 * jj + 1], acc[1]);
+                x[2 * jj] = load_global<uint4>(xp + (long)kn * 256 + xoff + 32 * jj);
+                x[2 * jj + 1] = load_global<uint4>(xp + (long)kn * 256 + xoff + 32 * jj + 16);
+                if constexpr (BITS == 16) {
+                    w.a.r[2 * jj] = small_chunk<16>(sa, kn, 2 * jj);
+                    w.a.r[2 * jj + 1] = small_chunk<16>(sa, kn, 2 * jj + 1);
+                    w.b.r[2 * jj] = small_chunk<16>(sb, kn, 2 * jj);
+                    w.b.r[2 * jj + 1] = small_chunk<16>(sb, kn, 2 * jj + 1);
+                } else if constexpr (BITS == 8) {
+                    w.a.r[jj] = small_chunk<8>(sa, kn, jj);
+                    w.b.r[jj] = small_chunk<8>(sb, kn, jj);
+                }
+                __builtin_amdgcn_sched_barrier(0x4);            // only SALU may cross
+            }
+        };
+        // past the end the loads re-read the last K-tile instead of branching
+        auto fetch = [&](SmallStrips<BITS>& w, int kt) {
+            small_strip<BITS>(sa, min(kt, k1 - 1), off2, w.a);
+            small_strip<BITS>(sb, min(kt, k1 - 1), off2, w.b);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        SmallStrips<BITS> w0;
+        fetch(w0, k0);
+        if constexpr (BITS == 16) {
+            for (int kt = k0; kt < k1; kt++) compute(w0, min(kt + 1, k1 - 1));
+        } else if constexpr (BITS == 8) {
+            for (int kt = k0; kt < k1; kt++) {
+                const int kn = min(kt + 1, k1 - 1);
+                adopt_strip<8>(w0.a, w0.a);
+                adopt_strip<8>(w0.b, w0.b);
+                uint32_t nx[4];
+                nx[0] = load_global<uint16_t>(sa.s + (long)kn * 128 + off2);
+                nx[1] = load_global<uint16_t>(sa.z + (long)kn * 128 + off2);
+                nx[2] = load_global<uint16_t>(sb.s + (long)kn * 128 + off2);
+                nx[3] = load_global<uint16_t>(sb.z + (long)kn * 128 + off2);
+                compute(w0, kn);
+                w0.a.s2 = nx[0]; w0.a.m2 = nx[1]; w0.b.s2 = nx[2]; w0.b.m2 = nx[3];
+            }
+        } else {
+            SmallStrips<BITS> w1;
+            auto step = [&](SmallStrips<BITS>& w, int kt) {
+                adopt_strip<BITS>(w.a, w.a);
+                adopt_strip<BITS>(w.b, w.b);
+                compute(w, min(kt + 1, k1 - 1));
+            };
+            for (int kt = k0; kt < k1; kt += 2) {
+                fetch(w1, kt + 1);
+                step(w0, kt);
+                if (kt + 1 >= k1) break;
+                fetch(w0, kt + 2);
+                step(w1, kt + 1);
+            }
+        }
+    }
+    // partial sums: [wavefront][register of strip a, then b][lane]
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) s_red[((wave * 2 + s) * 16 + i) * kWave + lane] = acc[s][i];
+    __syncthreads();
+    // wavefront w finishes registers 4 w .. 4 w + 3 of both strips: weight rows 8 w + 4 kb + 0 .. 3, token ln
+    float v[2][4];
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const float* const at = s_red + (s * 16 + 4 * wave + i) * kWave + lane;
+            v[s][i] = ((at[0] + at[2048]) + at[4096]) + at[6144];
+        }
+    if constexpr (MODE == 2) {
+        if (ln < rows) {
+            float* const dst = oout + (long)perm[row0 + ln] * N + 64L * nblock + 8 * wave + 4 * kb;
+            store_global(dst, make_float4(v[0][0], v[0][1], v[0][2], v[0][3]));
+            store_global(dst + 32, make_float4(v[1][0], v[1][1], v[1][2], v[1][3]));
+        }
+        return;
+    }
+    // SwiGLU; the 16-bit intermediate in the column order that the down projection of this expert reads (perm8 / perm16), turned
+    // round in LDS so that rows leave 64 bytes at a time
+    uint16_t hb[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const float h = v[0][i] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0][i])) * v[1][i];
+        hb[i] = (uint16_t)(BITS == 16 ? f32_to_bf16_bits(h) : f16_bits((_Float16)h));
+    }
+    __syncthreads();                                    // the partial sums have been read
+    uint16_t* const s_h = reinterpret_cast<uint16_t*>(s_red) + ln * 40;      // 32 features a row, padded to 80 bytes
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int f = 8 * wave + 4 * kb + i;            // feature of the block's 32
+        int at = f;
+        if constexpr (BITS == 4) at = (f & ~7) + 2 * (f & 3) + ((f >> 2) & 1);
+        else if constexpr (BITS == 2) at = (f & ~15) + 2 * (f & 7) + ((f >> 3) & 1);
+        s_h[at] = hb[i];
+    }
+    __syncthreads();
+    const int row = tid >> 2;
+    if (tid < 128 && row < rows)
+        *reinterpret_cast<uint4*>(hout + (long)(row0 + row) * N + 32L * nblock + 8 * (tid & 3)) =
+            *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(s_red) + row * 40 + 8 * (tid & 3));
+}
+
+template <int MODE>
+__global__ __launch_bounds__(kSmThreads, 3) void gemm_small_kernel(
+    const uint16_t* __restrict__ x_bf16, const uint16_t* __restrict__ x_h4, const uint16_t* __restrict__ x_h2,
+    const uint16_t* __restrict__ x_h8, const uint16_t* __restrict__ hbuf_in, const uint8_t* __restrict__ bits,
+    const dymoe_expert_fmt* __restrict__ table, const int32_t* __restrict__ plan, int P, int E, int k_route, int H, int F,
+    uint16_t* __restrict__ hbuf_out, float* __restrict__ opair, int max_tiles)
+{
+    __shared__ __attribute__((aligned(16))) float s_red[kSmWaves * 2 * 16 * kWave];
+    const PlanPtrs pp = plan_ptrs(const_cast<int32_t*>(plan), E, P);
+    const int K = (MODE == 1) ? H : F, N = (MODE == 1) ? F : H;
+    const int splits = (MODE == 2) ? pp.ntiles[kPlanSplits] : 1;
+    const int nblk = N / ((MODE == 1) ? 32 : 64);
+    const int unit = blockIdx.x / nblk, bx = blockIdx.x - unit * nblk;
+    const int tile = unit / splits, bz = unit - tile * splits;
+    if (tile >= max_tiles || tile >= pp.ntiles[0]) return;
+    const int e = pp.tiles[4 * tile + 0], row0 = pp.tiles[4 * tile + 1], rows = pp.tiles[4 * tile + 2];
+    const int b = bits[e];
+    const dymoe_expert_fmt ex = table[e];
+    const int nkt = K / kBK, per = (nkt + splits - 1) / splits;
+    const int kt_begin = min(nkt, bz * per), kt_end = min(nkt, kt_begin + per);      // (a split without K-tiles writes zeros)
+    float* const oz = opair + (size_t)bz * (size_t)P * (size_t)N;
+    const uint16_t* act = (MODE != 1) ? hbuf_in : (b == 16 ? x_bf16 : (b == 8 ? x_h8 : (b == 4 ? x_h4 : x_h2)));
+    if (b == 16) small_tile<MODE, 16>(act, pp.perm, k_route, ex, K, N, kt_begin, kt_end, row0, rows, bx, hbuf_out, oz, s_red);
+    else if (b == 8) small_tile<MODE, 8>(act, pp.perm, k_route, ex, K, N, kt_begin, kt_end, row0, rows, bx, hbuf_out, oz, s_red);
+    else if (b == 4) small_tile<MODE, 4>(act, pp.perm, k_route, ex, K, N, kt_begin, kt_end, row0, rows, bx, hbuf_out, oz, s_red);
+    else small_tile<MODE, 2>(act, pp.perm, k_route, ex, K, N, kt_begin, kt_end, row0, rows, bx, hbuf_out, oz, s_red);
+}
+
 // y[t,j] = sum_slot w[t,slot] * (sum over K splits of o[z,pair,j])  (pairs of skipped experts omitted)
 // Bound: the slabs' way from memory.  SLOTS slots' rows are requested together, whether or not their experts run (a row
 // inside the slab that no workgroup wrote is read and not used): one after the other behind their experts' bit widths, a
@@ -838,15 +1077,40 @@ bool ffn_gemm_fits(int T, int H, int F, int E, int k)
 // The intermediate takes half of its area (16-bit values where the other path has fp32): the slabs start behind it.
 static size_t slabs_offset(int T, int F, int k, const FfnLayout& L) { return L.hbuf + round256((size_t)T * k * F * 2); }
 
+// Whether the first GEMM takes gemm_small_kernel: tiles of one fragment, and no more workgroups than are resident together; more
+// of them pay a workgroup's start (plan -> expert -> pointers -> first rows, 3 us) once per round.  us, large / small: 7 tokens
+// x 6 of 16 experts, 1024 x 512 (256 workgroups) 9.7 / 5.9; 10 x 4 of 60, 1280 x 256 (240) 12.2 / 6.6; but 6 x 8 of 8, 1664 x
+// 3968 (992) 14.4 / 16.8 and 80 x 2 of 64, 512 x 4864 (9100) 39 / 52.
+static bool small_first(const dymoe_ctx* ctx, int T, int F, int E, int k)
+{
+    const long P = (long)T * k, tiles = E < P ? E : P;
+    return ffn_tile_rows(T, E, k) == kGemmTileSmall && (F / 32) * tiles <= 3L * ctx->num_cu;
+}
+
+// The second GEMM, which splits K as well: up to five rounds' worth of a workgroup per compute unit; not where a few experts'
+// long rows give the other kernel one and a half rounds of splits, since there the bf16 expert's workgroups are what the launch
+// waits for and a shorter chain does not help.  us, large / small: 33 tokens x 1 of 8, 384 x 2048 7.5 / 5.0; 25 x 1 of 128,
+// 1024 x 1408 15.8 / 10.1; 48 x 1 of 30, 2688 x 5504 57 / 49; 80 x 2 of 64, 512 x 4864 22.5 / 21.3; but 29 x 2 of 8, 2048 x 5248
+// 13.4 / 15.1, 24 x 2 of 8, 4096 x 14336 61 / 66 and 94 x 8 of 128, 1152 x 1152 (2300 workgroups) 23.8 / 27.5.
+static bool small_second(const dymoe_ctx* ctx, int T, int H, int F, int E, int k)
+{
+    const long P = (long)T * k, tiles = E < P ? E : P;
+    const long nblk = (H + 64 * kGmWaves - 1) / (64 * kGmWaves);
+    if (tiles <= 16 && F >= 24 * kBK && 8 * nblk * tiles >= 3L * ctx->num_cu / 2) return false;
+    return ffn_tile_rows(T, E, k) == kGemmTileSmall && (H / 64) * tiles <= 5L * ctx->num_cu;
+}
+
 SplitRule split_rule(const dymoe_ctx* ctx, int T, int H, int F, int E, int k, const FfnLayout& L)
 {
     const long P = (long)T * k;
     SplitRule r;
-    r.nblk = (H + 64 * kGmWaves - 1) / (64 * kGmWaves);
+    r.small = small_second(ctx, T, H, F, E, k);
+    r.nblk = r.small ? H / 64 : (H + 64 * kGmWaves - 1) / (64 * kGmWaves);
     r.n_kt = F / kBK;
     r.num_cu = ctx->num_cu;
     long most = (long)((L.xh - slabs_offset(T, F, k, L)) / ((size_t)P * H * 4));        // slabs the workspace holds
-    if (most > F / 256) most = F / 256;                                                 // two K-tiles per split at least
+    const int least = r.small ? 2 * kSmWaves * kBK : 2 * kBK;                           // two K-tiles per chain at least
+    if (most > F / least) most = F / least;
     // no more workgroups than 4 per compute unit if every expert has tokens (every one of them has a tile, and P / 128 more at most)
     const long blocks = r.nblk * ((E < P ? E : P) + P / (2 * kGemmTileM));
     if (most > 4L * r.num_cu / blocks) most = 4L * r.num_cu / blocks;
@@ -881,21 +1145,31 @@ int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     // what the kernels after the plan take as the bit widths: the plan's copy, 0 where the table lacks the format
     const uint8_t* run_bits = reinterpret_cast<const uint8_t*>(plan_ptrs(plan, E, P).cursor);
     constexpr size_t kLdsBytes = kGemmLdsBytes;
-    const int max_tiles = P / kGemmTileM + E;
-    const int cols1 = 32 * kGmWaves, cols2 = 64 * kGmWaves;
-    const int nblk1 = (F + cols1 - 1) / cols1;
-    const dim3 g1((unsigned)(8 * nblk1 * ((max_tiles + 7) / 8)));
-    dymoe_launch(ctx, DYMOE_K_GEMM1, (gemm_kernel<1>), g1, dim3(kGmThreads), kLdsBytes, st, xb, xh4, xh2, xh8,
-                 (const uint16_t*)nullptr, run_bits, table, plan, P, E, k, H, F, hbuf, (float*)nullptr, max_tiles);
+    const int max_tiles = P / ffn_tile_rows(T, E, k) + E;
+    if (small_first(ctx, T, F, E, k)) {
+        dymoe_launch(ctx, DYMOE_K_GEMM1, (gemm_small_kernel<1>), dim3((unsigned)((F / 32) * max_tiles)), dim3(kSmThreads), 0, st, xb, xh4,
+                     xh2, xh8, (const uint16_t*)nullptr, run_bits, table, plan, P, E, k, H, F, hbuf, (float*)nullptr, max_tiles);
+    } else {
+        const int cols1 = 32 * kGmWaves;
+        const int nblk1 = (F + cols1 - 1) / cols1;
+        const dim3 g1((unsigned)(8 * nblk1 * ((max_tiles + 7) / 8)));
+        dymoe_launch(ctx, DYMOE_K_GEMM1, (gemm_kernel<1>), g1, dim3(kGmThreads), kLdsBytes, st, xb, xh4, xh2, xh8,
+                     (const uint16_t*)nullptr, run_bits, table, plan, P, E, k, H, F, hbuf, (float*)nullptr, max_tiles);
+    }
     DYMOE_HIP_LAUNCH_CHECK();
     // The down projection has few output tiles: K is split so that the launch covers the chip.  Each split writes its own slab
     // of per-pair outputs and the combine kernel adds the slabs in a fixed order.  The plan chooses the number (it knows the
     // tiles); workgroups beyond it end at once.
-    const int nblk2 = (H + cols2 - 1) / cols2;
-    const int units = max_tiles * split_rule(ctx, T, H, F, E, k, L).max;
-    const dim3 g2((unsigned)(8 * nblk2 * ((units + 7) / 8)));
-    dymoe_launch(ctx, DYMOE_K_GEMM2, (gemm_kernel<2>), g2, dim3(kGmThreads), kLdsBytes, st, xb, xh4, xh2, xh8, hbuf,
-                 run_bits, table, plan, P, E, k, H, F, (uint16_t*)nullptr, opair, max_tiles);
+    const SplitRule rule = split_rule(ctx, T, H, F, E, k, L);
+    const int units = max_tiles * rule.max;
+    if (rule.small) {
+        dymoe_launch(ctx, DYMOE_K_GEMM2, (gemm_small_kernel<2>), dim3((unsigned)(rule.nblk * units)), dim3(kSmThreads), 0, st, xb, xh4,
+                     xh2, xh8, hbuf, run_bits, table, plan, P, E, k, H, F, (uint16_t*)nullptr, opair, max_tiles);
+    } else {
+        const dim3 g2((unsigned)(8 * rule.nblk * ((units + 7) / 8)));
+        dymoe_launch(ctx, DYMOE_K_GEMM2, (gemm_kernel<2>), g2, dim3(kGmThreads), kLdsBytes, st, xb, xh4, xh2, xh8, hbuf,
+                     run_bits, table, plan, P, E, k, H, F, (uint16_t*)nullptr, opair, max_tiles);
+    }
     DYMOE_HIP_LAUNCH_CHECK();
     const long n4 = (long)T * (H / 4);
     auto combine = [&](auto kernel) {

@@ -11,6 +11,14 @@ constexpr int kGemmTileM = 128;   // token rows per grouped-GEMM tile
 constexpr int kGemmTileTall = 160; // the last tile of an int4 / int2 expert also takes a remainder of up to 32 rows
 constexpr int kPlanTileMin = 32;  // sizing granularity of the tile list
 
+// Token rows per grouped-GEMM tile.  Few tokens per expert: tiles of one 32-row fragment, for the kernel that streams weights
+// with all four wavefronts of a workgroup on the same columns.
+constexpr int kGemmTileSmall = 32;
+static inline int ffn_tile_rows(int T, int E, int k)
+{
+    return (T <= 32 || (T <= 128 && (long)T * k <= 8L * E)) ? kGemmTileSmall : kGemmTileM;
+}
+
 struct FfnLayout {
     size_t hbuf;    // [P,F] SwiGLU intermediate: fp32 (GEMV) or 16-bit (GEMM)
     size_t part;    // GEMM: [P,H] fp32 per-pair outputs (the GEMV path keeps its partial sums on chip; the area is sized as before)

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const int32_t* __res
         s_count[e] = (b != 0 && !(b & 0x80)) ? total : 0;                           // ... and leave its pairs out
     }
     __syncthreads();
-    plan_scan(E, s_count, s_bits, s_off, s_tile0, splits, pp);
+    plan_scan(E, tile_m, s_count, s_bits, s_off, s_tile0, splits, pp);
     if (s_tile0[E] <= kPlanShortList) plan_tile_list(E, tile_m, s_count, s_bits, s_off, s_tile0, s_cnt, pp);
     else plan_tile_list_long(E, tile_m, s_count, s_bits, s_off, s_tile0, pp.tiles + 4 * (size_t)max_tiles, pp);
     plan_tables(E, s_count, s_bits, s_off, pp);
@@ -116,7 +116,7 @@ int plan_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const uint8_t
     uint16_t* xh8 = xh2 + round256((size_t)T * H * 2) / 2;
     const long n16 = (long)T * H / 16;
     dymoe_launch(ctx, DYMOE_K_PLAN, plan_kernel, dim3((unsigned)(1 + (n16 + kPlanThreads - 1) / kPlanThreads)), dim3(kPlanThreads), 0,
-                 st, idx, bits, table, T * k, E, kGemmTileM, L.max_tiles, splits, reinterpret_cast<int32_t*>(ws + L.plan), ctx->device_flags,
+                 st, idx, bits, table, T * k, E, ffn_tile_rows(T, E, k), L.max_tiles, splits, reinterpret_cast<int32_t*>(ws + L.plan), ctx->device_flags,
                  (const uint16_t*)x, n16, xh4, xh2, xh8);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
@@ -146,6 +146,7 @@ struct RankPlanArgs {
     int32_t* rank;
     const dymoe_expert_fmt* table;
     int formats;                       // sum of the bit widths the tiers can assign
+    int tile_m;
     SplitRule splits;
     int32_t* plan;
     unsigned* flags;
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(kPlanThreads) void rank_plan_kernel(const RankPlanA
         s_count[tid] = b ? total : 0;
     }
     __syncthreads();
-    plan_scan(E, s_count, s_bits, s_off, s_tile0, a.splits, pp);
+    plan_scan(E, a.tile_m, s_count, s_bits, s_off, s_tile0, a.splits, pp);
     // the wavefronts' first positions among all pairs; negative where the expert is left out
     for (int i = tid; i < kPlanWaves * E; i += kPlanThreads) {
         const int e = i % E;
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(kPlanThreads) void rank_plan_kernel(const RankPlanA
         }
     }
     plan_tables(E, s_count, s_bits, s_off, pp);
-    plan_tile_list(E, kGemmTileM, s_count, s_bits, s_off, s_tile0, s_cnt, pp);
+    plan_tile_list(E, a.tile_m, s_count, s_bits, s_off, s_tile0, s_cnt, pp);
 }
 
 bool rank_plan_fits(int T, int E, int k)
@@ -468,6 +469,7 @@ int rank_plan_launch(dymoe_ctx* ctx, bool prefill, const void* x, const int32_t*
     a.table = table;
     for (int i = 0; i < tiers.n; i++)
         if (tiers.count[i] > 0) a.formats |= tiers.bits[i] < floor_bits ? floor_bits : tiers.bits[i];
+    a.tile_m = ffn_tile_rows(T, E, k);
     a.splits = splits;
     a.plan = reinterpret_cast<int32_t*>(ws + L.plan);
     a.flags = ctx->device_flags;

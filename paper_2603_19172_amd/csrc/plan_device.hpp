@@ -17,9 +17,9 @@ __device__ __forceinline__ bool plan_tall(int c, int b)
     const int r = c % kGemmTileM;
     return (b == 4 || b == 2) && c > kGemmTileM && r >= 1 && r <= kGemmTileTall - kGemmTileM;
 }
-__device__ __forceinline__ int plan_tiles_of(int c, int b)
+__device__ __forceinline__ int plan_tiles_of(int c, int b, int tile_m)
 {
-    return (c + kGemmTileM - 1) / kGemmTileM - (plan_tall(c, b) ? 1 : 0);
+    return (c + tile_m - 1) / tile_m - (tile_m == kGemmTileM && plan_tall(c, b) ? 1 : 0);
 }
 
 // ints: counts[E] | offsets[E+1] | cursor[E] | ntiles (8 ints) | perm[P] | tiles[4*max_tiles] | draft[4*max_tiles]
@@ -121,9 +121,10 @@ __device__ __forceinline__ int plan_gather(int e, int E, int32_t* s_priv)
 }
 
 // Number of K splits of the second GEMM: nblk column blocks, n_kt K-tiles, up to max splits, num_cu compute units that hold two
-// workgroups each.
+// workgroups each (small: of the kernel for tiles of one fragment, which holds three).
 struct SplitRule {
     int nblk, n_kt, max, num_cu;
+    bool small;
 };
 constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the tile counts
 
@@ -134,7 +135,8 @@ constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the ti
 // (rounds + 0.3) / s beyond, and every split writes and reads a slab, 0.0147 blocks / n_kt (a copy's rate against the matrix
 // cores').  us, GEMM and combine: 512 tokens of the Mixtral shape (9 x 16) 1 split 328, 2 209, 3 170, 4 189, 6 180; 433
 // tokens x 4 of 2048 x 6272 (16 x 8) 101, 68, 77, 73; 580 x 4 of 896 x 2560 (20 x 4) 59, 39, 34; 315 x 2 of 1792 x 3584
-// (16 x 7) 40, 29, 31.
+// (16 x 7) 40, 29, 31.  The kernel for tiles of one fragment splits K over its wavefronts already: no more than 24 K-tiles per
+// split, so that a bf16 expert's workgroups do not outlast the launch (80 tokens of 512 x 4864: 25.4 us with 38, 21.3 with 19).
 // By one wavefront, a lane per number (max <= 64); the least cost, the smaller number of equals.
 __device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRule& r, const PlanPtrs& pp)
 {
@@ -142,8 +144,10 @@ __device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRul
     const int blocks = max(1, r.nblk * tiles);
     int best = 1;
     if (r.max > 1) {
-        if (pairs <= 32 * tiles) {
-            best = max(1, min(r.max, 3 * r.num_cu / blocks));
+        if (r.small || pairs <= 32 * tiles) {
+            best = 3 * r.num_cu / blocks;
+            if (r.small) best = max(best, (r.n_kt + 12) / 24);
+            best = max(1, min(r.max, best));
         } else {
             const int n = blocks * s;
             const float rounds = n <= r.num_cu ? 0.55f : n <= 2 * r.num_cu ? 1.0f : 0.5f * (float)n / (float)r.num_cu + 0.3f;
@@ -156,7 +160,7 @@ __device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRul
 
 // s_count, s_bits: pairs and bit width of every expert (no pairs where it does not run) -> first pair and first tile of
 // each, the totals to memory.  The caller's s_count and s_bits are visible to all; so are the results.
-__device__ __forceinline__ void plan_scan(int E, const int32_t* s_count, const uint8_t* s_bits, int32_t* s_off, int32_t* s_tile0,
+__device__ __forceinline__ void plan_scan(int E, int tile_m, const int32_t* s_count, const uint8_t* s_bits, int32_t* s_off, int32_t* s_tile0,
                                           const SplitRule& splits, const PlanPtrs& pp)
 {
     const int tid = threadIdx.x, wave = tid / kWave;
@@ -167,7 +171,7 @@ __device__ __forceinline__ void plan_scan(int E, const int32_t* s_count, const u
         for (int e0 = 0; e0 < E; e0 += kWave) {
             const int e = e0 + lane;
             const int c = (e < E) ? s_count[e] : 0;
-            const int nt_e = (e < E) ? plan_tiles_of(c, s_bits[e]) : 0;
+            const int nt_e = (e < E) ? plan_tiles_of(c, s_bits[e], tile_m) : 0;
             const int incl = wave_scan_dpp_i32(c), tincl = wave_scan_dpp_i32(nt_e);
             if (e < E) {
                 s_off[e] = run + incl - c;

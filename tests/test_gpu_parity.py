@@ -1229,3 +1229,32 @@ def test_decode_layer_equals_the_separate_calls(ctx, T, H, E, k, floor, chained)
     for u, v in zip((la.idx, la.gate, la.probs, la.imp, la.load, la.bits, la.rank, la.y),
                     (lb.idx, lb.gate, lb.probs, lb.imp, lb.load, lb.bits, lb.rank, lb.y)):
         assert torch.equal(u, v)
+
+
+# tiles of one fragment (up to 32 tokens, or up to 128 and eight pairs per expert): every format, expert loads around 32 rows, K-tiles
+# that the four wavefronts share unevenly or that are fewer than they, several splits, the larger kernel on the same tiles
+@pytest.mark.parametrize("T,H,F,E,k", [(5, 128, 128, 5, 2), (32, 256, 1152, 5, 5), (31, 384, 2048, 8, 1), (33, 128, 256, 8, 1),
+                                       (77, 640, 384, 40, 4), (128, 128, 640, 128, 8), (17, 2048, 4224, 8, 2), (9, 1280, 6272, 5, 3)])
+def test_ffn_gemm_one_fragment_tiles(ctx, T, H, F, E, k):
+    cfg = synth.scaled(synth.CONFIGS["tiny"], config_id=700 + T, T=T, H=H, F=F, E=E, k=k, tier_count=(E,))
+    x, _ = synth.activations(cfg)
+    rng = np.random.default_rng(T)
+    idx = np.stack([rng.permutation(E)[:k] for _ in range(T)]).astype(np.int32)
+    if T == 77:
+        idx[:40, 0] = 3                                          # 33 to 64 rows: two tiles, the second one short
+        for t in range(40):
+            idx[t, 1:] = [e for e in rng.permutation(E) if e != 3][:k - 1]
+    w = (rng.random((T, k)) + 0.1).astype(np.float32)
+    bits_np = np.array([(16, 8, 4, 2, 0)[e % 5] for e in range(E)], np.uint8)
+    host, dev, table, keep = build_layer(cfg, bits_np, path=B.PATH_GEMM)
+    ref = oracle_ffn(cfg, x, idx, w, bits_np, host)
+    y = run_ffn(ctx, cfg, x, idx, w, bits_np, table, B.PATH_GEMM)
+    some = (bits_np[idx] != 0).any(axis=1)
+    err = rel_err_per_token(y[some], ref[some])
+    print("one-fragment tiles", (T, H, F, E, k), "err=%.3e" % err)
+    assert err <= FFN_TOL and (y[~some] == 0).all()
+    # 16-bit experts without a tile copy are read row by row: same result
+    for e in range(0, E, 5):
+        dev[e].pop("wt")
+    table2, keep2 = B.make_expert_table(dev, DEV)
+    assert np.array_equal(y, run_ffn(ctx, cfg, x, idx, w, bits_np, table2, B.PATH_GEMM))
