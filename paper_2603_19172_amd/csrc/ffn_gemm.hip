@@ -1018,12 +1018,23 @@ __global__ __launch_bounds__(256) void gemm_combine_kernel(
             g[u] = w[p[u]];
             o[u] = load_global<float4>(opair + p[u] * H + j);
         }
-#pragma unroll 8 / SLOTS
-        for (int z = 1; z < splits; z++) {
+        // the other slabs, two at a time where the registers leave wavefronts enough
+        constexpr int kSlabs = SLOTS <= 4 ? 2 : 1;
+        for (int z = 1; z < splits; z += kSlabs) {
+            float4 oa[SLOTS], ob[SLOTS];
+            const bool two = kSlabs == 2 && z + 1 < splits;
+#pragma unroll
+            for (int u = 0; u < SLOTS; u++) oa[u] = load_global<float4>(opair + ((long)z * T * k + p[u]) * H + j);
+            if (two) {
+#pragma unroll
+                for (int u = 0; u < SLOTS; u++) ob[u] = load_global<float4>(opair + ((long)(z + 1) * T * k + p[u]) * H + j);
+            }
 #pragma unroll
             for (int u = 0; u < SLOTS; u++) {
-                const float4 oz = load_global<float4>(opair + ((long)z * T * k + p[u]) * H + j);
-                o[u].x += oz.x; o[u].y += oz.y; o[u].z += oz.z; o[u].w += oz.w;
+                o[u].x += oa[u].x; o[u].y += oa[u].y; o[u].z += oa[u].z; o[u].w += oa[u].w;
+                if (two) {
+                    o[u].x += ob[u].x; o[u].y += ob[u].y; o[u].z += ob[u].z; o[u].w += ob[u].w;
+                }
             }
         }
 #pragma unroll

@@ -19,7 +19,9 @@ __device__ __forceinline__ bool plan_tall(int c, int b)
 }
 __device__ __forceinline__ int plan_tiles_of(int c, int b, int tile_m)
 {
-    return (c + tile_m - 1) / tile_m - (tile_m == kGemmTileM && plan_tall(c, b) ? 1 : 0);
+    const int lg = tile_m == kGemmTileM ? 7 : 5;
+    static_assert(kGemmTileM == 1 << 7 && kGemmTileSmall == 1 << 5, "tiles of 128 or 32 rows");
+    return ((c + tile_m - 1) >> lg) - (tile_m == kGemmTileM && plan_tall(c, b) ? 1 : 0);
 }
 
 // ints: counts[E] | offsets[E+1] | cursor[E] | ntiles (8 ints) | perm[P] | tiles[4*max_tiles] | draft[4*max_tiles]
