@@ -27,6 +27,8 @@
 //                  and the errors e of the row are written;
 //   trail kernel   v[:, j] for the columns behind the panel: 256 chained fmas per element.
 // The working copy v of the matrix (fp32) lives in the caller's workspace.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dymoe {
@@ -34,6 +36,7 @@ namespace dymoe {
 constexpr int kGqGroup = 64;        // columns per group
 constexpr int kGqRows = 64;         // rows per row block
 constexpr int kGqPanel = 4;         // groups per panel
+constexpr int kGqChunk = 16;        // columns per piece of a group's chain
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
@@ -77,8 +80,10 @@ __device__ __forceinline__ float quad_bcast(float v)
 // from it, so the rounding to float is the quotient's own, in 3 dependent instructions instead of the dozen of an IEEE
 // division.  Halfway cases only exist among subnormal quotients: those are recognised and the group is done again with
 // the division itself.
-template <int BITS, typename Emit>
-__device__ __forceinline__ bool gq_group_chain(float (&x)[16], int q, float m, float s, float inv, const float* s_d,
+// One call does 16 columns, T0 .. T0 + 15 of the group: x[i] is column T0 + 4 i + q; what their errors do to the group's later
+// columns is the caller's.
+template <int BITS, int T0, typename Emit>
+__device__ __forceinline__ bool gq_chunk_chain(float (&x)[4], int q, float m, float s, float inv, const float* s_d,
                                                const double* s_inv, uint32_t* words, Emit emit)
 {
 #pragma clang fp contract(off)
@@ -86,35 +91,33 @@ __device__ __forceinline__ bool gq_group_chain(float (&x)[16], int q, float m, f
     constexpr int per_word = 32 / BITS;
     bool subnormal = false;
     float keep = 0.0f;
-    // the rows of the diagonal block, two steps' worth at a time, one batch ahead of their use: the scheduling barriers
-    // keep the compiler from fetching the whole block up front (and spilling it) or each row only when it is needed
-    float4 d[2][2][4];
+    // the rows of the diagonal block (the lane's four columns), two steps' worth at a time, one batch ahead of their use: the
+    // scheduling barriers keep the compiler from fetching each row only when it is needed
+    float4 d[2][2];
     double rcp[2][2];
     auto fetch = [&](int b) {
 #pragma unroll
         for (int c = 0; c < 2; c++) {
-            rcp[b & 1][c] = s_inv[2 * b + c];
-#pragma unroll
-            for (int j = 0; j < 4; j++)
-                if (4 * j + 3 >= b / 2) d[b & 1][c][j] = *reinterpret_cast<const float4*>(s_d + (2 * b + c) * kGqGroup + q * 16 + 4 * j);
+            rcp[b & 1][c] = s_inv[T0 + 2 * b + c];
+            d[b & 1][c] = *reinterpret_cast<const float4*>(s_d + (T0 + 2 * b + c) * kGqChunk + 4 * q);
         }
     };
     fetch(0);
 #pragma unroll
-    for (int b = 0; b < kGqGroup / 2; b++) {
+    for (int b = 0; b < kGqChunk / 2; b++) {
         __builtin_amdgcn_sched_barrier(0);
-        if (b + 1 < kGqGroup / 2) fetch(b + 1);
+        if (b + 1 < kGqChunk / 2) fetch(b + 1);
         __builtin_amdgcn_sched_barrier(0);
         const int k = b / 2;
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-            const int i = 2 * b + h, c = i & 3;
+            const int i = 2 * b + h, c = i & 3, at = T0 + i;
             const float xi = c == 0 ? quad_bcast<0>(x[k]) : c == 1 ? quad_bcast<1>(x[k]) : c == 2 ? quad_bcast<2>(x[k]) : quad_bcast<3>(x[k]);
             const float t = xi - m;
             float r = __builtin_rintf(t * inv);
             r = fminf(fmaxf(r, 0.0f), (float)qmax);
-            if (i % per_word == 0) words[i / per_word] = 0u;
-            words[i / per_word] |= (uint32_t)(int)r << (BITS * (i % per_word));
+            if (at % per_word == 0) words[at / per_word] = 0u;
+            words[at / per_word] |= (uint32_t)(int)r << (BITS * (at % per_word));
             float dq = r * s;
             dq = dq + m;
             const float rest = xi - dq;
@@ -123,22 +126,20 @@ __device__ __forceinline__ bool gq_group_chain(float (&x)[16], int q, float m, f
             const float ne = -e;
             keep = (q == c) ? ne : keep;
             // (columns of register k that are already done change too; nothing reads them any more)
+            const float dd[4] = {d[b & 1][h].x, d[b & 1][h].y, d[b & 1][h].z, d[b & 1][h].w};
 #pragma unroll
-            for (int j = (c == 3) ? k + 1 : k; j < 16; j++) {
-                const float4& dd = d[b & 1][h][j >> 2];
-                x[j] = __builtin_fmaf(ne, (j & 3) == 0 ? dd.x : (j & 3) == 1 ? dd.y : (j & 3) == 2 ? dd.z : dd.w, x[j]);
-            }
+            for (int j = (c == 3) ? k + 1 : k; j < 4; j++) x[j] = __builtin_fmaf(ne, dd[j], x[j]);
         }
-        if (b & 1) emit(k, keep);
+        if (b & 1) emit(T0 / 4 + k, keep);
     }
     return subnormal;
 }
 
-// The same group with the division itself, for rows with subnormal quotients: rare, so rolled up and in LDS (sx: the
-// wavefront's 16 x 64 values, overwritten).
+// A whole group with the division itself, for rows with subnormal quotients: rare, so rolled up and in LDS (sx: the
+// wavefront's 16 x 64 values, overwritten), the rows of U (ud: its diagonal block, row stride K) from memory.
 template <int BITS, typename Emit>
-__device__ __forceinline__ void gq_group_chain_exact(float* sx, int r, int q, float m, float s, float inv, const float* s_d,
-                                                  uint32_t* words, Emit emit)
+__device__ __forceinline__ void gq_group_chain_exact(float* sx, int r, int q, float m, float s, float inv, const float* __restrict__ ud,
+                                                     long K, uint32_t* words, Emit emit)
 {
 #pragma clang fp contract(off)
     constexpr int qmax = (1 << BITS) - 1;
@@ -152,11 +153,11 @@ __device__ __forceinline__ void gq_group_chain_exact(float* sx, int r, int q, fl
         t = fminf(fmaxf(__builtin_rintf(t), 0.0f), (float)qmax);
         float dq = t * s;
         dq = dq + m;
-        const float ne = -((xi - dq) / s_d[i * kGqGroup + (i & 3) * 16 + (i >> 2)]);
+        const float ne = -((xi - dq) / ud[(long)i * K + i]);
         keep = (q == (i & 3)) ? ne : keep;
         if ((i & 3) == 3) emit(i >> 2, keep);
         for (int j = (i & ~3) + q; j < kGqGroup; j += 4)
-            if (j > i) row[j] = __builtin_fmaf(ne, s_d[i * kGqGroup + q * 16 + (j >> 2)], row[j]);
+            if (j > i) row[j] = __builtin_fmaf(ne, ud[(long)i * K + j], row[j]);
         if (q == (i & 3)) row[i] = t;                           // the code, in the place of the value
     }
 #pragma unroll
@@ -168,10 +169,11 @@ __device__ __forceinline__ void gq_group_chain_exact(float* sx, int r, int q, fl
 
 // One panel of up to four groups: rows in blocks of 64 (a workgroup), 16 rows a wavefront.  FIRST: the values come from
 // the bf16 matrix itself (nothing has been corrected yet), so the working copy is never filled by a pass of its own.
-// Bound: the chain of 64 dependent quantise-and-correct steps per group.  Splitting a row over four lanes keeps the fmas
-// of a step (16 at most) under the step's latency and puts 896 wavefronts on the chip's 1024 SIMDs for 14336 rows, where
-// a lane per row had 224 wavefronts with up to 63 fmas to issue in a step.  14336 x 4096, int4: 40 us per panel, i.e.
-// 10 us per group with the corrections inside the panel; a lane per row took 19 us per group and 11 us for those.
+// Bound: the chain of 64 dependent quantise-and-correct steps per group, 52 ns each, and the products between groups.  Four
+// lanes share a row, so that 896 wavefronts work on the chip's 1024 SIMDs for 14336 rows; the chain corrects 16 columns only
+// (four a lane: as few as its own latency covers, and a quarter of the reads of U from LDS), the group's later columns get
+// those 16 errors as matrix products.  14336 x 4096, int4: 31 us per panel (2 to start, 4.5 per group, 8.6 between the groups);
+// with the chain correcting all 64 columns 40 us, with a lane per row 120.
 template <int BITS, bool FIRST>
 __global__ __launch_bounds__(256) void gptq_group_kernel(
     const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K, long base,
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(256) void gptq_group_kernel(
     constexpr int qmax = (1 << BITS) - 1;
     constexpr int n_words = kGqGroup * BITS / 32;               // 16 (int8), 8 (int4), 4 (int2)
     constexpr int kStride = kGqGroup + 4;
-    __shared__ __attribute__((aligned(16))) float s_d[kGqPanel][kGqGroup * kGqGroup];   // [c][j % 4][j / 4]
+    __shared__ __attribute__((aligned(16))) float s_d[kGqPanel][kGqGroup * kGqChunk];   // the 16 x 16 diagonal blocks, [c][j % 4][j / 4]
     __shared__ __attribute__((aligned(16))) double s_inv[kGqPanel * kGqGroup];
     __shared__ __attribute__((aligned(16))) float s_e[4][kGqPanel * kGqGroup * 16];   // per wavefront [column][row], negated
     __shared__ __attribute__((aligned(16))) float s_x[4][16 * kStride];
@@ -209,11 +211,11 @@ __global__ __launch_bounds__(256) void gptq_group_kernel(
         const long c = base + at;
         s_inv[at] = 1.0 / (double)u[c * K + c];
     }
-    for (int at = tid; at < n_groups * kGqGroup * 16; at += 256) {
-        const int g = at >> 10, c = (at >> 4) & 63, m = at & 15;
-        const float4 d = *reinterpret_cast<const float4*>(u + (base + kGqGroup * g + c) * K + base + kGqGroup * g + 4 * m);
-        float* dst = &s_d[g][c * kGqGroup + m];
-        dst[0] = d.x; dst[16] = d.y; dst[32] = d.z; dst[48] = d.w;
+    for (int at = tid; at < n_groups * kGqGroup * 4; at += 256) {
+        const int g = at >> 8, c = (at >> 2) & 63, i = at & 3;
+        const float4 d = *reinterpret_cast<const float4*>(u + (base + kGqGroup * g + c) * K + base + kGqGroup * g + (c & ~15) + 4 * i);
+        float* dst = &s_d[g][c * kGqChunk + i];
+        dst[0] = d.x; dst[4] = d.y; dst[8] = d.z; dst[12] = d.w;
     }
     __syncthreads();            // and every wavefront has its values in registers: v may now be overwritten by errors
     const int r = lane >> 2, q = lane & 3;                      // the chain's layout: row r, columns 4 m + q
@@ -273,12 +275,30 @@ __global__ __launch_bounds__(256) void gptq_group_kernel(
             for (int i = 0; i < 4; i++) cur[0][i] = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
         }
         if (g + 1 < n_groups) fetch(0, bp);
+        // U between the group's pieces of 16 columns: rows 16 t + 4 kk + rg, columns 16 tt + cl, tt > t
+        float between[24];
+        const float* const ud = u + (base + kGqGroup * g) * K + base + kGqGroup * g;
+        {
+            int n = 0;
+#pragma unroll
+            for (int t = 0; t < 3; t++)
+#pragma unroll
+                for (int tt = t + 1; tt < 4; tt++)
+#pragma unroll
+                    for (int kk = 0; kk < 4; kk++) between[n++] = load_global<float>(ud + (long)(16 * t + 4 * kk + rg) * K + 16 * tt + cl);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         float* const sx = s_x[wave];                            // one wavefront's own: no barrier
 #pragma unroll
         for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * rg + i) * kStride + 4 * cl]) = cur[0][i];
         float x[16];
 #pragma unroll
         for (int m = 0; m < 16; m++) x[m] = sx[r * kStride + 4 * m + q];
+        f32x4_t later[3];                                       // the pieces behind the first, in the matrix instructions' layout
+#pragma unroll
+        for (int tt = 1; tt < 4; tt++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) later[tt - 1][i] = sx[(4 * rg + i) * kStride + 16 * tt + cl];
         float lo = x[0], hi = x[0];
 #pragma unroll
         for (int m = 1; m < 16; m++) {
@@ -301,8 +321,41 @@ __global__ __launch_bounds__(256) void gptq_group_kernel(
             se[k * 64] = ne;
             eb[(long)(16 * g + k) * eld] = ne;                  // (unread behind the last panel; the place is dead all the same)
         };
-        if (__any(gq_group_chain<BITS>(x, q, m, s, inv, s_d[g], &s_inv[g * kGqGroup], words, emit)))
-            gq_group_chain_exact<BITS>(sx, r, q, m, s, inv, s_d[g], words, emit);
+        // Sixteen columns by the chain, then their products onto the pieces behind them, errors ascending as the chain would
+        // have applied them.
+        float piece[4] = {x[0], x[1], x[2], x[3]};
+        const double* const si = &s_inv[g * kGqGroup];
+        auto carry = [&](auto from) {
+            constexpr int T = decltype(from)::value, first = T == 0 ? 0 : T == 1 ? 12 : 20;
+            const float* const ap = &s_e[wave][(g * kGqGroup + 16 * T) * 16 + lane];
+            float a[4];
+#pragma unroll
+            for (int kk = 0; kk < 4; kk++) a[kk] = ap[kk * 64];
+#pragma unroll
+            for (int tt = T + 1; tt < 4; tt++) {
+#pragma unroll
+                for (int kk = 0; kk < 4; kk++)
+                    later[tt - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], between[first + 4 * (tt - T - 1) + kk], later[tt - 1], 0, 0, 0);
+                if (tt == T + 1) {
+#pragma unroll
+                    for (int i = 0; i < 4; i++) sx[(4 * rg + i) * kStride + 16 * tt + cl] = later[tt - 1][i];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) piece[i] = sx[r * kStride + 16 * tt + 4 * i + q];
+                }
+            }
+        };
+        bool subnormal = gq_chunk_chain<BITS, 0>(piece, q, m, s, inv, s_d[g], si, words, emit);
+        carry(std::integral_constant<int, 0>());
+        subnormal |= gq_chunk_chain<BITS, 16>(piece, q, m, s, inv, s_d[g], si, words, emit);
+        carry(std::integral_constant<int, 1>());
+        subnormal |= gq_chunk_chain<BITS, 32>(piece, q, m, s, inv, s_d[g], si, words, emit);
+        carry(std::integral_constant<int, 2>());
+        subnormal |= gq_chunk_chain<BITS, 48>(piece, q, m, s, inv, s_d[g], si, words, emit);
+        if (__any(subnormal)) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * rg + i) * kStride + 4 * cl]) = cur[0][i];
+            gq_group_chain_exact<BITS>(sx, r, q, m, s, inv, ud, K, words, emit);
+        }
         if (row < N) {
             uint8_t* dst = codes + (row * K + base + kGqGroup * g) * BITS / 8;
             constexpr int mine = n_words / 4;                   // each lane of a quad writes a quarter of the row's codes
