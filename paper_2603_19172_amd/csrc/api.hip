@@ -217,7 +217,7 @@ const char* dymoe_kernel_name(int kernel)
     case DYMOE_K_GPTQ_GROUP: return "gptq_group_kernel";
     case DYMOE_K_GPTQ_TRAIL: return "gptq_trail_kernel";
     case DYMOE_K_GPTQ_HESSIAN: return "gptq_hessian_kernel";
-    case DYMOE_K_GPTQ_FACTOR: return "gptq_chol_diag_kernel";
+    case DYMOE_K_GPTQ_FACTOR: return "gptq_step_kernel";
     case DYMOE_K_MFMA_PEAK: return "mfma_peak_kernel";
     case DYMOE_K_ROUTE_SELECT: return "route_select_kernel";
     default: return nullptr;

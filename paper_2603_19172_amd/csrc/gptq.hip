@@ -388,10 +388,10 @@ struct GqTile {
 // ap, bp: this wavefront's share of the operands, tile w % 2 and the c's 4 (w / 2) .. + 3 and 8 + 4 (w / 2) .. + 3 of a stage, at the
 // lane's own place (c = rg, row or column 4 cl); lda4, ldb4: four c's further.
 template <bool NEG_A>
-__device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, const float* ap, long lda4, const float* bp, long ldb4, int n)
+__device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int wave, const float* ap, long lda4, const float* bp, long ldb4, int n)
 {
     constexpr int kStage = 2 * 16 * kGqGroup;                   // floats of one operand
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     float* const put = s_op + (wave & 1) * 16 * kGqGroup + (wave >> 1) * 4 * kGqGroup + 4 * lane;
     const float* const get_a = s_op + (wave >> 1) * 16 * kGqGroup + 4 * lane;
     const float* const get_b = s_op + kStage + (wave & 1) * 16 * kGqGroup + 4 * lane;
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __re
     }
     long eld;
     const float* const eb = gq_err_block(err, min(2 * (long)rp + (wave & 1), n_blocks - 1), eld);
-    gq_tile_products<false>(acc, s_op, eb + (wave >> 1) * eld + 4 * lane, eld, u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl,
+    gq_tile_products<false>(acc, s_op, wave, eb + (wave >> 1) * eld + 4 * lane, eld, u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl,
                             4 * K, n_cols);
     if (!mine) return;
     float* dst = v + row0 * K + col0;
@@ -641,14 +641,11 @@ __global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t
 // With J the order-reversing permutation and A = J (H + damping) J = L L^T (plain Cholesky), U = J L^-1 J.
 // Cholesky and inverse run together, block of 64 columns after block: L^-1 is what forward substitution makes of the
 // unit vectors, and the columns of A to the left of a block are dead by the time their part of the substitution starts,
-// so both live in one lower triangle v.  Step k, two launches:
-//   solve kernel   P = the block row that every later row is corrected with, 64 x K: for rows j below the block the new
-//                  column block of L (P[c, j] = L[j, 64 k + c]: row j of A solved against L_kk), for columns j left of it
-//                  the finished rows of L^-1 (column j of the right-hand sides solved against L_kk), the inverse of L_kk
-//                  itself in between (unit vectors); the finished rows go to their mirrored place in u;
-//   update kernel  v[i, j] -= sum_c P[c, i] P[c, j] for the rows i below the block, columns j <= i (columns of the block
-//                  itself start from zero): fp32 matrix products.  Its first workgroup does the next diagonal block
-//                  before all else and factors it while the others are at work.
+// so both live in one lower triangle v.  Step k makes P, the block row that every later row is corrected with, 64 x K: for rows
+// j below the block the new column block of L (P[c, j] = L[j, 64 k + c]: row j of A solved against L_kk), for columns j left of
+// it the finished rows of L^-1 (column j of the right-hand sides solved against L_kk), the inverse of L_kk itself in between
+// (unit vectors); the finished rows go to their mirrored place in u.  What P does to the rest:
+//   v[i, j] -= sum_c P[c, i] P[c, j] for the rows i below the block, columns j <= i (columns of the block itself start from zero)
 
 // damping = damp * mean of the diagonal, a zero diagonal entry counting as (and becoming) 1
 __global__ __launch_bounds__(256) void gptq_damping_kernel(const float* __restrict__ hess, long K, float damp,
@@ -685,238 +682,357 @@ __global__ __launch_bounds__(256) void gptq_reverse_kernel(const float* __restri
     }
 }
 
-// Cholesky of the 64 x 64 block in LDS (lower triangle; row stride 68), by the whole workgroup: 16 columns at a time by the
-// first wavefront, a lane per row with the 16 values in registers (pivots and multipliers through v_readlane), then the
-// 16 columns' products taken from what is right of them by all threads.  r[c * 64 + j] = L[j, c] for j >= c, 0 otherwise.
-__device__ __forceinline__ void gq_chol_block(float* s_m, float* __restrict__ r)
+// The 16 columns p .. p + 15 of the Cholesky factor of the 64 x 64 block in LDS (row stride 68), by one wavefront: a lane per
+// row with its 16 values in registers, pivots and multipliers through v_readlane.  Also the 16 x 16 block on the diagonal as
+// the solving wavefronts read it (s_q[c][row % 4][row / 4]) and the diagonal with its reciprocals.
+constexpr int kGqLd = kGqGroup + 4;
+__device__ __forceinline__ void gq_chol_piece(float* s_m, int p, float* s_q, float2* s_inv)
 {
-    constexpr int kLd = kGqGroup + 4;
-    const int tid = threadIdx.x;
-    for (int p = 0; p < kGqGroup; p += 16) {
-        if (tid < kWave) {
-            float a[16];
-            bool ordinary = true;
+    const int row = threadIdx.x & (kWave - 1);
+    float a[16], dg = 0.0f;
+    bool ordinary = true;
 #pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const float4 t = *reinterpret_cast<const float4*>(s_m + tid * kLd + p + 4 * c);
-                a[4 * c] = t.x; a[4 * c + 1] = t.y; a[4 * c + 2] = t.z; a[4 * c + 3] = t.w;
-            }
+    for (int c = 0; c < 4; c++) {
+        const float4 t = *reinterpret_cast<const float4*>(s_m + row * kGqLd + p + 4 * c);
+        a[4 * c] = t.x; a[4 * c + 1] = t.y; a[4 * c + 2] = t.z; a[4 * c + 3] = t.w;
+    }
 #pragma unroll
-            for (int c = 0; c < 16; c++) {
-                const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[c]), p + c));
-                // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each (finite
-                // operands; see the solve kernel for infinite ones)
-                const float y = __builtin_amdgcn_rsqf(d);
-                const float s0 = d * y, l0 = a[c] * y;
-                const float sq = __builtin_fmaf(__builtin_fmaf(-s0, s0, d), 0.5f * y, s0);
-                float l = __builtin_fmaf(__builtin_fmaf(-sq, l0, a[c]), y, l0);
-                l = (tid == p + c) ? sq : l;
-                ordinary &= d > 1e-30f && d < 1e30f;
-                a[c] = l;
+    for (int c = 0; c < 16; c++) {
+        const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[c]), p + c));
+        // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each (finite operands; see
+        // the step kernel for infinite ones)
+        const float y = __builtin_amdgcn_rsqf(d);
+        const float s0 = d * y, l0 = a[c] * y;
+        const float sq = __builtin_fmaf(__builtin_fmaf(-s0, s0, d), 0.5f * y, s0);
+        float l = __builtin_fmaf(__builtin_fmaf(-sq, l0, a[c]), y, l0);
+        l = (row == p + c) ? sq : l;
+        ordinary &= d > 1e-30f && d < 1e30f;
+        a[c] = l;
 #pragma unroll
-                for (int j = c + 1; j < 16; j++) {
-                    const float lj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), p + j));
-                    a[j] = __builtin_fmaf(-l, lj, a[j]);
-                }
-            }
-            if (ordinary) {                                         // the same in every lane
-#pragma unroll
-                for (int c = 0; c < 4; c++)
-                    *reinterpret_cast<float4*>(s_m + tid * kLd + p + 4 * c) = make_float4(a[4 * c], a[4 * c + 1], a[4 * c + 2], a[4 * c + 3]);
-            } else {
-                // a pivot so large or small that the estimate's steps may leave the range (or none at all: NaN): root and
-                // division as they are, in LDS
+        for (int j = c + 1; j < 16; j++) {
+            const float lj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), p + j));
+            a[j] = __builtin_fmaf(-l, lj, a[j]);
+        }
+    }
+    if (!ordinary) {                                                // the same in every lane
+        // a pivot so large or small that the estimate's steps may leave the range (or none at all: NaN): root and division as
+        // they are, in LDS
 #pragma unroll 1
-                for (int c = 0; c < 16; c++) {
-                    const float root = sqrtf(s_m[(p + c) * kLd + p + c]);
-                    const float l = (tid == p + c) ? root : s_m[tid * kLd + p + c] / root;
-                    s_m[tid * kLd + p + c] = l;
-                    for (int j = c + 1; j < 16; j++)
-                        s_m[tid * kLd + p + j] = __builtin_fmaf(-l, s_m[(p + j) * kLd + p + c], s_m[tid * kLd + p + j]);
-                }
-            }
-        }
-        __syncthreads();
-        const int ty = tid >> 4, tx = tid & 15, n = 3 - p / 16;
-        float4 ri[3][4], rj[3][4];
-#pragma unroll
-        for (int t = 0; t < 3; t++) {
-            if (t >= n) break;
-#pragma unroll
-            for (int c = 0; c < 4; c++) {
-                ri[t][c] = *reinterpret_cast<const float4*>(s_m + (p + 16 + ty + 16 * t) * kLd + p + 4 * c);
-                rj[t][c] = *reinterpret_cast<const float4*>(s_m + (p + 16 + tx + 16 * t) * kLd + p + 4 * c);
-            }
+        for (int c = 0; c < 16; c++) {
+            const float root = sqrtf(s_m[(p + c) * kGqLd + p + c]);
+            const float l = (row == p + c) ? root : s_m[row * kGqLd + p + c] / root;
+            s_m[row * kGqLd + p + c] = l;
+            for (int j = c + 1; j < 16; j++)
+                s_m[row * kGqLd + p + j] = __builtin_fmaf(-l, s_m[(p + j) * kGqLd + p + c], s_m[row * kGqLd + p + j]);
         }
 #pragma unroll
-        for (int a = 0; a < 3; a++) {
-            if (a >= n) break;
-#pragma unroll
-            for (int b = 0; b <= a; b++) {                      // (the whole of a 16 x 16 diagonal tile; its upper half is not read)
-                float* const at = s_m + (p + 16 + ty + 16 * a) * kLd + p + 16 + tx + 16 * b;
-                float acc = *at;
-#pragma unroll
-                for (int c = 0; c < 4; c++) {
-                    acc = __builtin_fmaf(-ri[a][c].x, rj[b][c].x, acc);
-                    acc = __builtin_fmaf(-ri[a][c].y, rj[b][c].y, acc);
-                    acc = __builtin_fmaf(-ri[a][c].z, rj[b][c].z, acc);
-                    acc = __builtin_fmaf(-ri[a][c].w, rj[b][c].w, acc);
-                }
-                *at = acc;
-            }
-        }
-        __syncthreads();
+        for (int c = 0; c < 16; c++) a[c] = s_m[row * kGqLd + p + c];
     }
 #pragma unroll
-    for (int i = 0; i < kGqGroup * kGqGroup / 256; i++) {
-        const int at = i * 256 + tid, c = at >> 6, j = at & 63;
-        r[at] = (j >= c) ? s_m[j * kLd + c] : 0.0f;
+    for (int c = 0; c < 4; c++)
+        *reinterpret_cast<float4*>(s_m + row * kGqLd + p + 4 * c) = make_float4(a[4 * c], a[4 * c + 1], a[4 * c + 2], a[4 * c + 3]);
+    const int lr = row - p;
+    if (lr >= 0 && lr < 16) {
+#pragma unroll
+        for (int c = 0; c < 16; c++) {
+            s_q[(p + c) * kGqChunk + (lr & 3) * 4 + (lr >> 2)] = a[c];
+            dg = (lr == c) ? a[c] : dg;
+        }
+        s_inv[row] = make_float2(dg, 1.0f / dg);
     }
 }
 
-__global__ __launch_bounds__(256) void gptq_chol_diag_kernel(const float* __restrict__ v, long K, float* __restrict__ r)
+// One 16 x 16 tile (t, tt) of the block loses the products of the 16 columns from p on: m[row, col] = fma(-L[row, c], L[col, c],
+// m[row, col]), c ascending.
+__device__ __forceinline__ void gq_chol_tile(float* s_m, int p, int t, int tt)
 {
-    __shared__ __attribute__((aligned(16))) float s_m[kGqGroup * (kGqGroup + 4)];
+    const int lane = threadIdx.x & (kWave - 1), rg = lane >> 4, cl = lane & 15;
+    float* const at = s_m + (16 * t + 4 * rg) * kGqLd + 16 * tt + cl;
+    f32x4_t acc;
+    float x[4], y[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int at = i * 256 + threadIdx.x, row = at >> 4, col = 4 * (at & 15);
-        *reinterpret_cast<float4*>(s_m + row * (kGqGroup + 4) + col) = load_global<float4>(v + (long)row * K + col);
+    for (int i = 0; i < 4; i++) acc[i] = at[i * kGqLd];
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++) {
+        x[kk] = -s_m[(16 * t + cl) * kGqLd + p + 4 * kk + rg];
+        y[kk] = s_m[(16 * tt + cl) * kGqLd + p + 4 * kk + rg];
     }
-    __syncthreads();
-    gq_chol_block(s_m, r);
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[kk], y[kk], acc, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; i++) at[i * kGqLd] = acc[i];
 }
 
-// Step k's block row P (see above) against r = the diagonal block's factor, a workgroup per 64 columns j of P, a wavefront
-// 16 of them with four lanes each, as in the group kernel.  Bound: the chain of 64 steps (divide, hand over, correct), 9 us;
-// a lane per column took 17 us, twice per step (Cholesky's panel and the substitution were separate passes).
+// Where P of step s has its 64 columns `block`: in v's block row s, which nothing else needs any more (to the left of the
+// diagonal in the place of the rows it was solved from, to the right in the unused upper triangle), its own diagonal block, which
+// every workgroup of the step reads, in slot s.
+__device__ __forceinline__ const float* gq_p_block(const float* v, long K, const float* slots, long s, long block, long& ld)
+{
+    ld = (block == s) ? kGqGroup : K;
+    return (block == s) ? slots + s * kGqGroup * kGqGroup : v + s * kGqGroup * K + block * kGqGroup;
+}
+
+// Step k of the factorisation in one launch.  The first K / 64 workgroups solve: workgroup jb works out its 64 columns of P, and
+// for that the diagonal block and its own block of v as they are after all steps before, then the diagonal block's Cholesky
+// factor and, 16 columns behind it, the substitution.  The others bring the rest of v forward, two steps (a panel) at a time:
+//   pending     what is not yet in v when step k starts: steps k - 2 and k - 1 for even k, step k - 1 for odd k; the solving
+//               workgroups take it from P themselves
+//   even k      the panel (k - 2, k - 1) goes into block row and column k + 1, and into half of the blocks behind them
+//   odd k       the same panel goes into the other half
+// so a block of v is read and written once per panel, and the launch lasts as long as its chain: 1.5 us to start, 1 or 2 of
+// products, 5 stages of about 1.2 in which one wavefront factors 16 columns, three bring the diagonal block forward and four
+// substitute the 16 columns before.  K = 4096: @@ us a step; as two launches a step (substitution 9 us, update and Cholesky 13
+// to 25 with v crossing memory in every one of them) a factor took 1.8 ms.
 // The quotient is the product with the reciprocal and one residual step.  For finite operands that differs from a division
 // in the last place at most; an infinite operand or quotient gives NaN where the division gives infinity, but it has no
 // place in a positive definite matrix: what it is subtracted from, a later pivot, becomes NaN either way.
-__global__ __launch_bounds__(256) void gptq_solve_kernel(const float* __restrict__ v, long K, long k, const float* __restrict__ r,
-                                                         float* __restrict__ p_row, float* __restrict__ u)
+constexpr int kGqStepThreads = 512;
+constexpr int kGqStepLds = 2 * 128 * kGqGroup;                      // floats: the operands of 64 columns c, or the solver's blocks
+
+// Tiles (pairs of block rows x pairs of block columns) of panel q that the launches of its two successors bring forward: the
+// first takes block pair q + 1's column and row and `first` of the others, the second what is left.
+struct GqWide {
+    long q, pairs, rest, first;
+};
+static inline GqWide gq_wide(long nb, long k)
 {
-    constexpr int kStride = kGqGroup + 4;
-    __shared__ __attribute__((aligned(16))) float s_d[kGqGroup * kGqGroup];     // [c][j % 4][j / 4]
-    __shared__ __attribute__((aligned(16))) float2 s_inv[kGqGroup];             // diagonal entry and its reciprocal
-    __shared__ __attribute__((aligned(16))) float s_x[4][16 * kStride];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long jb = blockIdx.x, base = k * kGqGroup;
-    const int rr = lane >> 2, q = lane & 3;
-    const long j = jb * kGqGroup + 16 * wave + rr;
-    float x[16];
-    float4 raw[4];
-    if (jb > k) {
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-            raw[i] = *reinterpret_cast<const float4*>(v + (jb * kGqGroup + 16 * wave + 4 * (lane >> 4) + i) * K + base + 4 * (lane & 15));
-    } else if (jb < k) {
-#pragma unroll
-        for (int m = 0; m < 16; m++) x[m] = v[(base + 4 * m + q) * K + j];
-    } else {
-#pragma unroll
-        for (int m = 0; m < 16; m++) x[m] = (base + 4 * m + q == j) ? 1.0f : 0.0f;
-    }
-    if (tid < kGqGroup) {
-        const float dg = r[tid * kGqGroup + tid];
-        s_inv[tid] = make_float2(dg, 1.0f / dg);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int at = i * 256 + tid, c = at >> 4, m = at & 15;
-        const float4 d = *reinterpret_cast<const float4*>(r + c * kGqGroup + 4 * m);
-        float* dst = &s_d[c * kGqGroup + m];
-        dst[0] = d.x; dst[16] = d.y; dst[32] = d.z; dst[48] = d.w;
-    }
-    if (jb > k) {
-        float* const sx = s_x[wave];
-#pragma unroll
-        for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * (lane >> 4) + i) * kStride + 4 * (lane & 15)]) = raw[i];
-#pragma unroll
-        for (int m = 0; m < 16; m++) x[m] = sx[rr * kStride + 4 * m + q];
-    }
-    __syncthreads();
-    float* const pj = p_row + (long)q * K + j;
-    float* const uj = u + (K - 1 - base - q) * K + (K - 1 - j);
-    float keep = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kGqGroup; i++) {
-        const int k4 = i / 4, c = i % 4;
-        const float xi = c == 0 ? quad_bcast<0>(x[k4]) : c == 1 ? quad_bcast<1>(x[k4]) : c == 2 ? quad_bcast<2>(x[k4]) : quad_bcast<3>(x[k4]);
-        const float2 dg = s_inv[i];
-        const float e0 = xi * dg.y;
-        const float e = __builtin_fmaf(__builtin_fmaf(-dg.x, e0, xi), dg.y, e0);    // the quotient: one residual step
-        keep = (q == c) ? e : keep;
-        if (c == 3) {
-            pj[(long)4 * k4 * K] = keep;
-            uj[-(long)4 * k4 * K] = (jb > k) ? 0.0f : keep;
-        }
-#pragma unroll
-        for (int m = (c == 3) ? k4 + 1 : k4; m < 16; m++) x[m] = __builtin_fmaf(-e, s_d[i * kGqGroup + q * 16 + m], x[m]);
-    }
+    GqWide w;
+    w.q = k / 2 - 1;
+    w.pairs = (nb + 1) / 2;
+    // the others: pairs si >= q + 2, and si of the si + 1 column pairs each
+    w.rest = w.q < 0 ? 0 : (w.pairs * (w.pairs - 1) - (w.q + 2) * (w.q + 1)) / 2;
+    if (w.rest < 0) w.rest = 0;
+    w.first = (w.pairs + w.rest) / 2 - w.pairs;
+    if (w.first < 0) w.first = 0;
+    return w;
+}
+static inline long gq_wide_tiles(const GqWide& w, long nb, long k)
+{
+    if (w.q < 0 || k + 1 >= nb) return 0;
+    return (k & 1) ? w.rest - w.first : w.pairs + w.first;
 }
 
-// v[i, j] -= sum_c P[c, i] P[c, j] for the 64 x 64 blocks (ib, jb) with k < ib, jb <= ib, the block column k starting from
-// zero; a wavefront a block, a workgroup 2 x 2 of them.  Workgroup 0 does block (k + 1, k + 1) and factors it into r.
-// K = 4096: 25 us for the first steps (bound by the blocks' way from and to memory) down to 13 us for the last (bound by
-// workgroup 0: the products, 7.5 us of Cholesky); a whole factor takes 1.83 ms where the separate passes over 64 x 128
-// tiles of vector fmas, with a one-wavefront Cholesky of 20 us between them, took 5.65 ms.
-__global__ __launch_bounds__(256, 3) void gptq_update_kernel(float* v, long K, long k, const float* __restrict__ p_row,
-                                                          float* __restrict__ r)
+__global__ __launch_bounds__(kGqStepThreads, 4) void gptq_step_kernel(float* v, long K, long k, float* slots, float* __restrict__ u,
+                                                                     GqWide wide)
 {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ln = lane & 31, h = lane >> 5;
-    __shared__ __attribute__((aligned(16))) float s_op[2 * 2 * 2 * 16 * kGqGroup];
-    if (blockIdx.x == 0) {
-        constexpr int kLd = kGqGroup + 4;
-        float* const s_m = s_op;                                // 64 rows of 68
-        __builtin_amdgcn_s_setprio(3);                          // the launch's longest chain, beside wavefronts that only add work
-        const long i0 = (k + 1) * kGqGroup;
-        const int wi = wave >> 1, wj = wave & 1;
-        float16_t acc;
+    __shared__ __attribute__((aligned(16))) float s_all[kGqStepLds];
+    const long nb = K / kGqGroup;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = lane >> 4, cl = lane & 15;
+    if ((long)blockIdx.x >= nb) {
+        // ---- panel q into a tile of 128 x 128, 64 x 32 of it a wavefront
+        const long tile = (long)blockIdx.x - nb;
+        long si, sj;
+        const long own = wide.pairs;                    // tiles of block pair q + 1's column and row
+        if (!(k & 1) && tile < own) {
+            const long below = wide.pairs - wide.q - 1;
+            si = tile < below ? wide.q + 1 + tile : wide.q + 1;
+            sj = tile < below ? wide.q + 1 : tile - below;
+        } else {
+            const long at = ((k & 1) ? tile + wide.first : tile - own) + (wide.q + 2) * (wide.q + 1) / 2;
+            si = (long)((sqrt(8.0 * (double)at + 1.0) + 1.0) * 0.5);
+            while (si * (si - 1) / 2 > at) si--;
+            while ((si + 1) * si / 2 <= at) si++;
+            sj = at - si * (si - 1) / 2;
+            if (sj >= wide.q + 1) sj++;
+        }
+        const long last = nb - 1, s0 = 2 * wide.q;
+        const int wi = wave >> 2, wq = wave & 3;
+        const long ib = min(2 * si + wi, last), jb = min(2 * sj + (wq >> 1), last);
+        const bool mine = 2 * si + wi <= last && 2 * sj + (wq >> 1) <= last && jb <= ib && ib > s0 + 2 && jb != s0 + 2;
+        // the panel's two steps one after the other through LDS, 64 columns c at a time: [rows, columns][c][128]; the second
+        // step's operands are on their way while the first one's are multiplied
+        float4 stage[2][4];
+        auto fetch = [&](long s) {
 #pragma unroll
-        for (int i = 0; i < 16; i++)
-            acc[i] = v[(i0 + 32 * wi + 8 * (i >> 2) + 4 * h + (i & 3)) * K + i0 + 32 * wj + ln];
-        const float* ap = p_row + (long)h * K + i0 + 32 * wi + ln;
-        const float* bp = p_row + (long)h * K + i0 + 32 * wj + ln;
-#pragma unroll 16
-        for (int c = 0; c < kGqGroup; c += 2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[(long)c * K], bp[(long)c * K], acc, 0, 0, 0);
+            for (int o = 0; o < 2; o++)
 #pragma unroll
-        for (int i = 0; i < 16; i++) s_m[(32 * wi + 8 * (i >> 2) + 4 * h + (i & 3)) * kLd + 32 * wj + ln] = acc[i];
-        __syncthreads();
-        gq_chol_block(s_m, r);
+                for (int i = 0; i < 4; i++) {
+                    const int at = tid + kGqStepThreads * i, c = at >> 5, f4 = at & 31;
+                    long ld;
+                    const float* const from = gq_p_block(v, K, slots, s, min(2 * (o ? sj : si) + (f4 >> 4), last), ld);
+                    stage[o][i] = load_global<float4>(from + c * ld + 4 * (f4 & 15));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto park = [&] {
+#pragma unroll
+            for (int o = 0; o < 2; o++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(s_all + o * 128 * kGqGroup + 4 * (tid + kGqStepThreads * i)) = stage[o][i];
+            __syncthreads();
+        };
+        // interleaved as in GqTile, with two column tiles: register i of tile (x, y) is row 16 rg + 4 i + x, column 2 cl + y
+        f32x4_t acc[4][2];
+        auto multiply = [&] {
+            const float* ap = s_all + rg * 128 + 64 * wi + 4 * cl;
+            const float* bp = s_all + 128 * kGqGroup + rg * 128 + 32 * wq + 2 * cl;
+#pragma unroll 4
+            for (int kk = 0; kk < kGqGroup / 4; kk++) {
+                const float4 av = *reinterpret_cast<const float4*>(ap + kk * 512);
+                const float2 bv = *reinterpret_cast<const float2*>(bp + kk * 512);
+                const float ar[4] = {-av.x, -av.y, -av.z, -av.w};
+#pragma unroll
+                for (int x = 0; x < 4; x++) {
+                    acc[x][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[x], bv.x, acc[x][0], 0, 0, 0);
+                    acc[x][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[x], bv.y, acc[x][1], 0, 0, 0);
+                }
+            }
+        };
+        fetch(s0);
+        const uint32_t off = 16 * rg * (uint32_t)K + 2 * cl;
+        float* const dst = v + ib * kGqGroup * K + jb * kGqGroup + 32 * (wq & 1);
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            float2 val = make_float2(0.0f, 0.0f);       // (block columns of the panel itself: L^-1's part starts here)
+            if (jb != s0 && jb != s0 + 1) val = load_global<float2>(dst + r * K + off);
+            acc[r & 3][0][r >> 2] = val.x;
+            acc[r & 3][1][r >> 2] = val.y;
+        }
+        park();
+        fetch(s0 + 1);
+        multiply();
+        __syncthreads();                                // the first step's operands have been read
+        park();
+        if (jb == s0 + 1) {                             // ... with the panel's second step
+#pragma unroll
+            for (int x = 0; x < 4; x++) acc[x][0] = acc[x][1] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        multiply();
+        if (!mine) return;
+#pragma unroll
+        for (int r = 0; r < 16; r++) store_global(dst + r * K + off, make_float2(acc[r & 3][0][r >> 2], acc[r & 3][1][r >> 2]));
         return;
     }
-    // pairs of block rows from (k + 1) / 2 on, pair s with s + 1 pairs of block columns
-    const long s0 = (k + 1) >> 1;
-    const long at = (long)blockIdx.x - 1 + s0 * (s0 + 1) / 2;
-    long s = (long)((sqrt(8.0 * (double)at + 1.0) - 1.0) * 0.5);
-    while (s * (s + 1) / 2 > at) s--;
-    while ((s + 1) * (s + 2) / 2 <= at) s++;
-    const long last = K / kGqGroup - 1, sj = at - s * (s + 1) / 2;
-    const long ib = min(2 * s + (wave >> 1), last), jb = min(2 * sj + (wave & 1), last);
-    const long ia = min(2 * s + (wave & 1), last);              // the block whose rows this wavefront fetches for all four
-    const bool mine = ib > k && jb <= ib && 2 * s + (wave >> 1) <= last && !(ib == k + 1 && jb == k + 1);
-    const long i0 = ib * kGqGroup, j0 = jb * kGqGroup;
-    const int rg = lane >> 4, cl = lane & 15;
-    const uint32_t off = 16 * rg * (uint32_t)K + 4 * cl;
-    GqTile acc;
-    const float* const src = v + i0 * K + j0;
+    // ---- solve
+    float* const s_m = s_all;                                       // diagonal block, 64 rows of 68
+    float* const s_x = s_m + kGqGroup * kGqLd;                      // own block, [column j][c], 64 rows of 68
+    float* const s_q = s_x + kGqGroup * kGqLd;                      // 16 x 16 blocks of the factor's diagonal
+    float2* const s_inv = reinterpret_cast<float2*>(s_q + kGqGroup * kGqChunk);
+    float* const s_e = reinterpret_cast<float*>(s_inv + kGqGroup);  // [wavefront][c][column], negated
+    static_assert(2 * kGqGroup * kGqLd + kGqGroup * kGqChunk + 2 * kGqGroup + kGqGroup * kGqGroup <= kGqStepLds, "the solver's blocks fit");
+    __builtin_amdgcn_s_setprio(3);                                  // the launch's longest chain, beside wavefronts that only add work
+    const long jb = blockIdx.x, base = k * kGqGroup;
+    {
+        // P's columns of block k and of the own block, of up to two pending steps, into LDS: [step][block k, own][c][column], all
+        // requested at once (the workgroups of the launches before left them in other L2s, a microsecond away)
+        const long s0 = (k & 1) ? k - 1 : max(k - 2, 0L);           // first pending step
+        float4 stage[2][2][2];
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        float4 val = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (jb != k) val = load_global<float4>(src + r * K + off);
-        acc.t[r & 3][0][r >> 2] = val.x; acc.t[r & 3][1][r >> 2] = val.y; acc.t[r & 3][2][r >> 2] = val.z; acc.t[r & 3][3][r >> 2] = val.w;
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+                if (s0 + h < k && (b == 0 || jb > k || (jb < k && s0 + h >= jb))) {
+                    long ld;
+                    const float* const from = gq_p_block(v, K, slots, s0 + h, b ? jb : k, ld) + (tid >> 4) * ld + 4 * (tid & 15);
+#pragma unroll
+                    for (int i = 0; i < 2; i++) stage[h][b][i] = load_global<float4>(from + 32 * i * ld);
+                }
+        // wavefronts 0..3: a quadrant each of the diagonal block; 4..7: of the own one (below the diagonal transposed: rows j)
+        const bool own = wave >= 4;
+        const int w4 = wave & 3, wi = w4 >> 1, wj = w4 & 1, ln = lane & 31, h = lane >> 5;
+        const long rows = own && jb > k ? jb : k, cols = own && jb < k ? jb : k;
+        // (L^-1's part of a column block starts with that block's own step)
+        const bool fresh = cols < k && cols >= s0;
+        float16_t acc;
+        const float* const src = v + (rows * kGqGroup + 32 * wi + 4 * h) * K + cols * kGqGroup + 32 * wj + ln;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            acc[i] = 0.0f;
+            if (own && jb == k) acc[i] = (32 * wi + 8 * (i >> 2) + 4 * h + (i & 3) == 32 * wj + ln) ? 1.0f : 0.0f;
+            else if (!fresh) acc[i] = src[(long)(8 * (i >> 2) + (i & 3)) * K];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int hh = 0; hh < 2; hh++)
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+                if (s0 + hh < k)
+#pragma unroll
+                    for (int i = 0; i < 2; i++)
+                        *reinterpret_cast<float4*>(s_all + (2 * hh + b) * kGqGroup * kGqGroup + 4 * (tid + kGqStepThreads * i)) = stage[hh][b][i];
+        __syncthreads();
+        if (!(own && jb == k) && wave != 1)                         // (wavefront 1: above the diagonal, not needed)
+            for (int hh = 0; hh < 2; hh++) {
+                if (s0 + hh >= k || (cols < k && s0 + hh < cols)) continue;
+                const float* const at = s_all + 2 * hh * kGqGroup * kGqGroup;
+                const float* const ap = at + (rows == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wi + ln;
+                const float* const bp = at + (cols == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wj + ln;
+#pragma unroll 8
+                for (int c = 0; c < kGqGroup; c += 2)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[c * kGqGroup], bp[c * kGqGroup], acc, 0, 0, 0);
+            }
+        __syncthreads();                                            // the operands have been read
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int r = 32 * wi + 8 * (i >> 2) + 4 * h + (i & 3), c = 32 * wj + ln;
+            if (!own) s_m[r * kGqLd + c] = acc[i];
+            else if (jb > k) s_x[r * kGqLd + c] = acc[i];
+            else s_x[c * kGqLd + r] = acc[i];
+        }
     }
-    const float* const own = p_row + (long)(4 * (wave >> 1) + rg) * K + 4 * cl;
-    gq_tile_products<true>(acc, s_op, own + ia * kGqGroup, 4 * K, own + j0, 4 * K, kGqGroup);
-    if (!mine) return;
-    float* dst = v + i0 * K + j0;
-    asm("" : "+s"(dst));
+    __syncthreads();
+    const int w4 = wave & 3, rr = lane >> 2, q = lane & 3;
+    const long j = jb * kGqGroup + 16 * w4 + rr;                    // substitution: four lanes per column
+    float* const xr = s_x + 16 * w4 * kGqLd;
+    float* const se = s_e + w4 * kGqGroup * 16;
+    float* const pj = jb == k ? slots + k * kGqGroup * kGqGroup + q * kGqGroup + 16 * w4 + rr : v + (base + q) * K + j;
+    const long pld = jb == k ? kGqGroup : K;
+    float* const uj = u + (K - 1 - base - q) * K + (K - 1 - j);
+#pragma unroll 1
+    for (int s = 0; s < 5; s++) {
+        // the 16 columns before into the present ones, a tile a wavefront
+        if (s > 0 && s + wave < 4) gq_chol_tile(s_m, 16 * s - 16, s + wave, s);
+        __syncthreads();
+        if (wave == 0) {
+            if (s < 4) gq_chol_piece(s_m, 16 * s, s_q, s_inv);
+        } else if (wave < 4) {
+            // ... and into what is behind them: tiles (2, 2), (3, 2), (3, 3), then (3, 3)
+            if (s == 1) gq_chol_tile(s_m, 0, wave == 1 ? 2 : 3, wave == 3 ? 3 : 2);
+            else if (s == 2 && wave == 1) gq_chol_tile(s_m, 16, 3, 3);
+        } else if (s > 0) {
+            const int t0 = 16 * (s - 1);
+            float x[4], keep = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        const int i = r >> 2, a = r & 3;
-        store_global(dst + r * K + off, make_float4(acc.t[a][0][i], acc.t[a][1][i], acc.t[a][2][i], acc.t[a][3][i]));
+            for (int i = 0; i < 4; i++) x[i] = xr[rr * kGqLd + t0 + 4 * i + q];
+            const float4* const sd = reinterpret_cast<const float4*>(s_q + t0 * kGqChunk + 4 * q);
+#pragma unroll
+            for (int i = 0; i < kGqChunk; i++) {
+                const int k4 = i / 4, c = i % 4;
+                const float xi = c == 0 ? quad_bcast<0>(x[k4]) : c == 1 ? quad_bcast<1>(x[k4]) : c == 2 ? quad_bcast<2>(x[k4]) : quad_bcast<3>(x[k4]);
+                const float2 dg = s_inv[t0 + i];
+                const float e0 = xi * dg.y;
+                const float e = __builtin_fmaf(__builtin_fmaf(-dg.x, e0, xi), dg.y, e0);    // the quotient: one residual step
+                keep = (q == c) ? e : keep;
+                if (c == 3) {
+                    pj[(long)(t0 + 4 * k4) * pld] = keep;
+                    uj[-(long)(t0 + 4 * k4) * K] = (jb > k) ? 0.0f : keep;
+                    se[(t0 + 4 * k4 + q) * 16 + rr] = -keep;
+                }
+                const float4 d4 = sd[i * (kGqChunk / 4)];
+                const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+                for (int m = (c == 3) ? k4 + 1 : k4; m < 4; m++) x[m] = __builtin_fmaf(-e, dd[m], x[m]);
+            }
+            // ... and onto the columns behind them
+            float a[4];
+#pragma unroll
+            for (int kk = 0; kk < 4; kk++) a[kk] = se[(t0 + 4 * kk) * 16 + lane];
+            for (int tt = s; tt < 4; tt++) {
+                float* const at = xr + 4 * rg * kGqLd + 16 * tt + cl;
+                f32x4_t acc;
+                float y[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) acc[i] = at[i * kGqLd];
+#pragma unroll
+                for (int kk = 0; kk < 4; kk++) y[kk] = s_m[(16 * tt + cl) * kGqLd + t0 + 4 * kk + rg];
+#pragma unroll
+                for (int kk = 0; kk < 4; kk++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], y[kk], acc, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; i++) at[i * kGqLd] = acc[i];
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -991,7 +1107,7 @@ int dymoe_gptq_hessian(dymoe_ctx* ctx, const void* x_bf16, long n, long K, int a
 size_t dymoe_gptq_factor_workspace_bytes(long K)
 {
     if (K <= 0) return 0;
-    // the triangle that becomes factor and inverse, a block row P, the diagonal block's factor, the damping
+    // the triangle that becomes factor and inverse, a 64 x 64 block per step, the damping (in an area of 64 x 64 + 1)
     return dymoe::gq_round256((size_t)K * (size_t)K * 4) + dymoe::gq_round256((size_t)dymoe::kGqGroup * (size_t)K * 4) +
            dymoe::gq_round256(((size_t)dymoe::kGqGroup * dymoe::kGqGroup + 1) * 4);
 }
@@ -1008,23 +1124,18 @@ int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, flo
     hipStream_t st = (hipStream_t)stream;
     const size_t mat = gq_round256((size_t)K * (size_t)K * 4);
     float* v = reinterpret_cast<float*>(workspace);
-    float* p_row = reinterpret_cast<float*>((char*)workspace + mat);                    // 64 x K
-    float* r = reinterpret_cast<float*>((char*)p_row + gq_round256((size_t)kGqGroup * (size_t)K * 4));   // 64 x 64
-    float* lambda = r + kGqGroup * kGqGroup;
+    float* slots = reinterpret_cast<float*>((char*)workspace + mat);                    // 64 x 64 per step
+    float* lambda = reinterpret_cast<float*>((char*)slots + gq_round256((size_t)kGqGroup * (size_t)K * 4));
     hipLaunchKernelGGL(gptq_damping_kernel, dim3(1), dim3(256), 0, st, hess, K, damp, lambda);
     hipLaunchKernelGGL(gptq_reverse_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)(K / kGqGroup)), dim3(256), 0, st, hess, K,
                        (const float*)lambda, v);
     DYMOE_HIP_LAUNCH_CHECK();
-    dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_chol_diag_kernel, dim3(1), dim3(256), 0, st, (const float*)v, K, r);
-    const long nb = K / kGqGroup, pairs = (nb + 1) / 2;
+    const long nb = K / kGqGroup;
     for (long k = 0; k < nb; k++) {
-        dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, gptq_solve_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const float*)v, K, k,
-                     (const float*)r, p_row, u);
-        DYMOE_HIP_LAUNCH_CHECK();
-        if (k + 1 == nb) break;
-        const long s0 = (k + 1) / 2;
-        dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, gptq_update_kernel, dim3((unsigned)(1 + pairs * (pairs + 1) / 2 - s0 * (s0 + 1) / 2)),
-                     dim3(256), 0, st, v, K, k, (const float*)p_row, r);
+        const GqWide wide = gq_wide(nb, k);
+        const long tiles = gq_wide_tiles(wide, nb, k);
+        dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_step_kernel, dim3((unsigned)(nb + tiles)), dim3(kGqStepThreads), 0, st, v, K, k,
+                     slots, u, wide);
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;
