@@ -772,136 +772,153 @@ __device__ __forceinline__ const float* gq_p_block(const float* v, long K, const
     return (block == s) ? slots + s * kGqGroup * kGqGroup : v + s * kGqGroup * K + block * kGqGroup;
 }
 
-// Step k of the factorisation in one launch.  The first K / 64 workgroups solve: workgroup jb works out its 64 columns of P, and
-// for that the diagonal block and its own block of v as they are after all steps before, then the diagonal block's Cholesky
-// factor and, 16 columns behind it, the substitution.  The others bring the rest of v forward, two steps (a panel) at a time:
-//   pending     what is not yet in v when step k starts: steps k - 2 and k - 1 for even k, step k - 1 for odd k; the solving
-//               workgroups take it from P themselves
-//   even k      the panel (k - 2, k - 1) goes into block row and column k + 1, and into half of the blocks behind them
-//   odd k       the same panel goes into the other half
-// so a block of v is read and written once per panel, and the launch lasts as long as its chain: 1.5 us to start, 1 or 2 of
-// products, 5 stages of about 1.2 in which one wavefront factors 16 columns, three bring the diagonal block forward and four
-// substitute the 16 columns before.  K = 4096: @@ us a step; as two launches a step (substitution 9 us, update and Cholesky 13
-// to 25 with v crossing memory in every one of them) a factor took 1.8 ms.
+// Step k of the factorisation in one launch.  The first K / 64 workgroups solve: workgroup jb takes step k - 1 out of the diagonal
+// block and out of its own block of v, makes the diagonal block's Cholesky factor and, 16 columns behind it, the substitution.
+// The others bring the rest of v forward, steps in pairs (a panel: steps 2 q and 2 q + 1), so that a block of v is read and
+// written once per panel:
+//   k = 2 q + 2   panel q into the block pairs q + 1 and q + 2 (columns and rows) and into some of the blocks behind them
+//   k = 2 q + 3   panel q into the other blocks; step 2 q + 2 alone into block row and column 2 q + 4, which step 2 q + 4 needs
+// The launch lasts as long as its chain, or, for the first steps of a large K, as the matrix products: 1 us to start, 2 for the
+// operands, 2 of products, 5 stages of 1.4 to 1.9 in which one wavefront factors 16 columns, three bring the diagonal block
+// forward and four substitute the 16 columns before.  K = 4096: 20 us a step on average, 15 to 17 for the last ones; as two launches a step (substitution
+// 9 us, update and Cholesky 13 to 25 with v crossing memory in every one of them) 28.
 // The quotient is the product with the reciprocal and one residual step.  For finite operands that differs from a division
 // in the last place at most; an infinite operand or quotient gives NaN where the division gives infinity, but it has no
 // place in a positive definite matrix: what it is subtracted from, a later pivot, becomes NaN either way.
 constexpr int kGqStepThreads = 512;
-constexpr int kGqStepLds = 2 * 128 * kGqGroup;                      // floats: the operands of 64 columns c, or the solver's blocks
+constexpr int kGqStepLds = 3 * kGqGroup * kGqGroup;                 // floats: a tile's operands of 64 columns c
 
-// Tiles (pairs of block rows x pairs of block columns) of panel q that the launches of its two successors bring forward: the
-// first takes block pair q + 1's column and row and `first` of the others, the second what is left.
+// Tiles (pairs of block rows x pairs of block columns) of panel q: `near` of the pairs q + 1 and q + 2 and `first` of the
+// others in the first launch, `later` in the second.  single: half tiles that the second launch brings forward by one step.
 struct GqWide {
-    long q, pairs, rest, first;
+    long q, pairs, near, first, later, single;
 };
 static inline GqWide gq_wide(long nb, long k)
 {
     GqWide w;
     w.q = k / 2 - 1;
     w.pairs = (nb + 1) / 2;
-    // the others: pairs si >= q + 2, and si of the si + 1 column pairs each
-    w.rest = w.q < 0 ? 0 : (w.pairs * (w.pairs - 1) - (w.q + 2) * (w.q + 1)) / 2;
-    if (w.rest < 0) w.rest = 0;
-    w.first = (w.pairs + w.rest) / 2 - w.pairs;
-    if (w.first < 0) w.first = 0;
+    w.near = w.first = w.later = w.single = 0;
+    if (k + 1 >= nb) return w;                                      // the last step leaves nothing behind
+    if (w.q >= 0) {
+        w.near = w.pairs + (w.q + 2 < w.pairs ? w.pairs - 1 : 0);
+        // the others: pairs si >= q + 3, and si - 1 of the si + 1 column pairs each
+        long rest = ((w.pairs - 1) * (w.pairs - 2) - (w.q + 2) * (w.q + 1)) / 2;
+        if (rest < 0) rest = 0;
+        w.first = (w.near + rest) / 2 - w.near;
+        if (w.first < 0) w.first = 0;
+        w.later = rest - w.first;
+    }
+    if (k & 1) w.single = nb - (k + 1) + w.q + 2;                   // block column k + 1 from the diagonal down, block row k + 1
     return w;
 }
-static inline long gq_wide_tiles(const GqWide& w, long nb, long k)
-{
-    if (w.q < 0 || k + 1 >= nb) return 0;
-    return (k & 1) ? w.rest - w.first : w.pairs + w.first;
-}
+static inline long gq_wide_blocks(const GqWide& w, long k) { return (k & 1) ? w.single + 2 * w.later : 2 * (w.near + w.first); }
 
-__global__ __launch_bounds__(kGqStepThreads, 4) void gptq_step_kernel(float* v, long K, long k, float* slots, float* __restrict__ u,
+__global__ __launch_bounds__(kGqStepThreads, 6) void gptq_step_kernel(float* v, long K, long k, float* slots, float* __restrict__ u,
                                                                      GqWide wide)
 {
-    __shared__ __attribute__((aligned(16))) float s_all[kGqStepLds];
+    extern __shared__ __attribute__((aligned(16))) float s_all[];   // kGqStepLds at least
     const long nb = K / kGqGroup;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane >> 4, cl = lane & 15;
     if ((long)blockIdx.x >= nb) {
-        // ---- panel q into a tile of 128 x 128, 64 x 32 of it a wavefront
-        const long tile = (long)blockIdx.x - nb;
-        long si, sj;
-        const long own = wide.pairs;                    // tiles of block pair q + 1's column and row
-        if (!(k & 1) && tile < own) {
-            const long below = wide.pairs - wide.q - 1;
-            si = tile < below ? wide.q + 1 + tile : wide.q + 1;
-            sj = tile < below ? wide.q + 1 : tile - below;
-        } else {
-            const long at = ((k & 1) ? tile + wide.first : tile - own) + (wide.q + 2) * (wide.q + 1) / 2;
-            si = (long)((sqrt(8.0 * (double)at + 1.0) + 1.0) * 0.5);
-            while (si * (si - 1) / 2 > at) si--;
-            while ((si + 1) * si / 2 <= at) si++;
-            sj = at - si * (si - 1) / 2;
-            if (sj >= wide.q + 1) sj++;
-        }
-        const long last = nb - 1, s0 = 2 * wide.q;
+        // ---- 64 x 128, a block row of a tile, 32 x 32 of it a wavefront
+        const long last = nb - 1, q = wide.q;
         const int wi = wave >> 2, wq = wave & 3;
-        const long ib = min(2 * si + wi, last), jb = min(2 * sj + (wq >> 1), last);
-        const bool mine = 2 * si + wi <= last && 2 * sj + (wq >> 1) <= last && jb <= ib && ib > s0 + 2 && jb != s0 + 2;
-        // the panel's two steps one after the other through LDS, 64 columns c at a time: [rows, columns][c][128]; the second
-        // step's operands are on their way while the first one's are multiplied
-        float4 stage[2][4];
+        const long at0 = (long)blockIdx.x - nb, n_single = (k & 1) ? wide.single : 0;
+        const bool single = at0 < n_single;
+        long ib, sj;
+        if (single) {
+            const long below = nb - (k + 1);
+            ib = at0 < below ? k + 1 + at0 : k + 1;
+            sj = at0 < below ? q + 2 : at0 - below;
+        } else {
+            const long half = at0 - n_single, tile = half >> 1, below = wide.pairs - q - 1;
+            long si;
+            if (!(k & 1) && tile < wide.near) {
+                if (tile < below) { si = q + 1 + tile; sj = q + 1; }
+                else if (tile < wide.pairs) { si = q + 1; sj = tile - below; }
+                else if (tile < wide.pairs + below - 1) { si = q + 2 + tile - wide.pairs; sj = q + 2; }
+                else { si = q + 2; sj = tile - wide.pairs - (below - 1); }
+            } else {
+                // m = si - 1 column pairs (without q + 1 and q + 2) of every pair si >= q + 3
+                const long r = ((k & 1) ? tile + wide.first : tile - wide.near) + (q + 2) * (q + 1) / 2;
+                long m = (long)((sqrt(8.0 * (double)r + 1.0) + 1.0) * 0.5);
+                while (m * (m - 1) / 2 > r) m--;
+                while ((m + 1) * m / 2 <= r) m++;
+                si = m + 1;
+                sj = r - m * (m - 1) / 2;
+                if (sj >= q + 1) sj += 2;
+            }
+            ib = 2 * si + (half & 1);
+        }
+        const long s0 = single ? k - 1 : 2 * q;
+        const long jb = min(2 * sj + (wq >> 1), last);
+        if (ib > last || (!single && ib == s0 + 2)) return;         // (the same in the whole workgroup)
+        const bool mine = 2 * sj + (wq >> 1) <= last && jb <= ib && (single ? jb == k + 1 || (ib == k + 1 && jb != k) : jb != s0 + 2);
+        // the panel's two steps one after the other through LDS, 64 columns c at a time: rows [c][64], columns [c][128]; the
+        // second step's operands are on their way while the first one's are multiplied
+        float4 sa[2], sb[4];
         auto fetch = [&](long s) {
+            long ld;
+            const float* const pa = gq_p_block(v, K, slots, s, ib, ld);
 #pragma unroll
-            for (int o = 0; o < 2; o++)
+            for (int i = 0; i < 2; i++) sa[i] = load_global<float4>(pa + ((tid >> 4) + 32 * i) * ld + 4 * (tid & 15));
+            const int f4 = tid & 31;
+            const float* const pb = gq_p_block(v, K, slots, s, min(2 * sj + (f4 >> 4), last), ld);
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int at = tid + kGqStepThreads * i, c = at >> 5, f4 = at & 31;
-                    long ld;
-                    const float* const from = gq_p_block(v, K, slots, s, min(2 * (o ? sj : si) + (f4 >> 4), last), ld);
-                    stage[o][i] = load_global<float4>(from + c * ld + 4 * (f4 & 15));
-                }
+            for (int i = 0; i < 4; i++) sb[i] = load_global<float4>(pb + ((tid >> 5) + 16 * i) * ld + 4 * (f4 & 15));
             __builtin_amdgcn_sched_barrier(0);
         };
+        float* const s_b = s_all + kGqGroup * kGqGroup;
         auto park = [&] {
 #pragma unroll
-            for (int o = 0; o < 2; o++)
+            for (int i = 0; i < 2; i++) *reinterpret_cast<float4*>(s_all + 4 * (tid + kGqStepThreads * i)) = sa[i];
 #pragma unroll
-                for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(s_all + o * 128 * kGqGroup + 4 * (tid + kGqStepThreads * i)) = stage[o][i];
+            for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(s_b + 4 * (tid + kGqStepThreads * i)) = sb[i];
             __syncthreads();
         };
-        // interleaved as in GqTile, with two column tiles: register i of tile (x, y) is row 16 rg + 4 i + x, column 2 cl + y
-        f32x4_t acc[4][2];
+        // interleaved as in GqTile, with two row and two column tiles: register i of tile (x, y) is row 8 rg + 2 i + x, column
+        // 2 cl + y
+        f32x4_t acc[2][2];
         auto multiply = [&] {
-            const float* ap = s_all + rg * 128 + 64 * wi + 4 * cl;
-            const float* bp = s_all + 128 * kGqGroup + rg * 128 + 32 * wq + 2 * cl;
+            const float* ap = s_all + rg * kGqGroup + 32 * wi + 2 * cl;
+            const float* bp = s_b + rg * 128 + 32 * wq + 2 * cl;
 #pragma unroll 4
             for (int kk = 0; kk < kGqGroup / 4; kk++) {
-                const float4 av = *reinterpret_cast<const float4*>(ap + kk * 512);
+                const float2 av = *reinterpret_cast<const float2*>(ap + kk * 4 * kGqGroup);
                 const float2 bv = *reinterpret_cast<const float2*>(bp + kk * 512);
-                const float ar[4] = {-av.x, -av.y, -av.z, -av.w};
-#pragma unroll
-                for (int x = 0; x < 4; x++) {
-                    acc[x][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[x], bv.x, acc[x][0], 0, 0, 0);
-                    acc[x][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[x], bv.y, acc[x][1], 0, 0, 0);
-                }
+                acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.x, bv.x, acc[0][0], 0, 0, 0);
+                acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.x, bv.y, acc[0][1], 0, 0, 0);
+                acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.x, acc[1][0], 0, 0, 0);
+                acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, acc[1][1], 0, 0, 0);
             }
         };
         fetch(s0);
-        const uint32_t off = 16 * rg * (uint32_t)K + 2 * cl;
-        float* const dst = v + ib * kGqGroup * K + jb * kGqGroup + 32 * (wq & 1);
+        const uint32_t off = 8 * rg * (uint32_t)K + 2 * cl;
+        float* const dst = v + (ib * kGqGroup + 32 * wi) * K + jb * kGqGroup + 32 * (wq & 1);
 #pragma unroll
-        for (int r = 0; r < 16; r++) {
+        for (int r = 0; r < 8; r++) {
             float2 val = make_float2(0.0f, 0.0f);       // (block columns of the panel itself: L^-1's part starts here)
-            if (jb != s0 && jb != s0 + 1) val = load_global<float2>(dst + r * K + off);
-            acc[r & 3][0][r >> 2] = val.x;
-            acc[r & 3][1][r >> 2] = val.y;
+            if (jb != s0 && (single || jb != s0 + 1)) val = load_global<float2>(dst + r * K + off);
+            acc[r & 1][0][r >> 1] = val.x;
+            acc[r & 1][1][r >> 1] = val.y;
         }
         park();
-        fetch(s0 + 1);
+        if (!single) fetch(s0 + 1);
         multiply();
-        __syncthreads();                                // the first step's operands have been read
-        park();
-        if (jb == s0 + 1) {                             // ... with the panel's second step
+        if (!single) {
+            __syncthreads();                            // the first step's operands have been read
+            park();
+            if (jb == s0 + 1) {                         // ... with the panel's second step
 #pragma unroll
-            for (int x = 0; x < 4; x++) acc[x][0] = acc[x][1] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+                for (int x = 0; x < 2; x++) acc[x][0] = acc[x][1] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            multiply();
         }
-        multiply();
         if (!mine) return;
 #pragma unroll
-        for (int r = 0; r < 16; r++) store_global(dst + r * K + off, make_float2(acc[r & 3][0][r >> 2], acc[r & 3][1][r >> 2]));
+        for (int r = 0; r < 8; r++) store_global(dst + r * K + off, make_float2(acc[r & 1][0][r >> 1], acc[r & 1][1][r >> 1]));
         return;
     }
     // ---- solve
@@ -909,59 +926,51 @@ __global__ __launch_bounds__(kGqStepThreads, 4) void gptq_step_kernel(float* v, 
     float* const s_x = s_m + kGqGroup * kGqLd;                      // own block, [column j][c], 64 rows of 68
     float* const s_q = s_x + kGqGroup * kGqLd;                      // 16 x 16 blocks of the factor's diagonal
     float2* const s_inv = reinterpret_cast<float2*>(s_q + kGqGroup * kGqChunk);
-    float* const s_e = reinterpret_cast<float*>(s_inv + kGqGroup);  // [wavefront][c][column], negated
-    static_assert(2 * kGqGroup * kGqLd + kGqGroup * kGqChunk + 2 * kGqGroup + kGqGroup * kGqGroup <= kGqStepLds, "the solver's blocks fit");
+    float* const s_e = reinterpret_cast<float*>(s_inv + kGqGroup);  // [wavefront][c of the 16][column], negated
+    static_assert(2 * kGqGroup * kGqLd + kGqGroup * kGqChunk + 2 * kGqGroup + kGqChunk * kGqGroup <= kGqStepLds, "the solver's blocks fit");
     __builtin_amdgcn_s_setprio(3);                                  // the launch's longest chain, beside wavefronts that only add work
     const long jb = blockIdx.x, base = k * kGqGroup;
     {
-        // P's columns of block k and of the own block, of up to two pending steps, into LDS: [step][block k, own][c][column], all
-        // requested at once (the workgroups of the launches before left them in other L2s, a microsecond away)
-        const long s0 = (k & 1) ? k - 1 : max(k - 2, 0L);           // first pending step
-        float4 stage[2][2][2];
+        // columns of block k and of the own block of step k - 1's P into LDS, [block k, own][c][column]: all requested at once (the
+        // workgroups of the launch before left them in other L2s, a microsecond away)
+        const long before = k - 1;
+        const bool with_own = jb > k || (jb < k && k > 0);
+        float4 stage[2][2];
 #pragma unroll
-        for (int h = 0; h < 2; h++)
+        for (int b = 0; b < 2; b++)
+            if (k > 0 && (b == 0 || with_own)) {
+                long ld;
+                const float* const from = gq_p_block(v, K, slots, before, b ? jb : k, ld) + (tid >> 4) * ld + 4 * (tid & 15);
 #pragma unroll
-            for (int b = 0; b < 2; b++)
-                if (s0 + h < k && (b == 0 || jb > k || (jb < k && s0 + h >= jb))) {
-                    long ld;
-                    const float* const from = gq_p_block(v, K, slots, s0 + h, b ? jb : k, ld) + (tid >> 4) * ld + 4 * (tid & 15);
-#pragma unroll
-                    for (int i = 0; i < 2; i++) stage[h][b][i] = load_global<float4>(from + 32 * i * ld);
-                }
+                for (int i = 0; i < 2; i++) stage[b][i] = load_global<float4>(from + 32 * i * ld);
+            }
         // wavefronts 0..3: a quadrant each of the diagonal block; 4..7: of the own one (below the diagonal transposed: rows j)
         const bool own = wave >= 4;
         const int w4 = wave & 3, wi = w4 >> 1, wj = w4 & 1, ln = lane & 31, h = lane >> 5;
         const long rows = own && jb > k ? jb : k, cols = own && jb < k ? jb : k;
-        // (L^-1's part of a column block starts with that block's own step)
-        const bool fresh = cols < k && cols >= s0;
         float16_t acc;
         const float* const src = v + (rows * kGqGroup + 32 * wi + 4 * h) * K + cols * kGqGroup + 32 * wj + ln;
 #pragma unroll
         for (int i = 0; i < 16; i++) {
-            acc[i] = 0.0f;
+            acc[i] = 0.0f;                                          // (block column k - 1: L^-1's part starts with its own step)
             if (own && jb == k) acc[i] = (32 * wi + 8 * (i >> 2) + 4 * h + (i & 3) == 32 * wj + ln) ? 1.0f : 0.0f;
-            else if (!fresh) acc[i] = src[(long)(8 * (i >> 2) + (i & 3)) * K];
+            else if (cols != before) acc[i] = src[(long)(8 * (i >> 2) + (i & 3)) * K];
         }
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int hh = 0; hh < 2; hh++)
+        if (k > 0) {
 #pragma unroll
             for (int b = 0; b < 2; b++)
-                if (s0 + hh < k)
 #pragma unroll
-                    for (int i = 0; i < 2; i++)
-                        *reinterpret_cast<float4*>(s_all + (2 * hh + b) * kGqGroup * kGqGroup + 4 * (tid + kGqStepThreads * i)) = stage[hh][b][i];
+                for (int i = 0; i < 2; i++)
+                    *reinterpret_cast<float4*>(s_all + b * kGqGroup * kGqGroup + 4 * (tid + kGqStepThreads * i)) = stage[b][i];
+        }
         __syncthreads();
-        if (!(own && jb == k) && wave != 1)                         // (wavefront 1: above the diagonal, not needed)
-            for (int hh = 0; hh < 2; hh++) {
-                if (s0 + hh >= k || (cols < k && s0 + hh < cols)) continue;
-                const float* const at = s_all + 2 * hh * kGqGroup * kGqGroup;
-                const float* const ap = at + (rows == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wi + ln;
-                const float* const bp = at + (cols == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wj + ln;
+        if (k > 0 && !(own && jb == k) && wave != 1) {              // (wavefront 1: above the diagonal, not needed)
+            const float* const ap = s_all + (rows == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wi + ln;
+            const float* const bp = s_all + (cols == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wj + ln;
 #pragma unroll 8
-                for (int c = 0; c < kGqGroup; c += 2)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[c * kGqGroup], bp[c * kGqGroup], acc, 0, 0, 0);
-            }
+            for (int c = 0; c < kGqGroup; c += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[c * kGqGroup], bp[c * kGqGroup], acc, 0, 0, 0);
+        }
         __syncthreads();                                            // the operands have been read
 #pragma unroll
         for (int i = 0; i < 16; i++) {
@@ -975,7 +984,7 @@ __global__ __launch_bounds__(kGqStepThreads, 4) void gptq_step_kernel(float* v, 
     const int w4 = wave & 3, rr = lane >> 2, q = lane & 3;
     const long j = jb * kGqGroup + 16 * w4 + rr;                    // substitution: four lanes per column
     float* const xr = s_x + 16 * w4 * kGqLd;
-    float* const se = s_e + w4 * kGqGroup * 16;
+    float* const se = s_e + w4 * kGqChunk * 16;
     float* const pj = jb == k ? slots + k * kGqGroup * kGqGroup + q * kGqGroup + 16 * w4 + rr : v + (base + q) * K + j;
     const long pld = jb == k ? kGqGroup : K;
     float* const uj = u + (K - 1 - base - q) * K + (K - 1 - j);
@@ -1007,7 +1016,7 @@ __global__ __launch_bounds__(kGqStepThreads, 4) void gptq_step_kernel(float* v, 
                 if (c == 3) {
                     pj[(long)(t0 + 4 * k4) * pld] = keep;
                     uj[-(long)(t0 + 4 * k4) * K] = (jb > k) ? 0.0f : keep;
-                    se[(t0 + 4 * k4 + q) * 16 + rr] = -keep;
+                    se[(4 * k4 + q) * 16 + rr] = -keep;
                 }
                 const float4 d4 = sd[i * (kGqChunk / 4)];
                 const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
@@ -1017,7 +1026,7 @@ __global__ __launch_bounds__(kGqStepThreads, 4) void gptq_step_kernel(float* v, 
             // ... and onto the columns behind them
             float a[4];
 #pragma unroll
-            for (int kk = 0; kk < 4; kk++) a[kk] = se[(t0 + 4 * kk) * 16 + lane];
+            for (int kk = 0; kk < 4; kk++) a[kk] = se[4 * kk * 16 + lane];
             for (int tt = s; tt < 4; tt++) {
                 float* const at = xr + 4 * rg * kGqLd + 16 * tt + cl;
                 f32x4_t acc;
@@ -1133,9 +1142,14 @@ int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, flo
     const long nb = K / kGqGroup;
     for (long k = 0; k < nb; k++) {
         const GqWide wide = gq_wide(nb, k);
-        const long tiles = gq_wide_tiles(wide, nb, k);
-        dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_step_kernel, dim3((unsigned)(nb + tiles)), dim3(kGqStepThreads), 0, st, v, K, k,
-                     slots, u, wide);
+        const long blocks = nb + gq_wide_blocks(wide, k);
+        // Three workgroups fit on a compute unit, but while all of a launch's are resident together that puts two tiles beside a
+        // solver and three elsewhere, and the launch waits for the solver: 64 KB of LDS let two in, and the last tiles go
+        // where one has ended (K = 4096: 1.41 -> 1.35 ms).  Beyond one filling the tiles are what it waits for (14336: 28.4
+        // with two, 25.4 with three).
+        const size_t lds = blocks <= 3L * ctx->num_cu ? 4 * kGqGroup * kGqGroup * 4 : kGqStepLds * 4;
+        dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_step_kernel, dim3((unsigned)blocks), dim3(kGqStepThreads), lds, st, v, K, k, slots, u,
+                     wide);
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;

@@ -334,8 +334,10 @@ def test_gptq_sweep_subnormal_errors_reach_the_codes(ctx, N, K, bits, halfway):
     assert _same(got, want)
 
 
-# blocks of 64, updated in 2 x 2: one block, two, an odd number, and pivots outside the range of the estimate's steps
-@pytest.mark.parametrize("K,size", [(128, 1.0), (320, 1.0), (704, 1.0), (192, 1e-34), (192, 1e32)])
+# blocks of 64, brought forward two steps at a time in pairs of blocks: one to ten of them and a few odd numbers beyond, and pivots
+# outside the range of the estimate's steps
+@pytest.mark.parametrize("K,size", [(128, 1.0), (320, 1.0), (704, 1.0), (192, 1e-34), (192, 1e32), (256, 1.0), (384, 1.0), (448, 1.0),
+                                    (512, 1.0), (576, 1.0), (640, 1.0), (1088, 1.0)])
 def test_gptq_factor_block_edges(ctx, K, size):
     xb = synth.calibration_inputs(870 + K, 2 * K, K)
     H = O.gptq_hessian(xb)
