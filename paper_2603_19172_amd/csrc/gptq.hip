@@ -514,6 +514,78 @@ __global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __re
     }
 }
 
+// The same corrections for launches that the kernel above leaves the chip half empty in (its workgroup takes 15 us of matrix
+// instructions whatever there is beside it): a workgroup 64 x 64, a wavefront 32 x 32, the operands of 64 columns c at a time
+// through LDS.  Up to three quarters of a workgroup of the other kernel per compute unit; a whole sweep, us, other / this:
+// 200 x 4096 764 / 583, 1700 x 1024 179 / 151, 5097 x 832 162 / 141; 8000 x 1024 (252 workgroups and fewer) 203 / 203, 14336 x
+// 512 (224) 85 / 88.
+template <bool FIRST>
+__global__ __launch_bounds__(256, 4) void gptq_trail_small_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u,
+                                                               long N, long K, long base, int n_cols, long col_begin, GqErr err)
+{
+    __shared__ __attribute__((aligned(16))) float s_a[kGqGroup * kGqGroup], s_b[kGqGroup * kGqGroup];     // errors, rows of U: [c][64]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = lane >> 4, cl = lane & 15, wi = wave >> 1, wj = wave & 1;
+    const uint32_t n_blocks = (uint32_t)((N + kGqRows - 1) / kGqRows);
+    const long cb = blockIdx.x / n_blocks, block = blockIdx.x - (uint32_t)cb * n_blocks;
+    const long col0 = col_begin + cb * kGqGroup, row0 = block * kGqRows;
+    long eld;
+    const float* const eb = gq_err_block(err, block, eld);
+    float4 sa[4], sb[4];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int c = c0 + (tid >> 4) + 16 * i;
+            sa[i] = load_global<float4>(eb + (long)(c >> 2) * eld + (c & 3) * kGqRows + 4 * (tid & 15));
+            sb[i] = load_global<float4>(u + (base + c) * K + col0 + 4 * (tid & 15));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(0);
+    // interleaved: register i of tile (x, y) is row 8 rg + 2 i + x, column 2 cl + y of the wavefront's 32 x 32
+    f32x4_t acc[2][2];
+    const int r0 = 32 * wi + 8 * rg;
+    const long at = col0 + 32 * wj + 2 * cl;
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+        const long row = min(row0 + r0 + r, N - 1);
+        float2 val;
+        if constexpr (FIRST) {
+            const uint32_t raw = load_global<uint32_t>(w + row * K + at);
+            val = make_float2(bf16_lo(raw), bf16_hi(raw));
+        } else {
+            val = load_global<float2>(v + row * K + at);
+        }
+        acc[r & 1][0][r >> 1] = val.x;
+        acc[r & 1][1][r >> 1] = val.y;
+    }
+    const float* const ap = s_a + rg * kGqGroup + 32 * wi + 2 * cl;
+    const float* const bp = s_b + rg * kGqGroup + 32 * wj + 2 * cl;
+#pragma unroll 1
+    for (int c0 = 0; c0 < n_cols; c0 += kGqGroup) {
+        if (c0 > 0) __syncthreads();                    // the operands before have been read
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            *reinterpret_cast<float4*>(s_a + 4 * (tid + 256 * i)) = sa[i];
+            *reinterpret_cast<float4*>(s_b + 4 * (tid + 256 * i)) = sb[i];
+        }
+        __syncthreads();
+        fetch(min(c0 + kGqGroup, n_cols - kGqGroup));   // (past the end: the last ones again, unused)
+#pragma unroll 4
+        for (int kk = 0; kk < kGqGroup / 4; kk++) {
+            const float2 av = *reinterpret_cast<const float2*>(ap + kk * 4 * kGqGroup);
+            const float2 bv = *reinterpret_cast<const float2*>(bp + kk * 4 * kGqGroup);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.y, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.x, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.y, acc[1][1], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 8; r++)
+        if (row0 + r0 + r < N) store_global(v + (row0 + r0 + r) * K + at, make_float2(acc[r & 1][0][r >> 1], acc[r & 1][1][r >> 1]));
+}
+
 // ---------------------------------------------------------------------------
 // Hessian of the calibration inputs: hess (+)= X^T X, x [n, K] bf16, fp32 sums on the matrix cores
 // (v_mfma_f32_32x32x16_bf16: the products of bf16 numbers are exact in fp32).  Both operands of a tile are
@@ -1092,9 +1164,17 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
         DYMOE_HIP_LAUNCH_CHECK();
         if (next >= K) break;
         const long row_pairs = (n_blocks + 1) / 2, col_pairs = (K - next + 2 * kGqGroup - 1) / (2 * kGqGroup);
-        const dim3 grid((unsigned)(8 * ((row_pairs + 7) / 8) * col_pairs));
-        dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, first ? gptq_trail_kernel<true> : gptq_trail_kernel<false>, grid, dim3(256), 0, st,
-                     w, v, u, N, K, base, groups * kGqGroup, next, err);
+        auto trail = [&](auto kernel, long blocks) {
+            dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, v, u, N, K, base, groups * kGqGroup,
+                         next, err);
+        };
+        if (4 * row_pairs * col_pairs <= 3L * ctx->num_cu) {
+            const long blocks = n_blocks * ((K - next) / kGqGroup);
+            first ? trail(gptq_trail_small_kernel<true>, blocks) : trail(gptq_trail_small_kernel<false>, blocks);
+        } else {
+            const long blocks = 8 * ((row_pairs + 7) / 8) * col_pairs;
+            first ? trail(gptq_trail_kernel<true>, blocks) : trail(gptq_trail_kernel<false>, blocks);
+        }
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;

@@ -369,3 +369,18 @@ def test_gptq_workspaces_are_as_large_as_asked_for(ctx, N, K):
         ws = torch.full((need + 65536,), fill, dtype=torch.uint8, device=DEV)
         got = ctx.gptq_quantize_pack(to_bf16(wb), want_u, 4, workspace=ws[:need])
         assert all(torch.equal(a, b) for a, b in zip(got, want)) and (ws[need:] == fill).all()
+
+
+# corrections behind a panel: the two kernels on either side of the rule (192 workgroups of 128 x 128 on 256 compute units), whole and
+# ragged row blocks; rows are independent, so a few of them alone give the same codes
+@pytest.mark.parametrize("N,K", [(12288, 512), (12289, 512), (6144, 832), (6273, 768)])
+def test_gptq_corrections_of_few_and_many_workgroups(ctx, N, K):
+    g = torch.Generator(device=DEV).manual_seed(N)
+    w = (torch.randn((N, K), generator=g, device=DEV) * 0.02).bfloat16()
+    x = torch.randn((2 * K, K), generator=g, device=DEV)
+    u = ctx.gptq_factor(ctx.gptq_hessian((x + torch.randn((2 * K, 1), generator=g, device=DEV)).bfloat16()))
+    whole = ctx.gptq_quantize_pack(w, u, 4)
+    for rows in (slice(0, 70), slice(N - 131, N)):
+        part = ctx.gptq_quantize_pack(w[rows].contiguous(), u, 4)
+        for a, b in zip(whole, part):
+            assert torch.equal(a[rows].contiguous().view(torch.uint8), b.view(torch.uint8))
