@@ -387,7 +387,6 @@ struct GqTile {
 // from L2 twice as far ahead was bound by that traffic (85 TFLOP/s: the 32 KB of L1 hold no two wavefronts' batches).
 // ap, bp: this wavefront's share of the operands, tile w % 2 and the c's 4 (w / 2) .. + 3 and 8 + 4 (w / 2) .. + 3 of a stage, at the
 // lane's own place (c = rg, row or column 4 cl); lda4, ldb4: four c's further.
-template <bool NEG_A>
 __device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int wave, const float* ap, long lda4, const float* bp, long ldb4, int n)
 {
     constexpr int kStage = 2 * 16 * kGqGroup;                   // floats of one operand
@@ -418,7 +417,7 @@ __device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int w
         for (int k = 0; k < 4; k++) {
             const float4 av = *reinterpret_cast<const float4*>(get_a + buf * 2 * kStage + k * 4 * kGqGroup);
             const float4 bv = *reinterpret_cast<const float4*>(get_b + buf * 2 * kStage + k * 4 * kGqGroup);
-            const float ar[4] = {NEG_A ? -av.x : av.x, NEG_A ? -av.y : av.y, NEG_A ? -av.z : av.z, NEG_A ? -av.w : av.w};
+            const float ar[4] = {av.x, av.y, av.z, av.w};
             const float br[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
             for (int x = 0; x < 4; x++)
@@ -494,7 +493,7 @@ __global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __re
     }
     long eld;
     const float* const eb = gq_err_block(err, min(2 * (long)rp + (wave & 1), n_blocks - 1), eld);
-    gq_tile_products<false>(acc, s_op, wave, eb + (wave >> 1) * eld + 4 * lane, eld, u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl,
+    gq_tile_products(acc, s_op, wave, eb + (wave >> 1) * eld + 4 * lane, eld, u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl,
                             4 * K, n_cols);
     if (!mine) return;
     float* dst = v + row0 * K + col0;
