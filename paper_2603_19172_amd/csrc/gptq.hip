@@ -603,11 +603,15 @@ __device__ __forceinline__ int hs_swizzle(int c) { return (c ^ (c >> 3)) & 7; }
 constexpr int kHsSamples = 64;
 constexpr int kHsThreads = 256;
 
-__global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t* __restrict__ x, long n, long K,
-                                                                 int accumulate, float* __restrict__ hess)
+// PARTS: groups of four wavefronts that take the sample steps in turn; their sums meet in LDS, the first part's first.
+template <int PARTS>
+__global__ __launch_bounds__(PARTS* kHsThreads) void gptq_hessian_kernel(const uint16_t* __restrict__ x, long n, long K,
+                                                                        int accumulate, float* __restrict__ hess)
 {
-    __shared__ uint4 s_op[2][kHsTile * (kHsSamples / 8)];      // [operand][column][chunk of 8 samples]
-    const int tid = threadIdx.x;
+    __shared__ uint4 s_ops[PARTS][2][kHsTile * (kHsSamples / 8)];      // [part][operand][column][chunk of 8 samples]
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / kHsThreads);
+    uint4(*const s_op)[kHsTile * (kHsSamples / 8)] = s_ops[part];
+    const int tid = threadIdx.x & (kHsThreads - 1);
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int ln = lane & 31, kb = lane >> 5;
     // block -> tile (ti, tj), tj >= ti, rows of the upper triangle one after the other
@@ -643,8 +647,10 @@ __global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t
         for (int r = 0; r < 8; r++) raw[r] = load_global<uint4>(xc + min(s0 + 8 * sgrp + r, n - 1) * K);
         __builtin_amdgcn_sched_barrier(0);
     };
-    fetch(0);
-    for (long s0 = 0; s0 < n; s0 += kHsSamples) {
+    fetch(part * kHsSamples);
+    // (every part makes as many trips; a step past the end adds nothing)
+    for (long first = 0; first < n; first += PARTS * kHsSamples) {
+        const long s0 = first + part * kHsSamples;
         if (s0 + kHsSamples > n)                    // the last step
 #pragma unroll
             for (int r = 0; r < 8; r++)
@@ -671,7 +677,7 @@ __global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t
             s_op[op][c * (kHsSamples / 8) + (sgrp ^ hs_swizzle(c))] = out[i];
         }
         __syncthreads();
-        if (s0 + kHsSamples < n) fetch(s0 + kHsSamples);          // in flight during the products
+        if (first + PARTS * kHsSamples < n) fetch(s0 + PARTS * kHsSamples);          // in flight during the products
 #pragma unroll
         for (int ks = 0; ks < kHsSamples / 16; ks++) {
             const int chunk = 2 * ks + kb;
@@ -688,6 +694,23 @@ __global__ __launch_bounds__(kHsThreads) void gptq_hessian_kernel(const uint16_t
                 for (int b = 0; b < 2; b++)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
         }
+    }
+    if constexpr (PARTS == 2) {
+        float* const s_sum = reinterpret_cast<float*>(s_ops);       // [register][thread]
+        static_assert(sizeof(s_ops) >= 64 * kHsThreads * sizeof(float), "the second part's sums fit in the operands' place");
+        __syncthreads();
+        if (part == 1) {
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) s_sum[(16 * a + i) * kHsThreads + tid] = acc[a >> 1][a & 1][i];
+        }
+        __syncthreads();
+        if (part == 1) return;
+#pragma unroll
+        for (int a = 0; a < 4; a++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) acc[a >> 1][a & 1][i] += s_sum[(16 * a + i) * kHsThreads + tid];
     }
     // register i of lane (ln, kb): row 8 (i / 4) + 4 kb + i % 4 of the 32 x 32 tile, column ln
 #pragma unroll
@@ -1198,8 +1221,17 @@ int dymoe_gptq_hessian(dymoe_ctx* ctx, const void* x_bf16, long n, long K, int a
     DYMOE_REQUIRE(K <= 65536 && dymoe_aligned(x_bf16, 16) && dymoe_aligned(hess, 16));
     if (!ctx) return DYMOE_ENOCTX;
     const long nt = (K + kHsTile - 1) / kHsTile;
-    dymoe_launch(ctx, DYMOE_K_GPTQ_HESSIAN, gptq_hessian_kernel, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(kHsThreads), 0,
-                 (hipStream_t)stream, (const uint16_t*)x_bf16, n, K, accumulate, hess);
+    const long tiles = nt * (nt + 1) / 2;
+    auto go = [&](auto kernel, int parts) {
+        dymoe_launch(ctx, DYMOE_K_GPTQ_HESSIAN, kernel, dim3((unsigned)tiles), dim3((unsigned)(parts * kHsThreads)), 0, (hipStream_t)stream,
+                     (const uint16_t*)x_bf16, n, K, accumulate, hess);
+    };
+    // Not more tiles than compute units: a tile's steps are a chain of 1.3 us each (load, transpose, store, barriers,
+    // products), and two parts of a workgroup share it.  One part / two, us: 4096 samples of 256 columns 69.5 / 56.9, 2216 of
+    // 960 44.6 / 38.1, 2048 of 2048 43.7 / 37.5, 2048 of 2816 48.5 / 42.3, 1000 of 512 26.9 / 24.1; 300 of 960 16.1 / 16.7 (the
+    // exchange costs more than three steps less give).  With more tiles the other workgroups of a compute unit fill the gaps.
+    if (tiles <= ctx->num_cu && n > 8 * kHsSamples) go(gptq_hessian_kernel<2>, 2);
+    else go(gptq_hessian_kernel<1>, 1);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
 }

@@ -384,3 +384,18 @@ def test_gptq_corrections_of_few_and_many_workgroups(ctx, N, K):
         part = ctx.gptq_quantize_pack(w[rows].contiguous(), u, 4)
         for a, b in zip(whole, part):
             assert torch.equal(a[rows].contiguous().view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,K", [(512, 136), (513, 136), (576, 8), (640, 2816), (641, 2824), (1345, 264)])
+def test_gptq_hessian_of_few_and_many_tiles(ctx, n, K):
+    # the split of the samples between the halves of a workgroup: last steps of one or both halves, remainders of 64 samples.
+    # 16-bit inputs multiply exactly; a sum of n terms in fp32, in any order, is off by at most n 2^-24 of the sum of its magnitudes
+    x = to_bf16(synth.calibration_inputs(910 + n, n, K))
+    exact = x.double().t() @ x.double()
+    bound = (n + 1) * 2.0**-24 * (x.double().abs().t() @ x.double().abs())
+    got = ctx.gptq_hessian(x)
+    assert bool(((got.double() - exact).abs() <= bound).all())
+    assert torch.equal(got, got.t())
+    twice = ctx.gptq_hessian(x, out=got.clone(), accumulate=True)
+    assert torch.equal(twice, got + got)
