@@ -578,8 +578,7 @@ def main():
                 "hessian_ms": round(fac["gptq_hessian"][0], 3),
                 "hessian_TFLOPs_bf16": round(2.0 * n_cal * gK * gK / 2 / (fac["gptq_hessian"][0] * 1e-3) / 1e12, 1),
                 "factor_ms_wall": round((t1 - t0) * 1e3 - fac["gptq_hessian"][0], 2),
-                "factor_kernels_ms": {"first_block": round(fac["gptq_factor"][0], 2), "solve": round(fac["gptq_group"][0], 2),
-                                      "update": round(fac["gptq_trail"][0], 2)},
+                "factor_kernels_ms": {"steps": round(fac["gptq_factor"][0], 2)},
                 "sweep_ms_wall": round((t2 - t1) * 1e3, 2),
                 "sweep_kernels_ms": {"group": round(swp["gptq_group"][0], 2), "trail": round(swp["gptq_trail"][0], 2)},
                 "sweep_trail_TFLOPs_fp32": round(trail_flops / (swp["gptq_trail"][0] * 1e-3) / 1e12, 1),
