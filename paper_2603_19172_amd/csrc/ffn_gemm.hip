@@ -23,6 +23,7 @@
 //    compute unit: the two wavefronts of a SIMD belong to different workgroups,
 //    so one's barrier, waits, prologue and epilogue are covered by the other's
 //    MFMA work.
+//  * Calls of few tokens per expert plan tiles of 32 rows and take gemm_small_kernel, which keeps both operands in registers.
 //  * Results leave through LDS: in the MFMA result layout a lane holds a few
 //    outputs of one token's row, so stores made from it would touch 32 rows per
 //    instruction; the token-tile buffers, free after the K loop, turn the

@@ -20,8 +20,8 @@ static inline int ffn_tile_rows(int T, int E, int k)
 }
 
 struct FfnLayout {
-    size_t hbuf;    // [P,F] SwiGLU intermediate: fp32 (GEMV) or 16-bit (GEMM)
-    size_t part;    // GEMM: [P,H] fp32 per-pair outputs (the GEMV path keeps its partial sums on chip; the area is sized as before)
+    size_t hbuf;    // [P,F] SwiGLU intermediate: fp32 (GEMV) or 16-bit (GEMM; the splits' output slabs start right behind it)
+    size_t part;    // room for [P,H] fp32 per-pair outputs, one slab per split (the GEMV path keeps its partial sums on chip)
     size_t xh;      // GEMM: three [T,H] fp16 copies of the activations (int4 / int2 / natural column order)
     size_t plan;    // int32: counts[E], offsets[E+1], cursor[E], ntiles, perm[P], tiles[4*maxtiles], draft[4*maxtiles]
     size_t total;

@@ -1,6 +1,7 @@
 """One MoE layer with every buffer pre-allocated, so that a step is nothing but
-the five libdymoe calls enqueued back to back on one stream (no allocation, no
-host read-back): route -> importance -> precision -> quantize -> FFN.
+libdymoe calls enqueued back to back on one stream (no allocation, no host
+read-back): route -> importance -> precision -> FFN, each by itself or all
+through dymoe_layer_step / dymoe_decode_layer.
 
 Argument marshalling only; all arithmetic is in libdymoe.so.
 """
