@@ -21,7 +21,8 @@ constexpr int kAtThreads = 256;
 constexpr int kAtWaves = kAtThreads / kWave;
 // the LDS-staged kernels from this many 32-token fragments on (T > 992) ...
 constexpr int kAtWideFrags = 32;
-constexpr long kAtNarrowFrags = 512;   // ... if there are more than this over all heads
+template <int D>
+constexpr long kAtNarrowFrags = (D == 64) ? 768 : 512;   // ... if there are more than this over all heads
 
 // One lane's share of a 32-token fragment of one head (D columns): lane (ln, kb)
 // holds row ln; piece c covers columns 32 (c / 2) + 16 kb + 8 (c % 2) .. + 7, i.e.
@@ -559,10 +560,13 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     //    2500 x  8 (632)      79 /  87      120 / 100       45 /  66      66 /  79
     //    4096 x  6 (768)     184 / 135      188 / 138       99 / 100     102 / 105
     //    2048 x 16 (1024)    100 /  71      130 /  70       55 /  54      70 /  52
-    // so the line is right for d = 128; at d = 64, where a wavefront's share of the products is half as long, the narrow pair
-    // stays ahead up to about 768 fragments, by up to 30 %.
+    // so the line lies at 512 for d = 128, and at 768 for d = 64, where a wavefront's share of the products is half as long (three
+    // workgroups per compute unit instead of two).  There, narrow / wide, causal and not: 1500 x 16 (752) 33 / 44 and 44 / 52,
+    // 993 x 24 (768) 33 / 34 and 34 / 38, 3000 x 8 (752) 55 / 74 and 76 / 91, 6000 x 4 (752) 100 / 139 and 137 / 173, 16500 x 1
+    // (516) 190 / 359 and 356 / 458; error against 64 bits 7e-8 / 1.6e-7.
     // (Below 32 fragments the narrow pair stays for every number of heads: its four partial sums per key round less.)
-    const bool wide = nfrag >= dymoe::kAtWideFrags && (long)nfrag * n_heads > dymoe::kAtNarrowFrags;
+    const bool wide = nfrag >= dymoe::kAtWideFrags &&
+                      (long)nfrag * n_heads > (head_dim == 64 ? dymoe::kAtNarrowFrags<64> : dymoe::kAtNarrowFrags<128>);
     // A dimension of a launch holds fewer than 2^32 threads: beyond that (from 275 GB of queries on) a head per y, as in the
     // narrow pair's launches; 4096 x 32 takes 201 us that way and 199 in one dimension.
     const long blocks = (nfrag + 3L) / 4 * n_heads;

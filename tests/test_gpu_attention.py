@@ -68,6 +68,17 @@ def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
+# heads of 64 values take the staged kernels from more than 768 fragments on: the last count below that line and the first above it
+@pytest.mark.parametrize("T,Hh,Hkv", [(1024, 24, 8), (1025, 24, 8), (6113, 4, 4), (2975, 8, 2)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_score_small_heads_around_the_line(ctx, T, Hh, Hkv, causal):
+    cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=260 + T)
+    q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, 64, boost=1.0)
+    ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+    got = _run(ctx, q, k, causal)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
 # the sum over heads: one or two of them, batches of sixteen, whole, short by one and with one head left
 @pytest.mark.parametrize("Hh", [1, 2, 3, 15, 16, 17, 31, 32, 33])
 def test_attention_score_sums_every_head_once(ctx, Hh):
