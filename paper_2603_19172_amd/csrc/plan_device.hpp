@@ -133,11 +133,13 @@ constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the ti
 // Tiles of one fragment stream weights of different widths: one and a half rounds of workgroups level them out (24 tokens of
 // the Mixtral shape, 8 tiles x 16 blocks: GEMM and combine 87 us with 2 splits, 86 with 4, 73 with 5, 67 with 6, 69 with 8).
 // Tiles of more rows keep the matrix cores busy, and their workgroups last about the same: in units of a round of two
-// unsplit workgroups per compute unit, a launch takes 0.55 / s where each has a unit of its own, 1 / s up to one round and
+// unsplit workgroups per compute unit, a launch takes 0.6 / s where each has a unit of its own, 1 / s up to one round and
 // (rounds + 0.3) / s beyond, and every split writes and reads a slab, 0.0147 blocks / n_kt (a copy's rate against the matrix
 // cores').  us, GEMM and combine: 512 tokens of the Mixtral shape (9 x 16) 1 split 328, 2 209, 3 170, 4 189, 6 180; 433
 // tokens x 4 of 2048 x 6272 (16 x 8) 101, 68, 77, 73; 580 x 4 of 896 x 2560 (20 x 4) 59, 39, 34; 315 x 2 of 1792 x 3584
-// (16 x 7) 40, 29, 31.  The kernel for tiles of one fragment splits K over its wavefronts already: no more than 24 K-tiles per
+// (16 x 7) 40, 29, 31.  (The 0.6 lies between what these
+// say: 512 tokens of the Mixtral shape in 8 x 16 blocks, tall int4 and int2 tiles among them, 0.68 (2 splits 181, 4 138); 433
+// x 4 0.5.)  The kernel for tiles of one fragment splits K over its wavefronts already: no more than 24 K-tiles per
 // split, so that a bf16 expert's workgroups do not outlast the launch (80 tokens of 512 x 4864: 25.4 us with 38, 21.3 with 19).
 // By one wavefront, a lane per number (max <= 64); the least cost, the smaller number of equals.
 __device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRule& r, const PlanPtrs& pp)
@@ -152,7 +154,7 @@ __device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRul
             best = max(1, min(r.max, best));
         } else {
             const int n = blocks * s;
-            const float rounds = n <= r.num_cu ? 0.55f : n <= 2 * r.num_cu ? 1.0f : 0.5f * (float)n / (float)r.num_cu + 0.3f;
+            const float rounds = n <= r.num_cu ? 0.6f : n <= 2 * r.num_cu ? 1.0f : 0.5f * (float)n / (float)r.num_cu + 0.3f;
             const float cost = s <= r.max ? rounds / (float)s + 0.0147f * (float)blocks * (float)s / (float)r.n_kt : 1e30f;
             best = __ffsll((long long)__ballot(cost == -wave_max_dpp(-cost)));
         }
