@@ -83,6 +83,7 @@ __device__ __forceinline__ void route_logits(const uint16_t* __restrict__ x,
 // the entry.  The TB tokens are independent chains of the same arithmetic,
 // written side by side so that their latencies overlap; every token's result
 // is what TB = 1 gives.
+// A token none of whose logits is a number (NaN in its row) matches no expert: its indices are -1, and no load counts it.
 // t[b] < 0: token b is padding (computed, nothing written to global memory).
 // selp[b]: k floats of LDS scratch per token.  prob_sum (LDS, may be null):
 // prob_sum[e] += p[e]; load_cnt (LDS, may be null): load_cnt[e] += 1 for the
@@ -159,7 +160,7 @@ __device__ __forceinline__ void route_select_regs(float* const (&lg)[TB], float*
             }
             if (lane == 0) {
                 if (t[b] >= 0) idx[(size_t)t[b] * k + j] = bi;
-                if (load_cnt && t[b] >= 0) load_cnt[bi] += 1;
+                if (load_cnt && t[b] >= 0 && bi >= 0) load_cnt[bi] += 1;
             }
 #pragma unroll
             for (int c = 0; c < NC; c++)

@@ -1231,6 +1231,59 @@ def test_decode_layer_equals_the_separate_calls(ctx, T, H, E, k, floor, chained)
         assert torch.equal(u, v)
 
 
+# a token whose row holds NaN is routed nowhere: no expert's load counts it, nothing beside the loads is touched, its output is zero;
+# the decode layer with its logits in the workgroups and apart, one and two logits per lane, and behind a layer before; the front ends
+@pytest.mark.parametrize("T,H,E,k,chained", [(1, 256, 8, 2, False), (2, 256, 4, 2, False), (1, 4160, 4, 1, False), (4, 256, 64, 8, False),
+                                             (3, 512, 128, 8, False), (1, 2048, 128, 8, False), (1, 256, 8, 2, True),
+                                             (1, 4160, 4, 2, True), (1, 512, 65, 3, True)])
+def test_decode_with_a_token_that_is_routed_nowhere(ctx, T, H, E, k, chained):
+    g = torch.Generator(device=DEV).manual_seed(3 * H + E)
+    F = 192
+    rnd = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.05).bfloat16()
+    store = ExpertStore([[rnd(F, H), rnd(F, H), rnd(H, F)] for _ in range(E)], H, F, DEV, formats=(4, 2))
+    for b in (4, 2):
+        ctx.quantize_experts(store.table, torch.full((E,), b, dtype=torch.uint8, device=DEV), None, E, H, F, layout=B.LAYOUT_ROWMAJOR)
+    wg = rnd(E, H)
+    x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
+    lost = T // 2
+    if not chained:
+        x[lost, 17] = float("nan")
+    layers = [MoELayer(ctx, T, H, F, E, k, "decode", [1, E // 2, E - 1 - E // 2], [16, 4, 2], out_dtype=B.OUT_F32, device=DEV)
+              for _ in range(4)]
+    whole, front, calls, step = layers
+    st = B._stream(None)
+    for lay in layers:
+        lay.load.fill_(-5)
+        lay.y.fill_(7.0)
+    if chained:
+        y_prev = torch.randn((T, H), generator=g, device=DEV)
+        y_prev[0, H - 1] = float("nan")
+        h_out = torch.zeros_like(x)
+        B._check(B.lib.dymoe_decode_layer(
+            ctx._h, x.data_ptr(), y_prev.data_ptr(), 0.125, h_out.data_ptr(), wg.data_ptr(), None, 1, H, F, E, k, 1, 3,
+            ctypes.cast(whole._tc, ctypes.c_void_p), ctypes.cast(whole._tb, ctypes.c_void_p), 0, store.table.data_ptr(), 64, B.OUT_F32,
+            whole.idx.data_ptr(), whole.gate.data_ptr(), whole.probs.data_ptr(), whole.imp.data_ptr(), whole.load.data_ptr(),
+            whole.bits.data_ptr(), whole.rank.data_ptr(), whole.y.data_ptr(), whole.ws.data_ptr(), whole.ws_bytes, st), "dymoe_decode_layer")
+        x = h_out
+    else:
+        assert whole.decode_layer(x, wg, None, store, st)
+    front.front(x, wg, None, st)
+    front.ffn(x, store, st)
+    calls.route(x, wg, None, st)
+    calls.importance(x, st)
+    calls.assign(st)
+    calls.ffn(x, store, st)
+    assert step.decode_step(x, wg, None, store, st) == (E <= 64)
+    for lay in layers if E <= 64 else layers[:3]:
+        assert (lay.idx[lost] == -1).all() and int(lay.load.sum()) == (T - 1) * k
+        want = torch.bincount(lay.idx[lay.idx >= 0].long(), minlength=E)
+        assert torch.equal(lay.load.long(), want)
+        assert bool((lay.y[lost] == 0).all()) and bool(torch.isfinite(lay.y).all())
+        for name in ("idx", "gate", "probs", "imp", "load", "bits", "rank", "y"):
+            u, v = getattr(lay, name).float(), getattr(calls, name).float()
+            assert torch.equal(torch.nan_to_num(u, nan=-7.0), torch.nan_to_num(v, nan=-7.0)), name
+
+
 # tiles of one fragment (up to 32 tokens, or up to 128 and eight pairs per expert): every format, expert loads around 32 rows, K-tiles
 # that the four wavefronts share unevenly or that are fewer than they, several splits, the larger kernel on the same tiles
 @pytest.mark.parametrize("T,H,F,E,k", [(5, 128, 128, 5, 2), (32, 256, 1152, 5, 5), (31, 384, 2048, 8, 1), (33, 128, 256, 8, 1),
