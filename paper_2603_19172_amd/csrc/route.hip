@@ -52,9 +52,9 @@ __device__ __forceinline__ void store_norm(const uint16_t* __restrict__ x, int t
 // score (may be NULL) of the routing kernels below: the tokens' norms for a caller that ranks by them next, which would
 // otherwise wait for a launch of their own (5 us) behind this one.
 // A workgroup of NW wavefronts owns TW tokens: logits by all wavefronts, then
-// token tw is finished (softmax, top-k) by wavefront tw mod NW.  Few tokens:
-// TW = 1 and the experts spread over 8 wavefronts; many tokens: TW = NW = 4, so
-// that a router row is read once per four tokens.
+// token tw is finished (softmax, top-k) by wavefront tw.  Few tokens: TW = 1 and
+// the experts spread over 8 or 16 wavefronts; many tokens: TW = NW = 4, so that a
+// router row is read once per four tokens.
 template <int TW, int NCH, int NW, int EB>
 __global__ __launch_bounds__(NW* kWave) void route_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(NW* kWave) void route_kernel(
     extern __shared__ float smem[];
     const int wave = threadIdx.x / kWave;
     float* logit = smem;                                  // [TW][E]
-    float* selp = smem + (size_t)TW * E + (size_t)wave * k;   // [NW][k]
+    float* selp = smem + (size_t)TW * E + (size_t)wave * k;   // [TW][k]: only the first TW wavefronts select
     const int t0 = blockIdx.x * TW;
     route_logits<TW, NCH, NW, EB>(x, wg, bias, T, H, E, t0, logit);
     __syncthreads();
@@ -73,11 +73,8 @@ __global__ __launch_bounds__(NW* kWave) void route_kernel(
         static_assert(TW <= NW, "a wavefront takes one norm at most");
         if (tw < TW && t0 + tw < T) store_norm(x, t0 + tw, H, score);
     }
-    for (int tw = wave; tw < TW; tw += NW) {
-        const int t = t0 + tw;
-        if (t >= T) break;
-        route_select(logit + tw * E, selp, t, E, k, renorm, idx, w, probs, nullptr, nullptr);
-    }
+    if (wave < TW && t0 + wave < T)
+        route_select(logit + wave * E, selp, t0 + wave, E, k, renorm, idx, w, probs, nullptr, nullptr);
 }
 
 // Gating of many tokens against many experts: the logits are a dense contraction
@@ -498,7 +495,7 @@ static int launch_route(dymoe_ctx* ctx, const void* x, const void* wg, const flo
                         int k, int renorm, int32_t* idx, float* w, float* probs, float* score, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((T + TW - 1) / TW);
-    const size_t smem = ((size_t)TW * E + (size_t)NW * k) * sizeof(float);
+    const size_t smem = (size_t)TW * ((size_t)E + (size_t)k) * sizeof(float);      // up to 8 KiB a token
     dymoe_launch(ctx, DYMOE_K_ROUTE, (route_kernel<TW, NCH, NW, EB>), dim3(blocks), dim3(NW * kWave), smem, st,
                        (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm, idx, w,
                        probs, score);

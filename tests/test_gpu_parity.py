@@ -240,6 +240,29 @@ def test_route_topk_one_token_per_workgroup(ctx, T, H, E, k):
     _check_route(ctx, x, wg[:E], bias[:E], k, min_ok=0.8)
 
 
+# nearly as many experts selected as there are, in every form that gives a workgroup one or four tokens
+@pytest.mark.parametrize("T,H,k", [(5, 128, 961), (5, 128, 1024), (5, 2304, 1024), (5, 4104, 1024), (5, 8200, 1024), (257, 200, 1000),
+                                   (1025, 128, 1024)])
+def test_route_topk_of_nearly_all_experts(ctx, T, H, k):
+    E = 1024
+    g = torch.Generator(device=DEV).manual_seed(T + H + k)
+    x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
+    wg = (torch.randn((E, H), generator=g, device=DEV) * 0.02).bfloat16()
+    idx, w, probs = ctx.route_topk(x, wg, None, k)
+    sync()
+    # probabilities against float64: 8-bit mantissas multiply exactly in fp32, H of them are added in fp32, and the largest logit
+    # of these inputs is below 8: H 2^-24 of the sum of magnitudes, at most 8200 * 2^-24 * 8200 * 0.02 * 0.64 = 0.05
+    want = torch.softmax(x.double() @ wg.double().t(), dim=1)
+    assert bool(((probs - want).abs() <= 0.06 * want).all())
+    chosen = torch.gather(probs, 1, idx.long())
+    assert bool((chosen[:, 1:] <= chosen[:, :-1]).all())                       # in descending order
+    assert torch.equal(torch.sort(idx, dim=1).values.diff(dim=1) > 0, torch.ones((T, k - 1), dtype=torch.bool, device=DEV))
+    rest = probs.scatter(1, idx.long(), 0.0).max(dim=1).values
+    assert bool((rest <= chosen[:, -1]).all())
+    # gate weights: k probabilities added in fp32 in order, one division
+    assert bool((w - chosen / chosen.double().sum(dim=1, keepdim=True)).abs().max() <= (k + 2) * 2.0 ** -24 * float(w.max()))
+
+
 def test_route_topk_without_probabilities_takes_the_one_kernel_form_and_agrees(ctx):
     """The two-pass router keeps its logits in the caller's probs array; a caller that passes none gets the
     one-kernel form.  Same experts (outside the margin) and the same gate weights either way."""
