@@ -1126,13 +1126,38 @@ def test_gemv_rows_per_workgroup(ctx, T, H, F):
     ("decode", 32, 128, 256, 8, 0, [8, 4, 2], 0, False), ("decode", 33, 128, 250, 3, 0, [4, 2], 8, False),
     ("decode", 300, 128, 128, 7, 0, [16, 4, 2], 0, False), ("decode", 1, 128, 8, 2, 0, [4, 2], 0, False)])
 def test_layer_step_equals_the_separate_calls(ctx, phase, T, H, E, k, k_hh, bits, floor, quantize):
+    def spoil(x, g):
+        if T > 300:
+            x[T // 3] = float("nan")                                       # a token that is routed nowhere
+    _layer_step_against_the_separate_calls(ctx, phase, T, H, E, k, k_hh, bits, floor, quantize, spoil)
+
+
+# rows with NaN (routed nowhere; in the decode phase every expert's importance is then NaN, and all share one rank) and rows whose
+# norm overflows, fewer, as many and more of them than are heavy, on both sides of the direct ranking
+@pytest.mark.parametrize("phase,T,E,k,k_hh,n_nan,n_inf,quantize", [
+    ("decode", 1, 8, 2, 0, 1, 0, True), ("decode", 5, 8, 2, 0, 1, 0, True), ("decode", 33, 250, 3, 0, 1, 0, False),
+    ("decode", 300, 128, 7, 0, 2, 0, False), ("decode", 64, 256, 8, 0, 64, 0, False), ("decode", 40, 129, 4, 0, 3, 5, False),
+    ("prefill", 200, 8, 2, 10, 3, 9, False), ("prefill", 257, 16, 2, 13, 0, 5, False), ("prefill", 300, 16, 2, 13, 0, 13, False),
+    ("prefill", 1025, 16, 4, 51, 2, 52, False), ("prefill", 2049, 9, 3, 100, 1, 1500, True), ("prefill", 400, 8, 2, 20, 0, 400, False),
+    ("prefill", 400, 8, 2, 20, 381, 0, False), ("prefill", 400, 8, 2, 20, 400, 0, False)])
+def test_layer_step_of_rows_that_are_not_numbers(ctx, phase, T, E, k, k_hh, n_nan, n_inf, quantize):
+    def spoil(x, g):
+        rows = torch.randperm(T, generator=g, device=DEV)
+        x[rows[:n_nan], 3] = float("nan")
+        x[rows[n_nan:n_nan + n_inf], 5] = 1e30                             # (the logits stay finite)
+    imp, idx = _layer_step_against_the_separate_calls(ctx, phase, T, 128, E, k, k_hh, [16, 4, 2], 0, quantize, spoil)
+    assert int((idx < 0).sum()) == n_nan * k
+    if phase == "decode":
+        assert bool(torch.isnan(imp).all()) == (n_nan > 0)
+
+
+def _layer_step_against_the_separate_calls(ctx, phase, T, H, E, k, k_hh, bits, floor, quantize, spoil):
     from paper_2603_19172_amd.layer import ExpertStore, MoELayer
     g = torch.Generator(device=DEV).manual_seed(T * 1000 + E)
     F = 128
     x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
     x[T // 2:] = x[:T - T // 2].clone()                                    # equal norms: order by token index
-    if T > 300:
-        x[T // 3] = float("nan")                                           # a token that is routed nowhere
+    spoil(x, g)
     wg = (torch.randn((E, H), generator=g, device=DEV) * 0.05).bfloat16()
     w = [[(torch.randn(s, generator=g, device=DEV) * 0.05).bfloat16() for s in ((F, H), (F, H), (H, F))] for _ in range(E)]
     counts = [E // 4] * (len(bits) - 1) + [E - (E // 4) * (len(bits) - 1)]
@@ -1174,6 +1199,7 @@ def test_layer_step_equals_the_separate_calls(ctx, phase, T, H, E, k, k_hh, bits
                 for m in range(3):
                     for u, v in zip(pa[4].q[be][e][m], pb[4].q[be][e][m]):
                         assert torch.equal(u, v)
+    return a[3], a[0]
 
 
 def test_layer_step_declines_what_it_does_not_cover(ctx):
