@@ -49,13 +49,19 @@ __device__ __forceinline__ void store_norm(const uint16_t* __restrict__ x, int t
     if (lane == 0) score[t] = n;
 }
 
-// score (may be NULL) of the routing kernels below: the tokens' norms for a caller that ranks by them next, which would
-// otherwise wait for a launch of their own (5 us) behind this one.
+// SCORE of the routing kernels below: the tokens' norms (to score) for a caller that ranks by them next, which would
+// otherwise wait for a launch of their own (5 us) behind this one.  Instantiations of their own, so that the plain router
+// carries neither the registers nor the code (as a run-time choice it cost a version with 128 registers one more, and with it a
+// wavefront in four: 1000 tokens x 2560, 20 experts 10.8 -> 14.7 us).
 // A workgroup of NW wavefronts owns TW tokens: logits by all wavefronts, then
 // token tw is finished (softmax, top-k) by wavefront tw.  Few tokens: TW = 1 and
 // the experts spread over 8 or 16 wavefronts; many tokens: TW = NW = 4, so that a
-// router row is read once per four tokens.
-template <int TW, int NCH, int NW, int EB>
+// router row is read once per four tokens.  A wavefront has one router row on
+// its way at a time: with two or four the registers cost wavefronts, and the
+// rows past the last expert are traffic (us, a row / two / four at a time: 40
+// tokens x 1024, 24 experts by 16 wavefronts 3.7 / 3.9 / 4.9; 1000 tokens x 1024,
+// 20 experts by 8 wavefronts 5.5 / 7.0 / 8.5; 300 x 4096, 20 experts 6.3 / 7.2).
+template <int TW, int NCH, int NW, bool SCORE>
 __global__ __launch_bounds__(NW* kWave) void route_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
     const float* __restrict__ bias, int T, int H, int E, int k, int renorm,
@@ -66,9 +72,9 @@ __global__ __launch_bounds__(NW* kWave) void route_kernel(
     float* logit = smem;                                  // [TW][E]
     float* selp = smem + (size_t)TW * E + (size_t)wave * k;   // [TW][k]: only the first TW wavefronts select
     const int t0 = blockIdx.x * TW;
-    route_logits<TW, NCH, NW, EB>(x, wg, bias, T, H, E, t0, logit);
+    route_logits<TW, NCH, NW, 1>(x, wg, bias, T, H, E, t0, logit);
     __syncthreads();
-    if (score) {                                          // the tokens' norms, by the wavefronts that select last
+    if constexpr (SCORE) {                                // the tokens' norms, by the wavefronts that select last
         const int tw = (wave + NW - 1) % NW;
         static_assert(TW <= NW, "a wavefront takes one norm at most");
         if (tw < TW && t0 + tw < T) store_norm(x, t0 + tw, H, score);
@@ -101,6 +107,7 @@ constexpr int kRmBK = 128;       // columns per K-tile
 constexpr int kRmBatch = 4;      // tokens a wavefront takes through softmax and top-k side by side
 constexpr int kRmWChunks = kRmExperts * (kRmBK / 8) / kRmThreads;      // 16-byte chunks of router rows per thread and K-tile
 
+template <bool SCORE>
 __global__ __launch_bounds__(kRmThreads) void route_mfma_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
     const float* __restrict__ bias, int T, int H, int E, int k, int renorm,
@@ -170,7 +177,7 @@ __global__ __launch_bounds__(kRmThreads) void route_mfma_kernel(
         }
         __syncthreads();
     }
-    if (score)
+    if constexpr (SCORE)
         for (int tw = wave; tw < kRmTokens && t0 + tw < T; tw += kRmWaves) store_norm(x, t0 + tw, H, score);
     // wavefront `wave` finishes tokens wave, wave + 8, wave + 16, wave + 24, side by side
     {
@@ -289,6 +296,7 @@ constexpr int kRsThreads = kRsWaves * kWave;
 // Softmax and top-k from logits in memory.  The selection is a chain of cross-lane reductions, k rounds long, that one
 // wavefront cannot overlap with anything but itself: what shortens the pass is more wavefronts, so each takes kRsBatch
 // tokens only and reads their logits straight from memory (a lane holds every 64th expert).
+template <bool SCORE>
 __global__ __launch_bounds__(kRsThreads) void route_select_kernel(
     int T, int E, int k, int renorm, int32_t* __restrict__ idx, float* __restrict__ w,
     float* probs /* in: logits, out: probabilities */, const uint16_t* __restrict__ x, int H, float* __restrict__ score)
@@ -297,7 +305,7 @@ __global__ __launch_bounds__(kRsThreads) void route_select_kernel(
     const int wave = threadIdx.x / kWave;
     const int t0 = (blockIdx.x * kRsWaves + wave) * kRsBatch;
     if (t0 >= T) return;
-    if (score)
+    if constexpr (SCORE)
         for (int t = t0; t < min(t0 + kRsBatch, T); t++) store_norm(x, t, H, score);
     float* lgs[kRsBatch];
     float* sps[kRsBatch];
@@ -490,15 +498,15 @@ __global__ __launch_bounds__(256) void token_norm_kernel(const uint16_t* __restr
     if (lane == 0) score[t] = n;
 }
 
-template <int TW, int NCH, int NW, int EB>
+template <int TW, int NCH, int NW>
 static int launch_route(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E,
                         int k, int renorm, int32_t* idx, float* w, float* probs, float* score, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((T + TW - 1) / TW);
     const size_t smem = (size_t)TW * ((size_t)E + (size_t)k) * sizeof(float);      // up to 8 KiB a token
-    dymoe_launch(ctx, DYMOE_K_ROUTE, (route_kernel<TW, NCH, NW, EB>), dim3(blocks), dim3(NW * kWave), smem, st,
-                       (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm, idx, w,
-                       probs, score);
+    dymoe_launch(ctx, DYMOE_K_ROUTE, (score ? route_kernel<TW, NCH, NW, true> : route_kernel<TW, NCH, NW, false>),
+                 dim3(blocks), dim3(NW * kWave), smem, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm, idx, w,
+                 probs, score);
     DYMOE_HIP_LAUNCH_CHECK();
     return DYMOE_OK;
 }
@@ -509,9 +517,10 @@ constexpr size_t kRouteMfmaMaxLds = 128 * 1024;
 // the default limit (operand tiles, two partial tiles and the logits of 32 tokens).
 int route_init()
 {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&route_mfma_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kRouteMfmaMaxLds) != hipSuccess)
-        return DYMOE_EHIP;
+    for (auto kernel : {&route_mfma_kernel<false>, &route_mfma_kernel<true>})
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kRouteMfmaMaxLds) != hipSuccess)
+            return DYMOE_EHIP;
     return DYMOE_OK;
 }
 
@@ -531,41 +540,37 @@ int route_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bia
                      dim3(kRlThreads), 0, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, probs);
         DYMOE_HIP_LAUNCH_CHECK();
         const int per_wg = kRsWaves * kRsBatch;
-        dymoe_launch(ctx, DYMOE_K_ROUTE_SELECT, route_select_kernel, dim3((unsigned)((T + per_wg - 1) / per_wg)),
-                     dim3(kRsThreads), select_lds, st, T, E, k, renorm, idx, w, probs, (const uint16_t*)x, H, score);
+        dymoe_launch(ctx, DYMOE_K_ROUTE_SELECT, (score ? route_select_kernel<true> : route_select_kernel<false>),
+                     dim3((unsigned)((T + per_wg - 1) / per_wg)), dim3(kRsThreads), select_lds, st, T, E, k, renorm, idx, w, probs, (const uint16_t*)x, H, score);
         DYMOE_HIP_LAUNCH_CHECK();
         return DYMOE_OK;
     }
     if (T >= 128 && E >= 32 && H % 128 == 0 && mfma_lds <= kRouteMfmaMaxLds) {
-        dymoe_launch(ctx, DYMOE_K_ROUTE, route_mfma_kernel, dim3((unsigned)((T + kRmTokens - 1) / kRmTokens)),
-                     dim3(kRmThreads), mfma_lds, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm,
+        dymoe_launch(ctx, DYMOE_K_ROUTE, (score ? route_mfma_kernel<true> : route_mfma_kernel<false>),
+                     dim3((unsigned)((T + kRmTokens - 1) / kRmTokens)), dim3(kRmThreads), mfma_lds, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm,
                      idx, w, probs, score);
         DYMOE_HIP_LAUNCH_CHECK();
         return DYMOE_OK;
     }
     // tokens per workgroup chosen so that their activations fit in 128 VGPRs;
-    // few tokens: one per workgroup, its experts spread over 8 wavefronts
-#define DYMOE_ROUTE(TW_, NCH_, NW_, EB_) \
-    return launch_route<TW_, NCH_, NW_, EB_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, score, st)
-    if (H <= 4096 && T >= 1024) DYMOE_ROUTE(4, 8, 4, 1);
-    // One token per workgroup: few rounds to memory (16 wavefronts from 17 experts on, unless the tokens alone keep more than
-    // a workgroup on every compute unit; registers for the row lengths there are), and no row requested twice.  us, before
-    // (8 wavefronts of 128 registers for any row, two experts a round) / now: 61 tokens x 2048, 128 experts 17.2 / 11.0;
-    // 512 x 4096, 8 experts 8.7 / 6.8; 24 x 4096, 8 experts 6.7 / 5.2; 16 x 256, 8 experts 4.8 / 3.8.
-    const bool many = E > 16 && T <= ctx->num_cu;
+    // few tokens: one per workgroup, its experts spread over 8 or 16 wavefronts
+#define DYMOE_ROUTE(TW_, NCH_, NW_) return launch_route<TW_, NCH_, NW_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, score, st)
+    if (H <= 4096 && T >= 1024) DYMOE_ROUTE(4, 8, 4);
+    // One token per workgroup, registers for the row lengths there are.  16 wavefronts, so that each has few experts' rows to wait
+    // for, unless a wavefront has one or two anyway or the tokens alone keep more than a workgroup on every compute unit.
+    // us, 8 / 16 wavefronts: 40 tokens x 1024, 9 experts 3.55 / 3.30, 24 4.07 / 3.67, 100 8.2 / 6.0; 40 x 4096, 12 experts 4.23 /
+    // 4.41, 24 5.14 / 5.03; 300 x 1024, 24 experts 4.37 / 4.52, 1000 tokens 5.9 / 7.1.
+    const bool many = E > (H <= 2048 ? 8 : 16) && T <= ctx->num_cu;
     if (H <= 2048) {
-        if (many) DYMOE_ROUTE(1, 4, 16, 4);
-        if (E > 16) DYMOE_ROUTE(1, 4, 8, 4);
-        if (E > 8) DYMOE_ROUTE(1, 4, 8, 2);
-        DYMOE_ROUTE(1, 4, 8, 1);
+        if (many) DYMOE_ROUTE(1, 4, 16);
+        DYMOE_ROUTE(1, 4, 8);
     }
     if (H <= 4096) {
-        if (many) DYMOE_ROUTE(1, 8, 16, 2);
-        if (E > 8) DYMOE_ROUTE(1, 8, 8, 2);
-        DYMOE_ROUTE(1, 8, 8, 1);
+        if (many) DYMOE_ROUTE(1, 8, 16);
+        DYMOE_ROUTE(1, 8, 8);
     }
-    if (H <= 8192) DYMOE_ROUTE(1, 16, 8, 1);
-    DYMOE_ROUTE(1, 32, 8, 1);
+    if (H <= 8192) DYMOE_ROUTE(1, 16, 8);
+    DYMOE_ROUTE(1, 32, 8);
 #undef DYMOE_ROUTE
 }
 
