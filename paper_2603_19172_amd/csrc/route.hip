@@ -56,12 +56,9 @@ __device__ __forceinline__ void store_norm(const uint16_t* __restrict__ x, int t
 // A workgroup of NW wavefronts owns TW tokens: logits by all wavefronts, then
 // token tw is finished (softmax, top-k) by wavefront tw.  Few tokens: TW = 1 and
 // the experts spread over 8 or 16 wavefronts; many tokens: TW = NW = 4, so that a
-// router row is read once per four tokens.  A wavefront has one router row on
-// its way at a time: with two or four the registers cost wavefronts, and the
-// rows past the last expert are traffic (us, a row / two / four at a time: 40
-// tokens x 1024, 24 experts by 16 wavefronts 3.7 / 3.9 / 4.9; 1000 tokens x 1024,
-// 20 experts by 8 wavefronts 5.5 / 7.0 / 8.5; 300 x 4096, 20 experts 6.3 / 7.2).
-template <int TW, int NCH, int NW, bool SCORE>
+// router row is read once per four tokens.  A wavefront has EB router rows on
+// its way at a time.
+template <int TW, int NCH, int NW, int EB, bool SCORE>
 __global__ __launch_bounds__(NW* kWave) void route_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg,
     const float* __restrict__ bias, int T, int H, int E, int k, int renorm,
@@ -72,7 +69,7 @@ __global__ __launch_bounds__(NW* kWave) void route_kernel(
     float* logit = smem;                                  // [TW][E]
     float* selp = smem + (size_t)TW * E + (size_t)wave * k;   // [TW][k]: only the first TW wavefronts select
     const int t0 = blockIdx.x * TW;
-    route_logits<TW, NCH, NW, 1>(x, wg, bias, T, H, E, t0, logit);
+    route_logits<TW, NCH, NW, EB>(x, wg, bias, T, H, E, t0, logit);
     __syncthreads();
     if constexpr (SCORE) {                                // the tokens' norms, by the wavefronts that select last
         const int tw = (wave + NW - 1) % NW;
@@ -498,13 +495,13 @@ __global__ __launch_bounds__(256) void token_norm_kernel(const uint16_t* __restr
     if (lane == 0) score[t] = n;
 }
 
-template <int TW, int NCH, int NW>
+template <int TW, int NCH, int NW, int EB>
 static int launch_route(dymoe_ctx* ctx, const void* x, const void* wg, const float* bias, int T, int H, int E,
                         int k, int renorm, int32_t* idx, float* w, float* probs, float* score, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((T + TW - 1) / TW);
     const size_t smem = (size_t)TW * ((size_t)E + (size_t)k) * sizeof(float);      // up to 8 KiB a token
-    dymoe_launch(ctx, DYMOE_K_ROUTE, (score ? route_kernel<TW, NCH, NW, true> : route_kernel<TW, NCH, NW, false>),
+    dymoe_launch(ctx, DYMOE_K_ROUTE, (score ? route_kernel<TW, NCH, NW, EB, true> : route_kernel<TW, NCH, NW, EB, false>),
                  dim3(blocks), dim3(NW * kWave), smem, st, (const uint16_t*)x, (const uint16_t*)wg, bias, T, H, E, k, renorm, idx, w,
                  probs, score);
     DYMOE_HIP_LAUNCH_CHECK();
@@ -554,23 +551,34 @@ int route_launch(dymoe_ctx* ctx, const void* x, const void* wg, const float* bia
     }
     // tokens per workgroup chosen so that their activations fit in 128 VGPRs;
     // few tokens: one per workgroup, its experts spread over 8 or 16 wavefronts
-#define DYMOE_ROUTE(TW_, NCH_, NW_) return launch_route<TW_, NCH_, NW_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, score, st)
-    if (H <= 4096 && T >= 1024) DYMOE_ROUTE(4, 8, 4);
-    // One token per workgroup, registers for the row lengths there are.  16 wavefronts, so that each has few experts' rows to wait
-    // for, unless a wavefront has one or two anyway or the tokens alone keep more than a workgroup on every compute unit.
-    // us, 8 / 16 wavefronts: 40 tokens x 1024, 9 experts 3.55 / 3.30, 24 4.07 / 3.67, 100 8.2 / 6.0; 40 x 4096, 12 experts 4.23 /
-    // 4.41, 24 5.14 / 5.03; 300 x 1024, 24 experts 4.37 / 4.52, 1000 tokens 5.9 / 7.1.
+#define DYMOE_ROUTE(TW_, NCH_, NW_, EB_) \
+    return launch_route<TW_, NCH_, NW_, EB_>(ctx, x, wg, bias, T, H, E, k, renorm, idx, w, probs, score, st)
+    if (H <= 4096 && T >= 1024) DYMOE_ROUTE(4, 8, 4, 1);
+    // One token per workgroup, registers for the row lengths there are.
+    // 16 wavefronts, so that each has few experts' rows to wait for, unless it has one or two anyway or the tokens alone keep
+    // more than a workgroup on every compute unit.  us, router in the caches, 8 / 16 wavefronts: 40 tokens x 1024, 9 experts 3.55 /
+    // 3.30, 24 4.07 / 3.67, 100 8.2 / 6.0; 40 x 4096, 12 experts 4.23 / 4.41, 24 5.14 / 5.03; 300 x 1024, 24 experts 4.37 / 4.52,
+    // 1000 tokens 5.9 / 7.1.
+    // A row at a time: with two or four the registers cost wavefronts, and the rows past the last expert are traffic (a row / two /
+    // four at a time: 40 x 1024, 24 experts 3.7 / 3.9 / 4.9; 1000 x 1024, 20 experts by 8 wavefronts 5.5 / 7.0 / 8.5).  Except for
+    // many experts with short rows, which are so many trips to memory (us, router not in the caches: 40 x 1024, 64 experts 6.6 /
+    // 6.4 / 6.6, 100 8.6 / 8.0 / 9.0, 256 16.0 / 14.3 / 13.5; 40 x 2048, 100 9.6 / 10.1 / 12.0, 256 18.7 / 18.6 / 19.8; 40 x 1024 by
+    // 8 wavefronts, 48 7.8 / 7.2 / 7.7, 128 15.4 / 13.4 / 12.2; 40 x 4096 by 16, 256 32.8 / 32.2).
     const bool many = E > (H <= 2048 ? 8 : 16) && T <= ctx->num_cu;
     if (H <= 2048) {
-        if (many) DYMOE_ROUTE(1, 4, 16);
-        DYMOE_ROUTE(1, 4, 8);
+        if (many && E > 128 && H <= 1024) DYMOE_ROUTE(1, 4, 16, 4);
+        if (many && E > (H <= 1024 ? 48 : 64)) DYMOE_ROUTE(1, 4, 16, 2);
+        if (many) DYMOE_ROUTE(1, 4, 16, 1);
+        if (E > 32) DYMOE_ROUTE(1, 4, 8, 4);
+        DYMOE_ROUTE(1, 4, 8, 1);
     }
     if (H <= 4096) {
-        if (many) DYMOE_ROUTE(1, 8, 16);
-        DYMOE_ROUTE(1, 8, 8);
+        if (many) DYMOE_ROUTE(1, 8, 16, 1);
+        if (E > 32) DYMOE_ROUTE(1, 8, 8, 2);
+        DYMOE_ROUTE(1, 8, 8, 1);
     }
-    if (H <= 8192) DYMOE_ROUTE(1, 16, 8);
-    DYMOE_ROUTE(1, 32, 8);
+    if (H <= 8192) DYMOE_ROUTE(1, 16, 8, 1);
+    DYMOE_ROUTE(1, 32, 8, 1);
 #undef DYMOE_ROUTE
 }
 

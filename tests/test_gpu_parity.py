@@ -228,11 +228,12 @@ def test_route_topk_many_experts_multi_token_wavefronts(ctx):
         _check_route(ctx, x, wg, None, 2)
 
 
-# a token per workgroup: rows up to 2048 / 4096 columns and beyond, one or several experts of a wavefront one after the other, 8 or 16
+# a token per workgroup: rows up to 2048 / 4096 columns and beyond, one, two or four of a wavefront's experts at a time, 8 or 16
 # wavefronts (16 up to as many tokens as compute units), remainders of experts in the last round
 @pytest.mark.parametrize("T,H,E,k", [(5, 2048, 8, 2), (5, 2048, 9, 3), (6, 2040, 17, 2), (7, 2056, 8, 2), (7, 2056, 9, 2),
                                      (9, 4096, 33, 6), (9, 4104, 33, 2), (61, 2048, 130, 8), (127, 1024, 100, 5), (256, 512, 30, 4),
-                                     (257, 512, 30, 4), (257, 2304, 30, 4), (1025, 264, 17, 2)])
+                                     (257, 512, 30, 4), (257, 2304, 30, 4), (1025, 264, 17, 2),
+                                     (12, 512, 60, 4), (40, 1024, 250, 6), (300, 1000, 70, 3), (257, 2056, 70, 3)])
 def test_route_topk_one_token_per_workgroup(ctx, T, H, E, k):
     c = synth.scaled(synth.CONFIGS["fine_grained"], config_id=17 + T, T=T, E=E, H=H, k=k)
     x, _ = synth.activations(c)
