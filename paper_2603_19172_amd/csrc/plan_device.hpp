@@ -130,32 +130,34 @@ struct SplitRule {
 };
 constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the tile counts
 
-// Tiles of one fragment stream weights of different widths: one and a half rounds of workgroups level them out (24 tokens of
-// the Mixtral shape, 8 tiles x 16 blocks: GEMM and combine 87 us with 2 splits, 86 with 4, 73 with 5, 67 with 6, 69 with 8).
-// Tiles of more rows keep the matrix cores busy, and their workgroups last about the same: in units of a round of two
-// unsplit workgroups per compute unit, a launch takes 0.6 / s where each has a unit of its own, 1 / s up to one round and
-// (rounds + 0.3) / s beyond, and every split writes and reads a slab, 0.0147 blocks / n_kt (a copy's rate against the matrix
-// cores').  us, GEMM and combine: 512 tokens of the Mixtral shape (9 x 16) 1 split 328, 2 209, 3 170, 4 189, 6 180; 433
-// tokens x 4 of 2048 x 6272 (16 x 8) 101, 68, 77, 73; 580 x 4 of 896 x 2560 (20 x 4) 59, 39, 34; 315 x 2 of 1792 x 3584
-// (16 x 7) 40, 29, 31.  (The 0.6 lies between what these
-// say: 512 tokens of the Mixtral shape in 8 x 16 blocks, tall int4 and int2 tiles among them, 0.68 (2 splits 181, 4 138); 433
-// x 4 0.5.)  The kernel for tiles of one fragment splits K over its wavefronts already: no more than 24 K-tiles per
-// split, so that a bf16 expert's workgroups do not outlast the launch (80 tokens of 512 x 4864: 25.4 us with 38, 21.3 with 19).
-// By one wavefront, a lane per number (max <= 64); the least cost, the smaller number of equals.
-__device__ __forceinline__ void plan_splits(int tiles, int pairs, const SplitRule& r, const PlanPtrs& pp)
+// In units of a round of two unsplit workgroups per compute unit, n workgroups per compute unit of 1 / s of the K-tiles each take
+// 0.7 / s up to one (each has a unit to itself), (0.67 + 0.2 n) / s up to two (one round) and (0.25 + 0.5 n) / s beyond; every
+// split writes and reads a slab, 0.011 (0.4 + rows per tile / 128) per workgroup and K-tile.  Over 437 layers of 5 to 2100
+// tokens with a choice, every number timed, GEMM and combine are 1.0 % off the best on average, 12 of them more than 10 %
+// (always 3 num_cu / blocks splits for tiles of one fragment, else 0.6 / 1 / 0.3 + 0.5 n and 0.0147 whatever the rows: 1.8 %, 31 of
+// them).  us: 512 tokens of the Mixtral shape (8 tiles x 16 blocks) 2 splits 181, 4 138 (9 x 16: 1 328, 2 209, 3 170, 4 189); 172 x 6
+// of 3328 x 3072 (17 x 13) 1 74, 2 54; 1743 x 2 of 768 x 5120 (31 x 3) 1 101, 2 62, 3 56, 4 51, 5 50, 6 53; 187 x 2 of 512 x 7168
+// (63 x 2, one fragment) 4 32, 6 38.
+// With a 16-bit expert among tiles of one fragment, which stream weights of very different widths, one and a half rounds of
+// workgroups level them out (24 tokens of the Mixtral shape, 8 x 16: 2 splits 87, 4 86, 5 73, 6 67, 8 69).
+// The kernel for tiles of one fragment splits K over its wavefronts already: no more than 24 K-tiles per split, so that a bf16
+// expert's workgroups do not outlast the launch (80 tokens of 512 x 4864: 25.4 us with 38, 21.3 with 19).
+// By one wavefront, a lane per number (max <= 64); the least cost, the smaller number of equals.  wide: tiles of 16-bit experts.
+__device__ __forceinline__ void plan_splits(int tiles, int pairs, bool wide, const SplitRule& r, const PlanPtrs& pp)
 {
     const int lane = threadIdx.x & (kWave - 1), s = lane + 1;
     const int blocks = max(1, r.nblk * tiles);
     int best = 1;
     if (r.max > 1) {
-        if (r.small || pairs <= 32 * tiles) {
+        if (r.small || (wide && pairs <= 32 * tiles)) {
             best = 3 * r.num_cu / blocks;
             if (r.small) best = max(best, (r.n_kt + 12) / 24);
             best = max(1, min(r.max, best));
         } else {
-            const int n = blocks * s;
-            const float rounds = n <= r.num_cu ? 0.6f : n <= 2 * r.num_cu ? 1.0f : 0.5f * (float)n / (float)r.num_cu + 0.3f;
-            const float cost = s <= r.max ? rounds / (float)s + 0.0147f * (float)blocks * (float)s / (float)r.n_kt : 1e30f;
+            const float per_cu = (float)(blocks * s) / (float)r.num_cu;
+            const float rounds = per_cu <= 1.0f ? 0.7f : per_cu <= 2.0f ? 0.67f + 0.2f * per_cu : 0.25f + 0.5f * per_cu;
+            const float slab = 0.011f * (0.4f + (float)pairs / (128.0f * (float)max(1, tiles)));
+            const float cost = s <= r.max ? rounds / (float)s + slab * (float)blocks * (float)s / (float)r.n_kt : 1e30f;
             best = __ffsll((long long)__ballot(cost == -wave_max_dpp(-cost)));
         }
     }
@@ -193,8 +195,11 @@ __device__ __forceinline__ void plan_scan(int E, int tile_m, const int32_t* s_co
             pp.ntiles[2] = with_tiles;      // experts with at least one tile (the GEMM launches pick their XCD mapping by it)
         }
     }
+    bool wide = false;                          // (meanwhile)
+    if (wave == kPlanWaves - 1)
+        for (int e = tid & (kWave - 1); e < E; e += kWave) wide |= s_count[e] > 0 && s_bits[e] == 16;
     __syncthreads();
-    if (wave == kPlanWaves - 1) plan_splits(s_tile0[E], s_off[E], splits, pp);
+    if (wave == kPlanWaves - 1) plan_splits(s_tile0[E], s_off[E], __any(wide), splits, pp);
 }
 
 // Cost key of a tile, roughly the time a workgroup spends on it: streaming (bf16) or dequantising (int4, int2) the weights
