@@ -1089,27 +1089,34 @@ bool ffn_gemm_fits(int T, int H, int F, int E, int k)
 // The intermediate takes half of its area (16-bit values where the other path has fp32): the slabs start behind it.
 static size_t slabs_offset(int T, int F, int k, const FfnLayout& L) { return L.hbuf + round256((size_t)T * k * F * 2); }
 
-// Whether the first GEMM takes gemm_small_kernel: tiles of one fragment, and no more workgroups than are resident together; more
-// of them pay a workgroup's start (plan -> expert -> pointers -> first rows, 3 us) once per round.  us, large / small: 7 tokens
-// x 6 of 16 experts, 1024 x 512 (256 workgroups) 9.7 / 5.9; 10 x 4 of 60, 1280 x 256 (240) 12.2 / 6.6; but 6 x 8 of 8, 1664 x
-// 3968 (992) 14.4 / 16.8 and 80 x 2 of 64, 512 x 4864 (9100) 39 / 52.
-static bool small_first(const dymoe_ctx* ctx, int T, int F, int E, int k)
+// Whether a GEMM of blocks x tiles workgroups takes gemm_small_kernel, tiles of one fragment given.  Two things cost it its lead:
+// rounds, since every workgroup starts with a chain of dependent loads (plan -> expert -> pointers -> first rows, 3 us), and
+// token rows, which every wavefront reads for itself where the other kernel shares them through LDS (32 rows of K are as many bytes
+// as the int4 weights of a workgroup).  Up to a workgroup per compute unit it is ahead with any number of rows, up to two with
+// two thirds of a fragment, beyond with a few.  Time of the small kernel over the large one's, 720 layers of 4 to 16 experts, by
+// workgroups and pairs per expert:
+//   first GEMM   4-8   8-12  12-17  17-25  25-32        second GEMM   4-8   8-12  12-17  17-25  25-32
+//       256     0.66   0.67   0.68   0.73   0.80          up to 255  0.81   0.83   0.85   0.89   0.97
+//       512     0.84   0.87   0.90   0.93   1.10           384-511   0.88   0.89   0.92   0.98   1.08
+//       768     0.97   1.04   1.06   1.17   1.32               768   0.99   1.02   1.05   1.11   1.22
+// (One pair or two per expert, second GEMM of 1280 workgroups: 0.96.)
+static bool small_ahead(const dymoe_ctx* ctx, int T, int E, int k, long blocks, long most_rounds, long few)
 {
-    const long P = (long)T * k, tiles = E < P ? E : P;
-    return ffn_tile_rows(T, E, k) == kGemmTileSmall && (F / 32) * tiles <= 3L * ctx->num_cu;
+    const long P = (long)T * k, tiles = E < P ? E : P, wgs = blocks * tiles, cu = ctx->num_cu;
+    if (ffn_tile_rows(T, E, k) != kGemmTileSmall) return false;
+    return wgs <= cu || (wgs <= 2 * cu && P <= 20 * tiles) || (wgs <= most_rounds * cu && P <= few * tiles);
 }
+static bool small_first(const dymoe_ctx* ctx, int T, int F, int E, int k) { return small_ahead(ctx, T, E, k, F / 32, 3, 6); }
 
-// The second GEMM, which splits K as well: up to five rounds' worth of a workgroup per compute unit; not where a few experts'
-// long rows give the other kernel one and a half rounds of splits, since there the bf16 expert's workgroups are what the launch
-// waits for and a shorter chain does not help.  us, large / small: 33 tokens x 1 of 8, 384 x 2048 7.5 / 5.0; 25 x 1 of 128,
-// 1024 x 1408 15.8 / 10.1; 48 x 1 of 30, 2688 x 5504 57 / 49; 80 x 2 of 64, 512 x 4864 22.5 / 21.3; but 29 x 2 of 8, 2048 x 5248
-// 13.4 / 15.1, 24 x 2 of 8, 4096 x 14336 61 / 66 and 94 x 8 of 128, 1152 x 1152 (2300 workgroups) 23.8 / 27.5.
+// The second GEMM splits K as well.  Not where a few experts' long rows give the other kernel one and a half rounds of splits: there
+// the bf16 expert's workgroups are what the launch waits for and a shorter chain does not help (us, large / small: 29 tokens x 2
+// of 8, 2048 x 5248 13.4 / 15.1, 24 x 2 of 8, 4096 x 14336 61 / 66).
 static bool small_second(const dymoe_ctx* ctx, int T, int H, int F, int E, int k)
 {
     const long P = (long)T * k, tiles = E < P ? E : P;
     const long nblk = (H + 64 * kGmWaves - 1) / (64 * kGmWaves);
     if (tiles <= 16 && F >= 24 * kBK && 8 * nblk * tiles >= 3L * ctx->num_cu / 2) return false;
-    return ffn_tile_rows(T, E, k) == kGemmTileSmall && (H / 64) * tiles <= 5L * ctx->num_cu;
+    return small_ahead(ctx, T, E, k, H / 64, 5, 8);
 }
 
 SplitRule split_rule(const dymoe_ctx* ctx, int T, int H, int F, int E, int k, const FfnLayout& L)

@@ -1335,9 +1335,11 @@ def test_decode_with_a_token_that_is_routed_nowhere(ctx, T, H, E, k, chained):
 
 
 # tiles of one fragment (up to 32 tokens, or up to 128 and eight pairs per expert): every format, expert loads around 32 rows, K-tiles
-# that the four wavefronts share unevenly or that are fewer than they, several splits, the larger kernel on the same tiles
+# that the four wavefronts share unevenly or that are fewer than they, several splits, the larger kernel on the same tiles, pairs per
+# expert on both sides of the lines between the two kernels
 @pytest.mark.parametrize("T,H,F,E,k", [(5, 128, 128, 5, 2), (32, 256, 1152, 5, 5), (31, 384, 2048, 8, 1), (33, 128, 256, 8, 1),
-                                       (77, 640, 384, 40, 4), (128, 128, 640, 128, 8), (17, 2048, 4224, 8, 2), (9, 1280, 6272, 5, 3)])
+                                       (77, 640, 384, 40, 4), (128, 128, 640, 128, 8), (17, 2048, 4224, 8, 2), (9, 1280, 6272, 5, 3),
+                                       (12, 512, 3072, 8, 4), (13, 512, 3072, 8, 4), (32, 256, 2048, 8, 5), (32, 256, 2048, 8, 6)])
 def test_ffn_gemm_one_fragment_tiles(ctx, T, H, F, E, k):
     cfg = synth.scaled(synth.CONFIGS["tiny"], config_id=700 + T, T=T, H=H, F=F, E=E, k=k, tier_count=(E,))
     x, _ = synth.activations(cfg)
