@@ -1130,9 +1130,12 @@ SplitRule split_rule(const dymoe_ctx* ctx, int T, int H, int F, int E, int k, co
     long most = (long)((L.xh - slabs_offset(T, F, k, L)) / ((size_t)P * H * 4));        // slabs the workspace holds
     const int least = r.small ? 2 * kSmWaves * kBK : 2 * kBK;                           // two K-tiles per chain at least
     if (most > F / least) most = F / least;
-    // no more workgroups than 4 per compute unit if every expert has tokens (every one of them has a tile, and P / 128 more at most)
+    // no more workgroups than 4 per compute unit if every expert has tokens (every one of them has a tile, and P / 128 more at most),
+    // unless the small kernel's chains get too long (22 tokens x 4 of 30, 2048 x 4736: one split of 37 K-tiles 43.4 us, two 33.4)
     const long blocks = r.nblk * ((E < P ? E : P) + P / (2 * kGemmTileM));
-    if (most > 4L * r.num_cu / blocks) most = 4L * r.num_cu / blocks;
+    long room = 4L * r.num_cu / blocks;
+    if (r.small && room < split_chains(r.n_kt)) room = split_chains(r.n_kt);
+    if (most > room) most = room;
     r.max = (int)(most > 8 ? 8 : most < 1 ? 1 : most);
     return r;
 }

@@ -130,6 +130,8 @@ struct SplitRule {
 };
 constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the tile counts
 
+__host__ __device__ inline int split_chains(int n_kt) { return (n_kt + 12) / 24; }
+
 // In units of a round of two unsplit workgroups per compute unit, n workgroups per compute unit of 1 / s of the K-tiles each take
 // 0.7 / s up to one (each has a unit to itself), (0.67 + 0.2 n) / s up to two (one round) and (0.25 + 0.5 n) / s beyond; every
 // split writes and reads a slab, 0.011 (0.4 + rows per tile / 128) per workgroup and K-tile.  Over 437 layers of 5 to 2100
@@ -140,8 +142,8 @@ constexpr int kPlanSplits = 3;         // where the plan keeps it, behind the ti
 // (63 x 2, one fragment) 4 32, 6 38.
 // With a 16-bit expert among tiles of one fragment, which stream weights of very different widths, one and a half rounds of
 // workgroups level them out (24 tokens of the Mixtral shape, 8 x 16: 2 splits 87, 4 86, 5 73, 6 67, 8 69).
-// The kernel for tiles of one fragment splits K over its wavefronts already: no more than 24 K-tiles per split, so that a bf16
-// expert's workgroups do not outlast the launch (80 tokens of 512 x 4864: 25.4 us with 38, 21.3 with 19).
+// The kernel for tiles of one fragment splits K over its wavefronts already: about 24 K-tiles per split at most (split_chains), so
+// that a bf16 expert's workgroups do not outlast the launch (80 tokens of 512 x 4864: 25.4 us with 38, 21.3 with 19).
 // By one wavefront, a lane per number (max <= 64); the least cost, the smaller number of equals.  wide: tiles of 16-bit experts.
 __device__ __forceinline__ void plan_splits(int tiles, int pairs, bool wide, const SplitRule& r, const PlanPtrs& pp)
 {
@@ -151,7 +153,7 @@ __device__ __forceinline__ void plan_splits(int tiles, int pairs, bool wide, con
     if (r.max > 1) {
         if (r.small || (wide && pairs <= 32 * tiles)) {
             best = 3 * r.num_cu / blocks;
-            if (r.small) best = max(best, (r.n_kt + 12) / 24);
+            if (r.small) best = max(best, split_chains(r.n_kt));
             best = max(1, min(r.max, best));
         } else {
             const float per_cu = (float)(blocks * s) / (float)r.num_cu;
