@@ -943,21 +943,33 @@ bool decode_fused_fits(int T, int H, int E, int k)
     return T >= 1 && T <= kFusedMaxTokens && E <= 64 && k <= kFusedMaxK && H % 64 == 0 && H <= 4 * kSeg;
 }
 
+// The logits of a launch of their own wait in the workspace's part area, P * H floats at least.
+static bool logits_have_room(int H, int E, int k) { return (size_t)E <= (size_t)k * H; }
+
 // Where the logits come from: a launch of their own (3 us) unless a workgroup has all the router rows it needs in one trip to
 // memory (4 wavefronts, two rows each up to 4096 columns): every further trip costs every workgroup of the first phase 2 to 3
 // us.  us a step, in the workgroups / apart: 8 experts x 4096, one token 15.2 / 16.5, four 32.0 / 30.8; 16 x 4096 20.5 / 19.4;
-// 30 x 2048 18.3 / 15.4; 60 x 512 21.7 / 14.0; 64 x 1024, four tokens 71.9 / 38.5.  They wait in the workspace's part area,
-// P * H floats at least.
-static bool fused_logits_apart(int T, int H, int E, int k)
+// 30 x 2048 18.3 / 15.4; 60 x 512 21.7 / 14.0; 64 x 1024, four tokens 71.9 / 38.5.
+// With no more workgroups than compute units, nothing waits for a workgroup's trips but itself, and from 2049 columns on the
+// launch of few workgroups that makes the logits is no faster: a trip per token there (two for one token, or for rows of 6144
+// columns on) stays in the workgroups.  In / apart, up to a workgroup per compute unit: 2 tokens x 4 experts x 8192 21.4 / 23.9, 4 x 2
+// 26.5 / 31.4, 1 x 8 x 6144 20.2 / 20.9, 2 x 6 x 4096 18.5 / 19.2; but 1 x 9 x 6144 the same, 2 x 6 x 4160 the same, 4 x 6 x 4160 -1.5,
+// 2 x 10 x 4096 -1.5, 4 x 4 x 2048 -1.4; above: 4 x 2 x 8192 -1.2, 2 x 4 x 6144 -2.2, 1 x 8 x 4160 -2.7.
+static bool fused_logits_apart(const dymoe_ctx* ctx, int T, int H, int F, int E, int k)
 {
-    return (long)T * E > (H <= 2 * kSeg ? 2 * kGvWaves : kGvWaves) && (size_t)E <= (size_t)k * H;
+    const int trip = H <= 2 * kSeg ? 2 * kGvWaves : kGvWaves;
+    if (!logits_have_room(H, E, k) || (long)T * E <= trip) return false;
+    const int rows = phase1_rows_per_block((long)F * T * k);
+    const long workgroups = (long)((F + rows - 1) / rows) * T * k;
+    if (workgroups > ctx->num_cu || H <= kSeg) return true;
+    return !(E <= trip || (E <= 2 * kGvWaves && (T == 1 || H >= 3 * kSeg)));
 }
 
 // ... and the decode layer: up to kFusedMaxE experts, and one token behind the layer before's residual
 bool decode_layer_fits(int T, int H, int E, int k, bool residual)
 {
     if (T < 1 || T > (residual ? 1 : kFusedMaxTokens) || E > kFusedMaxE || k > kFusedMaxK || H % 64 != 0 || H > 4 * kSeg) return false;
-    return E <= 64 || fused_logits_apart(T, H, E, k);
+    return E <= 64 || logits_have_room(H, E, k);
 }
 
 int front_logits_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
@@ -994,7 +1006,7 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
         }
     };
     if (nseg1 > 4) return DYMOE_ENOTSUP;
-    if (fused_logits_apart(T, H, E, k)) {
+    if (fused_logits_apart(ctx, T, H, F, E, k)) {
         float* logits = reinterpret_cast<float*>((char*)workspace + L.part);
         const int rc = front_logits_launch(ctx, x, y_prev, alpha, h_out, wg, bias, T, H, E, logits, st);
         if (rc != DYMOE_OK) return rc;
