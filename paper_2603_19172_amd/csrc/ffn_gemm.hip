@@ -1072,14 +1072,15 @@ int ffn_gemm_init()
     return DYMOE_OK;
 }
 
-// Limits of the launch shapes below, checked by the entry point before anything is enqueued: the tile index is a
-// grid's y dimension, and the token-tile copies address a row through an unsigned 32-bit byte offset.
+// Limits of the launch shapes below, checked by the entry point before anything is enqueued: tiles and workgroups, and the
+// token rows, which are addressed through an unsigned 32-bit byte offset.
 bool ffn_gemm_fits(int T, int H, int F, int E, int k)
 {
     const size_t P = (size_t)T * (size_t)k;
-    const size_t tiles = P / kGemmTileM + (size_t)E;
+    const size_t tiles = (size_t)ffn_most_tiles(T, E, k);
     if (tiles > 65535) return false;
-    // both launches are one-dimensional: 8 * column blocks * ceil(units / 8) workgroups, units <= 8 * tiles
+    // every launch is one-dimensional, 8 * column blocks * ceil(units / 8) workgroups at most, and units are more than tiles only
+    // while they are no more than four per compute unit (split_rule)
     const size_t nblk = ((size_t)(F > H ? F : H) + 32 * kGmWaves - 1) / (32 * kGmWaves);
     if (8 * nblk * (tiles + 1) >= ((size_t)1 << 31)) return false;
     if ((size_t)T * H * 2 >= ((size_t)1 << 32) || P * (size_t)F * 2 >= ((size_t)1 << 32)) return false;
@@ -1167,7 +1168,7 @@ int ffn_gemm_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     // what the kernels after the plan take as the bit widths: the plan's copy, 0 where the table lacks the format
     const uint8_t* run_bits = reinterpret_cast<const uint8_t*>(plan_ptrs(plan, E, P).cursor);
     constexpr size_t kLdsBytes = kGemmLdsBytes;
-    const int max_tiles = P / ffn_tile_rows(T, E, k) + E;
+    const int max_tiles = ffn_most_tiles(T, E, k);
     if (small_first(ctx, T, F, E, k)) {
         dymoe_launch(ctx, DYMOE_K_GEMM1, (gemm_small_kernel<1>), dim3((unsigned)((F / 32) * max_tiles)), dim3(kSmThreads), 0, st, xb, xh4,
                      xh2, xh8, (const uint16_t*)nullptr, run_bits, table, plan, P, E, k, H, F, hbuf, (float*)nullptr, max_tiles);

@@ -19,6 +19,13 @@ static inline int ffn_tile_rows(int T, int E, int k)
     return (T <= 32 || (T <= 128 && (long)T * k <= 8L * E)) ? kGemmTileSmall : kGemmTileM;
 }
 
+// Tiles of T * k pairs at most: one of every expert with pairs is not whole.
+static inline int ffn_most_tiles(int T, int E, int k)
+{
+    const long P = (long)T * k;
+    return (int)(P / ffn_tile_rows(T, E, k) + (E < P ? E : P));
+}
+
 struct FfnLayout {
     size_t hbuf;    // [P,F] SwiGLU intermediate: fp32 (GEMV) or 16-bit (GEMM; the splits' output slabs start right behind it)
     size_t part;    // room for [P,H] fp32 per-pair outputs, one slab per split (the GEMV path keeps its partial sums on chip)
