@@ -396,7 +396,11 @@ int dymoe_pack_code_tiles(dymoe_ctx* ctx, const uint8_t* codes, const void* scal
  * GEMV path H <= 8192; GEMM path H, F multiples of 128; E <= DYMOE_MAX_EXPERTS.
  * Activations and the SwiGLU intermediate must stay inside fp16 range.
  * Every sum is taken in a fixed order (no atomics): the same inputs give the
- * same bits from launch to launch, on either path.
+ * same bits from launch to launch, on either path.  On the GEMM path that order
+ * belongs to the call, not to the token: the number of pieces that the down
+ * projection's contraction is cut into follows from the sizes and from how many
+ * row tiles the whole call's routing makes, so a token's result beside other
+ * tokens may differ in its last bits (fp32 sums of the same F products).
  */
 int dymoe_moe_ffn_mixed(dymoe_ctx* ctx, const void* x, const int32_t* idx, const float* w,
                         const uint8_t* bits, const dymoe_expert_fmt* table,
@@ -443,7 +447,7 @@ int dymoe_decode_layer(dymoe_ctx* ctx, const void* x, const float* y_prev, float
  * dymoe_rank_experts (prefill: by the row norms of x, left in token_score), dymoe_quantize_experts (quantize not 0; tile
  * layout) and dymoe_moe_ffn_mixed(path = DYMOE_PATH_GEMM), with their arguments, layouts, limits and errors; every output
  * (idx, w, probs, token_score, importance, load, bits, rank, the quantised formats, y) holds bit for bit what those calls
- * in turn write.  The norms come from the router's launch, and ranking, bit widths and the GEMM's token grouping are one
+ * in turn write (y with the call's own order of sums, see dymoe_moe_ffn_mixed).  The norms come from the router's launch, and ranking, bit widths and the GEMM's token grouping are one
  * launch.  probs and rank must not be NULL; token_score may be in the decode phase.
  * DYMOE_ENOTSUP outside E <= 256, T <= 8192, T * k <= 32768, k <= 256 and what the calls themselves cover: the caller then
  * makes the calls.

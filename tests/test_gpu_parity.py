@@ -1216,6 +1216,35 @@ def test_layer_step_declines_what_it_does_not_cover(ctx):
         assert int(layer.load.sum()) == T * k
 
 
+def test_ffn_gemm_result_of_a_token_beside_others(ctx):
+    """The K splits of the second GEMM follow from the tiles that the whole call makes: one token with the same expert and gate, beside
+    tokens spread over the experts and beside tokens of one expert, keeps its result up to the order of its fp32 sums."""
+    T, H, F, E = 1024, 2048, 4096, 16
+    g = torch.Generator(device=DEV).manual_seed(31)
+    x = torch.randn((T, H), generator=g, device=DEV).bfloat16()
+    w = [(torch.randn(s, generator=g, device=DEV) * 0.02).bfloat16() for s in ((F, H), (F, H), (H, F))]
+    table, keep = B.make_expert_table([{"w": w, "wt": [ctx.pack_tiles(m) for m in w]}] * E, DEV)
+    gate = torch.ones((T, 1), device=DEV)
+    bits = torch.full((E,), 16, dtype=torch.uint8, device=DEV)
+    spread = (torch.arange(T, device=DEV) % E).int()
+    crowd = torch.full((T,), 3, dtype=torch.int32, device=DEV)
+    crowd[0] = 0
+    ws = torch.empty((B.workspace_bytes(T, H, F, E, 1),), dtype=torch.uint8, device=DEV)
+    at = int(B.lib.dymoe_ffn_plan_offset(T, H, F, E, 1)) + 4 * (3 * E + 1)
+    got, splits = [], []
+    for idx in (spread, crowd, spread):
+        got.append(ctx.moe_ffn_mixed(x, idx[:, None].contiguous(), gate, bits, table, F, out_dtype=B.OUT_F32, path=B.PATH_GEMM, workspace=ws))
+        splits.append(int(ws[at:at + 16].view(torch.int32)[3]))
+    assert splits[0] != splits[1] and splits[0] == splits[2] and torch.equal(got[0], got[2])
+    # h is the same 16-bit row in both calls; F products summed in fp32 in two orders differ by at most 2 F 2^-24 of the sum of their
+    # magnitudes (the second 2: the reference's h is not rounded to 16 bits)
+    x0 = x[0].double()
+    h = torch.nn.functional.silu(w[0].double() @ x0) * (w[1].double() @ x0)
+    bound = 2 * 2 * F * 2.0 ** -24 * (w[2].double().abs() @ h.abs())
+    diff = (got[0][0].double() - got[1][0].double()).abs()
+    assert bool((diff <= bound).all())
+
+
 # a plan of 1024 tiles (a thread each) and of one more (laid out in memory): 1024 experts with the same weights, a few of them with
 # more pairs than a tile holds; every row is what one expert with all the tokens gives
 @pytest.mark.parametrize("more", [0, 1])
