@@ -408,7 +408,8 @@ int dymoe_moe_ffn_mixed(dymoe_ctx* ctx, const void* x, const int32_t* idx, const
                         void* y, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * A whole decode step on resident formats in two launches (three where a workgroup would go to the router several times): dymoe_decode_front
+ * A whole decode step on resident formats in two launches (three where a workgroup would go to the router several times, four where
+ * the first phase's workgroups besides are more than are resident together): dymoe_decode_front
  * (Sec. 4.2.2 Eq. 3 importance, Sec. 4.3 assignment) and dymoe_moe_ffn_mixed on its
  * GEMV path (Sec. 4.1: the executor on the mixed-precision weight set), with the
  * front end worked out by every workgroup of the FFN's first launch for itself

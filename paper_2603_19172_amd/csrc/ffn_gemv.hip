@@ -950,9 +950,10 @@ static bool logits_have_room(int H, int E, int k) { return (size_t)E <= (size_t)
 // memory (4 wavefronts, two rows each up to 4096 columns): every further trip costs every workgroup of the first phase 2 to 3
 // us.  us a step, in the workgroups / apart: 8 experts x 4096, one token 15.2 / 16.5, four 32.0 / 30.8; 16 x 4096 20.5 / 19.4;
 // 30 x 2048 18.3 / 15.4; 60 x 512 21.7 / 14.0; 64 x 1024, four tokens 71.9 / 38.5.
-// With no more workgroups than compute units, nothing waits for a workgroup's trips but itself, and from 2049 columns on the
-// launch of few workgroups that makes the logits is no faster: a trip per token there (two for one token, or for rows of 6144
-// columns on) stays in the workgroups.  In / apart, up to a workgroup per compute unit: 2 tokens x 4 experts x 8192 21.4 / 23.9, 4 x 2
+// With no more workgroups than compute units, nothing waits for a workgroup's trips but itself: two trips then cost what the launch
+// does (and the host a launch less, which is what small layers called one by one wait for: 2 tokens x 8 experts, 256 x 128, 13.8 /
+// 16.8 us a call), and from 2049 columns on the launch of few workgroups that makes the logits is no faster than a trip per token (two
+// for rows of 6144 columns on).  In / apart, up to a workgroup per compute unit: 2 tokens x 4 experts x 8192 21.4 / 23.9, 4 x 2
 // 26.5 / 31.4, 1 x 8 x 6144 20.2 / 20.9, 2 x 6 x 4096 18.5 / 19.2; but 1 x 9 x 6144 the same, 2 x 6 x 4160 the same, 4 x 6 x 4160 -1.5,
 // 2 x 10 x 4096 -1.5, 4 x 4 x 2048 -1.4; above: 4 x 2 x 8192 -1.2, 2 x 4 x 6144 -2.2, 1 x 8 x 4160 -2.7.
 static bool fused_logits_apart(const dymoe_ctx* ctx, int T, int H, int F, int E, int k)
@@ -961,8 +962,9 @@ static bool fused_logits_apart(const dymoe_ctx* ctx, int T, int H, int F, int E,
     if (!logits_have_room(H, E, k) || (long)T * E <= trip) return false;
     const int rows = phase1_rows_per_block((long)F * T * k);
     const long workgroups = (long)((F + rows - 1) / rows) * T * k;
-    if (workgroups > ctx->num_cu || H <= kSeg) return true;
-    return !(E <= trip || (E <= 2 * kGvWaves && (T == 1 || H >= 3 * kSeg)));
+    if (workgroups > ctx->num_cu) return true;
+    const int trips = (E + trip - 1) / trip;
+    return !(T * trips <= 2 || (H > kSeg && (trips == 1 || (trips == 2 && H >= 3 * kSeg))));
 }
 
 // ... and the decode layer: up to kFusedMaxE experts, and one token behind the layer before's residual
@@ -974,6 +976,8 @@ bool decode_layer_fits(int T, int H, int E, int k, bool residual)
 
 int front_logits_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
                         int T, int H, int E, float* logits, hipStream_t st);
+int front_finish_launch(dymoe_ctx* ctx, int T, int E, int k, int renorm, int32_t* idx, float* w, float* probs, const TierTable& tt,
+                        int floor_bits, float* importance, int32_t* load, uint8_t* bits, int32_t* rank, hipStream_t st);
 
 // y_prev not NULL: x is the layer before's input, y_prev its output, and the normalised row goes to h_out as well
 int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, float alpha, void* h_out, const void* wg, const float* bias,
@@ -1007,11 +1011,22 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
     };
     if (nseg1 > 4) return DYMOE_ENOTSUP;
     if (fused_logits_apart(ctx, T, H, F, E, k)) {
-        float* logits = reinterpret_cast<float*>((char*)workspace + L.part);
-        const int rc = front_logits_launch(ctx, x, y_prev, alpha, h_out, wg, bias, T, H, E, logits, st);
+        // More workgroups than are resident together (four, two or one per compute unit by the registers of 1, 2 or more segments)
+        // would do softmax, top-k and ranking once per round: then a launch does them, and the first phase is the stand-alone one.
+        // us a step, in every round / once: 4 tokens x 8 of 100 experts, 7360 x 192 (768 workgroups) 121 / 112, 4 x 8 of 8, 4096 x
+        // 4096 (2048) 236 / 208, 2 x 8 of 65, 6016 x 192 (384) 4.8 more; up to one round 2 to 4 less (4 x 8 of 128, 4096 x 192 (384)
+        // 3.3, 2048 x 768 (768) 3.6).
+        const bool once = (long)g1.x * g1.y > (nseg1 == 1 ? 4L : nseg1 == 2 ? 2L : 1L) * ctx->num_cu;
+        float* logits = (once && probs) ? probs : reinterpret_cast<float*>((char*)workspace + L.part);
+        int rc = front_logits_launch(ctx, x, y_prev, alpha, h_out, wg, bias, T, H, E, logits, st);
         if (rc != DYMOE_OK) return rc;
-        f.logits = logits;
         if (y_prev) f.x = (const uint16_t*)h_out;
+        if (once) {
+            rc = front_finish_launch(ctx, T, E, k, renorm, idx, w, logits, tt, floor_bits, importance, load, bits, rank, st);
+            if (rc != DYMOE_OK) return rc;
+            return ffn_gemv_launch(ctx, f.x, idx, w, bits, table, T, H, F, E, k, out_dtype, y, workspace, st);
+        }
+        f.logits = logits;
         if (E <= 64) by_width(std::integral_constant<int, 1>(), std::integral_constant<int, kFrontLogits>());
         else by_width(std::integral_constant<int, 2>(), std::integral_constant<int, kFrontLogits>());
     } else if (y_prev) {

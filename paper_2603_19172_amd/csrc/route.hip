@@ -484,6 +484,24 @@ __global__ __launch_bounds__(8 * kWave) void front_finish_kernel(
     assign_all<float>(8 * kWave, E, s_imp, s_load, tiers, floor_bits, bits, rank);
 }
 
+// probs: the logits, which become the probabilities
+int front_finish_launch(dymoe_ctx* ctx, int T, int E, int k, int renorm, int32_t* idx, float* w, float* probs, const TierTable& tt,
+                        int floor_bits, float* importance, int32_t* load, uint8_t* bits, int32_t* rank, hipStream_t st)
+{
+    const size_t smem = ((size_t)E + (size_t)k) * sizeof(float);
+    auto go = [&](auto kernel) {
+        dymoe_launch(ctx, DYMOE_K_DECODE_FRONT, kernel, dim3(1), dim3(8 * kWave), smem, st, T, E, k, renorm, idx, w, probs, tt, floor_bits,
+                     importance, load, bits, rank);
+    };
+    if (E <= 64) go(front_finish_kernel<1>);
+    else if (E <= 128) go(front_finish_kernel<2>);
+    else if (E <= 256) go(front_finish_kernel<4>);
+    else if (E <= 512) go(front_finish_kernel<8>);
+    else go(front_finish_kernel<16>);
+    DYMOE_HIP_LAUNCH_CHECK();
+    return DYMOE_OK;
+}
+
 // s_t = sqrt(sum_h x[t,h]^2), one wavefront per token
 __global__ __launch_bounds__(256) void token_norm_kernel(const uint16_t* __restrict__ x, int T,
                                                          int H, float* __restrict__ score)
@@ -623,17 +641,7 @@ int dymoe_decode_front(dymoe_ctx* ctx, const void* x, const void* wg, const floa
     if (probs && (size_t)E * (size_t)H * 2 >= ((size_t)256 << 10)) {
         const int rc = dymoe::front_logits_launch(ctx, x, nullptr, 0.0f, nullptr, wg, bias, T, H, E, probs, st);
         if (rc != DYMOE_OK) return rc;
-#define DYMOE_FINISH(NC_)                                                                                              \
-    dymoe_launch(ctx, DYMOE_K_DECODE_FRONT, (dymoe::front_finish_kernel<NC_>), dim3(1), dim3(8 * dymoe::kWave), smem, st, T, E, \
-                 k, renorm, idx, w, probs, tt, floor_bits, importance, load, bits, rank)
-        if (E <= 64) DYMOE_FINISH(1);
-        else if (E <= 128) DYMOE_FINISH(2);
-        else if (E <= 256) DYMOE_FINISH(4);
-        else if (E <= 512) DYMOE_FINISH(8);
-        else DYMOE_FINISH(16);
-#undef DYMOE_FINISH
-        DYMOE_HIP_LAUNCH_CHECK();
-        return DYMOE_OK;
+        return dymoe::front_finish_launch(ctx, T, E, k, renorm, idx, w, probs, tt, floor_bits, importance, load, bits, rank, st);
     }
 #define DYMOE_FRONT(NCH_, NC_)                                                                                          \
     dymoe_launch(ctx, DYMOE_K_DECODE_FRONT, (dymoe::decode_front_kernel<NCH_, NC_>), dim3(1), dim3(8 * dymoe::kWave), smem, st, \

@@ -1277,8 +1277,22 @@ def test_plan_with_long_tile_lists(ctx, more):
     (1, 256, 8, 2, 0, True), (1, 320, 9, 2, 4, True), (1, 2048, 63, 8, 0, True), (1, 2304, 128, 8, 0, True), (1, 64, 10, 2, 0, True),
     (1, 4096, 8, 2, 0, True), (1, 4160, 4, 2, 0, True), (1, 4160, 16, 4, 0, True), (1, 8192, 15, 2, 0, True)])
 def test_decode_layer_equals_the_separate_calls(ctx, T, H, E, k, floor, chained):
+    _decode_layer_against_the_separate_calls(ctx, T, H, 192, E, k, floor, chained)
+
+
+# more workgroups in the first phase than are resident together, rows of one, two and three segments: softmax, top-k and ranking in a
+# launch of their own; the same sizes with one workgroup row less, logits in the workgroups; with and without the probabilities
+@pytest.mark.parametrize("T,H,F,E,k,chained,probs", [
+    (4, 512, 2304, 65, 8, False, True), (4, 512, 2304, 64, 8, False, False), (4, 2112, 192, 60, 8, False, True),
+    (4, 2112, 128, 60, 8, False, True), (2, 4160, 192, 65, 8, False, False), (2, 4160, 128, 65, 8, False, True),
+    (1, 4160, 1024, 16, 8, True, True), (1, 4160, 1024, 100, 8, True, False), (1, 2112, 1088, 66, 8, True, True),
+    (2, 256, 128, 8, 1, False, True), (3, 256, 128, 8, 1, False, True), (1, 256, 128, 17, 2, True, True), (3, 3072, 64, 8, 2, False, False)])
+def test_decode_layer_by_workgroups(ctx, T, H, F, E, k, chained, probs):
+    _decode_layer_against_the_separate_calls(ctx, T, H, F, E, k, 0, chained, probs)
+
+
+def _decode_layer_against_the_separate_calls(ctx, T, H, F, E, k, floor, chained, probs=True):
     g = torch.Generator(device=DEV).manual_seed(H + E)
-    F = 192
     rnd = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.05).bfloat16()
     store = ExpertStore([[rnd(F, H), rnd(F, H), rnd(H, F)] for _ in range(E)], H, F, DEV, formats=(8, 4, 2))
     for b in (8, 4, 2):
@@ -1289,25 +1303,24 @@ def test_decode_layer_equals_the_separate_calls(ctx, T, H, E, k, floor, chained)
     la, lb = (MoELayer(ctx, T, H, F, E, k, "decode", counts, tbits, floor_bits=floor, out_dtype=B.OUT_F32, device=DEV) for _ in range(2))
     st = B._stream(None)
     la.ws.fill_(0xCC)
+    y_prev = torch.randn((T, H), generator=g, device=DEV) if chained else None
+    h_out, row = torch.zeros_like(x), torch.empty_like(x)
     if chained:
-        y_prev = torch.randn((T, H), generator=g, device=DEV)
-        h_out, row = torch.zeros_like(x), torch.empty_like(x)
         la.y.copy_(y_prev)                                                 # the step may overwrite the output it starts from
-        B._check(B.lib.dymoe_decode_layer(
-            ctx._h, x.data_ptr(), la.y.data_ptr(), 0.125, h_out.data_ptr(), wg.data_ptr(), bias.data_ptr(), 1, H, F, E, k, 1, 4,
-            ctypes.cast(la._tc, ctypes.c_void_p), ctypes.cast(la._tb, ctypes.c_void_p), floor, store.table.data_ptr(), 64, B.OUT_F32,
-            la.idx.data_ptr(), la.gate.data_ptr(), la.probs.data_ptr(), la.imp.data_ptr(), la.load.data_ptr(), la.bits.data_ptr(),
-            la.rank.data_ptr(), la.y.data_ptr(), la.ws.data_ptr(), la.ws_bytes, st), "dymoe_decode_layer")
+    B._check(B.lib.dymoe_decode_layer(
+        ctx._h, x.data_ptr(), la.y.data_ptr() if chained else None, 0.125, h_out.data_ptr() if chained else None, wg.data_ptr(),
+        bias.data_ptr(), T, H, F, E, k, 1, 4, ctypes.cast(la._tc, ctypes.c_void_p), ctypes.cast(la._tb, ctypes.c_void_p), floor,
+        store.table.data_ptr(), 64, B.OUT_F32, la.idx.data_ptr(), la.gate.data_ptr(), la.probs.data_ptr() if probs else None,
+        la.imp.data_ptr(), la.load.data_ptr(), la.bits.data_ptr(), la.rank.data_ptr(), la.y.data_ptr(), la.ws.data_ptr(), la.ws_bytes,
+        st), "dymoe_decode_layer")
+    if chained:
         B._check(B.lib.dymoe_residual_rmsnorm(ctx._h, x.data_ptr(), y_prev.data_ptr(), B.OUT_F32, 0.125, 1, H, row.data_ptr(), st), "norm")
         assert torch.equal(row, h_out)
         x = row
-    else:
-        assert la.decode_layer(x, wg, bias, store, st)
     lb.front(x, wg, bias, st)
     lb.ffn(x, store, st)
-    for u, v in zip((la.idx, la.gate, la.probs, la.imp, la.load, la.bits, la.rank, la.y),
-                    (lb.idx, lb.gate, lb.probs, lb.imp, lb.load, lb.bits, lb.rank, lb.y)):
-        assert torch.equal(u, v)
+    for name in ("idx", "gate", "imp", "load", "bits", "rank", "y") + (("probs",) if probs else ()):
+        assert torch.equal(getattr(la, name), getattr(lb, name)), name
 
 
 # a token whose row holds NaN is routed nowhere: no expert's load counts it, nothing beside the loads is touched, its output is zero;
