@@ -6,11 +6,11 @@ A step is one pass of the whole hot path over one batch: router gating + top-k
 the assignment sends to int4 / int2 -> dequant-fused SwiGLU expert FFN.
 
 Headline (`value`): tokens/s of that full step on the Mixtral-8x7B-shaped decode
-layer (batch 1, BASELINE configs[1]).  The same JSON line also carries, each under
+layer (batch 1: 4096 x 14336, 2 of 8 experts).  The same JSON line also carries, each under
 its own key: the FFN alone with the selected formats already resident and the two
 active experts forced to each pair of formats; the 512-token prefill of the same
-layer (configs[2]); the fine-grained 128-expert layer (configs[3]); the 32-layer
-decode stack with the experts in pinned host memory, 64 steps (configs[4]); the
+layer; the fine-grained layer (2048 tokens, 8 of 128 experts, 2048 x 768); the 32-layer
+decode stack with the experts in pinned host memory, 64 steps; the
 roofline of the dominant kernel of the timed step and of the two paths the targets
 are stated on (timed with HIP events attached to the dispatches by the library's
 per-kernel timers, over the same steps launched eagerly right after the timed
@@ -51,10 +51,10 @@ def main():
     ap.add_argument("--skip-prefill", action="store_true")
     ap.add_argument("--stack-steps", type=int, default=64,
                     help="decode steps through the 32-layer stack with the experts in pinned host memory "
-                         "(BASELINE configs[4] names 64); 0 skips the stack")
+                         "(the full workload is 64); 0 skips the stack")
     ap.add_argument("--stack-plans", default="literal,budget,paper",
                     help="which plans of the host-resident stack to run, each with look-ahead off and on: literal (bf16 "
-                         "travels and is quantised on arrival, as configs[4] words it), pools (the assigned format "
+                         "travels and is quantised on arrival), pools (the assigned format "
                          "travels, fixed pools per format), budget (the assigned format, one byte budget), paper "
                          "(4/2 tiers with the cosine depth schedule, one byte budget), paper-pools")
     ap.add_argument("--stack-warmup", type=int, default=1,
@@ -68,7 +68,7 @@ def main():
                          "int8, int4, int4+int2 and int2 (for a profiler run over the default workload: its extra "
                          "launches would blur the per-kernel averages)")
     ap.add_argument("--skip-fine-grained", action="store_true",
-                    help="skip the fine-grained layer (BASELINE configs[3]: 2048 tokens, 128 experts, top-8)")
+                    help="skip the fine-grained layer (2048 tokens, 128 experts, top-8)")
     ap.add_argument("--attention-long", action="store_true",
                     help="also time the attention-derived token score at 2048 and 8192 tokens (32 query / 8 key heads of "
                          "128), causal and not: the sizes its LDS-staged kernels serve")
@@ -331,7 +331,7 @@ def main():
         "warmup": args.warmup, "ms_per_step": round(ms_per_step, 5), "step_us": spread, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "bf16 weights/activations, int4+int2 codes, fp32 accumulate",
         "data": "synthetic",
-        "config": {"workload": "mixtral_decode (BASELINE configs[1]): H=4096 F=14336 E=8 top-2, 1 token, tiers 1 bf16 / 3 int4 / 4 int2, group 64",
+        "config": {"workload": "mixtral_decode: H=4096 F=14336 E=8 top-2, 1 token, tiers 1 bf16 / 3 int4 / 4 int2, group 64",
                    "active_experts": active, "active_bits": active_bits, "launch": launch_mode,
                    "us_per_step_by_launch_mode": launch_us,
                    "weight_copies_rotated": LAYER_COPIES, "setup_s": round(setup_s, 1)},
@@ -384,7 +384,7 @@ def main():
         ctx.timing_enable(())
         g_us = (pk["gemm1"][0] / max(pk["gemm1"][1], 1) + pk["gemm2"][0] / max(pk["gemm2"][1], 1)) * 1e3
         out["prefill_512"] = {
-            "workload": "mixtral_prefill (BASELINE configs[2]): 512 tokens, 26 heavy hitters x8, precision assigned at run time; expert weights shared with the decode workload",
+            "workload": "mixtral_prefill: 512 tokens, 26 heavy hitters x8, precision assigned at run time; expert weights shared with the decode workload",
             "tokens_per_s_full_path": round(pcfg.T * args.prefill_steps / psec, 1),
             "us_per_step_full_path": round(psec / args.prefill_steps * 1e6, 1),
             "tokens_per_s_formats_resident": round(pcfg.T * args.prefill_steps / psec2, 1),
@@ -520,7 +520,7 @@ def main():
         fg_us = (fk["gemm1"][0] / max(fk["gemm1"][1], 1) + fk["gemm2"][0] / max(fk["gemm2"][1], 1)) * 1e3
         fflops = 2.0 * 3 * fcfg.H * fcfg.F * fcfg.T * fcfg.k
         out["fine_grained_2048"] = {
-            "workload": "fine_grained (BASELINE configs[3]): 2048 tokens, 128 experts of 768, top-8, Zipf router bias, tiers 13/39/76",
+            "workload": "fine_grained: 2048 tokens, 128 experts of 768, top-8, Zipf router bias, tiers 13/39/76",
             "tokens_per_s_full_path": round(fcfg.T / fdt, 1), "us_per_step_full_path": round(fdt * 1e6, 1),
             "launch": fmode, "us_per_step_by_launch_mode": f_launch_us,
             "experts_with_load": int((flay.load > 0).sum()), "max_load": int(flay.load.max()),
@@ -731,7 +731,7 @@ def main():
                 torch.cuda.empty_cache()
         out["stack_decode_resident"] = {"workload": "the same 32 layers with every expert resident in device memory in every "
                                                     "format its tiers may name: no copies, no host decisions, a step is "
-                                                    "128 launches replayed as one HIP graph", "runs": resident}
+                                                    "65 launches, enqueued one by one or replayed as one HIP graph", "runs": resident}
         out["stack_decode"] = {"workload": "32 Mixtral-shaped layers, 1 token per step, experts in pinned host memory "
                                            "(16 distinct experts shared by the 256 layer-experts), every step a different token; eviction 'lru' is the "
                                            "paper's least-recently-used order, 'cyclic' evicts the expert whose layer comes up last; look-ahead of the next layer's 2 "
@@ -742,7 +742,7 @@ def main():
                                "host_pool_GB": round(sum(pool.buf[b].numel() for b in pool.buf) / 1e9, 2),
                                "section_wall_s": round(time.perf_counter() - t_stack, 1),
                                "runs": results}
-    # the two acceptance figures of the benchmark spec, side by side with what was measured in this run
+    # the two figures that the targets are stated on, side by side with what was measured in this run
     pg = out.get("prefill_512", {}).get("grouped_gemm_frac_mfma_bf16_peak")
     out["targets"] = {
         "decode_frac_hbm_on_packed_weights": {"target": 0.70, "kernels_only": roofline_decode["frac"],

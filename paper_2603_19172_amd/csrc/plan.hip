@@ -125,10 +125,10 @@ int plan_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const uint8_t
 // Ranking, bit widths and plan in one launch, for a layer's own step: dymoe_rank_experts' results (importance, load, bits,
 // rank; the norms come from the router's launch) and the plan of those bits, by the first workgroup; the others make the
 // fp16 copies of x that the tiers' formats can ask for.  The pairs are counted once, for the load and for the plan.
-// Bound: latency, a chain of about a dozen hand-overs through LDS behind two trips to memory.  us inside the kernel, and
-// the launches it stands for (norms, importance, assignment, plan): 16 tokens x 2 of 8 experts 6.0 for 3.7 + 5.5, 61 x 8 of
-// 128 (decode) 8.0 for 5.8 + 9.8, 512 x 2 of 8 8.2 for 5.6 + 5.5 + 4.9 + 14, 2048 x 8 of 128 20 for 5.1 + 9.7 + 6.1 + 31.
-// (There, 4 to 5 of the 20 are the first loads, behind the copies' traffic.)
+// Bound: latency, a chain of about a dozen hand-overs through LDS behind two trips to memory.  us among the other
+// launches of a step, and the launches it stands for (norms, importance, assignment, plan): 16 tokens x 2 of 8 experts 6.5 for
+// 3.7 + 5.5, 61 x 8 of 128 (decode) 9.5 for 5.8 + 9.8, 512 x 2 of 8 11 for 5.6 + 5.5 + 4.9 + 14, 2048 x 8 of 128 21 for
+// 5.1 + 9.7 + 6.1 + 31.  (There, 4 to 5 of the 21 are the first loads, behind the copies' traffic.)
 //   prefill  up to 256 tokens rank themselves by counting, as in importance_block_kernel; beyond, the k_hh-th largest score
 //            is found by a radix selection (11 bits at a time) and the heavy tokens are those above it, ties in token order
 //   decode   mean probability in token order, as in importance_block_kernel

@@ -68,7 +68,7 @@ class MoELayer:
         self.layout = B.LAYOUT_TILE if gemm else B.LAYOUT_ROWMAJOR
         self.ws_bytes = B.workspace_bytes(T, H, F, E, k)
         self.ws = torch.empty((self.ws_bytes,), dtype=torch.uint8, device=dev)
-        # a decode step on resident formats: dymoe_decode_layer (two or three launches) instead of front end + FFN (three or four)
+        # a decode step on resident formats: dymoe_decode_layer (two to four launches) instead of front end and FFN apart
         self.use_decode_step = True
 
     # the individual steps; each is one C call
@@ -132,7 +132,8 @@ class MoELayer:
                                           self.rank.data_ptr(), st), "dymoe_decode_front")
 
     def decode_step(self, x, wg, bias, store, st):
-        """S1 + S2 + S3 + S5 of a small decode step on resident formats in two launches; False when the sizes are
+        """S1 + S2 + S3 + S5 of a small decode step on resident formats in two to four launches, up to 64 experts
+        (a method for callers; step() takes decode_layer, which covers these sizes and more); False when the sizes are
         outside what the fused step covers (the caller then makes the separate calls)."""
         rc = B.lib.dymoe_decode_step(self.ctx._h, x.data_ptr(), wg.data_ptr(), bias.data_ptr() if bias is not None else None,
                                      self.T, self.H, self.F, self.E, self.k, 1, self._nt, C.cast(self._tc, C.c_void_p),

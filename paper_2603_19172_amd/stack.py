@@ -642,7 +642,7 @@ class ResidentDecodeStack:
             nxt = self.h[1] if h is self.h[0] else self.h[0]
             idx, gate, bits, table = self.idx[l].data_ptr(), self.gate[l].data_ptr(), self.bits[l].data_ptr(), \
                 self.tables[l].data_ptr()
-            # residual, front end and FFN in two launches, or without the residual; sizes those do not cover take the separate calls
+            # residual, front end and FFN in two to four launches, or without the residual; sizes those do not cover take the separate calls
             rc = B.ENOTSUP
             for with_residual in ((True, False) if owed else (False,)) if self.fused else ():
                 if owed and not with_residual:

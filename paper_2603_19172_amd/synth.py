@@ -26,7 +26,7 @@ _TID_EXPERT = 1000  # + 3*e + {0: W1, 1: W3, 2: W2}
 
 @dataclass(frozen=True)
 class MoEConfig:
-    """One MoE layer workload (shapes follow the benchmark's configs)."""
+    """One MoE layer workload (the named ones: CONFIGS below)."""
     name: str
     config_id: int
     T: int            # tokens in the step

@@ -1,4 +1,4 @@
-"""GPU parity at the benchmark's full sizes, in the launch configuration the
+"""GPU parity at the full sizes of the named workloads, in the launch configuration the
 benchmark times (pre-allocated layer runner, AUTO path).  Integer outputs are
 compared in full; the FFN is compared on the token rows the oracle can compute
 in seconds (all of them for decode, a seeded sample for the prefill layers)."""

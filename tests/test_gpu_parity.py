@@ -17,7 +17,7 @@ from paper_2603_19172_amd.layer import ExpertStore, MoELayer
 
 pytestmark = pytest.mark.gpu
 
-FFN_TOL = 2e-2   # max |y - ref| / rms(ref row), the bar of the benchmark spec
+FFN_TOL = 2e-2   # max |y - ref| / rms(ref row), the stated bar of the FFN's results
 
 
 @pytest.fixture(scope="module")
