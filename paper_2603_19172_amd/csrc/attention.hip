@@ -13,16 +13,14 @@
 // share the streamed operand between wavefronts, see below).  In the result a lane holds one
 // query (column) and 16 keys (rows): the softmax statistics of a query and the
 // running per-key sums both stay inside a lane until the very end.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dymoe {
 
 constexpr int kAtThreads = 256;
 constexpr int kAtWaves = kAtThreads / kWave;
-// the LDS-staged kernels from this many 32-token fragments on (T > 992) ...
-constexpr int kAtWideFrags = 32;
-template <int D>
-constexpr long kAtNarrowFrags = (D == 64) ? 768 : 512;   // ... if there are more than this over all heads
 
 // One lane's share of a 32-token fragment of one head (D columns): lane (ln, kb)
 // holds row ln; piece c covers columns 32 (c / 2) + 16 kb + 8 (c % 2) .. + 7, i.e.
@@ -208,269 +206,458 @@ __global__ __launch_bounds__(kAtThreads) void attn_colsum_kernel(
 }
 
 // ----------------------------------------------------------------------------
-// Long sequences: the streamed operand goes through LDS.  A workgroup owns 128 tokens (one 32-token fragment per
-// wavefront, kept in registers) and all four wavefronts multiply against the same streamed tokens, 64 at a time, which the
-// workgroup fetches once with whole-row coalesced loads, one stage ahead, and parks in LDS (two buffers; 16-byte chunk c
-// of row r at chunk position c ^ (r mod chunks-per-row), so that the operand reads of 16 consecutive rows fall on
-// different banks).  No merge between wavefronts: each owns its tokens' statistics or sums outright.
-// Bound: per 32 x 32 logits at d = 128 256 cycles of matrix instructions and about as many each of vector work and of
-// exponentials, overlapped between a SIMD's wavefronts.  4096 tokens, 32 / 8 heads, the whole score: d = 128 causal
-// 292 -> 195 us, unmasked 392 -> 341, d = 64 causal 247 -> 128, since two logits tiles are worked on side by side per
-// barrier, the register-held fragment is waited for before the loop, and blocks are dealt out by length (209, 358 and 139
-// before the sum over the heads asked for sixteen of them at a time).
-constexpr int kAtStageFrags = 2;
+// Long sequences: the streamed operand goes through LDS.  A workgroup of eight wavefronts owns OWNERS x 64 tokens: each
+// wavefront keeps two 32-token fragments in registers, so that what it reads from LDS feeds two products (with one fragment
+// the reads alone took the 128 bytes a cycle that LDS has), and the 8 / OWNERS wavefronts that own the same tokens share
+// the stream, two of a trip's fragments each; their statistics or sums meet in LDS at the end.
+// 16-byte chunk c of row r lies at chunk position c ^ (r mod chunks-per-row), so that the operand reads of 16 consecutive
+// rows fall on different banks.  The rows go from memory to LDS directly: through registers, the addresses and the stores took a
+// quarter of the vector instructions.
+// Bound: per 32 x 32 logits at d = 128 256 cycles of matrix instructions beside 32 multiply-adds and 16 exponentials (8 cycles each)
+// a lane, 256 cycles as well, and the chip's power allows both together at 1.7 GHz only (a loop of nothing else takes 206 ns per
+// 32 x 32, these kernels 230; the order of the instructions moves that by 2 %).  The whole score, 32 / 8 heads, d = 128, with one
+// fragment per wavefront, four wavefronts in a block of 128 tokens and every fragment's maximum -> so: 4096 tokens causal 194 -> 160 us,
+// unmasked 340 -> 276, 1024 causal 41 -> 28; 4096 x 6 heads 135 -> 77.
+constexpr int kAtWideThreads = 512;
 
-template <int D>
-struct AtStage {
-    static constexpr int kPerThread = kAtStageFrags * 32 * (D / 8) / kAtThreads;      // 4 (D = 128) or 2 (D = 64)
-    uint4 v[kPerThread];
+template <int D, int OWNERS>
+struct AtWide {
+    static constexpr int kStreams = 8 / OWNERS;
+    static constexpr int kEach = 2;                             // streamed fragments per wavefront and trip
+    static constexpr int kFrags = kEach * kStreams;
+    static constexpr int kRows = 32 * kFrags;
+    static constexpr int kFragBytes = 32 * D * 2;
+    static constexpr int kBufBytes = kRows * D * 2;
+    static constexpr int kBufs = (3 * kBufBytes <= 128 * 1024) ? 3 : 2;     // a trip's rows are requested kBufs - 1 trips ahead
+    static constexpr int kUnitRows = 1024 / (D * 2);            // rows that one copy of a wavefront fills
+    static constexpr int kUnits = kRows / kUnitRows / 8;        // copies per wavefront and trip
+    const char* base;           // the head's first row
+    uint32_t stride;            // bytes; a trip's 256 rows at most stay below 2^32 (65535 heads)
+    uint32_t row, chunk;        // this lane's row of the wavefront's first unit and its bytes' place in the row
+    uint32_t lds;               // LDS address of that unit, buffer 0
+
+    __device__ __forceinline__ AtWide(const uint16_t* head, int n_heads, const char* s_buf, int wave, int lane)
+    {
+        constexpr int CH = D / 8;
+        base = (const char*)head;
+        stride = (uint32_t)n_heads * (D * 2);
+        row = wave * kUnitRows + lane / CH;
+        chunk = ((lane ^ row) & (CH - 1)) * 16;                 // (units are 32 rows or more apart: the same in each)
+        lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)s_buf + wave * 1024;
+    }
+    // rows row0 .. row0 + ROWS - 1 to LDS from buffer `buf` on; rows past the end re-read the last token
+    template <int ROWS = kRows>
+    __device__ __forceinline__ void copy(int row0, int T, int buf) const
+    {
+        constexpr int units = ROWS / kUnitRows / 8;
+        const char* from = base + (long)row0 * stride;
+        const uint32_t to = lds + buf * kBufBytes;
+        const uint32_t left = T - 1 - row0;                     // (row0 is a token)
+        if (left >= ROWS - 1) {                                 // the same in every lane
+            const uint32_t off = row * stride + chunk;
+#pragma unroll
+            for (int i = 0; i < units; i++) lds_copy16(from + (long)(i * 8 * kUnitRows) * stride, off, to + i * 8192);
+        } else {
+#pragma unroll
+            for (int i = 0; i < units; i++)
+                lds_copy16(from, min(row + i * 8 * kUnitRows, left) * stride + chunk, to + i * 8192);
+        }
+    }
 };
 
 template <int D>
-__device__ __forceinline__ void stage_fetch(const uint16_t* __restrict__ head_base, long row_stride, int row0, int T,
-                                            AtStage<D>& st)
+__device__ __forceinline__ uint4 staged_piece(const char* frag, int ln, int kb, int c)
 {
-    constexpr int CH = D / 8;
-#pragma unroll
-    for (int i = 0; i < AtStage<D>::kPerThread; i++) {
-        const int at = i * kAtThreads + threadIdx.x;
-        const int r = at / CH, c = at % CH;
-        st.v[i] = load_global<uint4>(head_base + (long)min(row0 + r, T - 1) * row_stride + c * 8);
-    }
-    __builtin_amdgcn_sched_barrier(0);      // the loads leave here, not where they are stored to LDS
+    const int ch = (c >> 1) * 4 + kb * 2 + (c & 1);
+    return *reinterpret_cast<const uint4*>(frag + ln * (D * 2) + ((ch ^ (ln & (D / 8 - 1))) << 4));
 }
 
-template <int D>
-__device__ __forceinline__ void stage_store(char* buf, const AtStage<D>& st)
-{
-    constexpr int CH = D / 8;
-#pragma unroll
-    for (int i = 0; i < AtStage<D>::kPerThread; i++) {
-        const int at = i * kAtThreads + threadIdx.x;
-        const int r = at / CH, c = at % CH;
-        *reinterpret_cast<uint4*>(buf + r * (D * 2) + ((c ^ (r & (CH - 1))) << 4)) = st.v[i];
-    }
-}
-
-// The fragment has arrived from here on.  Without this the compiler waits for it inside the loop, and as loads return in
-// order that is a wait for the stage fetched in the same trip.
-template <int D>
-__device__ __forceinline__ void settle(AtFrag<D>& f)
-{
-#pragma unroll
-    for (int c = 0; c < D / 16; c++) asm volatile("" : "+v"(f.c[c].x), "+v"(f.c[c].y), "+v"(f.c[c].z), "+v"(f.c[c].w));
-}
-
-// Workgroup -> (block of four fragments, head) for the two kernels below.  An XCD gets whole heads, as above.  Under the
-// causal mask a block's work grows (pass 1) or shrinks (pass 2) with its position, and all workgroups of 4096 tokens x 32
-// heads are on the chip at once: dealt out head by head, a compute unit (every 32nd workgroup of its XCD) got the same
-// position of every head, the last one four of the longest blocks.  So the XCD's blocks are ordered by length over all its
-// heads and dealt out to and fro in rounds of 32.
-__device__ __forceinline__ void block_and_head(int nblk, int n_heads, int causal, int& blk, int& head)
+// Workgroup -> (block of 64 OWNERS tokens, head) for the two kernels below.  An XCD gets whole heads, as above.  Under the
+// causal mask a block's work grows (pass 1) or shrinks (pass 2) with its position: the longest blocks of all heads come
+// first, so that what a compute unit gets when it has finished one is the shorter the later it is (LONG_LAST: the last block
+// is the longest).
+template <bool LONG_LAST>
+__device__ __forceinline__ void block_and_head(int nblk, int n_heads, int& blk, int& head)
 {
     const int lin = blockIdx.x + nblk * blockIdx.y;           // grid = nblk n_heads, or (nblk, n_heads) if that is too long
+    int rank;
     if (n_heads % 8 == 0) {
         const int per = n_heads >> 3, xcd = lin & 7, j = lin >> 3;
-        const int round = j >> 5, in_round = min(32, per * nblk - 32 * round);
-        const int at = 32 * round + ((causal && (round & 1)) ? in_round - 1 - (j & 31) : (j & 31));
-        blk = at / per;
-        head = xcd * per + (at - blk * per);
+        rank = j / per;
+        head = xcd * per + (j - rank * per);
     } else {
-        head = lin / nblk;
-        blk = lin - head * nblk;
-        if (causal && (head & 1)) blk = nblk - 1 - blk;
+        rank = lin / n_heads;
+        head = lin - rank * n_heads;
     }
+    blk = LONG_LAST ? nblk - 1 - rank : rank;
 }
 
-// The stage's two logits tiles against one register-held fragment, side by side: sixteen matrix instructions in two
-// chains, so that one chain's latency passes behind the other.  KEYS_STAGED: the staged rows are the keys.
-template <int D, bool KEYS_STAGED>
-__device__ __forceinline__ void stage_tiles(const char* buf, int ln, int kb, const AtFrag<D>& own, float16_t (&acc)[2])
+// The logits tiles of one staged fragment against the two register-held ones, and beside them the vector work on the fragment
+// before: 32 values a lane, of which work(e, n) requests the exponentials of e .. e + n - 1 and uses those of the call before, so
+// that nothing waits for a result it has just asked for.  The order is pinned by scheduling barriers: left to itself the
+// compiler puts each LDS read right in front of its product and each exponential right in front of its use.
+// KEYS_STAGED: the staged rows are the keys.
+// 16-byte pieces requested from LDS ahead of their products (4096 x 32, unmasked, 2 / 3 / 4: d = 128 280 / 278 / 273 us, d = 64 203 / 204 / 207)
+template <int D>
+constexpr int kAtAhead = (D == 128) ? 4 : 3;
+
+// in: the first kAtAhead pieces, requested before; left with those of the fragment behind this one if MORE.
+template <int D, bool KEYS_STAGED, bool MORE, typename Work>
+__device__ __forceinline__ void staged_tiles(const char* frag, int ln, int kb, const AtFrag<D> (&own)[2], uint4 (&in)[kAtAhead<D>],
+                                             float16_t (&acc)[2], Work work)
 {
+    constexpr int N = D / 16, kEach = 32 / N;
+    uint4 piece[N + kAtAhead<D>];
 #pragma unroll
-    for (int s = 0; s < 2; s++)
+    for (int c = 0; c < kAtAhead<D>; c++) piece[c] = in[c];
 #pragma unroll
-        for (int i = 0; i < 16; i++) acc[s][i] = 0.0f;
-    constexpr int CH = D / 8;
+    for (int o = 0; o < 2; o++)
 #pragma unroll
-    for (int c = 0; c < D / 16; c++) {
-        const int ch = (c >> 1) * 4 + kb * 2 + (c & 1);
+        for (int i = 0; i < 16; i++) acc[o][i] = 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < 2; s++) {
-            const bf16x8_t staged = __builtin_bit_cast(
-                bf16x8_t, *reinterpret_cast<const uint4*>(buf + s * (32 * D * 2) + ln * (D * 2) + ((ch ^ (ln & (CH - 1))) << 4)));
-            const bf16x8_t mine = __builtin_bit_cast(bf16x8_t, own.c[c]);
-            acc[s] = KEYS_STAGED ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(staged, mine, acc[s], 0, 0, 0)
-                                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(mine, staged, acc[s], 0, 0, 0);
+    for (int c = 0; c < N; c++) {
+        if (c + kAtAhead<D> < N) piece[c + kAtAhead<D>] = staged_piece<D>(frag, ln, kb, c + kAtAhead<D>);
+        else if (MORE) piece[c + kAtAhead<D>] = staged_piece<D>(frag + 32 * D * 2, ln, kb, c + kAtAhead<D> - N);
+        const bf16x8_t staged = __builtin_bit_cast(bf16x8_t, piece[c]);
+#pragma unroll
+        for (int o = 0; o < 2; o++) {
+            const bf16x8_t mine = __builtin_bit_cast(bf16x8_t, own[o].c[c]);
+            acc[o] = KEYS_STAGED ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(staged, mine, acc[o], 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(mine, staged, acc[o], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            work(c * kEach + o * (kEach / 2), std::integral_constant<int, kEach / 2>());
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
+    if (MORE)
+#pragma unroll
+        for (int c = 0; c < kAtAhead<D>; c++) in[c] = piece[N + c];
 }
 
-// Pass 1, long sequences: wavefront w owns the query fragment 4 blk + w; keys stream through LDS.
-template <int D>
-__global__ __launch_bounds__(kAtThreads, 3) void attn_rowstats_wide_kernel(
+// The wavefront's two fragments of the block's rows, through the buffers that hold no stage yet (a lane's own loads of them would
+// touch 32 rows for 32 bytes each); start() starts the first stage's copies, which arrive with them.
+template <int D, int OWNERS, typename Start>
+__device__ __forceinline__ void own_fragments(const AtWide<D, OWNERS>& st, int blk, int owner, const char* from, int ln, int kb, int T,
+                                              AtFrag<D> (&own)[2], Start start)
+{
+    static_assert(OWNERS * 64 * D * 2 <= (AtWide<D, OWNERS>::kBufs - 1) * AtWide<D, OWNERS>::kBufBytes, "the block's rows fit behind the first stage");
+    st.template copy<OWNERS * 64>(blk * OWNERS * 64, T, 1);
+    start();
+    wait_lds_copies<0>();
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < 2; o++)
+#pragma unroll
+        for (int c = 0; c < D / 16; c++) own[o].c[c] = staged_piece<D>(from + (owner * 2 + o) * (32 * D * 2), ln, kb, c);
+    __syncthreads();                    // all have read theirs
+}
+
+// Pass 1, long sequences: a wavefront owns the queries of two fragments; keys stream through LDS.
+// m is a reference for the exponents, not always the maximum: it is raised to the maximum seen only when a sum of sixteen
+// exponentials exceeds kAtRaise (or is the first), so an argument exceeds m by 8 at most and the steady state needs neither
+// maxima nor rescaling.
+constexpr float kAtRaise = 256.0f;
+
+template <int D, int OWNERS>
+__global__ __launch_bounds__(kAtWideThreads, 2) void attn_rowstats_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, float2* __restrict__ stats)
 {
-    __shared__ __attribute__((aligned(16))) char s_buf[2][kAtStageFrags * 32 * D * 2];
+    using Stage = AtWide<D, OWNERS>;
+    __shared__ __attribute__((aligned(16))) char s_buf[Stage::kBufs][Stage::kBufBytes];
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, kb = lane >> 5;
     const int nfrag = (T + 31) >> 5;
+    const int owner = wave % OWNERS, stream = wave / OWNERS;
     int blk, h;
-    block_and_head((nfrag + 3) >> 2, n_heads, causal, blk, h);
-    const long q_stride = (long)n_heads * D, k_stride = (long)(n_heads / group) * D;
+    block_and_head<true>((nfrag + 2 * OWNERS - 1) / (2 * OWNERS), n_heads, blk, h);
     const uint16_t* qh = q + (long)h * D;
     const uint16_t* kh = k + (long)(h / group) * D;
-    const int qf = 4 * blk + wave;
-    const int query = qf * 32 + ln;
-    AtFrag<D> fq;
-    load_frag<D>(qh, q_stride, min(query, T - 1), kb, fq);
-    const int kf_last = causal ? min(4 * blk + 3, nfrag - 1) : nfrag - 1;
-    const int mine_last = (qf >= nfrag) ? -1 : causal ? qf : kf_last;        // the last fragment this wavefront's queries see
+    const int qf = 2 * (OWNERS * blk + owner);                  // and the fragment behind it
+    const int kf_last = causal ? min(2 * OWNERS * (blk + 1), nfrag) - 1 : nfrag - 1;
+    const int mine_last = (qf >= nfrag) ? -1 : causal ? min(qf + 1, nfrag - 1) : kf_last;     // the last fragment these queries see
     // the fragments before this one need no mask: all but the diagonal and a ragged last one
     const int plain_end = min(causal ? qf : nfrag, T >> 5);
-    AtStage<D> st;
-    stage_fetch<D>(kh, k_stride, 0, T, st);
-    stage_store<D>(s_buf[0], st);
-    __syncthreads();
-    settle<D>(fq);
-    float m = kMasked, l = 0.0f;
-    for (int kf0 = 0, buf = 0; kf0 <= kf_last; kf0 += kAtStageFrags, buf ^= 1) {
-        const bool more = kf0 + kAtStageFrags <= kf_last;       // the same in every thread
-        if (more) stage_fetch<D>(kh, k_stride, (kf0 + kAtStageFrags) * 32, T, st);
-        if (kf0 <= mine_last) {                                 // the same in every lane of the wavefront
-            float16_t acc[2];
-            stage_tiles<D, true>(s_buf[buf], ln, kb, fq, acc);
-            if (kf0 + 1 < plain_end) {
-                // the scale is positive, so the maximum is taken over the raw logits and the scale rides in the exponent's
-                // multiply-add
-                float raw0 = acc[0][0], raw1 = acc[1][0];
+    const Stage st(kh, n_heads / group, s_buf[0], wave, lane);
+    AtFrag<D> fq[2];
+    own_fragments<D, OWNERS>(Stage(qh, n_heads, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fq, [&] { st.copy(0, T, 0); });
+    if (Stage::kBufs == 3 && Stage::kFrags <= kf_last) st.copy(Stage::kRows, T, 1);
+    float m[2] = {kMasked, kMasked}, l[2] = {0.0f, 0.0f};
+    float sum[4], last[8];                                      // sum[2 o], sum[2 o + 1]: query fragment o
+    auto begin = [&] { sum[0] = sum[1] = sum[2] = sum[3] = 0.0f; };
+    auto exps = [&](const float16_t (&acc)[2], int e, auto n) {
+        constexpr int N = decltype(n)::value;
+        float t[N];
 #pragma unroll
-                for (int i = 1; i < 16; i++) {
-                    raw0 = fmaxf(raw0, acc[0][i]);
-                    raw1 = fmaxf(raw1, acc[1][i]);
-                }
-                const float mx = fmaxf(m, fmaxf(raw0, raw1) * scale_log2);
-                float add[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < N; j++) t[j] = fmaf(acc[(e + j) >> 4][(e + j) & 15], scale_log2, -m[(e + j) >> 4]);
 #pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    add[i & 1] += __builtin_amdgcn_exp2f(fmaf(acc[0][i], scale_log2, -mx));
-                    add[2 + (i & 1)] += __builtin_amdgcn_exp2f(fmaf(acc[1][i], scale_log2, -mx));
-                }
-                l = l * __builtin_amdgcn_exp2f(m - mx) + ((add[0] + add[1]) + (add[2] + add[3]));
-                m = mx;
-            } else {
+        for (int j = 0; j < N; j++) t[j] = __builtin_amdgcn_exp2f(t[j]);
 #pragma unroll
-                for (int s = 0; s < kAtStageFrags; s++) {
-                    float sv[16];
-                    float mx = m;
+        for (int j = 0; j < N; j++) {
+            if (e > 0) sum[2 * ((e - N + j) >> 4) + (j & 1)] += last[j];
+            last[j] = t[j];
+        }
+    };
+    auto finish = [&](auto n) {
+        constexpr int N = decltype(n)::value;
 #pragma unroll
-                    for (int i = 0; i < 16; i++) {
-                        const int key = tile_key(kf0 + s, kb, i);
-                        const bool ok = key < T && (!causal || key <= query);
-                        sv[i] = ok ? acc[s][i] * scale_log2 : kMasked;
-                        mx = fmaxf(mx, sv[i]);
-                    }
-                    float add = 0.0f;
+        for (int j = 0; j < N; j++) sum[2 + (j & 1)] += last[j];
+        return make_float2(sum[0] + sum[1], sum[2] + sum[3]);
+    };
+    auto plain = [&](const float16_t (&acc)[2]) {
+        begin();
 #pragma unroll
-                    for (int i = 0; i < 16; i++) add += (sv[i] > 0.5f * kMasked) ? __builtin_amdgcn_exp2f(sv[i] - mx) : 0.0f;
-                    l = l * __builtin_amdgcn_exp2f(m - mx) + add;
-                    m = mx;
-                }
+        for (int e = 0; e < 32; e += 8) exps(acc, e, std::integral_constant<int, 8>());
+        return finish(std::integral_constant<int, 8>());
+    };
+    auto take = [&](const float16_t (&acc)[2], float2 sum) {
+        if (__builtin_expect(__any(fmaxf(sum.x, sum.y) > kAtRaise), 0)) {
+#pragma unroll
+            for (int o = 0; o < 2; o++) {
+                // the scale is positive, so the maximum is taken over the raw logits
+                float raw = acc[o][0];
+#pragma unroll
+                for (int i = 1; i < 16; i++) raw = fmaxf(raw, acc[o][i]);
+                const float mx = fmaxf(m[o], raw * scale_log2);
+                float add = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; i++) add += __builtin_amdgcn_exp2f(fmaf(acc[o][i], scale_log2, -mx));
+                l[o] = l[o] * __builtin_amdgcn_exp2f(m[o] - mx) + add;
+                m[o] = mx;
+            }
+        } else {
+            l[0] += sum.x;
+            l[1] += sum.y;
+        }
+    };
+    // One fragment's products beside the exponentials of the one before (fragment kp).
+    auto hide = [&](float16_t (&acc)[2], int kf) {
+        if (__builtin_expect(kf >= plain_end, 0)) {
+#pragma unroll
+            for (int o = 0; o < 2; o++) {
+                // the last key this lane's query sees, counted from the lane's first key
+                const int last = (causal ? min((qf + o) * 32 + ln, T - 1) : T - 1) - kf * 32 - 4 * kb;
+#pragma unroll
+                for (int i = 0; i < 16; i++) acc[o][i] = (8 * (i >> 2) + (i & 3) <= last) ? acc[o][i] : -INFINITY;
             }
         }
-        if (more) stage_store<D>(s_buf[buf ^ 1], st);
+    };
+    float16_t acc0[2], acc1[2];
+#pragma unroll
+    for (int o = 0; o < 2; o++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc1[o][i] = -INFINITY;    // nothing before the first
+    int kp = -1;
+    uint4 in[kAtAhead<D>];
+    for (int base = 0, buf = 0; base <= kf_last; base += Stage::kFrags, buf = (buf == Stage::kBufs - 1) ? 0 : buf + 1) {
+        constexpr int ahead = (Stage::kBufs - 1) * Stage::kFrags;
+        const bool more = base + ahead <= kf_last;              // the same in every thread
+        if (more) st.copy((base + ahead) * 32, T, (buf == 0) ? Stage::kBufs - 1 : buf - 1);
+        const int kf = base + Stage::kEach * stream;
+        const char* frag = s_buf[buf] + Stage::kEach * stream * Stage::kFragBytes;
+        if (kf <= mine_last) {                                  // the same in every lane of the wavefront
+#pragma unroll
+            for (int c = 0; c < kAtAhead<D>; c++) in[c] = staged_piece<D>(frag, ln, kb, c);
+        }
+#pragma unroll
+        for (int f = 0; f < Stage::kEach; f++) {
+            if (kf + f <= mine_last) {
+                float16_t(&acc)[2] = (f & 1) ? acc1 : acc0;
+                float16_t(&before)[2] = (f & 1) ? acc0 : acc1;
+                hide(before, kp);
+                begin();
+                auto work = [&](int e, auto n) { exps(before, e, n); };
+                if (f + 1 < Stage::kEach) staged_tiles<D, true, true>(frag + f * Stage::kFragBytes, ln, kb, fq, in, acc, work);
+                else staged_tiles<D, true, false>(frag + f * Stage::kFragBytes, ln, kb, fq, in, acc, work);
+                take(before, finish(std::integral_constant<int, D == 128 ? 2 : 4>()));
+                kp = kf + f;
+            }
+        }
+        if (Stage::kBufs == 3 && more) wait_lds_copies<Stage::kUnits>();        // the next stage is there, the one behind it on its way
+        else wait_lds_copies<0>();
         __syncthreads();
     }
-    const float m2 = __shfl_xor(m, 32, kWave), l2 = __shfl_xor(l, 32, kWave);
-    const float M = fmaxf(m, m2);
-    const float L = l * __builtin_amdgcn_exp2f(m - M) + l2 * __builtin_amdgcn_exp2f(m2 - M);
-    // one number per query is all pass 2 needs: p = exp2(logit' - (m + log2 l))
-    if (kb == 0 && query < T) stats[(long)h * T + query] = make_float2(M + __builtin_amdgcn_logf(L), 0.0f);
+    if (kp & 1) {                                               // the last fragment's exponentials (odd where there is none, too)
+        hide(acc1, kp);
+        take(acc1, plain(acc1));
+    } else {
+        hide(acc0, kp);
+        take(acc0, plain(acc0));
+    }
+    float2(*const s_ml)[OWNERS * 64] = reinterpret_cast<float2(*)[OWNERS * 64]>(s_buf);
+#pragma unroll
+    for (int o = 0; o < 2; o++) {
+        const float m2 = __shfl_xor(m[o], 32, kWave), l2 = __shfl_xor(l[o], 32, kWave);
+        const float M = fmaxf(m[o], m2);
+        const float L = l[o] * __builtin_amdgcn_exp2f(m[o] - M) + l2 * __builtin_amdgcn_exp2f(m2 - M);
+        if (kb == 0) s_ml[stream][owner * 64 + o * 32 + ln] = make_float2(M, L);
+    }
+    __syncthreads();
+    const int query = blk * OWNERS * 64 + threadIdx.x;
+    if (threadIdx.x < OWNERS * 64 && query < T) {
+        float M = s_ml[0][threadIdx.x].x;
+#pragma unroll
+        for (int s = 1; s < Stage::kStreams; s++) M = fmaxf(M, s_ml[s][threadIdx.x].x);
+        float L = 0.0f;
+#pragma unroll
+        for (int s = 0; s < Stage::kStreams; s++) L += s_ml[s][threadIdx.x].y * __builtin_amdgcn_exp2f(s_ml[s][threadIdx.x].x - M);
+        stats[(long)h * T + query] = make_float2(M, 1.0f / L);
+    }
 }
 
-// Pass 2, long sequences: wavefront w owns the key fragment 4 blk + w; queries stream through LDS.
-template <int D>
-__global__ __launch_bounds__(kAtThreads, 3) void attn_colsum_wide_kernel(
+// Pass 2, long sequences: a wavefront owns the keys of two fragments; queries stream through LDS.
+template <int D, int OWNERS>
+__global__ __launch_bounds__(kAtWideThreads, 2) void attn_colsum_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, const float2* __restrict__ stats, float* __restrict__ partial)
 {
-    __shared__ __attribute__((aligned(16))) char s_buf[2][kAtStageFrags * 32 * D * 2];
+    using Stage = AtWide<D, OWNERS>;
+    __shared__ __attribute__((aligned(16))) char s_buf[Stage::kBufs][Stage::kBufBytes];
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, kb = lane >> 5;
     const int nfrag = (T + 31) >> 5;
+    const int owner = wave % OWNERS, stream = wave / OWNERS;
     int blk, h;
-    block_and_head((nfrag + 3) >> 2, n_heads, causal, blk, h);
-    const long q_stride = (long)n_heads * D, k_stride = (long)(n_heads / group) * D;
+    block_and_head<false>((nfrag + 2 * OWNERS - 1) / (2 * OWNERS), n_heads, blk, h);
     const uint16_t* qh = q + (long)h * D;
     const uint16_t* kh = k + (long)(h / group) * D;
     const float2* sh = stats + (long)h * T;
-    const int kf = 4 * blk + wave;
-    AtFrag<D> fk;
-    load_frag<D>(kh, k_stride, min(kf * 32 + ln, T - 1), kb, fk);
-    const int qf_first = causal ? 4 * blk : 0;
-    AtStage<D> st;
-    float next[kAtStageFrags], shift[kAtStageFrags];
-    auto shifts = [&](int qf) {
+    const int kf = 2 * (OWNERS * blk + owner);
+    const int first = causal ? 2 * OWNERS * blk : 0;
+    const int mine_first = (kf >= nfrag) ? nfrag : causal ? kf : 0;     // the first fragment of queries that see these keys
+    const Stage st(qh, n_heads, s_buf[0], wave, lane);
+    float2 next[Stage::kEach], now[Stage::kEach];               // (m, 1 / l) of the lane's query in the wavefront's fragments
+    auto request = [&](int qf) {
 #pragma unroll
-        for (int s = 0; s < kAtStageFrags; s++) next[s] = -sh[min((qf + s) * 32 + ln, T - 1)].x;
+        for (int s = 0; s < Stage::kEach; s++) next[s] = sh[min((qf + Stage::kEach * stream + s) * 32 + ln, T - 1)];
     };
-    shifts(qf_first);
-    stage_fetch<D>(qh, q_stride, qf_first * 32, T, st);
-    stage_store<D>(s_buf[0], st);
-    __syncthreads();
-    settle<D>(fk);
-    float col[16];
+    request(first);
+    AtFrag<D> fk[2];
+    own_fragments<D, OWNERS>(Stage(kh, n_heads / group, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fk,
+                             [&] { st.copy(first * 32, T, 0); });
+    if (Stage::kBufs == 3 && first + Stage::kFrags < nfrag) st.copy((first + Stage::kFrags) * 32, T, 1);
+    float col[2][16];
 #pragma unroll
-    for (int i = 0; i < 16; i++) col[i] = 0.0f;
-    for (int qf0 = qf_first, buf = 0; qf0 < nfrag; qf0 += kAtStageFrags, buf ^= 1) {
-        const bool more = qf0 + kAtStageFrags < nfrag;
+    for (int o = 0; o < 2; o++)
 #pragma unroll
-        for (int s = 0; s < kAtStageFrags; s++) shift[s] = next[s];
-        if (more) {
-            shifts(qf0 + kAtStageFrags);
-            stage_fetch<D>(qh, q_stride, (qf0 + kAtStageFrags) * 32, T, st);
+        for (int i = 0; i < 16; i++) col[o][i] = 0.0f;
+    // p = exp2(logit' - m) / l, the last factor with the addition
+    float last[8];
+    auto exps = [&](const float16_t (&acc)[2], float2 ml, int e, auto n) {
+        constexpr int N = decltype(n)::value;
+        float t[N];
+#pragma unroll
+        for (int j = 0; j < N; j++) t[j] = fmaf(acc[(e + j) >> 4][(e + j) & 15], scale_log2, -ml.x);
+#pragma unroll
+        for (int j = 0; j < N; j++) t[j] = __builtin_amdgcn_exp2f(t[j]);
+#pragma unroll
+        for (int j = 0; j < N; j++) {
+            if (e > 0) col[(e - N + j) >> 4][(e - N + j) & 15] = fmaf(last[j], ml.y, col[(e - N + j) >> 4][(e - N + j) & 15]);
+            last[j] = t[j];
         }
-        if (kf < nfrag && (!causal || qf0 + 1 >= kf)) {         // the same in every lane of the wavefront
-            float16_t acc[2];
-            stage_tiles<D, false>(s_buf[buf], ln, kb, fk, acc);
-            if ((qf0 + 2) * 32 <= T && kf * 32 + 32 <= T && (!causal || kf < qf0)) {
+    };
+    auto finish = [&](float2 ml, auto n) {
+        constexpr int N = decltype(n)::value;
+#pragma unroll
+        for (int j = 0; j < N; j++) col[1][16 - N + j] = fmaf(last[j], ml.y, col[1][16 - N + j]);
+    };
+    // A fragment that the mask or the last query cuts is added here, and what the next products then find before them adds
+    // nothing.  (Keys past the end are added to places of their own, which nothing reads.  What is masked adds zero whatever its
+    // query's statistics are: a query that is not a number spoils the keys that it sees and no others.)
+    auto cut = [&](float16_t (&acc)[2], float2& ml, int qf) {
+        if (__builtin_expect((qf + 1) * 32 > T || (causal && qf <= kf + 1), 0)) {
+            const int query = qf * 32 + ln;
+            // the last key this lane's query adds to, counted from the lane's first key
+            const int last = (query >= T || qf < 0) ? -1 : causal ? query - kf * 32 - 4 * kb : 64;
+#pragma unroll
+            for (int o = 0; o < 2; o++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) {
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(acc[0][i], scale_log2, shift[0]));
-                    const float p1 = __builtin_amdgcn_exp2f(fmaf(acc[1][i], scale_log2, shift[1]));
-                    col[i] += p0 + p1;
+                    float p = __builtin_amdgcn_exp2f(fmaf(acc[o][i], scale_log2, -ml.x)) * ml.y;
+                    p = (32 * o + 8 * (i >> 2) + (i & 3) <= last) ? p : 0.0f;
+                    col[o][i] += p;
+                    acc[o][i] = -INFINITY;
                 }
-            } else {
+            ml = make_float2(0.0f, 0.0f);
+        }
+    };
+    float16_t acc0[2], acc1[2];
 #pragma unroll
-                for (int s = 0; s < kAtStageFrags; s++) {
-                    const int query = (qf0 + s) * 32 + ln;
+    for (int o = 0; o < 2; o++)
 #pragma unroll
-                    for (int i = 0; i < 16; i++) {
-                        const int key = tile_key(kf, kb, i);
-                        const bool ok = query < T && key < T && (!causal || key <= query);
-                        const float p = __builtin_amdgcn_exp2f(fmaf(acc[s][i], scale_log2, shift[s]));
-                        col[i] += ok ? p : 0.0f;
-                    }
+        for (int i = 0; i < 16; i++) acc1[o][i] = -INFINITY;    // nothing before the first
+    int qp = -1;
+    uint4 in[kAtAhead<D>];
+    float2 ml = make_float2(0.0f, 0.0f);                        // what goes with the fragment before
+    for (int base = first, buf = 0; base < nfrag; base += Stage::kFrags, buf = (buf == Stage::kBufs - 1) ? 0 : buf + 1) {
+        constexpr int ahead = (Stage::kBufs - 1) * Stage::kFrags;
+        const bool more = base + ahead < nfrag;                 // the same in every thread
+#pragma unroll
+        for (int s = 0; s < Stage::kEach; s++) now[s] = next[s];
+        request(base + Stage::kFrags);
+        __builtin_amdgcn_sched_barrier(0);                      // ahead of the copies, which may still be on their way at the trip's end
+        if (more) st.copy((base + ahead) * 32, T, (buf == 0) ? Stage::kBufs - 1 : buf - 1);
+        const int qf = base + Stage::kEach * stream;
+        const char* frag = s_buf[buf] + Stage::kEach * stream * Stage::kFragBytes;
+#pragma unroll
+        for (int f = 0; f < Stage::kEach; f++) {
+            if (qf + f >= mine_first && qf + f < nfrag) {       // the same in every lane of the wavefront (mine_first is even)
+                if (f == 0) {
+#pragma unroll
+                    for (int c = 0; c < kAtAhead<D>; c++) in[c] = staged_piece<D>(frag + f * Stage::kFragBytes, ln, kb, c);
                 }
+                float16_t(&acc)[2] = (f & 1) ? acc1 : acc0;
+                float16_t(&before)[2] = (f & 1) ? acc0 : acc1;
+                cut(before, ml, qp);
+                auto work = [&](int e, auto n) { exps(before, ml, e, n); };
+                if (f + 1 < Stage::kEach) staged_tiles<D, false, true>(frag + f * Stage::kFragBytes, ln, kb, fk, in, acc, work);
+                else staged_tiles<D, false, false>(frag + f * Stage::kFragBytes, ln, kb, fk, in, acc, work);
+                finish(ml, std::integral_constant<int, D == 128 ? 2 : 4>());
+                qp = qf + f;
+                ml = now[f];
             }
         }
-        if (more) stage_store<D>(s_buf[buf ^ 1], st);
+        if (Stage::kBufs == 3 && more) wait_lds_copies<Stage::kUnits>();        // the next stage is there, the one behind it on its way
+        else wait_lds_copies<0>();
         __syncthreads();
     }
+    auto rest = [&](float16_t (&acc)[2]) {                      // the last fragment's exponentials
+        cut(acc, ml, qp);
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-        float v = col[i];
+        for (int e = 0; e < 32; e += 8) exps(acc, ml, e, std::integral_constant<int, 8>());
+        finish(ml, std::integral_constant<int, 8>());
+    };
+    if (qp & 1) rest(acc1);                                     // (none at all: nothing before the first)
+    else rest(acc0);
+    // Sums over the 32 queries that the lanes of each half hold: in every exchange a lane keeps half of its keys, so that it ends with
+    // one, number ln % 16 of the sixteen (bits reversed) ...
+    float* const s_col = reinterpret_cast<float*>(s_buf);       // [stream][OWNERS * 64]
 #pragma unroll
-        for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-        col[i] = v;
-    }
-    if (ln == 0 && kf < nfrag) {
+    for (int o = 0; o < 2; o++) {
+        int mine = 0;
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
-            const int key = tile_key(kf, kb, i);
-            if (key < T) partial[(long)h * T + key] = col[i];
+        for (int w = 8, bit = 1; w > 0; w >>= 1, bit <<= 1) {
+            const bool upper = (ln & bit) != 0;
+#pragma unroll
+            for (int i = 0; i < 8; i++)
+                if (i < w) {
+                    const float keep = upper ? col[o][i + w] : col[o][i], give = upper ? col[o][i] : col[o][i + w];
+                    col[o][i] = keep + __shfl_xor(give, bit, kWave);
+                }
+            mine += upper ? w : 0;
         }
+        const float v = col[o][0] + __shfl_xor(col[o][0], 16, kWave);
+        if (ln < 16) s_col[stream * (OWNERS * 64) + owner * 64 + o * 32 + tile_key(0, kb, mine)] = v;
+    }
+    __syncthreads();
+    // ... and over the wavefronts that share the keys, in their order
+    const int key = blk * OWNERS * 64 + threadIdx.x;
+    if (threadIdx.x < OWNERS * 64 && key < T) {
+        float v = s_col[threadIdx.x];
+#pragma unroll
+        for (int s = 1; s < Stage::kStreams; s++) v += s_col[s * (OWNERS * 64) + threadIdx.x];
+        partial[(long)h * T + key] = v;
     }
 }
 
@@ -513,6 +700,46 @@ __global__ __launch_bounds__(kAtScoreThreads) void attn_score_kernel(const float
     score[i] = s * inv;
 }
 
+// Which pair of kernels.  Few fragments over all heads: a workgroup per 32-token fragment, its wavefronts sharing the streamed
+// tokens (many workgroups, operands straight from global memory).  Else blocks of 128 or 256 tokens with the stream in LDS.
+// Whole score, us, narrow / wide (128-token blocks) by tokens x heads (fragments):
+//                      d = 128, causal  unmasked                        d = 64, causal    unmasked
+//    1400 x  4 (176)        - / -      35.6 / 39.2    3000 x  4 (376)   47.8 / 49.1   55.9 / 58.9
+//    2048 x  4 (256)      47.9 / 43.4  50.9 / 41.4    4096 x  4 (512)   69.2 / 60.8   74.3 / 60.2
+//    1000 x  8 (256)      27.7 / 29.4  28.9 / 31.1    2048 x  8 (512)   33.6 / 37.7   41.7 / 35.7
+//     512 x 16 (256)      18.3 / 21.1  18.9 / 18.8    1000 x 16 (512)   24.5 / 25.7   25.7 / 27.9
+//     300 x 32 (320)      19.4 / 20.2  20.6 / 20.6     512 x 32 (512)   17.7 / 19.4   17.8 / 17.0
+//    1400 x  8 (352)      40.9 / 35.5  52.8 / 39.7    1400 x 16 (704)   31.6 / 30.6   43.7 / 35.5
+//     512 x 32 (512)      26.5 / 21.4  27.0 / 19.0     700 x 32 (704)   23.0 / 23.1   27.5 / 24.4
+//    1000 x 32 (1024)     70.8 / 30.8  73.5 / 33.2    1000 x 32 (1024)  41.3 / 26.7   42.9 / 29.0
+// so the line lies at 320 fragments (d = 128) or 640 (d = 64, where a wavefront's share of the products is half as long), and at
+// 224 or 448 where the sequence is long: the narrow pair's chain goes over a quarter of it at a memory latency per fragment.
+static bool attn_wide(int nfrag, int n_heads, int d)
+{
+    const long all = (long)nfrag * n_heads;
+    if (nfrag < 9) return false;        // 64 tokens x 192 heads 14.7 / 19.6, 200 x 64 16.4 / 18.4, 300 x 64 27.6 / 21.7 (d = 128)
+    return d == 128 ? all > 320 || (all > 224 && nfrag >= 48) : all > 640 || (all > 448 && nfrag >= 96);
+}
+
+// Tokens per block of the wide pair, in units of 64: 4 with two wavefronts sharing a stream, or 2 with four.  A block takes a
+// start of about 5 fragments' time and then its stream, split over the sharing wavefronts; blocks of 128 tokens are twice as many
+// and read the stream twice as often (6 % per fragment, measured), but their chain is half as long.  Unmasked, all blocks are alike and
+// go over the chip in rounds; causal blocks come longest first and fill it evenly, unless the longest alone takes longer.
+// Whole score, d = 128, us, 128 / 256 tokens: 2048 x 16 causal 44.9 / 70.7, 4096 x 16 94.6 / 129, 6000 x 16 198 / 188, 2048 x 32 59.9 / 73.4,
+// 3000 x 32 118 / 105, 4096 x 32 186 / 156; unmasked 2048 x 16 45.5 / 67.7, 4096 x 16 157 / 140, 6000 x 16 341 / 405, 2048 x 32 87.3 / 76.8,
+// 3000 x 32 190 / 215, 4096 x 32 314 / 274.
+static int attn_owners(int nfrag, int n_heads, int causal, int num_cu)
+{
+    auto cost = [&](int owners, double each) {
+        const double blocks = (double)((nfrag + 2 * owners - 1) / (2 * owners)) * n_heads;
+        const int streams = 8 / owners;
+        const double longest = each * ((nfrag + streams - 1) / streams);
+        if (!causal) return ceil(blocks / num_cu) * (5.0 + longest);
+        return fmax(5.0 + longest, 1.1 * blocks * (5.0 + 0.5 * longest) / num_cu);
+    };
+    return cost(2, 1.06) < cost(4, 1.0) ? 2 : 4;
+}
+
 static size_t attn_stats_bytes(int T, int n_heads) { return ((size_t)T * n_heads * sizeof(float2) + 255) / 256 * 256; }
 
 }  // namespace dymoe
@@ -549,41 +776,30 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     const float s = (scale > 0.0f) ? scale : 1.0f / sqrtf((float)head_dim);
     const float scale_log2 = s * 1.44269504088896340736f;
     const int nfrag = (T + 31) / 32;
-    // Few fragments over all heads: a workgroup per 32-token fragment, its wavefronts sharing the streamed tokens (many
-    // workgroups, operands straight from global memory).  Else a workgroup per 128 tokens with the streamed operand in LDS:
-    // per logits tile several times cheaper, but a serial chain of all the tokens, 1 us per 32 of them, however few
-    // heads there are.  Whole score, us, narrow / wide by tokens x heads (fragments):
-    //                      d = 128, causal   unmasked    d = 64, causal   unmasked
-    //    1024 x 16 (512)      40 /  41       41 /  39       24 /  32      25 /  30
-    //    4096 x  4 (512)     126 / 131      128 / 136       68 /  99      71 / 103
-    //    1500 x 12 (564)      64 /  61       80 /  66       37 /  48      46 /  53
-    //    2500 x  8 (632)      79 /  87      120 / 100       45 /  66      66 /  79
-    //    4096 x  6 (768)     184 / 135      188 / 138       99 / 100     102 / 105
-    //    2048 x 16 (1024)    100 /  71      130 /  70       55 /  54      70 /  52
-    // so the line lies at 512 for d = 128, and at 768 for d = 64, where a wavefront's share of the products is half as long (three
-    // workgroups per compute unit instead of two).  There, narrow / wide, causal and not: 1500 x 16 (752) 33 / 44 and 44 / 52,
-    // 993 x 24 (768) 33 / 34 and 34 / 38, 3000 x 8 (752) 55 / 74 and 76 / 91, 6000 x 4 (752) 100 / 139 and 137 / 173, 16500 x 1
-    // (516) 190 / 359 and 356 / 458; error against 64 bits 7e-8 / 1.6e-7.
-    // (Below 32 fragments the narrow pair stays for every number of heads: its four partial sums per key round less.)
-    const bool wide = nfrag >= dymoe::kAtWideFrags &&
-                      (long)nfrag * n_heads > (head_dim == 64 ? dymoe::kAtNarrowFrags<64> : dymoe::kAtNarrowFrags<128>);
+    const bool wide = dymoe::attn_wide(nfrag, n_heads, head_dim);
+    const int owners = dymoe::attn_owners(nfrag, n_heads, causal, ctx->num_cu);
     // A dimension of a launch holds fewer than 2^32 threads: beyond that (from 275 GB of queries on) a head per y, as in the
-    // narrow pair's launches; 4096 x 32 takes 201 us that way and 199 in one dimension.
-    const long blocks = (nfrag + 3L) / 4 * n_heads;
+    // narrow pair's launches.
+    const int nblk = (nfrag + 2 * owners - 1) / (2 * owners);
+    const long blocks = (long)nblk * n_heads;
+    const int threads = wide ? dymoe::kAtWideThreads : dymoe::kAtThreads;
     const dim3 grid = !wide ? dim3((unsigned)nfrag, (unsigned)n_heads)
-                      : blocks * dymoe::kAtThreads < 1L << 32 ? dim3((unsigned)blocks)
-                                                              : dim3((unsigned)((nfrag + 3) / 4), (unsigned)n_heads);
+                      : blocks * dymoe::kAtWideThreads < 1L << 32 ? dim3((unsigned)blocks)
+                                                              : dim3((unsigned)nblk, (unsigned)n_heads);
 #define DYMOE_ATTN_PAIR(STATS_, COLSUM_)                                                                               \
     do {                                                                                                               \
-        dymoe_launch(ctx, DYMOE_K_ATTN_STATS, STATS_, grid, dim3(dymoe::kAtThreads), 0, st, qb, kbp, T, n_heads, group,  \
+        dymoe_launch(ctx, DYMOE_K_ATTN_STATS, STATS_, grid, dim3(threads), 0, st, qb, kbp, T, n_heads, group,            \
                      scale_log2, causal, stats);                                                                       \
         DYMOE_HIP_LAUNCH_CHECK();                                                                                      \
-        dymoe_launch(ctx, DYMOE_K_ATTN_COLSUM, COLSUM_, grid, dim3(dymoe::kAtThreads), 0, st, qb, kbp, T, n_heads, group, \
+        dymoe_launch(ctx, DYMOE_K_ATTN_COLSUM, COLSUM_, grid, dim3(threads), 0, st, qb, kbp, T, n_heads, group,          \
                      scale_log2, causal, (const float2*)stats, partial);                                               \
     } while (0)
+#define DYMOE_ATTN_WIDE(D_, OWNERS_) \
+    DYMOE_ATTN_PAIR((dymoe::attn_rowstats_wide_kernel<D_, OWNERS_>), (dymoe::attn_colsum_wide_kernel<D_, OWNERS_>))
 #define DYMOE_ATTN_LAUNCH(D_)                                                                                          \
     do {                                                                                                               \
-        if (wide) DYMOE_ATTN_PAIR(dymoe::attn_rowstats_wide_kernel<D_>, dymoe::attn_colsum_wide_kernel<D_>);           \
+        if (wide && owners == 4) DYMOE_ATTN_WIDE(D_, 4);                                                               \
+        else if (wide) DYMOE_ATTN_WIDE(D_, 2);                                                                         \
         else DYMOE_ATTN_PAIR(dymoe::attn_rowstats_kernel<D_>, dymoe::attn_colsum_kernel<D_>);                          \
     } while (0)
     if (head_dim == 64) DYMOE_ATTN_LAUNCH(64);

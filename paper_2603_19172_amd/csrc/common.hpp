@@ -316,4 +316,29 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// 16 bytes a lane, global memory -> LDS[lds_addr_lane0 + 16 * lane] without passing through registers.
+// The instruction is issued from inline assembly so that the compiler does not
+// make every later LDS read wait for it; completion is awaited explicitly
+// (wait_lds_copies) before the workgroup barrier that publishes the data.
+__device__ __forceinline__ void lds_copy16(const char* base, uint32_t lane_offset, uint32_t lds_addr_lane0)
+{
+    // base is the same for the whole wavefront (scalar registers), lane_offset an unsigned 32-bit byte offset
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_addr_lane0), "v"(lane_offset), "s"(base)
+                 : "memory");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_lds_copies()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+    // the same wait once more in a form the compiler's own bookkeeping reads
+    // (vmcnt = N, no wait on the export and LDS/scalar counters): it then knows
+    // that older loads have completed and does not wait for them again later,
+    // when such a wait would also cover copies issued in between
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
 }  // namespace dymoe

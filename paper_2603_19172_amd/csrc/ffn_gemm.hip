@@ -356,30 +356,6 @@ constexpr int ktile_loads()
 // positions for 16 consecutive rows, i.e. on all banks once.
 // Wavefront w fills rows 32 i + 4 w .. + 3 (i = 0 .. NTF-1); a thread's rows
 // all have the same r & 15, hence the same source chunk.
-// The instruction is issued from inline assembly so that the compiler does not
-// make every later LDS read wait for it; completion is awaited explicitly
-// (wait_tile_copies) before the workgroup barrier that publishes the tile.
-__device__ __forceinline__ void lds_copy16(const char* base, uint32_t lane_offset, uint32_t lds_addr_lane0)
-{
-    // base is the same for the whole wavefront (scalar registers), lane_offset an unsigned 32-bit byte offset
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_addr_lane0), "v"(lane_offset), "s"(base)
-                 : "memory");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_tile_copies()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-    // the same wait once more in a form the compiler's own bookkeeping reads
-    // (vmcnt = N, no wait on the export and LDS/scalar counters): it then knows
-    // that older loads have completed and does not wait for them again later,
-    // when such a wait would also cover copies issued in between
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
 constexpr int kRowsPerCopy = 4 * kGmWaves;      // tile rows the workgroup fills with one instruction per wavefront
 
 template <int NTF>
@@ -475,7 +451,7 @@ __device__ __forceinline__ void gemm_tile(
     load_strip<BITS>(sb, kt_begin, rb);
     adopt_strip<BITS>(ra, ra);
     adopt_strip<BITS>(rb, rb);
-    wait_tile_copies<0>();
+    wait_lds_copies<0>();
     __syncthreads();
     int buf = 0;          // buffer of tile kt
     for (int kt = kt_begin; kt < kt_end; kt++) {
@@ -516,7 +492,7 @@ __device__ __forceinline__ void gemm_tile(
             // (a wait placed there would also wait for the copies just issued)
             __builtin_amdgcn_sched_barrier(0);
         }
-        wait_tile_copies<ktile_loads<BITS>()>();
+        wait_lds_copies<ktile_loads<BITS>()>();
         __syncthreads();
         buf ^= 1;
         xa = xa0 + (uint32_t)(buf * kXsBufBytes);

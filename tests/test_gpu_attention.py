@@ -35,8 +35,8 @@ def _run(ctx, q, k, causal, scale=0.0):
 
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(16, 2, 2, 64), (77, 4, 2, 128), (1, 2, 1, 64), (33, 3, 3, 64),
                                         (160, 8, 2, 128), (512, 32, 8, 128),
-                                        # many tokens, few heads (512 fragments over all heads at most: operands
-                                        # straight from memory): ragged ends, a head count the XCD mapping does not
+                                        # many tokens, few heads (operands straight from memory up to 320 fragments
+                                        # over all heads of 128 values, 640 of 64): ragged ends, a head count the XCD mapping does not
                                         # divide, both head sizes
                                         (993, 8, 2, 128), (1100, 3, 3, 64), (1057, 5, 1, 128), (2048, 8, 8, 64),
                                         (4100, 2, 1, 128)])
@@ -53,9 +53,8 @@ def test_attention_score_matches_the_oracle(ctx, T, Hh, Hkv, d, causal):
     assert abs(got.sum() - 1.0) < 1e-5                      # every query hands out one unit of attention
 
 
-# the LDS-staged kernels need 32 fragments and more than 512 over all heads: both sides of that line, 64-token stages that
-# end whole, half and ragged, head counts that the XCD mapping divides and does not, rounds of blocks that are not whole.
-# The last four reach the second round of 32 blocks per XCD, which a causal mask deals in reverse: 36, 48, 48 and 33 blocks
+# the LDS-staged kernels at 512 fragments over all heads and more: stages of the stream that end whole, half and ragged, head counts that
+# the XCD mapping divides and does not
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(1024, 16, 4, 128), (1025, 16, 4, 128), (1057, 17, 1, 64), (1088, 24, 6, 64),
                                         (1120, 20, 5, 128), (2111, 8, 2, 128), (1100, 32, 8, 128), (1500, 32, 8, 128),
                                         (1500, 32, 8, 64), (4200, 8, 2, 64)])
@@ -68,7 +67,7 @@ def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-# heads of 64 values take the staged kernels from more than 768 fragments on: the last count below that line and the first above it
+# heads of 64 values around 768 fragments
 @pytest.mark.parametrize("T,Hh,Hkv", [(1024, 24, 8), (1025, 24, 8), (6113, 4, 4), (2975, 8, 2)])
 @pytest.mark.parametrize("causal", [True, False])
 def test_attention_score_small_heads_around_the_line(ctx, T, Hh, Hkv, causal):
@@ -77,6 +76,53 @@ def test_attention_score_small_heads_around_the_line(ctx, T, Hh, Hkv, causal):
     ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
     got = _run(ctx, q, k, causal)
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+# the staged kernels' blocks of 128 and of 256 tokens (the rule takes the larger where they fill the chip evenly), just past the lines
+# where they begin; last blocks of one token, one fragment and a fragment and a bit; trips of the stream that end whole and in
+# every remainder; wavefronts whose tokens lie past the end
+@pytest.mark.parametrize("T,Hh,Hkv,d", [(321, 30, 5, 128), (353, 32, 8, 128), (385, 32, 8, 128), (449, 24, 24, 128), (513, 20, 5, 128),
+                                        (1537, 5, 5, 128), (1665, 5, 1, 128), (2048, 32, 8, 128), (1900, 34, 17, 128), (2561, 24, 4, 128),
+                                        (673, 32, 8, 64), (705, 30, 10, 64), (1025, 21, 3, 64), (3073, 5, 5, 64), (2049, 32, 4, 64)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_score_staged_blocks(ctx, T, Hh, Hkv, d, causal):
+    cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=360 + T)
+    q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, d, boost=1.0)
+    ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+    got = _run(ctx, q, k, causal)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("rise", [90.0, -90.0])
+def test_attention_score_logits_that_rise_along_the_keys(ctx, T, Hh, d, causal, rise):
+    """The staged kernels raise their reference exponent only when a sum outgrows it: logits that climb (and fall) by 90 from the
+    first key to the last, so that it is raised many times, or never after the first fragment."""
+    q, k = (synth.normal_bf16(77 + T, 9200 + i, (T, Hh, d), 0.5) for i in range(2))
+    def values(bits):
+        return (bits.astype(np.uint32) << 16).view(np.float32)
+    def bf16(x):
+        return (np.ascontiguousarray(x, np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    qf, kf = values(q).copy(), values(k).copy()
+    qf[:, :, 0] = np.sqrt(d)
+    kf[:, :, 0] = rise * np.arange(T)[:, None] / T
+    q, k = bf16(qf), bf16(kf)
+    ref = O.token_score_attention(q, k, Hh, Hh, causal=causal)
+    got = _run(ctx, q, k, causal)
+    # arguments of the exponentials of up to 130 in base 2: a rounding of 2^-18 there is 5e-6 of a probability
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64), (1025, 32, 128)])
+def test_attention_score_a_query_that_is_no_number_spoils_the_keys_it_sees(ctx, T, Hh, d):
+    q, k = (synth.normal_bf16(277 + T, 9300 + i, (T, Hh, d), 1.0) for i in range(2))
+    ref = O.token_score_attention(q, k, Hh, Hh, causal=True)
+    bad = T // 2 + 5
+    q[bad, 3, 7] = 0x7FC0
+    got = _run(ctx, q, k, True)
+    assert np.isnan(got[:bad + 1]).all()
+    assert np.allclose(got[bad + 1:], ref[bad + 1:], rtol=RTOL, atol=ATOL)
 
 
 # the sum over heads: one or two of them, batches of sixteen, whole, short by one and with one head left
