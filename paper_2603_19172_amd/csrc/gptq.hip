@@ -603,9 +603,13 @@ __device__ __forceinline__ int hs_swizzle(int c) { return (c ^ (c >> 3)) & 7; }
 constexpr int kHsSamples = 64;
 constexpr int kHsThreads = 256;
 
+// Bound: per step and workgroup 96 KB through LDS (0.34 us), 1024 cycles of matrix instructions and the transposition beside them; 1.8 us for
+// a compute unit's three workgroups.  Three, because K = 4096 has 528 tiles: with two on a compute unit 16 of them were a
+// round of their own.  The mirror image leaves 16 bytes a lane at a time.  2048 samples of 4096 columns 102 -> 77 us, 130 samples 38 -> 19.5
+// (67 MB written), 2048 of 3072 63 -> 51.
 // PARTS: groups of four wavefronts that take the sample steps in turn; their sums meet in LDS, the first part's first.
 template <int PARTS>
-__global__ __launch_bounds__(PARTS* kHsThreads) void gptq_hessian_kernel(const uint16_t* __restrict__ x, long n, long K,
+__global__ __launch_bounds__(PARTS* kHsThreads, PARTS == 1 ? 3 : 2) void gptq_hessian_kernel(const uint16_t* __restrict__ x, long n, long K,
                                                                         int accumulate, float* __restrict__ hess)
 {
     __shared__ uint4 s_ops[PARTS][2][kHsTile * (kHsSamples / 8)];      // [part][operand][column][chunk of 8 samples]
@@ -664,8 +668,8 @@ __global__ __launch_bounds__(PARTS* kHsThreads) void gptq_hessian_kernel(const u
             for (int pr = 0; pr < 4; pr++) {
                 const uint32_t a = reinterpret_cast<const uint32_t*>(&raw[2 * pr])[dw];
                 const uint32_t b = reinterpret_cast<const uint32_t*>(&raw[2 * pr + 1])[dw];
-                even[pr] = (a & 0xffffu) | (b << 16);
-                odd[pr] = (a >> 16) | (b & 0xffff0000u);
+                even[pr] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+                odd[pr] = __builtin_amdgcn_perm(b, a, 0x07060302u);
             }
             out[2 * dw] = make_uint4(even[0], even[1], even[2], even[3]);
             out[2 * dw + 1] = make_uint4(odd[0], odd[1], odd[2], odd[3]);
@@ -712,22 +716,28 @@ __global__ __launch_bounds__(PARTS* kHsThreads) void gptq_hessian_kernel(const u
 #pragma unroll
             for (int i = 0; i < 16; i++) acc[a >> 1][a & 1][i] += s_sum[(16 * a + i) * kHsThreads + tid];
     }
-    // register i of lane (ln, kb): row 8 (i / 4) + 4 kb + i % 4 of the 32 x 32 tile, column ln
+    // register i of lane (ln, kb): row 8 (i / 4) + 4 kb + i % 4 of the 32 x 32 tile, column ln: four registers are four neighbours of the
+    // mirror image (K and the rows' starts are multiples of 4: all inside or all outside)
 #pragma unroll
     for (int a = 0; a < 2; a++)
 #pragma unroll
-        for (int b = 0; b < 2; b++)
+        for (int b = 0; b < 2; b++) {
+            const long c = j0 + 64 * wj + 32 * b + ln;
+            if (c >= K) continue;
 #pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const long r = i0 + 64 * wi + 32 * a + 8 * (i >> 2) + 4 * kb + (i & 3);
-                const long c = j0 + 64 * wj + 32 * b + ln;
-                if (r < K && c < K) {
-                    float val = acc[a][b][i];
-                    if (accumulate) val += hess[r * K + c];
-                    hess[r * K + c] = val;
-                    if (ti != tj) hess[c * K + r] = val;
+            for (int i0r = 0; i0r < 4; i0r++) {
+                const long r = i0 + 64 * wi + 32 * a + 8 * i0r + 4 * kb;
+                if (r >= K) continue;
+                float val[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    val[i] = acc[a][b][4 * i0r + i];
+                    if (accumulate) val[i] += hess[(r + i) * K + c];
+                    hess[(r + i) * K + c] = val[i];
                 }
+                if (ti != tj) store_global(hess + c * K + r, make_float4(val[0], val[1], val[2], val[3]));
             }
+        }
 }
 
 // ---------------------------------------------------------------------------
@@ -1227,9 +1237,10 @@ int dymoe_gptq_hessian(dymoe_ctx* ctx, const void* x_bf16, long n, long K, int a
                      (const uint16_t*)x_bf16, n, K, accumulate, hess);
     };
     // Not more tiles than compute units: a tile's steps are a chain of 1.3 us each (load, transpose, store, barriers,
-    // products), and two parts of a workgroup share it.  One part / two, us: 4096 samples of 256 columns 69.5 / 56.9, 2216 of
-    // 960 44.6 / 38.1, 2048 of 2048 43.7 / 37.5, 2048 of 2816 48.5 / 42.3, 1000 of 512 26.9 / 24.1; 300 of 960 16.1 / 16.7 (the
-    // exchange costs more than three steps less give).  With more tiles the other workgroups of a compute unit fill the gaps.
+    // products), and two parts of a workgroup share it.  One part / two, us: 4096 samples of 256 columns 65.7 / 50.8, 2216 of
+    // 960 39.9 / 32.1, 2048 of 2048 38.9 / 32.0, 2048 of 2816 43.0 / 38.4, 1000 of 512 20.2 / 17.0; 300 of 960 10.1 / 10.4 (the
+    // exchange costs more than three steps less give).  With more tiles the other workgroups of a compute unit fill the gaps: 2048 of
+    // 3072 50.3 / 60.3, of 4096 77.6 / 91.8.
     if (tiles <= ctx->num_cu && n > 8 * kHsSamples) go(gptq_hessian_kernel<2>, 2);
     else go(gptq_hessian_kernel<1>, 1);
     DYMOE_HIP_LAUNCH_CHECK();
