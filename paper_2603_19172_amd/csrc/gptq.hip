@@ -798,85 +798,128 @@ __global__ __launch_bounds__(256) void gptq_reverse_kernel(const float* __restri
     }
 }
 
-// The 16 columns p .. p + 15 of the Cholesky factor of the 64 x 64 block in LDS (row stride 68), by one wavefront: a lane per
-// row with its 16 values in registers, pivots and multipliers through v_readlane.  Also the 16 x 16 block on the diagonal as
-// the solving wavefronts read it (s_q[c][row % 4][row / 4]) and the diagonal with its reciprocals.
+// x of lane N of every row of sixteen lanes, to the row's sixteen lanes
+template <int N>
+__device__ __forceinline__ float row_bcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xF, 0xF, true));
+}
+
+// a[J + i] = fma(x of lane J + i of the row of sixteen, y, a[J + i]), i = 0 .. N - 1: the broadcast is part of the multiply-add, which the
+// compiler makes two instructions of.  (The waits: a value that is read across lanes must be two wait states old.)
+#define DYMOE_FMAC_BCAST(A_, I_) "v_fmac_f32_dpp %[" #A_ "], %[x], %[y] row_newbcast:%[" #I_ "] row_mask:0xf bank_mask:0xf\n\t"
+template <int J, int N>
+__device__ __forceinline__ void gq_fmac_bcast(float (&a)[16], float x, float y)
+{
+    if constexpr (N >= 7) {
+        asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) DYMOE_FMAC_BCAST(a1, j1) DYMOE_FMAC_BCAST(a2, j2)
+            DYMOE_FMAC_BCAST(a3, j3) DYMOE_FMAC_BCAST(a4, j4) DYMOE_FMAC_BCAST(a5, j5)
+            DYMOE_FMAC_BCAST(a6, j6)
+            : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2]), [a3] "+v"(a[J + 3]), [a4] "+v"(a[J + 4]),
+              [a5] "+v"(a[J + 5]), [a6] "+v"(a[J + 6])
+            : [x] "v"(x), [y] "v"(y), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2), [j3] "n"(J + 3), [j4] "n"(J + 4), [j5] "n"(J + 5),
+              [j6] "n"(J + 6));
+        gq_fmac_bcast<J + 7, N - 7>(a, x, y);
+    } else if constexpr (N >= 4) {
+        asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) DYMOE_FMAC_BCAST(a1, j1) DYMOE_FMAC_BCAST(a2, j2)
+            DYMOE_FMAC_BCAST(a3, j3)
+            : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2]), [a3] "+v"(a[J + 3])
+            : [x] "v"(x), [y] "v"(y), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2), [j3] "n"(J + 3));
+        gq_fmac_bcast<J + 4, N - 4>(a, x, y);
+    } else if constexpr (N >= 2) {
+        asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) DYMOE_FMAC_BCAST(a1, j1) "s_nop 1"
+            : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1])
+            : [x] "v"(x), [y] "v"(y), [j0] "n"(J), [j1] "n"(J + 1));
+        gq_fmac_bcast<J + 2, N - 2>(a, x, y);
+    } else if constexpr (N >= 1) {
+        asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) "s_nop 1"
+            : [a0] "+v"(a[J])
+            : [x] "v"(x), [y] "v"(y), [j0] "n"(J));
+        gq_fmac_bcast<J + 1, N - 1>(a, x, y);
+    }
+}
+#undef DYMOE_FMAC_BCAST
+
+// The Cholesky factor of the 16 x 16 block whose row lane % 16 the lane holds, by one wavefront (its four rows of sixteen lanes do
+// the same): pivots and multipliers through the data-parallel primitives, which the multiply-adds take as operands.  a: the row,
+// replaced by the factor's (what stands right of the diagonal is worth nothing).
+// Column C's chain is pivot, estimate, root, quotient, column C + 1; the column before goes to the other columns meanwhile.
+template <int C>
+__device__ __forceinline__ void gq_chol_column(float (&a)[16], float less_before, float before)
+{
+    // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each (finite operands; see
+    // the step kernel for infinite ones)
+    const float d = row_bcast<C>(a[C]);
+    const float y = __builtin_amdgcn_rsqf(d);
+    if constexpr (C > 0 && C < 15) {
+        gq_fmac_bcast<C + 1, 15 - C>(a, less_before, before);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const float s0 = d * y, l0 = a[C] * y;
+    const float sq = __builtin_fmaf(__builtin_fmaf(-s0, s0, d), 0.5f * y, s0);
+    const float l = __builtin_fmaf(__builtin_fmaf(-sq, l0, a[C]), y, l0);
+    const float less = -l;
+    if constexpr (C < 15) a[C + 1] = __builtin_fmaf(row_bcast<C + 1>(less), l, a[C + 1]);
+    a[C] = ((threadIdx.x & 15) == C) ? sq : l;
+    if constexpr (C < 15) gq_chol_column<C + 1>(a, less, l);
+}
+
+// Piece p of the diagonal block in LDS (rows and columns 16 p .. 16 p + 15, row stride kGqLd) becomes its Cholesky factor, by one
+// wavefront; also as the solving wavefronts read it (s_q[c][row % 4][row / 4]) and its diagonal with the reciprocals.
 constexpr int kGqLd = kGqGroup + 4;
 __device__ __forceinline__ void gq_chol_piece(float* s_m, int p, float* s_q, float2* s_inv)
 {
-    const int row = threadIdx.x & (kWave - 1);
-    float a[16], dg = 0.0f;
-    bool ordinary = true;
+    const int lane = threadIdx.x & (kWave - 1), row = lane & 15;
+    float* const own = s_m + (16 * p + row) * kGqLd + 16 * p;
+    float a[16], dg;
+    auto diagonal = [&] {
+        dg = a[0];
+#pragma unroll
+        for (int c = 1; c < 16; c++) dg = (row == c) ? a[c] : dg;
+    };
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-        const float4 t = *reinterpret_cast<const float4*>(s_m + row * kGqLd + p + 4 * c);
+        const float4 t = *reinterpret_cast<const float4*>(own + 4 * c);
         a[4 * c] = t.x; a[4 * c + 1] = t.y; a[4 * c + 2] = t.z; a[4 * c + 3] = t.w;
     }
-#pragma unroll
-    for (int c = 0; c < 16; c++) {
-        const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[c]), p + c));
-        // square root and quotient: the hardware's estimate of 1 / sqrt(d) and one residual step each (finite operands; see
-        // the step kernel for infinite ones)
-        const float y = __builtin_amdgcn_rsqf(d);
-        const float s0 = d * y, l0 = a[c] * y;
-        const float sq = __builtin_fmaf(__builtin_fmaf(-s0, s0, d), 0.5f * y, s0);
-        float l = __builtin_fmaf(__builtin_fmaf(-sq, l0, a[c]), y, l0);
-        l = (row == p + c) ? sq : l;
-        ordinary &= d > 1e-30f && d < 1e30f;
-        a[c] = l;
-#pragma unroll
-        for (int j = c + 1; j < 16; j++) {
-            const float lj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), p + j));
-            a[j] = __builtin_fmaf(-l, lj, a[j]);
-        }
-    }
-    if (!ordinary) {                                                // the same in every lane
+    gq_chol_column<0>(a, 0.0f, 0.0f);
+    diagonal();
+    if (!__all(dg > 1e-15f && dg < 1e15f)) {
         // a pivot so large or small that the estimate's steps may leave the range (or none at all: NaN): root and division as
-        // they are, in LDS
+        // they are, in LDS (the wavefront's rows of lanes write the same values)
 #pragma unroll 1
         for (int c = 0; c < 16; c++) {
-            const float root = sqrtf(s_m[(p + c) * kGqLd + p + c]);
-            const float l = (row == p + c) ? root : s_m[row * kGqLd + p + c] / root;
-            s_m[row * kGqLd + p + c] = l;
-            for (int j = c + 1; j < 16; j++)
-                s_m[row * kGqLd + p + j] = __builtin_fmaf(-l, s_m[(p + j) * kGqLd + p + c], s_m[row * kGqLd + p + j]);
+            const float root = sqrtf(s_m[(16 * p + c) * kGqLd + 16 * p + c]);
+            const float l = (row == c) ? root : own[c] / root;
+            own[c] = l;
+            for (int j = c + 1; j < 16; j++) own[j] = __builtin_fmaf(-l, s_m[(16 * p + j) * kGqLd + 16 * p + c], own[j]);
         }
 #pragma unroll
-        for (int c = 0; c < 16; c++) a[c] = s_m[row * kGqLd + p + c];
+        for (int c = 0; c < 16; c++) a[c] = own[c];
+        diagonal();
     }
+    if (lane < 16) {
 #pragma unroll
-    for (int c = 0; c < 4; c++)
-        *reinterpret_cast<float4*>(s_m + row * kGqLd + p + 4 * c) = make_float4(a[4 * c], a[4 * c + 1], a[4 * c + 2], a[4 * c + 3]);
-    const int lr = row - p;
-    if (lr >= 0 && lr < 16) {
+        for (int c = 0; c < 4; c++) *reinterpret_cast<float4*>(own + 4 * c) = make_float4(a[4 * c], a[4 * c + 1], a[4 * c + 2], a[4 * c + 3]);
 #pragma unroll
-        for (int c = 0; c < 16; c++) {
-            s_q[(p + c) * kGqChunk + (lr & 3) * 4 + (lr >> 2)] = a[c];
-            dg = (lr == c) ? a[c] : dg;
-        }
-        s_inv[row] = make_float2(dg, 1.0f / dg);
+        for (int c = 0; c < 16; c++) s_q[(16 * p + c) * kGqChunk + (row & 3) * 4 + (row >> 2)] = a[c];
+        s_inv[16 * p + row] = make_float2(dg, 1.0f / dg);
     }
 }
 
-// One 16 x 16 tile (t, tt) of the block loses the products of the 16 columns from p on: m[row, col] = fma(-L[row, c], L[col, c],
-// m[row, col]), c ascending.
-__device__ __forceinline__ void gq_chol_tile(float* s_m, int p, int t, int tt)
+// One 16 x 16 tile loses the products of 16 columns c, ascending: acc[row, col] = fma(-x[row, c], y[col, c], acc[row, col]).  x: where
+// lane (rg, cl) finds -x[row cl, c = rg], x_step: four columns further; y likewise (y[col cl, c = rg]), row stride kGqLd.
+__device__ __forceinline__ void gq_tile_less(f32x4_t& acc, const float* x, int x_step, float sign, const float* y)
 {
-    const int lane = threadIdx.x & (kWave - 1), rg = lane >> 4, cl = lane & 15;
-    float* const at = s_m + (16 * t + 4 * rg) * kGqLd + 16 * tt + cl;
-    f32x4_t acc;
-    float x[4], y[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) acc[i] = at[i * kGqLd];
+    float xv[4], yv[4];
 #pragma unroll
     for (int kk = 0; kk < 4; kk++) {
-        x[kk] = -s_m[(16 * t + cl) * kGqLd + p + 4 * kk + rg];
-        y[kk] = s_m[(16 * tt + cl) * kGqLd + p + 4 * kk + rg];
+        xv[kk] = sign * x[kk * x_step];
+        yv[kk] = y[4 * kk];
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < 4; kk++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[kk], y[kk], acc, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; i++) at[i * kGqLd] = acc[i];
+    for (int kk = 0; kk < 4; kk++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[kk], yv[kk], acc, 0, 0, 0);
 }
 
 // Where P of step s has its 64 columns `block`: in v's block row s, which nothing else needs any more (to the left of the
@@ -889,23 +932,26 @@ __device__ __forceinline__ const float* gq_p_block(const float* v, long K, const
 }
 
 // Step k of the factorisation in one launch.  The first K / 64 workgroups solve: workgroup jb takes step k - 1 out of the diagonal
-// block and out of its own block of v, makes the diagonal block's Cholesky factor and, 16 columns behind it, the substitution.
+// block and out of its own block of v, makes the diagonal block's Cholesky factor and substitutes.
 // The others bring the rest of v forward, steps in pairs (a panel: steps 2 q and 2 q + 1), so that a block of v is read and
 // written once per panel:
 //   k = 2 q + 2   panel q into the block pairs q + 1 and q + 2 (columns and rows) and into some of the blocks behind them
 //   k = 2 q + 3   panel q into the other blocks; step 2 q + 2 alone into block row and column 2 q + 4, which step 2 q + 4 needs
-// The launch lasts as long as its chain, or, for the first steps of a large K, as the matrix products: 1 us to start, 2 for the
-// operands, 2 of products, 5 stages of 1.4 to 1.9 in which one wavefront factors 16 columns, three bring the diagonal block
-// forward and four substitute the 16 columns before.  K = 4096: 20 us a step on average, 15 to 17 for the last ones; as two launches a step (substitution
-// 9 us, update and Cholesky 13 to 25 with v crossing memory in every one of them) 28.
+// A workgroup takes more than half of a compute unit's LDS and so has it to itself: beside tiles a solver took 3.5 us longer.
+// The launch lasts as long as the solver's chain (11 us and 2.3 to the next launch), or, for the first steps of a large K, as the tiles.
+// K = 4096: 1345 -> 1160 us, 1024: 259 -> 212, 256: 65 -> 54 (with solvers beside three tiles on a compute unit, step k - 1's products in
+// front of the chain, and a lane per row in the piece's factor).  Beyond 5120 columns the tiles are all there is and three of
+// them on a compute unit were as good (8192: 5.55 -> 5.73 ms, 14336: 25.8 -> 26.1).
 // The quotient is the product with the reciprocal and one residual step.  For finite operands that differs from a division
 // in the last place at most; an infinite operand or quotient gives NaN where the division gives infinity, but it has no
 // place in a positive definite matrix: what it is subtracted from, a later pivot, becomes NaN either way.
 constexpr int kGqStepThreads = 512;
-constexpr int kGqStepLds = 3 * kGqGroup * kGqGroup;                 // floats: a tile's operands of 64 columns c
+constexpr int kGqTileLds = 3 * kGqGroup * kGqGroup;                 // floats: a tile's operands of 64 columns c, one of two buffers
+constexpr int kGqPLd = kGqGroup + 16;                               // row stride of P's blocks in the solver: c and c + 1 on other banks
 
 // Tiles (pairs of block rows x pairs of block columns) of panel q: `near` of the pairs q + 1 and q + 2 and `first` of the
 // others in the first launch, `later` in the second.  single: half tiles that the second launch brings forward by one step.
+// A launch's tiles are taken by halves (a block row each).
 struct GqWide {
     long q, pairs, near, first, later, single;
 };
@@ -928,237 +974,415 @@ static inline GqWide gq_wide(long nb, long k)
     if (k & 1) w.single = nb - (k + 1) + w.q + 2;                   // block column k + 1 from the diagonal down, block row k + 1
     return w;
 }
-static inline long gq_wide_blocks(const GqWide& w, long k) { return (k & 1) ? w.single + 2 * w.later : 2 * (w.near + w.first); }
-
-__global__ __launch_bounds__(kGqStepThreads, 6) void gptq_step_kernel(float* v, long K, long k, float* slots, float* __restrict__ u,
-                                                                     GqWide wide)
+static inline long gq_wide_blocks(const GqWide& w, long k)
 {
-    extern __shared__ __attribute__((aligned(16))) float s_all[];   // kGqStepLds at least
-    const long nb = K / kGqGroup;
+    if (k & 1) return w.single + 2 * w.later;
+    return w.near ? 2 * (w.near + w.first) - 1 - (w.q + 1) : 0;     // without the halves in block row k
+}
+
+// The tiles' part of a launch: 64 x 128 block rows of tiles dealt out to the workers, of whom those behind the first `early` start when a
+// solver has left them a compute unit (kGqSkip blocks later).  32 x 32 of a block a wavefront; the operands of 64 columns c at a
+// time go straight to LDS, and they and the next block's values are on their way while the products before run.
+// Bound: fp32 matrix instructions, 3.6 us a block at 2.27 GHz; 4.4 to 5.4 measured, and 2.5 to start.  (Through registers, operands read from LDS where
+// they are used: 6.2.)
+constexpr int kGqSkip = 3;
+__device__ __forceinline__ void gq_step_tiles(float* s_all, float* v, long K, int k, const float* slots, const GqWide& wide, int worker,
+                                              int workers, int early, int blocks)
+{
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rg = lane >> 4, cl = lane & 15;
-    if ((long)blockIdx.x >= nb) {
-        // ---- 64 x 128, a block row of a tile, 32 x 32 of it a wavefront
-        const long last = nb - 1, q = wide.q;
-        const int wi = wave >> 2, wq = wave & 3;
-        const long at0 = (long)blockIdx.x - nb, n_single = (k & 1) ? wide.single : 0;
-        const bool single = at0 < n_single;
-        long ib, sj;
-        if (single) {
-            const long below = nb - (k + 1);
-            ib = at0 < below ? k + 1 + at0 : k + 1;
-            sj = at0 < below ? q + 2 : at0 - below;
+    const int rg = lane >> 4, cl = lane & 15, wi = wave >> 2, wq = wave & 3;
+    const int last = (int)(K / kGqGroup) - 1, q = (int)wide.q, n_single = (k & 1) ? (int)wide.single : 0;
+    struct Block {
+        int ib, sj, jb, s0;
+        bool single, mine;
+    };
+    auto locate = [&](int at, Block& b) {                           // false: nothing to do there (the same in the whole workgroup)
+        b.single = at < n_single;
+        if (b.single) {
+            const int below = last - k;
+            b.ib = at < below ? k + 1 + at : k + 1;
+            b.sj = at < below ? q + 2 : at - below;
         } else {
-            const long half = at0 - n_single, tile = half >> 1, below = wide.pairs - q - 1;
-            long si;
-            if (!(k & 1) && tile < wide.near) {
-                if (tile < below) { si = q + 1 + tile; sj = q + 1; }
-                else if (tile < wide.pairs) { si = q + 1; sj = tile - below; }
-                else if (tile < wide.pairs + below - 1) { si = q + 2 + tile - wide.pairs; sj = q + 2; }
-                else { si = q + 2; sj = tile - wide.pairs - (below - 1); }
+            // (block row k, the upper half of the pairs si = q + 1, is the solvers')
+            const int below = (int)wide.pairs - q - 1, upper = 2 * below - 1;
+            int half = at - n_single, si;
+            if (!(k & 1) && half < upper) {
+                half++;
+                si = q + 1 + (half >> 1);
+                b.sj = q + 1;
+            } else if (!(k & 1) && half < upper + q + 1) {
+                b.sj = half - upper;
+                si = q + 1;
+                half = 1;
             } else {
-                // m = si - 1 column pairs (without q + 1 and q + 2) of every pair si >= q + 3
-                const long r = ((k & 1) ? tile + wide.first : tile - wide.near) + (q + 2) * (q + 1) / 2;
-                long m = (long)((sqrt(8.0 * (double)r + 1.0) + 1.0) * 0.5);
-                while (m * (m - 1) / 2 > r) m--;
-                while ((m + 1) * m / 2 <= r) m++;
-                si = m + 1;
-                sj = r - m * (m - 1) / 2;
-                if (sj >= q + 1) sj += 2;
+                if (!(k & 1)) half += 2 * (int)wide.pairs - upper - (q + 1);
+                const int tile = half >> 1;
+                if (!(k & 1) && tile < (int)wide.near) {
+                    if (tile < (int)wide.pairs + below - 1) { si = q + 2 + tile - (int)wide.pairs; b.sj = q + 2; }
+                    else { si = q + 2; b.sj = tile - (int)wide.pairs - (below - 1); }
+                } else {
+                    // m = si - 1 column pairs (without q + 1 and q + 2) of every pair si >= q + 3
+                    const int r = ((k & 1) ? tile + (int)wide.first : tile - (int)wide.near) + (q + 2) * (q + 1) / 2;
+                    int m = (int)((sqrtf(8.0f * (float)r + 1.0f) + 1.0f) * 0.5f);
+                    while (m * (m - 1) / 2 > r) m--;
+                    while ((m + 1) * m / 2 <= r) m++;
+                    si = m + 1;
+                    b.sj = r - m * (m - 1) / 2;
+                    if (b.sj >= q + 1) b.sj += 2;
+                }
             }
-            ib = 2 * si + (half & 1);
+            b.ib = 2 * si + (half & 1);
         }
-        const long s0 = single ? k - 1 : 2 * q;
-        const long jb = min(2 * sj + (wq >> 1), last);
-        if (ib > last || (!single && ib == s0 + 2)) return;         // (the same in the whole workgroup)
-        const bool mine = 2 * sj + (wq >> 1) <= last && jb <= ib && (single ? jb == k + 1 || (ib == k + 1 && jb != k) : jb != s0 + 2);
-        // the panel's two steps one after the other through LDS, 64 columns c at a time: rows [c][64], columns [c][128]; the
-        // second step's operands are on their way while the first one's are multiplied
-        float4 sa[2], sb[4];
-        auto fetch = [&](long s) {
+        b.s0 = b.single ? k - 1 : 2 * q;
+        b.jb = min(2 * b.sj + (wq >> 1), last);
+        b.mine = 2 * b.sj + (wq >> 1) <= last && b.jb <= b.ib &&
+                 (b.single ? b.jb == k + 1 || (b.ib == k + 1 && b.jb != k) : b.jb != b.s0 + 2);
+        return b.ib <= last;
+    };
+    int round = worker < early ? 0 : kGqSkip;
+    auto next = [&](Block& b) {                                     // false: no block is left
+        for (;;) {
+            const int at = round < kGqSkip ? round * early + worker : kGqSkip * early + (round - kGqSkip) * workers + worker;
+            if (at >= blocks) return false;
+            round++;
+            if (locate(at, b)) return true;
+        }
+    };
+    // a step's operands: rows [c][64] and two column blocks [c][64] each, straight to LDS
+    const uint32_t lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float*)s_all;
+    auto copy = [&](const Block& b, int s, int buf) {
+        const uint32_t to = lds + (buf * kGqTileLds + wave * 4 * kGqGroup) * 4;
+#pragma unroll
+        for (int o = 0; o < 3; o++) {
             long ld;
-            const float* const pa = gq_p_block(v, K, slots, s, ib, ld);
+            const char* const from = (const char*)gq_p_block(v, K, slots, s, o == 0 ? b.ib : min(2 * b.sj + o - 1, last), ld);
+            const uint32_t row = (uint32_t)ld * 4, at = (4 * wave + rg) * row + cl * 16;
 #pragma unroll
-            for (int i = 0; i < 2; i++) sa[i] = load_global<float4>(pa + ((tid >> 4) + 32 * i) * ld + 4 * (tid & 15));
-            const int f4 = tid & 31;
-            const float* const pb = gq_p_block(v, K, slots, s, min(2 * sj + (f4 >> 4), last), ld);
+            for (int i = 0; i < 2; i++)
+                lds_copy16(from + (long)(32 * i) * row, at, to + (o * kGqGroup * kGqGroup + i * 32 * kGqGroup) * 4);
+        }
+    };
+    // interleaved as in GqTile, with two row and two column tiles: register i of tile (x, y) is row 8 rg + 2 i + x, column
+    // 2 cl + y
+    const uint32_t off = 8 * rg * (uint32_t)K + 2 * cl;
+    auto place = [&](const Block& b) { return v + ((long)b.ib * kGqGroup + 32 * wi) * K + (long)b.jb * kGqGroup + 32 * (wq & 1); };
+    float2 val[8];
+    auto request = [&](const Block& b) {
+        const float* const src = place(b);
+        const bool zero = b.jb == b.s0 || (!b.single && b.jb == b.s0 + 1);      // (block columns of the panel itself: L^-1's part starts here)
 #pragma unroll
-            for (int i = 0; i < 4; i++) sb[i] = load_global<float4>(pb + ((tid >> 5) + 16 * i) * ld + 4 * (f4 & 15));
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        float* const s_b = s_all + kGqGroup * kGqGroup;
-        auto park = [&] {
+        for (int r = 0; r < 8; r++) val[r] = zero ? make_float2(0.0f, 0.0f) : load_global<float2>(src + r * K + off);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    f32x4_t acc[2][2];                                              // negated: fma(-x, y, c) is -fma(x, y, -c)
+    // operands of sixteen columns c, four a product
+    float2 av[2][4], bv[2][4];
+    auto read = [&](int set, int buf, int g) {
+        const float* const ap = s_all + buf * kGqTileLds + (16 * g + rg) * kGqGroup + 32 * wi + 2 * cl;
+        const float* const bp = s_all + buf * kGqTileLds + (1 + (wq >> 1)) * kGqGroup * kGqGroup + (16 * g + rg) * kGqGroup + 32 * (wq & 1) + 2 * cl;
 #pragma unroll
-            for (int i = 0; i < 2; i++) *reinterpret_cast<float4*>(s_all + 4 * (tid + kGqStepThreads * i)) = sa[i];
+        for (int kk = 0; kk < 4; kk++) {
+            av[set][kk] = *reinterpret_cast<const float2*>(ap + kk * 4 * kGqGroup);
+            bv[set][kk] = *reinterpret_cast<const float2*>(bp + kk * 4 * kGqGroup);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int set) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(s_b + 4 * (tid + kGqStepThreads * i)) = sb[i];
-            __syncthreads();
-        };
-        // interleaved as in GqTile, with two row and two column tiles: register i of tile (x, y) is row 8 rg + 2 i + x, column
-        // 2 cl + y
-        f32x4_t acc[2][2];
-        auto multiply = [&] {
-            const float* ap = s_all + rg * kGqGroup + 32 * wi + 2 * cl;
-            const float* bp = s_b + rg * 128 + 32 * wq + 2 * cl;
-#pragma unroll 4
-            for (int kk = 0; kk < kGqGroup / 4; kk++) {
-                const float2 av = *reinterpret_cast<const float2*>(ap + kk * 4 * kGqGroup);
-                const float2 bv = *reinterpret_cast<const float2*>(bp + kk * 512);
-                acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.x, bv.x, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.x, bv.y, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.x, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, acc[1][1], 0, 0, 0);
-            }
-        };
-        fetch(s0);
-        const uint32_t off = 8 * rg * (uint32_t)K + 2 * cl;
-        float* const dst = v + (ib * kGqGroup + 32 * wi) * K + jb * kGqGroup + 32 * (wq & 1);
+        for (int kk = 0; kk < 4; kk++) {
+            const float2 x = av[set][kk], y = bv[set][kk];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.x, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.y, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, y.x, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, y.y, acc[1][1], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // The 64 columns in buffer buf; the last sixteen's products run when the next buffer's first operands are on their way, so that
+    // neither the barrier nor the reads behind it find the matrix cores idle.
+    auto pass = [&](int buf, bool more) {
+#pragma unroll
+        for (int g = 0; g < 3; g++) {
+            read((g + 1) & 1, buf, g + 1);
+            multiply(g & 1);
+        }
+        wait_lds_copies<0>();
+        __syncthreads();
+        if (more) read(0, buf ^ 1, 0);                              // the same in the whole workgroup
+        multiply(1);
+    };
+    Block b, then;
+    if (!next(b)) return;
+    copy(b, b.s0, 0);
+    request(b);
+    wait_lds_copies<0>();
+    __syncthreads();
+    read(0, 0, 0);
+    int buf = 0;
+    for (;;) {
 #pragma unroll
         for (int r = 0; r < 8; r++) {
-            float2 val = make_float2(0.0f, 0.0f);       // (block columns of the panel itself: L^-1's part starts here)
-            if (jb != s0 && (single || jb != s0 + 1)) val = load_global<float2>(dst + r * K + off);
-            acc[r & 1][0][r >> 1] = val.x;
-            acc[r & 1][1][r >> 1] = val.y;
+            acc[r & 1][0][r >> 1] = -val[r].x;
+            acc[r & 1][1][r >> 1] = -val[r].y;
         }
-        park();
-        if (!single) fetch(s0 + 1);
-        multiply();
-        if (!single) {
-            __syncthreads();                            // the first step's operands have been read
-            park();
-            if (jb == s0 + 1) {                         // ... with the panel's second step
+        if (!b.single) {
+            copy(b, b.s0 + 1, buf ^ 1);                             // (that buffer's last readers passed the barrier before)
+            pass(buf, true);
+            buf ^= 1;
+            if (b.jb == b.s0 + 1) {                                 // ... with the panel's second step
 #pragma unroll
                 for (int x = 0; x < 2; x++) acc[x][0] = acc[x][1] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
             }
-            multiply();
         }
-        if (!mine) return;
+        const bool more = next(then);
+        if (more) {
+            copy(then, then.s0, buf ^ 1);
+            request(then);
+        }
+        pass(buf, more);
+        buf ^= 1;
+        if (b.mine) {
+            float* const dst = place(b);
 #pragma unroll
-        for (int r = 0; r < 8; r++) store_global(dst + r * K + off, make_float2(acc[r & 1][0][r >> 1], acc[r & 1][1][r >> 1]));
-        return;
+            for (int r = 0; r < 8; r++) store_global(dst + r * K + off, make_float2(-acc[r & 1][0][r >> 1], -acc[r & 1][1][r >> 1]));
+        }
+        if (!more) return;
+        b = then;
     }
-    // ---- solve
-    float* const s_m = s_all;                                       // diagonal block, 64 rows of 68
-    float* const s_x = s_m + kGqGroup * kGqLd;                      // own block, [column j][c], 64 rows of 68
-    float* const s_q = s_x + kGqGroup * kGqLd;                      // 16 x 16 blocks of the factor's diagonal
+}
+
+// The solver's part: workgroup jb of step k.  Four stages of 16 columns; in each wavefront 0 factors the 16 x 16 piece on the
+// diagonal, then the rows below it and the own block's columns are substituted, 16 rows a wavefront (four lanes a row).  What the
+// stages' tiles need besides -- step k - 1's products, 64 columns deep, and those of the pieces before -- the other wavefronts
+// do while wavefront 0 factors, each tile just in time.
+//   slot (piece being factored)   wavefront 0    6                    7                    1, 2, 3, 5 (16 columns j of the own block each)
+//   0                             P 00           P 10, 20, 21         P 30, 31, 11         P of columns c 0, 1
+//   1                             - 11           - 21, P 22 - 22      - 31, P 32 - 32      - columns 1, P of columns 2, - columns 2
+//   2                             - 22           P 33 - - 33          - 32                 - columns 2, P of columns 3, - - columns 3
+//   3                             - 33                                                     - columns 3
+// (P: products of step k - 1, -: of one piece before; tiles by row and column.)  Wavefront 4 shares wavefront 0's SIMD and only substitutes:
+// beside matrix instructions there the factor of a piece took up to twice as long.
+// Bound: the chain, us: 1.5 to start and for the operands, 1.8 the first slot, 1.3 to 1.5 the others (a factor is 440 instructions of one
+// wavefront, 1.1), 1.1 a substitution.
+__device__ __forceinline__ void gq_step_solve(float* s_all, float* v, long K, long k, float* slots, float* __restrict__ u, long jb)
+{
+    constexpr int kXLd = kGqChunk + 4;
+    float* const s_p = s_all;                                       // P of step k - 1: block k, own block: [c][column]
+    float* const s_m = s_p + 2 * kGqGroup * kGqPLd;                 // diagonal block, [row][column]
+    float* const s_x = s_m + kGqGroup * kGqLd;                      // the own block's 16 columns of the stage, [column j][c]
+    float* const s_q = s_x + kGqGroup * kXLd;                       // 16 x 16 blocks of the factor's diagonal
     float2* const s_inv = reinterpret_cast<float2*>(s_q + kGqGroup * kGqChunk);
-    float* const s_e = reinterpret_cast<float*>(s_inv + kGqGroup);  // [wavefront][c of the 16][column], negated
-    static_assert(2 * kGqGroup * kGqLd + kGqGroup * kGqChunk + 2 * kGqGroup + kGqChunk * kGqGroup <= kGqStepLds, "the solver's blocks fit");
-    __builtin_amdgcn_s_setprio(3);                                  // the launch's longest chain, beside wavefronts that only add work
-    const long jb = blockIdx.x, base = k * kGqGroup;
-    {
-        // columns of block k and of the own block of step k - 1's P into LDS, [block k, own][c][column]: all requested at once (the
-        // workgroups of the launch before left them in other L2s, a microsecond away)
-        const long before = k - 1;
-        const bool with_own = jb > k || (jb < k && k > 0);
-        float4 stage[2][2];
+    float* const s_e = reinterpret_cast<float*>(s_inv + kGqGroup);  // [wavefront][piece][c of the 16][column], negated
+    static_assert(2 * kGqGroup * kGqPLd + kGqGroup * kGqLd + kGqGroup * kXLd + kGqGroup * kGqChunk + 2 * kGqGroup +
+                      4 * 4 * kGqChunk * 16 <= 2 * kGqTileLds, "the solver's blocks fit");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = lane >> 4, cl = lane & 15;
+    const long base = k * kGqGroup, before = k - 1;
+    // rows of 16: of the own block's columns (wavefronts 1, 2, 3, 5), or of the diagonal block (4, 6, 7: rows 1, 2, 3)
+    const bool own = wave == 5 || (wave >= 1 && wave <= 3);
+    const int w4 = wave == 5 ? 3 : wave - 1, drow = wave == 4 ? 1 : wave - 4;
+    if (wave == 0) __builtin_amdgcn_s_setprio(3);                   // the chain, beside wavefronts that only add work
+    // the operands, requested at once (the workgroups of the launch before left them in other L2s, a microsecond away) ...
+    const bool with_own = jb != k && k > 0;
+    float4 stage[2][2];
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+        if (k > 0 && (b == 0 || with_own)) {
+            long ld;
+            const float* const from = gq_p_block(v, K, slots, before, b ? jb : k, ld) + (tid >> 4) * ld + 4 * (tid & 15);
+#pragma unroll
+            for (int i = 0; i < 2; i++) stage[b][i] = load_global<float4>(from + 32 * i * ld);
+        }
+    // ... and the values of the wavefront's tiles, register i of lane (rg, cl): row 4 rg + i, column cl
+    f32x4_t acc[4];
+    // wavefront 0: tile 00 of the diagonal block; 6: 10, 20, 21, 22, 33; 7: 30, 31, 11, 32
+    f32x4_t more;
+    auto diag_tile = [&](f32x4_t& c, int row, int col) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) c[i] = load_global<float>(v + (base + 16 * row + 4 * rg + i) * K + base + 16 * col + cl);
+    };
+    if (own) {
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            // [column j][c]: above the diagonal (rows j of v) as it lies, below it transposed
+            if (jb == k) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) acc[t][i] = (16 * w4 + 4 * rg + i == 16 * t + cl) ? 1.0f : 0.0f;
+            } else if (jb == before) {                              // (L^-1's part starts with its own step)
+                acc[t] = (f32x4_t){0.0f, 0.0f, 0.0f, 0.0f};
+            } else if (jb > k) {
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    acc[t][i] = load_global<float>(v + (jb * kGqGroup + 16 * w4 + 4 * rg + i) * K + base + 16 * t + cl);
+            } else {
+                const float4 col = load_global<float4>(v + (base + 16 * t + cl) * K + jb * kGqGroup + 16 * w4 + 4 * rg);
+                acc[t][0] = col.x; acc[t][1] = col.y; acc[t][2] = col.z; acc[t][3] = col.w;
+            }
+        }
+    } else if (wave == 0) {
+        diag_tile(acc[0], 0, 0);
+    } else if (wave == 6) {
+        diag_tile(acc[0], 1, 0);
+        diag_tile(acc[1], 2, 0);
+        diag_tile(acc[2], 2, 1);
+        diag_tile(acc[3], 2, 2);
+        diag_tile(more, 3, 3);
+    } else if (wave == 7) {
+        diag_tile(acc[0], 3, 0);
+        diag_tile(acc[1], 3, 1);
+        diag_tile(acc[2], 1, 1);
+        diag_tile(acc[3], 3, 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (k > 0) {
 #pragma unroll
         for (int b = 0; b < 2; b++)
-            if (k > 0 && (b == 0 || with_own)) {
-                long ld;
-                const float* const from = gq_p_block(v, K, slots, before, b ? jb : k, ld) + (tid >> 4) * ld + 4 * (tid & 15);
 #pragma unroll
-                for (int i = 0; i < 2; i++) stage[b][i] = load_global<float4>(from + 32 * i * ld);
-            }
-        // wavefronts 0..3: a quadrant each of the diagonal block; 4..7: of the own one (below the diagonal transposed: rows j)
-        const bool own = wave >= 4;
-        const int w4 = wave & 3, wi = w4 >> 1, wj = w4 & 1, ln = lane & 31, h = lane >> 5;
-        const long rows = own && jb > k ? jb : k, cols = own && jb < k ? jb : k;
-        float16_t acc;
-        const float* const src = v + (rows * kGqGroup + 32 * wi + 4 * h) * K + cols * kGqGroup + 32 * wj + ln;
-#pragma unroll
-        for (int i = 0; i < 16; i++) {
-            acc[i] = 0.0f;                                          // (block column k - 1: L^-1's part starts with its own step)
-            if (own && jb == k) acc[i] = (32 * wi + 8 * (i >> 2) + 4 * h + (i & 3) == 32 * wj + ln) ? 1.0f : 0.0f;
-            else if (cols != before) acc[i] = src[(long)(8 * (i >> 2) + (i & 3)) * K];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (k > 0) {
-#pragma unroll
-            for (int b = 0; b < 2; b++)
-#pragma unroll
-                for (int i = 0; i < 2; i++)
-                    *reinterpret_cast<float4*>(s_all + b * kGqGroup * kGqGroup + 4 * (tid + kGqStepThreads * i)) = stage[b][i];
-        }
-        __syncthreads();
-        if (k > 0 && !(own && jb == k) && wave != 1) {              // (wavefront 1: above the diagonal, not needed)
-            const float* const ap = s_all + (rows == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wi + ln;
-            const float* const bp = s_all + (cols == k ? 0 : kGqGroup * kGqGroup) + h * kGqGroup + 32 * wj + ln;
-#pragma unroll 8
-            for (int c = 0; c < kGqGroup; c += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(-ap[c * kGqGroup], bp[c * kGqGroup], acc, 0, 0, 0);
-        }
-        __syncthreads();                                            // the operands have been read
-#pragma unroll
-        for (int i = 0; i < 16; i++) {
-            const int r = 32 * wi + 8 * (i >> 2) + 4 * h + (i & 3), c = 32 * wj + ln;
-            if (!own) s_m[r * kGqLd + c] = acc[i];
-            else if (jb > k) s_x[r * kGqLd + c] = acc[i];
-            else s_x[c * kGqLd + r] = acc[i];
-        }
+            for (int i = 0; i < 2; i++)
+                *reinterpret_cast<float4*>(s_p + b * kGqGroup * kGqPLd + ((tid >> 4) + 32 * i) * kGqPLd + 4 * (tid & 15)) = stage[b][i];
     }
     __syncthreads();
-    const int w4 = wave & 3, rr = lane >> 2, q = lane & 3;
-    const long j = jb * kGqGroup + 16 * w4 + rr;                    // substitution: four lanes per column
-    float* const xr = s_x + 16 * w4 * kGqLd;
-    float* const se = s_e + w4 * kGqChunk * 16;
+    // step k - 1's products: rows from block `block` (0: k, 1: own) of P, columns from block k
+    auto products = [&](f32x4_t& c, int block, int row, int col) {
+        if (k == 0 || (block == 1 && jb == k)) return;              // the same in the whole workgroup
+        const float* const ap = s_p + block * kGqGroup * kGqPLd + rg * kGqPLd + 16 * row + cl;
+        const float* const bp = s_p + rg * kGqPLd + 16 * col + cl;
+        float x[16], y[16];
+#pragma unroll
+        for (int kk = 0; kk < 16; kk++) {
+            x[kk] = ap[4 * kk * kGqPLd];
+            y[kk] = bp[4 * kk * kGqPLd];
+        }
+        __builtin_amdgcn_sched_barrier(0);                          // all of them requested before the first is waited for
+        c = -c;                                                     // (fma(-x, y, c) is -fma(x, y, -c))
+#pragma unroll
+        for (int kk = 0; kk < 16; kk++) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[kk], y[kk], c, 0, 0, 0);
+        c = -c;
+    };
+    auto put = [&](const f32x4_t& c, int row, int col) {            // a tile of the diagonal block
+#pragma unroll
+        for (int i = 0; i < 4; i++) s_m[(16 * row + 4 * rg + i) * kGqLd + 16 * col + cl] = c[i];
+    };
+    auto less = [&](f32x4_t& c, int row, int col, int piece) {      // ... loses a piece's products
+        gq_tile_less(c, s_m + (16 * row + cl) * kGqLd + 16 * piece + rg, 4, -1.0f, s_m + (16 * col + cl) * kGqLd + 16 * piece + rg);
+    };
+    float* const se = s_e + w4 * 4 * kGqChunk * 16;
+    auto own_less = [&](f32x4_t& c, int col, int piece) {
+        gq_tile_less(c, se + piece * kGqChunk * 16 + lane, 64, 1.0f, s_m + (16 * col + cl) * kGqLd + 16 * piece + rg);
+    };
+    const int rr = lane >> 2, q = lane & 3;                         // substitution: four lanes per row
+    const long j = jb * kGqGroup + 16 * w4 + rr;
     float* const pj = jb == k ? slots + k * kGqGroup * kGqGroup + q * kGqGroup + 16 * w4 + rr : v + (base + q) * K + j;
     const long pld = jb == k ? kGqGroup : K;
     float* const uj = u + (K - 1 - base - q) * K + (K - 1 - j);
-#pragma unroll 1
-    for (int s = 0; s < 5; s++) {
-        // the 16 columns before into the present ones, a tile a wavefront
-        if (s > 0 && s + wave < 4) gq_chol_tile(s_m, 16 * s - 16, s + wave, s);
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        // ---- the slot
+        if (own) {
+            if (s == 0) products(acc[0], 1, w4, 0);
+            else own_less(acc[s], s, s - 1);
+#pragma unroll
+            for (int i = 0; i < 4; i++) s_x[(16 * w4 + 4 * rg + i) * kXLd + cl] = acc[s][i];
+            if (s < 3) {
+                products(acc[s + 1], 1, w4, s + 1);
+#pragma unroll
+                for (int p = 0; p < s; p++) own_less(acc[s + 1], s + 1, p);
+            }
+        } else if (wave == 0) {
+            if (s == 0) {
+                products(acc[0], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; i++) acc[0][i] = s_m[(16 * s + 4 * rg + i) * kGqLd + 16 * s + cl];
+                less(acc[0], s, s, s - 1);
+            }
+            put(acc[0], s, s);
+            gq_chol_piece(s_m, s, s_q, s_inv);
+        } else if (wave == 6) {
+            // (the diagonal's next tile goes to LDS once wavefront 0 has only its last piece to take off)
+            if (s == 0) {
+                products(acc[0], 0, 1, 0);
+                put(acc[0], 1, 0);
+                products(acc[1], 0, 2, 0);
+                put(acc[1], 2, 0);
+                products(acc[2], 0, 2, 1);
+            } else if (s == 1) {
+                less(acc[2], 2, 1, 0);
+                put(acc[2], 2, 1);
+                products(acc[3], 0, 2, 2);
+                less(acc[3], 2, 2, 0);
+                put(acc[3], 2, 2);
+            } else if (s == 2) {
+                products(more, 0, 3, 3);
+                less(more, 3, 3, 0);
+                less(more, 3, 3, 1);
+                put(more, 3, 3);
+            }
+        } else if (wave == 7) {
+            if (s == 0) {
+                products(acc[0], 0, 3, 0);
+                put(acc[0], 3, 0);
+                products(acc[2], 0, 1, 1);
+                put(acc[2], 1, 1);
+                products(acc[1], 0, 3, 1);
+            } else if (s == 1) {
+                less(acc[1], 3, 1, 0);
+                put(acc[1], 3, 1);
+                products(acc[3], 0, 3, 2);
+                less(acc[3], 3, 2, 0);
+            } else if (s == 2) {
+                less(acc[3], 3, 2, 1);
+                put(acc[3], 3, 2);
+            }
+        }
         __syncthreads();
-        if (wave == 0) {
-            if (s < 4) gq_chol_piece(s_m, 16 * s, s_q, s_inv);
-        } else if (wave < 4) {
-            // ... and into what is behind them: tiles (2, 2), (3, 2), (3, 3), then (3, 3)
-            if (s == 1) gq_chol_tile(s_m, 0, wave == 1 ? 2 : 3, wave == 3 ? 3 : 2);
-            else if (s == 2 && wave == 1) gq_chol_tile(s_m, 16, 3, 3);
-        } else if (s > 0) {
-            const int t0 = 16 * (s - 1);
+        // ---- substitution
+        if (own || (wave >= 4 && drow > s)) {
+            float* const xr = own ? s_x + (16 * w4 + rr) * kXLd : s_m + (16 * drow + rr) * kGqLd + 16 * s;
             float x[4], keep = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 4; i++) x[i] = xr[rr * kGqLd + t0 + 4 * i + q];
-            const float4* const sd = reinterpret_cast<const float4*>(s_q + t0 * kGqChunk + 4 * q);
+            for (int i = 0; i < 4; i++) x[i] = xr[4 * i + q];
+            const float4* const sd = reinterpret_cast<const float4*>(s_q + 16 * s * kGqChunk + 4 * q);
+            float4 d[kGqChunk];
+            float2 dg[kGqChunk];
+#pragma unroll
+            for (int i = 0; i < kGqChunk; i++) {
+                d[i] = sd[i * (kGqChunk / 4)];
+                dg[i] = s_inv[16 * s + i];
+            }
 #pragma unroll
             for (int i = 0; i < kGqChunk; i++) {
                 const int k4 = i / 4, c = i % 4;
                 const float xi = c == 0 ? quad_bcast<0>(x[k4]) : c == 1 ? quad_bcast<1>(x[k4]) : c == 2 ? quad_bcast<2>(x[k4]) : quad_bcast<3>(x[k4]);
-                const float2 dg = s_inv[t0 + i];
-                const float e0 = xi * dg.y;
-                const float e = __builtin_fmaf(__builtin_fmaf(-dg.x, e0, xi), dg.y, e0);    // the quotient: one residual step
+                const float e0 = xi * dg[i].y;
+                const float e = __builtin_fmaf(__builtin_fmaf(-dg[i].x, e0, xi), dg[i].y, e0);    // the quotient: one residual step
                 keep = (q == c) ? e : keep;
                 if (c == 3) {
-                    pj[(long)(t0 + 4 * k4) * pld] = keep;
-                    uj[-(long)(t0 + 4 * k4) * K] = (jb > k) ? 0.0f : keep;
-                    se[(4 * k4 + q) * 16 + rr] = -keep;
+                    if (own) {
+                        pj[(long)(16 * s + 4 * k4) * pld] = keep;
+                        uj[-(long)(16 * s + 4 * k4) * K] = (jb > k) ? 0.0f : keep;
+                        se[s * kGqChunk * 16 + (4 * k4 + q) * 16 + rr] = -keep;
+                    } else {
+                        xr[4 * k4 + q] = keep;
+                    }
                 }
-                const float4 d4 = sd[i * (kGqChunk / 4)];
-                const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
+                const float dd[4] = {d[i].x, d[i].y, d[i].z, d[i].w};
 #pragma unroll
                 for (int m = (c == 3) ? k4 + 1 : k4; m < 4; m++) x[m] = __builtin_fmaf(-e, dd[m], x[m]);
             }
-            // ... and onto the columns behind them
-            float a[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; kk++) a[kk] = se[4 * kk * 16 + lane];
-            for (int tt = s; tt < 4; tt++) {
-                float* const at = xr + 4 * rg * kGqLd + 16 * tt + cl;
-                f32x4_t acc;
-                float y[4];
-#pragma unroll
-                for (int i = 0; i < 4; i++) acc[i] = at[i * kGqLd];
-#pragma unroll
-                for (int kk = 0; kk < 4; kk++) y[kk] = s_m[(16 * tt + cl) * kGqLd + t0 + 4 * kk + rg];
-#pragma unroll
-                for (int kk = 0; kk < 4; kk++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], y[kk], acc, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; i++) at[i * kGqLd] = acc[i];
-            }
         }
-        __syncthreads();
+        if (s < 3) __syncthreads();
     }
+}
+
+__global__ __launch_bounds__(kGqStepThreads, 2) void gptq_step_kernel(float* v, long K, long k, float* slots, float* __restrict__ u,
+                                                                     GqWide wide, int early, int blocks)
+{
+    __shared__ __attribute__((aligned(16))) float s_all[2 * kGqTileLds];
+    static_assert(sizeof(s_all) > 80 * 1024, "one workgroup per compute unit");
+    const int nb = (int)(K / kGqGroup);
+    if ((int)blockIdx.x < nb) gq_step_solve(s_all, v, K, k, slots, u, blockIdx.x);
+    else gq_step_tiles(s_all, v, K, (int)k, slots, wide, (int)blockIdx.x - nb, (int)gridDim.x - nb, early, blocks);
 }
 
 }  // namespace dymoe
@@ -1276,14 +1500,13 @@ int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, flo
     const long nb = K / kGqGroup;
     for (long k = 0; k < nb; k++) {
         const GqWide wide = gq_wide(nb, k);
-        const long blocks = nb + gq_wide_blocks(wide, k);
-        // Three workgroups fit on a compute unit, but while all of a launch's are resident together that puts two tiles beside a
-        // solver and three elsewhere, and the launch waits for the solver: 64 KB of LDS let two in, and the last tiles go
-        // where one has ended (K = 4096: 1.41 -> 1.35 ms).  Beyond one filling the tiles are what it waits for (14336: 28.4
-        // with two, 25.4 with three).
-        const size_t lds = blocks <= 3L * ctx->num_cu ? 4 * kGqGroup * kGqGroup * 4 : kGqStepLds * 4;
-        dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_step_kernel, dim3((unsigned)blocks), dim3(kGqStepThreads), lds, st, v, K, k, slots, u,
-                     wide);
+        const long blocks = gq_wide_blocks(wide, k);
+        // Workgroups for the tiles: one on each compute unit that the solvers leave; where these would take longer than kGqSkip blocks each,
+        // one behind each solver as well.
+        const long early = ctx->num_cu > nb ? ctx->num_cu - nb : 0;
+        const long workers = blocks <= kGqSkip * early ? (blocks < early ? blocks : early) : ctx->num_cu;
+        dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_step_kernel, dim3((unsigned)(nb + workers)), dim3(kGqStepThreads), 0, st, v, K, k, slots, u,
+                     wide, (int)early, (int)blocks);
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;

@@ -399,3 +399,22 @@ def test_gptq_hessian_of_few_and_many_tiles(ctx, n, K):
     assert torch.equal(got, got.t())
     twice = ctx.gptq_hessian(x, out=got.clone(), accumulate=True)
     assert torch.equal(twice, got + got)
+
+
+# tiles dealt out over several rounds: workgroups on the compute units that the solvers leave (61 blocks of columns) and also
+# behind the solvers (81), both with a last pair of blocks that is not whole
+@pytest.mark.parametrize("K", [3904, 5184])
+def test_gptq_factor_of_many_tiles(ctx, K):
+    g = torch.Generator(device=DEV).manual_seed(K)
+    x = torch.randn((2 * K, K), generator=g, device=DEV) + 1.5 * torch.randn((2 * K, 1), generator=g, device=DEV)
+    H = (x.T @ x).contiguous()
+    u = ctx.gptq_factor(H, damp=0.01).double()
+    torch.cuda.synchronize()
+    Hd = H.double()
+    Hd.diagonal().add_(0.01 * H.double().diagonal().mean())
+    eye = torch.eye(K, dtype=torch.float64, device=DEV)
+    assert torch.equal(u, u.triu())
+    # (U^T U)^-1 = Hd, so U Hd U^T = I: what binary32 leaves of that is its epsilon times the condition number (about a thousand)
+    err = (u @ Hd @ u.T - eye).abs().max().item()
+    print("K=%d: |U Hd U^T - I| = %.2e" % (K, err))
+    assert err < 1e3 * 2.0 ** -23
