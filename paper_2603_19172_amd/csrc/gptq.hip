@@ -20,12 +20,11 @@
 // corrections go through the matrix cores and keep the reference's bits: a register-only loop of those instructions holds
 // 140 to 155 TFLOP/s on random data, one of vector fmas 108 to 117, and a lane's operands serve four times the products.
 //
-// Rows are independent, columns are not.  Columns go in panels of 256 (four groups of 64), two launches each:
-//   group kernel   a wavefront owns 16 rows through the whole panel: a group's values lose the corrections of the
-//                  panel's earlier groups (16x16x4 products, errors from LDS), are turned round so that four lanes
-//                  share a row (a lane every fourth column), and are quantised column by column; codes, scale, zero
-//                  and the errors e of the row are written;
-//   trail kernel   v[:, j] for the columns behind the panel: 256 chained fmas per element.
+// Rows are independent, columns are not.  Columns go in panels of 256 (four groups of 64), a launch each, which does two things side by side:
+//   the panel      32 rows a workgroup: their values lose the errors of the panel before, then group after group is quantised
+//                  column by column (a chain of dependent steps: four lanes share a row, a lane every fourth column) and its errors
+//                  corrected in the panel's later groups; codes, scale, zero and the errors e are written;
+//   the rest       v[:, j] for the columns behind the panel loses the errors of the panel before: 256 chained fmas per element.
 // The working copy v of the matrix (fp32) lives in the caller's workspace.
 #include <type_traits>
 
@@ -34,7 +33,7 @@
 namespace dymoe {
 
 constexpr int kGqGroup = 64;        // columns per group
-constexpr int kGqRows = 64;         // rows per row block
+constexpr int kGqRows = 32;         // rows per row block
 constexpr int kGqPanel = 4;         // groups per panel
 constexpr int kGqChunk = 16;        // columns per piece of a group's chain
 
@@ -43,28 +42,37 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 static inline size_t gq_round256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline long gq_row_blocks(long N) { return (N + kGqRows - 1) / kGqRows; }
 
-// Groups per panel.  Where all rows make one ragged block, no block can keep its errors in v (see GqErr), and half a panel
-// is kept in the linear buffer.
-static inline int gq_panel(long N) { return (N < kGqRows) ? kGqPanel / 2 : kGqPanel; }
+// Groups per panel.  Below 64 rows half a panel, so that the errors of two panels of a ragged block find room in the buffer.
+static inline int gq_panel(long N) { return (N < 2 * kGqRows) ? kGqPanel / 2 : kGqPanel; }
 
-// bytes of the ragged row block's errors, a panel's columns of 64 rows; no ragged block, no buffer
-static inline size_t gq_tail_bytes(long N) { return (N % kGqRows) ? (size_t)gq_panel(N) * kGqGroup * kGqRows * sizeof(float) : 0; }
+// bytes of the ragged row block's errors, two panels' columns of 32 rows; no ragged block, no buffer (the buffer also where the last 32 of 64 rows are missing)
+static inline size_t gq_tail_bytes(long N)
+{
+    return (N % (2 * kGqRows)) ? 2 * (size_t)gq_panel(N) * kGqGroup * kGqRows * sizeof(float) : 0;
+}
 
-// Where the (negated) errors of a panel of four groups are kept between the two kernels.  The panel's own columns of
-// v are dead once its values are in registers, and a row block's 64 x 256 of them hold its 256 x 64 errors exactly:
-// element (column c of the panel, row r of the block) sits in row c / 4 of the block at offset (c % 4) * 64 + r.  The
-// ragged last row block has too few rows for that and uses a linear buffer of the same arrangement (row stride 256).
+// Where the (negated) errors of a panel of `cols` columns are kept until the next launch has used them.  The panel's own columns of
+// v are dead once its values are in registers, and a row block's 32 x cols of them hold its cols x 32 errors exactly:
+// element (column c of the panel, row r of the block) sits in row c / (cols / 32) of the block at offset (c % (cols / 32)) * 32 + r.  The
+// ragged last row block has too few rows for that and uses a linear buffer of the same arrangement (row stride cols).
 struct GqErr {
     float* whole;     // v + first column of the panel
-    long ld;          // row stride of v
     float* tail;      // linear buffer of the ragged block
+    long ld;          // row stride of v
     long full_blocks;
+    int cols;
 };
 __device__ __forceinline__ float* gq_err_block(const GqErr& g, long block, long& ld)
 {
     const bool full = block < g.full_blocks;
-    ld = full ? g.ld : 256;
+    ld = full ? g.ld : g.cols;
     return full ? g.whole + block * kGqRows * g.ld : g.tail;
+}
+// of element (c, r) within a block
+__device__ __forceinline__ long gq_err_at(const GqErr& g, long ld, int c, int r)
+{
+    const int shift = (g.cols == kGqPanel * kGqGroup) ? 3 : 2;                          // 8 or 4 columns c a row
+    return (long)(c >> shift) * ld + (c & ((1 << shift) - 1)) * kGqRows + r;
 }
 
 // x of column C, held by lane C % 4 of a quad in register C / 4, to the quad's four lanes
@@ -167,208 +175,314 @@ __device__ __forceinline__ void gq_group_chain_exact(float* sx, int r, int q, fl
     }
 }
 
-// One panel of up to four groups: rows in blocks of 64 (a workgroup), 16 rows a wavefront.  FIRST: the values come from
-// the bf16 matrix itself (nothing has been corrected yet), so the working copy is never filled by a pass of its own.
-// Bound: the chain of 64 dependent quantise-and-correct steps per group, 52 ns each, and the products between groups.  Four
-// lanes share a row, so that 896 wavefronts work on the chip's 1024 SIMDs for 14336 rows; the chain corrects 16 columns only
-// (four a lane: as few as its own latency covers, and a quarter of the reads of U from LDS), the group's later columns get
-// those 16 errors as matrix products.  14336 x 4096, int4: 31 us per panel (2 to start, 4.5 per group, 8.6 between the groups);
-// with the chain correcting all 64 columns 40 us, with a lane per row 120.
+// LDS of a panel's workgroup, floats: first two buffers for the corrections of the panel before (16 columns c: 256 columns of U and 32 rows
+// of errors), then the corrected values, then the errors [column][row]; behind them what is there throughout.
+constexpr int kGqULd = kGqPanel * kGqGroup + 16;                    // row stride of U in a buffer: c and c + 1 on other banks
+constexpr int kGqStage = 16 * kGqULd + 16 * kGqRows;
+constexpr int kGqHLd = kGqPanel * kGqGroup + 4;
+constexpr int kGqXLd = kGqGroup + 4;
+constexpr int kGqX = kGqRows * kGqHLd;                              // a group's values, [row][column]
+constexpr int kGqD = kGqX + kGqRows * kGqXLd;                       // two groups' 16 x 16 diagonal blocks, [c][j % 4][j / 4]
+constexpr int kGqInv = kGqD + 2 * kGqGroup * kGqChunk;              // two groups' 1 / U[c,c], 64 bits
+constexpr int kGqPanelLds = kGqInv + 2 * kGqGroup * 2;
+static_assert(2 * kGqStage <= kGqD && kGqPanel * kGqGroup * kGqRows <= kGqX, "what is there throughout stays so");
+
+// One panel of up to four groups for 32 rows.  FIRST: the values come from the bf16 matrix itself (nothing behind the first panel
+// has been corrected yet), so the working copy is never filled by a pass of its own.
+// Wavefronts 0 and 1 do the chains, 16 rows each; 2 and 3 meanwhile take the errors of the group before from the panel's last two groups,
+// and between two chains those of that group from the next one.
+// Bound: the chain of 64 dependent quantise-and-correct steps per group, 70 ns each, and the products between groups; the rest of the
+// launch's work runs beside it.  Four lanes share a row (two: 3 % more for the whole sweep, though fewer instructions); the chain corrects
+// 16 columns only (four a lane: as few as its own latency covers, and a quarter of the reads of U from LDS), the group's later
+// columns get those 16 errors as matrix products.  14336 rows, us: alone (the last panel) 21 for the values (7 of matrix instructions a
+// workgroup, 448 workgroups) and 6.5 a group; beside the rest 35 and 14, the vector instructions and the fp32 matrix
+// instructions taking their time from each other.
 template <int BITS, bool FIRST>
-__global__ __launch_bounds__(256) void gptq_group_kernel(
-    const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K, long base,
-    int n_groups, GqErr err, uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
+__device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
+                                              long base, int n_groups, const GqErr& before, const GqErr& err, bool corrections, bool last,
+                                              uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
 {
 #pragma clang fp contract(off)
     constexpr int qmax = (1 << BITS) - 1;
     constexpr int n_words = kGqGroup * BITS / 32;               // 16 (int8), 8 (int4), 4 (int2)
-    constexpr int kStride = kGqGroup + 4;
-    __shared__ __attribute__((aligned(16))) float s_d[kGqPanel][kGqGroup * kGqChunk];   // the 16 x 16 diagonal blocks, [c][j % 4][j / 4]
-    __shared__ __attribute__((aligned(16))) double s_inv[kGqPanel * kGqGroup];
-    __shared__ __attribute__((aligned(16))) float s_e[4][kGqPanel * kGqGroup * 16];   // per wavefront [column][row], negated
-    __shared__ __attribute__((aligned(16))) float s_x[4][16 * kStride];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long row0 = (long)blockIdx.x * kGqRows + 16 * wave;
-    // matrix-instruction layout: this lane holds rows 4 rg .. 4 rg + 3, columns 4 cl .. 4 cl + 3 of the 16 x 64 values
+    float* const s_e = s_all;                                   // errors, [column][row], negated
+    float* const s_x = s_all + kGqX;
+    float* const s_d = s_all + kGqD;
+    double* const s_inv = reinterpret_cast<double*>(s_all + kGqInv);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane >> 4, cl = lane & 15;
-    float4 cur[kGqPanel][4];
+    const long block = blockIdx.x, row0 = block * kGqRows;
+    // ---- the values, a group a wavefront, minus the errors of the panel before.  Register i of tile (t, x): row 16 t + 4 rg + i, column 4 cl + x.
+    {
+        f32x4_t acc[2][4];
+        if (wave < n_groups) {
 #pragma unroll
-    for (int g = 0; g < kGqPanel; g++) {
-        if (g >= n_groups) break;
+            for (int t = 0; t < 2; t++)
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const long row = min(row0 + 4 * rg + i, N - 1);     // rows past the last one redo it and keep the result to themselves
-            const long at = row * K + base + kGqGroup * g + 4 * cl;
-            if constexpr (FIRST) {
-                const uint2 raw = load_global<uint2>(w + at);
-                cur[g][i] = make_float4(bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y));
-            } else {
-                cur[g][i] = *reinterpret_cast<const float4*>(v + at);
+                for (int i = 0; i < 4; i++) {
+                    const long row = min(row0 + 16 * t + 4 * rg + i, N - 1);    // rows past the last one redo it and keep the result to themselves
+                    const long at = row * K + base + kGqGroup * wave + 4 * cl;
+                    float4 val;
+                    if constexpr (FIRST) {
+                        const uint2 raw = load_global<uint2>(w + at);
+                        val = make_float4(bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y));
+                    } else {
+                        val = load_global<float4>(v + at);
+                    }
+                    acc[t][0][i] = val.x; acc[t][1][i] = val.y; acc[t][2][i] = val.z; acc[t][3][i] = val.w;
+                }
+        }
+        if (corrections) {
+            long ld;
+            const float* const eb = gq_err_block(before, block, ld);
+            const float* const ub = u + (base - before.cols) * K + base;        // (a row's 256 floats may run over the end of U's columns, into its next row)
+            const uint32_t lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float*)s_all;
+            auto copy = [&](int c0, int buf) {
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    lds_copy16((const char*)(ub + (long)(c0 + 4 * wave + i) * K), lane * 16, lds + (buf * kGqStage + (4 * wave + i) * kGqULd) * 4);
+                if (wave < 2)
+                    lds_copy16((const char*)eb, (uint32_t)gq_err_at(before, ld, c0 + 8 * wave + (lane >> 3), 4 * (lane & 7)) * 4,
+                               lds + (buf * kGqStage + 16 * kGqULd + 8 * wave * kGqRows) * 4);
+            };
+            copy(0, 0);
+            wait_lds_copies<0>();
+            __syncthreads();
+            for (int c0 = 0, buf = 0; c0 < before.cols; c0 += 16, buf ^= 1) {
+                if (c0 + 16 < before.cols) copy(c0 + 16, buf ^ 1);              // (that buffer's last readers passed the barrier before)
+                if (wave < n_groups) {
+                    const float* const sb = s_all + buf * kGqStage + rg * kGqULd + kGqGroup * wave + 4 * cl;
+                    const float* const sa = s_all + buf * kGqStage + 16 * kGqULd + rg * kGqRows + cl;
+#pragma unroll
+                    for (int kk = 0; kk < 4; kk++) {
+                        const float4 b4 = *reinterpret_cast<const float4*>(sb + 4 * kk * kGqULd);
+                        const float a[2] = {sa[4 * kk * kGqRows], sa[4 * kk * kGqRows + 16]};
+                        const float b[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+                        for (int t = 0; t < 2; t++)
+#pragma unroll
+                            for (int x = 0; x < 4; x++) acc[t][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[x], acc[t][x], 0, 0, 0);
+                    }
+                }
+                wait_lds_copies<0>();
+                __syncthreads();
             }
         }
-    }
-    for (int at = tid; at < n_groups * kGqGroup; at += 256) {
-        const long c = base + at;
-        s_inv[at] = 1.0 / (double)u[c * K + c];
-    }
-    for (int at = tid; at < n_groups * kGqGroup * 4; at += 256) {
-        const int g = at >> 8, c = (at >> 2) & 63, i = at & 3;
-        const float4 d = *reinterpret_cast<const float4*>(u + (base + kGqGroup * g + c) * K + base + kGqGroup * g + (c & ~15) + 4 * i);
-        float* dst = &s_d[g][c * kGqChunk + i];
-        dst[0] = d.x; dst[4] = d.y; dst[8] = d.z; dst[12] = d.w;
-    }
-    __syncthreads();            // and every wavefront has its values in registers: v may now be overwritten by errors
-    const int r = lane >> 2, q = lane & 3;                      // the chain's layout: row r, columns 4 m + q
-    const long row = row0 + r;
-    long eld;
-    float* const eb = gq_err_block(err, blockIdx.x, eld) + q * kGqRows + 16 * wave + r;
-    // The rows of U that a group's values are corrected with come straight from memory, 32 columns ahead of their use; the
-    // first batch of the next group is requested before this group's chain and lies in registers behind it.
-    constexpr int kAhead = 8;
-    float4 ub[2][kAhead];
-    const float* bp = u + (base + rg) * K + base + kGqGroup + 4 * cl;
-    auto fetch = [&](int buf, const float* from) {
+        if (wave < n_groups) {
 #pragma unroll
-        for (int i = 0; i < kAhead; i++) ub[buf][i] = load_global<float4>(from + (long)i * 4 * K);
+            for (int t = 0; t < 2; t++)
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    *reinterpret_cast<float4*>(s_all + (16 * t + 4 * rg + i) * kGqHLd + kGqGroup * wave + 4 * cl) =
+                        make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
+        }
+    }
+    const bool chain = wave < 2;
+    const int cw = wave - 2;                                    // wavefronts 2 and 3: half of every group's columns
+    // the diagonal of U for a group's chain, by wavefronts 2 and 3
+    auto diagonal = [&](int g) {
+        const long first = base + kGqGroup * g;
+        const int at0 = tid - 128;
+        if (at0 < kGqGroup) s_inv[(g & 1) * kGqGroup + at0] = 1.0 / (double)u[(first + at0) * K + first + at0];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int at = at0 + 128 * h, c = at >> 2, i = at & 3;
+            const float4 d = load_global<float4>(u + (first + c) * K + first + (c & ~15) + 4 * i);
+            float* const dst = s_d + (g & 1) * kGqGroup * kGqChunk + c * kGqChunk + i;
+            dst[0] = d.x; dst[4] = d.y; dst[8] = d.z; dst[12] = d.w;
+        }
+    };
+    // the panel's later groups, o = 0: the next one.  Register i of tile (t, x): row 16 t + 4 rg + i, column 32 cw + 2 cl + x
+    f32x4_t rest[3][2][2];
+    if (!chain) diagonal(0);
+    __syncthreads();
+    if (!chain) {
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            const int at = tid - 128 + 128 * h, row = at >> 4, c = 4 * (at & 15);
+            *reinterpret_cast<float4*>(s_x + row * kGqXLd + c) = *reinterpret_cast<const float4*>(s_all + row * kGqHLd + c);
+        }
+#pragma unroll
+        for (int o = 0; o < 3; o++)
+            if (1 + o < n_groups)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        const float2 val = *reinterpret_cast<const float2*>(s_all + (16 * t + 4 * rg + i) * kGqHLd + kGqGroup * (1 + o) + 32 * cw + 2 * cl);
+                        rest[o][t][0][i] = val.x;
+                        rest[o][t][1][i] = val.y;
+                    }
+    }
+    __syncthreads();                                            // the values have been read: errors may take their place
+    long eld;
+    float* const eb = gq_err_block(err, block, eld);
+    float2 ub[16];
+    // rows of group g of U, this lane's two columns of group `of`
+    auto fetch = [&](int g, int of) {
+        const float* const from = u + (base + kGqGroup * g + rg) * K + base + kGqGroup * of + 32 * cw + 2 * cl;
+#pragma unroll
+        for (int kk = 0; kk < 16; kk++) ub[kk] = load_global<float2>(from + (long)(4 * kk) * K);
         __builtin_amdgcn_sched_barrier(0);
     };
+    auto correct = [&](f32x4_t (&c)[2][2], int g) {
+        const float* const ap = s_e + (kGqGroup * g + rg) * kGqRows + cl;
+#pragma unroll
+        for (int kk = 0; kk < 16; kk++) {
+            const float a[2] = {ap[4 * kk * kGqRows], ap[4 * kk * kGqRows + 16]};
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                c[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], ub[kk].x, c[t][0], 0, 0, 0);
+                c[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], ub[kk].y, c[t][1], 0, 0, 0);
+            }
+        }
+    };
+    if (chain) {
+#pragma unroll 1
+        for (int g = 0; g < n_groups; g++) {
+            const int r = lane >> 2, q = lane & 3;              // the chain's layout: row r, columns 4 m + q
+            const long row = row0 + 16 * wave + r;
+            float* const sx = s_x + 16 * wave * kGqXLd;         // this wavefront's own from here on
+            float* const se = s_e + kGqGroup * g * kGqRows + 16 * wave;
+            // U between the group's pieces of 16 columns: rows 16 t + 4 kk + rg, columns 16 tt + cl, tt > t
+            float between[24];
+            const float* const ud = u + (base + kGqGroup * g) * K + base + kGqGroup * g;
+            {
+                int n = 0;
+#pragma unroll
+                for (int t = 0; t < 3; t++)
+#pragma unroll
+                    for (int tt = t + 1; tt < 4; tt++)
+#pragma unroll
+                        for (int kk = 0; kk < 4; kk++) between[n++] = load_global<float>(ud + (long)(16 * t + 4 * kk + rg) * K + 16 * tt + cl);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            float x[16];
+#pragma unroll
+            for (int m = 0; m < 16; m++) x[m] = sx[r * kGqXLd + 4 * m + q];
+            f32x4_t later[3];                                   // the pieces behind the first, in the matrix instructions' layout
+#pragma unroll
+            for (int tt = 1; tt < 4; tt++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) later[tt - 1][i] = sx[(4 * rg + i) * kGqXLd + 16 * tt + cl];
+            float lo = x[0], hi = x[0];
+#pragma unroll
+            for (int m = 1; m < 16; m++) {
+                lo = fminf(lo, x[m]);
+                hi = fmaxf(hi, x[m]);
+            }
+            lo = fminf(lo, dpp_get<0xB1, 0xF>(lo));
+            hi = fmaxf(hi, dpp_get<0xB1, 0xF>(hi));
+            lo = fminf(lo, dpp_get<0x4E, 0xF>(lo));
+            hi = fmaxf(hi, dpp_get<0x4E, 0xF>(hi));
+            const _Float16 zh = (_Float16)lo;                   // round to nearest even
+            const float range = hi - lo;
+            const float step = range / (float)qmax;             // correctly rounded division
+            const _Float16 sh = (_Float16)step;
+            const float m = (float)zh, s = (float)sh;
+            const float inv = (s > 0.0f) ? (1.0f / s) : 0.0f;
+            uint32_t words[n_words];
+            auto emit = [&](int k, float ne) { se[(4 * k + q) * kGqRows + r] = ne; };      // the errors of columns 4 k .. 4 k + 3, this lane's 4 k + q
+            // Sixteen columns by the chain, then their products onto the pieces behind them, errors ascending as the chain would
+            // have applied them.
+            float piece[4] = {x[0], x[1], x[2], x[3]};
+            const double* const si = s_inv + (g & 1) * kGqGroup;
+            const float* const sd = s_d + (g & 1) * kGqGroup * kGqChunk;
+            auto carry = [&](auto from) {
+                constexpr int T = decltype(from)::value, first = T == 0 ? 0 : T == 1 ? 12 : 20;
+                const float* const ap = se + (16 * T + rg) * kGqRows + cl;
+                float a[4];
+#pragma unroll
+                for (int kk = 0; kk < 4; kk++) a[kk] = ap[4 * kk * kGqRows];
+#pragma unroll
+                for (int tt = T + 1; tt < 4; tt++) {
+#pragma unroll
+                    for (int kk = 0; kk < 4; kk++)
+                        later[tt - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], between[first + 4 * (tt - T - 1) + kk], later[tt - 1], 0, 0, 0);
+                    if (tt == T + 1) {
+#pragma unroll
+                        for (int i = 0; i < 4; i++) sx[(4 * rg + i) * kGqXLd + 16 * tt + cl] = later[tt - 1][i];
+#pragma unroll
+                        for (int i = 0; i < 4; i++) piece[i] = sx[r * kGqXLd + 16 * tt + 4 * i + q];
+                    }
+                }
+            };
+            bool subnormal = gq_chunk_chain<BITS, 0>(piece, q, m, s, inv, sd, si, words, emit);
+            carry(std::integral_constant<int, 0>());
+            subnormal |= gq_chunk_chain<BITS, 16>(piece, q, m, s, inv, sd, si, words, emit);
+            carry(std::integral_constant<int, 1>());
+            subnormal |= gq_chunk_chain<BITS, 32>(piece, q, m, s, inv, sd, si, words, emit);
+            carry(std::integral_constant<int, 2>());
+            subnormal |= gq_chunk_chain<BITS, 48>(piece, q, m, s, inv, sd, si, words, emit);
+            if (__any(subnormal)) {
+#pragma unroll
+                for (int m2 = 0; m2 < 16; m2++) sx[r * kGqXLd + 4 * m2 + q] = x[m2];
+                gq_group_chain_exact<BITS>(sx, r, q, m, s, inv, ud, K, words, emit);
+            }
+            if (row < N) {
+                uint8_t* dst = codes + (row * K + base + kGqGroup * g) * BITS / 8;
+                constexpr int mine = n_words / 4;               // each lane of a quad writes a quarter of the row's codes
+                uint32_t out[mine];
+#pragma unroll
+                for (int k = 0; k < mine; k++)
+                    out[k] = (q & 2) ? ((q & 1) ? words[3 * mine + k] : words[2 * mine + k]) : ((q & 1) ? words[mine + k] : words[k]);
+                if constexpr (mine == 4) store_global(dst + 16 * q, make_uint4(out[0], out[1], out[2], out[3]));
+                else if constexpr (mine == 2) store_global(dst + 8 * q, make_uint2(out[0], out[1]));
+                else store_global(dst + 4 * q, out[0]);
+                const long sg = row * (K / kGqGroup) + base / kGqGroup + g;
+                if (q == 0) store_global(scale + sg, (uint16_t)f16_bits(sh));
+                if (q == 1) store_global(zero + sg, (uint16_t)f16_bits(zh));
+            }
+            __syncthreads();                                    // the group's errors are there
+            __syncthreads();                                    // ... and the next one's values
+        }
+        return;
+    }
 #pragma unroll 1
     for (int g = 0; g < n_groups; g++) {
         if (g > 0) {
-            // the group's values move to the front (a run-time index would put them into private memory)
+            // group g - 1's errors from the groups behind the present one, and to memory for the next launch
 #pragma unroll
-            for (int o = 1; o < kGqPanel; o++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) cur[o - 1][i] = cur[o][i];
-            f32x4_t acc[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                acc[0][i] = cur[0][i].x; acc[1][i] = cur[0][i].y; acc[2][i] = cur[0][i].z; acc[3][i] = cur[0][i].w;
-            }
-            const float* ap = &s_e[wave][lane];
-            auto multiply = [&](int buf) {
-#pragma unroll
-                for (int i = 0; i < kAhead; i++) {
-                    const float a = ap[i * 64];
-                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].x, acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].y, acc[1], 0, 0, 0);
-                    acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].z, acc[2], 0, 0, 0);
-                    acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ub[buf][i].w, acc[3], 0, 0, 0);
+            for (int o = 0; o < 2; o++)
+                if (g + 1 + o < n_groups) {
+                    fetch(g - 1, g + 1 + o);
+                    correct(rest[o], g - 1);
                 }
-                ap += kAhead * 64;
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            const float* from = bp;
-#pragma unroll 1
-            for (int h = 1; h < g; h++) {                       // a group's 64 columns are two batches
-                fetch(1, from + (long)kAhead * 4 * K);
-                multiply(0);
-                from += (long)2 * kAhead * 4 * K;
-                fetch(0, from);
-                multiply(1);
-            }
-            fetch(1, from + (long)kAhead * 4 * K);
-            multiply(0);
-            multiply(1);
-            bp += kGqGroup;
+            if (!last)
 #pragma unroll
-            for (int i = 0; i < 4; i++) cur[0][i] = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-        }
-        if (g + 1 < n_groups) fetch(0, bp);
-        // U between the group's pieces of 16 columns: rows 16 t + 4 kk + rg, columns 16 tt + cl, tt > t
-        float between[24];
-        const float* const ud = u + (base + kGqGroup * g) * K + base + kGqGroup * g;
-        {
-            int n = 0;
-#pragma unroll
-            for (int t = 0; t < 3; t++)
-#pragma unroll
-                for (int tt = t + 1; tt < 4; tt++)
-#pragma unroll
-                    for (int kk = 0; kk < 4; kk++) between[n++] = load_global<float>(ud + (long)(16 * t + 4 * kk + rg) * K + 16 * tt + cl);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        float* const sx = s_x[wave];                            // one wavefront's own: no barrier
-#pragma unroll
-        for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * rg + i) * kStride + 4 * cl]) = cur[0][i];
-        float x[16];
-#pragma unroll
-        for (int m = 0; m < 16; m++) x[m] = sx[r * kStride + 4 * m + q];
-        f32x4_t later[3];                                       // the pieces behind the first, in the matrix instructions' layout
-#pragma unroll
-        for (int tt = 1; tt < 4; tt++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) later[tt - 1][i] = sx[(4 * rg + i) * kStride + 16 * tt + cl];
-        float lo = x[0], hi = x[0];
-#pragma unroll
-        for (int m = 1; m < 16; m++) {
-            lo = fminf(lo, x[m]);
-            hi = fmaxf(hi, x[m]);
-        }
-        lo = fminf(lo, dpp_get<0xB1, 0xF>(lo));
-        hi = fmaxf(hi, dpp_get<0xB1, 0xF>(hi));
-        lo = fminf(lo, dpp_get<0x4E, 0xF>(lo));
-        hi = fmaxf(hi, dpp_get<0x4E, 0xF>(hi));
-        const _Float16 zh = (_Float16)lo;                       // round to nearest even
-        const float range = hi - lo;
-        const float step = range / (float)qmax;                 // correctly rounded division
-        const _Float16 sh = (_Float16)step;
-        const float m = (float)zh, s = (float)sh;
-        const float inv = (s > 0.0f) ? (1.0f / s) : 0.0f;
-        uint32_t words[n_words];
-        float* const se = &s_e[wave][g * kGqGroup * 16 + q * 16 + r];
-        auto emit = [&](int k, float ne) {                      // the errors of columns 4 k .. 4 k + 3, this lane's 4 k + q
-            se[k * 64] = ne;
-            eb[(long)(16 * g + k) * eld] = ne;                  // (unread behind the last panel; the place is dead all the same)
-        };
-        // Sixteen columns by the chain, then their products onto the pieces behind them, errors ascending as the chain would
-        // have applied them.
-        float piece[4] = {x[0], x[1], x[2], x[3]};
-        const double* const si = &s_inv[g * kGqGroup];
-        auto carry = [&](auto from) {
-            constexpr int T = decltype(from)::value, first = T == 0 ? 0 : T == 1 ? 12 : 20;
-            const float* const ap = &s_e[wave][(g * kGqGroup + 16 * T) * 16 + lane];
-            float a[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; kk++) a[kk] = ap[kk * 64];
-#pragma unroll
-            for (int tt = T + 1; tt < 4; tt++) {
-#pragma unroll
-                for (int kk = 0; kk < 4; kk++)
-                    later[tt - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], between[first + 4 * (tt - T - 1) + kk], later[tt - 1], 0, 0, 0);
-                if (tt == T + 1) {
-#pragma unroll
-                    for (int i = 0; i < 4; i++) sx[(4 * rg + i) * kStride + 16 * tt + cl] = later[tt - 1][i];
-#pragma unroll
-                    for (int i = 0; i < 4; i++) piece[i] = sx[r * kStride + 16 * tt + 4 * i + q];
+                for (int h = 0; h < 4; h++) {
+                    const int at = tid - 128 + 128 * h, c = kGqGroup * (g - 1) + (at >> 3), r = 4 * (at & 7);
+                    store_global(eb + gq_err_at(err, eld, c, r), *reinterpret_cast<const float4*>(s_e + c * kGqRows + r));
                 }
-            }
-        };
-        bool subnormal = gq_chunk_chain<BITS, 0>(piece, q, m, s, inv, s_d[g], si, words, emit);
-        carry(std::integral_constant<int, 0>());
-        subnormal |= gq_chunk_chain<BITS, 16>(piece, q, m, s, inv, s_d[g], si, words, emit);
-        carry(std::integral_constant<int, 1>());
-        subnormal |= gq_chunk_chain<BITS, 32>(piece, q, m, s, inv, s_d[g], si, words, emit);
-        carry(std::integral_constant<int, 2>());
-        subnormal |= gq_chunk_chain<BITS, 48>(piece, q, m, s, inv, s_d[g], si, words, emit);
-        if (__any(subnormal)) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) *reinterpret_cast<float4*>(&sx[(4 * rg + i) * kStride + 4 * cl]) = cur[0][i];
-            gq_group_chain_exact<BITS>(sx, r, q, m, s, inv, ud, K, words, emit);
         }
-        if (row < N) {
-            uint8_t* dst = codes + (row * K + base + kGqGroup * g) * BITS / 8;
-            constexpr int mine = n_words / 4;                   // each lane of a quad writes a quarter of the row's codes
-            uint32_t out[mine];
+        if (g + 1 < n_groups) {
+            diagonal(g + 1);
+            fetch(g, g + 1);
+        }
+        __syncthreads();                                        // the group's errors are there
+        if (g + 1 < n_groups) {
+            correct(rest[0], g);
 #pragma unroll
-            for (int k = 0; k < mine; k++)
-                out[k] = (q & 2) ? ((q & 1) ? words[3 * mine + k] : words[2 * mine + k]) : ((q & 1) ? words[mine + k] : words[k]);
-            if constexpr (mine == 4) store_global(dst + 16 * q, make_uint4(out[0], out[1], out[2], out[3]));
-            else if constexpr (mine == 2) store_global(dst + 8 * q, make_uint2(out[0], out[1]));
-            else store_global(dst + 4 * q, out[0]);
-            const long sg = row * (K / kGqGroup) + base / kGqGroup + g;
-            if (q == 0) store_global(scale + sg, (uint16_t)f16_bits(sh));
-            if (q == 1) store_global(zero + sg, (uint16_t)f16_bits(zh));
+            for (int t = 0; t < 2; t++)
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    *reinterpret_cast<float2*>(s_x + (16 * t + 4 * rg + i) * kGqXLd + 32 * cw + 2 * cl) = make_float2(rest[0][t][0][i], rest[0][t][1][i]);
+#pragma unroll
+            for (int o = 0; o < 2; o++)
+#pragma unroll
+                for (int t = 0; t < 2; t++) {
+                    rest[o][t][0] = rest[o + 1][t][0];
+                    rest[o][t][1] = rest[o + 1][t][1];
+                }
+        }
+        __syncthreads();                                        // ... and the next one's values
+    }
+    if (!last) {
+        const int g = n_groups - 1;
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            const int at = tid - 128 + 128 * h, c = kGqGroup * g + (at >> 3), r = 4 * (at & 7);
+            store_global(eb + gq_err_at(err, eld, c, r), *reinterpret_cast<const float4*>(s_e + c * kGqRows + r));
         }
     }
 }
@@ -386,8 +500,10 @@ struct GqTile {
 // (2048 cycles of products per wavefront) before they are stored there: a wavefront that streams its own operands
 // from L2 twice as far ahead was bound by that traffic (85 TFLOP/s: the 32 KB of L1 hold no two wavefronts' batches).
 // ap, bp: this wavefront's share of the operands, tile w % 2 and the c's 4 (w / 2) .. + 3 and 8 + 4 (w / 2) .. + 3 of a stage, at the
-// lane's own place (c = rg, row or column 4 cl); lda4, ldb4: four c's further.
-__device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int wave, const float* ap, long lda4, const float* bp, long ldb4, int n)
+// lane's own place (c = rg, row or column 4 cl); lda8, ldb8: eight c's further.  values() requests acc's values, behind the first operands.
+template <typename Values>
+__device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int wave, const float* ap, long lda8, const float* bp, long ldb8, int n,
+                                                 Values values)
 {
     constexpr int kStage = 2 * 16 * kGqGroup;                   // floats of one operand
     const int lane = threadIdx.x & 63;
@@ -397,11 +513,11 @@ __device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int w
     float4 fa[2], fb[2];
     auto fetch = [&] {
         fa[0] = load_global<float4>(ap);
-        fa[1] = load_global<float4>(ap + 2 * lda4);
+        fa[1] = load_global<float4>(ap + lda8);
         fb[0] = load_global<float4>(bp);
-        fb[1] = load_global<float4>(bp + 2 * ldb4);
-        ap += 4 * lda4;
-        bp += 4 * ldb4;
+        fb[1] = load_global<float4>(bp + ldb8);
+        ap += 2 * lda8;
+        bp += 2 * ldb8;
         __builtin_amdgcn_sched_barrier(0);                      // or they move down to their use
     };
     auto park = [&](int buf) {
@@ -426,6 +542,8 @@ __device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int w
         }
     };
     fetch();
+    values();
+    __builtin_amdgcn_sched_barrier(0);
     park(0);
     int buf = 0;
 #pragma unroll 1
@@ -438,35 +556,34 @@ __device__ __forceinline__ void gq_tile_products(GqTile& acc, float* s_op, int w
     multiply(buf);
 }
 
-// v[r, j] = fma(-E[c, r], U[c, j], v[r, j]) for the panel's n_cols columns c in ascending order, every row r, columns
+// v[r, j] = fma(-E[c, r], U[c, j], v[r, j]) for the columns c of the panel before in ascending order, every row r, columns
 // [col_begin, K).  A wavefront owns 64 x 64 values, a workgroup 128 x 128; FIRST: v's values are still those of w.
-// Bound: fp32 matrix instructions (a register-only loop holds 150 TFLOP/s).  14336 rows, 256 columns over the 3840 behind
-// them: 250 us = 113 TFLOP/s, and v is passed over 16 times for 4096 columns; as vector fmas, 128 columns a pass, the
-// same corrections took 3.9 ms per matrix at 57 TFLOP/s where these take 2.1 ms.
+// Bound: fp32 matrix instructions (a register-only loop holds 150 TFLOP/s; with operands from LDS and barriers 148).  Behind 14336 rows
+// 256 columns more cost 17 us = 110 TFLOP/s, 120 without the chains beside them; the values' way in and out is 6 % of it.
 template <bool FIRST>
-__global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u,
-                                                         long N, long K, long base, int n_cols, long col_begin, GqErr err)
+__device__ __forceinline__ void gq_rest(float* s_op, const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K, long base,
+                                        const GqErr& err, long col_begin, uint32_t wg)
 {
+    constexpr int kRows = 2 * kGqRows;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rg = lane >> 4, cl = lane & 15;
     // Workgroups are dealt to the eight XCDs in turn: an XCD takes every eighth pair of row blocks, and walks them eight
     // pairs at a time across all columns, so that the 64 tiles it runs at a time share 8 row and 8 column operands in its L2.
-    const uint32_t row_pairs = (uint32_t)((N + 2 * kGqRows - 1) / (2 * kGqRows));
+    const uint32_t row_pairs = (uint32_t)((N + 2 * kRows - 1) / (2 * kRows));
     const uint32_t col_pairs = (uint32_t)((K - col_begin + 2 * kGqGroup - 1) / (2 * kGqGroup));
-    const uint32_t xcd = blockIdx.x & 7, at = blockIdx.x >> 3;
+    const uint32_t xcd = wg & 7, at = wg >> 3;
     const uint32_t per_xcd = (row_pairs + 7) >> 3;
     const uint32_t band = at / (8 * col_pairs), in_band = at - band * 8 * col_pairs;
     const uint32_t height = min(8u, per_xcd - 8 * band);
     const uint32_t cp = in_band / height, rp = xcd + 8 * (8 * band + in_band - cp * height);
     if (rp >= row_pairs) return;
     // a wavefront whose block lies outside (an odd number of blocks) works on the last one as well and keeps it to itself
-    const long n_blocks = (N + kGqRows - 1) / kGqRows;
+    const long n_blocks = (N + kRows - 1) / kRows;
     const long block = min(2 * (long)rp + (wave >> 1), n_blocks - 1);
     const long col0 = min(col_begin + (2 * (long)cp + (wave & 1)) * kGqGroup, K - kGqGroup);
     const bool mine = 2 * (long)rp + (wave >> 1) == block && col_begin + (2 * (long)cp + (wave & 1)) * kGqGroup == col0;
-    const long row0 = block * kGqRows;
-    const bool whole = row0 + kGqRows <= N;
-    __shared__ __attribute__((aligned(16))) float s_op[2 * 2 * 2 * 16 * kGqGroup];
+    const long row0 = block * kRows;
+    const bool whole = row0 + kRows <= N;
     const uint32_t off = 16 * rg * (uint32_t)K + 4 * cl;
     GqTile acc;
     auto load = [&](int i, int a, const void* at) {
@@ -483,18 +600,23 @@ __global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __re
         if constexpr (FIRST) return w + row0 * K + col0;
         else return (const float*)v + row0 * K + col0;
     }();
-    if (whole) {
+    auto values = [&] {
+        if (whole) {
 #pragma unroll
-        for (int r = 0; r < 16; r++) load(r >> 2, r & 3, src + r * K + off);
-    } else {
-        const int last = (int)(N - 1 - row0);
+            for (int r = 0; r < 16; r++) load(r >> 2, r & 3, src + r * K + off);
+        } else {
+            const int last = (int)(N - 1 - row0);
 #pragma unroll
-        for (int r = 0; r < 16; r++) load(r >> 2, r & 3, src + min(16 * rg + r, last) * K + 4 * cl);
-    }
+            for (int r = 0; r < 16; r++) load(r >> 2, r & 3, src + min(16 * rg + r, last) * K + 4 * cl);
+        }
+    };
+    // the errors of 64 rows are two blocks': lanes with cl < 8 read the first one's
+    const long e_blocks = (N + kGqRows - 1) / kGqRows;
     long eld;
-    const float* const eb = gq_err_block(err, min(2 * (long)rp + (wave & 1), n_blocks - 1), eld);
-    gq_tile_products(acc, s_op, wave, eb + (wave >> 1) * eld + 4 * lane, eld, u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl,
-                            4 * K, n_cols);
+    const float* const eb = gq_err_block(err, min(2 * min(2 * (long)rp + (wave & 1), n_blocks - 1) + (cl >> 3), e_blocks - 1), eld);
+    const int per = err.cols >> 5;                              // columns c a row of the errors, 8 or 4
+    gq_tile_products(acc, s_op, wave, eb + gq_err_at(err, eld, 4 * (wave >> 1) + rg, 4 * (cl & 7)), per == 8 ? eld : 2 * eld,
+                     u + (base + 4 * (wave >> 1) + rg) * K + col0 + 4 * cl, 8 * K, err.cols, values);
     if (!mine) return;
     float* dst = v + row0 * K + col0;
     asm("" : "+s"(dst));        // the loads' 16 addresses are worked out again here, not kept through the products
@@ -513,29 +635,29 @@ __global__ __launch_bounds__(256, 2) void gptq_trail_kernel(const uint16_t* __re
     }
 }
 
-// The same corrections for launches that the kernel above leaves the chip half empty in (its workgroup takes 15 us of matrix
-// instructions whatever there is beside it): a workgroup 64 x 64, a wavefront 32 x 32, the operands of 64 columns c at a time
-// through LDS.  Up to three quarters of a workgroup of the other kernel per compute unit; a whole sweep, us, other / this:
-// 200 x 4096 764 / 583, 1700 x 1024 179 / 151, 5097 x 832 162 / 141; 8000 x 1024 (252 workgroups and fewer) 203 / 203, 14336 x
-// 512 (224) 85 / 88.
+// The same corrections where those workgroups leave the chip half empty (one takes 15 us of matrix instructions whatever
+// there is beside it): a workgroup 64 x 64, a wavefront 32 x 32, the operands of 64 columns c at a time through LDS.  Up to three
+// quarters of a workgroup of the other kind per compute unit.
 template <bool FIRST>
-__global__ __launch_bounds__(256, 4) void gptq_trail_small_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u,
-                                                               long N, long K, long base, int n_cols, long col_begin, GqErr err)
+__device__ __forceinline__ void gq_rest_small(float* s_a, const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
+                                              long base, const GqErr& err, long col_begin, uint32_t wg)
 {
-    __shared__ __attribute__((aligned(16))) float s_a[kGqGroup * kGqGroup], s_b[kGqGroup * kGqGroup];     // errors, rows of U: [c][64]
+    constexpr int kRows = 2 * kGqRows;
+    float* const s_b = s_a + kGqGroup * kGqGroup;               // errors, rows of U: [c][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane >> 4, cl = lane & 15, wi = wave >> 1, wj = wave & 1;
-    const uint32_t n_blocks = (uint32_t)((N + kGqRows - 1) / kGqRows);
-    const long cb = blockIdx.x / n_blocks, block = blockIdx.x - (uint32_t)cb * n_blocks;
-    const long col0 = col_begin + cb * kGqGroup, row0 = block * kGqRows;
+    const uint32_t n_blocks = (uint32_t)((N + kRows - 1) / kRows);
+    const long cb = wg / n_blocks, block = wg - (uint32_t)cb * n_blocks;
+    const long col0 = col_begin + cb * kGqGroup, row0 = block * kRows;
     long eld;
-    const float* const eb = gq_err_block(err, block, eld);
+    const long e_blocks = (N + kGqRows - 1) / kGqRows;
+    const float* const eb = gq_err_block(err, min(2 * block + ((tid & 15) >> 3), e_blocks - 1), eld);
     float4 sa[4], sb[4];
     auto fetch = [&](int c0) {
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int c = c0 + (tid >> 4) + 16 * i;
-            sa[i] = load_global<float4>(eb + (long)(c >> 2) * eld + (c & 3) * kGqRows + 4 * (tid & 15));
+            sa[i] = load_global<float4>(eb + gq_err_at(err, eld, c, 4 * (tid & 7)));
             sb[i] = load_global<float4>(u + (base + c) * K + col0 + 4 * (tid & 15));
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -561,7 +683,7 @@ __global__ __launch_bounds__(256, 4) void gptq_trail_small_kernel(const uint16_t
     const float* const ap = s_a + rg * kGqGroup + 32 * wi + 2 * cl;
     const float* const bp = s_b + rg * kGqGroup + 32 * wj + 2 * cl;
 #pragma unroll 1
-    for (int c0 = 0; c0 < n_cols; c0 += kGqGroup) {
+    for (int c0 = 0; c0 < err.cols; c0 += kGqGroup) {
         if (c0 > 0) __syncthreads();                    // the operands before have been read
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -569,7 +691,7 @@ __global__ __launch_bounds__(256, 4) void gptq_trail_small_kernel(const uint16_t
             *reinterpret_cast<float4*>(s_b + 4 * (tid + 256 * i)) = sb[i];
         }
         __syncthreads();
-        fetch(min(c0 + kGqGroup, n_cols - kGqGroup));   // (past the end: the last ones again, unused)
+        fetch(min(c0 + kGqGroup, err.cols - kGqGroup));  // (past the end: the last ones again, unused)
 #pragma unroll 4
         for (int kk = 0; kk < kGqGroup / 4; kk++) {
             const float2 av = *reinterpret_cast<const float2*>(ap + kk * 4 * kGqGroup);
@@ -583,6 +705,26 @@ __global__ __launch_bounds__(256, 4) void gptq_trail_small_kernel(const uint16_t
 #pragma unroll
     for (int r = 0; r < 8; r++)
         if (row0 + r0 + r < N) store_global(v + (row0 + r0 + r) * K + at, make_float2(acc[r & 1][0][r >> 1], acc[r & 1][1][r >> 1]));
+}
+
+// A panel's launch: its rows first, 32 a workgroup, so that the chains start at once, then the columns behind it.
+// FIRST: the values of both are still those of w (the first two panels).
+// The whole sweep, us, with the panel's rows (64 a workgroup) and the columns behind it in launches of their own / so: 14336 x 4096
+// 2525 / 2340, 4096 x 4096 1166 / 944, 8000 x 1024 208 / 165, 2500 x 2048 391 / 325, 200 x 4096 588 / 548, 14336 x 512 90 / 87.
+template <int BITS, bool FIRST, bool SMALL>
+__global__ __launch_bounds__(256, 3) void gptq_panel_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
+                                                            long base, int n_groups, GqErr before, GqErr err, int row_blocks,
+                                                            uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
+{
+    __shared__ __attribute__((aligned(16))) float s_all[kGqPanelLds];
+    static_assert(kGqPanelLds >= 2 * 2 * 2 * 16 * kGqGroup, "the other workgroups' operands fit");
+    const long next = base + kGqGroup * n_groups;
+    if ((int)blockIdx.x < row_blocks)
+        gq_panel_rows<BITS, FIRST>(s_all, w, v, u, N, K, base, n_groups, before, err, base > 0, next >= K, codes, scale, zero);
+    else if constexpr (SMALL)
+        gq_rest_small<FIRST>(s_all, w, v, u, N, K, base - before.cols, before, next, blockIdx.x - row_blocks);
+    else
+        gq_rest<FIRST>(s_all, w, v, u, N, K, base - before.cols, before, next, blockIdx.x - row_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -1409,41 +1551,38 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
     if (workspace_bytes < dymoe_gptq_workspace_bytes(N, K)) return DYMOE_ENOSPC;
     if (!ctx) return DYMOE_ENOCTX;
     hipStream_t st = (hipStream_t)stream;
-    const long n_blocks = gq_row_blocks(N);
+    const long row_blocks = gq_row_blocks(N), n_blocks = (N + 2 * kGqRows - 1) / (2 * kGqRows);
     float* v = reinterpret_cast<float*>(workspace);
     float* tail = reinterpret_cast<float*>((char*)workspace + gq_round256((size_t)N * (size_t)K * 4));
-    const int panel = gq_panel(N);
+    const int panel = gq_panel(N), cols = panel * kGqGroup;
     const uint16_t* w = (const uint16_t*)w_bf16;
     uint16_t* sc = (uint16_t*)scale;
     uint16_t* zr = (uint16_t*)zero;
-    for (long base = 0; base < K; base += panel * kGqGroup) {
+    GqErr before = {};
+    for (long base = 0; base < K; base += cols) {
         const long left = (K - base) / kGqGroup;
         const int groups = (int)(left < panel ? left : panel);
         const long next = base + groups * kGqGroup;
-        const GqErr err = {v + base, K, tail, N / kGqRows};
-        auto go = [&](auto kernel) {
-            dymoe_launch(ctx, DYMOE_K_GPTQ_GROUP, kernel, dim3((unsigned)n_blocks), dim3(256), 0, st, w, v, u, N, K, base,
-                         groups, err, codes, sc, zr);
-        };
-        const bool first = base == 0;
-        if (bits == 8) first ? go(gptq_group_kernel<8, true>) : go(gptq_group_kernel<8, false>);
-        else if (bits == 4) first ? go(gptq_group_kernel<4, true>) : go(gptq_group_kernel<4, false>);
-        else first ? go(gptq_group_kernel<2, true>) : go(gptq_group_kernel<2, false>);
-        DYMOE_HIP_LAUNCH_CHECK();
-        if (next >= K) break;
+        const GqErr err = {v + base, tail + ((base / cols) & 1) * cols * kGqRows, K, N / kGqRows, cols};
+        // 128 x 128 a workgroup from three quarters of one per compute unit on, else 64 x 64
         const long row_pairs = (n_blocks + 1) / 2, col_pairs = (K - next + 2 * kGqGroup - 1) / (2 * kGqGroup);
-        auto trail = [&](auto kernel, long blocks) {
-            dymoe_launch(ctx, DYMOE_K_GPTQ_TRAIL, kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, v, u, N, K, base, groups * kGqGroup,
-                         next, err);
+        const bool first = base <= cols, small = 4 * row_pairs * col_pairs <= 3L * ctx->num_cu;
+        long rest = 0;
+        if (base > 0 && next < K) rest = small ? n_blocks * ((K - next) / kGqGroup) : 8 * ((row_pairs + 7) / 8) * col_pairs;
+        auto go = [&](auto kernel) {
+            dymoe_launch(ctx, rest ? DYMOE_K_GPTQ_TRAIL : DYMOE_K_GPTQ_GROUP, kernel, dim3((unsigned)(row_blocks + rest)), dim3(256), 0, st, w, v,
+                         u, N, K, base, groups, before, err, (int)row_blocks, codes, sc, zr);
         };
-        if (4 * row_pairs * col_pairs <= 3L * ctx->num_cu) {
-            const long blocks = n_blocks * ((K - next) / kGqGroup);
-            first ? trail(gptq_trail_small_kernel<true>, blocks) : trail(gptq_trail_small_kernel<false>, blocks);
-        } else {
-            const long blocks = 8 * ((row_pairs + 7) / 8) * col_pairs;
-            first ? trail(gptq_trail_kernel<true>, blocks) : trail(gptq_trail_kernel<false>, blocks);
-        }
+        auto pick = [&](auto bits) {
+            constexpr int BITS = decltype(bits)::value;
+            if (small) first ? go(gptq_panel_kernel<BITS, true, true>) : go(gptq_panel_kernel<BITS, false, true>);
+            else first ? go(gptq_panel_kernel<BITS, true, false>) : go(gptq_panel_kernel<BITS, false, false>);
+        };
+        if (bits == 8) pick(std::integral_constant<int, 8>());
+        else if (bits == 4) pick(std::integral_constant<int, 4>());
+        else pick(std::integral_constant<int, 2>());
         DYMOE_HIP_LAUNCH_CHECK();
+        before = err;
     }
     return DYMOE_OK;
 }

@@ -301,6 +301,15 @@ def test_gptq_sweep_panel_edges(ctx, N, K, bits):
     assert _same(got, want)
 
 
+# row blocks of 32 whose errors outlive the launch that makes them: one ragged block, a whole and a ragged one, two whole ones, three and a
+# half; half panels below 64 rows, last panels of every number of groups
+@pytest.mark.parametrize("N,K,bits", [(1, 704, 4), (31, 832, 8), (32, 640, 4), (33, 1152, 2), (63, 1088, 4), (95, 1344, 4), (96, 896, 2),
+                                      (97, 1216, 8), (128, 1536, 4), (161, 1024, 4)])
+def test_gptq_sweep_row_blocks(ctx, N, K, bits):
+    _, wb, U = _case(1200 + N, N, K)
+    assert _same(ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(U).to(DEV), bits), O.gptq_quantize_pack(wb, U, bits))
+
+
 @pytest.mark.parametrize("bits", [2, 4, 8])
 def test_gptq_sweep_subnormal_errors(ctx, bits):
     """Rows so small that rest / U[c,c] is subnormal, beside ordinary ones in the same groups: the ordinary rows' codes, and
