@@ -195,6 +195,35 @@ __device__ __forceinline__ bool mat_present(const ExpertMat& m, int b)
     return (b == 16) ? (m.w != nullptr) : (m.q != nullptr && m.s != nullptr && m.z != nullptr);
 }
 
+// What the second phase reads of a (token, expert) pair: its down projection, its gate weight and its bit width (0: the pair
+// adds nothing).  Left in the workspace by the first phase's workgroup that has the pair's first rows: read from the pair's
+// index on, expert, bit width and table entry are three loads that wait for each other, and the whole second phase is a few of
+// those long where the experts are small.
+struct alignas(32) PairDown {
+    const void* codes;      // bf16 rows where bits == 16
+    const uint16_t* s;
+    const uint16_t* z;
+    float gate;
+    int32_t bits;
+};
+static_assert(sizeof(PairDown) == 32, "one scalar load");
+
+// (called by the workgroup with the pair's first rows; a format that is not in the table leaves the pair out)
+__device__ __forceinline__ void leave_pair_down(PairDown* __restrict__ down, const ExpertMat& m2, int p, int b, float gate,
+                                                unsigned* __restrict__ flags)
+{
+    if (threadIdx.x != 0) return;
+    const bool there = mat_present(m2, b);
+    if (!there) atomicOr(flags, DYMOE_FLAG_FORMAT_MISSING);
+    PairDown d;
+    d.codes = b == 16 ? (const void*)m2.w : (const void*)m2.q;
+    d.s = m2.s;
+    d.z = m2.z;
+    d.gate = gate;
+    d.bits = there ? b : 0;
+    down[p] = d;
+}
+
 // what one lane loads of one row: NSEG segments starting at column seg0 * 2048
 template <int BITS, int NSEG> struct RowRegs;
 template <int NSEG> struct RowRegs<16, NSEG> { uint4 c[NSEG][4]; };      // (the first NCH of 4, see load_row)
@@ -401,8 +430,8 @@ __device__ __forceinline__ void phase1_bf16(const ExpertMat& m1, const ExpertMat
 // One (token, expert) pair p: rows [f_begin, f_end) of W1 and W3 of expert e at b bits.
 template <int NSEG>
 __device__ __forceinline__ void phase1_pair(const uint16_t* __restrict__ x, const dymoe_expert_fmt* __restrict__ table,
-                                            int p, int e, int b, int H, int F, int k, int rows_per_block,
-                                            float* __restrict__ hbuf, unsigned* __restrict__ flags)
+                                            int p, int e, int b, float gate, int H, int F, int k, int rows_per_block,
+                                            float* __restrict__ hbuf, PairDown* __restrict__ down, unsigned* __restrict__ flags)
 {
     const int t = p / k;
     const int f_begin = blockIdx.x * rows_per_block;
@@ -417,30 +446,36 @@ __device__ __forceinline__ void phase1_pair(const uint16_t* __restrict__ x, cons
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(flags, DYMOE_FLAG_FORMAT_MISSING);
     };
     if (b == 16) {
+        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 16), p, 16, gate, flags);
         phase1_bf16<NSEG>(pick_mat(ex, 0, 16), pick_mat(ex, 1, 16), xrow, H, f_begin, f_end, hrow, missing);
     } else if (b == 8) {
+        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 8), p, 8, gate, flags);
         phase1_quant<8, NSEG>(pick_mat(ex, 0, 8), pick_mat(ex, 1, 8), xrow, H, f_begin, f_end, hrow, missing);
     } else if (b == 4) {
+        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 4), p, 4, gate, flags);
         phase1_quant<4, NSEG>(pick_mat(ex, 0, 4), pick_mat(ex, 1, 4), xrow, H, f_begin, f_end, hrow, missing);
     } else {
+        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 2), p, 2, gate, flags);
         phase1_quant<2, NSEG>(pick_mat(ex, 0, 2), pick_mat(ex, 1, 2), xrow, H, f_begin, f_end, hrow, missing);
     }
 }
 
 template <int NSEG>
 __global__ __launch_bounds__(kGvThreads) void gemv_phase1_kernel(
-    const uint16_t* __restrict__ x, const int32_t* __restrict__ idx,
+    const uint16_t* __restrict__ x, const int32_t* __restrict__ idx, const float* __restrict__ w,
     const uint8_t* __restrict__ bits, const dymoe_expert_fmt* __restrict__ table, int H, int F,
-    int E, int k, int rows_per_block, float* __restrict__ hbuf, unsigned* __restrict__ flags)
+    int E, int k, int rows_per_block, float* __restrict__ hbuf, PairDown* __restrict__ down, unsigned* __restrict__ flags)
 {
     // pairs in reverse: a token's later slots carry the less important experts, hence the narrower formats,
     // whose workgroups are short and latency-bound; dispatched first they overlap the wide ones instead of forming the tail
     const int p = (int)gridDim.y - 1 - (int)blockIdx.y;
     const int e = idx[p];
-    if (e < 0 || e >= E) return;
-    const int b = bits[e];
-    if (b != 16 && b != 8 && b != 4 && b != 2) return;
-    phase1_pair<NSEG>(x, table, p, e, b, H, F, k, rows_per_block, hbuf, flags);
+    const int b = (e >= 0 && e < E) ? bits[e] : 0;
+    if (b != 16 && b != 8 && b != 4 && b != 2) {              // pairs of skipped experts add nothing
+        if (blockIdx.x == 0 && threadIdx.x == 0) down[p].bits = 0;
+        return;
+    }
+    phase1_pair<NSEG>(x, table, p, e, b, w[p], H, F, k, rows_per_block, hbuf, down, flags);
 }
 
 // The first phase with the decode step's front end in front of it (router gating and top-k, decode importance,
@@ -530,7 +565,7 @@ __device__ __forceinline__ void route_logits_of_row(const uint16_t* s_row, const
 template <int NSEG, int NCH, int NC, int FRONT>
 __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
     const FusedFront f, const dymoe_expert_fmt* __restrict__ table, int T, int H, int F, int E, int k, int rows_per_block,
-    float* __restrict__ hbuf, unsigned* __restrict__ flags)
+    float* __restrict__ hbuf, PairDown* __restrict__ down, unsigned* __restrict__ flags)
 {
     __shared__ float s_logit[64 * NC];
     __shared__ float s_selp[kFusedMaxK];
@@ -620,8 +655,11 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
         }
         b = tier_bits_at(pos, f.tiers, f.floor_bits);
     }
-    if (e < 0 || (b != 16 && b != 8 && b != 4 && b != 2)) return;
-    phase1_pair<NSEG>(FRONT == kFrontResidual ? s_row : f.x, table, p, e, b, H, F, k, rows_per_block, hbuf, flags);
+    if (e < 0 || (b != 16 && b != 8 && b != 4 && b != 2)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) down[p].bits = 0;
+        return;
+    }
+    phase1_pair<NSEG>(FRONT == kFrontResidual ? s_row : f.x, table, p, e, b, s_w[p], H, F, k, rows_per_block, hbuf, down, flags);
 }
 
 // ---------------------------------------------------------------- phase 2
@@ -632,6 +670,12 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
 // only after its last unit are the accumulators summed over the lanes (once per row instead of once per row and
 // segment), then over the wavefronts through LDS in a fixed order, and y is written: no partial sums in memory
 // and no separate combining launch.
+// What is not streaming is start-up: until the first rows are requested the memory stands idle (a launch of 17 us over eight
+// stacked layers, of 5 over small experts, waited 1.5 us for pair, expert, bit width and table entry, one after the other).  So
+// the pair's entry comes ready from the first phase, in one scalar load for both of a round's units; the activations are
+// requested with the first two batches of rows and not ahead of them; and the code in front of the loads is short.  From the
+// kernel's start to the first requests 1.5 -> 0.5 us; one token, us a step before / after: eight of 128 experts 2048 x 768, 4/2
+// bits 23.5 / 22.0, 4096 x 14336 16/4/2 bits 80.7 / 78.4, six of 64 1024 x 3072 31.1 / 29.9; 21 shapes 0.97.
 
 // rows a wavefront requests at a time: two batches at least
 template <int BITS, int ROWS> struct Phase2Rows { static constexpr int R = (ROWS == 4) ? 2 : (BITS == 16 || BITS == 8 || ROWS == 8) ? 4 : 8; };
@@ -658,10 +702,11 @@ __device__ __forceinline__ float dot_row_h(const RowRegs<16, 1>& rr, const LaneH
     return acc;
 }
 
-// one unit: segment `seg` of rows j_begin .. j_begin + ROWS - 1 (clamped to the last row H - 1)
-template <int BITS, int ROWS, int NCH, typename XT, typename DotFn>
+// one unit: segment `seg` of rows j_begin .. j_begin + ROWS - 1 (clamped to the last row H - 1).  arrange() makes the
+// unit's activations of what was requested before: the first rows are on their way when it waits for them.
+template <int BITS, int ROWS, int NCH, typename ArrangeFn, typename DotFn>
 __device__ __forceinline__ void phase2_unit(const ExpertMat& m2, int F, int seg, int j_begin, int H,
-                                            float gate, float (&tot)[ROWS], const XT& lx, DotFn dot)
+                                            float gate, float (&tot)[ROWS], ArrangeFn arrange, DotFn dot)
 {
     constexpr int R = Phase2Rows<BITS, ROWS>::R;
     constexpr int NB = ROWS / R;                 // 4 or 2 batches of rows
@@ -673,26 +718,29 @@ __device__ __forceinline__ void phase2_unit(const ExpertMat& m2, int F, int seg,
         for (int i = 0; i < R; i++) load_row<BITS, 1, NCH>(m2, min(j0 + i, H - 1), F, seg, lane, dst[i]);
     };
     fetch(ra, j_begin);
+    fetch(rb, j_begin + R);
+    __builtin_amdgcn_sched_barrier(0);
+    const auto lx = arrange();
 #pragma unroll
     for (int bt = 0; bt < NB; bt += 2) {
-        fetch(rb, j_begin + (bt + 1) * R);          // next batch first
 #pragma unroll
         for (int i = 0; i < R; i++) tot[bt * R + i] = fmaf(gate, dot(ra[i], lx), tot[bt * R + i]);
         if (bt + 2 < NB) fetch(ra, j_begin + (bt + 2) * R);
 #pragma unroll
         for (int i = 0; i < R; i++) tot[(bt + 1) * R + i] = fmaf(gate, dot(rb[i], lx), tot[(bt + 1) * R + i]);
+        if (bt + 3 < NB) fetch(rb, j_begin + (bt + 3) * R);
     }
 }
 
-// Two units of narrow formats (int4, int2) side by side: a wavefront's start-up chain (pair -> expert -> bit width ->
-// table entry -> activations -> first rows) is a string of dependent latencies, and with 16 rows of int4 or int2
-// there is little streaming to hide the second unit's chain behind.  Taken together, both chains run at once.
-template <int BA, int BB, int ROWS>
+// Two units of narrow formats (int4, int2) side by side: a wavefront's start-up chain (pair -> activations and first rows) is
+// a string of dependent latencies, and with 16 rows of int4 or int2 there is little streaming to hide the second unit's chain
+// behind.  Taken together, both chains run at once.
+template <int BA, int BB, int ROWS, typename ArrangeFn>
 __device__ __forceinline__ void phase2_two_units(const ExpertMat& ma, const ExpertMat& mb, int F, int sa, int sb,
                                                  int j_begin, int H, float ga, float gb,
-                                                 float (&tot)[ROWS], const LaneX (&la)[1], const LaneX (&lb)[1])
+                                                 float (&tot)[ROWS], ArrangeFn arrange)
 {
-    constexpr int R = (ROWS == 4) ? 2 : (BA == 2 && BB == 2 && ROWS > 8) ? 8 : 4;
+    constexpr int R = (ROWS == 4) ? 2 : 4;      // (eight int2 rows of both at a time spill: eight of 8 experts, 4096 x 6144, 97 / 87 us)
     constexpr int NB = ROWS / R;
     static_assert(NB % 2 == 0, "batches come in pairs");
     const int lane = threadIdx.x & (kWave - 1);
@@ -706,6 +754,7 @@ __device__ __forceinline__ void phase2_two_units(const ExpertMat& ma, const Expe
             load_row<BB, 1>(mb, row, F, sb, lane, db[i]);
         }
     };
+    LaneX la[1], lb[1];
     auto finish = [&](const RowRegs<BA, 1>(&da)[R], const RowRegs<BB, 1>(&db)[R], int bt) {
 #pragma unroll
         for (int i = 0; i < R; i++) {
@@ -714,6 +763,8 @@ __device__ __forceinline__ void phase2_two_units(const ExpertMat& ma, const Expe
         }
     };
     fetch(a0, b0, j_begin);
+    __builtin_amdgcn_sched_barrier(0);
+    arrange(la[0], lb[0]);
 #pragma unroll
     for (int bt = 0; bt < NB; bt += 2) {
         fetch(a1, b1, j_begin + (bt + 1) * R);
@@ -725,133 +776,140 @@ __device__ __forceinline__ void phase2_two_units(const ExpertMat& ma, const Expe
 
 template <int ROWS, int NCH>
 __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
-    const float* __restrict__ hbuf, const int32_t* __restrict__ idx, const float* __restrict__ w,
-    const uint8_t* __restrict__ bits, const dymoe_expert_fmt* __restrict__ table, int H, int F,
-    int E, int k, int nseg, int out_dtype, void* __restrict__ y, unsigned* __restrict__ flags)
+    const float* __restrict__ hbuf, const PairDown* __restrict__ down, int H, int F, int k, int nseg, unsigned nseg_inv,
+    int nwaves, int rounds, int out_dtype, void* __restrict__ y)
 {
     __shared__ float s_red[kP2MaxWaves][ROWS];
     const int t = blockIdx.y;
-    const int j_begin = blockIdx.x * ROWS;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int nwaves = blockDim.x / kWave;
     float tot[ROWS];
 #pragma unroll
     for (int i = 0; i < ROWS; i++) tot[i] = 0.0f;
     const int units = k * nseg;
-    const int rounds = (units + nwaves - 1) / nwaves;
     // odd wavefronts take their units in reverse: the slots of a token differ in format (the later, the narrower),
     // and a compute unit should at any time hold wavefronts on wide, bandwidth-bound rows beside wavefronts on
     // narrow, instruction-bound ones instead of all of them on the same kind
     struct Unit {
-        int valid, p, s, e, b;
+        int p, s, b;
+        float gate;
+        ExpertMat m2;
     };
     auto unit_of = [&](int r) {
-        Unit un = {0, 0, 0, 0, 0};
-        if (r >= rounds) return un;
         const int u = wave + nwaves * ((wave & 1) ? rounds - 1 - r : r);
-        if (u >= units) return un;
-        const int slot = u / nseg;
-        un.s = u - slot * nseg;
+        const bool one = r < rounds && u < units;
+        const int v = one ? u : 0;
+        int slot = nseg == 1 ? v : (int)__umulhi((unsigned)v, nseg_inv);      // v / nseg, or one more
+        if (slot * nseg > v) slot--;
+        Unit un;
+        un.s = v - slot * nseg;
         un.p = t * k + slot;
-        un.e = idx[un.p];
-        if (un.e < 0 || un.e >= E) return un;       // pairs of skipped experts add nothing
-        un.b = bits[un.e];
-        un.valid = (un.b == 16 || un.b == 8 || un.b == 4 || un.b == 2);
+        const PairDown d = down[un.p];
+        un.b = one ? d.bits : 0;
+        un.gate = d.gate;
+        un.m2.w = (const uint16_t*)d.codes;
+        un.m2.q = (const uint8_t*)d.codes;
+        un.m2.s = d.s;
+        un.m2.z = d.z;
         return un;
     };
+    // the unit's activations, of the lane's 32 columns in the order of quantised rows or in that of bf16 rows.  Columns past
+    // the end are read as the row's first and made zero when the activations are used: a load under a condition, or anything
+    // done to what it brought, would be waited for ahead of the first rows' loads.
     auto quant_x = [&](const Unit& un, float (&v)[32]) {
-        const float* hrow = hbuf + (long)un.p * F;
         const int col0 = un.s * kSeg + 32 * lane;
+        const float* from = hbuf + (long)un.p * F + (col0 < F ? col0 : 0);
 #pragma unroll
         for (int c = 0; c < 8; c++) {
-            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (col0 < F) q = *reinterpret_cast<const float4*>(hrow + col0 + 4 * c);
+            const float4 q = *reinterpret_cast<const float4*>(from + 4 * c);
             v[4 * c + 0] = q.x; v[4 * c + 1] = q.y; v[4 * c + 2] = q.z; v[4 * c + 3] = q.w;
         }
     };
-    auto one_unit = [&](const Unit& un) {
-        const int p = un.p, s = un.s, e = un.e, b = un.b;
-        const float gate = w[p];
-        const float* hrow = hbuf + (long)p * F;
-        const dymoe_expert_fmt ex = table[e];
-        auto missing = [&]() {                 // format not in the table: the pair is left out
-            if (blockIdx.x == 0 && lane == 0) atomicOr(flags, DYMOE_FLAG_FORMAT_MISSING);
-        };
-        if (b == 16) {
-            const ExpertMat m2 = pick_mat(ex, 2, 16);
-            if (!mat_present(m2, 16)) return missing();
-            LaneH lh;
+    auto quant_end = [&](const Unit& un, float (&v)[32]) {
+        const bool in = un.s * kSeg + 32 * lane < F;
 #pragma unroll
-            for (int c = 0; c < NCH; c++) {
-                const int col = s * kSeg + (c * kWave + lane) * 8;
+        for (int i = 0; i < 32; i++) v[i] = in ? v[i] : 0.0f;
+    };
+    auto bf16_x = [&](const Unit& un, LaneH& lh) {
+        const float* hrow = hbuf + (long)un.p * F;
 #pragma unroll
-                for (int i = 0; i < 8; i++) lh.v[c][i] = 0.0f;
-                if (col < F) {
-                    const float4 lo = *reinterpret_cast<const float4*>(hrow + col);
-                    const float4 hi = *reinterpret_cast<const float4*>(hrow + col + 4);
-                    lh.v[c][0] = lo.x; lh.v[c][1] = lo.y; lh.v[c][2] = lo.z; lh.v[c][3] = lo.w;
-                    lh.v[c][4] = hi.x; lh.v[c][5] = hi.y; lh.v[c][6] = hi.z; lh.v[c][7] = hi.w;
-                }
-            }
-            phase2_unit<16, ROWS, NCH>(m2, F, s, j_begin, H, gate, tot, lh,
-                            [](const RowRegs<16, 1>& rr, const LaneH& l) { return dot_row_h<NCH>(rr, l); });
-        } else {
-            const ExpertMat m2 = (b == 8) ? pick_mat(ex, 2, 8) : (b == 4) ? pick_mat(ex, 2, 4) : pick_mat(ex, 2, 2);
-            if (!mat_present(m2, b)) return missing();
-            float v[32];
-            quant_x(un, v);
-            LaneX lx[1];
-            if (b == 8) {
-                arrange_lane_x<8>(v, lx[0]);
-                phase2_unit<8, ROWS, 4>(m2, F, s, j_begin, H, gate, tot, lx,
-                               [](const RowRegs<8, 1>& rr, const LaneX (&l)[1]) { return dot_row_q<8, 1>(rr, l); });
-            } else if (b == 4) {
-                arrange_lane_x<4>(v, lx[0]);
-                phase2_unit<4, ROWS, 4>(m2, F, s, j_begin, H, gate, tot, lx,
-                               [](const RowRegs<4, 1>& rr, const LaneX (&l)[1]) { return dot_row_q<4, 1>(rr, l); });
-            } else {
-                arrange_lane_x<2>(v, lx[0]);
-                phase2_unit<2, ROWS, 4>(m2, F, s, j_begin, H, gate, tot, lx,
-                               [](const RowRegs<2, 1>& rr, const LaneX (&l)[1]) { return dot_row_q<2, 1>(rr, l); });
-            }
+        for (int c = 0; c < NCH; c++) {
+            const int col = un.s * kSeg + (c * kWave + lane) * 8;
+            const float* from = hrow + (col < F ? col : 0);
+            const float4 lo = *reinterpret_cast<const float4*>(from);
+            const float4 hi = *reinterpret_cast<const float4*>(from + 4);
+            lh.v[c][0] = lo.x; lh.v[c][1] = lo.y; lh.v[c][2] = lo.z; lh.v[c][3] = lo.w;
+            lh.v[c][4] = hi.x; lh.v[c][5] = hi.y; lh.v[c][6] = hi.z; lh.v[c][7] = hi.w;
+        }
+    };
+    auto bf16_end = [&](const Unit& un, LaneH& lh) {
+#pragma unroll
+        for (int c = 0; c < NCH; c++) {
+            const bool in = un.s * kSeg + (c * kWave + lane) * 8 < F;
+#pragma unroll
+            for (int i = 0; i < 8; i++) lh.v[c][i] = in ? lh.v[c][i] : 0.0f;
         }
     };
     for (int r = 0; r < rounds; r += 2) {
         const Unit ua = unit_of(r), ub = unit_of(r + 1);
-        bool both = ua.valid && ub.valid && (ua.b == 4 || ua.b == 2) && (ub.b == 4 || ub.b == 2);
-        ExpertMat ma = {}, mb = {};
-        if (both) {
-            ma = pick_mat(table[ua.e], 2, ua.b);
-            mb = pick_mat(table[ub.e], 2, ub.b);
-            both = mat_present(ma, ua.b) && mat_present(mb, ub.b);   // (if not: one by one, each tested again)
-        }
-        if (both) {
-            const float ga = w[ua.p], gb = w[ub.p];
-            LaneX la[1], lb[1];
-            {
+        // (hidden from the compiler, which otherwise computes the addresses of every row in every format before the loop:
+        // some two hundred instructions and spilled registers ahead of the first load)
+        int j_begin = (int)blockIdx.x * ROWS;
+        asm volatile("" : "+s"(j_begin));
+        auto one_unit = [&](const Unit& un) {
+            auto quantised = [&](auto bits) {
+                constexpr int BITS = decltype(bits)::value;
                 float v[32];
-                quant_x(ua, v);
-                if (ua.b == 4) arrange_lane_x<4>(v, la[0]);
-                else arrange_lane_x<2>(v, la[0]);
+                quant_x(un, v);
+                struct One {
+                    LaneX l[1];
+                };
+                phase2_unit<BITS, ROWS, 4>(un.m2, F, un.s, j_begin, H, un.gate, tot, [&] {
+                    One o;
+                    quant_end(un, v);
+                    arrange_lane_x<BITS>(v, o.l[0]);
+                    return o;
+                }, [](const RowRegs<BITS, 1>& rr, const One& o) { return dot_row_q<BITS, 1>(rr, o.l); });
+            };
+            if (un.b == 16) {
+                LaneH lh;
+                bf16_x(un, lh);
+                phase2_unit<16, ROWS, NCH>(un.m2, F, un.s, j_begin, H, un.gate, tot, [&] {
+                    bf16_end(un, lh);
+                    return lh;
+                },
+                                           [](const RowRegs<16, 1>& rr, const LaneH& l) { return dot_row_h<NCH>(rr, l); });
+            } else if (un.b == 8) {
+                quantised(std::integral_constant<int, 8>());
+            } else if (un.b == 4) {
+                quantised(std::integral_constant<int, 4>());
+            } else if (un.b == 2) {
+                quantised(std::integral_constant<int, 2>());
             }
-            {
-                float v[32];
-                quant_x(ub, v);
-                if (ub.b == 4) arrange_lane_x<4>(v, lb[0]);
-                else arrange_lane_x<2>(v, lb[0]);
-            }
-            if (ua.b == 4 && ub.b == 4)
-                phase2_two_units<4, 4, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
-            else if (ua.b == 4)
-                phase2_two_units<4, 2, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
-            else if (ub.b == 4)
-                phase2_two_units<2, 4, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
-            else
-                phase2_two_units<2, 2, ROWS>(ma, mb, F, ua.s, ub.s, j_begin, H, ga, gb, tot, la, lb);
+        };
+        if ((ua.b == 4 || ua.b == 2) && (ub.b == 4 || ub.b == 2)) {
+            auto both = [&](auto bits_a, auto bits_b) {
+                constexpr int BA = decltype(bits_a)::value, BB = decltype(bits_b)::value;
+                float va[32], vb[32];
+                quant_x(ua, va);
+                quant_x(ub, vb);
+                phase2_two_units<BA, BB, ROWS>(ua.m2, ub.m2, F, ua.s, ub.s, j_begin, H, ua.gate, ub.gate, tot,
+                                               [&](LaneX& la, LaneX& lb) {
+                    quant_end(ua, va);
+                    quant_end(ub, vb);
+                    arrange_lane_x<BA>(va, la);
+                    arrange_lane_x<BB>(vb, lb);
+                });
+            };
+            const std::integral_constant<int, 4> four;
+            const std::integral_constant<int, 2> two;
+            if (ua.b == 4 && ub.b == 4) both(four, four);
+            else if (ua.b == 4) both(four, two);
+            else if (ub.b == 4) both(two, four);
+            else both(two, two);
         } else {
-            if (ua.valid) one_unit(ua);
-            if (ub.valid) one_unit(ub);
+            one_unit(ua);
+            one_unit(ub);
         }
     }
     // lanes, then wavefronts (in wavefront order: the result does not depend on timing)
@@ -863,7 +921,7 @@ __global__ __launch_bounds__(kP2MaxWaves * kWave) void gemv_phase2_kernel(
     }
     if (lane < ROWS) s_red[wave][lane] = o;
     __syncthreads();
-    const int j = j_begin + (int)threadIdx.x;
+    const int j = (int)blockIdx.x * ROWS + (int)threadIdx.x;
     if (threadIdx.x < ROWS && j < H) {
         float acc = 0.0f;
         for (int wv = 0; wv < nwaves; wv++) acc += s_red[wv][threadIdx.x];
@@ -882,19 +940,17 @@ static int phase1_rows_per_block(long rows_total)
     return r;
 }
 
-static int phase2_launch(dymoe_ctx* ctx, const float* hbuf, const int32_t* idx, const float* w, const uint8_t* bits,
-                         const dymoe_expert_fmt* table, int T, int H, int F, int E, int k, int out_dtype, void* y,
-                         hipStream_t st)
+static int phase2_launch(dymoe_ctx* ctx, const float* hbuf, const PairDown* down, int T, int H, int F, int k, int out_dtype,
+                         void* y, hipStream_t st)
 {
     // as many wavefronts as (slot, segment) units, at most kP2MaxWaves; of the counts that need the
     // fewest rounds the smallest, so that no wavefront idles through the last round
     const int nseg2 = (F + kSeg - 1) / kSeg;
     const int units = k * nseg2;
     int nwaves = units < kP2MaxWaves ? units : kP2MaxWaves;
-    {
-        const int rounds = (units + nwaves - 1) / nwaves;
-        while (nwaves > 1 && (units + nwaves - 2) / (nwaves - 1) == rounds) nwaves--;
-    }
+    const int rounds = (units + nwaves - 1) / nwaves;
+    while (nwaves > 1 && (units + nwaves - 2) / (nwaves - 1) == rounds) nwaves--;
+    const unsigned nseg_inv = (unsigned)((1ull << 32) / (unsigned)nseg2 + 1);      // (one segment: the kernel does not ask)
     // 16 rows per workgroup, fewer while the workgroups then still find a compute unit each: more of them on a unit only
     // repeat the start-up chain.  One token, us with 16 / 8 / 4 rows: H = 4096, F = 14336, int4 18 / 23 / -; 2048 x 768, eight
     // experts 8.9 / 7.0 / 8.5; 1024 x 3072 9.2 / 7.0 / 5.7; 512 x 1024 8.5 / 6.3 / 5.0; two tokens of 2048 x 768 12.3 / 14.6 / 18.6.
@@ -902,8 +958,8 @@ static int phase2_launch(dymoe_ctx* ctx, const float* hbuf, const int32_t* idx, 
     while (rows > 4 && (long)T * ((H + rows / 2 - 1) / (rows / 2)) <= ctx->num_cu) rows /= 2;
     const dim3 g2((unsigned)((H + rows - 1) / rows), (unsigned)T), block((unsigned)(nwaves * kWave));
     auto go = [&](auto kernel) {
-        dymoe_launch(ctx, DYMOE_K_GEMV_PHASE2, kernel, g2, block, 0, st, hbuf, idx, w, bits, table, H, F, E, k, nseg2, out_dtype, y,
-                     ctx->device_flags);
+        dymoe_launch(ctx, DYMOE_K_GEMV_PHASE2, kernel, g2, block, 0, st, hbuf, down, H, F, k, nseg2, nseg_inv, nwaves, rounds,
+                     out_dtype, y);
     };
     // a segment's bf16 rows are four chunks of 512 columns: rows of at most 1024 columns need no more than two (2048 x 768,
     // eight bf16 experts: 12.4 us with all four, lanes past the end re-reading the tail, 10.2 with two)
@@ -919,6 +975,7 @@ int ffn_gemv_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
 {
     const FfnLayout L = ffn_layout(T, H, F, E, k);
     float* hbuf = reinterpret_cast<float*>((char*)workspace + L.hbuf);
+    PairDown* down = reinterpret_cast<PairDown*>((char*)workspace + L.part);    // room for 4 H bytes a pair, H >= 64
     const int P = T * k;
     const int nseg1 = (H + kSeg - 1) / kSeg;
     const int rows1 = phase1_rows_per_block((long)F * P);
@@ -926,15 +983,15 @@ int ffn_gemv_launch(dymoe_ctx* ctx, const void* x, const int32_t* idx, const flo
     const uint16_t* xb = (const uint16_t*)x;
     {
         switch (nseg1) {
-        case 1: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<1>), g1, dim3(kGvThreads), 0, st, xb, idx, bits, table, H, F, E, k, rows1, hbuf, ctx->device_flags); break;
-        case 2: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<2>), g1, dim3(kGvThreads), 0, st, xb, idx, bits, table, H, F, E, k, rows1, hbuf, ctx->device_flags); break;
-        case 3: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<3>), g1, dim3(kGvThreads), 0, st, xb, idx, bits, table, H, F, E, k, rows1, hbuf, ctx->device_flags); break;
-        case 4: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<4>), g1, dim3(kGvThreads), 0, st, xb, idx, bits, table, H, F, E, k, rows1, hbuf, ctx->device_flags); break;
+        case 1: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<1>), g1, dim3(kGvThreads), 0, st, xb, idx, w, bits, table, H, F, E, k, rows1, hbuf, down, ctx->device_flags); break;
+        case 2: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<2>), g1, dim3(kGvThreads), 0, st, xb, idx, w, bits, table, H, F, E, k, rows1, hbuf, down, ctx->device_flags); break;
+        case 3: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<3>), g1, dim3(kGvThreads), 0, st, xb, idx, w, bits, table, H, F, E, k, rows1, hbuf, down, ctx->device_flags); break;
+        case 4: dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, (gemv_phase1_kernel<4>), g1, dim3(kGvThreads), 0, st, xb, idx, w, bits, table, H, F, E, k, rows1, hbuf, down, ctx->device_flags); break;
         default: return DYMOE_ENOTSUP;
         }
     }
     DYMOE_HIP_LAUNCH_CHECK();
-    return phase2_launch(ctx, hbuf, idx, w, bits, table, T, H, F, E, k, out_dtype, y, st);
+    return phase2_launch(ctx, hbuf, down, T, H, F, k, out_dtype, y, st);
 }
 
 // Whether the fused decode step covers these sizes.
@@ -987,6 +1044,9 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
 {
     const FfnLayout L = ffn_layout(T, H, F, E, k);
     float* hbuf = reinterpret_cast<float*>((char*)workspace + L.hbuf);
+    // (not in the part area, whose logits the first phase still reads; 6 H bytes a token and up to kFusedMaxK pairs, H >= 64)
+    static_assert(kFusedMaxK * sizeof(PairDown) <= 6 * 64, "the pairs' entries fit beside the logits");
+    PairDown* down = reinterpret_cast<PairDown*>((char*)workspace + L.xh);
     const int P = T * k;
     const int nseg1 = (H + kSeg - 1) / kSeg;
     const int rows1 = phase1_rows_per_block((long)F * P);
@@ -997,7 +1057,7 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
     f.idx = idx; f.w = w; f.probs = probs; f.importance = importance; f.load = load; f.bits = bits; f.rank = rank;
     auto go = [&](auto kernel) {
         dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, kernel, g1, dim3(kGvThreads), 0, st, f, table, T, H, F, E, k, rows1, hbuf,
-                     ctx->device_flags);
+                     down, ctx->device_flags);
     };
     // NCH: 16-byte chunks of an activation row per lane, as in dymoe_decode_front (8 up to 4096 columns, then 16)
     auto by_width = [&](auto experts, auto front) {
@@ -1035,7 +1095,7 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
         by_width(std::integral_constant<int, 1>(), std::integral_constant<int, kFrontRouter>());
     }
     DYMOE_HIP_LAUNCH_CHECK();
-    return phase2_launch(ctx, hbuf, idx, w, bits, table, T, H, F, E, k, out_dtype, y, st);
+    return phase2_launch(ctx, hbuf, down, T, H, F, k, out_dtype, y, st);
 }
 
 }  // namespace dymoe

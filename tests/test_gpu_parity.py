@@ -1114,6 +1114,41 @@ def test_gemv_rows_per_workgroup(ctx, T, H, F):
     assert rel_err_per_token(y.cpu().numpy().astype(np.float64), ref) <= 2e-2
 
 
+# what the first GEMV phase leaves for the second, pair by pair: pairs that drop out (no expert, a width of 0 or none of the four, a down
+# projection that is not in the table) in a workspace that still holds a call's entries for them; k segments beside each other
+# (1, 3 and 6 of 2048 columns) divided over the wavefronts
+@pytest.mark.parametrize("T,H,F", [(1, 256, 512), (3, 128, 4160), (2, 64, 10304)])
+def test_gemv_pairs_that_drop_out(ctx, T, H, F):
+    E, k = 6, 5
+    cfg = synth.scaled(synth.CONFIGS["tiny"], T=T, H=H, F=F, E=E, k=k, tier_count=(E,), config_id=1180 + T)
+    x, _ = synth.activations(cfg)
+    full = np.array([16, 8, 4, 2, 4, 2], np.uint8)
+    host, dev, table, keep = build_layer(cfg, full)
+    rng = np.random.default_rng(F)
+    idx = np.stack([rng.permutation(E)[:k] for _ in range(T)]).astype(np.int32)
+    g = (rng.random((T, k)) + 0.1).astype(np.float32)
+    ws = torch.empty((B.workspace_bytes(T, H, F, E, k),), dtype=torch.uint8, device=DEV)
+    def run(i, b, t):
+        y = ctx.moe_ffn_mixed(to_bf16(x), torch.from_numpy(i).to(DEV), torch.from_numpy(g).to(DEV), torch.from_numpy(b).to(DEV), t, F,
+                              out_dtype=B.OUT_F32, path=B.PATH_GEMV, workspace=ws)
+        sync()
+        return y.cpu().numpy().astype(np.float64)
+    assert rel_err_per_token(run(idx, full, table), oracle_ffn(cfg, x, idx, g, full, host)) <= FFN_TOL
+    # expert 1 skipped, expert 2 of an unknown width, expert 3 without its down projection, one pair without an expert
+    bits = np.where(np.arange(E) == 1, 0, np.where(np.arange(E) == 2, 3, full)).astype(np.uint8)
+    dev3 = [dict(d) for d in dev]
+    dev3[3] = {"q2": list(dev[3]["q2"][:2]) + [(None, None, None)]}
+    table3, keep3 = B.make_expert_table(dev3, DEV)
+    idx3 = idx.copy()
+    idx3[T - 1, 0] = -1
+    left = np.where(np.isin(np.arange(E), (1, 2, 3)), 0, full).astype(np.uint8)
+    g_ref = np.where(idx3 < 0, 0.0, g)
+    ref = O.moe_ffn_mixed(x, np.where(idx3 < 0, 1, idx3), g_ref, left, [h if left[e] else {} for e, h in enumerate(host)])
+    assert ctx.device_flags() == 0
+    assert rel_err_per_token(run(idx3, bits, table3), ref) <= FFN_TOL
+    assert ctx.device_flags() == (B.FLAG_FORMAT_MISSING if (idx3 == 3).any() else 0)
+
+
 # the whole step in one call against the separate calls: tokens on both sides of the direct ranking (256), pairs on both sides of what
 # a thread keeps (2, 16, 32 a thread), experts and formats at their limits, tied scores at the boundary, every and no token heavy, staged
 # probabilities in one and several trips
