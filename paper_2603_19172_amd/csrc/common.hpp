@@ -283,12 +283,15 @@ __device__ __forceinline__ int wave_scan_dpp_i32(int v)
 
 __device__ __forceinline__ float wave_max_dpp(float v)
 {
-    v = fmaxf(v, dpp_get_or_self<0xB1, 0xF>(v));
-    v = fmaxf(v, dpp_get_or_self<0x4E, 0xF>(v));
-    v = fmaxf(v, dpp_get_or_self<0x141, 0xF>(v));
-    v = fmaxf(v, dpp_get_or_self<0x140, 0xF>(v));
-    v = fmaxf(v, dpp_get_or_self<0x142, 0xA>(v));
-    v = fmaxf(v, dpp_get_or_self<0x143, 0xC>(v));
+    // One instruction a step (rows that a step leaves out keep their value).  Through fmaxf every step is five: the compiler
+    // keeps a copy for those rows and quiets the operand, which a number that arithmetic has made does not need.
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 1" : "+v"(v));
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 

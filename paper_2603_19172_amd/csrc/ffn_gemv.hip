@@ -580,6 +580,7 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t s_row[FRONT == kFrontResidual ? NSEG * kSeg : 8];
     const int wave = threadIdx.x / kWave;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+    __builtin_assume(k >= 1 && k <= kFusedMaxK);
     for (int e = threadIdx.x; e < E; e += kGvThreads) {
         s_imp[e] = 0.0f;
         s_load[e] = 0;

@@ -241,6 +241,41 @@ def test_route_topk_one_token_per_workgroup(ctx, T, H, E, k):
     _check_route(ctx, x, wg[:E], bias[:E], k, min_ok=0.8)
 
 
+# the rounds of the selection on logits that are known exactly (a zero row leaves the bias): ties, infinities (a round that finds only
+# the smallest takes the lowest index, also again), one that is not a number (never taken); experts and selected ones on both
+# sides of a wavefront; one token alone, in the decode front end with its load counts, and many beside each other
+@pytest.mark.parametrize("E,k", [(5, 5), (30, 3), (64, 8), (65, 8), (100, 64), (128, 8), (130, 65), (300, 7)])
+def test_route_rounds_on_known_logits(ctx, E, k):
+    rng = np.random.default_rng(E + k)
+    logit = rng.integers(-3, 4, E).astype(np.float32)                          # many ties
+    logit[rng.permutation(E)[:max(1, E - k + 2)]] = -np.inf                    # fewer finite ones than rounds
+    for nan in (False, True):
+        if nan:
+            logit[E // 2] = np.nan
+        v, want, top = logit.copy(), [], []
+        for _ in range(k):
+            top.append(np.nanmax(v))
+            want.append(int(np.flatnonzero(v == top[-1])[0]))
+            v[want[-1]] = -np.inf
+        wg, bias = torch.zeros((E, 128), dtype=torch.bfloat16, device=DEV), torch.from_numpy(logit).to(DEV)
+        p = np.exp(np.float64(logit) - np.nanmax(logit))
+        p /= p.sum()
+        p_top = np.exp(np.float64(top) - np.nanmax(logit)) / np.exp(np.float64(logit) - np.nanmax(logit)).sum()
+        for T in (1, 3, 37):
+            x = torch.zeros((T, 128), dtype=torch.bfloat16, device=DEV)
+            for renorm in (True, False):
+                for out in [ctx.route_topk(x, wg, bias, k, renorm=renorm)] + (
+                        [ctx.decode_front(x, wg, bias, k, [E], [4], renorm=renorm)] if T <= 4 and k <= 8 else []):
+                    sync()
+                    assert out[0].cpu().tolist() == [want] * T
+                    # k + E additions and a few roundings of exponential and quotient in fp32
+                    w = p_top / p_top.sum() if renorm else p_top
+                    np.testing.assert_allclose(out[1].cpu().numpy(), np.tile(w, (T, 1)), rtol=(k + E + 8) * 2.0 ** -24, atol=0)
+                    np.testing.assert_allclose(out[2].cpu().numpy(), np.tile(p, (T, 1)), rtol=(E + 8) * 2.0 ** -24, atol=0)
+                    if len(out) > 3:
+                        assert out[4].cpu().tolist() == (T * np.bincount(want, minlength=E)).tolist()
+
+
 # nearly as many experts selected as there are, in every form that gives a workgroup one or four tokens
 @pytest.mark.parametrize("T,H,k", [(5, 128, 961), (5, 128, 1024), (5, 2304, 1024), (5, 4104, 1024), (5, 8200, 1024), (257, 200, 1000),
                                    (1025, 128, 1024)])
