@@ -313,10 +313,11 @@ __device__ __forceinline__ float dot_row_b(const RowRegs<16, NSEG>& rr, const La
 
 template <int BITS> struct Phase1Rows { static constexpr int RF = (BITS == 16) ? 1 : (BITS == 2 ? 4 : 2); };
 
-template <int BITS, int NSEG, typename XT, typename DotFn>
+// arrange() makes the activations of what was requested before: the first rows are on their way when it waits for them.
+template <int BITS, int NSEG, typename ArrangeFn, typename DotFn>
 __device__ __forceinline__ void phase1_rows(const ExpertMat& m1, const ExpertMat& m3, int H,
                                             int f_begin, int f_end, float* __restrict__ hrow,
-                                            const XT& lx, DotFn dot)
+                                            ArrangeFn arrange, DotFn dot)
 {
     constexpr int RF = Phase1Rows<BITS>::RF;
     const int lane = threadIdx.x & (kWave - 1);
@@ -335,6 +336,9 @@ __device__ __forceinline__ void phase1_rows(const ExpertMat& m1, const ExpertMat
             load_row<BITS, NSEG>(m3, fi, H, 0, lane, dst[2 * i + 1]);
         }
     };
+    fetch(ra, f);
+    __builtin_amdgcn_sched_barrier(0);
+    const auto lx = arrange();
     auto finish = [&](const RowRegs<BITS, NSEG>(&src)[2 * RF], int f0) {
         float a[RF], g[RF];
 #pragma unroll
@@ -354,7 +358,6 @@ __device__ __forceinline__ void phase1_rows(const ExpertMat& m1, const ExpertMat
             if (lane == i) hv = a[i] / (1.0f + __expf(-a[i])) * g[i];
         if (lane < RF && f0 + lane < f_end) hrow[f0 + lane] = hv;
     };
-    fetch(ra, f);
     if constexpr (BITS >= 8) {
         for (; f < f_end; f += 2 * kStep) {
             fetch(rb, f + kStep);                    // next batch first
@@ -381,28 +384,40 @@ __device__ __forceinline__ void phase1_quant(const ExpertMat& m1, const ExpertMa
                                              int f_end, float* __restrict__ hrow, Missing missing)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    LaneX lx[NSEG];
+    // (columns past the end are read as the row's first and made zero when they are used)
+    uint4 raw[NSEG][4];
 #pragma unroll
     for (int s = 0; s < NSEG; s++) {
-        float v[32];
         const int col0 = s * kSeg + 32 * lane;
+        const uint16_t* from = xrow + (col0 < H ? col0 : 0);
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
-            uint4 raw = make_uint4(0, 0, 0, 0);
-            if (col0 < H) raw = *reinterpret_cast<const uint4*>(xrow + col0 + 8 * c);
-            v[8 * c + 0] = bf16_lo(raw.x); v[8 * c + 1] = bf16_hi(raw.x);
-            v[8 * c + 2] = bf16_lo(raw.y); v[8 * c + 3] = bf16_hi(raw.y);
-            v[8 * c + 4] = bf16_lo(raw.z); v[8 * c + 5] = bf16_hi(raw.z);
-            v[8 * c + 6] = bf16_lo(raw.w); v[8 * c + 7] = bf16_hi(raw.w);
-        }
-        arrange_lane_x<BITS>(v, lx[s]);
+        for (int c = 0; c < 4; c++) raw[s][c] = *reinterpret_cast<const uint4*>(from + 8 * c);
     }
     // (tested here and not before the loads above: the table's pointers and the activations then arrive together)
     if (!mat_present(m1, BITS) || !mat_present(m3, BITS)) return missing();
-    phase1_rows<BITS, NSEG>(m1, m3, H, f_begin, f_end, hrow, lx,
-                            [](const RowRegs<BITS, NSEG>& rr, const LaneX (&l)[NSEG]) {
-                                return dot_row_q<BITS, NSEG>(rr, l);
-                            });
+    struct Lanes {
+        LaneX l[NSEG];
+    };
+    phase1_rows<BITS, NSEG>(m1, m3, H, f_begin, f_end, hrow, [&] {
+        Lanes o;
+#pragma unroll
+        for (int s = 0; s < NSEG; s++) {
+            const bool in = s * kSeg + 32 * lane < H;
+            float v[32];
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const uint32_t u[4] = {raw[s][c].x, raw[s][c].y, raw[s][c].z, raw[s][c].w};
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const uint32_t q = in ? u[i] : 0;
+                    v[8 * c + 2 * i] = bf16_lo(q);
+                    v[8 * c + 2 * i + 1] = bf16_hi(q);
+                }
+            }
+            arrange_lane_x<BITS>(v, o.l[s]);
+        }
+        return o;
+    }, [](const RowRegs<BITS, NSEG>& rr, const Lanes& o) { return dot_row_q<BITS, NSEG>(rr, o.l); });
 }
 
 template <int NSEG, typename Missing>
@@ -411,30 +426,33 @@ __device__ __forceinline__ void phase1_bf16(const ExpertMat& m1, const ExpertMat
                                             int f_end, float* __restrict__ hrow, Missing missing)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    LaneXB<NSEG> lx;
+    LaneXB<NSEG> raw;
 #pragma unroll
     for (int s = 0; s < NSEG; s++)
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             const int col = s * kSeg + (j * kWave + lane) * 8;
-            lx.r[s][j] = make_uint4(0, 0, 0, 0);
-            if (col < H) lx.r[s][j] = *reinterpret_cast<const uint4*>(xrow + col);
+            raw.r[s][j] = *reinterpret_cast<const uint4*>(xrow + (col < H ? col : 0));
         }
     if (!mat_present(m1, 16) || !mat_present(m3, 16)) return missing();
-    phase1_rows<16, NSEG>(m1, m3, H, f_begin, f_end, hrow, lx,
-                          [](const RowRegs<16, NSEG>& rr, const LaneXB<NSEG>& l) {
-                              return dot_row_b<NSEG>(rr, l);
-                          });
+    phase1_rows<16, NSEG>(m1, m3, H, f_begin, f_end, hrow, [&] {
+#pragma unroll
+        for (int s = 0; s < NSEG; s++)
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (s * kSeg + (j * kWave + lane) * 8 >= H) raw.r[s][j] = make_uint4(0, 0, 0, 0);
+        return raw;
+    }, [](const RowRegs<16, NSEG>& rr, const LaneXB<NSEG>& l) { return dot_row_b<NSEG>(rr, l); });
 }
 
-// One (token, expert) pair p: rows [f_begin, f_end) of W1 and W3 of expert e at b bits.
+// One (token, expert) pair p: workgroup bx's rows of W1 and W3 of expert e at b bits
 template <int NSEG>
-__device__ __forceinline__ void phase1_pair(const uint16_t* __restrict__ x, const dymoe_expert_fmt* __restrict__ table,
+__device__ __forceinline__ void phase1_pair(const uint16_t* __restrict__ x, const dymoe_expert_fmt* __restrict__ table, int bx,
                                             int p, int e, int b, float gate, int H, int F, int k, int rows_per_block,
                                             float* __restrict__ hbuf, PairDown* __restrict__ down, unsigned* __restrict__ flags)
 {
     const int t = p / k;
-    const int f_begin = blockIdx.x * rows_per_block;
+    const int f_begin = bx * rows_per_block;
     const int f_end = min(F, f_begin + rows_per_block);
     const uint16_t* xrow = x + (long)t * H;
     float* hrow = hbuf + (long)p * F;
@@ -443,19 +461,19 @@ __device__ __forceinline__ void phase1_pair(const uint16_t* __restrict__ x, cons
     // intermediate are set to zero, so that the second phase adds nothing for it even where it finds the down projection.
     auto missing = [&]() {
         for (int f = f_begin + (int)threadIdx.x; f < f_end; f += kGvThreads) hrow[f] = 0.0f;
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(flags, DYMOE_FLAG_FORMAT_MISSING);
+        if (bx == 0 && threadIdx.x == 0) atomicOr(flags, DYMOE_FLAG_FORMAT_MISSING);
     };
     if (b == 16) {
-        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 16), p, 16, gate, flags);
+        if (bx == 0) leave_pair_down(down, pick_mat(ex, 2, 16), p, 16, gate, flags);
         phase1_bf16<NSEG>(pick_mat(ex, 0, 16), pick_mat(ex, 1, 16), xrow, H, f_begin, f_end, hrow, missing);
     } else if (b == 8) {
-        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 8), p, 8, gate, flags);
+        if (bx == 0) leave_pair_down(down, pick_mat(ex, 2, 8), p, 8, gate, flags);
         phase1_quant<8, NSEG>(pick_mat(ex, 0, 8), pick_mat(ex, 1, 8), xrow, H, f_begin, f_end, hrow, missing);
     } else if (b == 4) {
-        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 4), p, 4, gate, flags);
+        if (bx == 0) leave_pair_down(down, pick_mat(ex, 2, 4), p, 4, gate, flags);
         phase1_quant<4, NSEG>(pick_mat(ex, 0, 4), pick_mat(ex, 1, 4), xrow, H, f_begin, f_end, hrow, missing);
     } else {
-        if (blockIdx.x == 0) leave_pair_down(down, pick_mat(ex, 2, 2), p, 2, gate, flags);
+        if (bx == 0) leave_pair_down(down, pick_mat(ex, 2, 2), p, 2, gate, flags);
         phase1_quant<2, NSEG>(pick_mat(ex, 0, 2), pick_mat(ex, 1, 2), xrow, H, f_begin, f_end, hrow, missing);
     }
 }
@@ -475,7 +493,7 @@ __global__ __launch_bounds__(kGvThreads) void gemv_phase1_kernel(
         if (blockIdx.x == 0 && threadIdx.x == 0) down[p].bits = 0;
         return;
     }
-    phase1_pair<NSEG>(x, table, p, e, b, w[p], H, F, k, rows_per_block, hbuf, down, flags);
+    phase1_pair<NSEG>(x, table, (int)blockIdx.x, p, e, b, w[p], H, F, k, rows_per_block, hbuf, down, flags);
 }
 
 // The first phase with the decode step's front end in front of it (router gating and top-k, decode importance,
@@ -564,8 +582,8 @@ __device__ __forceinline__ void route_logits_of_row(const uint16_t* s_row, const
 
 template <int NSEG, int NCH, int NC, int FRONT>
 __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
-    const FusedFront f, const dymoe_expert_fmt* __restrict__ table, int T, int H, int F, int E, int k, int rows_per_block,
-    float* __restrict__ hbuf, PairDown* __restrict__ down, unsigned* __restrict__ flags)
+    const FusedFront f, const dymoe_expert_fmt* __restrict__ table, int T, int H, int F, int E, int k, int front_apart,
+    int rows_per_block, float* __restrict__ hbuf, PairDown* __restrict__ down, unsigned* __restrict__ flags)
 {
     __shared__ float s_logit[64 * NC];
     __shared__ float s_selp[kFusedMaxK];
@@ -580,6 +598,13 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t s_row[FRONT == kFrontResidual ? NSEG * kSeg : 8];
     const int wave = threadIdx.x / kWave;
     const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+    // front_apart: a workgroup of its own, the first, writes the front end's outputs, and the rest are the pairs' one after the other
+    int bx = (int)blockIdx.x, pair = (int)blockIdx.y;
+    if (NC > 1 && front_apart) {
+        const int blocks = (F + rows_per_block - 1) / rows_per_block;
+        pair = (bx - 1) / blocks;
+        bx = bx == 0 ? -1 : bx - 1 - pair * blocks;
+    }
     __builtin_assume(k >= 1 && k <= kFusedMaxK);
     for (int e = threadIdx.x; e < E; e += kGvThreads) {
         s_imp[e] = 0.0f;
@@ -623,7 +648,7 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
         s_imp[e] = (T <= 1) ? g : g / (float)T;
     }
     __syncthreads();
-    const int p = (int)gridDim.y - 1 - (int)blockIdx.y;
+    const int p = T * k - 1 - pair;
     const int e = s_idx[p];
     int b = 0;
     if (first) {
@@ -641,6 +666,7 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
             f.bits[i] = s_bits[i];
             if (f.rank) f.rank[i] = s_rank[i];
         }
+        if (bx < 0) return;
         b = s_bits[max(e, 0)];
     } else if (e >= 0) {
         // the others need the bit width of one expert: its position is the number of lanes whose experts precede it
@@ -657,10 +683,10 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
         b = tier_bits_at(pos, f.tiers, f.floor_bits);
     }
     if (e < 0 || (b != 16 && b != 8 && b != 4 && b != 2)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) down[p].bits = 0;
+        if (bx == 0 && threadIdx.x == 0) down[p].bits = 0;
         return;
     }
-    phase1_pair<NSEG>(FRONT == kFrontResidual ? s_row : f.x, table, p, e, b, s_w[p], H, F, k, rows_per_block, hbuf, down, flags);
+    phase1_pair<NSEG>(FRONT == kFrontResidual ? s_row : f.x, table, bx, p, e, b, s_w[p], H, F, k, rows_per_block, hbuf, down, flags);
 }
 
 // ---------------------------------------------------------------- phase 2
@@ -1056,8 +1082,18 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
     f.x = (const uint16_t*)x; f.y_prev = y_prev; f.alpha = alpha; f.h_out = (uint16_t*)h_out;
     f.wg = (const uint16_t*)wg; f.bias = bias; f.renorm = renorm; f.floor_bits = floor_bits; f.tiers = tt;
     f.idx = idx; f.w = w; f.probs = probs; f.importance = importance; f.load = load; f.bits = bits; f.rank = rank;
+    // From 65 experts on the front end's outputs are a workgroup's work: ranking them and writing everything down is 5 us on top of
+    // what each does for itself, and the workgroup that went on to rows after it was the last to end.  With a workgroup of its own,
+    // where that is resident beside the others (one token, us a step, without / with: eight of 128 experts, 2048 x 768, int4 20.6 /
+    // 18.1, bf16 24.1 / 23.6; four tokens, 1024 x 768, 36.2 / 35.1); up to 64 experts it is 0.6 us and not the last.
+    // Resident together: four, two or one per compute unit by the registers of 1, 2 or more segments.
+    const long resident = (nseg1 == 1 ? 4L : nseg1 == 2 ? 2L : 1L) * ctx->num_cu;
+    const long workgroups = (long)g1.x * g1.y;
+    const bool front_apart = E > 64 && workgroups + 1 <= resident;
+    const dim3 grid = front_apart ? dim3((unsigned)workgroups + 1) : g1;
     auto go = [&](auto kernel) {
-        dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, kernel, g1, dim3(kGvThreads), 0, st, f, table, T, H, F, E, k, rows1, hbuf,
+        dymoe_launch(ctx, DYMOE_K_GEMV_PHASE1, kernel, grid, dim3(kGvThreads), 0, st, f, table, T, H, F, E, k,
+                     (int)front_apart, rows1, hbuf,
                      down, ctx->device_flags);
     };
     // NCH: 16-byte chunks of an activation row per lane, as in dymoe_decode_front (8 up to 4096 columns, then 16)
@@ -1072,12 +1108,11 @@ int decode_fused_launch(dymoe_ctx* ctx, const void* x, const float* y_prev, floa
     };
     if (nseg1 > 4) return DYMOE_ENOTSUP;
     if (fused_logits_apart(ctx, T, H, F, E, k)) {
-        // More workgroups than are resident together (four, two or one per compute unit by the registers of 1, 2 or more segments)
-        // would do softmax, top-k and ranking once per round: then a launch does them, and the first phase is the stand-alone one.
+        // More workgroups than are resident together would do softmax, top-k and ranking once per round: then a launch does them, and the first phase is the stand-alone one.
         // us a step, in every round / once: 4 tokens x 8 of 100 experts, 7360 x 192 (768 workgroups) 121 / 112, 4 x 8 of 8, 4096 x
         // 4096 (2048) 236 / 208, 2 x 8 of 65, 6016 x 192 (384) 4.8 more; up to one round 2 to 4 less (4 x 8 of 128, 4096 x 192 (384)
         // 3.3, 2048 x 768 (768) 3.6).
-        const bool once = (long)g1.x * g1.y > (nseg1 == 1 ? 4L : nseg1 == 2 ? 2L : 1L) * ctx->num_cu;
+        const bool once = workgroups > resident;
         float* logits = (once && probs) ? probs : reinterpret_cast<float*>((char*)workspace + L.part);
         int rc = front_logits_launch(ctx, x, y_prev, alpha, h_out, wg, bias, T, H, E, logits, st);
         if (rc != DYMOE_OK) return rc;

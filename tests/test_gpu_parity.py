@@ -1356,7 +1356,9 @@ def test_decode_layer_equals_the_separate_calls(ctx, T, H, E, k, floor, chained)
     (4, 512, 2304, 65, 8, False, True), (4, 512, 2304, 64, 8, False, False), (4, 2112, 192, 60, 8, False, True),
     (4, 2112, 128, 60, 8, False, True), (2, 4160, 192, 65, 8, False, False), (2, 4160, 128, 65, 8, False, True),
     (1, 4160, 1024, 16, 8, True, True), (1, 4160, 1024, 100, 8, True, False), (1, 2112, 1088, 66, 8, True, True),
-    (2, 256, 128, 8, 1, False, True), (3, 256, 128, 8, 1, False, True), (1, 256, 128, 17, 2, True, True), (3, 3072, 64, 8, 2, False, False)])
+    (2, 256, 128, 8, 1, False, True), (3, 256, 128, 8, 1, False, True), (1, 256, 128, 17, 2, True, True), (3, 3072, 64, 8, 2, False, False),
+    # from 65 experts on: with and without room for a workgroup of the front end's own beside the others, one ragged
+    (3, 4160, 128, 65, 5, False, True), (1, 2112, 1088, 128, 7, True, False), (1, 512, 64, 128, 1, False, True)])
 def test_decode_layer_by_workgroups(ctx, T, H, F, E, k, chained, probs):
     _decode_layer_against_the_separate_calls(ctx, T, H, F, E, k, 0, chained, probs)
 
