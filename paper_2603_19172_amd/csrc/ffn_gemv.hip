@@ -531,11 +531,11 @@ struct FusedFront {
     int32_t* rank;
 };
 
-// Logits of one token from its row in LDS, which is made between the request for the first router rows and their use
-// (route_logits' arithmetic for TW = 1).
-template <int NCH, typename MakeRow>
+// Logits of one token from its row in LDS (route_logits' arithmetic for TW = 1).  request() asks for what the row is made of, ahead
+// of the first router rows, which come back behind it; make_row() makes the row while they are on their way.
+template <int NCH, typename Request, typename MakeRow>
 __device__ __forceinline__ void route_logits_of_row(const uint16_t* s_row, const uint16_t* __restrict__ wg, const float* __restrict__ bias,
-                                                    int H, int E, float* logit, MakeRow make_row)
+                                                    int H, int E, float* logit, Request request, MakeRow make_row)
 {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     constexpr int EB = (NCH <= 8) ? 2 : 1;
@@ -551,7 +551,10 @@ __device__ __forceinline__ void route_logits_of_row(const uint16_t* s_row, const
             }
         }
     };
+    request();
+    __builtin_amdgcn_sched_barrier(0);
     fetch(wave);
+    __builtin_amdgcn_sched_barrier(0);
     make_row();
 #pragma unroll
     for (int c = 0; c < NCH; c++) {
@@ -612,15 +615,26 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
     }
     for (int t = 0; t < T; t++) {
         if constexpr (FRONT == kFrontResidual) {
+            // (columns past the end are read as the row's first and made zero: a load under a condition is waited for on the spot)
+            uint4 h_raw[NSEG];
+            float4 y_raw[NSEG][2];
             route_logits_of_row<NCH>(s_row, f.wg, f.bias, H, E, s_logit, [&] {
+#pragma unroll
+                for (int i = 0; i < NSEG; i++) {
+                    const int j = (i * kNormThreads + (int)threadIdx.x) * 8, from = j < H ? j : 0;
+                    h_raw[i] = load_global<uint4>(f.x + from);
+                    y_raw[i][0] = load_global<float4>(f.y_prev + from);
+                    y_raw[i][1] = load_global<float4>(f.y_prev + from + 4);
+                }
+            }, [&] {
                 float v[NSEG][8], ss = 0.0f;
 #pragma unroll
                 for (int i = 0; i < NSEG; i++) {
-                    const int j = (i * kNormThreads + (int)threadIdx.x) * 8;
-                    if (j < H) {
-                        residual_value<float, true>(f.x, f.y_prev, f.alpha, j, v[i]);
-                        residual_square<true>(v[i], ss);
-                    }
+                    residual_add(h_raw[i], y_raw[i][0], y_raw[i][1], f.alpha, v[i]);
+                    const bool in = (i * kNormThreads + (int)threadIdx.x) * 8 < H;
+#pragma unroll
+                    for (int n = 0; n < 8; n++) v[i][n] = in ? v[i][n] : 0.0f;
+                    residual_square<true>(v[i], ss);
                 }
                 const float inv = residual_inv_rms(ss, H, s_part);
 #pragma unroll

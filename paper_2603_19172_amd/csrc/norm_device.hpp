@@ -12,26 +12,27 @@ namespace dymoe {
 // summed per thread, per wavefront, then over the wavefronts in order.  s_part: 4 floats of LDS.
 constexpr int kNormThreads = 256;
 
+__device__ __forceinline__ void residual_add(const uint4& h, const float4& y0, const float4& y1, float alpha, float (&v)[8])
+{
+    const float hv[8] = {bf16_lo(h.x), bf16_hi(h.x), bf16_lo(h.y), bf16_hi(h.y), bf16_lo(h.z), bf16_hi(h.z), bf16_lo(h.w), bf16_hi(h.w)};
+    const float yv[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = fmaf(alpha, yv[i], hv[i]);
+}
+
 template <typename YT, bool VEC>
 __device__ __forceinline__ void residual_value(const uint16_t* __restrict__ hr, const YT* __restrict__ yr, float alpha, int j,
                                                float (&v)[VEC ? 8 : 1])
 {
     if constexpr (VEC) {
-        float hv[8], yv[8];
-        const uint4 hraw = *reinterpret_cast<const uint4*>(hr + j);
-        hv[0] = bf16_lo(hraw.x); hv[1] = bf16_hi(hraw.x); hv[2] = bf16_lo(hraw.y); hv[3] = bf16_hi(hraw.y);
-        hv[4] = bf16_lo(hraw.z); hv[5] = bf16_hi(hraw.z); hv[6] = bf16_lo(hraw.w); hv[7] = bf16_hi(hraw.w);
+        const uint4 h = *reinterpret_cast<const uint4*>(hr + j);
         if constexpr (sizeof(YT) == 2) {
-            const uint4 yraw = *reinterpret_cast<const uint4*>(yr + j);
-            yv[0] = bf16_lo(yraw.x); yv[1] = bf16_hi(yraw.x); yv[2] = bf16_lo(yraw.y); yv[3] = bf16_hi(yraw.y);
-            yv[4] = bf16_lo(yraw.z); yv[5] = bf16_hi(yraw.z); yv[6] = bf16_lo(yraw.w); yv[7] = bf16_hi(yraw.w);
+            const uint4 y = *reinterpret_cast<const uint4*>(yr + j);
+            residual_add(h, make_float4(bf16_lo(y.x), bf16_hi(y.x), bf16_lo(y.y), bf16_hi(y.y)),
+                         make_float4(bf16_lo(y.z), bf16_hi(y.z), bf16_lo(y.w), bf16_hi(y.w)), alpha, v);
         } else {
-            const float4 a = *reinterpret_cast<const float4*>(yr + j);
-            const float4 b = *reinterpret_cast<const float4*>(yr + j + 4);
-            yv[0] = a.x; yv[1] = a.y; yv[2] = a.z; yv[3] = a.w; yv[4] = b.x; yv[5] = b.y; yv[6] = b.z; yv[7] = b.w;
+            residual_add(h, *reinterpret_cast<const float4*>(yr + j), *reinterpret_cast<const float4*>(yr + j + 4), alpha, v);
         }
-#pragma unroll
-        for (int i = 0; i < 8; i++) v[i] = fmaf(alpha, yv[i], hv[i]);
     } else {
         float yv;
         if constexpr (sizeof(YT) == 2) yv = bf16_bits_to_f32(yr[j]);
