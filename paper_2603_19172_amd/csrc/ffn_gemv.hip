@@ -500,7 +500,7 @@ __global__ __launch_bounds__(kGvThreads) void gemv_phase1_kernel(
 // bit-width assignment: the arithmetic of dymoe_decode_front, same device functions, same order of every sum, so the
 // same bits).  Every workgroup works the front end out for itself, in LDS, and goes on to its rows without a launch
 // boundary and without the chain of dependent loads (pair -> expert -> bit width) the stand-alone kernel starts with;
-// workgroup (0, 0) also writes the front end's outputs to memory for the second phase and for the caller.  FRONT says
+// the first workgroup also writes the front end's outputs to memory, for the caller.  FRONT says
 // where the logits come from:
 //   kFrontRouter    the router's rows, read by every workgroup (64 KiB for 8 experts of 4096: from L2 by all but the first)
 //   kFrontResidual  the same, of the row that residual and normalisation make of the layer before (one token): every

@@ -28,8 +28,8 @@ static inline int ffn_most_tiles(int T, int E, int k)
 
 struct FfnLayout {
     size_t hbuf;    // [P,F] SwiGLU intermediate: fp32 (GEMV) or 16-bit (GEMM; the splits' output slabs start right behind it)
-    size_t part;    // room for [P,H] fp32 per-pair outputs, one slab per split (the GEMV path keeps its partial sums on chip)
-    size_t xh;      // GEMM: three [T,H] fp16 copies of the activations (int4 / int2 / natural column order)
+    size_t part;    // room for [P,H] fp32 per-pair outputs, one slab per split (GEMV: the pairs' entries, or the fused front end's logits)
+    size_t xh;      // GEMM: three [T,H] fp16 copies of the activations (int4 / int2 / natural column order); fused GEMV: the pairs' entries
     size_t plan;    // int32: counts[E], offsets[E+1], cursor[E], ntiles, perm[P], tiles[4*maxtiles], draft[4*maxtiles]
     size_t total;
     int max_tiles;
