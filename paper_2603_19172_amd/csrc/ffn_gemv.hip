@@ -605,8 +605,9 @@ __global__ __launch_bounds__(kGvThreads) void decode_fused_phase1_kernel(
     int bx = (int)blockIdx.x, pair = (int)blockIdx.y;
     if (NC > 1 && front_apart) {
         const int blocks = (F + rows_per_block - 1) / rows_per_block;
-        pair = (bx - 1) / blocks;
-        bx = bx == 0 ? -1 : bx - 1 - pair * blocks;
+        bx--;
+        pair = max(bx, 0) / blocks;
+        bx -= pair * blocks;                                        // (-1: the front end's)
     }
     __builtin_assume(k >= 1 && k <= kFusedMaxK);
     for (int e = threadIdx.x; e < E; e += kGvThreads) {
