@@ -328,11 +328,12 @@ __device__ __forceinline__ float token_norm(const uint16_t* __restrict__ row, in
 // (wait_lds_copies) before the workgroup barrier that publishes the data.
 __device__ __forceinline__ void lds_copy16(const char* base, uint32_t lane_offset, uint32_t lds_addr_lane0)
 {
-    // base is the same for the whole wavefront (scalar registers), lane_offset an unsigned 32-bit byte offset
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    // base is the same for the whole wavefront (scalar registers), lane_offset an unsigned 32-bit byte offset.  A load to LDS needs a
+    // wait state behind the scalar write of M0 that it takes its LDS address from; the compiler puts none inside an assembly block.
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds_addr_lane0), "v"(lane_offset), "s"(base)
-                 : "memory");
+                 : "memory", "m0");
 }
 
 template <int N>

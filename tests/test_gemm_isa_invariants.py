@@ -8,6 +8,7 @@ that the body is one straight-line block, that the memory instructions on the
 path from the last copy to the wait (within one trip, or over the back edge when
 the copies follow the wait) are exactly N, and that a wait for everything
 precedes the loop (the copies issued before the loop are waited for there)."""
+import functools
 import os
 import re
 import shutil
@@ -19,18 +20,19 @@ import pytest
 from paper_2603_19172_amd import build as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "paper_2603_19172_amd", "csrc", "ffn_gemm.hip")
 
 VMEM = re.compile(r"^\s*(global_|buffer_|flat_|scratch_)(load|store|atomic)")
 
 
-def _assembly():
+@functools.lru_cache(maxsize=None)
+def _assembly(name="ffn_gemm.hip"):
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not found")
     with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "ffn_gemm.s")
+        out = os.path.join(tmp, "kernels.s")
         # the flags the library is built with
-        cmd = ["hipcc", *B.COMMON, *B.PER_FILE.get("ffn_gemm.hip", []), "-S", "--cuda-device-only", SRC, "-o", out]
+        cmd = ["hipcc", *B.COMMON, *B.PER_FILE.get(name, []), "-S", "--cuda-device-only",
+               os.path.join(ROOT, "paper_2603_19172_amd", "csrc", name), "-o", out]
         subprocess.run(cmd, check=True, capture_output=True)
         with open(out) as f:
             return f.read().split("\n")
@@ -129,3 +131,14 @@ def test_counted_waits_cover_the_tile_copies():
             k += 1
         assert waited, "copy at line %d reaches a barrier without a wait for everything" % c[0]
     assert checked >= 32         # 4 precisions x 4 fragment counts x 2 projections
+
+
+@pytest.mark.parametrize("name", ["ffn_gemm.hip", "attention.hip", "gptq.hip"])
+def test_a_wait_state_between_m0_and_the_load_that_reads_it(name):
+    """A load to LDS takes its LDS address from M0 and may not be the very next instruction after a scalar write of M0."""
+    code = [l.split(";")[0].strip() for l in _assembly(name)]
+    code = [l for l in code if l and not l.startswith(".") and not l.endswith(":")]
+    loads = [i for i, l in enumerate(code) if re.match(r"(global|buffer|scratch)_load_(lds_|\S+ .*\blds\b)", l)]
+    assert loads
+    for i in loads:
+        assert not re.match(r"s_\w+ m0\b", code[i - 1]), "%s directly behind %s" % (code[i], code[i - 1])
