@@ -330,10 +330,11 @@ __device__ __forceinline__ void lds_copy16(const char* base, uint32_t lane_offse
 {
     // base is the same for the whole wavefront (scalar registers), lane_offset an unsigned 32-bit byte offset.  A load to LDS needs a
     // wait state behind the scalar write of M0 that it takes its LDS address from; the compiler puts none inside an assembly block.
+    // (M0 is a reserved register, which a clobber list cannot name: the kernels that copy have no other use for it.)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds_addr_lane0), "v"(lane_offset), "s"(base)
-                 : "memory", "m0");
+                 : "memory");
 }
 
 template <int N>

@@ -142,3 +142,5 @@ def test_a_wait_state_between_m0_and_the_load_that_reads_it(name):
     assert loads
     for i in loads:
         assert not re.match(r"s_\w+ m0\b", code[i - 1]), "%s directly behind %s" % (code[i], code[i - 1])
+    # the assembly block cannot tell the compiler that it writes M0: nothing else may count on it
+    assert sum(bool(re.search(r"\bm0\b", l)) for l in code) == len(loads)
