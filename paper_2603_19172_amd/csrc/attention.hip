@@ -15,12 +15,12 @@
 // running per-key sums both stay inside a lane until the very end.
 #include <type_traits>
 
+#include "attention_rule.hpp"
 #include "common.hpp"
 
 namespace dymoe {
 
-constexpr int kAtThreads = 256;
-constexpr int kAtWaves = kAtThreads / kWave;
+constexpr int kAtThreads = kAtWaves * kWave;
 
 // One lane's share of a 32-token fragment of one head (D columns): lane (ln, kb)
 // holds row ln; piece c covers columns 32 (c / 2) + 16 kb + 8 (c % 2) .. + 7, i.e.
@@ -700,46 +700,6 @@ __global__ __launch_bounds__(kAtScoreThreads) void attn_score_kernel(const float
     score[i] = s * inv;
 }
 
-// Which pair of kernels.  Few fragments over all heads: a workgroup per 32-token fragment, its wavefronts sharing the streamed
-// tokens (many workgroups, operands straight from global memory).  Else blocks of 128 or 256 tokens with the stream in LDS.
-// Whole score, us, narrow / wide (128-token blocks) by tokens x heads (fragments):
-//                      d = 128, causal  unmasked                        d = 64, causal    unmasked
-//    1400 x  4 (176)        - / -      35.6 / 39.2    3000 x  4 (376)   47.8 / 49.1   55.9 / 58.9
-//    2048 x  4 (256)      47.9 / 43.4  50.9 / 41.4    4096 x  4 (512)   69.2 / 60.8   74.3 / 60.2
-//    1000 x  8 (256)      27.7 / 29.4  28.9 / 31.1    2048 x  8 (512)   33.6 / 37.7   41.7 / 35.7
-//     512 x 16 (256)      18.3 / 21.1  18.9 / 18.8    1000 x 16 (512)   24.5 / 25.7   25.7 / 27.9
-//     300 x 32 (320)      19.4 / 20.2  20.6 / 20.6     512 x 32 (512)   17.7 / 19.4   17.8 / 17.0
-//    1400 x  8 (352)      40.9 / 35.5  52.8 / 39.7    1400 x 16 (704)   31.6 / 30.6   43.7 / 35.5
-//     512 x 32 (512)      26.5 / 21.4  27.0 / 19.0     700 x 32 (704)   23.0 / 23.1   27.5 / 24.4
-//    1000 x 32 (1024)     70.8 / 30.8  73.5 / 33.2    1000 x 32 (1024)  41.3 / 26.7   42.9 / 29.0
-// so the line lies at 320 fragments (d = 128) or 640 (d = 64, where a wavefront's share of the products is half as long), and at
-// 224 or 448 where the sequence is long: the narrow pair's chain goes over a quarter of it at a memory latency per fragment.
-static bool attn_wide(int nfrag, int n_heads, int d)
-{
-    const long all = (long)nfrag * n_heads;
-    if (nfrag < 9) return false;        // 64 tokens x 192 heads 14.7 / 19.6, 200 x 64 16.4 / 18.4, 300 x 64 27.6 / 21.7 (d = 128)
-    return d == 128 ? all > 320 || (all > 224 && nfrag >= 48) : all > 640 || (all > 448 && nfrag >= 96);
-}
-
-// Tokens per block of the wide pair, in units of 64: 4 with two wavefronts sharing a stream, or 2 with four.  A block takes a
-// start of about 5 fragments' time and then its stream, split over the sharing wavefronts; blocks of 128 tokens are twice as many
-// and read the stream twice as often (6 % per fragment, measured), but their chain is half as long.  Unmasked, all blocks are alike and
-// go over the chip in rounds; causal blocks come longest first and fill it evenly, unless the longest alone takes longer.
-// Whole score, d = 128, us, 128 / 256 tokens: 2048 x 16 causal 44.9 / 70.7, 4096 x 16 94.6 / 129, 6000 x 16 198 / 188, 2048 x 32 59.9 / 73.4,
-// 3000 x 32 118 / 105, 4096 x 32 186 / 156; unmasked 2048 x 16 45.5 / 67.7, 4096 x 16 157 / 140, 6000 x 16 341 / 405, 2048 x 32 87.3 / 76.8,
-// 3000 x 32 190 / 215, 4096 x 32 314 / 274.
-static int attn_owners(int nfrag, int n_heads, int causal, int num_cu)
-{
-    auto cost = [&](int owners, double each) {
-        const double blocks = (double)((nfrag + 2 * owners - 1) / (2 * owners)) * n_heads;
-        const int streams = 8 / owners;
-        const double longest = each * ((nfrag + streams - 1) / streams);
-        if (!causal) return ceil(blocks / num_cu) * (5.0 + longest);
-        return fmax(5.0 + longest, 1.1 * blocks * (5.0 + 0.5 * longest) / num_cu);
-    };
-    return cost(2, 1.06) < cost(4, 1.0) ? 2 : 4;
-}
-
 static size_t attn_stats_bytes(int T, int n_heads) { return ((size_t)T * n_heads * sizeof(float2) + 255) / 256 * 256; }
 
 }  // namespace dymoe
@@ -776,11 +736,11 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     const float s = (scale > 0.0f) ? scale : 1.0f / sqrtf((float)head_dim);
     const float scale_log2 = s * 1.44269504088896340736f;
     const int nfrag = (T + 31) / 32;
-    const bool wide = dymoe::attn_wide(nfrag, n_heads, head_dim);
-    const int owners = dymoe::attn_owners(nfrag, n_heads, causal, ctx->num_cu);
+    const int owners = dymoe::attn_owners(nfrag, n_heads, causal, head_dim, ctx->num_cu);
+    const bool wide = owners != 0;
     // A dimension of a launch holds fewer than 2^32 threads: beyond that (from 275 GB of queries on) a head per y, as in the
     // narrow pair's launches.
-    const int nblk = (nfrag + 2 * owners - 1) / (2 * owners);
+    const int nblk = wide ? (nfrag + 2 * owners - 1) / (2 * owners) : 0;
     const long blocks = (long)nblk * n_heads;
     const int threads = wide ? dymoe::kAtWideThreads : dymoe::kAtThreads;
     const dim3 grid = !wide ? dim3((unsigned)nfrag, (unsigned)n_heads)
@@ -805,6 +765,7 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     if (head_dim == 64) DYMOE_ATTN_LAUNCH(64);
     else DYMOE_ATTN_LAUNCH(128);
 #undef DYMOE_ATTN_LAUNCH
+#undef DYMOE_ATTN_WIDE
 #undef DYMOE_ATTN_PAIR
     DYMOE_HIP_LAUNCH_CHECK();
     hipLaunchKernelGGL(dymoe::attn_score_kernel, dim3((unsigned)((T + dymoe::kAtScoreThreads - 1) / dymoe::kAtScoreThreads)),
