@@ -206,9 +206,9 @@ __global__ __launch_bounds__(kAtThreads) void attn_colsum_kernel(
 }
 
 // ----------------------------------------------------------------------------
-// Long sequences: the streamed operand goes through LDS.  A workgroup of eight wavefronts owns OWNERS x 64 tokens: each
+// Long sequences: the streamed operand goes through LDS.  A workgroup of eight wavefronts (or four) owns OWNERS x 64 tokens: each
 // wavefront keeps two 32-token fragments in registers, so that what it reads from LDS feeds two products (with one fragment
-// the reads alone took the 128 bytes a cycle that LDS has), and the 8 / OWNERS wavefronts that own the same tokens share
+// the reads alone took the 128 bytes a cycle that LDS has), and the WAVES / OWNERS wavefronts that own the same tokens share
 // the stream, two of a trip's fragments each; their statistics or sums meet in LDS at the end.
 // 16-byte chunk c of row r lies at chunk position c ^ (r mod chunks-per-row), so that the operand reads of 16 consecutive
 // rows fall on different banks.  The rows go from memory to LDS directly: through registers, the addresses and the stores took a
@@ -218,19 +218,20 @@ __global__ __launch_bounds__(kAtThreads) void attn_colsum_kernel(
 // 32 x 32, these kernels 230; the order of the instructions moves that by 2 %).  The whole score, 32 / 8 heads, d = 128, with one
 // fragment per wavefront, four wavefronts in a block of 128 tokens and every fragment's maximum -> so: 4096 tokens causal 194 -> 160 us,
 // unmasked 340 -> 276, 1024 causal 41 -> 28; 4096 x 6 heads 135 -> 77.
-constexpr int kAtWideThreads = 512;
-
-template <int D, int OWNERS>
+// At d = 64 the products are half of that and the vector work is the bound, whose latencies two wavefronts a SIMD leave open: where the
+// blocks are many, three workgroups of four wavefronts share a compute unit (causal, one workgroup of eight / so: 2500 x 64 heads 123 -> 89 us,
+// 4096 x 48 200 -> 153; with one fragment per wavefront 107 and 189).
+template <int D, int OWNERS, int WAVES>
 struct AtWide {
-    static constexpr int kStreams = 8 / OWNERS;
+    static constexpr int kStreams = WAVES / OWNERS;
     static constexpr int kEach = 2;                             // streamed fragments per wavefront and trip
     static constexpr int kFrags = kEach * kStreams;
     static constexpr int kRows = 32 * kFrags;
     static constexpr int kFragBytes = 32 * D * 2;
     static constexpr int kBufBytes = kRows * D * 2;
-    static constexpr int kBufs = (3 * kBufBytes <= 128 * 1024) ? 3 : 2;     // a trip's rows are requested kBufs - 1 trips ahead
+    static constexpr int kBufs = (3 * kBufBytes <= WAVES * 16 * 1024) ? 3 : 2;     // a trip's rows are requested kBufs - 1 trips ahead
     static constexpr int kUnitRows = 1024 / (D * 2);            // rows that one copy of a wavefront fills
-    static constexpr int kUnits = kRows / kUnitRows / 8;        // copies per wavefront and trip
+    static constexpr int kUnits = kRows / kUnitRows / WAVES;        // copies per wavefront and trip
     const char* base;           // the head's first row
     uint32_t stride;            // bytes; a trip's 256 rows at most stay below 2^32 (65535 heads)
     uint32_t row, chunk;        // this lane's row of the wavefront's first unit and its bytes' place in the row
@@ -242,25 +243,25 @@ struct AtWide {
         base = (const char*)head;
         stride = (uint32_t)n_heads * (D * 2);
         row = wave * kUnitRows + lane / CH;
-        chunk = ((lane ^ row) & (CH - 1)) * 16;                 // (units are 32 rows or more apart: the same in each)
+        chunk = ((lane ^ row) & (CH - 1)) * 16;                 // (units are 16 rows or more apart: the same in each)
         lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)s_buf + wave * 1024;
     }
     // rows row0 .. row0 + ROWS - 1 to LDS from buffer `buf` on; rows past the end re-read the last token
     template <int ROWS = kRows>
     __device__ __forceinline__ void copy(int row0, int T, int buf) const
     {
-        constexpr int units = ROWS / kUnitRows / 8;
+        constexpr int units = ROWS / kUnitRows / WAVES;
         const char* from = base + (long)row0 * stride;
         const uint32_t to = lds + buf * kBufBytes;
         const uint32_t left = T - 1 - row0;                     // (row0 is a token)
         if (left >= ROWS - 1) {                                 // the same in every lane
             const uint32_t off = row * stride + chunk;
 #pragma unroll
-            for (int i = 0; i < units; i++) lds_copy16(from + (long)(i * 8 * kUnitRows) * stride, off, to + i * 8192);
+            for (int i = 0; i < units; i++) lds_copy16(from + (long)(i * WAVES * kUnitRows) * stride, off, to + i * WAVES * 1024);
         } else {
 #pragma unroll
             for (int i = 0; i < units; i++)
-                lds_copy16(from, min(row + i * 8 * kUnitRows, left) * stride + chunk, to + i * 8192);
+                lds_copy16(from, min(row + i * WAVES * kUnitRows, left) * stride + chunk, to + i * WAVES * 1024);
         }
     }
 };
@@ -298,18 +299,19 @@ __device__ __forceinline__ void block_and_head(int nblk, int n_heads, int& blk, 
 // compiler puts each LDS read right in front of its product and each exponential right in front of its use.
 // KEYS_STAGED: the staged rows are the keys.
 // 16-byte pieces requested from LDS ahead of their products (4096 x 32, unmasked, 2 / 3 / 4: d = 128 280 / 278 / 273 us, d = 64 203 / 204 / 207)
-template <int D>
-constexpr int kAtAhead = (D == 128) ? 4 : 3;
+// (with four wavefronts a workgroup, three of which are to be resident: two)
+template <int D, int WAVES>
+constexpr int kAtAhead = (D == 128) ? 4 : (WAVES == 8) ? 3 : 2;
 
-// in: the first kAtAhead pieces, requested before; left with those of the fragment behind this one if MORE.
-template <int D, bool KEYS_STAGED, bool MORE, typename Work>
-__device__ __forceinline__ void staged_tiles(const char* frag, int ln, int kb, const AtFrag<D> (&own)[2], uint4 (&in)[kAtAhead<D>],
+// in: the first AHEAD pieces, requested before; left with those of the fragment behind this one if MORE.
+template <int D, bool KEYS_STAGED, bool MORE, int AHEAD, typename Work>
+__device__ __forceinline__ void staged_tiles(const char* frag, int ln, int kb, const AtFrag<D> (&own)[2], uint4 (&in)[AHEAD],
                                              float16_t (&acc)[2], Work work)
 {
     constexpr int N = D / 16, kEach = 32 / N;
-    uint4 piece[N + kAtAhead<D>];
+    uint4 piece[N + AHEAD];
 #pragma unroll
-    for (int c = 0; c < kAtAhead<D>; c++) piece[c] = in[c];
+    for (int c = 0; c < AHEAD; c++) piece[c] = in[c];
 #pragma unroll
     for (int o = 0; o < 2; o++)
 #pragma unroll
@@ -317,8 +319,8 @@ __device__ __forceinline__ void staged_tiles(const char* frag, int ln, int kb, c
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < N; c++) {
-        if (c + kAtAhead<D> < N) piece[c + kAtAhead<D>] = staged_piece<D>(frag, ln, kb, c + kAtAhead<D>);
-        else if (MORE) piece[c + kAtAhead<D>] = staged_piece<D>(frag + 32 * D * 2, ln, kb, c + kAtAhead<D> - N);
+        if (c + AHEAD < N) piece[c + AHEAD] = staged_piece<D>(frag, ln, kb, c + AHEAD);
+        else if (MORE) piece[c + AHEAD] = staged_piece<D>(frag + 32 * D * 2, ln, kb, c + AHEAD - N);
         const bf16x8_t staged = __builtin_bit_cast(bf16x8_t, piece[c]);
 #pragma unroll
         for (int o = 0; o < 2; o++) {
@@ -332,16 +334,16 @@ __device__ __forceinline__ void staged_tiles(const char* frag, int ln, int kb, c
     }
     if (MORE)
 #pragma unroll
-        for (int c = 0; c < kAtAhead<D>; c++) in[c] = piece[N + c];
+        for (int c = 0; c < AHEAD; c++) in[c] = piece[N + c];
 }
 
 // The wavefront's two fragments of the block's rows, through the buffers that hold no stage yet (a lane's own loads of them would
 // touch 32 rows for 32 bytes each); start() starts the first stage's copies, which arrive with them.
-template <int D, int OWNERS, typename Start>
-__device__ __forceinline__ void own_fragments(const AtWide<D, OWNERS>& st, int blk, int owner, const char* from, int ln, int kb, int T,
+template <int D, int OWNERS, int WAVES, typename Start>
+__device__ __forceinline__ void own_fragments(const AtWide<D, OWNERS, WAVES>& st, int blk, int owner, const char* from, int ln, int kb, int T,
                                               AtFrag<D> (&own)[2], Start start)
 {
-    static_assert(OWNERS * 64 * D * 2 <= (AtWide<D, OWNERS>::kBufs - 1) * AtWide<D, OWNERS>::kBufBytes, "the block's rows fit behind the first stage");
+    static_assert(OWNERS * 64 * D * 2 <= (AtWide<D, OWNERS, WAVES>::kBufs - 1) * AtWide<D, OWNERS, WAVES>::kBufBytes, "the block's rows fit behind the first stage");
     st.template copy<OWNERS * 64>(blk * OWNERS * 64, T, 1);
     start();
     wait_lds_copies<0>();
@@ -359,12 +361,12 @@ __device__ __forceinline__ void own_fragments(const AtWide<D, OWNERS>& st, int b
 // maxima nor rescaling.
 constexpr float kAtRaise = 256.0f;
 
-template <int D, int OWNERS>
-__global__ __launch_bounds__(kAtWideThreads, 2) void attn_rowstats_wide_kernel(
+template <int D, int OWNERS, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_rowstats_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, float2* __restrict__ stats)
 {
-    using Stage = AtWide<D, OWNERS>;
+    using Stage = AtWide<D, OWNERS, WAVES>;
     __shared__ __attribute__((aligned(16))) char s_buf[Stage::kBufs][Stage::kBufBytes];
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, kb = lane >> 5;
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_rowstats_wide_kernel(
     const int plain_end = min(causal ? qf : nfrag, T >> 5);
     const Stage st(kh, n_heads / group, s_buf[0], wave, lane);
     AtFrag<D> fq[2];
-    own_fragments<D, OWNERS>(Stage(qh, n_heads, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fq, [&] { st.copy(0, T, 0); });
+    own_fragments<D, OWNERS, WAVES>(Stage(qh, n_heads, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fq, [&] { st.copy(0, T, 0); });
     if (Stage::kBufs == 3 && Stage::kFrags <= kf_last) st.copy(Stage::kRows, T, 1);
     float m[2] = {kMasked, kMasked}, l[2] = {0.0f, 0.0f};
     float sum[4], last[8];                                      // sum[2 o], sum[2 o + 1]: query fragment o
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_rowstats_wide_kernel(
 #pragma unroll
         for (int i = 0; i < 16; i++) acc1[o][i] = -INFINITY;    // nothing before the first
     int kp = -1;
-    uint4 in[kAtAhead<D>];
+    uint4 in[kAtAhead<D, WAVES>];
     for (int base = 0, buf = 0; base <= kf_last; base += Stage::kFrags, buf = (buf == Stage::kBufs - 1) ? 0 : buf + 1) {
         constexpr int ahead = (Stage::kBufs - 1) * Stage::kFrags;
         const bool more = base + ahead <= kf_last;              // the same in every thread
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_rowstats_wide_kernel(
         const char* frag = s_buf[buf] + Stage::kEach * stream * Stage::kFragBytes;
         if (kf <= mine_last) {                                  // the same in every lane of the wavefront
 #pragma unroll
-            for (int c = 0; c < kAtAhead<D>; c++) in[c] = staged_piece<D>(frag, ln, kb, c);
+            for (int c = 0; c < kAtAhead<D, WAVES>; c++) in[c] = staged_piece<D>(frag, ln, kb, c);
         }
 #pragma unroll
         for (int f = 0; f < Stage::kEach; f++) {
@@ -507,12 +509,12 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_rowstats_wide_kernel(
 }
 
 // Pass 2, long sequences: a wavefront owns the keys of two fragments; queries stream through LDS.
-template <int D, int OWNERS>
-__global__ __launch_bounds__(kAtWideThreads, 2) void attn_colsum_wide_kernel(
+template <int D, int OWNERS, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_colsum_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, const float2* __restrict__ stats, float* __restrict__ partial)
 {
-    using Stage = AtWide<D, OWNERS>;
+    using Stage = AtWide<D, OWNERS, WAVES>;
     __shared__ __attribute__((aligned(16))) char s_buf[Stage::kBufs][Stage::kBufBytes];
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int ln = lane & 31, kb = lane >> 5;
@@ -532,9 +534,9 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_colsum_wide_kernel(
 #pragma unroll
         for (int s = 0; s < Stage::kEach; s++) next[s] = sh[min((qf + Stage::kEach * stream + s) * 32 + ln, T - 1)];
     };
-    request(first);
+    if (WAVES == 8) request(first);
     AtFrag<D> fk[2];
-    own_fragments<D, OWNERS>(Stage(kh, n_heads / group, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fk,
+    own_fragments<D, OWNERS, WAVES>(Stage(kh, n_heads / group, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fk,
                              [&] { st.copy(first * 32, T, 0); });
     if (Stage::kBufs == 3 && first + Stage::kFrags < nfrag) st.copy((first + Stage::kFrags) * 32, T, 1);
     float col[2][16];
@@ -588,14 +590,15 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_colsum_wide_kernel(
 #pragma unroll
         for (int i = 0; i < 16; i++) acc1[o][i] = -INFINITY;    // nothing before the first
     int qp = -1;
-    uint4 in[kAtAhead<D>];
+    uint4 in[kAtAhead<D, WAVES>];
     float2 ml = make_float2(0.0f, 0.0f);                        // what goes with the fragment before
     for (int base = first, buf = 0; base < nfrag; base += Stage::kFrags, buf = (buf == Stage::kBufs - 1) ? 0 : buf + 1) {
         constexpr int ahead = (Stage::kBufs - 1) * Stage::kFrags;
         const bool more = base + ahead < nfrag;                 // the same in every thread
+        if (WAVES == 4) request(base);                          // (a trip ahead four registers spill, and two other wavefronts cover the wait)
 #pragma unroll
         for (int s = 0; s < Stage::kEach; s++) now[s] = next[s];
-        request(base + Stage::kFrags);
+        if (WAVES == 8) request(base + Stage::kFrags);
         __builtin_amdgcn_sched_barrier(0);                      // ahead of the copies, which may still be on their way at the trip's end
         if (more) st.copy((base + ahead) * 32, T, (buf == 0) ? Stage::kBufs - 1 : buf - 1);
         const int qf = base + Stage::kEach * stream;
@@ -605,7 +608,7 @@ __global__ __launch_bounds__(kAtWideThreads, 2) void attn_colsum_wide_kernel(
             if (qf + f >= mine_first && qf + f < nfrag) {       // the same in every lane of the wavefront (mine_first is even)
                 if (f == 0) {
 #pragma unroll
-                    for (int c = 0; c < kAtAhead<D>; c++) in[c] = staged_piece<D>(frag + f * Stage::kFragBytes, ln, kb, c);
+                    for (int c = 0; c < kAtAhead<D, WAVES>; c++) in[c] = staged_piece<D>(frag + f * Stage::kFragBytes, ln, kb, c);
                 }
                 float16_t(&acc)[2] = (f & 1) ? acc1 : acc0;
                 float16_t(&before)[2] = (f & 1) ? acc0 : acc1;
@@ -736,15 +739,16 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
     const float s = (scale > 0.0f) ? scale : 1.0f / sqrtf((float)head_dim);
     const float scale_log2 = s * 1.44269504088896340736f;
     const int nfrag = (T + 31) / 32;
-    const int owners = dymoe::attn_owners(nfrag, n_heads, causal, head_dim, ctx->num_cu);
+    const dymoe::AtChoice choice = dymoe::attn_choice(nfrag, n_heads, causal, head_dim, ctx->num_cu);
+    const int owners = choice.owners, waves = choice.waves;
     const bool wide = owners != 0;
     // A dimension of a launch holds fewer than 2^32 threads: beyond that (from 275 GB of queries on) a head per y, as in the
     // narrow pair's launches.
     const int nblk = wide ? (nfrag + 2 * owners - 1) / (2 * owners) : 0;
     const long blocks = (long)nblk * n_heads;
-    const int threads = wide ? dymoe::kAtWideThreads : dymoe::kAtThreads;
+    const int threads = waves * dymoe::kWave;
     const dim3 grid = !wide ? dim3((unsigned)nfrag, (unsigned)n_heads)
-                      : blocks * dymoe::kAtWideThreads < 1L << 32 ? dim3((unsigned)blocks)
+                      : blocks * threads < 1L << 32 ? dim3((unsigned)blocks)
                                                               : dim3((unsigned)nblk, (unsigned)n_heads);
 #define DYMOE_ATTN_PAIR(STATS_, COLSUM_)                                                                               \
     do {                                                                                                               \
@@ -754,17 +758,17 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
         dymoe_launch(ctx, DYMOE_K_ATTN_COLSUM, COLSUM_, grid, dim3(threads), 0, st, qb, kbp, T, n_heads, group,          \
                      scale_log2, causal, (const float2*)stats, partial);                                               \
     } while (0)
-#define DYMOE_ATTN_WIDE(D_, OWNERS_) \
-    DYMOE_ATTN_PAIR((dymoe::attn_rowstats_wide_kernel<D_, OWNERS_>), (dymoe::attn_colsum_wide_kernel<D_, OWNERS_>))
-#define DYMOE_ATTN_LAUNCH(D_)                                                                                          \
-    do {                                                                                                               \
-        if (wide && owners == 4) DYMOE_ATTN_WIDE(D_, 4);                                                               \
-        else if (wide) DYMOE_ATTN_WIDE(D_, 2);                                                                         \
-        else DYMOE_ATTN_PAIR(dymoe::attn_rowstats_kernel<D_>, dymoe::attn_colsum_kernel<D_>);                          \
-    } while (0)
-    if (head_dim == 64) DYMOE_ATTN_LAUNCH(64);
-    else DYMOE_ATTN_LAUNCH(128);
-#undef DYMOE_ATTN_LAUNCH
+#define DYMOE_ATTN_WIDE(D_, OWNERS_, WAVES_) \
+    DYMOE_ATTN_PAIR((dymoe::attn_rowstats_wide_kernel<D_, OWNERS_, WAVES_>), (dymoe::attn_colsum_wide_kernel<D_, OWNERS_, WAVES_>))
+    if (head_dim == 128) {
+        if (owners == 4) DYMOE_ATTN_WIDE(128, 4, 8);
+        else if (owners == 2) DYMOE_ATTN_WIDE(128, 2, 8);
+        else DYMOE_ATTN_PAIR(dymoe::attn_rowstats_kernel<128>, dymoe::attn_colsum_kernel<128>);
+    } else {
+        if (owners == 2 && waves == 4) DYMOE_ATTN_WIDE(64, 2, 4);
+        else if (owners == 2) DYMOE_ATTN_WIDE(64, 2, 8);
+        else DYMOE_ATTN_PAIR(dymoe::attn_rowstats_kernel<64>, dymoe::attn_colsum_kernel<64>);
+    }
 #undef DYMOE_ATTN_WIDE
 #undef DYMOE_ATTN_PAIR
     DYMOE_HIP_LAUNCH_CHECK();

@@ -8,27 +8,34 @@ namespace dymoe {
 constexpr int kAtWaves = 4;         // wavefronts of a workgroup of the narrow pair
 
 // Which pair of kernels, by what each is expected to take.  Narrow: a workgroup per 32-token fragment, its wavefronts sharing the streamed
-// tokens (many workgroups, operands straight from global memory).  Wide: blocks of 128 or 256 tokens with the stream in LDS, four
-// wavefronts sharing a stream or two.  The numbers are those of the whole score in us, fitted to 372 sizes a head size (1 to 64
-// heads of 257 to 8000 tokens, both masks; the wide pairs' errors are 4 % rms, the narrow one's 4 to 5 in the range where it matters), so that
-// the pair taken is 0.2 % (d = 128) and 0.4 % (d = 64) slower than the best of them on average (with lines drawn at fragment counts alone 1.4 % and 1.3,
-// and up to half).
+// tokens (many workgroups, operands straight from global memory).  Wide: blocks of 128 or 256 tokens with the stream in LDS.  The
+// numbers are those of the whole score in us, fitted to 372 sizes a head size (1 to 64 heads of 257 to 8000 tokens, both masks;
+// errors 4 to 5 % rms, the narrow pair's in the range where it matters), so that the pair taken is 0.2 % slower than the best of
+// them on average; with lines drawn at fragment counts alone it was 1.4 % and more, up to half.
+struct AtChoice {
+    int owners;                 // 0: the narrow pair, else tokens per block of the wide pair, in units of 64
+    int waves;                  // wavefronts of a workgroup
+};
 struct AtCost {
+    AtChoice form;
+    int resident;               // blocks at a time on a compute unit
     double start;               // launches, score kernel, ends of both passes
     double block;               // a block's own start and end
-    double fragment;            // a streamed fragment of a block's chain
+    double alone, shared;       // a streamed fragment of a block's chain; of each of several blocks beside each other
     double even;                // causal: what an uneven end adds
 };
 
 // Unmasked, all blocks are alike and go over the chip in rounds; causal blocks come longest first and fill it evenly, unless the
 // longest alone takes longer.
-inline double attn_wide_us(int nfrag, int n_heads, int causal, int num_cu, int owners, const AtCost& c)
+inline double attn_wide_us(int nfrag, int n_heads, int causal, int num_cu, const AtCost& c)
 {
+    const int owners = c.form.owners, streams = c.form.waves / owners;
     const double blocks = (double)((nfrag + 2 * owners - 1) / (2 * owners)) * n_heads;
-    const int streams = 8 / owners;
-    const double chain = (nfrag + streams - 1) / streams * c.fragment;
-    if (!causal) return c.start + std::ceil(blocks / num_cu) * (c.block + chain);
-    return c.start + std::fmax(c.block + chain, c.even + blocks / num_cu * (c.block + 0.5 * chain));
+    const double chain = (nfrag + streams - 1) / streams, places = (double)num_cu * c.resident;
+    if (causal) return c.start + std::fmax(c.block + chain * c.alone, c.even + blocks / num_cu * (c.block / c.resident + 0.5 * chain * c.shared));
+    auto round = [&](double beside) { return beside > 0.0 ? c.block + chain * std::fmax(c.alone, beside * c.shared) : 0.0; };
+    const double whole = std::floor(blocks / places);
+    return c.start + whole * round(c.resident) + round(std::ceil((blocks - whole * places) / num_cu));
 }
 
 // The narrow pair's workgroups are all resident where it is in question (up to five a compute unit): a unit takes the longest one's
@@ -55,24 +62,33 @@ inline double attn_narrow_us(int nfrag, int n_heads, int causal, int num_cu, dou
     return start + std::fmax(chain * alone, most * shared);
 }
 
-// 0: the narrow pair, else tokens per block of the wide pair, in units of 64.  Whole score, us, narrow / 128 / 256 tokens a block:
-//                    d = 128, causal          unmasked                 d = 64, causal           unmasked
-//     512 x  20   26.1 / 19.3 / 28.2   27.2 / 18.2 / 24.5      16.6 / 17.6 / 25.5   16.7 / 16.1 / 22.0
-//    1000 x   8   26.9 / 27.6 / 42.9   27.4 / 26.4 / 39.6      16.3 / 24.0 / 37.5   17.0 / 22.7 / 34.4
-//    1200 x   8   33.5 / 31.4 / 48.3   44.8 / 30.6 / 45.3      19.9 / 26.7 / 42.0   26.7 / 25.6 / 38.8
-//    2048 x   8   57.0 / 43.0 / 70.0   68.7 / 41.9 / 66.9      31.6 / 35.7 / 60.1   38.6 / 34.4 / 56.9
-//    4096 x   1   81.9 / 73.5 / 126    83.5 / 72.4 / 122       39.9 / 58.6 / 106    41.1 / 57.6 / 103
-//    1400 x  48  133.6 / 58.1 / 55.1    203 / 96.1 / 99.9      68.8 / 48.7 / 46.6    106 / 74.2 / 81.5
-inline int attn_owners(int nfrag, int n_heads, int causal, int head_dim, int num_cu)
+// Whole score, us, narrow / blocks of 128 / of 256 tokens (d = 128) or three at a time of 128 on a unit (d = 64):
+//                    d = 128, causal           unmasked              d = 64, causal            unmasked
+//     512 x 20   26.1 / 19.3 / 28.2     27.2 / 18.2 / 24.5     16.6 / 17.6 / 17.8     16.7 / 16.1 / 15.9
+//    1000 x  8   26.9 / 27.6 / 42.9     27.4 / 26.4 / 39.6     16.3 / 24.0 / 26.0     17.0 / 22.7 / 24.2
+//    1200 x  8   33.5 / 31.4 / 48.3     44.8 / 30.6 / 45.3     19.9 / 26.7 / 29.7     26.7 / 25.6 / 28.0
+//    2048 x  8   57.0 / 43.0 / 70.0     68.7 / 41.9 / 66.9     31.6 / 35.7 / 40.6     38.6 / 34.4 / 38.9
+//    4096 x  1   81.9 / 73.5 / 126      83.5 / 72.4 / 122      39.9 / 58.6 / 69.8     41.1 / 57.6 / 67.5
+//    1400 x 48   134 / 58.1 / 55.1      203 / 96.1 / 99.9      68.8 / 48.7 / 36.8     106 / 74.2 / 55.7
+//    4096 x 48   809 / 274 / 251        1414 / 475 / 423       426 / 207 / 153        723 / 340 / 278
+// (256 tokens a block at d = 64 are nowhere the fastest.)
+inline AtChoice attn_choice(int nfrag, int n_heads, int causal, int head_dim, int num_cu)
 {
-    if (nfrag < 9) return 0;            // 64 tokens x 192 heads 14.7 / 19.6, 200 x 64 16.4 / 18.4, 300 x 64 27.6 / 21.7 (d = 128)
-    const AtCost two = head_dim == 128 ? AtCost{0.4, 10.5, 2.05, 8.2} : AtCost{3.3, 7.7, 1.51, 7.4};
-    const AtCost four = head_dim == 128 ? AtCost{0.0, 11.7, 1.85, 15.8} : AtCost{3.6, 7.5, 1.5, 15.0};
-    const double narrow = head_dim == 128 ? attn_narrow_us(nfrag, n_heads, causal, num_cu, 8.0, 2.3, 1.9)
-                                          : attn_narrow_us(nfrag, n_heads, causal, num_cu, 8.1, 0.97, 0.92);
-    const double us2 = attn_wide_us(nfrag, n_heads, causal, num_cu, 2, two), us4 = attn_wide_us(nfrag, n_heads, causal, num_cu, 4, four);
-    if (narrow <= std::fmin(us2, us4)) return 0;
-    return us2 < us4 ? 2 : 4;
+    const AtChoice none = {0, kAtWaves};
+    if (nfrag < 9) return none;         // 64 tokens x 192 heads 14.7 / 19.6, 200 x 64 16.4 / 18.4, 300 x 64 27.6 / 21.7 (d = 128)
+    static constexpr AtCost d128[] = {{{2, 8}, 1, 0.4, 10.5, 2.05, 2.05, 8.2}, {{4, 8}, 1, 0.0, 11.7, 1.85, 1.85, 15.8}};
+    static constexpr AtCost d64[] = {{{2, 8}, 1, 3.3, 7.7, 1.51, 1.51, 7.4}, {{2, 4}, 3, 6.1, 3.8, 0.96, 0.72, 9.2}};
+    double best = head_dim == 128 ? attn_narrow_us(nfrag, n_heads, causal, num_cu, 8.0, 2.3, 1.9)
+                                  : attn_narrow_us(nfrag, n_heads, causal, num_cu, 8.1, 0.97, 0.92);
+    AtChoice choice = none;
+    for (const AtCost& c : head_dim == 128 ? d128 : d64) {
+        const double us = attn_wide_us(nfrag, n_heads, causal, num_cu, c);
+        if (us < best) {
+            best = us;
+            choice = c.form;
+        }
+    }
+    return choice;
 }
 
 }  // namespace dymoe

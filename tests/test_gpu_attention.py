@@ -93,7 +93,22 @@ def test_attention_score_staged_blocks(ctx, T, Hh, Hkv, d, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64)])
+# heads of 64 values in so many blocks of 128 tokens that three workgroups of four wavefronts share a compute unit: last blocks of one
+# token, a fragment, a fragment and a bit and all but one token, trips of four fragments that end in every remainder
+THREE_ON_A_UNIT = [(897, 64, 8, 64), (929, 64, 8, 64), (970, 64, 16, 64), (1023, 64, 64, 64), (1089, 49, 7, 64), (2625, 32, 8, 64)]
+
+
+@pytest.mark.parametrize("T,Hh,Hkv,d", THREE_ON_A_UNIT)
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_score_three_workgroups_on_a_unit(ctx, T, Hh, Hkv, d, causal):
+    cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=460 + T)
+    q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, d, boost=1.0)
+    ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+    got = _run(ctx, q, k, causal)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64), (900, 64, 64)])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("rise", [90.0, -90.0])
 def test_attention_score_logits_that_rise_along_the_keys(ctx, T, Hh, d, causal, rise):
@@ -114,7 +129,7 @@ def test_attention_score_logits_that_rise_along_the_keys(ctx, T, Hh, d, causal, 
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64), (1025, 32, 128)])
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64), (1025, 32, 128), (900, 64, 64)])
 def test_attention_score_a_query_that_is_no_number_spoils_the_keys_it_sees(ctx, T, Hh, d):
     q, k = (synth.normal_bf16(277 + T, 9300 + i, (T, Hh, d), 1.0) for i in range(2))
     ref = O.token_score_attention(q, k, Hh, Hh, causal=True)
