@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gptq_steps.hpp"
 
 namespace dymoe {
 
@@ -1082,8 +1083,10 @@ __device__ __forceinline__ const float* gq_p_block(const float* v, long K, const
 // A workgroup takes more than half of a compute unit's LDS and so has it to itself: beside tiles a solver took 3.5 us longer.
 // The launch lasts as long as the solver's chain (11 us and 2.3 to the next launch), or, for the first steps of a large K, as the tiles.
 // K = 4096: 1345 -> 1160 us, 1024: 259 -> 212, 256: 65 -> 54 (with solvers beside three tiles on a compute unit, step k - 1's products in
-// front of the chain, and a lane per row in the piece's factor).  Beyond 5120 columns the tiles are all there is and three of
-// them on a compute unit were as good (8192: 5.55 -> 5.73 ms, 14336: 25.8 -> 26.1).
+// front of the chain, and a lane per row in the piece's factor).  Beyond 5120 columns the tiles are all there is, and one workgroup of them on a
+// unit is as good as three small ones only while its rounds are whole and its operands come from its XCD's L2: with a panel's
+// tiles split for whole rounds (gptq_steps.hpp) and neighbouring blocks on one XCD 4096: 1138 -> 1112 us, 6144 2790 -> 2668 (three
+// small ones 2825), 8192 5619 -> 5474 (5539), 14336 25.65 -> 25.21 ms (25.49).
 // The quotient is the product with the reciprocal and one residual step.  For finite operands that differs from a division
 // in the last place at most; an infinite operand or quotient gives NaN where the division gives infinity, but it has no
 // place in a positive definite matrix: what it is subtracted from, a later pivot, becomes NaN either way.
@@ -1091,43 +1094,11 @@ constexpr int kGqStepThreads = 512;
 constexpr int kGqTileLds = 3 * kGqGroup * kGqGroup;                 // floats: a tile's operands of 64 columns c, one of two buffers
 constexpr int kGqPLd = kGqGroup + 16;                               // row stride of P's blocks in the solver: c and c + 1 on other banks
 
-// Tiles (pairs of block rows x pairs of block columns) of panel q: `near` of the pairs q + 1 and q + 2 and `first` of the
-// others in the first launch, `later` in the second.  single: half tiles that the second launch brings forward by one step.
-// A launch's tiles are taken by halves (a block row each).
-struct GqWide {
-    long q, pairs, near, first, later, single;
-};
-static inline GqWide gq_wide(long nb, long k)
-{
-    GqWide w;
-    w.q = k / 2 - 1;
-    w.pairs = (nb + 1) / 2;
-    w.near = w.first = w.later = w.single = 0;
-    if (k + 1 >= nb) return w;                                      // the last step leaves nothing behind
-    if (w.q >= 0) {
-        w.near = w.pairs + (w.q + 2 < w.pairs ? w.pairs - 1 : 0);
-        // the others: pairs si >= q + 3, and si - 1 of the si + 1 column pairs each
-        long rest = ((w.pairs - 1) * (w.pairs - 2) - (w.q + 2) * (w.q + 1)) / 2;
-        if (rest < 0) rest = 0;
-        w.first = (w.near + rest) / 2 - w.near;
-        if (w.first < 0) w.first = 0;
-        w.later = rest - w.first;
-    }
-    if (k & 1) w.single = nb - (k + 1) + w.q + 2;                   // block column k + 1 from the diagonal down, block row k + 1
-    return w;
-}
-static inline long gq_wide_blocks(const GqWide& w, long k)
-{
-    if (k & 1) return w.single + 2 * w.later;
-    return w.near ? 2 * (w.near + w.first) - 1 - (w.q + 1) : 0;     // without the halves in block row k
-}
-
 // The tiles' part of a launch: 64 x 128 block rows of tiles dealt out to the workers, of whom those behind the first `early` start when a
 // solver has left them a compute unit (kGqSkip blocks later).  32 x 32 of a block a wavefront; the operands of 64 columns c at a
 // time go straight to LDS, and they and the next block's values are on their way while the products before run.
 // Bound: fp32 matrix instructions, 3.6 us a block at 2.27 GHz; 4.4 to 5.4 measured, and 2.5 to start.  (Through registers, operands read from LDS where
 // they are used: 6.2.)
-constexpr int kGqSkip = 3;
 __device__ __forceinline__ void gq_step_tiles(float* s_all, float* v, long K, int k, const float* slots, const GqWide& wide, int worker,
                                               int workers, int early, int blocks)
 {
@@ -1517,6 +1488,15 @@ __device__ __forceinline__ void gq_step_solve(float* s_all, float* v, long K, lo
     }
 }
 
+// A workgroup's place in the order of the blocks.  Workgroups are handed to the eight XCDs in turn: neighbouring blocks, which share their
+// rows' operands, go to one XCD's, so that its L2 fetches them once (11008 columns 12.40 -> 12.20 ms, 2048 445 -> 434 us).
+__device__ __forceinline__ int gq_worker(int w, int workers, int early)
+{
+    const int first = w < early ? 0 : early, n = (w < early ? min(early, workers) : workers) - first;
+    const int xcd = (w - first) & 7;
+    return first + xcd * (n >> 3) + min(xcd, n & 7) + ((w - first) >> 3);
+}
+
 __global__ __launch_bounds__(kGqStepThreads, 2) void gptq_step_kernel(float* v, long K, long k, float* slots, float* __restrict__ u,
                                                                      GqWide wide, int early, int blocks)
 {
@@ -1524,7 +1504,7 @@ __global__ __launch_bounds__(kGqStepThreads, 2) void gptq_step_kernel(float* v, 
     static_assert(sizeof(s_all) > 80 * 1024, "one workgroup per compute unit");
     const int nb = (int)(K / kGqGroup);
     if ((int)blockIdx.x < nb) gq_step_solve(s_all, v, K, k, slots, u, blockIdx.x);
-    else gq_step_tiles(s_all, v, K, (int)k, slots, wide, (int)blockIdx.x - nb, (int)gridDim.x - nb, early, blocks);
+    else gq_step_tiles(s_all, v, K, (int)k, slots, wide, gq_worker((int)blockIdx.x - nb, (int)gridDim.x - nb, early), (int)gridDim.x - nb, early, blocks);
 }
 
 }  // namespace dymoe
@@ -1638,14 +1618,10 @@ int dymoe_gptq_factor(dymoe_ctx* ctx, const float* hess, long K, float damp, flo
     DYMOE_HIP_LAUNCH_CHECK();
     const long nb = K / kGqGroup;
     for (long k = 0; k < nb; k++) {
-        const GqWide wide = gq_wide(nb, k);
-        const long blocks = gq_wide_blocks(wide, k);
-        // Workgroups for the tiles: one on each compute unit that the solvers leave; where these would take longer than kGqSkip blocks each,
-        // one behind each solver as well.
-        const long early = ctx->num_cu > nb ? ctx->num_cu - nb : 0;
-        const long workers = blocks <= kGqSkip * early ? (blocks < early ? blocks : early) : ctx->num_cu;
+        const GqWide wide = gq_wide(nb, k, ctx->num_cu);
+        const long blocks = gq_wide_blocks(wide, k), workers = gq_workers(nb, ctx->num_cu, blocks);
         dymoe_launch(ctx, DYMOE_K_GPTQ_FACTOR, gptq_step_kernel, dim3((unsigned)(nb + workers)), dim3(kGqStepThreads), 0, st, v, K, k, slots, u,
-                     wide, (int)early, (int)blocks);
+                     wide, (int)gq_early(nb, ctx->num_cu), (int)blocks);
         DYMOE_HIP_LAUNCH_CHECK();
     }
     return DYMOE_OK;

@@ -1,0 +1,81 @@
+// How the factorisation's tiles (gptq.hip) are divided over its launches and over a launch's workgroups: host code only.
+#pragma once
+#include <initializer_list>
+
+namespace dymoe {
+
+// Tiles (pairs of block rows x pairs of block columns) of panel q: `near` of the pairs q + 1 and q + 2 and `first` of the
+// others in the first launch, `later` in the second.  single: half tiles that the second launch brings forward by one step.
+// A launch's tiles are taken by halves (a block row each).
+struct GqWide {
+    long q, pairs, near, first, later, single;
+};
+// Blocks that a worker takes before those behind the solvers start.
+constexpr int kGqSkip = 3;
+// Workgroups for the tiles: `early` on the compute units that the solvers leave; where these would take longer than kGqSkip blocks each, one
+// behind each solver as well.
+inline long gq_early(long nb, long num_cu) { return num_cu > nb ? num_cu - nb : 0; }
+inline long gq_workers(long nb, long num_cu, long blocks)
+{
+    const long early = gq_early(nb, num_cu);
+    return blocks <= kGqSkip * early ? (blocks < early ? blocks : early) : num_cu;
+}
+// How long a launch takes, in blocks of the worker with the most of them (5 us each): the solver's chain is 2.7 of them, a worker's start half of one.
+inline double gq_launch_length(long nb, long num_cu, long blocks)
+{
+    const long early = gq_early(nb, num_cu);
+    const long rounds = blocks <= kGqSkip * early ? (blocks + early - 1) / (early > 0 ? early : 1)
+                                                  : kGqSkip + (blocks - kGqSkip * early + num_cu - 1) / num_cu;
+    return rounds + 0.5 > 2.7 ? rounds + 0.5 : 2.7;
+}
+// The tiles of panel q's two launches, whose blocks are `fixed` + 2 first and `all` less those: the split for which both together take
+// the fewest rounds, of those the most even one.  (In equal halves each launch's last round is half empty on average: K = 8192 5614 us, so
+// 5474; 4096 1139 and 1112.)
+inline long gq_split(long nb, long num_cu, long fixed, long rest, long all)
+{
+    const long early = gq_early(nb, num_cu), even = (all / 2 - fixed) / 2;
+    auto inside = [&](long first) { return first < 0 ? 0 : first > rest ? rest : first; };
+    auto length = [&](long first) { return gq_launch_length(nb, num_cu, fixed + 2 * first) + gq_launch_length(nb, num_cu, all - fixed - 2 * first); };
+    long best = inside(even);
+    double least = length(best);
+    // launches that end with a whole round: the first with r of them, or the second
+    const long middle = all / 2 <= kGqSkip * early ? all / 2 / (early > 0 ? early : 1) : kGqSkip + (all / 2 - kGqSkip * early) / num_cu;
+    for (long r = middle > 3 ? middle - 3 : 1; r <= middle + 3; r++) {
+        const long full = r <= kGqSkip ? r * early : kGqSkip * early + (r - kGqSkip) * num_cu;
+        for (const long first : {inside((full - fixed) / 2), inside((all - full - fixed + 1) / 2)}) {
+            const double len = length(first);
+            const long off = first > even ? first - even : even - first, best_off = best > even ? best - even : even - best;
+            if (len < least || (len == least && off < best_off)) {
+                least = len;
+                best = first;
+            }
+        }
+    }
+    return best;
+}
+inline GqWide gq_wide(long nb, long k, long num_cu)
+{
+    GqWide w;
+    w.q = k / 2 - 1;
+    w.pairs = (nb + 1) / 2;
+    w.near = w.first = w.later = w.single = 0;
+    if (k + 1 >= nb) return w;                                      // the last step leaves nothing behind
+    if (w.q >= 0) {
+        w.near = w.pairs + (w.q + 2 < w.pairs ? w.pairs - 1 : 0);
+        // the others: pairs si >= q + 3, and si - 1 of the si + 1 column pairs each
+        long rest = ((w.pairs - 1) * (w.pairs - 2) - (w.q + 2) * (w.q + 1)) / 2;
+        if (rest < 0) rest = 0;
+        const long fixed = 2 * w.near - 1 - (w.q + 1), single = nb - (2 * w.q + 4) + w.q + 2;      // (the other launch's if k is even)
+        w.first = gq_split(nb, num_cu, fixed, rest, fixed + 2 * rest + single);
+        w.later = rest - w.first;
+    }
+    if (k & 1) w.single = nb - (k + 1) + w.q + 2;                   // block column k + 1 from the diagonal down, block row k + 1
+    return w;
+}
+inline long gq_wide_blocks(const GqWide& w, long k)
+{
+    if (k & 1) return w.single + 2 * w.later;
+    return w.near ? 2 * (w.near + w.first) - 1 - (w.q + 1) : 0;     // without the halves in block row k
+}
+
+}  // namespace dymoe
