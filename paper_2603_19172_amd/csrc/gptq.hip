@@ -200,7 +200,7 @@ static_assert(2 * kGqStage <= kGqD && kGqPanel * kGqGroup * kGqRows <= kGqX, "wh
 // instructions taking their time from each other.
 template <int BITS, bool FIRST>
 __device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
-                                              long base, int n_groups, const GqErr& before, const GqErr& err, bool corrections, bool last,
+                                              long base, int n_groups, const GqErr& before, const GqErr& err, bool corrections, bool last, bool spread,
                                               uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
 {
 #pragma clang fp contract(off)
@@ -210,7 +210,9 @@ __device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __re
     float* const s_x = s_all + kGqX;
     float* const s_d = s_all + kGqD;
     double* const s_inv = reinterpret_cast<double*>(s_all + kGqInv);
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // spread: the chains (wavefronts 0 and 1 of what follows) on the workgroup's first and third
+    const int tid = spread ? (threadIdx.x & 63) | (threadIdx.x & 64) << 1 | (threadIdx.x & 128) >> 1 : threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane >> 4, cl = lane & 15;
     const long block = blockIdx.x, row0 = block * kGqRows;
     // ---- the values, a group a wavefront, minus the errors of the panel before.  Register i of tile (t, x): row 16 t + 4 rg + i, column 4 cl + x.
@@ -714,14 +716,14 @@ __device__ __forceinline__ void gq_rest_small(float* s_a, const uint16_t* __rest
 // 2525 / 2340, 4096 x 4096 1166 / 944, 8000 x 1024 208 / 165, 2500 x 2048 391 / 325, 200 x 4096 588 / 548, 14336 x 512 90 / 87.
 template <int BITS, bool FIRST, bool SMALL>
 __global__ __launch_bounds__(256, 3) void gptq_panel_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
-                                                            long base, int n_groups, GqErr before, GqErr err, int row_blocks,
+                                                            long base, int n_groups, GqErr before, GqErr err, int row_blocks, int spread,
                                                             uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
 {
     __shared__ __attribute__((aligned(16))) float s_all[kGqPanelLds];
     static_assert(kGqPanelLds >= 2 * 2 * 2 * 16 * kGqGroup, "the other workgroups' operands fit");
     const long next = base + kGqGroup * n_groups;
     if ((int)blockIdx.x < row_blocks)
-        gq_panel_rows<BITS, FIRST>(s_all, w, v, u, N, K, base, n_groups, before, err, base > 0, next >= K, codes, scale, zero);
+        gq_panel_rows<BITS, FIRST>(s_all, w, v, u, N, K, base, n_groups, before, err, base > 0, next >= K, spread, codes, scale, zero);
     else if constexpr (SMALL)
         gq_rest_small<FIRST>(s_all, w, v, u, N, K, base - before.cols, before, next, blockIdx.x - row_blocks);
     else
@@ -1549,9 +1551,14 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
         const bool first = base <= cols, small = 4 * row_pairs * col_pairs <= 3L * ctx->num_cu;
         long rest = 0;
         if (base > 0 && next < K) rest = small ? n_blocks * ((K - next) / kGqGroup) : 8 * ((row_pairs + 7) / 8) * col_pairs;
+        // A workgroup's wavefronts begin one SIMD on from the one's before it on the compute unit: with both chains on neighbouring wavefronts,
+        // two workgroups on a unit have two chains on one SIMD.  us, neighbours / spread: 14336 x 64 8.4 / 7.0, x 256 30.2 / 28.2, x 1024 229 / 226, 18000 x
+        // 1024 297 / 278.  Beside more columns than are resident, or with several rounds of row blocks, they are as good or better together
+        // (12289 x 4096 2148 / 2163, 57344 x 512 243 / 247).
+        const bool spread = row_blocks > ctx->num_cu && row_blocks <= 4L * ctx->num_cu && rest <= 3L * ctx->num_cu;
         auto go = [&](auto kernel) {
             dymoe_launch(ctx, rest ? DYMOE_K_GPTQ_TRAIL : DYMOE_K_GPTQ_GROUP, kernel, dim3((unsigned)(row_blocks + rest)), dim3(256), 0, st, w, v,
-                         u, N, K, base, groups, before, err, (int)row_blocks, codes, sc, zr);
+                         u, N, K, base, groups, before, err, (int)row_blocks, (int)spread, codes, sc, zr);
         };
         auto pick = [&](auto bits) {
             constexpr int BITS = decltype(bits)::value;
