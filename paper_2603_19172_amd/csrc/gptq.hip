@@ -198,7 +198,8 @@ static_assert(2 * kGqStage <= kGqD && kGqPanel * kGqGroup * kGqRows <= kGqX, "wh
 // columns get those 16 errors as matrix products.  14336 rows, us: alone (the last panel) 21 for the values (7 of matrix instructions a
 // workgroup, 448 workgroups) and 6.5 a group; beside the rest 35 and 14, the vector instructions and the fp32 matrix
 // instructions taking their time from each other.
-template <int BITS, bool FIRST>
+// HALVES (no more than two groups): two wavefronts share a group's values, 16 rows each (8000 x 320 42.0 -> 38.6 us, 4096 x 384 46.7 -> 43.2).
+template <int BITS, bool FIRST, bool HALVES>
 __device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
                                               long base, int n_groups, const GqErr& before, const GqErr& err, bool corrections, bool last, bool spread,
                                               uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
@@ -215,16 +216,19 @@ __device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __re
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane >> 4, cl = lane & 15;
     const long block = blockIdx.x, row0 = block * kGqRows;
-    // ---- the values, a group a wavefront, minus the errors of the panel before.  Register i of tile (t, x): row 16 t + 4 rg + i, column 4 cl + x.
+    // ---- the values, a group a wavefront or two, minus the errors of the panel before.
+    // Register i of tile (t, x): row r16 + 16 t + 4 rg + i, column 4 cl + x.
     {
-        f32x4_t acc[2][4];
-        if (wave < n_groups) {
+        constexpr int kTiles = HALVES ? 1 : 2;
+        const int group = HALVES ? wave >> 1 : wave, r16 = HALVES ? 16 * (wave & 1) : 0;
+        f32x4_t acc[kTiles][4];
+        if (group < n_groups) {
 #pragma unroll
-            for (int t = 0; t < 2; t++)
+            for (int t = 0; t < kTiles; t++)
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const long row = min(row0 + 16 * t + 4 * rg + i, N - 1);    // rows past the last one redo it and keep the result to themselves
-                    const long at = row * K + base + kGqGroup * wave + 4 * cl;
+                    const long row = min(row0 + r16 + 16 * t + 4 * rg + i, N - 1);  // rows past the last one redo it and keep the result to themselves
+                    const long at = row * K + base + kGqGroup * group + 4 * cl;
                     float4 val;
                     if constexpr (FIRST) {
                         const uint2 raw = load_global<uint2>(w + at);
@@ -253,16 +257,18 @@ __device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __re
             __syncthreads();
             for (int c0 = 0, buf = 0; c0 < before.cols; c0 += 16, buf ^= 1) {
                 if (c0 + 16 < before.cols) copy(c0 + 16, buf ^ 1);              // (that buffer's last readers passed the barrier before)
-                if (wave < n_groups) {
-                    const float* const sb = s_all + buf * kGqStage + rg * kGqULd + kGqGroup * wave + 4 * cl;
-                    const float* const sa = s_all + buf * kGqStage + 16 * kGqULd + rg * kGqRows + cl;
+                if (group < n_groups) {
+                    const float* const sb = s_all + buf * kGqStage + rg * kGqULd + kGqGroup * group + 4 * cl;
+                    const float* const sa = s_all + buf * kGqStage + 16 * kGqULd + rg * kGqRows + r16 + cl;
 #pragma unroll
                     for (int kk = 0; kk < 4; kk++) {
                         const float4 b4 = *reinterpret_cast<const float4*>(sb + 4 * kk * kGqULd);
-                        const float a[2] = {sa[4 * kk * kGqRows], sa[4 * kk * kGqRows + 16]};
+                        float a[kTiles];
+#pragma unroll
+                        for (int t = 0; t < kTiles; t++) a[t] = sa[4 * kk * kGqRows + 16 * t];
                         const float b[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-                        for (int t = 0; t < 2; t++)
+                        for (int t = 0; t < kTiles; t++)
 #pragma unroll
                             for (int x = 0; x < 4; x++) acc[t][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[x], acc[t][x], 0, 0, 0);
                     }
@@ -271,12 +277,12 @@ __device__ __forceinline__ void gq_panel_rows(float* s_all, const uint16_t* __re
                 __syncthreads();
             }
         }
-        if (wave < n_groups) {
+        if (group < n_groups) {
 #pragma unroll
-            for (int t = 0; t < 2; t++)
+            for (int t = 0; t < kTiles; t++)
 #pragma unroll
                 for (int i = 0; i < 4; i++)
-                    *reinterpret_cast<float4*>(s_all + (16 * t + 4 * rg + i) * kGqHLd + kGqGroup * wave + 4 * cl) =
+                    *reinterpret_cast<float4*>(s_all + (r16 + 16 * t + 4 * rg + i) * kGqHLd + kGqGroup * group + 4 * cl) =
                         make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
         }
     }
@@ -714,7 +720,8 @@ __device__ __forceinline__ void gq_rest_small(float* s_a, const uint16_t* __rest
 // FIRST: the values of both are still those of w (the first two panels).
 // The whole sweep, us, with the panel's rows (64 a workgroup) and the columns behind it in launches of their own / so: 14336 x 4096
 // 2525 / 2340, 4096 x 4096 1166 / 944, 8000 x 1024 208 / 165, 2500 x 2048 391 / 325, 200 x 4096 588 / 548, 14336 x 512 90 / 87.
-template <int BITS, bool FIRST, bool SMALL>
+enum GqBehind { kGqNothing, kGqSmall, kGqLarge };        // columns behind: none and no more than two groups in the panel; 64 x 64, 128 x 128 a workgroup
+template <int BITS, bool FIRST, GqBehind BEHIND>
 __global__ __launch_bounds__(256, 3) void gptq_panel_kernel(const uint16_t* __restrict__ w, float* v, const float* __restrict__ u, long N, long K,
                                                             long base, int n_groups, GqErr before, GqErr err, int row_blocks, int spread,
                                                             uint8_t* __restrict__ codes, uint16_t* __restrict__ scale, uint16_t* __restrict__ zero)
@@ -723,10 +730,10 @@ __global__ __launch_bounds__(256, 3) void gptq_panel_kernel(const uint16_t* __re
     static_assert(kGqPanelLds >= 2 * 2 * 2 * 16 * kGqGroup, "the other workgroups' operands fit");
     const long next = base + kGqGroup * n_groups;
     if ((int)blockIdx.x < row_blocks)
-        gq_panel_rows<BITS, FIRST>(s_all, w, v, u, N, K, base, n_groups, before, err, base > 0, next >= K, spread, codes, scale, zero);
-    else if constexpr (SMALL)
+        gq_panel_rows<BITS, FIRST, BEHIND == kGqNothing>(s_all, w, v, u, N, K, base, n_groups, before, err, base > 0, next >= K, spread, codes, scale, zero);
+    else if constexpr (BEHIND == kGqSmall)
         gq_rest_small<FIRST>(s_all, w, v, u, N, K, base - before.cols, before, next, blockIdx.x - row_blocks);
-    else
+    else if constexpr (BEHIND == kGqLarge)
         gq_rest<FIRST>(s_all, w, v, u, N, K, base - before.cols, before, next, blockIdx.x - row_blocks);
 }
 
@@ -1562,8 +1569,9 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
         };
         auto pick = [&](auto bits) {
             constexpr int BITS = decltype(bits)::value;
-            if (small) first ? go(gptq_panel_kernel<BITS, true, true>) : go(gptq_panel_kernel<BITS, false, true>);
-            else first ? go(gptq_panel_kernel<BITS, true, false>) : go(gptq_panel_kernel<BITS, false, false>);
+            if (next >= K && groups <= 2) first ? go(gptq_panel_kernel<BITS, true, kGqNothing>) : go(gptq_panel_kernel<BITS, false, kGqNothing>);
+            else if (small) first ? go(gptq_panel_kernel<BITS, true, kGqSmall>) : go(gptq_panel_kernel<BITS, false, kGqSmall>);
+            else first ? go(gptq_panel_kernel<BITS, true, kGqLarge>) : go(gptq_panel_kernel<BITS, false, kGqLarge>);
         };
         if (bits == 8) pick(std::integral_constant<int, 8>());
         else if (bits == 4) pick(std::integral_constant<int, 4>());

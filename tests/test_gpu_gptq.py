@@ -310,8 +310,9 @@ def test_gptq_sweep_row_blocks(ctx, N, K, bits):
     assert _same(ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(U).to(DEV), bits), O.gptq_quantize_pack(wb, U, bits))
 
 
-# more row blocks than compute units, whose chains then lie on other wavefronts: one panel and a second, whole and ragged last row blocks
-@pytest.mark.parametrize("N,K,bits", [(8193, 64, 2), (8224, 256, 8), (8256, 448, 4)])
+# more row blocks than compute units, whose chains then lie on other wavefronts: one panel, a last panel of one group, of two (two
+# wavefronts share a group's values) and of three, whole and ragged last row blocks
+@pytest.mark.parametrize("N,K,bits", [(8193, 64, 2), (8224, 256, 8), (8225, 320, 4), (8287, 384, 2), (8256, 448, 4)])
 def test_gptq_sweep_more_row_blocks_than_compute_units(ctx, N, K, bits):
     _, wb, U = _case(1500 + N, N, K)
     assert _same(ctx.gptq_quantize_pack(to_bf16(wb), torch.from_numpy(U).to(DEV), bits), O.gptq_quantize_pack(wb, U, bits))
