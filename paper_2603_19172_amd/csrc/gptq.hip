@@ -1516,37 +1516,13 @@ __global__ __launch_bounds__(kGqStepThreads, 2) void gptq_step_kernel(float* v, 
     else gq_step_tiles(s_all, v, K, (int)k, slots, wide, gq_worker((int)blockIdx.x - nb, (int)gridDim.x - nb, early), (int)gridDim.x - nb, early, blocks);
 }
 
-}  // namespace dymoe
-
-extern "C" {
-
-size_t dymoe_gptq_workspace_bytes(long N, long K)
+// The sweep over up to kGqMostRows rows, a launch a panel; v: their place in the working copy.
+constexpr long kGqMostRows = 1L << 28;
+static int gq_sweep(dymoe_ctx* ctx, const uint16_t* w, const float* u, long N, long K, int bits, uint8_t* codes, uint16_t* sc, uint16_t* zr,
+                    float* v, float* tail, hipStream_t st)
 {
-    if (N <= 0 || K <= 0) return 0;
-    return dymoe::gq_round256((size_t)N * (size_t)K * 4) + dymoe::gq_tail_bytes(N);
-}
-
-int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u, long N, long K, int bits, int group,
-                             uint8_t* codes, void* scale, void* zero, void* workspace, size_t workspace_bytes,
-                             void* stream)
-{
-    using namespace dymoe;
-    DYMOE_REQUIRE(w_bf16 && u && codes && scale && zero && workspace);
-    DYMOE_REQUIRE(N > 0 && K > 0 && (bits == 2 || bits == 4 || bits == 8));
-    DYMOE_REQUIRE(group == kGqGroup && K % kGqGroup == 0);
-    DYMOE_REQUIRE(N * K < ((long)1 << 40));
-    DYMOE_REQUIRE(dymoe_aligned(w_bf16, 16) && dymoe_aligned(u, 16) && dymoe_aligned(codes, 16) &&
-                  dymoe_aligned(scale, 2) && dymoe_aligned(zero, 2) && dymoe_aligned(workspace, 256));
-    if (workspace_bytes < dymoe_gptq_workspace_bytes(N, K)) return DYMOE_ENOSPC;
-    if (!ctx) return DYMOE_ENOCTX;
-    hipStream_t st = (hipStream_t)stream;
     const long row_blocks = gq_row_blocks(N), n_blocks = (N + 2 * kGqRows - 1) / (2 * kGqRows);
-    float* v = reinterpret_cast<float*>(workspace);
-    float* tail = reinterpret_cast<float*>((char*)workspace + gq_round256((size_t)N * (size_t)K * 4));
     const int panel = gq_panel(N), cols = panel * kGqGroup;
-    const uint16_t* w = (const uint16_t*)w_bf16;
-    uint16_t* sc = (uint16_t*)scale;
-    uint16_t* zr = (uint16_t*)zero;
     GqErr before = {};
     for (long base = 0; base < K; base += cols) {
         const long left = (K - base) / kGqGroup;
@@ -1578,6 +1554,42 @@ int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u,
         else pick(std::integral_constant<int, 2>());
         DYMOE_HIP_LAUNCH_CHECK();
         before = err;
+    }
+    return DYMOE_OK;
+}
+
+}  // namespace dymoe
+
+extern "C" {
+
+size_t dymoe_gptq_workspace_bytes(long N, long K)
+{
+    if (N <= 0 || K <= 0) return 0;
+    return dymoe::gq_round256((size_t)N * (size_t)K * 4) + dymoe::gq_tail_bytes(N);
+}
+
+int dymoe_gptq_quantize_pack(dymoe_ctx* ctx, const void* w_bf16, const float* u, long N, long K, int bits, int group,
+                             uint8_t* codes, void* scale, void* zero, void* workspace, size_t workspace_bytes,
+                             void* stream)
+{
+    using namespace dymoe;
+    DYMOE_REQUIRE(w_bf16 && u && codes && scale && zero && workspace);
+    DYMOE_REQUIRE(N > 0 && K > 0 && (bits == 2 || bits == 4 || bits == 8));
+    DYMOE_REQUIRE(group == kGqGroup && K % kGqGroup == 0);
+    DYMOE_REQUIRE(N * K < ((long)1 << 40));
+    DYMOE_REQUIRE(dymoe_aligned(w_bf16, 16) && dymoe_aligned(u, 16) && dymoe_aligned(codes, 16) &&
+                  dymoe_aligned(scale, 2) && dymoe_aligned(zero, 2) && dymoe_aligned(workspace, 256));
+    if (workspace_bytes < dymoe_gptq_workspace_bytes(N, K)) return DYMOE_ENOSPC;
+    if (!ctx) return DYMOE_ENOCTX;
+    float* v = reinterpret_cast<float*>(workspace);
+    float* tail = reinterpret_cast<float*>((char*)workspace + gq_round256((size_t)N * (size_t)K * 4));
+    // A dimension of a launch holds fewer than 2^32 threads, a workgroup of 256 takes 32 rows, and rows are independent: 2^28 at a
+    // time.  (Only the last of them can be ragged: the buffer for its errors is one.)
+    for (long row = 0; row < N; row += kGqMostRows) {
+        const int rc = gq_sweep(ctx, (const uint16_t*)w_bf16 + row * K, u, N - row < kGqMostRows ? N - row : kGqMostRows, K, bits,
+                                codes + row * K * bits / 8, (uint16_t*)scale + row * (K / kGqGroup), (uint16_t*)zero + row * (K / kGqGroup),
+                                v + row * K, tail, (hipStream_t)stream);
+        if (rc != DYMOE_OK) return rc;
     }
     return DYMOE_OK;
 }

@@ -435,3 +435,27 @@ def test_gptq_factor_of_many_tiles(ctx, K):
     err = (u @ Hd @ u.T - eye).abs().max().item()
     print("K=%d: |U Hd U^T - I| = %.2e" % (K, err))
     assert err < 1e3 * 2.0 ** -23
+
+
+def test_gptq_sweep_of_more_rows_than_one_launch_holds(ctx):
+    """A dimension of a launch holds fewer than 2^32 threads, 2^29 rows of a panel: one row block more, ragged, on top of that."""
+    K, bits, rows, N = 64, 2, 1 << 20, (1 << 29) + 65
+    torch.cuda.empty_cache()
+    need = N * K * 2 + N * K * bits // 8 + N * 4 + int(B.lib.dymoe_gptq_workspace_bytes(N, K)) + (8 << 30)
+    if torch.cuda.mem_get_info()[0] < need:
+        pytest.skip("needs %d GB of free device memory" % (need >> 30))
+    g = torch.Generator(device=DEV).manual_seed(29)
+    some = (torch.randn((rows, K), generator=g, device=DEV) * 0.02).bfloat16()
+    u = (torch.eye(K, device=DEV) + 0.1 * torch.randn((K, K), generator=g, device=DEV).triu(1)).contiguous()
+    want = ctx.gptq_quantize_pack(some, u, bits)
+    w = torch.empty((N, K), dtype=torch.bfloat16, device=DEV)
+    for r in range(0, N, rows):
+        w[r:r + rows] = some[:min(rows, N - r)]
+    ws = torch.empty((int(B.lib.dymoe_gptq_workspace_bytes(N, K)),), dtype=torch.uint8, device=DEV)
+    out = tuple(torch.full(s, 0, dtype=t, device=DEV) for s, t in (((N, K * bits // 8), torch.uint8), ((N, 1), torch.float16), ((N, 1), torch.float16)))
+    got = ctx.gptq_quantize_pack(w, u, bits, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    same = all(torch.equal(a[r:r + rows], b[:min(rows, N - r)]) for r in range(0, N, rows) for a, b in zip(got, want))
+    del w, ws, out, got
+    torch.cuda.empty_cache()
+    assert same
