@@ -967,25 +967,25 @@ __device__ __forceinline__ void gq_fmac_bcast(float (&a)[16], float x, float y)
         asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) DYMOE_FMAC_BCAST(a1, j1) DYMOE_FMAC_BCAST(a2, j2)
             DYMOE_FMAC_BCAST(a3, j3) DYMOE_FMAC_BCAST(a4, j4) DYMOE_FMAC_BCAST(a5, j5)
             DYMOE_FMAC_BCAST(a6, j6)
-            : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2]), [a3] "+v"(a[J + 3]), [a4] "+v"(a[J + 4]),
-              [a5] "+v"(a[J + 5]), [a6] "+v"(a[J + 6])
+            : [a0] "+&v"(a[J]), [a1] "+&v"(a[J + 1]), [a2] "+&v"(a[J + 2]), [a3] "+&v"(a[J + 3]), [a4] "+&v"(a[J + 4]),
+              [a5] "+&v"(a[J + 5]), [a6] "+&v"(a[J + 6])
             : [x] "v"(x), [y] "v"(y), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2), [j3] "n"(J + 3), [j4] "n"(J + 4), [j5] "n"(J + 5),
               [j6] "n"(J + 6));
         gq_fmac_bcast<J + 7, N - 7>(a, x, y);
     } else if constexpr (N >= 4) {
         asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) DYMOE_FMAC_BCAST(a1, j1) DYMOE_FMAC_BCAST(a2, j2)
             DYMOE_FMAC_BCAST(a3, j3)
-            : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1]), [a2] "+v"(a[J + 2]), [a3] "+v"(a[J + 3])
+            : [a0] "+&v"(a[J]), [a1] "+&v"(a[J + 1]), [a2] "+&v"(a[J + 2]), [a3] "+&v"(a[J + 3])
             : [x] "v"(x), [y] "v"(y), [j0] "n"(J), [j1] "n"(J + 1), [j2] "n"(J + 2), [j3] "n"(J + 3));
         gq_fmac_bcast<J + 4, N - 4>(a, x, y);
     } else if constexpr (N >= 2) {
         asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) DYMOE_FMAC_BCAST(a1, j1) "s_nop 1"
-            : [a0] "+v"(a[J]), [a1] "+v"(a[J + 1])
+            : [a0] "+&v"(a[J]), [a1] "+&v"(a[J + 1])
             : [x] "v"(x), [y] "v"(y), [j0] "n"(J), [j1] "n"(J + 1));
         gq_fmac_bcast<J + 2, N - 2>(a, x, y);
     } else if constexpr (N >= 1) {
         asm("s_nop 1\n\t" DYMOE_FMAC_BCAST(a0, j0) "s_nop 1"
-            : [a0] "+v"(a[J])
+            : [a0] "+&v"(a[J])
             : [x] "v"(x), [y] "v"(y), [j0] "n"(J));
         gq_fmac_bcast<J + 1, N - 1>(a, x, y);
     }

@@ -25,14 +25,18 @@ VMEM = re.compile(r"^\s*(global_|buffer_|flat_|scratch_)(load|store|atomic)")
 
 
 @functools.lru_cache(maxsize=None)
-def _assembly(name="ffn_gemm.hip"):
+def _assembly(name="ffn_gemm.hip", behind=""):
+    """a source's compiled code, with the text `behind` appended to it"""
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not found")
     with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "kernels.s")
+        src, out = os.path.join(ROOT, "paper_2603_19172_amd", "csrc", name), os.path.join(tmp, "kernels.s")
+        if behind:
+            with open(os.path.join(tmp, "probe.hip"), "w") as f:
+                f.write('#include "%s"\n%s' % (src, behind))
+            src = f.name
         # the flags the library is built with
-        cmd = ["hipcc", *B.COMMON, *B.PER_FILE.get(name, []), "-S", "--cuda-device-only",
-               os.path.join(ROOT, "paper_2603_19172_amd", "csrc", name), "-o", out]
+        cmd = ["hipcc", *B.COMMON, *B.PER_FILE.get(name, []), "-S", "--cuda-device-only", src, "-o", out]
         subprocess.run(cmd, check=True, capture_output=True)
         with open(out) as f:
             return f.read().split("\n")
@@ -144,3 +148,27 @@ def test_a_wait_state_between_m0_and_the_load_that_reads_it(name):
         assert not re.match(r"s_\w+ m0\b", code[i - 1]), "%s directly behind %s" % (code[i], code[i - 1])
     # the assembly block cannot tell the compiler that it writes M0: nothing else may count on it
     assert sum(bool(re.search(r"\bm0\b", l)) for l in code) == len(loads)
+
+
+# the broadcast and the factor are two of the values that are written, and not read again
+PROBE = """
+__global__ void probe(float* p)
+{
+    float a[16];
+    for (int i = 0; i < 16; i++) a[i] = p[64 * i + threadIdx.x];
+    dymoe::gq_fmac_bcast<1, 7>(a, a[2], a[1]);
+    for (int i = 0; i < 16; i++) p[64 * i + threadIdx.x] = a[i];
+}
+"""
+
+
+def test_broadcast_multiply_adds_read_what_they_have_not_written():
+    """Several multiply-adds in one assembly block: the registers of the first ones' results must not be those that the later
+    ones read, also where the compiler could share a register because the values going in are the same."""
+    lines = _assembly("gptq.hip", PROBE)
+    blocks = [re.findall(r"v_fmac_f32_dpp (v\d+), (v\d+), (v\d+)", b[2]) for b in _blocks(lines)]
+    blocks = [b for b in blocks if b]
+    assert len(blocks) > 15
+    for b in blocks:
+        written = {d for d, _, _ in b}
+        assert len(written) == len(b) and not written & {r for _, x, y in b for r in (x, y)}, b
