@@ -172,3 +172,40 @@ def test_broadcast_multiply_adds_read_what_they_have_not_written():
     for b in blocks:
         written = {d for d, _, _ in b}
         assert len(written) == len(b) and not written & {r for _, x, y in b for r in (x, y)}, b
+
+
+def test_counted_waits_cover_the_attention_stages():
+    """The wide attention kernels request a stage of the stream kBufs - 1 trips ahead and wait for "at most N memory operations in
+    flight" at a trip's end.  Operations retire in order, so the stage before has landed if at least N were issued behind it: each trip
+    issues its own stage, in one of two straight pieces of code (whole or ragged), and each of them must hold exactly N copies."""
+    lines = _assembly("attention.hip")
+    starts = [i for i, l in enumerate(lines) if re.match(r"^_ZN5dymoe\d+attn_(rowstats|colsum)_wide_kernel\w+:", l)]
+    assert len(starts) == 8              # two head sizes, two forms each, two passes
+    counted = 0
+    for start in starts:
+        end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
+        body = lines[start:end]
+        head = next(i for i, l in enumerate(body) if "Inner Loop Header" in l)
+        in_asm = {k for b in _blocks(body) for k in range(b[0], b[1] + 1)}
+        assert not any(re.match(r"\s*scratch_", l) for l in body), "spilled registers are loaded among the copies"
+        waits = {int(m.group(1)) for i, l in enumerate(body) if i in in_asm and (m := re.search(r"s_waitcnt vmcnt\((\d+)\)", l))}
+        assert 0 in waits and len(waits) <= 2
+        n = max(waits)
+        pieces, copies = [], 0
+        for i, l in enumerate(body[head:] + [".LBB:"]):
+            if re.match(r"^\.LBB", l) or re.match(r"\s*s_c?branch", l):
+                pieces.append(copies)
+                copies = 0
+            copies += "global_load_lds_dwordx4" in l
+        pieces = [p for p in pieces if p]
+        assert len(pieces) == 2 and len(set(pieces)) == 1, pieces
+        if n:
+            assert pieces[0] == n, "%d copies a trip, %d allowed in flight" % (pieces[0], n)
+            counted += 1
+            # behind the counted wait the barrier that publishes the stage, with no copy in between
+            k = next(i for i in range(head, len(body)) if i in in_asm and "s_waitcnt vmcnt(%d)" % n in body[i])
+            label = re.search(r"s_branch (\.LBB\d+_\d+)", "\n".join(body[k:k + 6]))
+            at = next(i for i, l in enumerate(body) if l.startswith(label.group(1) + ":")) if label else k
+            behind = "\n".join(body[at:at + 60])
+            assert "s_barrier" in behind and "global_load_lds" not in behind[:behind.index("s_barrier")]
+    assert counted == 6
