@@ -319,7 +319,7 @@ int dymoe_quantize_pack(dymoe_ctx* ctx, const void* w, long N, long K, int bits,
  * K) bytes of device memory, 256-byte aligned (an fp32 copy of the matrix and, N
  * not a multiple of 64, up to 64 KiB); its contents are garbage afterwards.  Other arguments,
  * limits and errors as dymoe_quantize_pack; DYMOE_ENOSPC if the workspace is
- * too small.  Enqueues about K/128 launches on `stream`; never synchronises.
+ * too small.  Enqueues a launch per 256 columns on `stream` (128 below 64 rows); never synchronises.
  */
 /*
  * The two steps before it (GPTQ as published; Sec. 5 of the paper only names it).
@@ -644,7 +644,9 @@ size_t dymoe_cache_bytes_resident(const dymoe_cache* cache);
  * dymoe_timing_read: waits for the recorded launches of `kernel`, drops their records and returns
  * their summed duration in milliseconds and their count (host pointers).
  * Do not enable timing while the stream is being captured into a graph.
- * dymoe_kernel_name: the kernel's name as a profiler shows it, NULL if unknown.
+ * dymoe_kernel_name: the kernel's name as a profiler shows it, NULL if unknown.  Where sizes choose between kernels
+ * for a step it is one of theirs (attn_rowstats_kernel, for attn_rowstats_wide_kernel as well); gptq_group and
+ * gptq_trail are launches of one kernel, a panel alone and a panel with the columns behind it.
  */
 int dymoe_timing_enable(dymoe_ctx* ctx, unsigned kernel_mask);
 int dymoe_timing_read(dymoe_ctx* ctx, int kernel, double* total_ms, int* launches);

@@ -214,7 +214,7 @@ const char* dymoe_kernel_name(int kernel)
     case DYMOE_K_DECODE_FRONT: return "decode_front_kernel";
     case DYMOE_K_ATTN_STATS: return "attn_rowstats_kernel";
     case DYMOE_K_ATTN_COLSUM: return "attn_colsum_kernel";
-    case DYMOE_K_GPTQ_GROUP: return "gptq_panel_kernel (nothing behind)";
+    case DYMOE_K_GPTQ_GROUP:
     case DYMOE_K_GPTQ_TRAIL: return "gptq_panel_kernel";
     case DYMOE_K_GPTQ_HESSIAN: return "gptq_hessian_kernel";
     case DYMOE_K_GPTQ_FACTOR: return "gptq_step_kernel";

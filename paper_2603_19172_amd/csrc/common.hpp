@@ -223,13 +223,6 @@ __device__ __forceinline__ float dpp_get(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, true));
 }
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_get_or_self(float v)
-{
-    // lanes whose row is masked out, or whose source lane does not exist, read their own value
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
-}
-
 // Every lane's sum with the lane 32 away, then 16, 8, 4, 2, 1: all in the vector unit.  From 8 on the values repeat with twice the
 // distance, so that a rotation of the row brings what an exchange would.  (As shuffles each step is a trip through the LDS
 // crossbar, and the next waits for it: with the residual requested ahead of the router rows, 3.9 -> 3.3 us from a decode layer's

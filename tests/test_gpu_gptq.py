@@ -291,8 +291,8 @@ def test_gptq_sweep_edge_rows(ctx):
     assert np.allclose(h.cpu().numpy(), O.gptq_hessian(xb), rtol=1e-6, atol=0)
 
 
-# a panel is four groups of 64 columns, a row block 64 rows, a trail workgroup two row blocks by two groups: rows below,
-# at and beyond each edge (below 64 rows panels are two groups wide), columns that end inside a panel and inside a pair
+# a panel is four groups of 64 columns, a row block 32 rows, a workgroup of the columns behind takes 64 rows by 64 columns or 128 by 128: rows
+# below, at and beyond each edge (below 64 rows panels are two groups wide), columns that end inside a panel and inside a pair of groups
 @pytest.mark.parametrize("N,K,bits", [(63, 320, 4), (64, 512, 2), (65, 576, 8), (127, 256, 4), (129, 832, 2), (200, 704, 4)])
 def test_gptq_sweep_panel_edges(ctx, N, K, bits):
     _, wb, U = _case(800 + N, N, K)
