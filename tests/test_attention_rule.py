@@ -67,3 +67,8 @@ def test_any_chip_and_any_size_has_an_answer(owners, num_cu):
 def test_the_gpu_tests_take_the_forms_they_name(owners):
     for T, heads, _, d in G.THREE_ON_A_UNIT:
         assert owners(d, 1, heads, T) == owners(d, 0, heads, T) == (2, 4)
+    for T, heads, _, causal in G.BLOCKS_OF_256:
+        assert owners(128, causal, heads, T) == (4, 8)
+    for d, causal, heads, _, T, form, behind in G.AROUND_THE_LINES:
+        assert (owners(d, causal, heads, T), owners(d, causal, heads, T + 1)) == (form, behind)
+    assert (owners(128, 1, 64, 900), owners(64, 1, 64, 900)) == ((4, 8), (2, 4))

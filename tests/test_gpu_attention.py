@@ -35,9 +35,8 @@ def _run(ctx, q, k, causal, scale=0.0):
 
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(16, 2, 2, 64), (77, 4, 2, 128), (1, 2, 1, 64), (33, 3, 3, 64),
                                         (160, 8, 2, 128), (512, 32, 8, 128),
-                                        # many tokens, few heads (operands straight from memory up to 320 fragments
-                                        # over all heads of 128 values, 640 of 64): ragged ends, a head count the XCD mapping does not
-                                        # divide, both head sizes
+                                        # many tokens, few heads (operands straight from memory, but for the last and for 2048
+                                        # unmasked): ragged ends, a head count the XCD mapping does not divide, both head sizes
                                         (993, 8, 2, 128), (1100, 3, 3, 64), (1057, 5, 1, 128), (2048, 8, 8, 64),
                                         (4100, 2, 1, 128)])
 @pytest.mark.parametrize("causal", [True, False])
@@ -53,8 +52,7 @@ def test_attention_score_matches_the_oracle(ctx, T, Hh, Hkv, d, causal):
     assert abs(got.sum() - 1.0) < 1e-5                      # every query hands out one unit of attention
 
 
-# the LDS-staged kernels at 512 fragments over all heads and more: stages of the stream that end whole, half and ragged, head counts that
-# the XCD mapping divides and does not
+# the LDS-staged kernels: stages of the stream that end whole, half and ragged, head counts that the XCD mapping divides and does not
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(1024, 16, 4, 128), (1025, 16, 4, 128), (1057, 17, 1, 64), (1088, 24, 6, 64),
                                         (1120, 20, 5, 128), (2111, 8, 2, 128), (1100, 32, 8, 128), (1500, 32, 8, 128),
                                         (1500, 32, 8, 64), (4200, 8, 2, 64)])
@@ -67,10 +65,28 @@ def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-# heads of 64 values around 768 fragments
+# on both sides of where the rule changes (attention_rule.hpp): the last size of one form and, a fragment of one token more, the first of the
+# next; forms as tokens per block in units of 64 (0: operands straight from memory) and wavefronts
+AROUND_THE_LINES = [(128, True, 5, 1, 1408, (0, 4), (2, 8)), (128, True, 20, 5, 416, (0, 4), (2, 8)), (128, False, 8, 2, 1024, (0, 4), (2, 8)),
+                    (128, True, 32, 8, 288, (0, 4), (2, 8)), (64, True, 20, 5, 832, (0, 4), (2, 8)), (64, False, 8, 8, 1024, (0, 4), (2, 8)),
+                    (64, True, 8, 2, 2432, (0, 4), (2, 8)), (64, False, 5, 5, 1632, (0, 4), (2, 8)), (128, True, 32, 8, 2432, (2, 8), (4, 8)),
+                    (128, False, 32, 8, 1024, (2, 8), (4, 8)), (64, False, 20, 5, 1536, (2, 8), (2, 4)), (64, True, 33, 11, 896, (2, 8), (2, 4))]
+
+
+@pytest.mark.parametrize("d,causal,Hh,Hkv,T,form,form_behind", AROUND_THE_LINES)
+def test_attention_score_around_the_lines(ctx, d, causal, Hh, Hkv, T, form, form_behind):
+    for tokens in (T, T + 1):
+        cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=tokens, k_hh=max(1, T // 20), config_id=560 + tokens)
+        q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, d, boost=1.0)
+        ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+        got = _run(ctx, q, k, causal)
+        assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+# heads of 64 values in blocks of 128 tokens by eight wavefronts
 @pytest.mark.parametrize("T,Hh,Hkv", [(1024, 24, 8), (1025, 24, 8), (6113, 4, 4), (2975, 8, 2)])
 @pytest.mark.parametrize("causal", [True, False])
-def test_attention_score_small_heads_around_the_line(ctx, T, Hh, Hkv, causal):
+def test_attention_score_small_heads(ctx, T, Hh, Hkv, causal):
     cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=260 + T)
     q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, 64, boost=1.0)
     ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
@@ -78,9 +94,8 @@ def test_attention_score_small_heads_around_the_line(ctx, T, Hh, Hkv, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-# the staged kernels' blocks of 128 and of 256 tokens (the rule takes the larger where they fill the chip evenly), just past the lines
-# where they begin; last blocks of one token, one fragment and a fragment and a bit; trips of the stream that end whole and in
-# every remainder; wavefronts whose tokens lie past the end
+# the staged kernels' blocks of 128 tokens; last blocks of one token, one fragment and a fragment and a bit; trips of the stream that end
+# whole and in every remainder; wavefronts whose tokens lie past the end
 @pytest.mark.parametrize("T,Hh,Hkv,d", [(321, 30, 5, 128), (353, 32, 8, 128), (385, 32, 8, 128), (449, 24, 24, 128), (513, 20, 5, 128),
                                         (1537, 5, 5, 128), (1665, 5, 1, 128), (2048, 32, 8, 128), (1900, 34, 17, 128), (2561, 24, 4, 128),
                                         (673, 32, 8, 64), (705, 30, 10, 64), (1025, 21, 3, 64), (3073, 5, 5, 64), (2049, 32, 4, 64)])
@@ -88,6 +103,21 @@ def test_attention_score_small_heads_around_the_line(ctx, T, Hh, Hkv, causal):
 def test_attention_score_staged_blocks(ctx, T, Hh, Hkv, d, causal):
     cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=360 + T)
     q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, d, boost=1.0)
+    ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+    got = _run(ctx, q, k, causal)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+# blocks of 256 tokens, under the mask and without it: last blocks of one token, one fragment, a fragment and a bit, all but one token, and
+# wavefronts whose tokens lie past the end; the stream of two sharing wavefronts ends in every remainder
+BLOCKS_OF_256 = [(1025, 64, 8, True), (1056, 64, 16, True), (1070, 64, 64, True), (1279, 64, 8, True), (2625, 32, 8, True), (900, 64, 8, True),
+                 (2600, 33, 11, True), (1025, 64, 8, False), (1056, 64, 8, False), (929, 64, 16, False), (1313, 32, 8, False), (900, 33, 3, False)]
+
+
+@pytest.mark.parametrize("T,Hh,Hkv,causal", BLOCKS_OF_256)
+def test_attention_score_blocks_of_256(ctx, T, Hh, Hkv, causal):
+    cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=660 + T)
+    q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, 128, boost=1.0)
     ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
     got = _run(ctx, q, k, causal)
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
@@ -108,7 +138,7 @@ def test_attention_score_three_workgroups_on_a_unit(ctx, T, Hh, Hkv, d, causal):
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64), (900, 64, 64)])
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 64, 128), (900, 24, 64), (900, 64, 64)])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("rise", [90.0, -90.0])
 def test_attention_score_logits_that_rise_along_the_keys(ctx, T, Hh, d, causal, rise):
@@ -129,7 +159,7 @@ def test_attention_score_logits_that_rise_along_the_keys(ctx, T, Hh, d, causal, 
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 24, 64), (1025, 32, 128), (900, 64, 64)])
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 64, 128), (900, 24, 64), (1025, 32, 128), (900, 64, 64)])
 def test_attention_score_a_query_that_is_no_number_spoils_the_keys_it_sees(ctx, T, Hh, d):
     q, k = (synth.normal_bf16(277 + T, 9300 + i, (T, Hh, d), 1.0) for i in range(2))
     ref = O.token_score_attention(q, k, Hh, Hh, causal=True)
