@@ -1521,7 +1521,7 @@ constexpr long kGqMostRows = 1L << 28;
 static int gq_sweep(dymoe_ctx* ctx, const uint16_t* w, const float* u, long N, long K, int bits, uint8_t* codes, uint16_t* sc, uint16_t* zr,
                     float* v, float* tail, hipStream_t st)
 {
-    const long row_blocks = gq_row_blocks(N), n_blocks = (N + 2 * kGqRows - 1) / (2 * kGqRows);
+    const long row_blocks = gq_row_blocks(N);
     const int panel = gq_panel(N), cols = panel * kGqGroup;
     GqErr before = {};
     for (long base = 0; base < K; base += cols) {
@@ -1529,11 +1529,9 @@ static int gq_sweep(dymoe_ctx* ctx, const uint16_t* w, const float* u, long N, l
         const int groups = (int)(left < panel ? left : panel);
         const long next = base + groups * kGqGroup;
         const GqErr err = {v + base, tail + ((base / cols) & 1) * cols * kGqRows, K, N / kGqRows, cols};
-        // 128 x 128 a workgroup from three quarters of one per compute unit on, else 64 x 64
-        const long row_pairs = (n_blocks + 1) / 2, col_pairs = (K - next + 2 * kGqGroup - 1) / (2 * kGqGroup);
-        const bool first = base <= cols, small = 4 * row_pairs * col_pairs <= 3L * ctx->num_cu;
-        long rest = 0;
-        if (base > 0 && next < K) rest = small ? n_blocks * ((K - next) / kGqGroup) : 8 * ((row_pairs + 7) / 8) * col_pairs;
+        const GqBehindGrid behind = gq_behind_grid(N, K, base, next, ctx->num_cu);
+        const long rest = behind.workgroups;
+        const bool first = base <= cols;
         // A workgroup's wavefronts begin one SIMD on from the one's before it on the compute unit: with both chains on neighbouring wavefronts,
         // two workgroups on a unit have two chains on one SIMD.  us, neighbours / spread: 14336 x 64 8.4 / 7.0, x 256 30.2 / 28.2, x 1024 229 / 226, 18000 x
         // 1024 297 / 278.  Beside more columns than are resident, or with several rounds of row blocks, they are as good or better together
@@ -1546,7 +1544,7 @@ static int gq_sweep(dymoe_ctx* ctx, const uint16_t* w, const float* u, long N, l
         auto pick = [&](auto bits) {
             constexpr int BITS = decltype(bits)::value;
             if (next >= K && groups <= 2) first ? go(gptq_panel_kernel<BITS, true, kGqNothing>) : go(gptq_panel_kernel<BITS, false, kGqNothing>);
-            else if (small) first ? go(gptq_panel_kernel<BITS, true, kGqSmall>) : go(gptq_panel_kernel<BITS, false, kGqSmall>);
+            else if (behind.small) first ? go(gptq_panel_kernel<BITS, true, kGqSmall>) : go(gptq_panel_kernel<BITS, false, kGqSmall>);
             else first ? go(gptq_panel_kernel<BITS, true, kGqLarge>) : go(gptq_panel_kernel<BITS, false, kGqLarge>);
         };
         if (bits == 8) pick(std::integral_constant<int, 8>());

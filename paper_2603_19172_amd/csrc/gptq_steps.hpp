@@ -1,4 +1,4 @@
-// How the factorisation's tiles (gptq.hip) are divided over its launches and over a launch's workgroups: host code only.
+// How the factorisation's tiles and the sweep's columns (gptq.hip) are divided over launches and workgroups: host code only.
 #pragma once
 #include <initializer_list>
 
@@ -76,6 +76,20 @@ inline long gq_wide_blocks(const GqWide& w, long k)
 {
     if (k & 1) return w.single + 2 * w.later;
     return w.near ? 2 * (w.near + w.first) - 1 - (w.q + 1) : 0;     // without the halves in block row k
+}
+
+// The sweep: workgroups for the columns [next, K) behind the panel that begins at `base`, which lose the errors of the panel before (the first
+// panel has none).  128 rows x 128 columns each from three quarters of one per compute unit on, else 64 x 64.
+struct GqBehindGrid {
+    bool small;
+    long workgroups;
+};
+inline GqBehindGrid gq_behind_grid(long N, long K, long base, long next, long num_cu)
+{
+    const long blocks = (N + 63) / 64, row_pairs = (blocks + 1) / 2, col_pairs = (K - next + 127) / 128;
+    const bool small = 4 * row_pairs * col_pairs <= 3 * num_cu;
+    if (base == 0 || next >= K) return {small, 0};
+    return {small, small ? blocks * ((K - next) / 64) : 8 * ((row_pairs + 7) / 8) * col_pairs};
 }
 
 }  // namespace dymoe

@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+import test_gpu_gptq as G
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
@@ -12,8 +14,16 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "gptq_steps.hpp"
 using namespace dymoe;
-int main(int, char** a)
+int main(int n, char** a)
 {
+    if (n == 4) {       // workgroups behind each panel of 256 columns, negative: the small ones
+        const long N = atol(a[1]), K = atol(a[2]);
+        for (long base = 0; base < K; base += 256) {
+            const GqBehindGrid g = gq_behind_grid(N, K, base, base + 256 < K ? base + 256 : K, atol(a[3]));
+            std::printf("%ld ", g.small ? -g.workgroups : g.workgroups);
+        }
+        return 0;
+    }
     const long num_cu = atol(a[1]);
     for (long nb = 1; nb <= 1024; nb += nb < 300 ? 1 : 61) {
         for (long q = 0; 2 * q + 2 < nb; q++) {
@@ -64,3 +74,14 @@ def test_a_panels_launches_take_all_tiles_in_the_fewest_rounds(program, num_cu):
     r = subprocess.run([program, str(num_cu)], capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
     print(r.stdout)
+
+
+def test_the_gpu_tests_reach_both_kernels_of_the_columns_behind(program):
+    for kind, sizes in G.CORRECTIONS.items():
+        for N, K, _ in sizes:
+            r = subprocess.run([program, str(N), str(K), "256"], check=True, capture_output=True, text=True)
+            launches = [int(v) for v in r.stdout.split()]
+            assert {"small": min(launches) < 0, "large": max(launches) > 0, "none": not any(launches)}[kind], (N, K, launches)
+            # the large kernel's values: of the matrix behind the second panel, of the working copy behind later ones
+            if (N, K) == (12353, 960):
+                assert launches[1] > 0 and launches[2] > 0

@@ -34,7 +34,7 @@ def _same(got, want):
             and np.array_equal(bits_of(zero), want[2]))
 
 
-# rows: fewer than a workgroup's 64, a ragged tail, several workgroups; columns: one group (no
+# rows: fewer than a workgroup's 32, a ragged tail, several workgroups; columns: one group (no
 # trailing update), a ragged 128-column trail tile, many steps
 @pytest.mark.parametrize("N,K", [(24, 64), (24, 192), (130, 320), (64, 1024), (257, 2048)])
 @pytest.mark.parametrize("bits", [2, 4, 8])
@@ -388,19 +388,29 @@ def test_gptq_workspaces_are_as_large_as_asked_for(ctx, N, K):
         assert all(torch.equal(a, b) for a, b in zip(got, want)) and (ws[need:] == fill).all()
 
 
-# corrections behind a panel: the two kernels on either side of the rule (192 workgroups of 128 x 128 on 256 compute units), whole and
-# ragged row blocks; rows are independent, so a few of them alone give the same codes
-@pytest.mark.parametrize("N,K", [(12288, 512), (12289, 512), (6144, 832), (6273, 768)])
-def test_gptq_corrections_of_few_and_many_workgroups(ctx, N, K):
+# corrections behind a panel: both kernels on either side of the rule (192 workgroups of 128 x 128 on 256 compute units), their values from the
+# matrix itself and from the working copy; an odd number of 64-row blocks, last ones of 1, 32 and 42 rows, last pairs of column
+# blocks that are one; and panels with nothing behind them
+CORRECTIONS = {"small": [(12288, 704, 4), (6144, 832, 4), (6273, 768, 4)],
+               "large": [(12353, 704, 2), (12458, 704, 8), (12448, 960, 4), (12353, 960, 4)],
+               "none": [(12288, 512, 4), (12289, 512, 4)]}
+
+
+# rows are independent: a few of them alone give the same codes, and the oracle's
+@pytest.mark.parametrize("N,K,bits", [c for v in CORRECTIONS.values() for c in v])
+def test_gptq_corrections_of_few_and_many_workgroups(ctx, N, K, bits):
     g = torch.Generator(device=DEV).manual_seed(N)
     w = (torch.randn((N, K), generator=g, device=DEV) * 0.02).bfloat16()
     x = torch.randn((2 * K, K), generator=g, device=DEV)
     u = ctx.gptq_factor(ctx.gptq_hessian((x + torch.randn((2 * K, 1), generator=g, device=DEV)).bfloat16()))
-    whole = ctx.gptq_quantize_pack(w, u, 4)
+    whole = ctx.gptq_quantize_pack(w, u, bits)
     for rows in (slice(0, 70), slice(N - 131, N)):
-        part = ctx.gptq_quantize_pack(w[rows].contiguous(), u, 4)
+        part = ctx.gptq_quantize_pack(w[rows].contiguous(), u, bits)
         for a, b in zip(whole, part):
             assert torch.equal(a[rows].contiguous().view(torch.uint8), b.view(torch.uint8))
+    for rows in (slice(60, 68), slice(N - 45, N)):
+        wb = w[rows].contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+        assert _same(tuple(a[rows].contiguous() for a in whole), O.gptq_quantize_pack(wb, u.cpu().numpy(), bits))
 
 
 @pytest.mark.gpu
