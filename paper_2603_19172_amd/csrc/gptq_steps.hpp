@@ -12,9 +12,10 @@ struct GqWide {
 };
 // Blocks that a worker takes before those behind the solvers start.
 constexpr int kGqSkip = 3;
-// Workgroups for the tiles: `early` on the compute units that the solvers leave; where these would take longer than kGqSkip blocks each, one
-// behind each solver as well.
-inline long gq_early(long nb, long num_cu) { return num_cu > nb ? num_cu - nb : 0; }
+// Workgroups for the tiles: `early` on the compute units that the solvers leave, or, from as many solvers as units on, that have one solver less
+// than the others (17408 columns, 272 solvers on 256 units: 45.3 ms with every worker the same share, 43.6 so, 43.9 with three small workgroups
+// on a unit); where these would take longer than kGqSkip blocks each, one behind each other solver as well.
+inline long gq_early(long nb, long num_cu) { return num_cu - nb % num_cu; }
 inline long gq_workers(long nb, long num_cu, long blocks)
 {
     const long early = gq_early(nb, num_cu);
