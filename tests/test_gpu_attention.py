@@ -68,8 +68,8 @@ def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
 # on both sides of where the rule changes (attention_rule.hpp): the last size of one form and, a fragment of one token more, the first of the
 # next; forms as tokens per block in units of 64 (0: operands straight from memory) and wavefronts
 AROUND_THE_LINES = [(128, True, 5, 1, 1408, (0, 4), (2, 8)), (128, True, 20, 5, 416, (0, 4), (2, 8)), (128, False, 8, 2, 1024, (0, 4), (2, 8)),
-                    (128, True, 32, 8, 288, (0, 4), (2, 8)), (64, True, 20, 5, 832, (0, 4), (2, 8)), (64, False, 8, 8, 1024, (0, 4), (2, 8)),
-                    (64, True, 8, 2, 2432, (0, 4), (2, 8)), (64, False, 5, 5, 1632, (0, 4), (2, 8)), (128, True, 32, 8, 2432, (2, 8), (4, 8)),
+                    (128, True, 32, 8, 288, (0, 4), (2, 8)), (64, True, 20, 5, 2816, (2, 8), (2, 4)), (64, False, 8, 8, 1024, (0, 4), (2, 8)),
+                    (64, True, 8, 2, 2432, (0, 4), (2, 8)), (64, False, 5, 5, 1632, (0, 4), (2, 8)), (128, True, 32, 8, 2304, (2, 8), (4, 8)),
                     (128, False, 32, 8, 1024, (2, 8), (4, 8)), (64, False, 20, 5, 1536, (2, 8), (2, 4)), (64, True, 33, 11, 896, (2, 8), (2, 4))]
 
 
@@ -111,7 +111,7 @@ def test_attention_score_staged_blocks(ctx, T, Hh, Hkv, d, causal):
 # blocks of 256 tokens, under the mask and without it: last blocks of one token, one fragment, a fragment and a bit, all but one token, and
 # wavefronts whose tokens lie past the end; the stream of two sharing wavefronts ends in every remainder
 BLOCKS_OF_256 = [(1025, 64, 8, True), (1056, 64, 16, True), (1070, 64, 64, True), (1279, 64, 8, True), (2625, 32, 8, True), (900, 64, 8, True),
-                 (2600, 33, 11, True), (1025, 64, 8, False), (1056, 64, 8, False), (929, 64, 16, False), (1313, 32, 8, False), (900, 33, 3, False)]
+                 (2600, 33, 11, True), (1025, 32, 8, False), (1312, 32, 4, False), (929, 64, 16, False), (1313, 32, 8, False), (900, 33, 3, False)]
 
 
 @pytest.mark.parametrize("T,Hh,Hkv,causal", BLOCKS_OF_256)
