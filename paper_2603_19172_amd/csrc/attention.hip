@@ -221,6 +221,9 @@ __global__ __launch_bounds__(kAtThreads) void attn_colsum_kernel(
 // At d = 64 the products are half of that and the vector work is the bound, whose latencies two wavefronts a SIMD leave open: where the
 // blocks are many, three workgroups of four wavefronts share a compute unit (causal, one workgroup of eight / so: 2500 x 64 heads 123 -> 89 us,
 // 4096 x 48 200 -> 153; with one fragment per wavefront 107 and 189).
+// At d = 128 registers and LDS leave room for two such workgroups: no more wavefronts than in one of eight, but one that ends or waits at
+// its barriers no longer idles the unit, and half as long a chain fills the chip more evenly (causal, one of eight / so: 1600 x 44 66.1 ->
+// 53.6 us, unmasked 110 -> 92.2).
 template <int D, int OWNERS, int WAVES>
 struct AtWide {
     static constexpr int kStreams = WAVES / OWNERS;
@@ -362,7 +365,7 @@ __device__ __forceinline__ void own_fragments(const AtWide<D, OWNERS, WAVES>& st
 constexpr float kAtRaise = 256.0f;
 
 template <int D, int OWNERS, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_rowstats_wide_kernel(
+__global__ __launch_bounds__(WAVES * kWave, at_resident(D, WAVES) * WAVES / 4) void attn_rowstats_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, float2* __restrict__ stats)
 {
@@ -510,7 +513,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_rowsta
 
 // Pass 2, long sequences: a wavefront owns the keys of two fragments; queries stream through LDS.
 template <int D, int OWNERS, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_colsum_wide_kernel(
+__global__ __launch_bounds__(WAVES * kWave, at_resident(D, WAVES) * WAVES / 4) void attn_colsum_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int T, int n_heads, int group,
     float scale_log2, int causal, const float2* __restrict__ stats, float* __restrict__ partial)
 {
@@ -534,7 +537,8 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_colsum
 #pragma unroll
         for (int s = 0; s < Stage::kEach; s++) next[s] = sh[min((qf + Stage::kEach * stream + s) * 32 + ln, T - 1)];
     };
-    if (WAVES == 8) request(first);
+    constexpr bool three = at_resident(D, WAVES) * WAVES == 12;  // wavefronts a SIMD: a trip ahead four registers spill, and the two others cover the wait
+    if (!three) request(first);
     AtFrag<D> fk[2];
     own_fragments<D, OWNERS, WAVES>(Stage(kh, n_heads / group, s_buf[0], wave, lane), blk, owner, s_buf[1], ln, kb, T, fk,
                              [&] { st.copy(first * 32, T, 0); });
@@ -595,10 +599,10 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 4 ? 3 : 2) void attn_colsum
     for (int base = first, buf = 0; base < nfrag; base += Stage::kFrags, buf = (buf == Stage::kBufs - 1) ? 0 : buf + 1) {
         constexpr int ahead = (Stage::kBufs - 1) * Stage::kFrags;
         const bool more = base + ahead < nfrag;                 // the same in every thread
-        if (WAVES == 4) request(base);                          // (a trip ahead four registers spill, and two other wavefronts cover the wait)
+        if (three) request(base);
 #pragma unroll
         for (int s = 0; s < Stage::kEach; s++) now[s] = next[s];
-        if (WAVES == 8) request(base + Stage::kFrags);
+        if (!three) request(base + Stage::kFrags);
         __builtin_amdgcn_sched_barrier(0);                      // ahead of the copies, which may still be on their way at the trip's end
         if (more) st.copy((base + ahead) * 32, T, (buf == 0) ? Stage::kBufs - 1 : buf - 1);
         const int qf = base + Stage::kEach * stream;
@@ -761,7 +765,8 @@ int dymoe_token_score_attention(dymoe_ctx* ctx, const void* q, const void* k, in
 #define DYMOE_ATTN_WIDE(D_, OWNERS_, WAVES_) \
     DYMOE_ATTN_PAIR((dymoe::attn_rowstats_wide_kernel<D_, OWNERS_, WAVES_>), (dymoe::attn_colsum_wide_kernel<D_, OWNERS_, WAVES_>))
     if (head_dim == 128) {
-        if (owners == 4) DYMOE_ATTN_WIDE(128, 4, 8);
+        if (owners == 2 && waves == 4) DYMOE_ATTN_WIDE(128, 2, 4);
+        else if (owners == 4) DYMOE_ATTN_WIDE(128, 4, 8);
         else if (owners == 2) DYMOE_ATTN_WIDE(128, 2, 8);
         else DYMOE_ATTN_PAIR(dymoe::attn_rowstats_kernel<128>, dymoe::attn_colsum_kernel<128>);
     } else {

@@ -180,7 +180,7 @@ def test_counted_waits_cover_the_attention_stages():
     issues its own stage, in one of two straight pieces of code (whole or ragged), and each of them must hold exactly N copies."""
     lines = _assembly("attention.hip")
     starts = [i for i, l in enumerate(lines) if re.match(r"^_ZN5dymoe\d+attn_(rowstats|colsum)_wide_kernel\w+:", l)]
-    assert len(starts) == 8              # two head sizes, two forms each, two passes
+    assert len(starts) == 10             # three forms of 128 values a head and two of 64, two passes
     counted = 0
     for start in starts:
         end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))

@@ -67,10 +67,11 @@ def test_attention_score_staged_kernels(ctx, T, Hh, Hkv, d, causal):
 
 # on both sides of where the rule changes (attention_rule.hpp): the last size of one form and, a fragment of one token more, the first of the
 # next; forms as tokens per block in units of 64 (0: operands straight from memory) and wavefronts
-AROUND_THE_LINES = [(128, True, 5, 1, 1408, (0, 4), (2, 8)), (128, True, 20, 5, 416, (0, 4), (2, 8)), (128, False, 8, 2, 1024, (0, 4), (2, 8)),
-                    (128, True, 32, 8, 288, (0, 4), (2, 8)), (64, True, 20, 5, 2816, (2, 8), (2, 4)), (64, False, 8, 8, 1024, (0, 4), (2, 8)),
-                    (64, True, 8, 2, 2432, (0, 4), (2, 8)), (64, False, 5, 5, 1632, (0, 4), (2, 8)), (128, True, 32, 8, 2304, (2, 8), (4, 8)),
-                    (128, False, 32, 8, 1024, (2, 8), (4, 8)), (64, False, 20, 5, 1536, (2, 8), (2, 4)), (64, True, 33, 11, 896, (2, 8), (2, 4))]
+AROUND_THE_LINES = [(128, True, 5, 1, 1536, (0, 4), (2, 8)), (128, True, 20, 5, 416, (0, 4), (2, 8)), (128, False, 8, 2, 1024, (0, 4), (2, 8)),
+                    (128, True, 32, 8, 288, (0, 4), (2, 4)), (128, True, 32, 8, 1536, (2, 8), (2, 4)), (128, False, 32, 8, 1024, (2, 8), (4, 8)),
+                    (128, False, 32, 8, 2048, (4, 8), (2, 4)), (128, True, 32, 8, 3456, (2, 4), (4, 8)), (128, False, 32, 8, 320, (2, 4), (2, 8)),
+                    (64, True, 20, 5, 2944, (2, 8), (2, 4)), (64, False, 8, 8, 1280, (0, 4), (2, 8)), (64, True, 8, 2, 2592, (0, 4), (2, 8)),
+                    (64, False, 5, 5, 1632, (0, 4), (2, 8)), (64, False, 20, 5, 1536, (2, 8), (2, 4)), (64, True, 33, 11, 1408, (2, 8), (2, 4))]
 
 
 @pytest.mark.parametrize("d,causal,Hh,Hkv,T,form,form_behind", AROUND_THE_LINES)
@@ -110,13 +111,29 @@ def test_attention_score_staged_blocks(ctx, T, Hh, Hkv, d, causal):
 
 # blocks of 256 tokens, under the mask and without it: last blocks of one token, one fragment, a fragment and a bit, all but one token, and
 # wavefronts whose tokens lie past the end; the stream of two sharing wavefronts ends in every remainder
-BLOCKS_OF_256 = [(1025, 64, 8, True), (1056, 64, 16, True), (1070, 64, 64, True), (1279, 64, 8, True), (2625, 32, 8, True), (900, 64, 8, True),
-                 (2600, 33, 11, True), (1025, 32, 8, False), (1312, 32, 4, False), (929, 64, 16, False), (1313, 32, 8, False), (900, 33, 3, False)]
+BLOCKS_OF_256 = [(5121, 21, 7, True), (5185, 21, 21, True), (3457, 32, 8, True), (3560, 30, 10, True), (257, 88, 8, False), (290, 88, 11, False),
+                 (400, 68, 4, False), (1025, 32, 8, False), (1312, 32, 4, False), (929, 64, 16, False), (1313, 32, 8, False), (900, 33, 3, False)]
 
 
 @pytest.mark.parametrize("T,Hh,Hkv,causal", BLOCKS_OF_256)
 def test_attention_score_blocks_of_256(ctx, T, Hh, Hkv, causal):
     cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=660 + T)
+    q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, 128, boost=1.0)
+    ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
+    got = _run(ctx, q, k, causal)
+    assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
+
+
+# heads of 128 values in blocks of 128 tokens by four wavefronts, two workgroups of which share a compute unit: last blocks of one token, a
+# fragment and a bit, three fragments, all but one token; trips of four fragments that end in every remainder
+TWO_ON_A_UNIT = [(257, 64, 8, True), (300, 64, 16, True), (900, 64, 8, True), (1025, 64, 8, True), (1056, 64, 16, True), (1070, 64, 64, True),
+                 (1279, 64, 8, True), (1536, 64, 4, True), (2600, 33, 11, True), (2625, 32, 8, True), (257, 64, 64, False), (300, 64, 8, False),
+                 (1089, 64, 64, False), (1120, 64, 8, False), (1409, 64, 4, False), (1535, 64, 8, False), (2049, 32, 8, False)]
+
+
+@pytest.mark.parametrize("T,Hh,Hkv,causal", TWO_ON_A_UNIT)
+def test_attention_score_two_workgroups_on_a_unit(ctx, T, Hh, Hkv, causal):
+    cfg = synth.scaled(synth.CONFIGS["mixtral_prefill"], T=T, k_hh=max(1, T // 20), config_id=760 + T)
     q, k, heavy = synth.attention_inputs(cfg, Hh, Hkv, 128, boost=1.0)
     ref = O.token_score_attention(q, k, Hh, Hkv, causal=causal)
     got = _run(ctx, q, k, causal)
@@ -159,7 +176,7 @@ def test_attention_score_logits_that_rise_along_the_keys(ctx, T, Hh, d, causal, 
     assert np.allclose(got, ref, rtol=RTOL, atol=ATOL) and abs(got.sum() - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 64, 128), (900, 24, 64), (1025, 32, 128), (900, 64, 64)])
+@pytest.mark.parametrize("T,Hh,d", [(900, 24, 128), (900, 64, 128), (900, 24, 64), (1025, 32, 128), (3457, 32, 128), (900, 64, 64)])
 def test_attention_score_a_query_that_is_no_number_spoils_the_keys_it_sees(ctx, T, Hh, d):
     q, k = (synth.normal_bf16(277 + T, 9300 + i, (T, Hh, d), 1.0) for i in range(2))
     ref = O.token_score_attention(q, k, Hh, Hh, causal=True)
